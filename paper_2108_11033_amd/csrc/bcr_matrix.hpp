@@ -53,18 +53,20 @@ struct MmaLayout {
 // Layout for the row-gathering matrix-core SpMM kernel (fp16 / bf16; block heights that divide 16
 // or are multiples of 16).  The rows of the matrix in stored order (stored strip p, local row r ->
 // p * BR + r) are cut into runs of 16, the MFMA tile height: a run is one strip for BR = 16, a
-// quarter of a strip for BR = 64, four strips for BR = 4.  The kept columns of the blocks that
-// reach into a run, in column-block order, are cut into groups of 8 k slots (a block's columns
-// padded to a multiple of 8; a group belongs to one block and carries that block's kept rows
-// inside the run as a 16-bit mask) and groups into steps of 32 k slots -- one v_mfma_f32_16x16x32
+// quarter of a strip for BR = 64, four strips for BR = 4.  The distinct columns that the blocks
+// reaching into a run keep, ascending, are cut into groups of 8 k slots (a group carries the rows
+// of the run that keep any of its columns as a 16-bit mask; a row's weight is zero at the columns
+// its own block does not keep) and groups into steps of 32 k slots -- one v_mfma_f32_16x16x32
 // per 16 columns of X.  Nothing depends on how K is cut: a wave takes any contiguous range of a
-// run's steps.
+// run's steps.  Groups used to belong to one block each; shared columns and no padding per block
+// bring a run of four 4 x 16 strips keeping 4 of 16 columns from 32 k slots per column block to
+// 10.9 (the bound of these kernels is the rows of X fetched per run).
 //   rows   : per step 32 x u32, the row of X behind k slot g * 8 + j at position j * 4 + g
 //            (0xffffffff = padding: the slot multiplies zeros), so that the lane that fetches slots
 //            j, j + 8, j + 16, j + 24 reads its four row numbers with one 16-byte load;
-//   desc   : per step and group the block's row bit mask (u32) and the place of the group's
+//   desc   : per step and group the row bit mask (u32) and the place of the group's
 //            weights in `payload`, in 16-byte units (u32);
-//   payload: per group, for every KEPT row of the block 8 weights (16 bytes).
+//   payload: per group, for every row in its mask 8 weights (16 bytes).
 struct GatherLayout {
     bool present = false;
     int64_t nsteps = 0;
