@@ -802,7 +802,7 @@ static bool skinny_on_matrix_cores(const grim_bcr_matrix *A, const void *X_dev, 
 }
 
 // which kernel family a grim_bcr_spmm_tuned call runs
-enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_WIDE };
+enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_GATHER_ANY, ROUTE_WIDE };
 
 // what the columns the wide-tile kernel leaves over cost on the kernels that take any N
 static double rest_cost(const grim_bcr_matrix *A, int64_t n) {
@@ -839,6 +839,7 @@ static SpmmRoute spmm_route(const grim_bcr_matrix *A, const void *X_dev, int64_t
         const double wide = wide_plan(A, X_dev, N, ldx, Y_dev, ldy, rest_cost, wide_tn, wide_cols);
         if (wide >= 0 && (staged < 0 || wide < staged) && (gather < 0 || wide < gather)) return ROUTE_WIDE;
         if (gather >= 0 && (staged < 0 || gather < staged)) return ROUTE_GATHER;
+        if (gather < 0 && gather_any_applies(A, X_dev)) return ROUTE_GATHER_ANY;
     }
     if (mma) return ROUTE_MMA;
     return A->BR > 64 ? ROUTE_NONE : ROUTE_FMA;
@@ -857,7 +858,8 @@ grim_status grim_bcr_spmm_tuned(const grim_bcr_matrix *A, const void *X_dev, int
             return launch_spmv(nullptr, d, nullptr, 1, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc,
                                A->gemv.vec, A->gemv.krmax, A->gemv.kcmax, X_dev, 0, (int32_t)N, ldx, Y_dev, 0, ldy, stream);
         }
-        case ROUTE_GATHER: return launch_spmm_gather(A, X_dev, N, ldx, Y_dev, ldy, stream);
+        case ROUTE_GATHER:
+        case ROUTE_GATHER_ANY: return launch_spmm_gather(A, X_dev, N, ldx, Y_dev, ldy, stream);
         case ROUTE_WIDE: {
             // whole rounds of fat workgroups, the few columns left over on whatever suits them: in the same launch when
             // that is the row-gathering kernel in the form the combined kernel carries, else in a launch of their own
@@ -907,6 +909,8 @@ const char *grim_bcr_spmm_kernel_name(const grim_bcr_matrix *A, const void *X_de
         case ROUTE_SPMV: return "bcr_spmv";
         case ROUTE_WIDE: return "bcr_spmm_wide";
         case ROUTE_GATHER: return "bcr_spmm_gather";
+        // (rows of X at any alignment: reported as the family that is otherwise the matrix's for such operands)
+        case ROUTE_GATHER_ANY: return A->mma.present ? "bcr_spmm_mma" : "bcr_spmm_fma";
         case ROUTE_MMA: return "bcr_spmm_mma";
         case ROUTE_FMA: return "bcr_spmm_fma";
         case ROUTE_NONE: break;

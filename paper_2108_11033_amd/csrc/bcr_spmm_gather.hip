@@ -13,6 +13,9 @@ bool gather_wave_per_strip(const grim_bcr_matrix *A, int64_t pairs, int64_t pair
 bool gather_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx) {
     return A->gather.present && N >= 4 && N % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 8 == 0;
 }
+bool gather_any_applies(const grim_bcr_matrix *A, const void *X) {
+    return A->gather.present && reinterpret_cast<uintptr_t>(X) % 2 == 0;
+}
 
 // Bytes through one compute unit, the quantity both matrix-core kernels are bound by at these
 // sizes: a workgroup fetches the rows of X its strip keeps (128 bytes each) and the strip's
@@ -38,7 +41,7 @@ bool gather_pair_applies(const grim_bcr_matrix *A, const void *X, const grim_bcr
 // Parameters, grid and kernel form of a launch (see launch_spmm_gather); GRIM_ERR_UNSUPPORTED when the kernel does not apply.
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                          const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form) {
-    if (!gather_applies(A, X, N, ldx)) return GRIM_ERR_UNSUPPORTED;
+    if (!gather_any_applies(A, X)) return GRIM_ERR_UNSUPPORTED;
     if (A2 && !gather_pair_applies(A, X, A2, X2, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     GatherParams p;
     p.sptr = A->gather.d_sptr;
@@ -52,14 +55,13 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     p.nbr = (int32_t)A->gather.nstrips;
     p.K = (int32_t)A->K;
     p.usteps = A->gather.usteps;
-    p.ntiles = (int32_t)((N + 63) / 64);
-    p.yvec = (reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 4 == 0 && N % 4 == 0) ? 4 : 1;
-    p.second = GatherSecond{p.sptr, p.out_row, p.rows, p.desc, p.payload, p.X, p.Y, p.usteps};
-    if (A2) {
+    // fewer than 64 columns: one tile of the narrowest width that holds them
+    const int nt = N > 32 ? 4 : N > 16 ? 2 : 1;
+    p.ntiles = (int32_t)((N + nt * 16 - 1) / (nt * 16));
+    p.second = GatherSecond{p.sptr, p.out_row, p.rows, p.desc, p.payload, p.X, p.Y, p.usteps, p.K};
+    if (A2)
         p.second = GatherSecond{A2->gather.d_sptr, A2->gather.d_out_row, A2->gather.d_rows, A2->gather.d_desc,
-                                A2->gather.d_payload, static_cast<const unsigned short *>(X2), Y2, A2->gather.usteps};
-        if (reinterpret_cast<uintptr_t>(Y2) % 16 != 0) p.yvec = 1;
-    }
+                                A2->gather.d_payload, static_cast<const unsigned short *>(X2), Y2, A2->gather.usteps, (int32_t)A2->K};
     // strips of at most 8 steps (two batches of a wave) with enough (tile, strip) pairs to fill the GPU: wave per pair;
     // long strips and fewer workgroups than compute units: eight waves per strip
     const bool narrow = N < 64;
@@ -77,8 +79,9 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     form->narrow = narrow;
     form->solo = solo;
     form->eight = eight;
-    form->wide = N % 8 == 0 && ldx % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
-                 (!A2 || reinterpret_cast<uintptr_t>(X2) % 16 == 0);
+    form->nt = nt;
+    form->aligned = N % 8 == 0 && ldx % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
+                    (!A2 || reinterpret_cast<uintptr_t>(X2) % 16 == 0);
     form->nwg = nwg;
     *out = p;
     return GRIM_OK;
@@ -90,13 +93,13 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
     GatherForm form;
     const grim_status st = gather_setup(A, X, N, ldx, Y, ldy, A2, X2, Y2, &p, &form);
     if (st != GRIM_OK) return st;
-    const bool narrow = form.narrow, solo = form.solo, eight = form.eight, wide = form.wide;
+    const bool narrow = form.narrow, solo = form.solo, eight = form.eight, aligned = form.aligned;
     const int64_t nwg = form.nwg;
-    const size_t lds = (eight ? kGatherLongWaves : 4) * 8192;
+    const size_t lds = (size_t)(eight ? kGatherLongWaves : 4) * gather_wave_lds(form.nt);
     const dim3 grid((unsigned)nwg, A2 ? 2u : 1u), block(eight ? kGatherLongWaves * 64 : 256);
-#define GRIM_GATHER(BF, WD, NR, SO, EI)                                                                              \
+#define GRIM_GATHER(BF, AL, NR, SO, EI, NT)                                                                              \
     do {                                                                                                             \
-        auto kern = bcr_spmm_gather<BF, WD, NR, SO, EI>;                                                             \
+        auto kern = bcr_spmm_gather<BF, AL, NR, SO, EI, NT>;                                                          \
         static std::atomic<bool> attr_done{false};   /* raising a kernel's LDS limit is needed once per process */  \
         if (lds > 64 * 1024 && !attr_done) {                                                                         \
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -108,13 +111,18 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
         }                                                                                                            \
         hipLaunchKernelGGL(kern, grid, block, lds, stream, p);                                                       \
     } while (0)
-#define GRIM_GATHER_DT(BF)                                                                                         \
-    if (narrow) { if (wide) GRIM_GATHER(BF, true, true, false, false); else GRIM_GATHER(BF, false, true, false, false); }        \
-    else if (solo) { if (wide) GRIM_GATHER(BF, true, false, true, false); else GRIM_GATHER(BF, false, false, true, false); }     \
-    else if (eight) { if (wide) GRIM_GATHER(BF, true, false, false, true); else GRIM_GATHER(BF, false, false, false, true); }    \
-    else { if (wide) GRIM_GATHER(BF, true, false, false, false); else GRIM_GATHER(BF, false, false, false, false); }
+#define GRIM_GATHER_AL(BF, AL)                                                                                       \
+    if (narrow && form.nt == 1) GRIM_GATHER(BF, AL, true, false, false, 1);                                          \
+    else if (narrow && form.nt == 2) GRIM_GATHER(BF, AL, true, false, false, 2);                                     \
+    else if (narrow) GRIM_GATHER(BF, AL, true, false, false, 4);                                                     \
+    else if (solo) GRIM_GATHER(BF, AL, false, true, false, 4);                                                       \
+    else if (eight) GRIM_GATHER(BF, AL, false, false, true, 4);                                                      \
+    else GRIM_GATHER(BF, AL, false, false, false, 4);
+#define GRIM_GATHER_DT(BF)                                                                                           \
+    if (aligned) { GRIM_GATHER_AL(BF, true) } else { GRIM_GATHER_AL(BF, false) }
     if (A->dtype == GRIM_BF16) { GRIM_GATHER_DT(true) } else { GRIM_GATHER_DT(false) }
 #undef GRIM_GATHER_DT
+#undef GRIM_GATHER_AL
 #undef GRIM_GATHER
     return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
 }

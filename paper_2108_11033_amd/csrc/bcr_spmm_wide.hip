@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(kWideThreads) bcr_spmm_wide_rest(WideParams wp
     const int vblock = (int)blockIdx.x - wide_wgs;
     int tile, unit;
     if (!xcd_map_at(gp.map, vblock, gp.ntiles, &tile, &unit) || unit >= gp.nbr) return;
-    gather_body<BF16, true, false, false, true, kWideMulWaves + kWideFetchWaves>(gp, lds, vblock, 0);
+    gather_body<BF16, true, false, false, true, 4, kWideMulWaves + kWideFetchWaves>(gp, lds, vblock, 0);
 }
 
 template <bool BF16, int BR, int NT>
@@ -166,9 +166,9 @@ grim_status launch_spmm_wide_with_rest(const grim_bcr_matrix *A, const void *X, 
     const char *x_rest = static_cast<const char *>(X) + wide_cols * dtype_size(A->dtype);
     st = gather_setup(A, x_rest, N - wide_cols, ldx, Y + wide_cols, ldy, nullptr, nullptr, nullptr, &gp, &form);
     if (st != GRIM_OK) return st;
-    if (!form.wide || form.narrow || form.solo || !form.eight) return GRIM_ERR_UNSUPPORTED;
+    if (!form.aligned || form.narrow || form.solo || !form.eight) return GRIM_ERR_UNSUPPORTED;
     if (wide_wgs + form.nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
-    const size_t lds = std::max<size_t>((size_t)wide_lds_bytes(A, tn), (size_t)(kWideMulWaves + kWideFetchWaves) * 8192);
+    const size_t lds = std::max<size_t>((size_t)wide_lds_bytes(A, tn), (size_t)(kWideMulWaves + kWideFetchWaves) * gather_wave_lds(4));
     const bool bf = A->dtype == GRIM_BF16;
     if (A->BR == 16) {
         if (tn == 128)

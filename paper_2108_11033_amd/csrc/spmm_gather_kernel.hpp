@@ -33,6 +33,7 @@ struct GatherSecond {
     const unsigned short *X;
     float *Y;
     int32_t usteps;
+    int32_t K;
 };
 
 struct GatherParams {
@@ -46,7 +47,6 @@ struct GatherParams {
     int64_t N, ldx, ldy;
     int32_t nbr, ntiles;      // nbr: 16-row runs of the stored row order
     int32_t usteps;           // > 0: steps of every run (sptr is not read)
-    int32_t yvec;
     int32_t K;                // rows of X
     int32_t touch;            // start the tile's rows of X on their way from HBM when the workgroup starts
     XcdMap map;
@@ -56,26 +56,42 @@ struct GatherParams {
 
 // which form of the kernel a launch takes, and its workgroups
 struct GatherForm {
-    bool wide, narrow, solo, eight;
+    bool aligned, narrow, solo, eight;
+    int nt;                   // sub-tiles of 16 columns per tile
     int64_t nwg;
 };
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                          const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form);
 
-// WIDE: rows of X are 16-byte aligned (else 8-byte: two loads per piece); NARROW: N < 64;
+// 16 bytes of X at any 2-byte alignment; four results at any 4-byte alignment (both are single accesses on this GPU)
+struct __attribute__((packed, aligned(2))) GatherPiece {
+    unsigned int d[4];
+};
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// ALIGNED: rows of X are 16-byte aligned and N a multiple of 8.  Otherwise a piece is still one 16-byte load, at
+// whatever alignment its row has: from an 8-byte-aligned row it costs the vector L1 next to nothing more, from a row that
+// starts at an odd element about three aligned ones -- against the staged and vector-ALU kernels, which took such
+// products element by element before (512 x 4608 at 147 columns: 114 -> 13 us).
+// NARROW: N below the tile's width: one tile, whose pieces past N are fetched from column 0 and never stored.
+// NT: 16-column sub-tiles of a tile (4; 2 and 1 for products of at most 32 and 16 columns, whose pieces then take a half
+// or a quarter of the load instructions and LDS traffic of a padded 64-column tile).
 // SOLO: strips of a few steps only (a 3 x 3 layer of 64 channels has 5, a dense first layer 1) -- every wave takes a
 // (tile, strip) of its own, four consecutive strips per workgroup: no split of K, no partial tiles, no barrier
 // EIGHT: eight waves split a strip's steps instead of four (few workgroups, long strips: the 14 x 14 layers)
 // The body of the kernel as a function of the workgroup's number (block_x; block_y: second product of a pair), so that
 // another kernel can run such workgroups next to its own (the wide-tile kernel does, for the columns it leaves over).
-// Its first NWV waves must call it together; `lds` = NWV * 8 KB of workgroup memory.
+// Its first NWV waves must call it together; `lds` = NWV * gather_wave_lds(NT) bytes of workgroup memory.
 // LONGW: the waves that split a strip in the EIGHT form (eight in the kernel of its own; a caller with more waves to
 // spare may pass more: fewer steps per wave, fewer dependent batches).
-template <bool BF16, bool WIDE, bool NARROW, bool SOLO, bool EIGHT, int LONGW = kGatherLongWaves>
+constexpr int gather_wave_lds(int nt) { return nt * 2048; }    // two step buffers of 32 rows x 16 nt columns
+template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves>
 __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, int block_x, int block_y) {
     constexpr int NWV = EIGHT ? LONGW : 4;                     // waves of the workgroup
-    constexpr int NT = 4, TN = 64, PITCH = 128, CPR = 8;
+    constexpr int TN = NT * 16, PITCH = TN * 2, CPR = 2 * NT;  // columns, bytes and 16-byte pieces of a staged row
+    constexpr int RPI = 64 / CPR, LI = 32 / RPI;               // rows per load instruction, load instructions per step
     constexpr int SB = 4;                        // steps a wave has in flight
+    static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
     // workgroup -> (tile, stored strip, or four of them for SOLO)
     const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile, unit;
@@ -89,15 +105,15 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     const unsigned short *X = p.X;
     float *Y = p.Y;
     int usteps = p.usteps;
+    int K = p.K;
     if constexpr (NARROW) {
         if (block_y) {
             sptr = p.second.sptr; out_row = p.second.out_row; rows = p.second.rows; desc = p.second.desc;
-            payload = p.second.payload; X = p.second.X; Y = p.second.Y; usteps = p.second.usteps;
+            payload = p.second.payload; X = p.second.X; Y = p.second.Y; usteps = p.second.usteps; K = p.second.K;
         }
     }
     int64_t n0 = (int64_t)tile * TN;
-    if (n0 + TN > p.N && p.N >= TN) n0 = p.N - TN;   // ragged last tile: overlap the neighbour (N % 4 == 0)
-    // N < 64: one tile that starts at column 0; its pieces past N are fetched from column 0 instead (never stored)
+    if (!NARROW && n0 + TN > p.N) n0 = p.N - TN;     // ragged last tile: overlap the neighbour
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -110,9 +126,9 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     if constexpr (!NARROW) {
         if (p.touch) {
             const int units = p.map.per_tile;                          // workgroups of this tile
-            const int per = (p.K + units - 1) / units;
-            const int r_end = (unit + 1) * per < p.K ? (unit + 1) * per : p.K;
-            const char *base = reinterpret_cast<const char *>(X + n0) + (tid & 1) * 127;
+            const int per = (K + units - 1) / units;
+            const int r_end = (unit + 1) * per < K ? (unit + 1) * per : K;
+            const char *base = reinterpret_cast<const char *>(X + n0) + (tid & 1) * (TN * 2 - 1);
             for (int r = unit * per + (tid >> 1); r < r_end; r += NWV * 32)
                 (void)*reinterpret_cast<const volatile unsigned char *>(base + (int64_t)r * p.ldx * 2);
         }
@@ -121,68 +137,88 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     const int g0 = usteps ? t * usteps : sptr[t], nst = usteps ? usteps : sptr[t + 1] - g0;
     const int s_beg = SOLO ? g0 : g0 + (int)((int64_t)nst * wave / NWV);
     const int s_end = SOLO ? g0 + nst : g0 + (int)((int64_t)nst * (wave + 1) / NWV);
-    char *buf = lds + wave * 8192;               // two step buffers of 32 rows x 128 bytes
+    char *buf = lds + wave * gather_wave_lds(NT);    // two step buffers of 32 rows x TN columns
 
-    // fetch side: lane = (row slot rs, 16-byte piece c); its i-th load is k slot i * 8 + rs
-    const int rs = lane >> 3, c = lane & 7;
-    const bool in_a = !NARROW || c * 8 < p.N, in_b = !NARROW || c * 8 + 4 < p.N;
-    const unsigned short *xcol = X + n0 + (in_a ? c * 8 : 0);
-    const int boff = in_b ? 4 : 0;               // second half of a piece (8-byte aligned rows)
-    int wr_off[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int lrow = i * 8 + rs;
-        wr_off[i] = lrow * PITCH + ((c ^ swizzle<CPR>(lrow)) << 4);
-    }
+    // fetch side: lane = (row slot rs, 16-byte piece c); its i-th load is k slot i * RPI + rs
+    const int rs = lane / CPR, c = lane % CPR;
+    const bool in_n = !NARROW || c * 8 < p.N;
+    const unsigned short *xcol = X + n0 + (in_n ? c * 8 : 0);
+    // NARROW: pieces may reach past the last element of X (row K - 1, columns from N on): rows from this one on are put
+    // together from single guarded loads
+    const int64_t x_end = (int64_t)(K - 1) * p.ldx + p.N;
+    // (the swizzle is the same for the rows of all load instructions: RPI is a multiple of its period)
+    const int wr_off = rs * PITCH + ((c ^ (CPR == 2 ? 0 : swizzle<CPR>(rs))) << 4);
     // multiply side: lane = (output row m_row, k group); the two transpose reads of a sub-tile
     // name k slots kgroup * 8 + qd and + 4
     const int i16 = lane & 15, kgroup = lane >> 4, qd = i16 >> 2, m_row = i16;
     const unsigned int below = (1u << m_row) - 1u;
     const int ncolb = (4 * (i16 & 3)) * 2, cl = ncolb >> 4, within = ncolb & 15;
-    const int r0 = kgroup * 8 + qd, r1 = r0 + 4;
-    const int sw0 = swizzle<CPR>(r0), sw1 = swizzle<CPR>(r1);
-    const int x0 = r0 * PITCH + within, x1 = r1 * PITCH + within;
+    // The first read of sub-tile q: row r0, 16-byte chunk (2 q + cl) ^ swizzle.  The second is row r0 + 4, whose swizzle
+    // differs from row r0's by 4 (8 chunks per row) or not at all: the address of the first read of sub-tile q ^ 2 or
+    // of q itself, plus four rows -- a constant, so that the reads take NT address registers and no arithmetic.
+    const int r0 = kgroup * 8 + qd;
+    const int sw0 = CPR == 2 ? 0 : swizzle<CPR>(r0);
+    const char *tr[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) tr[q] = buf + r0 * PITCH + within + (((q * 2 + cl) ^ sw0) << 4);
 
     f32x4 acc[NT];
 #pragma unroll
     for (int q = 0; q < NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int orow = out_row[(int64_t)t * 16 + (lane & 15)];     // asked for now, needed at the very end
 
-    const u32x4 *rows4 = reinterpret_cast<const u32x4 *>(rows);
     const uint2 *desc2 = reinterpret_cast<const uint2 *>(desc);
     const i16x8 *pay = reinterpret_cast<const i16x8 *>(payload);
+    // the row numbers of the lane's k slots of a step: slot s sits at position (s % 8) * 4 + s / 8
+    typedef unsigned int Hdr __attribute__((ext_vector_type(LI)));
+    auto ask_hdr = [&](int st) {
+        Hdr h;
+        if constexpr (NT == 4) {
+            h = reinterpret_cast<const Hdr *>(rows)[(int64_t)st * 8 + rs];
+        } else {
+#pragma unroll
+            for (int i = 0; i < LI; ++i) h[i] = rows[(int64_t)st * 32 + (rs & 7) * 4 + (rs >> 3) + 2 * i];
+        }
+        return h;
+    };
     // Row numbers and descriptor of the first step of the next batch are asked for together with
     // the current batch's, so that a wave whose steps do not fit one batch (18 steps over 4 waves:
     // 4 + 1) starts the rows of X of the next batch without another dependent round trip.
-    u32x4 nhdr = {0u, 0u, 0u, 0u};
+    Hdr nhdr = 0u;
     uint2 ndsc = {0u, 0u};
     if (s_beg < s_end) {
-        nhdr = rows4[(int64_t)s_beg * 8 + rs];
+        nhdr = ask_hdr(s_beg);
         ndsc = desc2[(int64_t)s_beg * 4 + kgroup];
     }
     // The rows of X of a step (pad: bit i set = the lane's i-th k slot is padding and multiplies zeros; kept instead of
     // the row numbers) and its weights, asked for into a register set
-    struct StepRows { u32x4 rx[4]; unsigned int pad; };
-    auto ask_rows = [&](StepRows &r, const u32x4 &h) {
+    struct StepRows { u32x4 rx[LI]; unsigned int pad; };
+    auto ask_rows = [&](StepRows &r, const Hdr &h) {
         r.pad = 0u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < LI; ++i) {
             r.pad |= h[i] == 0xffffffffu ? 1u << i : 0u;
             const unsigned int row = h[i] == 0xffffffffu ? 0u : h[i];
             const unsigned short *src = xcol + (int64_t)row * p.ldx;
-            if constexpr (WIDE) {
+            if constexpr (ALIGNED) {
                 r.rx[i] = *reinterpret_cast<const u32x4 *>(src);
+            } else if (NARROW && (src - X) + 8 > x_end) {
+                unsigned int d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if ((src - X) + e < x_end) d[e >> 1] |= (unsigned int)src[e] << (16 * (e & 1));
+                r.rx[i] = u32x4{d[0], d[1], d[2], d[3]};
             } else {
-                const uint2 a = *reinterpret_cast<const uint2 *>(src);
-                const uint2 b = *reinterpret_cast<const uint2 *>(NARROW ? src + boff : src + 4);
-                r.rx[i] = u32x4{a.x, a.y, b.x, b.y};
+                GatherPiece v;
+                __builtin_memcpy(&v, src, 16);
+                r.rx[i] = u32x4{v.d[0], v.d[1], v.d[2], v.d[3]};
             }
         }
     };
     auto ask_weights = [&](const uint2 &d) {
         const bool kept = (d.x >> m_row) & 1u;
         const unsigned int idx = d.y + (kept ? __builtin_popcount(d.x & below) : 0);
-        const i16x8 wv = pay[idx];               // a block's first kept row if this lane's is not kept (zeroed below)
+        const i16x8 wv = pay[idx];               // a group's first row if it does not have this lane's (zeroed below)
         return kept ? wv : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
     };
     // A batch: SB steps in flight.  The rows of the first step of the NEXT batch are asked for as soon as this batch's
@@ -195,19 +231,19 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     auto batch = [&](int s, auto first_tag) {
         constexpr bool FIRST = decltype(first_tag)::value;
         const int nb = s_end - s < SB ? s_end - s : SB;
-        u32x4 hdr[SB];
+        Hdr hdr[SB];
         uint2 dsc[SB];
         hdr[0] = nhdr;
         dsc[0] = ndsc;
 #pragma unroll
         for (int u = 1; u < SB; ++u) {
             const int st = s + (u < nb ? u : nb - 1);
-            hdr[u] = rows4[(int64_t)st * 8 + rs];
+            hdr[u] = ask_hdr(st);
             dsc[u] = desc2[(int64_t)st * 4 + kgroup];
         }
         {
             const int st = s + SB < s_end ? s + SB : s_end - 1;
-            nhdr = rows4[(int64_t)st * 8 + rs];
+            nhdr = ask_hdr(st);
             ndsc = desc2[(int64_t)st * 4 + kgroup];
         }
         StepRows R[SB];
@@ -221,19 +257,18 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
-                char *b = buf + (u & 1) * 4096;
+                char *b = buf + (u & 1) * (32 * PITCH);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < LI; ++i) {
                     const u32x4 v = (R[u].pad >> i) & 1u ? u32x4{0u, 0u, 0u, 0u} : R[u].rx[i];
-                    *reinterpret_cast<u32x4 *>(b + wr_off[i]) = v;
+                    *reinterpret_cast<u32x4 *>(b + wr_off + i * (RPI * PITCH)) = v;
                 }
                 __builtin_amdgcn_wave_barrier();
                 if (u == 0 && s + SB < s_end) ask_rows(early, nhdr);   // set 0's rows are out of their registers
 #pragma unroll
                 for (int q = 0; q < NT; ++q) {
-                    const int cq = q * 2 + cl;
-                    const i16x4 lo = lds_tr_read(b + x0 + ((cq ^ sw0) << 4));
-                    const i16x4 hi = lds_tr_read(b + x1 + ((cq ^ sw1) << 4));
+                    const i16x4 lo = lds_tr_read(tr[q] + (u & 1) * (32 * PITCH));
+                    const i16x4 hi = lds_tr_read(tr[NT == 4 ? q ^ 2 : q] + 4 * PITCH + (u & 1) * (32 * PITCH));
                     const i16x8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                     acc[q] = mfma16<BF16>(x, PW[u], acc[q]);
                 }
@@ -244,58 +279,48 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     if (s_beg < s_end) batch(s_beg, std::true_type{});
     for (int s = s_beg + SB; s < s_end; s += SB) batch(s, std::false_type{});
 
-    if constexpr (SOLO) {
-        // the wave owns the whole 16 x 64 tile: D[n][m], lane holds m = lane % 16, n = 4 * (lane / 16) + 0..3 of sub-tile q
+    // D[n][m] of sub-tile q: lane holds m = lane % 16, n = 4 * (lane / 16) + 0..3
+    auto put = [&](int q, const f32x4 &v) {
         const int64_t row = orow;
-        if (row >= 0) {
+        const int64_t n = n0 + q * 16 + 4 * (lane >> 4);
+        if (row < 0 || (NARROW && n >= p.N)) return;
+        float *dst = Y + row * p.ldy + n;
+        if (!NARROW || n + 4 <= p.N) {
+            *reinterpret_cast<f32x4_any *>(dst) = v;
+        } else {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) {
-                const int64_t n = n0 + q * 16 + 4 * (lane >> 4);
-                if (n < p.N) {
-                    float *dst = Y + row * p.ldy + n;
-                    if (p.yvec == 4) {
-                        *reinterpret_cast<f32x4 *>(dst) = acc[q];
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) dst[e] = acc[q][e];
-                    }
-                }
-            }
+            for (int e = 0; e < 3; ++e)
+                if (n + e < p.N) dst[e] = v[e];
         }
+    };
+    if constexpr (SOLO) {
+        // the wave owns the whole 16-row tile
+#pragma unroll
+        for (int q = 0; q < NT; ++q) put(q, acc[q]);
         return;
     }
     // add the waves' partial tiles in wave order; wave q finishes sub-tile q.  A wave parks its
     // partial tile in its own (now idle) step buffers.
+    constexpr int RPW = gather_wave_lds(NT) / 16;
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
-    for (int q = 0; q < NT; ++q) red[wave * 512 + q * 64 + lane] = acc[q];
+    for (int q = 0; q < NT; ++q) red[wave * RPW + q * 64 + lane] = acc[q];
     __syncthreads();
-    if (EIGHT && wave >= NT) return;             // the first four waves finish the four sub-tiles
+    if (wave >= NT) return;                      // the first waves finish the sub-tiles
     const int q = wave;
     f32x4 sum = red[q * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NWV; ++w) {
-        const f32x4 v = red[w * 512 + q * 64 + lane];
+        const f32x4 v = red[w * RPW + q * 64 + lane];
         sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
     }
-    // D[n][m]: lane holds m = lane % 16, n = 4 * (lane / 16) + 0..3
-    const int64_t row = orow;
-    const int64_t n = n0 + q * 16 + 4 * (lane >> 4);
-    if (row >= 0 && n < p.N) {                   // n, N multiples of 4: all four columns or none
-        float *dst = Y + row * p.ldy + n;
-        if (p.yvec == 4) {
-            *reinterpret_cast<f32x4 *>(dst) = sum;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dst[e] = sum[e];
-        }
-    }
+    put(q, sum);
 }
 
-template <bool BF16, bool WIDE, bool NARROW, bool SOLO, bool EIGHT>
+template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT>
 __global__ void __launch_bounds__(EIGHT ? kGatherLongWaves * 64 : 256, EIGHT ? 1024 / (kGatherLongWaves * 64) : 4) bcr_spmm_gather(GatherParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    gather_body<BF16, WIDE, NARROW, SOLO, EIGHT>(p, lds, blockIdx.x, blockIdx.y);
+    gather_body<BF16, ALIGNED, NARROW, SOLO, EIGHT, NT>(p, lds, blockIdx.x, blockIdx.y);
 }
 
 }  // namespace grim

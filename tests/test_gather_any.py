@@ -1,0 +1,43 @@
+"""Products whose rows of X have any alignment, on the row-gathering kernel (grim_bcr_spmm with N or ldx not a multiple of
+4): every tile width of products below 64 columns and its edges, tiles that overlap at a ragged end, padded leading
+dimensions, the last rows of X (nothing past its last element may be read into a result), mixed and empty blocks."""
+import numpy as np
+import pytest
+
+import bcr_inputs as gen
+from helpers import assert_close, oracle_product, pack_workload, run_spmm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2108_11033_amd as mod
+    mod.load_library()
+    return mod
+
+
+@pytest.mark.parametrize("dtype,BR,BC", [(gen.F16, 16, 32), (gen.BF16, 32, 32), (gen.F16, 4, 16)])
+@pytest.mark.parametrize("N,ldx_pad", [(9, 0), (11, 2), (15, 0), (17, 0), (18, 0), (31, 1), (33, 0), (63, 0), (65, 0), (66, 1),
+                                       (127, 0), (130, 0), (1001, 0), (64, 1)])
+def test_rows_of_any_alignment(g, dtype, BR, BC, N, ldx_pad):
+    M, K = 96, 32 * 21
+    mask = gen.random_mask(M, K, BR, BC, tuple(sorted({0, 1, BR // 2, BR})), (0, 3, 8, 16), seed=900 + N)
+    W = gen.normal_weights(M, K, dtype, seed=901)
+    X = gen.normal_activations(K, N, dtype, seed=902)
+    A = pack_workload(g, W, dtype, mask)
+    Yref, S = oracle_product(W, X, dtype, mask)
+    Y = run_spmm(g, A, X, dtype, M, N, ldx=N + ldx_pad, ldy=N + 3)
+    assert_close(Y, Yref, S, dtype, f"{dtype} {BR}x{BC} N={N} ldx=N+{ldx_pad}")
+
+
+def test_rows_of_any_alignment_wave_per_strip(g):
+    # thousands of (tile, strip) pairs of a few steps, and a strip that keeps nothing
+    dtype, M, K, N = gen.F16, 96, 96, 33333
+    mask = gen.random_mask(M, K, 16, 32, (0, 3, 8, 16), (0, 5, 8, 32), seed=910)
+    W = gen.normal_weights(M, K, dtype, seed=911)
+    X = gen.normal_activations(K, N, dtype, seed=912, relu=True)
+    Yref, S = oracle_product(W, X, dtype, mask)
+    Y = run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, N)
+    assert_close(Y, Yref, S, dtype, "wave per strip, odd N")
+    assert np.isfinite(Y).all()
