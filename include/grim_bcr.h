@@ -174,7 +174,8 @@ grim_status grim_bcr_spmm_tuned(const grim_bcr_matrix *A, const void *X_dev, int
 
 /* grim_bcr_spmm_kernel_name -- which kernel family the grim_bcr_spmm_tuned call with these arguments
  * would launch: "bcr_spmm_wide" (first launch of a large
- * product), "bcr_spmm_gather", "bcr_spmm_mma" (staged), "bcr_spmm_fma", "bcr_spmv" (N <= 8, but see grim_bcr_spmv), or
+ * product), "bcr_spmm_gather", "bcr_spmm_mma" (staged), "bcr_spmm_fma" (fp32 multiply-adds, on the
+ * matrix cores where the matrix has that layout), "bcr_spmv" (N <= 8, but see grim_bcr_spmv), or
  * "none" when the call would fail.  A product whose rows of X are not 8-byte aligned (N or ldx not a multiple of 4) runs on
  * the row-gathering kernel's any-alignment form where the matrix has that layout and is reported under the family that
  * takes such operands otherwise ("bcr_spmm_mma" with the staged layout, else "bcr_spmm_fma").  A static string; launches nothing.  For profiling and reports. */
@@ -185,11 +186,11 @@ const char *grim_bcr_spmm_kernel_name(const grim_bcr_matrix *A, const void *X_de
  * grim_bcr_spmv -- y = W_bcr * x for 1..8 right-hand sides (Section 3.1: FC and RNN
  * gate matrices are matrix-vector products).  Same conventions as grim_bcr_spmm with
  * N = batch: x_dev is K x batch (ldx >= batch), y_dev is M x batch fp32 (ldy >= batch).
- * Reads the compact weights exactly once; the bytes moved are the stored weights plus
- * 8 bytes of row/column bit masks per block.  One case runs on the matrix cores instead, as
- * one padded tile of the row-gathering SpMM kernel, because that is quicker: batch = 8 of an
- * fp16 / bf16 matrix that kernel takes, with ldx a multiple of 8 and x_dev 16-byte aligned
- * (grim_bcr_spmm with N = 8 makes the same choice; grim_bcr_spmm_kernel_name reports it).
+ * A uniformly pruned matrix reads its compact weights exactly once, plus 8 bytes of row/column bit
+ * masks per block.  Matrices the wave-per-strip kernels are not compiled for (blocks pruned at
+ * different rates, other kept counts, more column sets than compute units) run on the matrix cores, as
+ * one padded tile of a row-gathering kernel, because that is quicker (grim_bcr_spmm with N <= 8 makes
+ * the same choice; grim_bcr_spmm_kernel_name reports it).
  * Errors: as grim_bcr_spmm; batch outside 1..8 is GRIM_ERR_SHAPE.
  */
 grim_status grim_bcr_spmv(const grim_bcr_matrix *A, const void *x_dev, int32_t batch, int64_t ldx,

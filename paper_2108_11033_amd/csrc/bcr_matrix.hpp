@@ -67,6 +67,8 @@ struct MmaLayout {
 //   desc   : per step and group the row bit mask (u32) and the place of the group's
 //            weights in `payload`, in 16-byte units (u32);
 //   payload: per group, for every row in its mask 8 weights (16 bytes).
+// fp32 (`gather32`): groups of 4 k slots that all belong to one block, steps of 16 slots.  rows: per step 16 x u32 at
+// position g * 4 + j; payload: per group, for every row in its mask 4 weights.
 struct GatherLayout {
     bool present = false;
     int64_t nsteps = 0;
@@ -137,6 +139,7 @@ struct grim_bcr_matrix {
     grim::MmaLayout mma;
     grim::MmaLayout mmaw;   // the same records cut for chunks of at most 128 rows (wide-tile kernel)
     grim::GatherLayout gather;
+    grim::GatherLayout gather32;   // fp32
     grim::GemvLayout gemv;
     // exchange words of the whole-sequence recurrent kernel (2 x H x 8 bytes), allocated by the first such call
     mutable void *seq_exch = nullptr;
@@ -213,10 +216,14 @@ double wide_plan(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx
 grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y,
                                int64_t ldy, hipStream_t stream, const grim_bcr_matrix *A2 = nullptr,
                                const void *X2 = nullptr, float *Y2 = nullptr);
+// fp32 row-gathering kernel: any N, any ldx
+bool gather32_applies(const grim_bcr_matrix *A, const void *X);
+grim_status launch_spmm_gather32(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
+                                 hipStream_t stream);
 bool gather_pair_applies(const grim_bcr_matrix *A, const void *X, const grim_bcr_matrix *A2, const void *X2, int64_t N,
                          int64_t ldx);
 bool gather_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx);
-bool gather_any_applies(const grim_bcr_matrix *A, const void *X);   // the same with rows of X at any alignment and any N
+bool gather_any_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx);   // the same with rows of X at any alignment and any N
 // launch form of the row-gathering kernels: a (tile, strip) pair per wave instead of four waves per strip
 bool gather_wave_per_strip(const grim_bcr_matrix *A, int64_t pairs, int64_t pairs_for_long_strips);
 // convolution on the row-gathering layout, the im2col matrix never formed
@@ -250,6 +257,7 @@ bool spmv_cell_applies(int kind, int64_t M, int64_t K, int32_t BR, int32_t BC, i
 constexpr int32_t kCellMaxBatch = 32;
 bool spmv_cell_batch_ok(int64_t H, int32_t BR, int32_t batch);   // all sets of workgroups in one round on this GPU?
 bool spmv_exact_applies(int32_t dtype, int32_t ukr, int32_t ukc, int64_t K);
+bool spmv_many_strips_applies(int64_t count, int64_t nbr, int32_t dtype, int32_t ukr, int32_t ukc, int64_t K, int32_t BC, int32_t batch);
 bool spmv_column_sets_ok(int64_t count, int64_t nbr, int32_t batch);   // columns as sets of workgroups of the one-column kernel
 grim_status launch_spmv_cell(int kind, const GemvDesc &d1, const GemvDesc *d2, int64_t M, int64_t K, int32_t BR, int32_t BC,
                              int32_t dtype, int32_t ukr, int32_t ukc, const void *x, int64_t x_stride, int32_t batch, int64_t ldx,

@@ -287,6 +287,72 @@ void build_gather_layout(grim_bcr_matrix *A) {
     L.present = true;
 }
 
+// ---- derived layout: row-gathering SpMM, fp32 ------------------------------------------------
+// A block's kept columns in groups of four (a group never holds columns of two blocks: the row mask then says exactly
+// which rows keep its columns).
+void build_gather32_layout(grim_bcr_matrix *A) {
+    GatherLayout &L = A->gather32;
+    L = GatherLayout();
+    if (A->dtype != GRIM_F32 || A->K > 0x7fffffff || A->M > 0x7fffffff) return;
+    if (!(16 % A->BR == 0 || A->BR % 16 == 0)) return;
+    const float *w = reinterpret_cast<const float *>(A->weights.data());
+    const int64_t nss = (A->M + 15) / 16;
+    L.nstrips = nss;
+    L.sptr.assign((size_t)nss + 1, 0);
+    L.out_row.assign((size_t)nss * 16, -1);
+    for (int64_t p = 0; p < A->nbr; ++p)
+        for (int32_t r = 0; r < A->BR; ++r)
+            L.out_row[(size_t)(p * A->BR + r)] = (int32_t)((int64_t)A->strip_order[p] * A->BR + r);
+    size_t units = 0;                                                        // 16-byte units of payload written
+    L.payload.reserve(A->weights.size() + A->weights.size() / 8);
+    for (int64_t u = 0; u < nss; ++u) {
+        L.sptr[(size_t)u] = (int32_t)L.nsteps;
+        int g = 4;                                                           // next group of the last step
+        const int64_t row0 = u * 16, row1 = std::min<int64_t>(A->M, row0 + 16);
+        const int64_t p0 = row0 / A->BR, p1 = (row1 - 1) / A->BR;            // stored strips that overlap this run
+        for (int64_t c = 0; c < A->nbc; ++c) {
+            for (int64_t p = p0; p <= p1; ++p) {
+                const int64_t t = p * A->nbc + c, base = p * A->BR;
+                int32_t q0 = A->row_ptr[t], q1 = A->row_ptr[t + 1];
+                while (q0 < q1 && base + A->row_idx[q0] < row0) ++q0;
+                while (q0 < q1 && base + A->row_idx[q1 - 1] >= row1) --q1;
+                if (q0 == q1) continue;
+                const int32_t c0 = A->col_ptr[t], kc = A->col_ptr[t + 1] - c0;
+                uint32_t rowmask = 0;
+                for (int32_t q = q0; q < q1; ++q) rowmask |= 1u << (base + A->row_idx[q] - row0);
+                for (int32_t j = 0; j < kc; j += 4) {
+                    if (g == 4) {
+                        if (L.nsteps >= 0x7fffffff) { L = GatherLayout(); return; }
+                        ++L.nsteps;
+                        L.rows.resize((size_t)L.nsteps * 16, 0xffffffffu);
+                        L.desc.resize((size_t)L.nsteps * 8, 0u);
+                        g = 0;
+                    }
+                    const int32_t n = std::min<int32_t>(4, kc - j);
+                    const size_t step = (size_t)L.nsteps - 1;
+                    for (int32_t e = 0; e < n; ++e) L.rows[step * 16 + (size_t)g * 4 + e] = (uint32_t)(c * A->BC + A->col_idx[c0 + j + e]);
+                    if (units + 16 > 0xffffffffu) { L = GatherLayout(); return; }
+                    L.desc[step * 8 + (size_t)g * 2] = rowmask;
+                    L.desc[step * 8 + (size_t)g * 2 + 1] = (uint32_t)units;
+                    L.payload.resize((units + (size_t)(q1 - q0)) * 16);
+                    for (int32_t q = q0; q < q1; ++q, ++units)
+                        std::memcpy(L.payload.data() + units * 16, w + A->blk_ptr[t] + (int64_t)(q - A->row_ptr[t]) * kc + j, (size_t)n * 4);
+                    L.xrows += n;
+                    ++g;
+                }
+            }
+        }
+    }
+    L.sptr[(size_t)nss] = (int32_t)L.nsteps;
+    L.usteps = L.sptr[1];
+    for (int64_t u = 0; u < nss; ++u) {
+        const int32_t n = L.sptr[(size_t)u + 1] - L.sptr[(size_t)u];
+        if (n != L.usteps) L.usteps = 0;
+        L.max_steps = std::max<int32_t>(L.max_steps, n);
+    }
+    L.present = true;
+}
+
 // ---- derived layout: SpMV --------------------------------------------------------------
 void build_gemv_layout(grim_bcr_matrix *A) {
     GemvLayout &G = A->gemv;
@@ -361,6 +427,14 @@ grim_status upload(grim_bcr_matrix *A) {
         o_gd = s.add(bytes(A->gather.desc) + 16);
         o_gp = s.add(bytes(A->gather.payload) + 16);
     }
+    size_t o_hs = 0, o_hq = 0, o_hr = 0, o_hd = 0, o_hp = 0;
+    if (A->gather32.present) {
+        o_hs = s.add(bytes(A->gather32.sptr));
+        o_hq = s.add(bytes(A->gather32.out_row));
+        o_hr = s.add(bytes(A->gather32.rows));
+        o_hd = s.add(bytes(A->gather32.desc));
+        o_hp = s.add(bytes(A->gather32.payload) + 16);
+    }
     size_t mma_end = s.total;
     if (A->gemv.present) {
         o_gm = s.add(bytes(A->gemv.masks));
@@ -385,6 +459,9 @@ grim_status upload(grim_bcr_matrix *A) {
     if (ok && A->gather.present)
         ok = put(o_gs, A->gather.sptr.data(), bytes(A->gather.sptr)) && put(o_gq, A->gather.out_row.data(), bytes(A->gather.out_row)) && put(o_gr, A->gather.rows.data(), bytes(A->gather.rows)) &&
              put(o_gd, A->gather.desc.data(), bytes(A->gather.desc)) && put(o_gp, A->gather.payload.data(), bytes(A->gather.payload));
+    if (ok && A->gather32.present)
+        ok = put(o_hs, A->gather32.sptr.data(), bytes(A->gather32.sptr)) && put(o_hq, A->gather32.out_row.data(), bytes(A->gather32.out_row)) && put(o_hr, A->gather32.rows.data(), bytes(A->gather32.rows)) &&
+             put(o_hd, A->gather32.desc.data(), bytes(A->gather32.desc)) && put(o_hp, A->gather32.payload.data(), bytes(A->gather32.payload));
     if (ok && A->gemv.present)
         ok = put(o_gm, A->gemv.masks.data(), bytes(A->gemv.masks)) && put(o_go, A->gemv.woff.data(), bytes(A->gemv.woff));
     if (!ok) { (void)hipGetLastError(); (void)hipFree(base); return GRIM_ERR_DEVICE; }
@@ -417,6 +494,14 @@ grim_status upload(grim_bcr_matrix *A) {
         A->gather.d_desc = reinterpret_cast<uint32_t *>(base + o_gd);
         A->gather.d_payload = reinterpret_cast<unsigned char *>(base + o_gp);
         A->gather.bytes = (int64_t)(o_gp + bytes(A->gather.payload) + 16 - o_gs);
+    }
+    if (A->gather32.present) {
+        A->gather32.d_sptr = reinterpret_cast<int32_t *>(base + o_hs);
+        A->gather32.d_out_row = reinterpret_cast<int32_t *>(base + o_hq);
+        A->gather32.d_rows = reinterpret_cast<uint32_t *>(base + o_hr);
+        A->gather32.d_desc = reinterpret_cast<uint32_t *>(base + o_hd);
+        A->gather32.d_payload = reinterpret_cast<unsigned char *>(base + o_hp);
+        A->gather32.bytes = (int64_t)(o_hp + bytes(A->gather32.payload) + 16 - o_hs);
     }
     if (A->gemv.present) {
         A->gemv.d_masks = reinterpret_cast<uint32_t *>(base + o_gm);
@@ -549,6 +634,7 @@ grim_status grim_bcr_pack(const void *W_host, grim_dtype dt, int64_t M, int64_t 
                 }
             }
             build_gather_layout(A);
+            build_gather32_layout(A);
             build_gemv_layout(A);
             if (f1.valid()) f1.get(); else mma();
             if (f2.valid()) f2.get(); else wide();
@@ -785,8 +871,6 @@ grim_status grim_bcr_arrays(const grim_bcr_matrix *A, grim_bcr_view *v) {
     return GRIM_OK;
 }
 
-// Eight right-hand sides in 16-byte-aligned rows: one (padded) tile of the row-gathering matrix-core
-// kernel beats the vector-ALU SpMV kernel (4096 x 2048 at 10.7x: 8.0 -> 5.6 us; at 4 it does not)
 // a few columns of a uniformly pruned matrix: the one-column SpMV kernel on a set of workgroups per column, while all
 // sets fit the GPU in one round
 // (`count`: products of this shape in the launch -- 2 for the two sides of a GRU step)
@@ -796,13 +880,27 @@ static bool columns_as_sets(const grim_bcr_matrix *A, int64_t N, int count) {
            spmv_column_sets_ok(count, A->nbr, (int32_t)N);
 }
 
+// Up to eight right-hand sides of a matrix the wave-per-strip SpMV kernels are not compiled for (blocks pruned at
+// different rates, kept counts outside their pairs, too many columns for sets of workgroups): one padded 16-column tile
+// of a row-gathering matrix-core kernel, at any alignment.  Against the workgroup-per-strip kernel bcr_spmv, whose cost
+// grows with the columns: 4096 x 4096 of mixed rates at 1 / 2 / 5 / 8 columns 13.5 / 11.6 / 15.1 / 16 -> 6.3 / 5.4 / 6.1 /
+// 5.1 us, 512 x 512 5.2 / 5.2 / 5.3 / 5.9 -> 5.2 / 4.7 / 4.7 / 4.2 us, fp32 4096 x 2048 12.5 / 9.0 / 11.5 / 13.6 ->
+// 5.5 / 5.5 / 5.9 / 5.4 us.  Uniform blocks stay: one column of 4096 x 2048 4.3 us against 6.1.
 static bool skinny_on_matrix_cores(const grim_bcr_matrix *A, const void *X_dev, int64_t N, int64_t ldx, int count = 1) {
-    return N == 8 && !columns_as_sets(A, N, count) && ldx % 8 == 0 && reinterpret_cast<uintptr_t>(X_dev) % 16 == 0 &&
-           gather_applies(A, X_dev, N, ldx);
+    if (N > 8 || columns_as_sets(A, N, count)) return false;
+    // (blocks the SpMV kernels do not take are left to the choice among the SpMM kernels)
+    if (!gemv_ok(A, N) && !(N == 8 && ldx % 8 == 0 && reinterpret_cast<uintptr_t>(X_dev) % 16 == 0)) return false;
+    if (N == 1 && gemv_ok(A, 1) && spmv_exact_applies(A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->K)) return false;
+    if (N < 8 && gemv_ok(A, N) && spmv_many_strips_applies(count, A->nbr, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->K, A->BC, (int32_t)N))
+        return false;
+    return A->dtype == GRIM_F32 ? gather32_applies(A, X_dev) : gather_any_applies(A, X_dev, N, ldx);
+}
+static grim_status launch_skinny(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, hipStream_t stream) {
+    return A->dtype == GRIM_F32 ? launch_spmm_gather32(A, X, N, ldx, Y, ldy, stream) : launch_spmm_gather(A, X, N, ldx, Y, ldy, stream);
 }
 
 // which kernel family a grim_bcr_spmm_tuned call runs
-enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_GATHER_ANY, ROUTE_WIDE };
+enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_GATHER_ANY, ROUTE_GATHER32, ROUTE_WIDE };
 
 // what the columns the wide-tile kernel leaves over cost on the kernels that take any N
 static double rest_cost(const grim_bcr_matrix *A, int64_t n) {
@@ -827,7 +925,7 @@ static SpmmRoute spmm_route(const grim_bcr_matrix *A, const void *X_dev, int64_t
         *wide_cols = N;
         return !strips_per_wg && wide_applies(A, X_dev, N, ldx, Y_dev, ldy, tile_n) ? ROUTE_WIDE : ROUTE_NONE;
     }
-    if (free_choice && skinny_on_matrix_cores(A, X_dev, N, ldx)) return ROUTE_GATHER;
+    if (free_choice && skinny_on_matrix_cores(A, X_dev, N, ldx)) return A->dtype == GRIM_F32 ? ROUTE_GATHER32 : ROUTE_GATHER;
     if (free_choice && gemv_ok(A, N)) return ROUTE_SPMV;
     const bool mma = A->mma.present && kernel != 1;
     if (kernel == 2 && !mma) return ROUTE_NONE;
@@ -839,7 +937,8 @@ static SpmmRoute spmm_route(const grim_bcr_matrix *A, const void *X_dev, int64_t
         const double wide = wide_plan(A, X_dev, N, ldx, Y_dev, ldy, rest_cost, wide_tn, wide_cols);
         if (wide >= 0 && (staged < 0 || wide < staged) && (gather < 0 || wide < gather)) return ROUTE_WIDE;
         if (gather >= 0 && (staged < 0 || gather < staged)) return ROUTE_GATHER;
-        if (gather < 0 && gather_any_applies(A, X_dev)) return ROUTE_GATHER_ANY;
+        if (gather < 0 && gather_any_applies(A, X_dev, N, ldx)) return ROUTE_GATHER_ANY;
+        if (gather32_applies(A, X_dev)) return ROUTE_GATHER32;
     }
     if (mma) return ROUTE_MMA;
     return A->BR > 64 ? ROUTE_NONE : ROUTE_FMA;
@@ -860,6 +959,7 @@ grim_status grim_bcr_spmm_tuned(const grim_bcr_matrix *A, const void *X_dev, int
         }
         case ROUTE_GATHER:
         case ROUTE_GATHER_ANY: return launch_spmm_gather(A, X_dev, N, ldx, Y_dev, ldy, stream);
+        case ROUTE_GATHER32: return launch_spmm_gather32(A, X_dev, N, ldx, Y_dev, ldy, stream);
         case ROUTE_WIDE: {
             // whole rounds of fat workgroups, the few columns left over on whatever suits them: in the same launch when
             // that is the row-gathering kernel in the form the combined kernel carries, else in a launch of their own
@@ -912,6 +1012,8 @@ const char *grim_bcr_spmm_kernel_name(const grim_bcr_matrix *A, const void *X_de
         // (rows of X at any alignment: reported as the family that is otherwise the matrix's for such operands)
         case ROUTE_GATHER_ANY: return A->mma.present ? "bcr_spmm_mma" : "bcr_spmm_fma";
         case ROUTE_MMA: return "bcr_spmm_mma";
+        // (fp32 multiply-adds on the vector ALUs or, where the matrix has that layout, on the matrix cores)
+        case ROUTE_GATHER32:
         case ROUTE_FMA: return "bcr_spmm_fma";
         case ROUTE_NONE: break;
     }
@@ -930,7 +1032,7 @@ grim_status grim_bcr_spmv(const grim_bcr_matrix *A, const void *x_dev, int32_t b
     grim_status st = check_call(A, x_dev, batch, ldx, y_dev, ldy);
     if (st != GRIM_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (skinny_on_matrix_cores(A, x_dev, batch, ldx)) return launch_spmm_gather(A, x_dev, batch, ldx, y_dev, ldy, stream);
+    if (skinny_on_matrix_cores(A, x_dev, batch, ldx)) return launch_skinny(A, x_dev, batch, ldx, y_dev, ldy, stream);
     if (gemv_ok(A, batch)) {
         GemvDesc d = desc_of(A);
         return launch_spmv(nullptr, d, nullptr, 1, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc,
@@ -1100,9 +1202,9 @@ int32_t grim_bcr_rnn_step_launches(const grim_bcr_matrix *A, const grim_bcr_matr
                        spmv_cell_applies(2, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->M / 3);
     if (fused) return 1;
     // both products in one launch (SpMV kernels up to 8 columns when the matrices have one shape; the row-gathering
-    // kernel for 4 .. 60 columns in multiples of 4), then the cell; otherwise a launch per product
+    // kernel below 64 columns), then the cell; otherwise a launch per product
     const bool one_spmv = batch <= 8 && same && A->K * batch * dtype_size(A->dtype) <= kGemvMaxXBytes;
-    const bool one_gather = batch < 64 && batch % 4 == 0 && A->gather.present && Ah->gather.present &&
+    const bool one_gather = batch < 64 && A->gather.present && Ah->gather.present &&
                             A->gather.nstrips == Ah->gather.nstrips;
     return one_spmv || one_gather ? 2 : 3;
 }
@@ -1255,7 +1357,7 @@ grim_status grim_bcr_gru_step(const grim_bcr_matrix *Ai, const grim_bcr_matrix *
     const int esz = dtype_size(Ai->dtype);
     const ptrdiff_t xd = static_cast<const char *>(hin_dev) - static_cast<const char *>(x_dev);
     const ptrdiff_t yd = reinterpret_cast<const char *>(gh_dev) - reinterpret_cast<const char *>(gi_dev);
-    // (8 columns in 16-byte-aligned rows are quicker on the matrix cores, as for a lone product)
+    // (few columns of a matrix the wave-per-strip kernels are not compiled for: on the matrix cores, as for a lone product)
     if (spmv_cell_batch_ok(H, Ai->BR, batch) && Ai->K == Ah->K && Ai->BR == Ah->BR && Ai->BC == Ah->BC && Ai->gemv.present && Ah->gemv.present &&
         Ai->gemv.uniform_kr == Ah->gemv.uniform_kr && Ai->gemv.uniform_kc == Ah->gemv.uniform_kc && ldx == ldhin && ldgi == ldgh &&
         xd % esz == 0 && yd % 4 == 0) {
@@ -1272,10 +1374,10 @@ grim_status grim_bcr_gru_step(const grim_bcr_matrix *Ai, const grim_bcr_matrix *
             if (st != GRIM_ERR_UNSUPPORTED) return st;
         }
     }
-    const bool eight_on_matrix_cores = ldx == ldhin && ldgi == ldgh && skinny_on_matrix_cores(Ai, x_dev, batch, ldx, 2) &&
+    const bool few_on_matrix_cores = ldx == ldhin && ldgi == ldgh && skinny_on_matrix_cores(Ai, x_dev, batch, ldx, 2) &&
                                        skinny_on_matrix_cores(Ah, hin_dev, batch, ldx, 2) &&
                                        gather_pair_applies(Ai, x_dev, Ah, hin_dev, batch, ldx);
-    if (!eight_on_matrix_cores && batch <= 8 && Ai->K == Ah->K && Ai->BR == Ah->BR && Ai->BC == Ah->BC && gemv_ok(Ai, batch) &&
+    if (!few_on_matrix_cores && batch <= 8 && Ai->K == Ah->K && Ai->BR == Ah->BR && Ai->BC == Ah->BC && gemv_ok(Ai, batch) &&
         gemv_ok(Ah, batch) && ldx == ldhin && ldgi == ldgh && xd % esz == 0 && yd % 4 == 0) {
         const GemvDesc di = desc_of(Ai), dh = desc_of(Ah);
         const bool same = Ai->gemv.uniform_kr == Ah->gemv.uniform_kr && Ai->gemv.uniform_kc == Ah->gemv.uniform_kc;
@@ -1284,7 +1386,7 @@ grim_status grim_bcr_gru_step(const grim_bcr_matrix *Ai, const grim_bcr_matrix *
                          std::max(Ai->gemv.krmax, Ah->gemv.krmax), std::max(Ai->gemv.kcmax, Ah->gemv.kcmax), x_dev, xd / esz,
                          batch, ldx, gi_dev, yd / 4, ldgi, static_cast<hipStream_t>(hip_stream));
     } else if (ldx == ldhin && ldgi == ldgh && gather_pair_applies(Ai, x_dev, Ah, hin_dev, batch, ldx)) {
-        // 4 .. 60 columns on the matrix cores: one launch of the row-gathering kernel, grid.y = product
+        // fewer than 64 columns on the matrix cores: one launch of the row-gathering kernel, grid.y = product
         st = launch_spmm_gather(Ai, x_dev, batch, ldx, gi_dev, ldgi, static_cast<hipStream_t>(hip_stream), Ah, hin_dev, gh_dev);
     } else {
         st = grim_bcr_spmm(Ai, x_dev, batch, ldx, gi_dev, ldgi, hip_stream);

@@ -13,8 +13,9 @@ bool gather_wave_per_strip(const grim_bcr_matrix *A, int64_t pairs, int64_t pair
 bool gather_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx) {
     return A->gather.present && N >= 4 && N % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 8 == 0;
 }
-bool gather_any_applies(const grim_bcr_matrix *A, const void *X) {
-    return A->gather.present && reinterpret_cast<uintptr_t>(X) % 2 == 0;
+// (below 64 columns the kernel reads the last 16 bytes of X as a whole: there have to be that many)
+bool gather_any_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx) {
+    return A->gather.present && reinterpret_cast<uintptr_t>(X) % 2 == 0 && (N >= 64 || (A->K - 1) * ldx + N >= 8);
 }
 
 // Bytes through one compute unit, the quantity both matrix-core kernels are bound by at these
@@ -34,14 +35,14 @@ double gather_cost(const grim_bcr_matrix *A, int64_t N) {
 // same element type, number of 16-row runs, N and leading dimensions; K may differ.
 bool gather_pair_applies(const grim_bcr_matrix *A, const void *X, const grim_bcr_matrix *A2, const void *X2, int64_t N,
                          int64_t ldx) {
-    return N < 64 && gather_applies(A, X, N, ldx) && gather_applies(A2, X2, N, ldx) && A->dtype == A2->dtype &&
+    return N < 64 && gather_any_applies(A, X, N, ldx) && gather_any_applies(A2, X2, N, ldx) && A->dtype == A2->dtype &&
            A->gather.nstrips == A2->gather.nstrips;
 }
 
 // Parameters, grid and kernel form of a launch (see launch_spmm_gather); GRIM_ERR_UNSUPPORTED when the kernel does not apply.
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                          const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form) {
-    if (!gather_any_applies(A, X)) return GRIM_ERR_UNSUPPORTED;
+    if (!gather_any_applies(A, X, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     if (A2 && !gather_pair_applies(A, X, A2, X2, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     GatherParams p;
     p.sptr = A->gather.d_sptr;
@@ -55,13 +56,15 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     p.nbr = (int32_t)A->gather.nstrips;
     p.K = (int32_t)A->K;
     p.usteps = A->gather.usteps;
+    p.exact = exact_arrays(A);
     // fewer than 64 columns: one tile of the narrowest width that holds them
     const int nt = N > 32 ? 4 : N > 16 ? 2 : 1;
     p.ntiles = (int32_t)((N + nt * 16 - 1) / (nt * 16));
-    p.second = GatherSecond{p.sptr, p.out_row, p.rows, p.desc, p.payload, p.X, p.Y, p.usteps, p.K};
+    p.second = GatherSecond{p.sptr, p.out_row, p.rows, p.desc, p.payload, p.X, p.Y, p.usteps, p.K, exact_arrays(A)};
     if (A2)
         p.second = GatherSecond{A2->gather.d_sptr, A2->gather.d_out_row, A2->gather.d_rows, A2->gather.d_desc,
-                                A2->gather.d_payload, static_cast<const unsigned short *>(X2), Y2, A2->gather.usteps, (int32_t)A2->K};
+                                A2->gather.d_payload, static_cast<const unsigned short *>(X2), Y2, A2->gather.usteps, (int32_t)A2->K,
+                                exact_arrays(A2)};
     // strips of at most 8 steps (two batches of a wave) with enough (tile, strip) pairs to fill the GPU: wave per pair;
     // long strips and fewer workgroups than compute units: eight waves per strip
     const bool narrow = N < 64;
@@ -70,7 +73,7 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     // save (12.0 -> 12.4 us on a 2304-row product, five-step strips 15.5 -> 24 us).
     p.touch = !narrow && A->gather.max_steps >= 40 ? 1 : 0;
     const bool solo = !narrow && gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 1536);
-    const bool eight = !narrow && !solo && A->gather.max_steps >= 16 && (int64_t)p.ntiles * p.nbr <= 256;
+    const bool eight = !solo && A->gather.max_steps >= 16 && (narrow || (int64_t)p.ntiles * p.nbr <= 256);
     const int64_t per_tile = solo ? (p.nbr + 3) / 4 : p.nbr;
     if (((int64_t)p.ntiles + 7) / 8 * 8 * per_tile > 0x7fffffff) return GRIM_ERR_SHAPE;
     int64_t nwg = 0;
@@ -95,7 +98,7 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
     if (st != GRIM_OK) return st;
     const bool narrow = form.narrow, solo = form.solo, eight = form.eight, aligned = form.aligned;
     const int64_t nwg = form.nwg;
-    const size_t lds = (size_t)(eight ? kGatherLongWaves : 4) * gather_wave_lds(form.nt);
+    const size_t lds = (size_t)(eight ? kGatherLongWaves : 4) * gather_wave_lds(form.nt) + kGatherWatchBytes;
     const dim3 grid((unsigned)nwg, A2 ? 2u : 1u), block(eight ? kGatherLongWaves * 64 : 256);
 #define GRIM_GATHER(BF, AL, NR, SO, EI, NT)                                                                              \
     do {                                                                                                             \
@@ -112,9 +115,9 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
         hipLaunchKernelGGL(kern, grid, block, lds, stream, p);                                                       \
     } while (0)
 #define GRIM_GATHER_AL(BF, AL)                                                                                       \
-    if (narrow && form.nt == 1) GRIM_GATHER(BF, AL, true, false, false, 1);                                          \
-    else if (narrow && form.nt == 2) GRIM_GATHER(BF, AL, true, false, false, 2);                                     \
-    else if (narrow) GRIM_GATHER(BF, AL, true, false, false, 4);                                                     \
+    if (narrow && form.nt == 1) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 1); else GRIM_GATHER(BF, AL, true, false, false, 1); } \
+    else if (narrow && form.nt == 2) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 2); else GRIM_GATHER(BF, AL, true, false, false, 2); } \
+    else if (narrow) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 4); else GRIM_GATHER(BF, AL, true, false, false, 4); } \
     else if (solo) GRIM_GATHER(BF, AL, false, true, false, 4);                                                       \
     else if (eight) GRIM_GATHER(BF, AL, false, false, true, 4);                                                      \
     else GRIM_GATHER(BF, AL, false, false, false, 4);

@@ -1056,10 +1056,8 @@ grim_status launch_spmv(const GemvDesc *table, const GemvDesc &single, const Gem
             if (st != GRIM_ERR_UNSUPPORTED) return st;
         }
     }
-    if (batch > 1 && dtype != GRIM_F32 && ukr > 0 && ukc > 0 && (ukr * ukc * esz) % 16 == 0 && ukr * ukc * esz <= 384 &&
-        K / BC <= 64 && (int64_t)K * batch * esz <= 64 * 1024 && (int64_t)count * nbr >= 1024) {
-        // uniform blocks, several right-hand sides, a launch of at least 128 workgroups: wave per
-        // strip, 8 waves share x in LDS (smaller launches are quicker with a workgroup per strip)
+    if (spmv_many_strips_applies(count, nbr, dtype, ukr, ukc, K, BC, batch)) {
+        // wave per strip, 8 waves share x in LDS
         const int nv = ukr * ukc * esz / 16, nw = 8;
         GemvParams q = p;
         q.seg_blocks = 64;
@@ -1135,6 +1133,14 @@ bool spmv_exact_applies(int32_t dtype, int32_t ukr, int32_t ukc, int64_t K) {
     const int esz = dtype_size(dtype);
     if (!((ukr == 4 || ukr == 8 || ukr == 16) && (ukc == 4 || ukc == 8 || ukc == 12 || ukc == 16))) return false;
     return (ukr * ukc * esz) % 16 == 0 && ukr * ukc * esz <= 384 && K * esz <= 32 * 1024;
+}
+
+// uniform blocks, several right-hand sides, a launch of at least 128 workgroups of the wave-per-strip kernel for several
+// columns (smaller launches are quicker with a workgroup per strip)
+bool spmv_many_strips_applies(int64_t count, int64_t nbr, int32_t dtype, int32_t ukr, int32_t ukc, int64_t K, int32_t BC, int32_t batch) {
+    const int esz = dtype_size(dtype);
+    return batch > 1 && dtype != GRIM_F32 && ukr > 0 && ukc > 0 && (ukr * ukc * esz) % 16 == 0 && ukr * ukc * esz <= 384 &&
+           K / BC <= 64 && K * batch * esz <= 64 * 1024 && count * nbr >= 1024;
 }
 
 // `count` products of nbr strips each on `batch` columns as sets of workgroups of the one-column kernel (four strips per

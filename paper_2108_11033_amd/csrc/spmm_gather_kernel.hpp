@@ -2,7 +2,7 @@
 #pragma once
 #include <type_traits>
 
-#include "spmm_common.hpp"
+#include "spmm_exact.hpp"
 
 namespace grim {
 
@@ -34,6 +34,7 @@ struct GatherSecond {
     float *Y;
     int32_t usteps;
     int32_t K;
+    ExactArrays exact;
 };
 
 struct GatherParams {
@@ -50,6 +51,7 @@ struct GatherParams {
     int32_t K;                // rows of X
     int32_t touch;            // start the tile's rows of X on their way from HBM when the workgroup starts
     XcdMap map;
+    ExactArrays exact;
     GatherSecond second;
 };
 
@@ -85,12 +87,16 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // LONGW: the waves that split a strip in the EIGHT form (eight in the kernel of its own; a caller with more waves to
 // spare may pass more: fewer steps per wave, fewer dependent batches).
 constexpr int gather_wave_lds(int nt) { return nt * 2048; }    // two step buffers of 32 rows x 16 nt columns
+constexpr int kGatherWatchBytes = 64;                          // behind them: a word per wave (WATCH forms)
 template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves>
 __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, int block_x, int block_y) {
     constexpr int NWV = EIGHT ? LONGW : 4;                     // waves of the workgroup
     constexpr int TN = NT * 16, PITCH = TN * 2, CPR = 2 * NT;  // columns, bytes and 16-byte pieces of a staged row
     constexpr int RPI = 64 / CPR, LI = 32 / RPI;               // rows per load instruction, load instructions per step
-    constexpr int SB = 4;                        // steps a wave has in flight
+    // forms of operands that other kernels used to take, which multiply kept weights only: an infinity or NaN in X must
+    // not reach the rows of the run that do not keep its column
+    constexpr bool WATCH = NARROW || !ALIGNED;
+    constexpr int SB = NT == 1 ? 8 : !NARROW && WATCH && !EIGHT ? 3 : 4;      // steps a wave has in flight (as its registers allow)
     static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
     // workgroup -> (tile, stored strip, or four of them for SOLO)
     const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -106,8 +112,10 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     float *Y = p.Y;
     int usteps = p.usteps;
     int K = p.K;
+    const ExactArrays *exact = &p.exact;
     if constexpr (NARROW) {
         if (block_y) {
+            exact = &p.second.exact;
             sptr = p.second.sptr; out_row = p.second.out_row; rows = p.second.rows; desc = p.second.desc;
             payload = p.second.payload; X = p.second.X; Y = p.second.Y; usteps = p.second.usteps; K = p.second.K;
         }
@@ -143,9 +151,10 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     const int rs = lane / CPR, c = lane % CPR;
     const bool in_n = !NARROW || c * 8 < p.N;
     const unsigned short *xcol = X + n0 + (in_n ? c * 8 : 0);
-    // NARROW: pieces may reach past the last element of X (row K - 1, columns from N on): rows from this one on are put
-    // together from single guarded loads
-    const int64_t x_end = (int64_t)(K - 1) * p.ldx + p.N;
+    // NARROW: pieces may reach past the last element of X (row K - 1, columns from N on): such a piece is fetched from
+    // `x_last`, the last 16 bytes of X, and shifted into place when it is parked -- a branch around the load instead cost
+    // the other loads their overlap (4096 x 4096 at 5 columns: 7.9 us)
+    const unsigned short *x_last = X + ((int64_t)(K - 1) * p.ldx + p.N - 8);
     // (the swizzle is the same for the rows of all load instructions: RPI is a multiple of its period)
     const int wr_off = rs * PITCH + ((c ^ (CPR == 2 ? 0 : swizzle<CPR>(rs))) << 4);
     // multiply side: lane = (output row m_row, k group); the two transpose reads of a sub-tile
@@ -162,6 +171,14 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 #pragma unroll
     for (int q = 0; q < NT; ++q) tr[q] = buf + r0 * PITCH + within + (((q * 2 + cl) ^ sw0) << 4);
 
+    // WATCH: exponent bits of the piece's columns below N, and the largest exponents met at each position of a dword
+    constexpr unsigned int kExponents = BF16 ? 0x7f807f80u : 0x7c007c00u;
+    unsigned int exps[4] = {kExponents, kExponents, kExponents, kExponents}, largest = 0u;
+    if constexpr (NARROW) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            exps[d] = kExponents & ((c * 8 + 2 * d < p.N ? 0xffffu : 0u) | (c * 8 + 2 * d + 1 < p.N ? 0xffff0000u : 0u));
+    }
     f32x4 acc[NT];
 #pragma unroll
     for (int q = 0; q < NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -191,7 +208,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
         ndsc = desc2[(int64_t)s_beg * 4 + kgroup];
     }
     // The rows of X of a step (pad: bit i set = the lane's i-th k slot is padding and multiplies zeros; kept instead of
-    // the row numbers) and its weights, asked for into a register set
+    // the row numbers; bits 8 + 4 i: elements its piece was fetched early) and its weights, asked for into a register set
     struct StepRows { u32x4 rx[LI]; unsigned int pad; };
     auto ask_rows = [&](StepRows &r, const Hdr &h) {
         r.pad = 0u;
@@ -202,12 +219,12 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             const unsigned short *src = xcol + (int64_t)row * p.ldx;
             if constexpr (ALIGNED) {
                 r.rx[i] = *reinterpret_cast<const u32x4 *>(src);
-            } else if (NARROW && (src - X) + 8 > x_end) {
-                unsigned int d[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if ((src - X) + e < x_end) d[e >> 1] |= (unsigned int)src[e] << (16 * (e & 1));
-                r.rx[i] = u32x4{d[0], d[1], d[2], d[3]};
+            } else if constexpr (NARROW) {
+                const int over = src > x_last ? (int)(src - x_last) : 0;      // elements, below 8
+                r.pad |= (unsigned int)over << (8 + 4 * i);
+                GatherPiece v;
+                __builtin_memcpy(&v, src - over, 16);
+                r.rx[i] = u32x4{v.d[0], v.d[1], v.d[2], v.d[3]};
             } else {
                 GatherPiece v;
                 __builtin_memcpy(&v, src, 16);
@@ -258,9 +275,28 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
                 char *b = buf + (u & 1) * (32 * PITCH);
+                if constexpr (NARROW && !ALIGNED) {
+                    if (__builtin_amdgcn_ballot_w64(R[u].pad >> 8 != 0)) {       // (the last rows of X only)
+#pragma unroll
+                        for (int i = 0; i < LI; ++i) {
+                            const u32x4 f = R[u].rx[i];
+                            unsigned __int128 x = (unsigned __int128)f[0] | (unsigned __int128)f[1] << 32 |
+                                                  (unsigned __int128)f[2] << 64 | (unsigned __int128)f[3] << 96;
+                            x >>= 16 * ((R[u].pad >> (8 + 4 * i)) & 15u);
+                            R[u].rx[i] = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
+                        }
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < LI; ++i) {
                     const u32x4 v = (R[u].pad >> i) & 1u ? u32x4{0u, 0u, 0u, 0u} : R[u].rx[i];
+                    if constexpr (WATCH) {
+                        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                        for (int d = 0; d < 4; ++d)
+                            largest = __builtin_bit_cast(unsigned int, __builtin_elementwise_max(__builtin_bit_cast(u16x2, largest),
+                                                                                                 __builtin_bit_cast(u16x2, v[d] & exps[d])));
+                    }
                     *reinterpret_cast<u32x4 *>(b + wr_off + i * (RPI * PITCH)) = v;
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -293,7 +329,22 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
                 if (n + e < p.N) dst[e] = v[e];
         }
     };
+    auto put_exact = [&](int q) {
+        const int64_t n = n0 + q * 16 + 4 * (lane >> 4);
+        if (orow < 0 || n >= p.N) return;
+        float v[4];
+        exact_row<BF16 ? GRIM_BF16 : GRIM_F16, 4>(*exact, X, p.N, p.ldx, (int64_t)t * 16 + (lane & 15), n, v);
+        put(q, f32x4{v[0], v[1], v[2], v[3]});
+    };
+    bool met = false;                            // this wave fetched an infinity or NaN
+    if constexpr (WATCH)
+        met = __builtin_amdgcn_ballot_w64((largest & 0xffffu) == (kExponents & 0xffffu) || (largest >> 16) == (kExponents >> 16)) != 0;
     if constexpr (SOLO) {
+        if (WATCH && met) {
+#pragma unroll 1
+            for (int q = 0; q < NT; ++q) put_exact(q);
+            return;
+        }
         // the wave owns the whole 16-row tile
 #pragma unroll
         for (int q = 0; q < NT; ++q) put(q, acc[q]);
@@ -305,9 +356,20 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
     for (int q = 0; q < NT; ++q) red[wave * RPW + q * 64 + lane] = acc[q];
+    int *mets = reinterpret_cast<int *>(lds + NWV * gather_wave_lds(NT));      // WATCH: a word per wave
+    if (WATCH && lane == 0) mets[wave] = met;
     __syncthreads();
     if (wave >= NT) return;                      // the first waves finish the sub-tiles
     const int q = wave;
+    if constexpr (WATCH) {
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) any |= mets[w];
+        if (__builtin_amdgcn_readfirstlane(any)) {
+            put_exact(q);
+            return;
+        }
+    }
     f32x4 sum = red[q * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NWV; ++w) {
@@ -318,7 +380,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 }
 
 template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT>
-__global__ void __launch_bounds__(EIGHT ? kGatherLongWaves * 64 : 256, EIGHT ? 1024 / (kGatherLongWaves * 64) : 4) bcr_spmm_gather(GatherParams p) {
+__global__ void __launch_bounds__(EIGHT ? kGatherLongWaves * 64 : 256, EIGHT ? 1024 / (kGatherLongWaves * 64) : NARROW ? 2 : 4) bcr_spmm_gather(GatherParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     gather_body<BF16, ALIGNED, NARROW, SOLO, EIGHT, NT>(p, lds, blockIdx.x, blockIdx.y);
 }
