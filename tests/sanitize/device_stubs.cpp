@@ -15,6 +15,9 @@ double wide_plan(const grim_bcr_matrix *, const void *, int64_t, int64_t, const 
 grim_status launch_spmm_gather(const grim_bcr_matrix *, const void *, int64_t, int64_t, float *, int64_t, hipStream_t, const grim_bcr_matrix *, const void *, float *) { return GRIM_ERR_DEVICE; }
 bool gather_pair_applies(const grim_bcr_matrix *, const void *, const grim_bcr_matrix *, const void *, int64_t, int64_t) { return false; }
 bool gather_applies(const grim_bcr_matrix *, const void *, int64_t, int64_t) { return false; }
+bool gather_any_applies(const grim_bcr_matrix *, const void *, int64_t, int64_t) { return false; }
+bool gather32_applies(const grim_bcr_matrix *, const void *) { return false; }
+grim_status launch_spmm_gather32(const grim_bcr_matrix *, const void *, int64_t, int64_t, float *, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
 bool gather_wave_per_strip(const grim_bcr_matrix *, int64_t, int64_t) { return false; }
 grim_status launch_conv_gather(const grim_bcr_matrix *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, int32_t, void *, int32_t, int64_t, hipStream_t, int32_t, int32_t, int64_t, int64_t, const uint32_t *, int32_t, int64_t, int64_t) { return GRIM_ERR_DEVICE; }
 uint32_t conv_plan_word(uint32_t, int32_t, int32_t, int32_t, int32_t) { return 0; }
@@ -29,6 +32,7 @@ grim_status launch_spmv_cell(int, const GemvDesc &, const GemvDesc *, int64_t, i
 grim_status rnn_seq_static_exchange(void **) { return GRIM_ERR_DEVICE; }
 bool spmv_cell_batch_ok(int64_t, int32_t, int32_t) { return false; }
 bool spmv_exact_applies(int32_t, int32_t, int32_t, int64_t) { return false; }
+bool spmv_many_strips_applies(int64_t, int64_t, int32_t, int32_t, int32_t, int64_t, int32_t, int32_t) { return false; }
 bool spmv_column_sets_ok(int64_t, int64_t, int32_t) { return false; }
 bool rnn_seq_applies(int, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t, int64_t, int64_t, int64_t, int32_t) { return false; }
 grim_status launch_rnn_seq(int, const GemvDesc &, const GemvDesc *, const int32_t *, const int32_t *, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t, int64_t, int64_t, int64_t, int32_t, int32_t, const void *, int64_t, const void *, const float *, const float *, float *, void *, int64_t, float *, int64_t, void *, int32_t *, uint32_t, hipStream_t) { return GRIM_ERR_DEVICE; }
