@@ -47,9 +47,10 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
     p.f_img_stride = f_img_stride;
     p.y_img_stride = y_img_stride;
     p.stride = stride;
-    p.hmul = stride == 2 && W % 8 == 0 ? 2 : 1;
+    p.Ho = (H + stride - 1) / stride;
     p.Wo = (W + stride - 1) / stride;
-    int64_t Nv = p.hmul == 2 ? (int64_t)((H + 1) / 2) * W : N;
+    p.Wp = (p.Wo + 7) / 8 * 8;
+    int64_t Nv = stride == 2 ? (int64_t)p.Ho * p.Wp : N;
     p.img0 = img0;
     p.pos_begin = 0;
     if (pos_end > 0) {
@@ -59,19 +60,26 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
         Nv = pos_end;
     }
     p.Nv = (int32_t)Nv;
-    p.tiles_per_img = (int32_t)((Nv - p.pos_begin + 63) / 64);
+    // 32-position tiles for maps of 14 x 14 and less, where 64-position tiles leave compute units without a workgroup, if
+    // a wave's share of a strip's steps is one batch: of three steps, or (stride 1) of six where 64-position tiles would
+    // take two batches (72 steps at 14 x 14: 12.0 -> 9.4 us; 36 steps at stride 2 onto 7 x 7: 11.9 -> 7.5)
+    const int share = (A->gather.max_steps + kConvLongWaves - 1) / kConvLongWaves;
+    const int nt = plan && pos_end <= 0 && A->gather.max_steps >= 16 && share <= (stride == 2 ? 3 : 6) &&
+                   (Nv + 31) / 32 * batch * (int64_t)A->gather.nstrips <= 256 ? 2 : 4;
+    form->batch = nt == 4 ? conv_batch(stride) : share <= 3 ? 3 : 6;
+    p.tiles_per_img = (int32_t)((Nv - p.pos_begin + nt * 16 - 1) / (nt * 16));
     if ((int64_t)p.tiles_per_img * batch > 0x7fffffff / 16) return GRIM_ERR_SHAPE;
     p.ntiles = p.tiles_per_img * batch;
     // four consecutive outputs of a row in one store: 16 bytes of fp32, 8 bytes of fp16 / bf16
     const int esz_out = odt == GRIM_F32 ? 4 : 2;
-    p.yvec = (stride == 1 && reinterpret_cast<uintptr_t>(Y) % (odt == GRIM_F32 ? 16 : 8) == 0 && ldy % 4 == 0 && N % 4 == 0 &&
+    p.yvec = (reinterpret_cast<uintptr_t>(Y) % (odt == GRIM_F32 ? 16 : 8) == 0 && ldy % 4 == 0 && (stride == 1 ? N : p.Wo) % 4 == 0 &&
               (batch == 1 || (y_img_stride * esz_out) % (odt == GRIM_F32 ? 16 : 8) == 0)) ? 4 : 1;
     // the same launch forms as the row-gathering kernel
     const bool solo = gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 4096);
     const int64_t pairs = (int64_t)p.ntiles * p.nbr;
     // long strips and few pairs: twelve waves per strip up to 256 pairs (one workgroup per compute unit), eight up to 512
     // (two per compute unit; 28 x 28 layers: 11.0 -> 9.4 us with 18 steps, 14.1 -> 13.3 us with 36)
-    const int longw = !solo && A->gather.max_steps >= 16 ? (pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 0) : 0;
+    const int longw = !solo && A->gather.max_steps >= 16 ? (nt == 2 || pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 0) : 0;
     const int64_t per_tile = solo ? (p.nbr + 3) / 4 : p.nbr;
     if (((int64_t)p.ntiles + 7) / 8 * 8 * per_tile > 0x7fffffff) return GRIM_ERR_SHAPE;
     int64_t nwg = 0;
@@ -82,7 +90,8 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
     form->longw = longw;
     form->mode = stride == 2 ? 2 : plan ? 1 : 0;
     form->nwg = nwg;
-    form->lds = (size_t)(longw ? longw : 4) * 8192 + kConvTableBytes;
+    form->nt = nt;
+    form->lds = (size_t)(longw ? longw : 4) * conv_wave_lds(nt) + kConvTableBytes;
     *out = p;
     return GRIM_OK;
 }
@@ -100,9 +109,9 @@ grim_status launch_conv_gather(const grim_bcr_matrix *A, const void *F, int32_t 
     const int longw = form.longw, mode = form.mode;
     const size_t lds = form.lds;
     const dim3 grid((unsigned)form.nwg), block(longw ? longw * 64 : 256);
-#define GRIM_CONV_M(BF, SO, EI, MO)                                                                                  \
+#define GRIM_CONV_M(BF, SO, EI, MO, NT, SB)                                                                                  \
     do {                                                                                                             \
-        auto kern = bcr_conv_gather<BF, SO, EI, MO>;                                                                 \
+        auto kern = bcr_conv_gather<BF, SO, EI, MO, NT, SB>;                                                                 \
         static std::atomic<bool> attr_done{false};                                                                   \
         if (lds > 64 * 1024 && !attr_done) {                                                                         \
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -116,10 +125,19 @@ grim_status launch_conv_gather(const grim_bcr_matrix *A, const void *F, int32_t 
     } while (0)
 #define GRIM_CONV(BF, SO, EI)                                                                                        \
     do {                                                                                                             \
-        if (mode == 0) GRIM_CONV_M(BF, SO, EI, 0); else if (mode == 1) GRIM_CONV_M(BF, SO, EI, 1); else GRIM_CONV_M(BF, SO, EI, 2); \
+        if (mode == 0) GRIM_CONV_M(BF, SO, EI, 0, 4, conv_batch(1)); else if (mode == 1) GRIM_CONV_M(BF, SO, EI, 1, 4, conv_batch(1)); \
+        else GRIM_CONV_M(BF, SO, EI, 2, 4, conv_batch(2)); \
     } while (0)
-    if (A->dtype == GRIM_BF16) { if (solo) GRIM_CONV(true, true, 0); else if (longw == 12) GRIM_CONV(true, false, 12); else if (longw == 8) GRIM_CONV(true, false, 8); else GRIM_CONV(true, false, 0); }
+#define GRIM_CONV_2(BF)                                                                                              \
+    do {                                                                                                             \
+        if (mode == 2) GRIM_CONV_M(BF, false, kConvLongWaves, 2, 2, 3);                                              \
+        else if (form.batch == 3) GRIM_CONV_M(BF, false, kConvLongWaves, 1, 2, 3);                                   \
+        else GRIM_CONV_M(BF, false, kConvLongWaves, 1, 2, 6);                                                        \
+    } while (0)
+    if (form.nt == 2) { if (A->dtype == GRIM_BF16) GRIM_CONV_2(true); else GRIM_CONV_2(false); }
+    else if (A->dtype == GRIM_BF16) { if (solo) GRIM_CONV(true, true, 0); else if (longw == 12) GRIM_CONV(true, false, 12); else if (longw == 8) GRIM_CONV(true, false, 8); else GRIM_CONV(true, false, 0); }
     else { if (solo) GRIM_CONV(false, true, 0); else if (longw == 12) GRIM_CONV(false, false, 12); else if (longw == 8) GRIM_CONV(false, false, 8); else GRIM_CONV(false, false, 0); }
+#undef GRIM_CONV_2
 #undef GRIM_CONV
 #undef GRIM_CONV_M
     return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;

@@ -44,11 +44,10 @@ struct ConvParams {
     const uint32_t *plan;
     int32_t batch, tiles_per_img;        // images; ntiles = batch * tiles_per_img
     int64_t f_img_stride, y_img_stride;  // elements between images of F and of Y
-    // stride 1: the 64 positions of a tile are output positions.  stride 2: they are positions of the INPUT grid, of
-    // which only those with even row and column are stored (output (h / 2, w / 2)); hmul = 2: the tiles walk the even
-    // rows only (needs W % 8 == 0, so that a lane's 8 positions never straddle two rows), hmul = 1: all rows
-    int32_t stride, hmul, Wo;
-    int32_t Nv;                  // positions the tiles of one image walk: (rows walked) * W (or the end of a range)
+    // The 64 positions of a tile are output positions; stride 2: of output rows padded to Wp, a multiple of 8, so that a
+    // lane's 8 positions never straddle two rows (Ho x Wo outputs; stride 1: Wp is not used)
+    int32_t stride, Ho, Wo, Wp;
+    int32_t Nv;                  // positions the tiles of one image walk: H * W, the end of a range, or Ho * Wp
     int32_t img0, pos_begin;     // first image of the launch; first position the tiles walk (a range of one image)
     XcdMap map;
 };
@@ -75,13 +74,17 @@ constexpr int kConvTableBytes = (kConvMaxTaps + 1) * 8 * 16;   // validity masks
 // The body as a function of the workgroup's number, so that another kernel can run such workgroups behind its own (the
 // wide-tile convolution does, for the positions it leaves over).  All (LONGW ? LONGW : 4) waves call it together; `lds`:
 // 8 KB per wave plus the validity table.
-template <bool BF16, bool SOLO, int LONGW, int MODE>   // LONGW: 0, or the waves that split a long strip's steps (8 or 12)
+// LONGW: 0, or the waves that split a long strip's steps (8 or 12).  NT: 16-column sub-tiles of a tile, 4 or 2.
+// SB: steps a wave has in flight (steps past its last are fetched too: no more than its share)
+constexpr int conv_batch(int stride) { return stride == 2 ? 2 : 3; }      // of a 64-position tile, as the registers allow
+constexpr int conv_wave_lds(int nt) { return nt * 2048; }      // two step buffers of 32 rows x 16 nt columns
+template <bool BF16, bool SOLO, int LONGW, int MODE, int NT = 4, int SB = conv_batch(MODE == 2 ? 2 : 1)>
 __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds, int block_x) {
     constexpr bool EIGHT = LONGW > 0;
     constexpr bool PLAN = MODE != 0, S2 = MODE == 2;
-    const int hmul = S2 ? p.hmul : 1;
-    constexpr int NT = 4, TN = 64, PITCH = 128, CPR = 8;
-    constexpr int SB = 3;                        // steps a wave has in flight
+    constexpr int TN = NT * 16, PITCH = TN * 2, CPR = 2 * NT;  // columns, bytes and 16-byte pieces of a staged row
+    constexpr int RPI = 64 / CPR, LI = 32 / RPI;               // rows per load instruction, windows per lane and step
+    constexpr int LW = S2 ? 2 : 1;               // 16-byte loads per window (stride 2: 16 elements, of which every second one counts)
     constexpr int NWV = EIGHT ? LONGW : 4;       // waves of the workgroup
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -104,7 +107,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     const int g0 = p.usteps ? t * p.usteps : p.sptr[t], nst = p.usteps ? p.usteps : p.sptr[t + 1] - g0;
     const int s_beg = SOLO ? g0 : g0 + (int)((int64_t)nst * wave / NWV);
     const int s_end = SOLO ? g0 + nst : g0 + (int)((int64_t)nst * (wave + 1) / NWV);
-    char *buf = lds + wave * 8192;
+    char *buf = lds + wave * conv_wave_lds(NT);
     // The first batch's row numbers and block descriptors are asked for before the validity table is built,
     // so that their latency runs under it.
     const int kgroup0 = lane >> 4;
@@ -122,20 +125,22 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     }
     // per (tap, piece of the tile) the 16-byte validity mask of the piece's 8 positions; entry KK
     // is all zero (padding slots).
-    u32x4 *vtab = reinterpret_cast<u32x4 *>(lds + NWV * 8192);
+    u32x4 *vtab = reinterpret_cast<u32x4 *>(lds + NWV * conv_wave_lds(NT));
     const int ph = p.kh >> 1, pw = p.kw >> 1;
-    if (tid < (p.KK + 1) * 8) {
-        const int tap = tid >> 3, cc = tid & 7;
+    if (tid < (p.KK + 1) * CPR) {
+        const int tap = tid / CPR, cc = tid % CPR;
         const int r = tap / p.kw, q = tap - r * p.kw;
         const int dr = r - ph, dq = q - pw;
         const int nb = n0 + cc * 8;
-        const int h0 = nb / p.W, w0 = nb - h0 * p.W;
+        const int rowlen = S2 ? p.Wp : p.W;
+        const int h0 = nb / rowlen, w0 = nb - h0 * rowlen;
         unsigned int m[4] = {0u, 0u, 0u, 0u};
         if (tap < p.KK) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                int h = h0 * hmul, w = w0 + j;
-                while (w >= p.W) { w -= p.W; h += hmul; }  // once at most for W >= 8 (positions past the last, of a small map: h >= H, never stored)
+                int h = S2 ? h0 * 2 : h0, w = S2 ? (w0 + j) * 2 : w0 + j;
+                if constexpr (!S2)
+                    while (w >= p.W) { w -= p.W; ++h; }    // once at most for W >= 8 (positions past the last, of a small map: h >= H, never stored)
                 const bool ok = h + dr >= 0 && h + dr < p.H && w + dq >= 0 && w + dq < p.W;
                 m[j >> 1] |= ok ? (j & 1 ? 0xffff0000u : 0x0000ffffu) : 0u;
             }
@@ -146,8 +151,8 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     if (SOLO && !active) return;                 // (no barrier follows in that form)
 
     // fetch side: lane = (row slot rs, piece c): positions n0 + 8 c .. n0 + 8 c + 7 of the tile
-    const int rs = lane >> 3, c = lane & 7;
-    const int wr_off0 = rs * PITCH + ((c ^ swizzle<CPR>(rs)) << 4);     // the swizzle does not depend on i (row i * 8 + rs)
+    const int rs = lane / CPR, c = lane % CPR;
+    const int wr_off0 = rs * PITCH + ((c ^ swizzle<CPR>(rs)) << 4);     // the swizzle does not depend on i (row i * RPI + rs: RPI is a multiple of its period)
     // multiply side (as in the row-gathering kernel)
     const int i16 = lane & 15, kgroup = lane >> 4, qd = i16 >> 2, m_row = i16;
     const unsigned int below = (1u << m_row) - 1u;
@@ -167,22 +172,20 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     const char *Fb = reinterpret_cast<const char *>(Fimg);
     const int HW = p.N, wstep = p.W - p.kw, emax = p.total - 8;
     const int centre = ph * p.W + pw;            // offset of the centre tap: window starts are relative to it
-    // element (inside a channel) of the first of the 8 positions of piece cc: the position itself, or with every
-    // second row skipped (2 * row * W + column)
+    // element (inside a channel) under the centre tap for the first of the 8 positions of piece cc
     auto pos_off = [&](int cc) {
         const int nb = n0 + cc * 8;
-        return hmul == 1 ? nb : nb + (nb / p.W) * p.W;
+        if constexpr (!S2) return nb;
+        const int h = nb / p.Wp, in = h < p.Ho ? h : p.Ho - 1;           // (a row past the last: never stored)
+        return 2 * (in * p.W + (nb - h * p.Wp));
     };
     // Stride 1: the tile's first position goes into the (uniform) window start of a k slot and a lane adds only its
     // piece's 8 c -- this split, not the sum formed per lane, is what keeps the fetch loop within its registers.
-    const int tile_pos = S2 ? pos_off(0) : n0;
+    const int tile_pos = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0)) : n0;
     const int cofs = (S2 ? pos_off(c) - tile_pos : c * 8) - (1 << 25);     // this lane's piece, and the bias of the packed form
-    const int off7 = S2 ? pos_off(7) - tile_pos : 56;                       // piece 7 relative to tile_pos
-    // Windows that start at an odd element are fetched one element early and shifted (see below), which takes the
-    // next piece to continue this one in memory: true unless rows are skipped
-    const bool use_shift = hmul == 1;
     // can a window of this tile start before the feature map or end behind it?  (only in the first / last channel)
-    const bool tile_edge = pos_off(0) < centre || pos_off(7) + 8 + centre > HW;
+    const bool tile_edge = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0) < centre || pos_off(CPR - 1) + 16 + centre > HW) != 0
+                              : pos_off(0) < centre || pos_off(CPR - 1) + 8 + centre > HW;
     for (int s = s_beg; s < s_end; s += SB) {
         const int nb = s_end - s < SB ? s_end - s : SB;
         // Lane j takes k slot j % 32 of every step of the batch: it splits the slot's row number once into
@@ -202,13 +205,13 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                 dsc[u] = desc2[(int64_t)st * 4 + kgroup];
             }
         }
-        u32x4 RX[SB][4];
+        u32x4 RX[SB][LI][LW];
         unsigned int vsel[SB];                   // per step, 8 bits per window: validity mask (the tap; KK: padding) | odd start << 7
         i16x8 PW[SB];
         unsigned int ext[SB];
         // window start of piece (u, i) for this lane, and the selector of its validity mask
         auto piece = [&](int u, int i, unsigned int &sel) {
-            const unsigned int v = (unsigned int)__shfl((int)pk[u], i * 8 + rs);
+            const unsigned int v = (unsigned int)__shfl((int)pk[u], i * RPI + rs);
             sel = v >> 27;
             return (int)(v & 0x7ffffffu) + cofs;
         };
@@ -219,7 +222,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
 #pragma unroll
             for (int u = 0; u < SB; ++u) {
                 bool is_pad;
-                int eb;                          // window start for the tile's first position (stride 2: for position 0)
+                int eb;                          // window start for the tile's first position
                 if constexpr (PLAN) {            // already split when the plan was made
                     is_pad = (int)(pk[u] >> 27) == p.KK;
                     eb = (int)(pk[u] & 0x7ffffffu) - (1 << 25) + tile_pos;
@@ -240,31 +243,39 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                 // element is therefore fetched one element early; when the step is written the lane shifts it
                 // by 16 bits and takes its last element from the next lane's first dword.  The last lane of a
                 // row piece has no such neighbour: lanes 0..31 fetch the boundary element of their k slot with
-                // one extra 2-byte load per step, handed over by a lane permute.
-                const int e7 = eb + off7;
-                bool need = use_shift && lane < 32 && !is_pad && (e7 & 1);
-                if constexpr (SAFE) need = need && e7 + 7 >= 0 && e7 + 7 < p.total;
-                ext[u] = need ? (unsigned int)Fimg[e7 + 7] : 0u;
+                // one extra 2-byte load per step, handed over by a lane permute.  (Stride 2: the window's 16 elements
+                // start at the even element below, and the even or the odd eight of them are the window.)
+                if constexpr (!S2) {
+                    const int e7 = eb + (CPR - 1) * 8;
+                    bool need = lane < 32 && !is_pad && (e7 & 1);
+                    if constexpr (SAFE) need = need && e7 + 7 >= 0 && e7 + 7 < p.total;
+                    ext[u] = need ? (unsigned int)Fimg[e7 + 7] : 0u;
+                }
             }
             bool edge_any = false;
 #pragma unroll
             for (int u = 0; u < SB; ++u) {
                 vsel[u] = 0u;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < LI; ++i) {
                     unsigned int sel;
                     const int e0 = piece(u, i, sel);
-                    const int odd = use_shift ? e0 & 1 : 0;
+                    const int odd = e0 & 1;
                     vsel[u] |= (sel | (unsigned int)odd << 7) << (8 * i);
                     int ea = e0 - odd;
                     if constexpr (SAFE) {
-                        const bool edge = e0 < 0 || e0 > emax;
+                        const bool edge = e0 < 0 || (S2 ? ea + 8 : e0) > emax;
                         edge_any |= edge;
                         ea = edge ? 0 : ea;
                     }
-                    ConvWindow wv;
-                    __builtin_memcpy(&wv, Fb + (unsigned int)(ea * 2), 16);      // byte offset below 2^31
-                    RX[u][i] = u32x4{wv.d[0], wv.d[1], wv.d[2], wv.d[3]};
+#pragma unroll
+                    for (int l = 0; l < LW; ++l) {
+                        // (byte offset below 2^31; a map of fewer than 16 elements: every window is put together below)
+                        const int el = SAFE && l > 0 && ea + 8 > emax ? 0 : ea + 8 * l;
+                        ConvWindow wv;
+                        __builtin_memcpy(&wv, Fb + (unsigned int)(el * 2), 16);
+                        RX[u][i][l] = u32x4{wv.d[0], wv.d[1], wv.d[2], wv.d[3]};
+                    }
                 }
             }
             if constexpr (SAFE) {
@@ -272,20 +283,23 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
 #pragma unroll
                     for (int u = 0; u < SB; ++u) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
+                        for (int i = 0; i < LI; ++i) {
                             unsigned int sel;
                             const int e0 = piece(u, i, sel);
-                            if (e0 < 0 || e0 > emax) {
-                                // the same eight elements the common path fetches (one early for an odd start), so
+                            if (e0 < 0 || (S2 ? (e0 & ~1) + 8 : e0) > emax) {
+                                // the same elements the common path fetches (one early for an odd start), so
                                 // that the lane's neighbours find what they expect in its first dword
-                                unsigned int d[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-                                for (int j = 0; j < 8; ++j) {
-                                    const int e = e0 - (use_shift ? e0 & 1 : 0) + j;
-                                    const unsigned int v = e >= 0 && e < p.total ? Fimg[e] : 0u;
-                                    d[j >> 1] |= v << ((j & 1) * 16);
+                                for (int l = 0; l < LW; ++l) {
+                                    unsigned int d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                                    for (int j = 0; j < 8; ++j) {
+                                        const int e = (e0 & ~1) + 8 * l + j;
+                                        const unsigned int v = e >= 0 && e < p.total ? Fimg[e] : 0u;
+                                        d[j >> 1] |= v << ((j & 1) * 16);
+                                    }
+                                    RX[u][i][l] = u32x4{d[0], d[1], d[2], d[3]};
                                 }
-                                RX[u][i] = u32x4{d[0], d[1], d[2], d[3]};
                             }
                         }
                     }
@@ -303,22 +317,31 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
-                char *b = buf + (u & 1) * 4096;
+                char *b = buf + (u & 1) * (32 * PITCH);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < LI; ++i) {
                     const unsigned int sel = (vsel[u] >> (8 * i)) & 0xffu;
-                    const u32x4 vm = vtab[(sel & 0x7fu) * 8 + c];
-                    const unsigned int sh = (sel >> 7) * 16u;             // 16: the window starts one element into the fetch
-                    // the dword after the lane's four: the next lane's first one, or the boundary element
-                    const unsigned int w0 = RX[u][i][0];
-                    const unsigned int nxt = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)w0, 0x101 /* row_shl:1 */, 0xf, 0xf, true);
-                    const unsigned int bnd = (unsigned int)__shfl((int)ext[u], i * 8 + rs);
-                    const unsigned int w4 = c == 7 ? bnd : nxt;
-                    const u32x4 v = {__builtin_amdgcn_alignbit(RX[u][i][1], w0, sh) & vm[0],
-                                     __builtin_amdgcn_alignbit(RX[u][i][2], RX[u][i][1], sh) & vm[1],
-                                     __builtin_amdgcn_alignbit(RX[u][i][3], RX[u][i][2], sh) & vm[2],
-                                     __builtin_amdgcn_alignbit(w4, RX[u][i][3], sh) & vm[3]};
-                    *reinterpret_cast<u32x4 *>(b + wr_off0 + i * 8 * PITCH) = v;
+                    const u32x4 vm = vtab[(sel & 0x7fu) * CPR + c];
+                    u32x4 v;
+                    if constexpr (S2) {
+                        const unsigned int pick = sel >> 7 ? 0x07060302u : 0x05040100u;       // odd or even halves of two dwords
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) {
+                            const u32x4 &f = RX[u][i][d >> 1];
+                            v[d] = __builtin_amdgcn_perm(f[2 * d % 4 + 1], f[2 * d % 4], pick) & vm[d];
+                        }
+                    } else {
+                        const u32x4 &f = RX[u][i][0];
+                        const unsigned int sh = (sel >> 7) * 16u;         // 16: the window starts one element into the fetch
+                        // the dword after the lane's four: the next lane's first one, or the boundary element
+                        const unsigned int w0 = f[0];
+                        const unsigned int nxt = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)w0, 0x101 /* row_shl:1 */, 0xf, 0xf, true);
+                        const unsigned int bnd = (unsigned int)__shfl((int)ext[u], i * RPI + rs);
+                        const unsigned int w4 = c == CPR - 1 ? bnd : nxt;
+                        v = u32x4{__builtin_amdgcn_alignbit(f[1], w0, sh) & vm[0], __builtin_amdgcn_alignbit(f[2], f[1], sh) & vm[1],
+                                  __builtin_amdgcn_alignbit(f[3], f[2], sh) & vm[2], __builtin_amdgcn_alignbit(w4, f[3], sh) & vm[3]};
+                    }
+                    *reinterpret_cast<u32x4 *>(b + wr_off0 + i * RPI * PITCH) = v;
                 }
                 __builtin_amdgcn_wave_barrier();
                 // The 16-byte chunk of sub-tile q is (2 q + cl) ^ swizzle = (cl ^ swizzle) ^ 2 q: the eight
@@ -326,7 +349,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                 // holding all eight in registers across the loop (they would not fit and spill).
                 unsigned int a0 = tr0, a1 = tr1;
                 asm volatile("" : "+v"(a0), "+v"(a1));
-                const unsigned int sb = buf_lds + (u & 1) * 4096;
+                const unsigned int sb = buf_lds + (u & 1) * (32 * PITCH);
 #pragma unroll
                 for (int q = 0; q < NT; ++q) {
                     const i16x4 lo = lds_tr_read_at(sb + (a0 ^ (unsigned int)(q << 5)));
@@ -358,17 +381,12 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
             sum[e] += b;
             if (p.relu) sum[e] = sum[e] > 0.f ? sum[e] : 0.f;     // NaN stays NaN
         }
-        const int left = (int)(p.Nv - n);            // below 4 only in the one tile of a map of fewer than 64 positions
+        // how many of the four are outputs, and where the first goes
+        int left = (int)(p.Nv - n);                  // below 4 only in the one tile of a map of fewer than 64 positions
         if constexpr (S2) {
-            // positions of the input grid: the ones with even row and column are outputs
-            int hv = (int)(n / p.W), w = (int)(n - (int64_t)hv * p.W);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int h = hv * hmul;
-                if (e < left && !(h & 1) && !(w & 1)) store_one(row * p.ldy + (int64_t)(h >> 1) * p.Wo + (w >> 1), sum[e]);
-                if (++w == p.W) { w = 0; ++hv; }
-            }
-            return;
+            const int h = (int)n / p.Wp, w = (int)n - h * p.Wp;
+            left = h < p.Ho ? p.Wo - w : 0;
+            n = (int64_t)h * p.Wo + w;
         }
         const bool vec = p.yvec == 4 && (n & 3) == 0;
         if (p.odt == GRIM_F32) {
@@ -412,29 +430,29 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     // the waves' partial tiles go through their step buffers; the tables behind them stay intact
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
-    for (int q = 0; q < NT; ++q) red[wave * 512 + q * 64 + lane] = acc[q];
+    for (int q = 0; q < NT; ++q) red[wave * (conv_wave_lds(NT) / 16) + q * 64 + lane] = acc[q];
     __syncthreads();
-    if (EIGHT && wave >= NT) return;             // the first four waves finish the four sub-tiles
+    if (wave >= NT) return;                      // the first waves finish the sub-tiles
     const int q = wave;
     f32x4 sum = red[q * 64 + lane];
 #pragma unroll
     for (int w = 1; w < NWV; ++w) {
-        const f32x4 v = red[w * 512 + q * 64 + lane];
+        const f32x4 v = red[w * (conv_wave_lds(NT) / 16) + q * 64 + lane];
         sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
     }
     if (row >= 0) finish(row, n0 + q * 16 + 4 * (lane >> 4), sum);
 }
 
-template <bool BF16, bool SOLO, int LONGW, int MODE>
-__global__ void __launch_bounds__(LONGW ? LONGW * 64 : 256, LONGW ? 1024 / (LONGW * 64) : 4) bcr_conv_gather(ConvParams p) {
+template <bool BF16, bool SOLO, int LONGW, int MODE, int NT, int SB>
+__global__ void __launch_bounds__(LONGW ? LONGW * 64 : 256, LONGW ? 1024 / (LONGW * 64) : MODE == 2 ? 3 : 4) bcr_conv_gather(ConvParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    conv_gather_body<BF16, SOLO, LONGW, MODE>(p, lds, blockIdx.x);
+    conv_gather_body<BF16, SOLO, LONGW, MODE, NT, SB>(p, lds, blockIdx.x);
 }
 
 // which form of the kernel a launch takes, its workgroups and workgroup memory
 struct ConvForm {
     bool solo;
-    int longw, mode;
+    int longw, mode, nt, batch;      // batch: steps in flight
     int64_t nwg;
     size_t lds;
 };

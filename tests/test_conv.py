@@ -613,3 +613,34 @@ def test_conv_refusals():
     assert e.value.name == "GRIM_ERR_UNSUPPORTED"
     torch.cuda.synchronize()
     assert (Y == 5.0).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("H,W,kh,kw,stride,B,cols,pad", [
+    (13, 11, 3, 3, 2, 2, 16, 1),      # stride 2, 32-position tiles: output rows of 6 padded to 8, odd image strides
+    (14, 14, 3, 3, 2, 1, 16, 0),      # 7 x 7 outputs
+    (1, 9, 3, 3, 2, 1, 16, 0),        # one output row; windows that reach past the map in the first and last channel
+    (30, 16, 3, 3, 2, 1, 16, 0),      # rows of 8 outputs: no padding, 16-byte stores
+    (14, 14, 3, 3, 1, 1, 16, 0),      # stride 1, 32-position tiles: a batch of three steps per wave
+    (9, 11, 3, 3, 1, 2, 32, 3),       # ... of six
+    (3, 5, 5, 5, 1, 1, 32, 0),        # a map smaller than a tile
+    (2, 3, 1, 3, 2, 1, 16, 0),        # fewer than 16 elements per channel
+])
+def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, cols, pad):
+    """Strips of 16 steps and more on small maps (32-position tiles), and output rows of stride 2 padded to pieces."""
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload, TOL
+    M, Cin = 48, 32 * 9 * 4 // (kh * kw) // 32 * 32
+    K = Cin * kh * kw
+    mask = gen.random_mask(M, K, 16, 32, (0, 4, 16), (cols,), seed=790 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=791)
+    F = gen.normal_activations(Cin, B * H * W, dtype, seed=792, relu=True).reshape(Cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    bias = (0.05 * np.random.default_rng(793).standard_normal(M)).astype(np.float32)
+    Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
+    Yref = np.maximum(conv_ref.conv2d(Wm, F64, kh, kw, stride) + bias[None, :, None, None], 0.0)
+    S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, stride) + np.abs(bias)[None, :, None, None]
+    Y = _run_plan(g, pack_workload(g, Wt, dtype, mask), F, dtype, M, kh, kw, stride, bias=bias, relu=True, pad=pad)
+    assert np.isfinite(Y).all()
+    assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
+    assert np.abs(Y - Yref).max() <= TOL[dtype] * np.abs(Yref).max()
