@@ -158,21 +158,15 @@ void build_mma_layout(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_rows_opt, 
 }
 
 // ---- derived layout: row-gathering SpMM ----------------------------------------------------
-void build_gather_layout(grim_bcr_matrix *A) {
-    GatherLayout &L = A->gather;
-    L = GatherLayout();
-    // Block heights that divide 16 or are multiples of 16 map onto 16-row MFMA tiles: stored rows
-    // (stored strip p, local row r) are numbered p * BR + r and cut into runs of 16.
-    if (A->dtype == GRIM_F32 || A->K > 0x7fffffff || A->M > 0x7fffffff) return;
-    if (!(16 % A->BR == 0 || A->BR % 16 == 0)) return;
+// The steps of the 16-row runs u0 .. u1 - 1, numbered from zero.
+struct GatherChunk {
+    std::vector<int64_t> steps;           // per run
+    std::vector<uint32_t> rows, desc;
+    std::vector<unsigned char> payload;
+    int64_t nsteps = 0, xrows = 0;
+};
+bool build_gather_runs(const grim_bcr_matrix *A, int64_t u0, int64_t u1, GatherChunk &C) {
     const uint16_t *w = reinterpret_cast<const uint16_t *>(A->weights.data());
-    const int64_t nss = (A->M + 15) / 16;                 // 16-row strips of the stored order
-    L.nstrips = nss;
-    L.sptr.assign((size_t)nss + 1, 0);
-    L.out_row.assign((size_t)nss * 16, -1);
-    for (int64_t p = 0; p < A->nbr; ++p)
-        for (int32_t r = 0; r < A->BR; ++r)
-            L.out_row[(size_t)(p * A->BR + r)] = (int32_t)((int64_t)A->strip_order[p] * A->BR + r);
     // A group is the next eight distinct columns that any row of the run keeps, whichever strip and block they belong to:
     // the strips of a run of small blocks meet in shared columns, and a block that keeps a number of columns that is not
     // a multiple of eight leaves no padding behind.
@@ -190,34 +184,36 @@ void build_gather_layout(grim_bcr_matrix *A) {
         if (slots == 0) return true;
         const size_t gi = (size_t)ngroups++, step = gi / 4, g = gi % 4;
         if (g == 0) {
-            if ((uint64_t)L.nsteps >= 0x7fffffffu) return false;
-            ++L.nsteps;
-            L.rows.resize((step + 1) * 32, 0xffffffffu);
-            L.desc.resize((step + 1) * 8, 0u);
+            if ((uint64_t)C.nsteps >= 0x7fffffffu) return false;
+            ++C.nsteps;
+            C.rows.resize((step + 1) * 32, 0xffffffffu);
+            C.desc.resize((step + 1) * 8, 0u);
         }
-        const size_t pl0 = L.payload.size();
+        const size_t pl0 = C.payload.size();
         if (pl0 / 16 + 16 > 0xffffffffu) return false;
-        for (uint32_t j = 0; j < slots; ++j) L.rows[step * 32 + (size_t)j * 4 + g] = cols[j];
-        L.desc[step * 8 + g * 2] = rowmask;
-        L.desc[step * 8 + g * 2 + 1] = (uint32_t)(pl0 / 16);
-        L.payload.resize(pl0 + (size_t)__builtin_popcount(rowmask) * 16);
-        unsigned char *dst = L.payload.data() + pl0;
+        for (uint32_t j = 0; j < slots; ++j) C.rows[step * 32 + (size_t)j * 4 + g] = cols[j];
+        C.desc[step * 8 + g * 2] = rowmask;
+        C.desc[step * 8 + g * 2 + 1] = (uint32_t)(pl0 / 16);
+        C.payload.resize(pl0 + (size_t)__builtin_popcount(rowmask) * 16);
+        unsigned char *dst = C.payload.data() + pl0;
         for (int32_t r = 0; r < 16; ++r)
             if ((rowmask >> r) & 1u) { std::memcpy(dst, dense[r], 16); dst += 16; }
-        L.xrows += slots;
+        C.xrows += slots;
         std::memset(dense, 0, sizeof(dense));
         rowmask = slots = 0;
         return true;
     };
     std::memset(dense, 0, sizeof(dense));
     // (an estimate, so that the arrays grow once: every group full)
-    const size_t steps_about = A->BR >= 16 ? A->col_idx.size() * (size_t)(A->BR / 16) / 32 + (size_t)nss : A->col_idx.size() / 32 + (size_t)nss;
-    L.rows.reserve(steps_about * 32);
-    L.desc.reserve(steps_about * 8);
-    L.payload.reserve(A->weights.size() * 5 / 4);
-    for (int64_t u = 0; u < nss; ++u) {
-        L.sptr[(size_t)u] = (int32_t)L.nsteps;
-        ngroups = L.nsteps * 4;                                              // a run starts with a step of its own
+    const int64_t nss = (A->M + 15) / 16;
+    const size_t share = (size_t)((nss + u1 - u0 - 1) / (u1 - u0));
+    const size_t steps_about = (A->BR >= 16 ? A->col_idx.size() * (size_t)(A->BR / 16) : A->col_idx.size()) / 32 / share + (size_t)(u1 - u0);
+    C.rows.reserve(steps_about * 32);
+    C.desc.reserve(steps_about * 8);
+    C.payload.reserve(A->weights.size() / share * 5 / 4);
+    for (int64_t u = u0; u < u1; ++u) {
+        C.steps.push_back(-C.nsteps);
+        ngroups = C.nsteps * 4;                                              // a run starts with a step of its own
         const int64_t row0 = u * 16, row1 = std::min<int64_t>(A->M, row0 + 16);
         const int64_t p0 = row0 / A->BR, np = (row1 - 1) / A->BR - p0 + 1;   // stored strips that overlap this run
         if (np == 1) {
@@ -239,10 +235,11 @@ void build_gather_layout(grim_bcr_matrix *A) {
                     }
                     slots += (uint32_t)n;
                     j += n;
-                    if (slots == 8 && !flush_group()) { L = GatherLayout(); return; }
+                    if (slots == 8 && !flush_group()) return false;
                 }
             }
-            if (!flush_group()) { L = GatherLayout(); return; }
+            if (!flush_group()) return false;
+            C.steps.back() += C.nsteps;
             continue;
         }
         for (int64_t c = 0; c < A->nbc; ++c) {
@@ -273,17 +270,79 @@ void build_gather_layout(grim_bcr_matrix *A) {
                     }
                 }
                 cols[slots++] = (uint32_t)(c * A->BC + col);
-                if (slots == 8 && !flush_group()) { L = GatherLayout(); return; }
+                if (slots == 8 && !flush_group()) return false;
             }
         }
-        if (!flush_group()) { L = GatherLayout(); return; }
+        if (!flush_group()) return false;
+        C.steps.back() += C.nsteps;
     }
+    return true;
+}
+
+void build_gather_layout(grim_bcr_matrix *A) {
+    GatherLayout &L = A->gather;
+    L = GatherLayout();
+    // Block heights that divide 16 or are multiples of 16 map onto 16-row MFMA tiles: stored rows
+    // (stored strip p, local row r) are numbered p * BR + r and cut into runs of 16.
+    if (A->dtype == GRIM_F32 || A->K > 0x7fffffff || A->M > 0x7fffffff) return;
+    if (!(16 % A->BR == 0 || A->BR % 16 == 0)) return;
+    const int64_t nss = (A->M + 15) / 16;                 // 16-row strips of the stored order
+    L.nstrips = nss;
+    L.sptr.assign((size_t)nss + 1, 0);
+    L.out_row.assign((size_t)nss * 16, -1);
+    for (int64_t p = 0; p < A->nbr; ++p)
+        for (int32_t r = 0; r < A->BR; ++r)
+            L.out_row[(size_t)(p * A->BR + r)] = (int32_t)((int64_t)A->strip_order[p] * A->BR + r);
+    // Runs are independent of one another: with enough to write, in four parts side by side (4096 x 4096 of mixed rates:
+    // the whole pack 20 -> 12 ms)
+    const int64_t parts = A->nnz >= 32 * 1024 && nss >= 8 ? 4 : 1;
+    std::vector<GatherChunk> chunk((size_t)parts);
+    std::vector<std::future<bool>> done((size_t)parts);
+    auto build = [&](int64_t i) { return build_gather_runs(A, nss * i / parts, nss * (i + 1) / parts, chunk[(size_t)i]); };
+    for (int64_t i = 1; i < parts; ++i) {
+        try {
+            done[(size_t)i] = std::async(std::launch::async, build, i);
+        } catch (const std::system_error &) {           // no thread to be had
+        }
+    }
+    bool ok = true;
+    std::exception_ptr failed;
+    for (int64_t i = 0; i < parts; ++i) {               // (every thread is waited for before anything it writes goes away)
+        try {
+            ok = (done[(size_t)i].valid() ? done[(size_t)i].get() : build(i)) && ok;
+        } catch (...) {
+            failed = std::current_exception();
+        }
+    }
+    if (failed) std::rethrow_exception(failed);
+    int64_t nsteps = 0;
+    size_t payload = 0;
+    for (const GatherChunk &C : chunk) { nsteps += C.nsteps; payload += C.payload.size(); L.xrows += C.xrows; }
+    if (!ok || nsteps > 0x7fffffff || payload / 16 > 0xffffffffu) { L = GatherLayout(); return; }
+    L.nsteps = nsteps;
+    if (parts == 1) {
+        L.rows = std::move(chunk[0].rows); L.desc = std::move(chunk[0].desc); L.payload = std::move(chunk[0].payload);
+    } else {
+        L.rows.reserve((size_t)nsteps * 32);
+        L.desc.reserve((size_t)nsteps * 8);
+        L.payload.reserve(payload);
+        for (GatherChunk &C : chunk) {
+            const uint32_t at = (uint32_t)(L.payload.size() / 16);
+            for (size_t i = 1; i < C.desc.size(); i += 2) C.desc[i] += at;
+            L.rows.insert(L.rows.end(), C.rows.begin(), C.rows.end());
+            L.desc.insert(L.desc.end(), C.desc.begin(), C.desc.end());
+            L.payload.insert(L.payload.end(), C.payload.begin(), C.payload.end());
+        }
+    }
+    int64_t at = 0, u = 0;
+    for (const GatherChunk &C : chunk)
+        for (int64_t n : C.steps) { L.sptr[(size_t)u++] = (int32_t)at; at += n; }
     L.sptr[(size_t)nss] = (int32_t)L.nsteps;
     L.usteps = nss > 0 ? L.sptr[1] - L.sptr[0] : 0;
-    for (int64_t u = 0; u < nss && L.usteps > 0; ++u)
+    for (u = 0; u < nss && L.usteps > 0; ++u)
         if (L.sptr[(size_t)u + 1] - L.sptr[(size_t)u] != L.usteps) L.usteps = 0;
     L.max_steps = 0;
-    for (int64_t u = 0; u < nss; ++u) L.max_steps = std::max<int32_t>(L.max_steps, L.sptr[(size_t)u + 1] - L.sptr[(size_t)u]);
+    for (u = 0; u < nss; ++u) L.max_steps = std::max<int32_t>(L.max_steps, L.sptr[(size_t)u + 1] - L.sptr[(size_t)u]);
     L.present = true;
 }
 
