@@ -1,0 +1,289 @@
+// Planned convolution with 64 rows of the matrix to a workgroup (Section 3.1: CONV = filter matrix x im2col matrix;
+// Section 4.5: rows of that matrix whose weights are all pruned are skipped; Section 4.4: a formed row is reused by all
+// kept rows).
+#include "conv_gather_kernel.hpp"
+
+namespace grim {
+
+// The fetch of bcr_conv_gather -- windows of the feature map at any alignment, shifted, masked and parked in LDS -- costs a
+// wave far more than the multiplies that follow, and the 16-row runs of a matrix cut into small blocks fetch nearly the same
+// rows over and over: four runs of 4 x 16 blocks that keep 4 of 16 columns name 2.7 rows for every distinct one, four of
+// 8 x 16 or 16 x 16 blocks about 1.9.  Here the steps belong to runs of 64 rows (a layout the plan holds) and feed four
+// 16-row multiplies each.  Bound by the latency of a step's fetch over the two waves a SIMD holds (three steps in flight
+// spill; two asked for as a batch, without the rolling requests below, take 18.4 us where this takes 15.9: 256 channels,
+// 3 x 3, four 28 x 28 maps in 4 x 16 blocks, 25.0 on 16-row runs).
+//
+// Workgroup = (tile of 64 positions, 64-row run), its waves split the run's steps.  64 accumulators and two steps in
+// flight leave two waves per SIMD, so a wave covers its own latencies: a step's windows are asked for D steps ahead, into
+// the registers of the step that was just parked, its weights likewise after that step's multiplies, and its slot words and
+// descriptors D steps before that.
+template <bool BF16, bool S2, int NWV>
+__global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvParams p) {
+    constexpr int R = kConvTallRuns, NT = 4, TN = 64, PITCH = 128, CPR = 8, LI = 4;
+    constexpr int LW = S2 ? 2 : 1;               // 16-byte loads per window
+    constexpr int D = 2;                         // steps in flight
+    constexpr int WAVE_LDS = R * NT * 1024;      // D step buffers of 4 KB, later the partial tiles
+    static_assert(D * 32 * PITCH <= WAVE_LDS, "step buffers fit");
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tile, t;
+    if (!xcd_map_at(p.map, blockIdx.x, p.ntiles, &tile, &t) || t >= p.nbr) return;
+    const int img = __builtin_amdgcn_readfirstlane(tile / p.tiles_per_img);
+    tile = __builtin_amdgcn_readfirstlane(tile - img * p.tiles_per_img);
+    const unsigned short *Fimg = p.F + (int64_t)img * p.f_img_stride;
+    int n0 = tile * TN;
+    if (n0 + TN > p.Nv) n0 = p.Nv - TN;          // ragged last tile: overlap the neighbour
+    n0 = n0 < 0 ? 0 : n0;                        // fewer than 64 positions: one tile, its columns past them never stored
+    const int g0 = p.usteps ? t * p.usteps : p.sptr[t], nst = p.usteps ? p.usteps : p.sptr[t + 1] - g0;
+    const int s_beg = g0 + (int)((int64_t)nst * wave / NWV), s_end = g0 + (int)((int64_t)nst * (wave + 1) / NWV);
+    char *buf = lds + wave * WAVE_LDS;
+
+    const int kgroup = lane >> 4, i16 = lane & 15;
+    const uint2 *desc2 = reinterpret_cast<const uint2 *>(p.desc);
+    const i16x8 *pay = reinterpret_cast<const i16x8 *>(p.payload);
+    // a step's slot word for k slot lane % 32 and the descriptors of this lane's group (past the last step: the last)
+    struct Header { unsigned int pk; uint2 d[R]; };
+    auto ask_header = [&](Header &h, int st) {
+        st = st < s_end ? st : s_end - 1;
+        st = st < 0 ? 0 : st;
+        h.pk = p.plan[(int64_t)st * 32 + (lane & 7) * 4 + ((lane >> 3) & 3)];
+#pragma unroll
+        for (int m = 0; m < R; ++m) h.d[m] = desc2[((int64_t)st * R + m) * 4 + kgroup];
+    };
+    Header hd[D];
+#pragma unroll
+    for (int u = 0; u < D; ++u) ask_header(hd[u], s_beg + u);
+    u32x4 *vtab = reinterpret_cast<u32x4 *>(lds + NWV * WAVE_LDS);
+    for (int e = tid; e < (p.KK + 1) * CPR; e += NWV * 64) vtab[e] = conv_piece_mask<S2>(p, e / CPR, n0 + e % CPR * 8);
+    __syncthreads();
+
+    const int rs = lane >> 3, c = lane & 7;
+    const int wr_off = rs * PITCH + ((c ^ swizzle<CPR>(rs)) << 4);
+    const unsigned int below = (1u << i16) - 1u;
+    const int qd = i16 >> 2, ncolb = (4 * (i16 & 3)) * 2, cl = ncolb >> 4, within = ncolb & 15;
+    const int r0 = kgroup * 8 + qd, r1 = r0 + 4;
+    const unsigned int buf_lds = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)buf;
+    const unsigned int tr0 = buf_lds + r0 * PITCH + within + ((cl ^ swizzle<CPR>(r0)) << 4);
+    const unsigned int tr1 = buf_lds + r1 * PITCH + within + ((cl ^ swizzle<CPR>(r1)) << 4);
+
+    const char *Fb = reinterpret_cast<const char *>(Fimg);
+    const int emax = p.total - 8, centre = (p.kh >> 1) * p.W + (p.kw >> 1);
+    auto pos_off = [&](int cc) {                 // as in bcr_conv_gather
+        const int nb = n0 + cc * 8;
+        if constexpr (!S2) return nb;
+        const int h = nb / p.Wp, in = h < p.Ho ? h : p.Ho - 1;
+        return 2 * (in * p.W + (nb - h * p.Wp));
+    };
+    const int tile_pos = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0)) : n0;
+    const int cofs = (S2 ? pos_off(c) - tile_pos : c * 8) - (1 << 25);
+    const bool tile_edge = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0) < centre || pos_off(CPR - 1) + 16 + centre > p.N) != 0
+                              : pos_off(0) < centre || pos_off(CPR - 1) + 8 + centre > p.N;
+
+    f32x4 acc[R][NT];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) acc[m][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 XW[D][LI * LW];
+    unsigned int xsel[D], xext[D];               // xsel: 8 bits per window: tap (KK: padding) | odd start << 7
+    i16x8 PW[D][R];
+
+    // the windows of a step (see bcr_conv_gather: an odd start is fetched one element early, and the element behind a row
+    // piece's last window comes with one extra load; SAFE: for tiles at the map's edge)
+    auto fetch_rows = [&](int u, unsigned int word, auto safe_tag) {
+        constexpr bool SAFE = decltype(safe_tag)::value;
+        const unsigned int pk = word + (unsigned int)tile_pos;               // (the start has 27 bits, never reached)
+        if constexpr (!S2) {
+            const int e7 = (int)(pk & 0x7ffffffu) - (1 << 25) + (CPR - 1) * 8;
+            bool need = lane < 32 && (int)(word >> 27) != p.KK && (e7 & 1);
+            if constexpr (SAFE) need = need && e7 + 7 >= 0 && e7 + 7 < p.total;
+            xext[u] = need ? (unsigned int)Fimg[e7 + 7] : 0u;
+        }
+        xsel[u] = 0u;
+        int off[LI * LW];                        // SAFE: elements the load was moved by to stay inside the map
+        bool moved = false;
+#pragma unroll
+        for (int i = 0; i < LI; ++i) {
+            const unsigned int v = (unsigned int)__shfl((int)pk, i * 8 + rs);
+            const int e0 = (int)(v & 0x7ffffffu) + cofs, odd = e0 & 1;
+            xsel[u] |= (v >> 27 | (unsigned int)odd << 7) << (8 * i);
+#pragma unroll
+            for (int l = 0; l < LW; ++l) {
+                int ea = e0 - odd + 8 * l;
+                if constexpr (SAFE) {
+                    const int ec = ea < 0 ? 0 : ea > emax ? emax : ea;
+                    off[i * LW + l] = ea - ec;
+                    moved |= ea != ec;
+                    ea = ec;
+                }
+                ConvWindow wv;
+                __builtin_memcpy(&wv, Fb + (unsigned int)(ea * 2), 16);
+                XW[u][i * LW + l] = u32x4{wv.d[0], wv.d[1], wv.d[2], wv.d[3]};
+            }
+        }
+        if constexpr (SAFE) {
+            if (__builtin_amdgcn_ballot_w64(moved)) {        // (first or last channel; what lies outside the map is masked)
+#pragma unroll
+                for (int i = 0; i < LI * LW; ++i) {
+                    const u32x4 f = XW[u][i];
+                    unsigned __int128 x = (unsigned __int128)f[0] | (unsigned __int128)f[1] << 32 |
+                                          (unsigned __int128)f[2] << 64 | (unsigned __int128)f[3] << 96;
+                    const int d = off[i];
+                    x = d >= 8 || d <= -8 ? (unsigned __int128)0 : d > 0 ? x >> (16 * d) : x << (16 * -d);
+                    XW[u][i] = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
+                }
+            }
+        }
+    };
+    auto fetch_weights = [&](i16x8 (&w)[R], const Header &h) {
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            const bool kept = (h.d[m].x >> i16) & 1u;
+            const i16x8 wv = pay[h.d[m].y + (kept ? __builtin_popcount(h.d[m].x & below) : 0)];
+            w[m] = kept ? wv : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        }
+    };
+    auto park = [&](int u) {
+        char *b = buf + u * (32 * PITCH);
+#pragma unroll
+        for (int i = 0; i < LI; ++i) {
+            const unsigned int sel = (xsel[u] >> (8 * i)) & 0xffu;
+            const u32x4 vm = vtab[(sel & 0x7fu) * CPR + c];
+            u32x4 v;
+            if constexpr (S2) {
+                const unsigned int pick = sel >> 7 ? 0x07060302u : 0x05040100u;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const u32x4 f = d < 2 ? XW[u][i * LW] : XW[u][i * LW + LW - 1];
+                    v[d] = __builtin_amdgcn_perm(d % 2 ? f[3] : f[1], d % 2 ? f[2] : f[0], pick) & vm[d];
+                }
+            } else {
+                const u32x4 &f = XW[u][i * LW];
+                const unsigned int sh = (sel >> 7) * 16u, w0 = f[0];
+                const unsigned int nxt = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)w0, 0x101 /* row_shl:1 */, 0xf, 0xf, true);
+                const unsigned int bnd = (unsigned int)__shfl((int)xext[u], i * 8 + rs);
+                const unsigned int w4 = c == CPR - 1 ? bnd : nxt;
+                v = u32x4{__builtin_amdgcn_alignbit(f[1], w0, sh) & vm[0], __builtin_amdgcn_alignbit(f[2], f[1], sh) & vm[1],
+                          __builtin_amdgcn_alignbit(f[3], f[2], sh) & vm[2], __builtin_amdgcn_alignbit(w4, f[3], sh) & vm[3]};
+            }
+            *reinterpret_cast<u32x4 *>(b + wr_off + i * 8 * PITCH) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto multiply = [&](int u, const i16x8 (&w)[R]) {
+        unsigned int a0 = tr0 + u * (32 * PITCH), a1 = tr1 + u * (32 * PITCH);
+        asm volatile("" : "+v"(a0), "+v"(a1));
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const i16x4 lo = lds_tr_read_at(a0 ^ (unsigned int)(q << 5)), hi = lds_tr_read_at(a1 ^ (unsigned int)(q << 5));
+            const i16x8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+            for (int m = 0; m < R; ++m) acc[m][q] = mfma16<BF16>(x, w[m], acc[m][q]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto walk = [&](auto safe_tag) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            fetch_rows(u, hd[u].pk, safe_tag);
+            fetch_weights(PW[u], hd[u]);
+            ask_header(hd[u], s_beg + D + u);
+        }
+        int s = s_beg;
+        for (; s + 2 * D <= s_end; s += D) {     // no condition on any load in here: a wait then counts the younger ones
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                park(u);
+                fetch_rows(u, hd[u].pk, safe_tag);
+                multiply(u, PW[u]);
+                fetch_weights(PW[u], hd[u]);
+                ask_header(hd[u], s + 2 * D + u);
+            }
+        }
+        const int left = s_end - s;              // below 2 D
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            if (u < left) {
+                park(u);
+                if (D + u < left) fetch_rows(u, hd[u].pk, safe_tag);
+                multiply(u, PW[u]);
+                if (D + u < left) fetch_weights(PW[u], hd[u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < D - 1; ++u) {
+            if (D + u < left) {
+                park(u);
+                multiply(u, PW[u]);
+            }
+        }
+    };
+    if (s_beg < s_end) {
+        if (tile_edge) walk(std::true_type{}); else walk(std::false_type{});
+    }
+
+    // the waves' partial tiles, added in wave order; the waves finish the (16-row run, sub-tile) pairs in turn
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) red[wave * (WAVE_LDS / 16) + (m * NT + q) * 64 + lane] = acc[m][q];
+    __syncthreads();
+    for (int i = wave; i < R * NT; i += NWV) {
+        const int64_t row = p.out_row[((int64_t)t * R + i / NT) * 16 + i16];
+        f32x4 sum = red[i * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < NWV; ++w) {
+            const f32x4 v = red[w * (WAVE_LDS / 16) + i * 64 + lane];
+            sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
+        }
+        if (row >= 0) conv_finish<S2>(p, img, row, n0 + i % NT * 16 + 4 * kgroup, sum);
+    }
+}
+
+grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
+                             int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
+                             int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride) {
+    ConvParams p;
+    ConvForm form;
+    const grim_status st = conv_gather_setup(A, F, Cin, H, W, kh, kw, bias, relu, Y, odt, ldy, batch, stride, f_img_stride,
+                                             y_img_stride, L.d_rows, 0, 0, 0, &p, &form);
+    if (st != GRIM_OK) return st;
+    p.sptr = L.d_sptr;
+    p.out_row = L.d_out_row;
+    p.desc = L.d_desc;
+    p.payload = L.d_payload;
+    p.nbr = (int32_t)L.nstrips;
+    p.usteps = L.usteps;
+    p.tiles_per_img = (p.Nv + 63) / 64;
+    p.ntiles = p.tiles_per_img * batch;
+    int64_t nwg = 0;
+    p.map = xcd_map(p.ntiles, p.nbr, &nwg);
+    if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
+    const int waves = (int64_t)p.ntiles * p.nbr <= 256 ? 8 : 4;
+    const size_t lds = (size_t)waves * kConvTallRuns * 4096 + kConvTableBytes;
+#define GRIM_TALL(BF, S2, NW)                                                                                        \
+    do {                                                                                                             \
+        auto kern = bcr_conv_tall<BF, S2, NW>;                                                                       \
+        static std::atomic<bool> attr_done{false};   /* raising a kernel's LDS limit is needed once per process */  \
+        if (lds > 64 * 1024 && !attr_done) {                                                                         \
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                    160 * 1024) != hipSuccess) {                                                     \
+                (void)hipGetLastError();                                                                             \
+                return GRIM_ERR_DEVICE;                                                                              \
+            }                                                                                                        \
+            attr_done = true;                                                                                        \
+        }                                                                                                            \
+        hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NW * 64), lds, stream, p);                                \
+    } while (0)
+#define GRIM_TALL_DT(BF)                                                                                             \
+    if (stride == 2) { if (waves == 8) GRIM_TALL(BF, true, 8); else GRIM_TALL(BF, true, 4); }                        \
+    else { if (waves == 8) GRIM_TALL(BF, false, 8); else GRIM_TALL(BF, false, 4); }
+    if (A->dtype == GRIM_BF16) { GRIM_TALL_DT(true) } else { GRIM_TALL_DT(false) }
+#undef GRIM_TALL_DT
+#undef GRIM_TALL
+    return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
+}
+
+}  // namespace grim

@@ -158,27 +158,30 @@ void build_mma_layout(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_rows_opt, 
 }
 
 // ---- derived layout: row-gathering SpMM ----------------------------------------------------
-// The steps of the 16-row runs u0 .. u1 - 1, numbered from zero.
+// The steps of the runs u0 .. u1 - 1 of 16 R rows, numbered from zero.
 struct GatherChunk {
     std::vector<int64_t> steps;           // per run
     std::vector<uint32_t> rows, desc;
     std::vector<unsigned char> payload;
     int64_t nsteps = 0, xrows = 0;
 };
+template <int R>
 bool build_gather_runs(const grim_bcr_matrix *A, int64_t u0, int64_t u1, GatherChunk &C) {
+    constexpr int HEIGHT = 16 * R;
     const uint16_t *w = reinterpret_cast<const uint16_t *>(A->weights.data());
     // A group is the next eight distinct columns that any row of the run keeps, whichever strip and block they belong to:
     // the strips of a run of small blocks meet in shared columns, and a block that keeps a number of columns that is not
     // a multiple of eight leaves no padding behind.
-    const int64_t most_strips = std::max<int64_t>(1, 16 / A->BR);        // strips that reach into a run
+    const int64_t most_strips = std::max<int64_t>(1, HEIGHT / A->BR);        // strips that reach into a run
     struct Part {                                                        // a strip's block in the current column block
         int64_t base;                                                    // its first row, from the run's first
         const uint16_t *q0, *q1, *col, *end, *w;                         // kept rows; next and last kept column; its weights
         int32_t kc;
     };
     std::vector<Part> parts((size_t)most_strips);
-    uint16_t dense[16][8];                                               // weights of the group being filled
-    uint32_t rowmask = 0, slots = 0, cols[8];
+    uint16_t dense[HEIGHT][8];                                            // weights of the group being filled
+    uint64_t rowmask = 0;
+    uint32_t slots = 0, cols[8];
     int64_t ngroups = 0;
     auto flush_group = [&]() {
         if (slots == 0) return true;
@@ -187,34 +190,38 @@ bool build_gather_runs(const grim_bcr_matrix *A, int64_t u0, int64_t u1, GatherC
             if ((uint64_t)C.nsteps >= 0x7fffffffu) return false;
             ++C.nsteps;
             C.rows.resize((step + 1) * 32, 0xffffffffu);
-            C.desc.resize((step + 1) * 8, 0u);
+            C.desc.resize((step + 1) * 8 * R, 0u);
         }
         const size_t pl0 = C.payload.size();
-        if (pl0 / 16 + 16 > 0xffffffffu) return false;
+        if (pl0 / 16 + HEIGHT > 0xffffffffu) return false;
         for (uint32_t j = 0; j < slots; ++j) C.rows[step * 32 + (size_t)j * 4 + g] = cols[j];
-        C.desc[step * 8 + g * 2] = rowmask;
-        C.desc[step * 8 + g * 2 + 1] = (uint32_t)(pl0 / 16);
-        C.payload.resize(pl0 + (size_t)__builtin_popcount(rowmask) * 16);
+        C.payload.resize(pl0 + (size_t)__builtin_popcountll(rowmask) * 16);
         unsigned char *dst = C.payload.data() + pl0;
-        for (int32_t r = 0; r < 16; ++r)
-            if ((rowmask >> r) & 1u) { std::memcpy(dst, dense[r], 16); dst += 16; }
+        for (int32_t m = 0; m < R; ++m) {
+            const uint32_t mask = (uint32_t)(rowmask >> (16 * m)) & 0xffffu;
+            C.desc[(step * R + m) * 8 + g * 2] = mask;
+            C.desc[(step * R + m) * 8 + g * 2 + 1] = mask ? (uint32_t)((dst - C.payload.data()) / 16) : 0u;
+            for (int32_t r = 0; r < 16; ++r)
+                if ((mask >> r) & 1u) { std::memcpy(dst, dense[16 * m + r], 16); dst += 16; }
+        }
         C.xrows += slots;
         std::memset(dense, 0, sizeof(dense));
-        rowmask = slots = 0;
+        rowmask = 0;
+        slots = 0;
         return true;
     };
     std::memset(dense, 0, sizeof(dense));
     // (an estimate, so that the arrays grow once: every group full)
-    const int64_t nss = (A->M + 15) / 16;
+    const int64_t nss = (A->M + HEIGHT - 1) / HEIGHT;
     const size_t share = (size_t)((nss + u1 - u0 - 1) / (u1 - u0));
-    const size_t steps_about = (A->BR >= 16 ? A->col_idx.size() * (size_t)(A->BR / 16) : A->col_idx.size()) / 32 / share + (size_t)(u1 - u0);
+    const size_t steps_about = (A->BR >= 16 ? A->col_idx.size() * (size_t)std::max(1, A->BR / HEIGHT) : A->col_idx.size()) / 32 / share + (size_t)(u1 - u0);
     C.rows.reserve(steps_about * 32);
-    C.desc.reserve(steps_about * 8);
+    C.desc.reserve(steps_about * 8 * R);
     C.payload.reserve(A->weights.size() / share * 5 / 4);
     for (int64_t u = u0; u < u1; ++u) {
         C.steps.push_back(-C.nsteps);
         ngroups = C.nsteps * 4;                                              // a run starts with a step of its own
-        const int64_t row0 = u * 16, row1 = std::min<int64_t>(A->M, row0 + 16);
+        const int64_t row0 = u * HEIGHT, row1 = std::min<int64_t>(A->M, row0 + HEIGHT);
         const int64_t p0 = row0 / A->BR, np = (row1 - 1) / A->BR - p0 + 1;   // stored strips that overlap this run
         if (np == 1) {
             // one strip: a block's columns in turn, as many at a time as the group has room for
@@ -230,7 +237,7 @@ bool build_gather_runs(const grim_bcr_matrix *A, int64_t u0, int64_t u1, GatherC
                     for (int32_t e = 0; e < n; ++e) cols[slots + e] = (uint32_t)(c * A->BC + A->col_idx[c0 + j + e]);
                     for (int32_t q = q0; q < q1; ++q) {
                         const int64_t r = base + A->row_idx[q] - row0;
-                        rowmask |= 1u << r;
+                        rowmask |= uint64_t(1) << r;
                         std::memcpy(&dense[r][slots], w + A->blk_ptr[t] + (int64_t)(q - A->row_ptr[t]) * kc + j, (size_t)n * 2);
                     }
                     slots += (uint32_t)n;
@@ -265,7 +272,7 @@ bool build_gather_runs(const grim_bcr_matrix *A, int64_t u0, int64_t u1, GatherC
                     const uint16_t *pw = pt.w++;                             // the column's weights, kc apart
                     ++pt.col;
                     for (const uint16_t *q = pt.q0; q < pt.q1; ++q, pw += pt.kc) {
-                        rowmask |= 1u << (pt.base + *q);
+                        rowmask |= uint64_t(1) << (pt.base + *q);
                         dense[pt.base + *q][slots] = *pw;
                     }
                 }
@@ -279,17 +286,20 @@ bool build_gather_runs(const grim_bcr_matrix *A, int64_t u0, int64_t u1, GatherC
     return true;
 }
 
-void build_gather_layout(grim_bcr_matrix *A) {
-    GatherLayout &L = A->gather;
+// The layout of runs of 16 R rows (R = 1: the matrix's own; R = 4: a convolution plan's, desc and masks per 16 rows).
+// L is left empty where the matrix does not have it.
+template <int R>
+void build_gather_layout(const grim_bcr_matrix *A, GatherLayout &L) {
+    constexpr int HEIGHT = 16 * R;
     L = GatherLayout();
     // Block heights that divide 16 or are multiples of 16 map onto 16-row MFMA tiles: stored rows
     // (stored strip p, local row r) are numbered p * BR + r and cut into runs of 16.
     if (A->dtype == GRIM_F32 || A->K > 0x7fffffff || A->M > 0x7fffffff) return;
-    if (!(16 % A->BR == 0 || A->BR % 16 == 0)) return;
-    const int64_t nss = (A->M + 15) / 16;                 // 16-row strips of the stored order
+    if (!(HEIGHT % A->BR == 0 || A->BR % HEIGHT == 0)) return;
+    const int64_t nss = (A->M + HEIGHT - 1) / HEIGHT;     // runs of the stored order
     L.nstrips = nss;
     L.sptr.assign((size_t)nss + 1, 0);
-    L.out_row.assign((size_t)nss * 16, -1);
+    L.out_row.assign((size_t)nss * HEIGHT, -1);
     for (int64_t p = 0; p < A->nbr; ++p)
         for (int32_t r = 0; r < A->BR; ++r)
             L.out_row[(size_t)(p * A->BR + r)] = (int32_t)((int64_t)A->strip_order[p] * A->BR + r);
@@ -298,7 +308,7 @@ void build_gather_layout(grim_bcr_matrix *A) {
     const int64_t parts = A->nnz >= 32 * 1024 && nss >= 8 ? 4 : 1;
     std::vector<GatherChunk> chunk((size_t)parts);
     std::vector<std::future<bool>> done((size_t)parts);
-    auto build = [&](int64_t i) { return build_gather_runs(A, nss * i / parts, nss * (i + 1) / parts, chunk[(size_t)i]); };
+    auto build = [&](int64_t i) { return build_gather_runs<R>(A, nss * i / parts, nss * (i + 1) / parts, chunk[(size_t)i]); };
     for (int64_t i = 1; i < parts; ++i) {
         try {
             done[(size_t)i] = std::async(std::launch::async, build, i);
@@ -324,7 +334,7 @@ void build_gather_layout(grim_bcr_matrix *A) {
         L.rows = std::move(chunk[0].rows); L.desc = std::move(chunk[0].desc); L.payload = std::move(chunk[0].payload);
     } else {
         L.rows.reserve((size_t)nsteps * 32);
-        L.desc.reserve((size_t)nsteps * 8);
+        L.desc.reserve((size_t)nsteps * 8 * R);
         L.payload.reserve(payload);
         for (GatherChunk &C : chunk) {
             const uint32_t at = (uint32_t)(L.payload.size() / 16);
@@ -692,7 +702,7 @@ grim_status grim_bcr_pack(const void *W_host, grim_dtype dt, int64_t M, int64_t 
                 } catch (const std::system_error &) {       // no thread to be had
                 }
             }
-            build_gather_layout(A);
+            build_gather_layout<1>(A, A->gather);
             build_gather32_layout(A);
             build_gemv_layout(A);
             if (f1.valid()) f1.get(); else mma();
@@ -1134,7 +1144,48 @@ struct grim_bcr_conv_plan {
     int32_t Cin = 0, H = 0, W = 0, kh = 0, kw = 0, stride = 1;
     int device = -1;
     uint32_t *d_words = nullptr;
+    // the rows cut into runs of 64 (where that leaves fewer rows of the im2col matrix to form); `rows` are window-start words
+    GatherLayout tall;
+    void *d_tall = nullptr;          // one allocation for all of it
 };
+
+// Steps of 64-row runs against steps of the 16-row runs they replace: worth their own layout from here on
+static bool tall_pays(const GatherLayout &tall, const GatherLayout &own) {
+    return tall.present && tall.nsteps * 4 <= own.nsteps * 3;
+}
+
+static grim_status add_tall_layout(grim_bcr_conv_plan *P) {
+    const grim_bcr_matrix *A = P->A;
+    GatherLayout &L = P->tall;
+    try {
+        if (A->M > 16) build_gather_layout<kConvTallRuns>(A, L);
+        if (!tall_pays(L, A->gather)) { L = GatherLayout(); return GRIM_OK; }
+        for (uint32_t &r : L.rows) r = conv_plan_word(r, P->H, P->W, P->kh, P->kw);
+    } catch (const std::bad_alloc &) {
+        return GRIM_ERR_ALLOC;
+    }
+    Slab s;
+    auto bytes = [](const auto &v) { return v.size() * sizeof(v[0]); };
+    const size_t o_s = s.add(bytes(L.sptr)), o_q = s.add(bytes(L.out_row)), o_r = s.add(bytes(L.rows)), o_d = s.add(bytes(L.desc)),
+                 o_p = s.add(bytes(L.payload) + 16);
+    char *base = nullptr;
+    if (hipMalloc(reinterpret_cast<void **>(&base), s.total + 256) != hipSuccess) { (void)hipGetLastError(); return GRIM_ERR_ALLOC; }
+    auto put = [&](size_t off, const void *src, size_t n) { return n == 0 || hipMemcpy(base + off, src, n, hipMemcpyHostToDevice) == hipSuccess; };
+    if (!(put(o_s, L.sptr.data(), bytes(L.sptr)) && put(o_q, L.out_row.data(), bytes(L.out_row)) && put(o_r, L.rows.data(), bytes(L.rows)) &&
+          put(o_d, L.desc.data(), bytes(L.desc)) && put(o_p, L.payload.data(), bytes(L.payload)))) {
+        (void)hipGetLastError();
+        (void)hipFree(base);
+        return GRIM_ERR_DEVICE;
+    }
+    P->d_tall = base;
+    L.d_sptr = reinterpret_cast<int32_t *>(base + o_s);
+    L.d_out_row = reinterpret_cast<int32_t *>(base + o_q);
+    L.d_rows = reinterpret_cast<uint32_t *>(base + o_r);
+    L.d_desc = reinterpret_cast<uint32_t *>(base + o_d);
+    L.d_payload = reinterpret_cast<unsigned char *>(base + o_p);
+    L.rows = {}; L.desc = {}; L.payload = {}; L.out_row = {};            // (the host copies have done their work)
+    return GRIM_OK;
+}
 
 grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw,
                                       int32_t stride, grim_bcr_conv_plan **out) {
@@ -1147,6 +1198,7 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
     if (hipGetDevice(&dev) != hipSuccess || dev != A->device) { (void)hipGetLastError(); return GRIM_ERR_DEVICE; }
     if (!A->gather.present || kh * kw > 31 || (int64_t)Cin * H * W > (int64_t(1) << 26) || A->gather.rows.empty())
         return GRIM_ERR_UNSUPPORTED;
+    grim_status st = GRIM_OK;
     std::vector<uint32_t> words(A->gather.rows.size());
     for (size_t i = 0; i < words.size(); ++i) words[i] = conv_plan_word(A->gather.rows[i], H, W, kh, kw);
     std::unique_ptr<grim_bcr_conv_plan> P(new (std::nothrow) grim_bcr_conv_plan);
@@ -1160,6 +1212,11 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
         return GRIM_ERR_DEVICE;
     }
     P->d_words = static_cast<uint32_t *>(ptr);
+    st = add_tall_layout(P.get());
+    if (st != GRIM_OK) {
+        (void)hipFree(ptr);
+        return st;
+    }
     *out = P.release();
     return GRIM_OK;
 }
@@ -1167,7 +1224,24 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
 void grim_bcr_conv_plan_free(grim_bcr_conv_plan *P) {
     if (!P) return;
     if (P->d_words) (void)hipFree(P->d_words);
+    if (P->d_tall) (void)hipFree(P->d_tall);
     delete P;
+}
+
+// Runs of 64 rows pay once there are about as many (tile, run) pairs as two thirds of the compute units -- below that the
+// four times as many 16-row workgroups are quicker (512 channels on one 28 x 28 map, 104 pairs: 13.6 -> 19.4 us) -- and, at
+// stride 1, for strips of some length that name each row nearly twice and more.  Measured, 16-row against 64-row runs:
+// 256 channels, 3 x 3, four 28 x 28 maps in 16 x 32 / 8 x 16 / 16 x 16 / 32 x 32 / 4 x 16 blocks (rows named 1.5 / 1.9 /
+// 2.1 / 2.7 / 2.7 times) 13.5 -> 13.7, 18.0 -> 16.1, 17.9 -> 16.5, 18.2 -> 13.8, 25.7 -> 16.4 us; 128 channels on eight
+// 56 x 56 maps 21.9 -> 26.1, 31.8 -> 29.3, 32.2 -> 29.5, 32.1 -> 26.5, 41.5 -> 30.2; 1 x 1 with 8 steps 7.1 -> 7.5.  At
+// stride 2, where a window is two loads, 128 -> 256 channels from four 56 x 56 maps 13.5 -> 11.1, 17.2 -> 12.6, 17.0 ->
+// 12.6, 17.2 -> 12.0, 21.9 -> 12.6 and its 1 x 1 shortcut of four steps 7.6 -> 6.8.
+static bool conv_on_tall_runs(const grim_bcr_conv_plan *P, int32_t batch) {
+    if (!P->tall.present) return false;
+    const int64_t Ho = (P->H + 1) / 2, Wp = ((P->W + 1) / 2 + 7) / 8 * 8;
+    const int64_t positions = P->stride == 2 ? Ho * Wp : (int64_t)P->H * P->W;
+    if ((positions + 63) / 64 * batch * P->tall.nstrips < 160) return false;
+    return P->stride == 2 || (P->tall.max_steps >= 12 && P->tall.nsteps * 7 <= P->A->gather.nsteps * 4);
 }
 
 grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev, int32_t batch, int64_t f_image_stride,
@@ -1186,6 +1260,12 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev,
         const grim_status st = launch_conv_wide(P->A, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, batch, f_image_stride, bias_dev,
                                                 relu ? 1 : 0, out_dev, (int32_t)out_dt, ldo, out_image_stride,
                                                 static_cast<hipStream_t>(hip_stream));
+        if (st != GRIM_ERR_UNSUPPORTED) return st;
+    }
+    if (conv_on_tall_runs(P, batch)) {
+        const grim_status st = launch_conv_tall(P->A, P->tall, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
+                                                (int32_t)out_dt, ldo, static_cast<hipStream_t>(hip_stream), batch, P->stride, f_image_stride,
+                                                out_image_stride);
         if (st != GRIM_ERR_UNSUPPORTED) return st;
     }
     return launch_conv_gather(P->A, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev, (int32_t)out_dt,

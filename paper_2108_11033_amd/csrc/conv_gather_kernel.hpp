@@ -60,6 +60,77 @@ __device__ __forceinline__ unsigned short conv_f32_to_bf16(float f) {
     return (unsigned short)(u >> 16);
 }
 
+// which of the 8 positions from nb on see a pixel of the image under a kernel tap, as a 16-byte mask; tap KK: none
+template <bool S2>
+__device__ __forceinline__ u32x4 conv_piece_mask(const ConvParams &p, int tap, int nb) {
+    const int r = tap / p.kw, q = tap - r * p.kw;
+    const int dr = r - (p.kh >> 1), dq = q - (p.kw >> 1);
+    const int rowlen = S2 ? p.Wp : p.W;
+    const int h0 = nb / rowlen, w0 = nb - h0 * rowlen;
+    unsigned int m[4] = {0u, 0u, 0u, 0u};
+    if (tap < p.KK) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            int h = S2 ? h0 * 2 : h0, w = S2 ? (w0 + j) * 2 : w0 + j;
+            if constexpr (!S2)
+                while (w >= p.W) { w -= p.W; ++h; }    // once at most for W >= 8 (positions past the last, of a small map: h >= H, never stored)
+            const bool ok = h + dr >= 0 && h + dr < p.H && w + dq >= 0 && w + dq < p.W;
+            m[j >> 1] |= ok ? (j & 1 ? 0xffff0000u : 0x0000ffffu) : 0u;
+        }
+    }
+    return u32x4{m[0], m[1], m[2], m[3]};
+}
+
+// epilogue of a layer for four consecutive positions n .. n + 3 of output channel `row`: bias, rectifier,
+// rounding to the next layer's element type
+template <bool S2>
+__device__ __forceinline__ void conv_finish(const ConvParams &p, int img, int64_t row, int64_t n, f32x4 sum) {
+    char *Yimg = static_cast<char *>(p.Y) + (int64_t)img * p.y_img_stride * (p.odt == GRIM_F32 ? 4 : 2);
+    const float b = p.bias ? p.bias[row] : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        sum[e] += b;
+        if (p.relu) sum[e] = sum[e] > 0.f ? sum[e] : 0.f;     // NaN stays NaN
+    }
+    // how many of the four are outputs, and where the first goes
+    int left = (int)(p.Nv - n);                  // below 4 only in the one tile of a map of fewer than 64 positions
+    if constexpr (S2) {
+        const int h = (int)n / p.Wp, w = (int)n - h * p.Wp;
+        left = h < p.Ho ? p.Wo - w : 0;
+        n = (int64_t)h * p.Wo + w;
+    }
+    const bool vec = p.yvec == 4 && (n & 3) == 0;
+    if (p.odt == GRIM_F32) {
+        float *dst = reinterpret_cast<float *>(Yimg) + row * p.ldy + n;
+        if (vec && left >= 4) {
+            *reinterpret_cast<f32x4 *>(dst) = sum;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < left) dst[e] = sum[e];
+        }
+    } else {
+        unsigned short h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (p.odt == GRIM_F16) {
+                const _Float16 v = (_Float16)sum[e];
+                __builtin_memcpy(&h[e], &v, 2);
+            } else {
+                h[e] = conv_f32_to_bf16(sum[e]);
+            }
+        }
+        unsigned short *dst = reinterpret_cast<unsigned short *>(Yimg) + row * p.ldy + n;
+        if (vec && left >= 4) {
+            *reinterpret_cast<uint2 *>(dst) = uint2{(unsigned int)h[0] | ((unsigned int)h[1] << 16), (unsigned int)h[2] | ((unsigned int)h[3] << 16)};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < left) dst[e] = h[e];
+        }
+    }
+}
+
 struct __attribute__((packed, aligned(4))) ConvWindow {
     unsigned int d[4];
 };
@@ -129,23 +200,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     const int ph = p.kh >> 1, pw = p.kw >> 1;
     if (tid < (p.KK + 1) * CPR) {
         const int tap = tid / CPR, cc = tid % CPR;
-        const int r = tap / p.kw, q = tap - r * p.kw;
-        const int dr = r - ph, dq = q - pw;
-        const int nb = n0 + cc * 8;
-        const int rowlen = S2 ? p.Wp : p.W;
-        const int h0 = nb / rowlen, w0 = nb - h0 * rowlen;
-        unsigned int m[4] = {0u, 0u, 0u, 0u};
-        if (tap < p.KK) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                int h = S2 ? h0 * 2 : h0, w = S2 ? (w0 + j) * 2 : w0 + j;
-                if constexpr (!S2)
-                    while (w >= p.W) { w -= p.W; ++h; }    // once at most for W >= 8 (positions past the last, of a small map: h >= H, never stored)
-                const bool ok = h + dr >= 0 && h + dr < p.H && w + dq >= 0 && w + dq < p.W;
-                m[j >> 1] |= ok ? (j & 1 ? 0xffff0000u : 0x0000ffffu) : 0u;
-            }
-        }
-        vtab[tid] = u32x4{m[0], m[1], m[2], m[3]};
+        vtab[tid] = conv_piece_mask<S2>(p, tap, n0 + cc * 8);
     }
     __syncthreads();
     if (SOLO && !active) return;                 // (no barrier follows in that form)
@@ -362,68 +417,11 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
         }
     }
 
-    // epilogue of a layer for four consecutive positions n .. n + 3 of output channel `row`: bias, rectifier,
-    // rounding to the next layer's element type
-    char *Yimg = static_cast<char *>(p.Y) + (int64_t)img * p.y_img_stride * (p.odt == GRIM_F32 ? 4 : 2);
-    auto store_one = [&](int64_t at, float v) {
-        if (p.odt == GRIM_F32) {
-            reinterpret_cast<float *>(Yimg)[at] = v;
-        } else if (p.odt == GRIM_F16) {
-            reinterpret_cast<_Float16 *>(Yimg)[at] = (_Float16)v;
-        } else {
-            reinterpret_cast<unsigned short *>(Yimg)[at] = conv_f32_to_bf16(v);
-        }
-    };
-    auto finish = [&](int64_t row, int64_t n, f32x4 sum) {
-        const float b = p.bias ? p.bias[row] : 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sum[e] += b;
-            if (p.relu) sum[e] = sum[e] > 0.f ? sum[e] : 0.f;     // NaN stays NaN
-        }
-        // how many of the four are outputs, and where the first goes
-        int left = (int)(p.Nv - n);                  // below 4 only in the one tile of a map of fewer than 64 positions
-        if constexpr (S2) {
-            const int h = (int)n / p.Wp, w = (int)n - h * p.Wp;
-            left = h < p.Ho ? p.Wo - w : 0;
-            n = (int64_t)h * p.Wo + w;
-        }
-        const bool vec = p.yvec == 4 && (n & 3) == 0;
-        if (p.odt == GRIM_F32) {
-            float *dst = reinterpret_cast<float *>(Yimg) + row * p.ldy + n;
-            if (vec && left >= 4) {
-                *reinterpret_cast<f32x4 *>(dst) = sum;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (e < left) dst[e] = sum[e];
-            }
-        } else {
-            unsigned short h[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (p.odt == GRIM_F16) {
-                    const _Float16 v = (_Float16)sum[e];
-                    __builtin_memcpy(&h[e], &v, 2);
-                } else {
-                    h[e] = conv_f32_to_bf16(sum[e]);
-                }
-            }
-            unsigned short *dst = reinterpret_cast<unsigned short *>(Yimg) + row * p.ldy + n;
-            if (vec && left >= 4) {
-                *reinterpret_cast<uint2 *>(dst) = uint2{(unsigned int)h[0] | ((unsigned int)h[1] << 16), (unsigned int)h[2] | ((unsigned int)h[3] << 16)};
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (e < left) dst[e] = h[e];
-            }
-        }
-    };
     const int64_t row = p.out_row[(int64_t)t * 16 + (lane & 15)];
     if constexpr (SOLO) {
         if (row >= 0) {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) finish(row, n0 + q * 16 + 4 * (lane >> 4), acc[q]);
+            for (int q = 0; q < NT; ++q) conv_finish<S2>(p, img, row, n0 + q * 16 + 4 * (lane >> 4), acc[q]);
         }
         return;
     }
@@ -440,7 +438,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
         const f32x4 v = red[w * (conv_wave_lds(NT) / 16) + q * 64 + lane];
         sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
     }
-    if (row >= 0) finish(row, n0 + q * 16 + 4 * (lane >> 4), sum);
+    if (row >= 0) conv_finish<S2>(p, img, row, n0 + q * 16 + 4 * (lane >> 4), sum);
 }
 
 template <bool BF16, bool SOLO, int LONGW, int MODE, int NT, int SB>

@@ -644,3 +644,30 @@ def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, col
     assert np.isfinite(Y).all()
     assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
     assert np.abs(Y - Yref).max() <= TOL[dtype] * np.abs(Yref).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,BC,H,W,kh,kw,stride,B,pad,cin", [
+    (96, 4, 16, 70, 75, 3, 3, 1, 1, 3, 32),      # a second 64-row run of 32 rows; odd sizes and strides; 18 steps over four waves
+    (64, 32, 32, 56, 56, 3, 3, 1, 4, 0, 96),     # one 64-row run, 196 tiles
+    (80, 16, 16, 40, 36, 3, 3, 1, 8, 0, 96),     # a run of 16 rows; strips that keep nothing
+    (256, 8, 16, 33, 47, 3, 3, 2, 4, 1, 64),     # stride 2, rows of 24 outputs
+    (128, 128, 32, 9, 9, 3, 3, 2, 48, 0, 32),    # blocks taller than a run; 5 x 5 outputs: one partly filled tile per image
+    (192, 4, 16, 40, 40, 1, 1, 2, 8, 0, 32),     # fewer steps than waves
+])
+def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pad, cin):
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload, TOL
+    K = cin * kh * kw
+    mask = gen.random_mask(M, K, BR, BC, tuple(sorted({0, BR // 2, BR})), (BC // 4, BC // 2), seed=800 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=801)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=802, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    bias = (0.05 * np.random.default_rng(803).standard_normal(M)).astype(np.float32)
+    Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
+    Yref = conv_ref.conv2d(Wm, F64, kh, kw, stride) + bias[None, :, None, None]
+    S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, stride) + np.abs(bias)[None, :, None, None]
+    Y = _run_plan(g, pack_workload(g, Wt, dtype, mask), F, dtype, M, kh, kw, stride, bias=bias, pad=pad)
+    assert np.isfinite(Y).all()
+    assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
+    assert np.abs(Y - Yref).max() <= TOL[dtype] * np.abs(Yref).max()
