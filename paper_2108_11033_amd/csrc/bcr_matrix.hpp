@@ -267,6 +267,11 @@ bool spmv_column_sets_ok(int64_t count, int64_t nbr, int32_t batch);   // column
 grim_status launch_spmv_cell(int kind, const GemvDesc &d1, const GemvDesc *d2, int64_t M, int64_t K, int32_t BR, int32_t BC,
                              int32_t dtype, int32_t ukr, int32_t ukc, const void *x, int64_t x_stride, int32_t batch, int64_t ldx,
                              float *y, int64_t y_stride, int64_t ldy, const RnnCell &cell, hipStream_t stream);
+// a recurrent step for a batch of columns in one launch on the row-gathering layout (A2: the hidden-side matrix of a GRU)
+bool rnn_gather_applies(const grim_bcr_matrix *A, const void *X, int64_t ldx, const grim_bcr_matrix *A2, const void *X2, int64_t ldx2,
+                        int64_t H, int32_t batch);
+grim_status launch_rnn_gather(const grim_bcr_matrix *A, const void *X, int64_t ldx, float *G, int64_t ldg, const grim_bcr_matrix *A2,
+                              const void *X2, int64_t ldx2, float *G2, int64_t ldg2, int32_t batch, const RnnCell &cell, hipStream_t stream);
 // a recurrent layer over a whole sequence in one launch (kind 1: LSTM, K1 = I + H; kind 2: GRU, K1 = I, K2 = H), `batch`
 // sequences side by side (1 .. kSeqMaxBatch); exch: at most 2 * batch * H words of 8 bytes; hidden sizes up to kSeqMaxH
 constexpr int64_t kSeqMaxH = 8192;

@@ -1320,6 +1320,14 @@ grim_status grim_bcr_lstm_step(const grim_bcr_matrix *A, const void *xh_dev, int
             if (st0 != GRIM_ERR_UNSUPPORTED) return st0;
         }
     }
+    if (rnn_gather_applies(A, xh_dev, ldx, nullptr, nullptr, 0, H, batch)) {
+        grim_status st0 = check_call(A, xh_dev, batch, ldx, gates_dev, ldg);
+        if (st0 != GRIM_OK) return st0;
+        if (!(h_dev && ranges_overlap(xh_dev, ((A->K - 1) * ldx + batch) * dtype_size(A->dtype), h_dev, ((H - 1) * ldh + batch) * dtype_size(A->dtype)))) {
+            RnnCell cell{nullptr, nullptr, bias_dev, nullptr, c_dev, h_dev, h32_dev, ldc, ldh, ldh32, (int32_t)H, A->dtype};
+            return launch_rnn_gather(A, xh_dev, ldx, gates_dev, ldg, nullptr, nullptr, 0, nullptr, 0, batch, cell, static_cast<hipStream_t>(hip_stream));
+        }
+    }
     grim_status st = batch <= 8 ? grim_bcr_spmv(A, xh_dev, batch, ldx, gates_dev, ldg, hip_stream)
                                 : grim_bcr_spmm(A, xh_dev, batch, ldx, gates_dev, ldg, hip_stream);
     if (st != GRIM_OK) return st;
@@ -1511,6 +1519,14 @@ grim_status grim_bcr_gru_step(const grim_bcr_matrix *Ai, const grim_bcr_matrix *
             st = launch_spmv_cell(2, di, &dh, Ai->M, Ai->K, Ai->BR, Ai->BC, Ai->dtype, Ai->gemv.uniform_kr, Ai->gemv.uniform_kc,
                                   x_dev, xd / esz, batch, ldx, gi_dev, yd / 4, ldgi, cell, static_cast<hipStream_t>(hip_stream));
             if (st != GRIM_ERR_UNSUPPORTED) return st;
+        }
+    }
+    if (rnn_gather_applies(Ai, x_dev, ldx, Ah, hin_dev, ldhin, H, batch)) {
+        const bool aliased = hout_dev && (ranges_overlap(hin_dev, ((Ah->K - 1) * ldhin + batch) * esz, hout_dev, ((H - 1) * ldhout + batch) * esz) ||
+                                          ranges_overlap(x_dev, ((Ai->K - 1) * ldx + batch) * esz, hout_dev, ((H - 1) * ldhout + batch) * esz));
+        if (!aliased) {
+            RnnCell cell{nullptr, nullptr, bias_i_dev, bias_h_dev, h32_dev, hout_dev, nullptr, ldh32, ldhout, 0, (int32_t)H, Ai->dtype};
+            return launch_rnn_gather(Ai, x_dev, ldx, gi_dev, ldgi, Ah, hin_dev, ldhin, gh_dev, ldgh, batch, cell, static_cast<hipStream_t>(hip_stream));
         }
     }
     const bool few_on_matrix_cores = ldx == ldhin && ldgi == ldgh && skinny_on_matrix_cores(Ai, x_dev, batch, ldx, 2) &&

@@ -30,6 +30,8 @@ int64_t mma_whole_rounds(const grim_bcr_matrix *, int64_t N, bool, int *, int *)
 grim_status launch_spmv(const GemvDesc *, const GemvDesc &, const GemvDesc *, int32_t, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, const void *, int64_t, int32_t, int64_t, float *, int64_t, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
 bool spmv_cell_applies(int, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t) { return false; }
 grim_status launch_spmv_cell(int, const GemvDesc &, const GemvDesc *, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, const void *, int64_t, int32_t, int64_t, float *, int64_t, int64_t, const RnnCell &, hipStream_t) { return GRIM_ERR_DEVICE; }
+bool rnn_gather_applies(const grim_bcr_matrix *, const void *, int64_t, const grim_bcr_matrix *, const void *, int64_t, int64_t, int32_t) { return false; }
+grim_status launch_rnn_gather(const grim_bcr_matrix *, const void *, int64_t, float *, int64_t, const grim_bcr_matrix *, const void *, int64_t, float *, int64_t, int32_t, const RnnCell &, hipStream_t) { return GRIM_ERR_DEVICE; }
 grim_status rnn_seq_static_exchange(void **) { return GRIM_ERR_DEVICE; }
 bool spmv_cell_batch_ok(int64_t, int32_t, int32_t) { return false; }
 bool spmv_exact_applies(int32_t, int32_t, int32_t, int64_t) { return false; }

@@ -293,3 +293,77 @@ def test_gru_step_of_several_columns_in_one_launch(dtype, H, BR, kr, kc, B, ld):
     if ld > B:
         assert (h32[:, B:] == 7.0).all() and (hout[:, B:].float() == 7.0).all()
         assert torch.isnan(gates[:, :, B:]).all()
+
+
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("H,I,BR,kr,kc,B,ld", [
+    (64, 64, 32, (0, 8, 32), (4, 12, 32), 3, 4),      # mixed rates, strips stored out of order, few columns
+    (48, 96, 16, (4, 8, 16), (0, 12, 20), 17, 17),    # two column tiles, the second of one column; odd rows
+    (32, 32, 8, (4,), (8,), 15, 16),                  # two strips per run, stored in their original order
+    (96, 32, 32, (8, 16), (4, 32), 64, 64),
+    (64, 4096, 32, (8, 16), (16, 32), 9, 9),          # more than one batch of steps per wave
+    (16, 32, 16, (4, 16), (8, 32), 1, 1),             # one column: the pieces of the last rows end behind X
+])
+@pytest.mark.parametrize("odd", [None, np.inf, np.nan])
+def test_steps_of_a_batch_on_the_matrix_cores(dtype, H, I, BR, kr, kc, B, ld, odd):
+    """LSTM and GRU steps whose products and cell run in one launch on the matrix cores; an infinity or NaN among the
+    inputs reaches the pre-activations of the gate rows that keep it and no others."""
+    from helpers import to_device, pack_workload, oracle_product, TOL
+    torch, dev, g = _gpu()
+    rng = np.random.default_rng(970)
+    stream, tdt = torch.cuda.current_stream(), _tdt(torch, dtype)
+    mats = []                                        # (mask, weights, packed, inputs) of LSTM's and the GRU's two products
+    for M, K, seed in ((4 * H, I + H, 971), (3 * H, I, 973), (3 * H, H, 975)):
+        mask = gen.random_mask(M, K, BR, 32, kr, kc, seed=seed) if K % 32 == 0 else gen.random_mask(M, K, BR, 16, kr, tuple(min(c, 16) for c in kc), seed=seed)
+        W = gen.normal_weights(M, K, dtype, seed=seed + 1)
+        X = gen.normal_activations(K, B, dtype, seed=seed + 10)
+        mats.append((mask, W, pack_workload(g, W, dtype, mask), X))
+    if odd is not None:
+        for m in mats:
+            m[3][len(m[3]) // 2, B // 2] = odd if dtype == gen.F16 else (np.array([odd], np.float32).view(np.uint32) >> 16).astype(np.uint16)[0]
+    dev_in = []
+    for mask, W, A, X in mats:
+        x = torch.full((X.shape[0], ld), 7.0, dtype=tdt, device=dev); x[:, :B] = to_device(X, dtype)
+        dev_in.append(x)
+    full = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device=dev)
+    b4, b3i, b3h = [(0.2 * rng.standard_normal(n * H)).astype(np.float32) for n in (4, 3, 3)]
+    d4, d3i, d3h = [torch.from_numpy(b).to(dev) for b in (b4, b3i, b3h)]
+    s0 = rng.standard_normal((H, B)).astype(np.float32)
+    state = lambda: torch.cat([torch.from_numpy(s0).to(dev), torch.full((H, ld - B), 7.0, device=dev)], 1).contiguous()
+    gates, gi, gh = full(4 * H, ld), full(3 * H, ld), full(3 * H, ld)
+    c, h, h32, hs, hg = state(), torch.full((H, ld), 7.0, dtype=tdt, device=dev), full(H, ld), state(), torch.full((H, ld), 7.0, dtype=tdt, device=dev)
+    g.lstm_step(mats[0][2], dev_in[0], B, ld, gates, ld, d4, c, ld, h, ld, h32, ld, stream)
+    g.gru_step(mats[1][2], mats[2][2], dev_in[1], ld, dev_in[2], ld, B, gi, ld, gh, ld, d3i, d3h, hs, ld, hg, ld, stream)
+    torch.cuda.synchronize()
+    pre = []
+    for (mask, W, A, X), G in zip(mats, (gates, gi, gh)):
+        Gh = G.cpu().numpy()
+        assert np.isnan(Gh[:, B:]).all(), "wrote outside the columns"
+        clean = X.copy()
+        if odd is not None:
+            clean[len(X) // 2, B // 2] = 0
+        ref, S = oracle_product(W, clean, dtype, mask)
+        ok = np.ones(ref.shape, dtype=bool)
+        if odd is not None:
+            cb, j = divmod(len(X) // 2, mask.BC)
+            for s in range(mask.nbr):
+                b = s * mask.nbc + cb
+                if j in mask.col_idx[mask.col_ptr[b]:mask.col_ptr[b + 1]]:
+                    ok[s * mask.BR + mask.row_idx[mask.row_ptr[b]:mask.row_ptr[b + 1]].astype(int), B // 2] = False
+            assert not np.isfinite(Gh[:, :B][~ok]).any()
+        assert (np.abs(Gh[:, :B] - ref)[ok] <= TOL[dtype] * np.maximum(S[ok], 1e-30)).all()
+        pre.append(ref)
+    sig = lambda v: 1.0 / (1.0 + np.exp(-v))
+    cols = [b for b in range(B) if odd is None or b != B // 2]
+    p4 = [pre[0][k * H:(k + 1) * H] + b4[k * H:(k + 1) * H, None] for k in range(4)]
+    c_ref = sig(p4[1]) * s0 + sig(p4[0]) * np.tanh(p4[2])
+    assert np.abs(c.cpu().numpy()[:, :B] - c_ref)[:, cols].max(initial=0) <= TOL[dtype] * max(1.0, np.abs(c_ref).max())
+    assert np.abs(h32.cpu().numpy()[:, :B] - sig(p4[3]) * np.tanh(c_ref))[:, cols].max(initial=0) <= TOL[dtype]
+    i3 = [pre[1][k * H:(k + 1) * H] + b3i[k * H:(k + 1) * H, None] for k in range(3)]
+    h3 = [pre[2][k * H:(k + 1) * H] + b3h[k * H:(k + 1) * H, None] for k in range(3)]
+    z, n = sig(i3[1] + h3[1]), np.tanh(i3[2] + sig(i3[0] + h3[0]) * h3[2])
+    h_ref = (1 - z) * n + z * s0
+    got = hs.cpu().numpy()
+    assert (got[:, B:] == 7.0).all() and (hg[:, B:].float() == 7.0).all() and (h[:, B:].float() == 7.0).all()
+    assert np.abs(got[:, :B] - h_ref)[:, cols].max(initial=0) <= 2 * TOL[dtype] * max(1.0, np.abs(h_ref).max())
+    assert np.abs(hg.float().cpu().numpy()[:, :B] - h_ref)[:, cols].max(initial=0) <= 2 * TOL[dtype] * max(1.0, np.abs(h_ref).max()) + 2.0 ** -7
