@@ -41,7 +41,7 @@ bool gather_pair_applies(const grim_bcr_matrix *A, const void *X, const grim_bcr
 
 // Parameters, grid and kernel form of a launch (see launch_spmm_gather); GRIM_ERR_UNSUPPORTED when the kernel does not apply.
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
-                         const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form) {
+                         const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form, bool may_take_small_tiles) {
     if (!gather_any_applies(A, X, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     if (A2 && !gather_pair_applies(A, X, A2, X2, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     GatherParams p;
@@ -58,7 +58,12 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     p.usteps = A->gather.usteps;
     p.exact = exact_arrays(A);
     // fewer than 64 columns: one tile of the narrowest width that holds them
-    const int nt = N > 32 ? 4 : N > 16 ? 2 : 1;
+    // Long strips and few tiles (14 x 14 maps and less): 32-column tiles, whose twice as many workgroups have twelve waves
+    // with three steps in flight -- 512 x 4608 at 147 columns 8.0 -> 5.1 us, at 64 / 196 / 256 columns 5.8 / 6.6 / 5.9 ->
+    // 4.0 / 5.2 / 4.3, 256 x 4608 in 16 x 16 blocks at 392 columns 8.5 -> 6.6 -- while every workgroup has a compute unit.
+    // Strips below 16 steps stay (256 x 1152 at 256 columns 3.8 us either way).
+    const bool small_tiles = may_take_small_tiles && N >= 64 && A->gather.max_steps >= 16 && (N + 31) / 32 * p.nbr <= 256;
+    const int nt = small_tiles ? 2 : N > 32 ? 4 : N > 16 ? 2 : 1;
     p.ntiles = (int32_t)((N + nt * 16 - 1) / (nt * 16));
     p.second = GatherSecond{p.sptr, p.out_row, p.rows, p.desc, p.payload, p.X, p.Y, p.usteps, p.K, exact_arrays(A)};
     if (A2)
@@ -72,8 +77,8 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     // last 512 columns of a 4608-row product: 10 -> 7.7 us); with 18-step strips the extra requests cost more than they
     // save (12.0 -> 12.4 us on a 2304-row product, five-step strips 15.5 -> 24 us).
     p.touch = !narrow && A->gather.max_steps >= 40 ? 1 : 0;
-    const bool solo = !narrow && gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 1536);
-    const bool eight = !solo && A->gather.max_steps >= 16 && (narrow || (int64_t)p.ntiles * p.nbr <= 256);
+    const bool solo = !narrow && !small_tiles && gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 1536);
+    const bool eight = !solo && A->gather.max_steps >= 16 && (narrow || small_tiles || (int64_t)p.ntiles * p.nbr <= 256);
     const int64_t per_tile = solo ? (p.nbr + 3) / 4 : p.nbr;
     if (((int64_t)p.ntiles + 7) / 8 * 8 * per_tile > 0x7fffffff) return GRIM_ERR_SHAPE;
     int64_t nwg = 0;
@@ -98,8 +103,9 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
     if (st != GRIM_OK) return st;
     const bool narrow = form.narrow, solo = form.solo, eight = form.eight, aligned = form.aligned;
     const int64_t nwg = form.nwg;
-    const size_t lds = (size_t)(eight ? kGatherLongWaves : 4) * gather_wave_lds(form.nt) + kGatherWatchBytes;
-    const dim3 grid((unsigned)nwg, A2 ? 2u : 1u), block(eight ? kGatherLongWaves * 64 : 256);
+    const int waves = gather_waves(narrow, eight, form.nt);
+    const size_t lds = (size_t)waves * gather_wave_lds(form.nt) + kGatherWatchBytes;
+    const dim3 grid((unsigned)nwg, A2 ? 2u : 1u), block(waves * 64);
 #define GRIM_GATHER(BF, AL, NR, SO, EI, NT)                                                                              \
     do {                                                                                                             \
         auto kern = bcr_spmm_gather<BF, AL, NR, SO, EI, NT>;                                                          \
@@ -118,6 +124,7 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
     if (narrow && form.nt == 1) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 1); else GRIM_GATHER(BF, AL, true, false, false, 1); } \
     else if (narrow && form.nt == 2) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 2); else GRIM_GATHER(BF, AL, true, false, false, 2); } \
     else if (narrow) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 4); else GRIM_GATHER(BF, AL, true, false, false, 4); } \
+    else if (form.nt == 2) GRIM_GATHER(BF, AL, false, false, true, 2);                                               \
     else if (solo) GRIM_GATHER(BF, AL, false, true, false, 4);                                                       \
     else if (eight) GRIM_GATHER(BF, AL, false, false, true, 4);                                                      \
     else GRIM_GATHER(BF, AL, false, false, false, 4);

@@ -164,7 +164,7 @@ grim_status launch_spmm_wide_with_rest(const grim_bcr_matrix *A, const void *X, 
     GatherParams gp;
     GatherForm form;
     const char *x_rest = static_cast<const char *>(X) + wide_cols * dtype_size(A->dtype);
-    st = gather_setup(A, x_rest, N - wide_cols, ldx, Y + wide_cols, ldy, nullptr, nullptr, nullptr, &gp, &form);
+    st = gather_setup(A, x_rest, N - wide_cols, ldx, Y + wide_cols, ldy, nullptr, nullptr, nullptr, &gp, &form, false);
     if (st != GRIM_OK) return st;
     if (!form.aligned || form.narrow || form.solo || !form.eight) return GRIM_ERR_UNSUPPORTED;
     if (wide_wgs + form.nwg > 0x7fffffff) return GRIM_ERR_SHAPE;

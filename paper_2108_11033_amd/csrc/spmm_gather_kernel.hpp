@@ -63,7 +63,8 @@ struct GatherForm {
     int64_t nwg;
 };
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
-                         const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form);
+                         const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form,
+                         bool may_take_small_tiles = true);
 
 // 16 bytes of X at any 2-byte alignment; four results at any 4-byte alignment (both are single accesses on this GPU)
 struct __attribute__((packed, aligned(2))) GatherPiece {
@@ -77,7 +78,7 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // products element by element before (512 x 4608 at 147 columns: 114 -> 7.7 us).
 // NARROW: N below the tile's width: one tile, whose pieces past N are fetched from column 0 and never stored.
 // NT: 16-column sub-tiles of a tile (4; 2 and 1 for products of at most 32 and 16 columns, whose pieces then take a half
-// or a quarter of the load instructions and LDS traffic of a padded 64-column tile).
+// or a quarter of the load instructions and LDS traffic of a padded 64-column tile; 2 also for long strips and few tiles).
 // SOLO: strips of a few steps only (a 3 x 3 layer of 64 channels has 5, a dense first layer 1) -- every wave takes a
 // (tile, strip) of its own, four consecutive strips per workgroup: no split of K, no partial tiles, no barrier
 // EIGHT: eight waves split a strip's steps instead of four (few workgroups, long strips: the 14 x 14 layers)
@@ -96,7 +97,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     // forms of operands that other kernels used to take, which multiply kept weights only: an infinity or NaN in X must
     // not reach the rows of the run that do not keep its column
     constexpr bool WATCH = NARROW || !ALIGNED;
-    constexpr int SB = NT == 1 ? 8 : !NARROW && WATCH && !EIGHT ? 3 : 4;      // steps a wave has in flight (as its registers allow)
+    constexpr int SB = NT == 1 ? 8 : !NARROW && (NT == 2 || (WATCH && !EIGHT)) ? 3 : 4;      // steps a wave has in flight (as its registers allow)
     static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
     // workgroup -> (tile, stored strip, or four of them for SOLO)
     const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -370,19 +371,28 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             return;
         }
     }
-    f32x4 sum = red[q * 64 + lane];
+    // (the small-tile form's twelve: three sums of four, so that more partial tiles do not mean a longer chain of roundings)
+    constexpr int CHAIN = NT == 2 && !NARROW ? 4 : NWV;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 1; w < NWV; ++w) {
-        const f32x4 v = red[w * RPW + q * 64 + lane];
-        sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
+    for (int g = 0; g < NWV; g += CHAIN) {
+        f32x4 s = red[g * RPW + q * 64 + lane];
+#pragma unroll
+        for (int w = g + 1; w < g + CHAIN; ++w) {
+            const f32x4 v = red[w * RPW + q * 64 + lane];
+            s[0] += v[0]; s[1] += v[1]; s[2] += v[2]; s[3] += v[3];
+        }
+        if (g == 0) sum = s;
+        else { sum[0] += s[0]; sum[1] += s[1]; sum[2] += s[2]; sum[3] += s[3]; }
     }
     put(q, sum);
 }
 
+constexpr int gather_waves(bool narrow, bool eight, int nt) { return !eight ? 4 : nt == 2 && !narrow ? kGatherSmallTileWaves : kGatherLongWaves; }
 template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT>
-__global__ void __launch_bounds__(EIGHT ? kGatherLongWaves * 64 : 256, EIGHT ? 1024 / (kGatherLongWaves * 64) : NARROW ? 2 : 4) bcr_spmm_gather(GatherParams p) {
+__global__ void __launch_bounds__((gather_waves(NARROW, EIGHT, NT) * 64), (EIGHT ? 2 : NARROW ? 2 : 4)) bcr_spmm_gather(GatherParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    gather_body<BF16, ALIGNED, NARROW, SOLO, EIGHT, NT>(p, lds, blockIdx.x, blockIdx.y);
+    gather_body<BF16, ALIGNED, NARROW, SOLO, EIGHT, NT, gather_waves(NARROW, EIGHT, NT)>(p, lds, blockIdx.x, blockIdx.y);
 }
 
 }  // namespace grim

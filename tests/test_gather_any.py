@@ -41,3 +41,18 @@ def test_rows_of_any_alignment_wave_per_strip(g):
     Y = run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, N)
     assert_close(Y, Yref, S, dtype, "wave per strip, odd N")
     assert np.isfinite(Y).all()
+
+
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,BC,N,ldx_pad", [(48, 16, 32, 64, 0), (48, 16, 32, 65, 0), (64, 32, 32, 96, 0), (32, 4, 16, 97, 2),
+                                               (32, 8, 16, 200, 8), (16, 16, 32, 8192, 0), (16, 16, 32, 8191, 1)])
+def test_long_strips_and_few_tiles(g, dtype, M, BR, BC, N, ldx_pad):
+    """32-column tiles with twelve waves to a strip: fewer steps than three to a wave, a few more, and several batches; the
+    last workgroup count of the form and the columns around it, aligned and odd."""
+    K = 32 * 60
+    mask = gen.random_mask(M, K, BR, BC, tuple(sorted({0, BR // 2, BR})), (BC // 4, BC // 2, BC), seed=920 + N)
+    W = gen.normal_weights(M, K, dtype, seed=921)
+    X = gen.normal_activations(K, N, dtype, seed=922)
+    Yref, S = oracle_product(W, X, dtype, mask)
+    Y = run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, N, ldx=N + ldx_pad, ldy=N + 1)
+    assert_close(Y, Yref, S, dtype, f"{dtype} {M}x{K} {BR}x{BC} N={N}")
