@@ -69,16 +69,11 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvParams p) {
 
     const char *Fb = reinterpret_cast<const char *>(Fimg);
     const int emax = p.total - 8, centre = (p.kh >> 1) * p.W + (p.kw >> 1);
-    auto pos_off = [&](int cc) {                 // as in bcr_conv_gather
-        const int nb = n0 + cc * 8;
-        if constexpr (!S2) return nb;
-        const int h = nb / p.Wp, in = h < p.Ho ? h : p.Ho - 1;
-        return 2 * (in * p.W + (nb - h * p.Wp));
-    };
+    auto pos_off = [&](int cc) { return conv_piece_start<S2>(n0 + cc * 8, p.W, p.Ho, p.Wp); };       // as in bcr_conv_gather
     const int tile_pos = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0)) : n0;
     const int cofs = (S2 ? pos_off(c) - tile_pos : c * 8) - (1 << 25);
-    const bool tile_edge = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0) < centre || pos_off(CPR - 1) + 16 + centre > p.N) != 0
-                              : pos_off(0) < centre || pos_off(CPR - 1) + 8 + centre > p.N;
+    bool tile_edge = conv_tile_at_edge<S2>(pos_off(0), pos_off(CPR - 1), centre, p.N);
+    if constexpr (S2) tile_edge = __builtin_amdgcn_readfirstlane(tile_edge) != 0;
 
     f32x4 acc[R][NT];
 #pragma unroll

@@ -1,5 +1,6 @@
 // Kernel of bcr_conv.hip as a header: the wide-tile convolution's launcher builds a kernel that runs both.
 #pragma once
+#include "conv_window.hpp"
 #include "spmm_common.hpp"
 
 namespace grim {
@@ -228,19 +229,14 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     const int HW = p.N, wstep = p.W - p.kw, emax = p.total - 8;
     const int centre = ph * p.W + pw;            // offset of the centre tap: window starts are relative to it
     // element (inside a channel) under the centre tap for the first of the 8 positions of piece cc
-    auto pos_off = [&](int cc) {
-        const int nb = n0 + cc * 8;
-        if constexpr (!S2) return nb;
-        const int h = nb / p.Wp, in = h < p.Ho ? h : p.Ho - 1;           // (a row past the last: never stored)
-        return 2 * (in * p.W + (nb - h * p.Wp));
-    };
+    auto pos_off = [&](int cc) { return conv_piece_start<S2>(n0 + cc * 8, p.W, p.Ho, p.Wp); };
     // Stride 1: the tile's first position goes into the (uniform) window start of a k slot and a lane adds only its
     // piece's 8 c -- this split, not the sum formed per lane, is what keeps the fetch loop within its registers.
     const int tile_pos = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0)) : n0;
     const int cofs = (S2 ? pos_off(c) - tile_pos : c * 8) - (1 << 25);     // this lane's piece, and the bias of the packed form
     // can a window of this tile start before the feature map or end behind it?  (only in the first / last channel)
-    const bool tile_edge = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0) < centre || pos_off(CPR - 1) + 16 + centre > HW) != 0
-                              : pos_off(0) < centre || pos_off(CPR - 1) + 8 + centre > HW;
+    bool tile_edge = conv_tile_at_edge<S2>(pos_off(0), pos_off(CPR - 1), centre, HW);
+    if constexpr (S2) tile_edge = __builtin_amdgcn_readfirstlane(tile_edge) != 0;
     for (int s = s_beg; s < s_end; s += SB) {
         const int nb = s_end - s < SB ? s_end - s : SB;
         // Lane j takes k slot j % 32 of every step of the batch: it splits the slot's row number once into

@@ -438,6 +438,8 @@ def _run_plan(g, A, F, dtype, M, kh, kw, stride, bias=None, relu=False, out_dtyp
     (32, 7, 7, 1, 1, 16, 32, 2, 3, 0),       # 1 x 1 at stride 2 (a down-sampling shortcut), fewer than 64 positions
     (4, 56, 56, 5, 5, 16, 20, 2, 1, 0),
     (24, 9, 16, 3, 1, 16, 24, 2, 2, 5),
+    (32, 1, 47, 1, 1, 16, 32, 2, 2, 1),      # 1 x 1 at stride 2 on flat maps: fewer than 64 positions in rows of 24
+    (32, 3, 33, 1, 1, 16, 32, 2, 3, 0),
 ])
 def test_conv_plan_batch_and_stride(dtype, Cin, H, W, kh, kw, BR, BC, stride, B, pad):
     import paper_2108_11033_amd as g
@@ -626,6 +628,7 @@ def test_conv_refusals():
     (9, 11, 3, 3, 1, 2, 32, 3),       # ... of six
     (3, 5, 5, 5, 1, 1, 32, 0),        # a map smaller than a tile
     (2, 3, 1, 3, 2, 1, 16, 0),        # fewer than 16 elements per channel
+    (1, 33, 1, 1, 2, 1, 16, 1),       # 1 x 1 at stride 2, one output row of 24 positions in a tile of 32
 ])
 def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, cols, pad):
     """Strips of 16 steps and more on small maps (32-position tiles), and output rows of stride 2 padded to pieces."""
@@ -655,6 +658,7 @@ def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, col
     (256, 8, 16, 33, 47, 3, 3, 2, 4, 1, 64),     # stride 2, rows of 24 outputs
     (128, 128, 32, 9, 9, 3, 3, 2, 48, 0, 32),    # blocks taller than a run; 5 x 5 outputs: one partly filled tile per image
     (192, 4, 16, 40, 40, 1, 1, 2, 8, 0, 32),     # fewer steps than waves
+    (128, 4, 16, 3, 47, 1, 1, 2, 80, 0, 64),     # flat maps at stride 2: a tile of 48 positions
 ])
 def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pad, cin):
     import paper_2108_11033_amd as g

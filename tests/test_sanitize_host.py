@@ -5,6 +5,7 @@ their decoders, the BCRC export -- is built with g++ -fsanitize=address,undefine
 kernel launchers (tests/sanitize/device_stubs.cpp), and the host-side test files run against that build in a
 child interpreter with the sanitizer runtimes preloaded.  Any out-of-bounds access, use after free or
 undefined operation in the index-building code aborts the child and fails this test."""
+import ctypes
 import os
 import subprocess
 import sys
@@ -45,3 +46,23 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     tail = (run.stdout + run.stderr)[-4000:]
     assert run.returncode == 0, tail
     assert "passed" in run.stdout and "AddressSanitizer" not in tail and "runtime error" not in tail, tail
+
+
+def test_convolution_loads_without_range_checks_stay_inside_the_map(tmp_path):
+    """Every load of every tile that the convolution kernels fetch without range checks, by their own arithmetic
+    (csrc/conv_window.hpp) built for the host: small, flat and odd maps, both strides and both tile widths."""
+    lib = str(tmp_path / "conv_windows.so")
+    res = subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2108_11033_amd", "csrc"),
+                          os.path.join(ROOT, "tests", "sanitize", "conv_windows.cpp"), "-o", lib], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    outside = ctypes.CDLL(lib).conv_loads_outside
+    outside.restype = ctypes.c_int64
+    sizes = list(range(1, 21)) + list(range(21, 131, 3)) + [33, 47, 48, 63, 64, 65, 79, 95, 111, 112, 113, 128, 129]
+    for stride in (1, 2):
+        for kh, kw in ((1, 1), (3, 3), (1, 3), (3, 1), (5, 5)):
+            for H in (1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 14, 15, 28, 57):
+                for W in sizes:
+                    for tn in (32, 64):
+                        for Cin in (1, 3):
+                            n = outside(Cin, H, W, kh, kw, stride, tn)
+                            assert n == 0, (n, dict(Cin=Cin, H=H, W=W, kh=kh, kw=kw, stride=stride, tile=tn))
