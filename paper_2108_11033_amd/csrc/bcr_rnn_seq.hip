@@ -28,6 +28,7 @@
 #include <mutex>
 
 #include "bcr_matrix.hpp"
+#include "rnn_seq_placement.hpp"
 #include "spmv_common.hpp"
 
 namespace grim {
@@ -44,7 +45,6 @@ struct SeqParams {
     int32_t K1, K2;                // LSTM: K1 = I + H; GRU: K1 = I, K2 = H
     int32_t I, H, T;
     int32_t B;                     // sequences side by side (1 .. 32), dealt to grid.y sets of workgroups
-    int32_t sets;                  // > 0: sets of workgroups, each on an XCD of its own (1-D grid); 0: grid.y is the set
     int32_t SPB, NQ;               // sequences per workgroup; pairs of them = exchange words per hidden unit
     int32_t xvec16;                // rows of xs can be copied with 16-byte loads
     const void *xs;                // T x B rows of I inputs, row t * B + b
@@ -73,8 +73,9 @@ constexpr int kSeqXVec = 4;   // 16-byte pieces of a step's inputs a thread fetc
 constexpr int kSeqPolls = 2;    // reads of an exchange word a waiting workgroup sends out at once ...
 constexpr int kSeqPollGap = 8;  // ... this many times 64 cycles apart (2 x 8, 3 x 5 .. 12, 4 x 4 measured: LSTM alike, the GRU best with two)
 
-// MULTI: a workgroup carries more than one sequence
-template <int DT, int KR, int KC, int CELL, bool MULTI>
+// MULTI: a workgroup carries more than one sequence.  PLACED: every set of workgroups on an XCD of its own (1-D grid);
+// otherwise grid.y is the set.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
+template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
 __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams p) {
     using T = typename GElem<DT>::type;
     static_assert(sizeof(T) == 2, "two-byte element types");
@@ -89,14 +90,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     const int H = p.H;
     // this workgroup's sequences: b0 .. b0 + B - 1 of the p.B
     int set = blockIdx.y, unit = blockIdx.x;
-    // A set's workgroups on one XCD (ids are dealt to the eight of them round-robin): the exchange words of a set then live
-    // in one L2 instead of crossing the fabric between eight.  Where they land is speed only, not correctness.
-    if (p.sets) {
-        const int nwg = H / p.BR, slot = (int)blockIdx.x >> 3;
-        set = slot / nwg * 8 + ((int)blockIdx.x & 7);
-        unit = slot % nwg;
-        if (set >= p.sets) return;
-    }
+    if constexpr (PLACED) seq_placed_at(blockIdx.x, H / p.BR, &set, &unit);
     const int b0 = set * p.SPB;
     const int B = MULTI ? (p.SPB < p.B - b0 ? p.SPB : p.B - b0) : 1;
     const int NQ = MULTI ? p.NQ : 1;
@@ -250,11 +244,10 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     // (straight-line code, so that the wait for an older read leaves the younger ones in flight); a
                     // wave moves on as a whole, each lane with the first complete set of words it has seen (a slot is
                     // written again two steps later at the earliest, so a later read cannot show anything else).
-                    // (A set on one XCD needs none of this: its words come round soon enough that one read at a time is
-                    // quicker, 2.39 -> 2.30 us per LSTM step of 1024 units.)
+                    // (A set on one XCD: one read at a time is quicker, 2.39 -> 2.30 us per LSTM step of 1024 units.)
                     unsigned int polls = 0;
                     bool ok = false, dead = false;
-                    if (!p.sets) {
+                    if constexpr (!PLACED) {
 #pragma unroll
                         for (int d = 0; d < NP; ++d) {
                             ask(w[d]);
@@ -277,7 +270,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     }
                     // one read at a time (from here on)
                     while (!ok && !dead) {
-                        if (polls) __builtin_amdgcn_s_sleep(1);
+                        if (!PLACED || polls) __builtin_amdgcn_s_sleep(1);
                         ask(w[0]);
                         const int st_ = seen(w[0]);
                         if (st_ > 0) {
@@ -458,9 +451,9 @@ __global__ void __launch_bounds__(256) rnn_seq_clear(unsigned long long *exch, i
     if (i == 0) *status = 0;
 }
 
-template <int DT, int KR, int KC, int CELL, bool MULTI>
+template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
 static grim_status launch_seq_inst(const SeqParams &p, dim3 grid, size_t lds, hipStream_t stream) {
-    auto kern = bcr_rnn_seq<DT, KR, KC, CELL, MULTI>;
+    auto kern = bcr_rnn_seq<DT, KR, KC, CELL, MULTI, PLACED>;
     static std::atomic<bool> attr_done{false};
     if (lds > 64 * 1024 && !attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSeqMaxLds) != hipSuccess) {
@@ -474,11 +467,15 @@ static grim_status launch_seq_inst(const SeqParams &p, dim3 grid, size_t lds, hi
 }
 
 template <int DT, int CELL>
-static grim_status launch_seq(const SeqParams &p, int kr, int kc, dim3 grid, size_t lds, hipStream_t stream) {
-#define GRIM_SEQ(R, C)                                                                                   \
-    if (kr == (R) && kc == (C))                                                                          \
-        return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true>(p, grid, lds, stream)                   \
-                         : launch_seq_inst<DT, R, C, CELL, false>(p, grid, lds, stream);
+static grim_status launch_seq(const SeqParams &p, int kr, int kc, bool placed, dim3 grid, size_t lds, hipStream_t stream) {
+#define GRIM_SEQ(R, C)                                                                                             \
+    if (kr == (R) && kc == (C)) {                                                                                  \
+        if (placed)                                                                                                \
+            return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, true>(p, grid, lds, stream)                   \
+                             : launch_seq_inst<DT, R, C, CELL, false, true>(p, grid, lds, stream);                 \
+        return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, false>(p, grid, lds, stream)                      \
+                         : launch_seq_inst<DT, R, C, CELL, false, false>(p, grid, lds, stream);                    \
+    }
     GRIM_SEQ(4, 4) GRIM_SEQ(4, 8) GRIM_SEQ(4, 12) GRIM_SEQ(4, 16)
     GRIM_SEQ(8, 4) GRIM_SEQ(8, 8) GRIM_SEQ(8, 12) GRIM_SEQ(8, 16)
     GRIM_SEQ(16, 4) GRIM_SEQ(16, 8) GRIM_SEQ(16, 12)
@@ -575,17 +572,17 @@ grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, con
     const int64_t words = (int64_t)sets * 2 * p.NQ * H;                // at most 2 * kSeqMaxBatch * H
     hipLaunchKernelGGL(rnn_seq_clear, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, p.exch, words, status);
     if (hipGetLastError() != hipSuccess) return GRIM_ERR_DEVICE;
-    // A set per XCD while that leaves every workgroup a compute unit of its own (32 to an XCD): eight sequences through an LSTM
-    // layer of 1024 units 2.52 -> 2.30 us per step, one through 256 units 2.24 -> 2.07, the GRU 2.56 -> 2.39.
-    const int64_t rounds = (sets + 7) / 8;
-    p.sets = rounds * (H / BR) <= 32 ? sets : 0;
-    const dim3 grid(p.sets ? (unsigned)(rounds * (H / BR) * 8) : (unsigned)(H / BR), p.sets ? 1u : (unsigned)sets);
+    // Eight sequences through an LSTM layer of 1024 / 512 / 256 units 2.59 / 2.33 / 2.23 us per step in the plain order, 2.36 /
+    // 2.01 / 1.93 placed; GRU 2.64 / 2.47 / 2.40 -> 2.38 / 2.12 / 2.11; 32 sequences of 1024 units 5.5 -> 5.4, GRU 6.0 -> 5.9.
+    const bool placed = seq_sets_on_xcds(sets);
+    const int64_t wgs = H / BR;
+    const dim3 grid(placed ? (unsigned)(sets * wgs) : (unsigned)wgs, placed ? 1u : (unsigned)sets);
     const size_t lds = seq_lds_bytes(kind, K1, K2, BR, per_wg);
     if (kind == 1)
-        return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 1>(p, ukr, ukc, grid, lds, stream)
-                                 : launch_seq<GRIM_BF16, 1>(p, ukr, ukc, grid, lds, stream);
-    return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 2>(p, ukr, ukc, grid, lds, stream)
-                             : launch_seq<GRIM_BF16, 2>(p, ukr, ukc, grid, lds, stream);
+        return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 1>(p, ukr, ukc, placed, grid, lds, stream)
+                                 : launch_seq<GRIM_BF16, 1>(p, ukr, ukc, placed, grid, lds, stream);
+    return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 2>(p, ukr, ukc, placed, grid, lds, stream)
+                             : launch_seq<GRIM_BF16, 2>(p, ukr, ukc, placed, grid, lds, stream);
 }
 
 // Exchange words for callers that must not allocate: one array per GPU, part of the loaded code object, shared by

@@ -1,13 +1,7 @@
 // Where the windows of a convolution tile lie in a feature map: the arithmetic that decides whether a tile's loads need
 // range checks, shared by the convolution kernels and by the host check that walks every load of every tile.
 #pragma once
-
-#if defined(__HIPCC__)
-#include <hip/hip_runtime.h>
-#define GRIM_HOST_DEVICE __host__ __device__ __forceinline__
-#else
-#define GRIM_HOST_DEVICE inline
-#endif
+#include "host_device.hpp"
 
 namespace grim {
 

@@ -412,3 +412,35 @@ def test_sequence_batch_limits_and_a_tiny_wait_limit():
         g.lstm_sequence_batch(A, xd, I, 3, 0, None, hd, c, hs, H, None, 0, st)
     assert "SHAPE" in str(e.value)
     torch.cuda.synchronize()
+
+
+def test_sequences_of_separate_matrices_on_separate_streams():
+    """Calls that may overlap in time, each on a matrix and a stream of its own: every one ends with status 0 and the bits it
+    has alone."""
+    from helpers import to_device
+    torch, dev, g = _gpu()
+    dtype, H, I, T = gen.F16, 512, 64, 24
+    cases = []
+    for k in range(4):
+        A, _ = _lstm_case(g, dtype, H, I, 32, 32, 8, 8, seed=1900 + 10 * k, scale=2.0)
+        cases.append((A, to_device(_inputs(T, I, dtype, 1950 + k), dtype), torch.cuda.Stream()))
+
+    def call(A, xs, stream):
+        h0 = torch.zeros(H, dtype=xs.dtype, device=dev)
+        c = torch.zeros(H, dtype=torch.float32, device=dev)
+        hs = torch.empty((T, H), dtype=xs.dtype, device=dev)
+        status = torch.full((1,), -1, dtype=torch.int32, device=dev)
+        stream.wait_stream(torch.cuda.current_stream())
+        g.lstm_sequence(A, xs, I, T, None, h0, c, hs, H, None, 0, status, 0, stream)
+        return hs, c, status, h0
+
+    alone = []
+    for case in cases:
+        alone.append(call(*case))
+        torch.cuda.synchronize()
+    for _ in range(3):
+        together = [call(*case) for case in cases]
+        torch.cuda.synchronize()
+        for a, b in zip(alone, together):
+            assert int(a[2]) == 0 and int(b[2]) == 0
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])

@@ -48,14 +48,19 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     assert "passed" in run.stdout and "AddressSanitizer" not in tail and "runtime error" not in tail, tail
 
 
+def _host_library(tmp_path, name):
+    """tests/sanitize/<name>.cpp built for the host with the library's headers."""
+    lib = str(tmp_path / (name + ".so"))
+    res = subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2108_11033_amd", "csrc"),
+                          os.path.join(ROOT, "tests", "sanitize", name + ".cpp"), "-o", lib], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    return ctypes.CDLL(lib)
+
+
 def test_convolution_loads_without_range_checks_stay_inside_the_map(tmp_path):
     """Every load of every tile that the convolution kernels fetch without range checks, by their own arithmetic
     (csrc/conv_window.hpp) built for the host: small, flat and odd maps, both strides and both tile widths."""
-    lib = str(tmp_path / "conv_windows.so")
-    res = subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2108_11033_amd", "csrc"),
-                          os.path.join(ROOT, "tests", "sanitize", "conv_windows.cpp"), "-o", lib], capture_output=True, text=True)
-    assert res.returncode == 0, res.stderr[-4000:]
-    outside = ctypes.CDLL(lib).conv_loads_outside
+    outside = _host_library(tmp_path, "conv_windows").conv_loads_outside
     outside.restype = ctypes.c_int64
     sizes = list(range(1, 21)) + list(range(21, 131, 3)) + [33, 47, 48, 63, 64, 65, 79, 95, 111, 112, 113, 128, 129]
     for stride in (1, 2):
@@ -66,3 +71,12 @@ def test_convolution_loads_without_range_checks_stay_inside_the_map(tmp_path):
                         for Cin in (1, 3):
                             n = outside(Cin, H, W, kh, kw, stride, tn)
                             assert n == 0, (n, dict(Cin=Cin, H=H, W=W, kh=kh, kw=kw, stride=stride, tile=tn))
+
+
+def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
+    """Workgroups of a sequence call wait for one another: placing its sets on XCDs must not put more of them on any XCD than
+    the plain order does, or calls on several streams could each hold a part of one XCD and wait for the rest."""
+    excess = _host_library(tmp_path, "seq_placement").seq_placement_excess
+    for sets in range(1, 33):
+        for wgs in (1, 2, 3, 7, 8, 31, 32, 64):
+            assert excess(sets, wgs) == 0, (sets, wgs)
