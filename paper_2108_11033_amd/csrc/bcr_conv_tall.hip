@@ -17,8 +17,52 @@ namespace grim {
 // flight leave two waves per SIMD, so a wave covers its own latencies: a step's windows are asked for D steps ahead, into
 // the registers of the step that was just parked, its weights likewise after that step's multiplies, and its slot words and
 // descriptors D steps before that.
+//
+// A formed row meets all 64 rows of the run, with zero weights in those that do not keep it, so an infinity or NaN in the map
+// would reach 64 output channels; on 16-row runs it reaches the 16 of the runs that name it.  Every sum of such a position is
+// then not finite, whichever rows keep it: where a sum is not, the output is formed again from the matrix's own 16-row runs
+// (conv_own_run), which costs the tiles that meet no such value nothing but the look at their sums.
+struct ConvTallParams : ConvParams {
+    // the matrix's 16-row runs, `own_plan` their window-start words
+    const int32_t *own_sptr;
+    const uint32_t *own_plan, *own_desc;
+    const unsigned char *own_payload;
+    int32_t own_usteps;
+};
+
+// output row r of 16-row run `run` at position n: the run's k slots in order, zero weights where row r does not keep one
+template <bool BF16, bool S2>
+__device__ __forceinline__ float conv_own_run(const ConvTallParams &p, const unsigned short *Fimg, int run, int r, int n) {
+    constexpr int DT = BF16 ? GRIM_BF16 : GRIM_F16;
+    using T = typename Elem<DT>::type;
+    const int rowlen = S2 ? p.Wp : p.W, ho = n / rowlen, wo = n - ho * rowlen;
+    const int h = S2 ? 2 * ho : ho, w = S2 ? 2 * wo : wo, start = h * p.W + w - (1 << 25);
+    const int s0 = p.own_usteps ? run * p.own_usteps : p.own_sptr[run], s1 = p.own_usteps ? s0 + p.own_usteps : p.own_sptr[run + 1];
+    float sum = 0.f;
+#pragma unroll 1
+    for (int s = s0; s < s1; ++s) {
+#pragma unroll 1
+        for (int g = 0; g < 4; ++g) {
+            const uint2 d = reinterpret_cast<const uint2 *>(p.own_desc)[(int64_t)s * 4 + g];
+            const bool kept = (d.x >> r) & 1u;
+            const T *wt = reinterpret_cast<const T *>(p.own_payload) + ((int64_t)d.y + (kept ? __builtin_popcount(d.x & ((1u << r) - 1u)) : 0)) * 8;
+#pragma unroll 1
+            for (int j = 0; j < 8; ++j) {
+                const unsigned int word = p.own_plan[(int64_t)s * 32 + j * 4 + g];
+                const int tap = (int)(word >> 27);
+                if (tap == p.KK) continue;       // padding
+                const int hh = h + tap / p.kw - (p.kh >> 1), ww = w + tap % p.kw - (p.kw >> 1);
+                const bool inside = hh >= 0 && hh < p.H && ww >= 0 && ww < p.W;
+                const unsigned short x = inside ? Fimg[(int)(word & 0x7ffffffu) + start] : (unsigned short)0;
+                sum = __builtin_fmaf(kept ? to_f32<DT>(wt[j]) : 0.f, to_f32<DT>(__builtin_bit_cast(T, x)), sum);
+            }
+        }
+    }
+    return sum;
+}
+
 template <bool BF16, bool S2, int NWV>
-__global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvParams p) {
+__global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
     constexpr int R = kConvTallRuns, NT = 4, TN = 64, PITCH = 128, CPR = 8, LI = 4;
     constexpr int LW = S2 ? 2 : 1;               // 16-byte loads per window
     constexpr int D = 2;                         // steps in flight
@@ -225,6 +269,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvParams p) {
 #pragma unroll
         for (int q = 0; q < NT; ++q) red[wave * (WAVE_LDS / 16) + (m * NT + q) * 64 + lane] = acc[m][q];
     __syncthreads();
+    unsigned int again = 0u;                     // bit per pair: one of the lane's four sums is not finite
     for (int i = wave; i < R * NT; i += NWV) {
         const int64_t row = p.out_row[((int64_t)t * R + i / NT) * 16 + i16];
         f32x4 sum = red[i * 64 + lane];
@@ -233,18 +278,38 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvParams p) {
             const f32x4 v = red[w * (WAVE_LDS / 16) + i * 64 + lane];
             sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
         }
+        float nan = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nan = __builtin_fmaf(sum[e], 0.f, nan);
+        again |= nan != nan ? 1u << i : 0u;
         if (row >= 0) conv_finish<S2>(p, img, row, n0 + i % NT * 16 + 4 * kgroup, sum);
+    }
+    if (__builtin_amdgcn_ballot_w64(again != 0u)) {
+#pragma unroll 1
+        for (int i = wave; i < R * NT; i += NWV) {
+            const int run = t * R + i / NT, n = n0 + i % NT * 16 + 4 * kgroup;
+            const int64_t row = p.out_row[(int64_t)run * 16 + i16];
+            if (row < 0 || !((again >> i) & 1u)) continue;
+            f32x4 sum;
+#pragma unroll 1
+            for (int e = 0; e < 4; ++e) {
+                const float v = n + e < p.Nv ? conv_own_run<BF16, S2>(p, Fimg, run, i16, n + e) : 0.f;
+                sum[0] = e == 0 ? v : sum[0]; sum[1] = e == 1 ? v : sum[1]; sum[2] = e == 2 ? v : sum[2]; sum[3] = e == 3 ? v : sum[3];
+            }
+            conv_finish<S2>(p, img, row, n, sum);
+        }
     }
 }
 
-grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
+grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
                              int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
                              int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride) {
-    ConvParams p;
+    ConvTallParams p;
     ConvForm form;
     const grim_status st = conv_gather_setup(A, F, Cin, H, W, kh, kw, bias, relu, Y, odt, ldy, batch, stride, f_img_stride,
                                              y_img_stride, L.d_rows, 0, 0, 0, &p, &form);
     if (st != GRIM_OK) return st;
+    p.own_sptr = p.sptr; p.own_plan = own_words; p.own_desc = p.desc; p.own_payload = p.payload; p.own_usteps = p.usteps;
     p.sptr = L.d_sptr;
     p.out_row = L.d_out_row;
     p.desc = L.d_desc;

@@ -235,8 +235,8 @@ grim_status launch_conv_gather(const grim_bcr_matrix *A, const void *F, int32_t 
                                hipStream_t stream, int32_t batch = 1, int32_t stride = 1, int64_t f_img_stride = 0,
                                int64_t y_img_stride = 0, const uint32_t *plan = nullptr, int32_t img0 = 0,
                                int64_t pos_begin = 0, int64_t pos_end = 0);   // pos_end > 0: positions [pos_begin, pos_end) of image img0 only
-// the same on a plan's layout of 64-row runs, whose `rows` are window-start words
-grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
+// the same on a plan's layout of 64-row runs, whose `rows` are window-start words (own_words: those of the matrix's layout)
+grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
                              int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
                              int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride);
 uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw);

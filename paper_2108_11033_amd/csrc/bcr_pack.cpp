@@ -1263,7 +1263,7 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev,
         if (st != GRIM_ERR_UNSUPPORTED) return st;
     }
     if (conv_on_tall_runs(P, batch)) {
-        const grim_status st = launch_conv_tall(P->A, P->tall, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
+        const grim_status st = launch_conv_tall(P->A, P->tall, P->d_words, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
                                                 (int32_t)out_dt, ldo, static_cast<hipStream_t>(hip_stream), batch, P->stride, f_image_stride,
                                                 out_image_stride);
         if (st != GRIM_ERR_UNSUPPORTED) return st;

@@ -675,3 +675,44 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
     assert np.isfinite(Y).all()
     assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
     assert np.abs(Y - Yref).max() <= TOL[dtype] * np.abs(Yref).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B", [
+    (128, 4, 16, 64, 28, 27, 3, 1, 9),       # 64-row runs
+    (208, 16, 16, 64, 29, 31, 3, 2, 12),     # 64-row runs at stride 2, a last run of 16 rows
+    (48, 16, 32, 256, 13, 14, 3, 1, 1),      # 32-position tiles
+    (48, 16, 32, 256, 13, 14, 3, 2, 1),
+    (48, 8, 16, 16, 17, 19, 3, 1, 2),        # 64-position tiles
+])
+def test_conv_plan_infinities_and_nans_stay_in_the_16_row_runs_that_name_them(dtype, M, BR, BC, cin, H, W, kh, stride, B):
+    """A value of the feature map that is not finite may turn up in any row of a 16-row run (of the stored order) with a row
+    that keeps its column; rows of other runs are right, and rows that keep it are not finite."""
+    import paper_2108_11033_amd as g
+    from helpers import TOL
+    K = cin * kh * kh
+    mask = gen.random_mask(M, K, BR, BC, (0, BR // 2), (BC // 4, BC // 2), seed=820 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=821)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=822, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    Wm = _masked(Wt, dtype, mask)
+    clean = gen.storage_to_f64(F, dtype)
+    spots = np.zeros(F.shape, dtype=bool)
+    bits = {gen.F16: (0x7c00, 0xfc00, 0x7e00), gen.BF16: (0x7f80, 0xff80, 0x7fc0)}[dtype]
+    raw = F.view(np.uint16)
+    rng = np.random.default_rng(823)
+    for i, (b, c, h, w) in enumerate([(0, 0, 0, 0), (B - 1, cin - 1, H - 1, W - 1)] + [tuple(rng.integers(0, F.shape)) for _ in range(10)]):
+        raw[b, c, h, w] = bits[i % 3]
+        spots[b, c, h, w] = True
+    finite = np.where(spots, 0.0, clean)
+    A = g.pack(Wt, dtype, BR, BC, mask.row_ptr, mask.row_idx, mask.col_ptr, mask.col_idx, no_reorder=True)
+    Y = _run_plan(g, A, F, dtype, M, kh, kh, stride)
+    keep = Wm != 0                                              # (no stored weight is zero)
+    named = np.repeat(np.add.reduceat(keep, np.arange(0, M, 16), axis=0) > 0, 16, axis=0)[:M]
+    kept_here = conv_ref.conv2d(keep.astype(np.float64), spots.astype(np.float64), kh, kh, stride) > 0
+    may = conv_ref.conv2d(named.astype(np.float64), spots.astype(np.float64), kh, kh, stride) > 0
+    assert kept_here.any() and (may & ~kept_here).any() and (~may).any()
+    assert not np.isfinite(Y[kept_here]).any()
+    Yref, S = conv_ref.conv2d(Wm, finite, kh, kh, stride), conv_ref.conv2d(np.abs(Wm), np.abs(finite), kh, kh, stride)
+    assert np.isfinite(Y[~may]).all()
+    assert (np.abs(Y - Yref)[~may] <= TOL[dtype] * S[~may]).all()
