@@ -238,7 +238,7 @@ grim_status grim_bcr_conv2d(const grim_bcr_matrix *A, const void *F_dev, int32_t
 /*
  * grim_bcr_conv2d_act -- the same convolution with the rest of a CONV layer in its epilogue (Section 6.1:
  * the evaluated networks are chains of CONV + bias + rectifier layers, run in fp16 on the GPU):
- *     out[m][n] = round_to(out_dt, act(Y[m][n] + bias[m])),   act = max(., 0) when relu != 0, else identity
+ *     out[m][n] = round_to(out_dt, act(Y[m][n] + bias[m])),   act = max(., 0) when relu != 0 (NaN stays NaN), else identity
  *   bias_dev  M fp32, or NULL (no bias)
  *   out_dev   M x (H * W) of element type out_dt (fp32, fp16 or bf16; round to nearest even), leading
  *             dimension ldo >= H * W, overwritten.  In fp16 / bf16 it is the next layer's feature map

@@ -716,3 +716,33 @@ def test_conv_plan_infinities_and_nans_stay_in_the_16_row_runs_that_name_them(dt
     Yref, S = conv_ref.conv2d(Wm, finite, kh, kh, stride), conv_ref.conv2d(np.abs(Wm), np.abs(finite), kh, kh, stride)
     assert np.isfinite(Y[~may]).all()
     assert (np.abs(Y - Yref)[~may] <= TOL[dtype] * S[~may]).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B", [
+    (128, 4, 16, 64, 28, 27, 3, 1, 9),       # 64-row runs
+    (128, 16, 24, 8, 224, 224, 3, 1, 1),     # wide tiles, blocks of 16 and of 32 rows
+    (256, 32, 32, 32, 96, 88, 1, 1, 3),
+    (48, 16, 32, 32, 17, 19, 3, 2, 2),
+])
+def test_conv_rectifier_keeps_nans(dtype, M, BR, BC, cin, H, W, kh, stride, B):
+    """relu = max(., 0) of the same call without it, NaN staying NaN (an output that is wrong must not look like a zero)."""
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload
+    K = cin * kh * kh
+    mask = gen.random_mask(M, K, BR, BC, (BR // 4, BR // 2), (BC // 4, BC // 2), seed=840 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=841)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=842).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    rng = np.random.default_rng(843)
+    raw, bits = F.view(np.uint16), {gen.F16: (0x7c00, 0xfc00, 0x7e00), gen.BF16: (0x7f80, 0xff80, 0x7fc0)}[dtype]
+    for i in range(12):
+        raw[tuple(rng.integers(0, F.shape))] = bits[i % 3]
+    A = pack_workload(g, Wt, dtype, mask)
+    plain = _run_plan(g, A, F, dtype, M, kh, kh, stride)
+    assert np.isnan(plain).any() and (plain < 0).any()
+    for out_dtype in (gen.F32, dtype):
+        act = _run_plan(g, A, F, dtype, M, kh, kh, stride, relu=True, out_dtype=out_dtype)
+        assert np.array_equal(np.isnan(act), np.isnan(plain))
+        if out_dtype == gen.F32:
+            assert np.array_equal(act, np.maximum(plain, 0.0), equal_nan=True)
