@@ -266,10 +266,10 @@ grim_status grim_bcr_conv2d_act(const grim_bcr_matrix *A, const void *F_dev, int
  *                               b * f_image_stride elements; out_dev: batch outputs [M][ldo] (ldo >= Ho * Wo) of
  *                               element type out_dt, image b at out_dev + b * out_image_stride elements, overwritten
  *                               (entries n < Ho * Wo of each row); bias_dev (M fp32 or NULL), relu and the rounding as
- *                               grim_bcr_conv2d_act.  With batch = 1 the image strides are ignored.  Sums in fp32 in
- *                               the same order as grim_bcr_conv2d: with stride 1 the two write the same bits.  Stride 2
- *                               computes on the input grid and stores the even positions (every second row is skipped
- *                               when W is a multiple of 8).  Enqueues one launch on hip_stream, allocates nothing.
+ *                               grim_bcr_conv2d_act.  With batch = 1 the image strides are ignored.  Sums in fp32; with
+ *                               stride 1 and one image in the same order as grim_bcr_conv2d, which writes the same bits (a
+ *                               batch may split a sum over another number of waves, or take the 64-row form of the kernel).
+ *                               Enqueues one launch on hip_stream, allocates nothing.
  *                               Errors: NULL, SHAPE (batch < 1, ldo or an image stride too small), DTYPE, DEVICE,
  *                               UNSUPPORTED.
  *   grim_bcr_conv_plan_free     frees the plan (not the matrix).

@@ -12,6 +12,31 @@ uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw
     return (uint32_t)tap << 27 | (uint32_t)(eb + (1 << 25));
 }
 
+// a wave's share of the steps of the longest strip when twelve waves split it
+static int conv_share(const grim_bcr_matrix *A) { return (A->gather.max_steps + kConvLongWaves - 1) / kConvLongWaves; }
+
+// 32-position tiles (two sub-tiles of 16) for maps of 14 x 14 and less, where 64-position tiles leave compute units without a
+// workgroup, if a wave's share of a strip's steps is one batch: of three steps, or (stride 1) of six where 64-position tiles
+// would take two batches (72 steps at 14 x 14: 12.0 -> 9.4 us; 36 steps at stride 2 onto 7 x 7: 11.9 -> 7.5)
+static int conv_subtiles(const grim_bcr_matrix *A, int64_t positions, int32_t batch, int32_t stride, bool planned) {
+    return planned && A->gather.max_steps >= 16 && conv_share(A) <= (stride == 2 ? 3 : 6) &&
+                   (positions + 31) / 32 * batch * (int64_t)A->gather.nstrips <= 256 ? 2 : 4;
+}
+
+// Waves that split a strip's steps, by the number of (tile, strip) pairs: the launch forms of the row-gathering kernel (one
+// wave: a pair per wave); long strips and few pairs: twelve up to 256 pairs (one workgroup per compute unit), eight up to 512
+// (two per compute unit; 28 x 28 layers: 11.0 -> 9.4 us with 18 steps, 14.1 -> 13.3 us with 36)
+static int conv_strip_waves(const grim_bcr_matrix *A, int nt, int64_t pairs) {
+    if (gather_wave_per_strip(A, pairs, 4096)) return 1;
+    return A->gather.max_steps < 16 ? 4 : nt == 2 || pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 4;
+}
+
+bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch) {
+    const int64_t tiles = (positions + 63) / 64 * (int64_t)A->gather.nstrips;
+    const int nt = conv_subtiles(A, positions, batch, 1, true), nt_one = conv_subtiles(A, positions, 1, 1, true);
+    return conv_strip_waves(A, nt, tiles * batch) == conv_strip_waves(A, nt_one, tiles);
+}
+
 grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw,
                               const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, int32_t batch, int32_t stride,
                               int64_t f_img_stride, int64_t y_img_stride, const uint32_t *plan, int32_t img0, int64_t pos_begin,
@@ -60,12 +85,8 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
         Nv = pos_end;
     }
     p.Nv = (int32_t)Nv;
-    // 32-position tiles for maps of 14 x 14 and less, where 64-position tiles leave compute units without a workgroup, if
-    // a wave's share of a strip's steps is one batch: of three steps, or (stride 1) of six where 64-position tiles would
-    // take two batches (72 steps at 14 x 14: 12.0 -> 9.4 us; 36 steps at stride 2 onto 7 x 7: 11.9 -> 7.5)
-    const int share = (A->gather.max_steps + kConvLongWaves - 1) / kConvLongWaves;
-    const int nt = plan && pos_end <= 0 && A->gather.max_steps >= 16 && share <= (stride == 2 ? 3 : 6) &&
-                   (Nv + 31) / 32 * batch * (int64_t)A->gather.nstrips <= 256 ? 2 : 4;
+    const int share = conv_share(A);
+    const int nt = pos_end > 0 ? 4 : conv_subtiles(A, Nv, batch, stride, plan != nullptr);
     form->batch = nt == 4 ? conv_batch(stride) : share <= 3 ? 3 : 6;
     p.tiles_per_img = (int32_t)((Nv - p.pos_begin + nt * 16 - 1) / (nt * 16));
     if ((int64_t)p.tiles_per_img * batch > 0x7fffffff / 16) return GRIM_ERR_SHAPE;
@@ -74,12 +95,9 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
     const int esz_out = odt == GRIM_F32 ? 4 : 2;
     p.yvec = (reinterpret_cast<uintptr_t>(Y) % (odt == GRIM_F32 ? 16 : 8) == 0 && ldy % 4 == 0 && (stride == 1 ? N : p.Wo) % 4 == 0 &&
               (batch == 1 || (y_img_stride * esz_out) % (odt == GRIM_F32 ? 16 : 8) == 0)) ? 4 : 1;
-    // the same launch forms as the row-gathering kernel
-    const bool solo = gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 4096);
-    const int64_t pairs = (int64_t)p.ntiles * p.nbr;
-    // long strips and few pairs: twelve waves per strip up to 256 pairs (one workgroup per compute unit), eight up to 512
-    // (two per compute unit; 28 x 28 layers: 11.0 -> 9.4 us with 18 steps, 14.1 -> 13.3 us with 36)
-    const int longw = !solo && A->gather.max_steps >= 16 ? (nt == 2 || pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 0) : 0;
+    const int waves = conv_strip_waves(A, nt, (int64_t)p.ntiles * p.nbr);
+    const bool solo = waves == 1;
+    const int longw = waves > 4 ? waves : 0;
     const int64_t per_tile = solo ? (p.nbr + 3) / 4 : p.nbr;
     if (((int64_t)p.ntiles + 7) / 8 * 8 * per_tile > 0x7fffffff) return GRIM_ERR_SHAPE;
     int64_t nwg = 0;

@@ -239,6 +239,8 @@ grim_status launch_conv_gather(const grim_bcr_matrix *A, const void *F, int32_t 
 grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
                              int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
                              int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride);
+// at stride 1, does a batch split a strip's sum over as many waves as one image does?  (Its sums then have the same bits.)
+bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch);
 uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw);
 // stride-1 convolution of layers with many positions on the wide-tile kernel (whole rounds of workgroups plus a narrow
 // rest); GRIM_ERR_UNSUPPORTED when the layer is too small or does not qualify: the caller then takes the kernel above

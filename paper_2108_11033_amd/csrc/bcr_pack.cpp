@@ -1241,6 +1241,8 @@ static bool conv_on_tall_runs(const grim_bcr_conv_plan *P, int32_t batch) {
     const int64_t Ho = (P->H + 1) / 2, Wp = ((P->W + 1) / 2 + 7) / 8 * 8;
     const int64_t positions = P->stride == 2 ? Ho * Wp : (int64_t)P->H * P->W;
     if ((positions + 63) / 64 * batch * P->tall.nstrips < 160) return false;
+    // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
+    if (P->stride == 1 && conv_batch_sums_as_one_image(P->A, positions, batch)) return false;
     return P->stride == 2 || (P->tall.max_steps >= 12 && P->tall.nsteps * 7 <= P->A->gather.nsteps * 4);
 }
 

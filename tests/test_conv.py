@@ -659,6 +659,7 @@ def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, col
     (128, 128, 32, 9, 9, 3, 3, 2, 48, 0, 32),    # blocks taller than a run; 5 x 5 outputs: one partly filled tile per image
     (192, 4, 16, 40, 40, 1, 1, 2, 8, 0, 32),     # fewer steps than waves
     (128, 4, 16, 3, 47, 1, 1, 2, 80, 0, 64),     # flat maps at stride 2: a tile of 48 positions
+    (96, 4, 16, 70, 75, 3, 3, 1, 2, 3, 32),      # (the first shape as a batch of two)
 ])
 def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pad, cin):
     import paper_2108_11033_amd as g
@@ -746,3 +747,24 @@ def test_conv_rectifier_keeps_nans(dtype, M, BR, BC, cin, H, W, kh, stride, B):
         assert np.array_equal(np.isnan(act), np.isnan(plain))
         if out_dtype == gen.F32:
             assert np.array_equal(act, np.maximum(plain, 0.0), equal_nan=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,B", [
+    (96, 4, 16, 32, 70, 75, 3, 1),           # one image, as many workgroups as the 64-row form of the kernel asks for
+    (64, 8, 16, 64, 101, 103, 3, 1),
+    (96, 4, 16, 96, 100, 75, 3, 2),          # a batch that splits its sums as one image does
+    (48, 16, 32, 256, 13, 14, 3, 1),         # 32-position tiles
+])
+def test_conv_plan_writes_the_bits_of_the_unplanned_convolution(dtype, M, BR, BC, cin, H, W, kh, B):
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload
+    K = cin * kh * kh
+    mask = gen.random_mask(M, K, BR, BC, (BR // 2, BR), (BC // 4, BC // 2), seed=860 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=861)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=862, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    A = pack_workload(g, Wt, dtype, mask)
+    Y = _run_plan(g, A, F, dtype, M, kh, kh, 1)
+    for b in range(B):
+        assert np.array_equal(_run(g, A, F[b], dtype, M, cin, H, W, kh, kh), Y[b].astype(np.float32))
