@@ -356,6 +356,42 @@ void build_gather_layout(const grim_bcr_matrix *A, GatherLayout &L) {
     L.present = true;
 }
 
+// The steps the layout of R-run strips would have, without writing it.
+struct RunSteps {
+    int64_t total = 0;
+    int32_t longest = 0;
+    int64_t runs = 0;
+};
+template <int R>
+RunSteps count_run_steps(const grim_bcr_matrix *A) {
+    constexpr int HEIGHT = 16 * R;
+    RunSteps n;
+    if (!(HEIGHT % A->BR == 0 || A->BR % HEIGHT == 0)) return n;
+    n.runs = (A->M + HEIGHT - 1) / HEIGHT;
+    std::vector<uint64_t> met((size_t)(A->BC + 63) / 64);                    // columns of a block that a strip of the run keeps
+    for (int64_t u = 0; u < n.runs; ++u) {
+        const int64_t row0 = u * HEIGHT, row1 = std::min<int64_t>(A->M, row0 + HEIGHT);
+        const int64_t p0 = row0 / A->BR, p1 = (row1 - 1) / A->BR;
+        int64_t columns = 0;
+        for (int64_t c = 0; c < A->nbc; ++c) {
+            std::fill(met.begin(), met.end(), uint64_t(0));
+            for (int64_t p = p0; p <= p1; ++p) {
+                const int64_t t = p * A->nbc + c;
+                int32_t q0 = A->row_ptr[t], q1 = A->row_ptr[t + 1];
+                while (q0 < q1 && p * A->BR + A->row_idx[q0] < row0) ++q0;
+                while (q0 < q1 && p * A->BR + A->row_idx[q1 - 1] >= row1) --q1;
+                if (q0 == q1) continue;
+                for (int32_t j = A->col_ptr[t]; j < A->col_ptr[t + 1]; ++j) met[(size_t)A->col_idx[j] / 64] |= uint64_t(1) << (A->col_idx[j] % 64);
+            }
+            for (uint64_t w : met) columns += __builtin_popcountll(w);
+        }
+        const int64_t steps = (columns + 31) / 32;
+        n.total += steps;
+        n.longest = (int32_t)std::max<int64_t>(n.longest, steps);
+    }
+    return n;
+}
+
 // ---- derived layout: row-gathering SpMM, fp32 ------------------------------------------------
 // A block's kept columns in groups of four (a group never holds columns of two blocks: the row mask then says exactly
 // which rows keep its columns).
@@ -1146,45 +1182,69 @@ struct grim_bcr_conv_plan {
     uint32_t *d_words = nullptr;
     // the rows cut into runs of 64 (where that leaves fewer rows of the im2col matrix to form); `rows` are window-start words
     GatherLayout tall;
+    RunSteps tall_steps;
     void *d_tall = nullptr;          // one allocation for all of it
 };
 
-// Steps of 64-row runs against steps of the 16-row runs they replace: worth their own layout from here on
-static bool tall_pays(const GatherLayout &tall, const GatherLayout &own) {
-    return tall.present && tall.nsteps * 4 <= own.nsteps * 3;
+// Runs of 64 rows pay once there are about as many (tile, run) pairs as two thirds of the compute units -- below that the
+// four times as many 16-row workgroups are quicker (512 channels on one 28 x 28 map, 104 pairs: 13.6 -> 19.4 us) -- and, at
+// stride 1, for strips of some length that name each row nearly twice and more.  Measured, 16-row against 64-row runs:
+// 256 channels, 3 x 3, four 28 x 28 maps in 16 x 32 / 8 x 16 / 16 x 16 / 32 x 32 / 4 x 16 blocks (rows named 1.5 / 1.9 /
+// 2.1 / 2.7 / 2.7 times) 13.5 -> 13.7, 18.0 -> 16.1, 17.9 -> 16.5, 18.2 -> 13.8, 25.7 -> 16.4 us; 128 channels on eight
+// 56 x 56 maps 21.9 -> 26.1, 31.8 -> 29.3, 32.2 -> 29.5, 32.1 -> 26.5, 41.5 -> 30.2; 1 x 1 with 8 steps 7.1 -> 7.5.  At
+// stride 2, where a window is two loads, 128 -> 256 channels from four 56 x 56 maps 13.5 -> 11.1, 17.2 -> 12.6, 17.0 ->
+// 12.6, 17.2 -> 12.0, 21.9 -> 12.6 and its 1 x 1 shortcut of four steps 7.6 -> 6.8.
+static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, int32_t H, int32_t W, int32_t stride, int32_t batch) {
+    if (A->M <= 16 || tall.runs == 0 || tall.total * 4 > A->gather.nsteps * 3) return false;
+    if (stride == 1 && (tall.longest < 12 || tall.total * 7 > A->gather.nsteps * 4)) return false;
+    const int64_t Ho = (H + 1) / 2, Wp = ((W + 1) / 2 + 7) / 8 * 8;
+    const int64_t positions = stride == 2 ? Ho * Wp : (int64_t)H * W;
+    if ((positions + 63) / 64 * batch * tall.runs < 160) return false;
+    // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
+    return stride == 2 || !conv_batch_sums_as_one_image(A, positions, batch);
 }
 
-static grim_status add_tall_layout(grim_bcr_conv_plan *P) {
+// The layout of 64-row runs, where it has fewer steps.  A plan that cannot have it (no memory) does without.
+static void add_tall_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
     GatherLayout &L = P->tall;
+    RunSteps steps;
     try {
-        if (A->M > 16) build_gather_layout<kConvTallRuns>(A, L);
-        if (!tall_pays(L, A->gather)) { L = GatherLayout(); return GRIM_OK; }
+        steps = count_run_steps<kConvTallRuns>(A);
+        if (A->M <= 16 || steps.runs == 0 || steps.total * 4 > A->gather.nsteps * 3) return;
+        build_gather_layout<kConvTallRuns>(A, L);
         for (uint32_t &r : L.rows) r = conv_plan_word(r, P->H, P->W, P->kh, P->kw);
     } catch (const std::bad_alloc &) {
-        return GRIM_ERR_ALLOC;
+        L = GatherLayout();
+        return;
     }
+    if (!L.present) return;
     Slab s;
     auto bytes = [](const auto &v) { return v.size() * sizeof(v[0]); };
     const size_t o_s = s.add(bytes(L.sptr)), o_q = s.add(bytes(L.out_row)), o_r = s.add(bytes(L.rows)), o_d = s.add(bytes(L.desc)),
                  o_p = s.add(bytes(L.payload) + 16);
     char *base = nullptr;
-    if (hipMalloc(reinterpret_cast<void **>(&base), s.total + 256) != hipSuccess) { (void)hipGetLastError(); return GRIM_ERR_ALLOC; }
+    if (hipMalloc(reinterpret_cast<void **>(&base), s.total + 256) != hipSuccess) {
+        (void)hipGetLastError();
+        L = GatherLayout();
+        return;
+    }
     auto put = [&](size_t off, const void *src, size_t n) { return n == 0 || hipMemcpy(base + off, src, n, hipMemcpyHostToDevice) == hipSuccess; };
     if (!(put(o_s, L.sptr.data(), bytes(L.sptr)) && put(o_q, L.out_row.data(), bytes(L.out_row)) && put(o_r, L.rows.data(), bytes(L.rows)) &&
           put(o_d, L.desc.data(), bytes(L.desc)) && put(o_p, L.payload.data(), bytes(L.payload)))) {
         (void)hipGetLastError();
         (void)hipFree(base);
-        return GRIM_ERR_DEVICE;
+        L = GatherLayout();
+        return;
     }
     P->d_tall = base;
+    P->tall_steps = steps;
     L.d_sptr = reinterpret_cast<int32_t *>(base + o_s);
     L.d_out_row = reinterpret_cast<int32_t *>(base + o_q);
     L.d_rows = reinterpret_cast<uint32_t *>(base + o_r);
     L.d_desc = reinterpret_cast<uint32_t *>(base + o_d);
     L.d_payload = reinterpret_cast<unsigned char *>(base + o_p);
     L.rows = {}; L.desc = {}; L.payload = {}; L.out_row = {};            // (the host copies have done their work)
-    return GRIM_OK;
 }
 
 grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw,
@@ -1198,7 +1258,6 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
     if (hipGetDevice(&dev) != hipSuccess || dev != A->device) { (void)hipGetLastError(); return GRIM_ERR_DEVICE; }
     if (!A->gather.present || kh * kw > 31 || (int64_t)Cin * H * W > (int64_t(1) << 26) || A->gather.rows.empty())
         return GRIM_ERR_UNSUPPORTED;
-    grim_status st = GRIM_OK;
     std::vector<uint32_t> words(A->gather.rows.size());
     for (size_t i = 0; i < words.size(); ++i) words[i] = conv_plan_word(A->gather.rows[i], H, W, kh, kw);
     std::unique_ptr<grim_bcr_conv_plan> P(new (std::nothrow) grim_bcr_conv_plan);
@@ -1212,11 +1271,7 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
         return GRIM_ERR_DEVICE;
     }
     P->d_words = static_cast<uint32_t *>(ptr);
-    st = add_tall_layout(P.get());
-    if (st != GRIM_OK) {
-        (void)hipFree(ptr);
-        return st;
-    }
+    add_tall_layout(P.get());
     *out = P.release();
     return GRIM_OK;
 }
@@ -1226,24 +1281,6 @@ void grim_bcr_conv_plan_free(grim_bcr_conv_plan *P) {
     if (P->d_words) (void)hipFree(P->d_words);
     if (P->d_tall) (void)hipFree(P->d_tall);
     delete P;
-}
-
-// Runs of 64 rows pay once there are about as many (tile, run) pairs as two thirds of the compute units -- below that the
-// four times as many 16-row workgroups are quicker (512 channels on one 28 x 28 map, 104 pairs: 13.6 -> 19.4 us) -- and, at
-// stride 1, for strips of some length that name each row nearly twice and more.  Measured, 16-row against 64-row runs:
-// 256 channels, 3 x 3, four 28 x 28 maps in 16 x 32 / 8 x 16 / 16 x 16 / 32 x 32 / 4 x 16 blocks (rows named 1.5 / 1.9 /
-// 2.1 / 2.7 / 2.7 times) 13.5 -> 13.7, 18.0 -> 16.1, 17.9 -> 16.5, 18.2 -> 13.8, 25.7 -> 16.4 us; 128 channels on eight
-// 56 x 56 maps 21.9 -> 26.1, 31.8 -> 29.3, 32.2 -> 29.5, 32.1 -> 26.5, 41.5 -> 30.2; 1 x 1 with 8 steps 7.1 -> 7.5.  At
-// stride 2, where a window is two loads, 128 -> 256 channels from four 56 x 56 maps 13.5 -> 11.1, 17.2 -> 12.6, 17.0 ->
-// 12.6, 17.2 -> 12.0, 21.9 -> 12.6 and its 1 x 1 shortcut of four steps 7.6 -> 6.8.
-static bool conv_on_tall_runs(const grim_bcr_conv_plan *P, int32_t batch) {
-    if (!P->tall.present) return false;
-    const int64_t Ho = (P->H + 1) / 2, Wp = ((P->W + 1) / 2 + 7) / 8 * 8;
-    const int64_t positions = P->stride == 2 ? Ho * Wp : (int64_t)P->H * P->W;
-    if ((positions + 63) / 64 * batch * P->tall.nstrips < 160) return false;
-    // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
-    if (P->stride == 1 && conv_batch_sums_as_one_image(P->A, positions, batch)) return false;
-    return P->stride == 2 || (P->tall.max_steps >= 12 && P->tall.nsteps * 7 <= P->A->gather.nsteps * 4);
 }
 
 grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev, int32_t batch, int64_t f_image_stride,
@@ -1264,7 +1301,7 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev,
                                                 static_cast<hipStream_t>(hip_stream));
         if (st != GRIM_ERR_UNSUPPORTED) return st;
     }
-    if (conv_on_tall_runs(P, batch)) {
+    if (P->tall.present && conv_on_tall_runs(P->A, P->tall_steps, P->H, P->W, P->stride, batch)) {
         const grim_status st = launch_conv_tall(P->A, P->tall, P->d_words, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
                                                 (int32_t)out_dt, ldo, static_cast<hipStream_t>(hip_stream), batch, P->stride, f_image_stride,
                                                 out_image_stride);

@@ -44,13 +44,41 @@ grim_status launch_lstm_cell(const float *, int64_t, const float *, float *, int
 grim_status launch_gru_cell(const float *, int64_t, const float *, int64_t, const float *, const float *, float *, int64_t, void *, int32_t, int64_t, int64_t, int32_t, hipStream_t) { return GRIM_ERR_DEVICE; }
 }  // namespace grim
 
-// the HIP runtime calls the host side makes (allocation and upload of a packed matrix): no device here
+// the HIP runtime calls the host side makes (allocation and upload of a packed matrix): no device here, unless a test asks for
+// one made of host memory, whose allocations can be counted and made to fail
+#include <cstdlib>
+#include <cstring>
 extern "C" {
-hipError_t hipGetDeviceCount(int *n) { if (n) *n = 0; return hipErrorNoDevice; }
-hipError_t hipGetDevice(int *d) { if (d) *d = -1; return hipErrorNoDevice; }
+static int g_device = 0, g_allocations_left = -1, g_live = 0;
+// device: 1 = a device made of host memory; allocations_left: allocations that succeed from now on (-1: all)
+void grim_stub_device(int device, int allocations_left) { g_device = device; g_allocations_left = allocations_left; }
+int grim_stub_live_allocations() { return g_live; }
+hipError_t hipGetDeviceCount(int *n) { if (n) *n = g_device; return g_device ? hipSuccess : hipErrorNoDevice; }
+hipError_t hipGetDevice(int *d) { if (d) *d = g_device ? 0 : -1; return g_device ? hipSuccess : hipErrorNoDevice; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipMalloc(void **p, size_t) { if (p) *p = nullptr; return hipErrorNoDevice; }
-hipError_t hipFree(void *) { return hipErrorNoDevice; }
-hipError_t hipMemset(void *, int, size_t) { return hipErrorNoDevice; }
-hipError_t hipMemcpy(void *, const void *, size_t, hipMemcpyKind) { return hipErrorNoDevice; }
+hipError_t hipMalloc(void **p, size_t n) {
+    *p = nullptr;
+    if (!g_device) return hipErrorNoDevice;
+    if (g_allocations_left == 0) return hipErrorOutOfMemory;
+    if (g_allocations_left > 0) --g_allocations_left;
+    *p = std::malloc(n);
+    if (*p) ++g_live;
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void *p) {
+    if (!g_device) return hipErrorNoDevice;
+    if (p) --g_live;
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemset(void *p, int v, size_t n) {
+    if (!g_device) return hipErrorNoDevice;
+    std::memset(p, v, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void *d, const void *src, size_t n, hipMemcpyKind) {
+    if (!g_device) return hipErrorNoDevice;
+    std::memcpy(d, src, n);
+    return hipSuccess;
+}
 }

@@ -1,0 +1,43 @@
+"""Convolution plans on a device made of host memory (tests/sanitize/device_stubs.cpp): what a plan allocates and what it does
+without memory for it.  Runs in the child of tests/test_sanitize_host.py; elsewhere there is no such device."""
+import pytest
+
+import bcr_inputs as gen
+import paper_2108_11033_amd as g
+
+
+@pytest.fixture
+def device():
+    lib = g.load_library()
+    if not hasattr(lib, "grim_stub_device"):
+        pytest.skip("the library of this process runs on a GPU")
+    lib.grim_stub_device(1, -1)
+    yield lib
+    lib.grim_stub_device(0, -1)
+
+
+def _matrix(M, K, BR, BC, kr, kc):
+    mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=M + K)
+    W = gen.normal_weights(M, K, gen.F16, seed=3)
+    return g.pack(W, gen.F16, BR, BC, mask.row_ptr, mask.row_idx, mask.col_ptr, mask.col_idx)
+
+
+def test_a_plan_without_memory_for_the_layout_of_64_row_runs(device):
+    """4 x 16 blocks at stride 2 ask for the second layout; its allocation failing leaves a plan on the 16-row runs."""
+    A = _matrix(128, 64 * 9, 4, 16, 2, 4)
+    live = device.grim_stub_live_allocations()
+    plan = g.ConvPlan(A, 64, 28, 28, 3, 3, 2)
+    assert device.grim_stub_live_allocations() == live + 2
+    del plan
+    assert device.grim_stub_live_allocations() == live
+    device.grim_stub_device(1, 1)
+    plan = g.ConvPlan(A, 64, 28, 28, 3, 3, 2)
+    assert device.grim_stub_live_allocations() == live + 1
+    del plan
+    device.grim_stub_device(1, 0)
+    with pytest.raises(g.GrimError) as e:
+        g.ConvPlan(A, 64, 28, 28, 3, 3, 2)
+    assert e.value.name == "GRIM_ERR_ALLOC"
+    device.grim_stub_device(1, -1)
+    A.free()
+
