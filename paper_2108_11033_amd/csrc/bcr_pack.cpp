@@ -1204,14 +1204,15 @@ static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, in
     return stride == 2 || !conv_batch_sums_as_one_image(A, positions, batch);
 }
 
-// The layout of 64-row runs, where it has fewer steps.  A plan that cannot have it (no memory) does without.
+// The layout of 64-row runs, if some batch would run on it.  A plan that cannot have it (no memory) does without.
 static void add_tall_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
     GatherLayout &L = P->tall;
     RunSteps steps;
     try {
         steps = count_run_steps<kConvTallRuns>(A);
-        if (A->M <= 16 || steps.runs == 0 || steps.total * 4 > A->gather.nsteps * 3) return;
+        // (the splits of a sum over waves follow one another with the batch: the largest stands for all that are not one image's)
+        if (!conv_on_tall_runs(A, steps, P->H, P->W, P->stride, 1 << 20)) return;
         build_gather_layout<kConvTallRuns>(A, L);
         for (uint32_t &r : L.rows) r = conv_plan_word(r, P->H, P->W, P->kh, P->kw);
     } catch (const std::bad_alloc &) {

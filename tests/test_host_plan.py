@@ -41,3 +41,16 @@ def test_a_plan_without_memory_for_the_layout_of_64_row_runs(device):
     device.grim_stub_device(1, -1)
     A.free()
 
+
+@pytest.mark.parametrize("M,cin,BR,BC,kr,kc,stride", [
+    (128, 512, 16, 32, 16, 2, 2),      # runs of 64 rows would name nearly as many columns as four of 16
+    (16, 32, 4, 16, 2, 4, 2),          # a single 16-row run
+    (128, 32, 4, 16, 2, 4, 1),         # stride 1: too few steps
+])
+def test_a_plan_holds_no_layout_it_cannot_use(device, M, cin, BR, BC, kr, kc, stride):
+    A = _matrix(M, cin * 9, BR, BC, kr, kc)
+    live = device.grim_stub_live_allocations()
+    plan = g.ConvPlan(A, cin, 28, 28, 3, 3, stride)
+    assert device.grim_stub_live_allocations() == live + 1
+    del plan
+    A.free()
