@@ -399,7 +399,7 @@ void build_gather32_layout(grim_bcr_matrix *A) {
     GatherLayout &L = A->gather32;
     L = GatherLayout();
     if (A->dtype != GRIM_F32 || A->K > 0x7fffffff || A->M > 0x7fffffff) return;
-    if (!(16 % A->BR == 0 || A->BR % 16 == 0)) return;
+    if (!(16 % A->BR == 0 || A->BR % 16 == 0) || A->BR > 64) return;         // (taller blocks: no fp32 kernel takes them)
     const float *w = reinterpret_cast<const float *>(A->weights.data());
     const int64_t nss = (A->M + 15) / 16;
     L.nstrips = nss;

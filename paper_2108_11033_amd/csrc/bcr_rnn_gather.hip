@@ -179,8 +179,8 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
 
 static bool rnn_gather_matrix_ok(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, int64_t H) {
     // the 16 gate rows of 16 units are one run: inside a strip, or across strips that are stored in original order
-    return A->gather.present && H % 16 == 0 && (A->BR % 16 == 0 ? H % A->BR == 0 : A->order_identity) && A->M <= 0x7fffffff &&
-           reinterpret_cast<uintptr_t>(X) % 2 == 0 && (A->K - 1) * ldx + N >= 8;
+    return gather_any_applies(A, X, N, ldx) && (A->K - 1) * ldx + N >= 8 && H % 16 == 0 &&
+           (A->BR % 16 == 0 ? H % A->BR == 0 : A->order_identity);
 }
 
 // A workgroup per compute unit at most: beyond that the products as a launch of their own are quicker (LSTM, 2048 units, 512

@@ -13,9 +13,11 @@ bool gather_wave_per_strip(const grim_bcr_matrix *A, int64_t pairs, int64_t pair
 bool gather_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx) {
     return A->gather.present && N >= 4 && N % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 8 == 0;
 }
-// (below 64 columns the kernel reads the last 16 bytes of X as a whole: there have to be that many)
+// (Below 64 columns the kernel reads the last 16 bytes of X as a whole: there have to be that many.  Blocks of more than 64
+// rows are taken with the aligned rows of gather_applies only.)
 bool gather_any_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx) {
-    return A->gather.present && reinterpret_cast<uintptr_t>(X) % 2 == 0 && (N >= 64 || (A->K - 1) * ldx + N >= 8);
+    return A->gather.present && reinterpret_cast<uintptr_t>(X) % 2 == 0 && (N >= 64 || (A->K - 1) * ldx + N >= 8) &&
+           (A->BR <= 64 || gather_applies(A, X, N, ldx));
 }
 
 // Bytes through one compute unit, the quantity both matrix-core kernels are bound by at these

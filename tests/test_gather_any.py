@@ -56,3 +56,50 @@ def test_long_strips_and_few_tiles(g, dtype, M, BR, BC, N, ldx_pad):
     Yref, S = oracle_product(W, X, dtype, mask)
     Y = run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, N, ldx=N + ldx_pad, ldy=N + 1)
     assert_close(Y, Yref, S, dtype, f"{dtype} {M}x{K} {BR}x{BC} N={N}")
+
+
+@pytest.mark.parametrize("dtype", [gen.F32, gen.F16, gen.BF16])
+def test_blocks_of_more_than_64_rows(g, dtype):
+    """Only the row-gathering kernels on 8-byte-aligned rows take them: the rest is refused, and leaves the output alone."""
+    import torch
+    from helpers import to_device
+    M, K, BR = 384, 64, 128
+    mask = gen.random_mask(M, K, BR, 16, (8, 64, 128), (4, 16), seed=930)
+    W = gen.normal_weights(M, K, dtype, seed=931)
+    A = pack_workload(g, W, dtype, mask)
+    for N, ldx in [(1, 1), (3, 3), (4, 4), (5, 5), (8, 8), (9, 9), (12, 12), (12, 13), (33, 33), (64, 64), (66, 66), (101, 101)]:
+        X = gen.normal_activations(K, N, dtype, seed=932)
+        if dtype != gen.F32 and N % 4 == 0 and ldx % 4 == 0:
+            Yref, S = oracle_product(W, X, dtype, mask)
+            assert_close(run_spmm(g, A, X, dtype, M, N), Yref, S, dtype, f"{dtype} BR=128 N={N}")
+            continue
+        xd = torch.zeros((K, ldx), dtype=torch.float32, device="cuda").to(to_device(X, dtype).dtype)
+        y = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+        for call in [lambda: g.spmm(A, xd, N, ldx, y, N)] + ([lambda: g.spmv(A, xd, N, ldx, y, N)] if N <= 8 else []):
+            with pytest.raises(g.GrimError) as e:
+                call()
+            assert e.value.name == "GRIM_ERR_UNSUPPORTED", (N, ldx)
+        torch.cuda.synchronize()
+        assert (y == 7.0).all()
+
+
+@pytest.mark.parametrize("batch", [5, 12])
+def test_recurrent_steps_of_blocks_of_more_than_64_rows(g, batch):
+    import torch
+    H, I, BR = 128, 64, 128
+    mats = []
+    for M, K in ((4 * H, I + H), (3 * H, I), (3 * H, H)):
+        mask = gen.random_mask(M, K, BR, 16, (8, 64, 128), (4, 16), seed=940 + K)
+        mats.append(pack_workload(g, gen.normal_weights(M, K, gen.F16, seed=941), gen.F16, mask))
+    half, full = (lambda n: torch.zeros((n, batch), dtype=torch.float16, device="cuda")), (lambda n: torch.zeros((n, batch), device="cuda"))
+    calls = [lambda: g.lstm_step(mats[0], half(I + H), batch, batch, full(4 * H), batch, None, full(H), batch, half(H), batch, full(H), batch),
+             lambda: g.gru_step(mats[1], mats[2], half(I), batch, half(H), batch, batch, full(3 * H), batch, full(3 * H), batch, None, None,
+                                full(H), batch, half(H), batch)]
+    for call in calls:
+        if batch % 4 == 0:
+            call()
+            continue
+        with pytest.raises(g.GrimError) as e:
+            call()
+        assert e.value.name == "GRIM_ERR_UNSUPPORTED"
+    torch.cuda.synchronize()
