@@ -97,8 +97,27 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     return GRIM_OK;
 }
 
+// X of fewer than the eight elements that make up a 16-byte load (one row of four columns): an output per thread
+template <int DT>
+__global__ void __launch_bounds__(256) bcr_spmm_few_elements(ExactArrays a, const int32_t *out_row, const void *X, int64_t N, int64_t ldx, float *Y,
+                                                             int64_t ldy, int64_t rows) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, sr = i / N, n = i - sr * N;
+    if (sr >= rows || out_row[sr] < 0) return;
+    float v[1];
+    exact_row<DT, 1>(a, X, N, ldx, sr, n, v);
+    Y[out_row[sr] * ldy + n] = v[0];
+}
+
 grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                                hipStream_t stream, const grim_bcr_matrix *A2, const void *X2, float *Y2) {
+    if (!A2 && gather_applies(A, X, N, ldx) && !gather_any_applies(A, X, N, ldx)) {
+        const int64_t rows = A->gather.nstrips * 16;
+        if (rows * N / 256 > 0x7ffffffe) return GRIM_ERR_SHAPE;
+        const dim3 few((unsigned)((rows * N + 255) / 256));
+        if (A->dtype == GRIM_BF16) hipLaunchKernelGGL(bcr_spmm_few_elements<GRIM_BF16>, few, dim3(256), 0, stream, exact_arrays(A), A->gather.d_out_row, X, N, ldx, Y, ldy, rows);
+        else hipLaunchKernelGGL(bcr_spmm_few_elements<GRIM_F16>, few, dim3(256), 0, stream, exact_arrays(A), A->gather.d_out_row, X, N, ldx, Y, ldy, rows);
+        return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
+    }
     GatherParams p;
     GatherForm form;
     const grim_status st = gather_setup(A, X, N, ldx, Y, ldy, A2, X2, Y2, &p, &form);

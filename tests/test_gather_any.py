@@ -103,3 +103,14 @@ def test_recurrent_steps_of_blocks_of_more_than_64_rows(g, batch):
             call()
         assert e.value.name == "GRIM_ERR_UNSUPPORTED"
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,kernel", [(96, 48, 0), (32, 16, 3), (64, 32, 3), (256, 128, 0), (192, 64, 0)])
+def test_products_of_one_row_of_four(g, dtype, M, BR, kernel):
+    """K = 1 and four columns: X is shorter than the 16 bytes the kernel loads at a time."""
+    mask = gen.random_mask(M, 1, BR, 1, (BR // 2, BR), (1,), seed=950)
+    W = gen.normal_weights(M, 1, dtype, seed=951)
+    X = gen.normal_activations(1, 4, dtype, seed=952)
+    Yref, S = oracle_product(W, X, dtype, mask)
+    assert_close(run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, 4, ldy=5, kernel=kernel), Yref, S, dtype, f"BR={BR}")
