@@ -1,7 +1,7 @@
 // Products with non-finite values of X on the kernels that multiply whole 16-row runs on the matrix cores: there a row of
 // the run that does not keep a column multiplies that row of X by zero, which an infinity or NaN turns into NaN.  The
-// kernels that include this look for such values in what they fetch; where there is one, the outputs of the (tile, run)
-// are formed from the canonical arrays instead, kept weights only, as on the vector ALUs.
+// kernels that include this look for such values in what they fetch, or for sums that are not finite (every row of the run
+// has one then); the outputs concerned are formed from the canonical arrays instead, kept weights only, as on the vector ALUs.
 #pragma once
 #include "spmm_common.hpp"
 

@@ -88,7 +88,6 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // LONGW: the waves that split a strip in the EIGHT form (eight in the kernel of its own; a caller with more waves to
 // spare may pass more: fewer steps per wave, fewer dependent batches).
 constexpr int gather_wave_lds(int nt) { return nt * 2048; }    // two step buffers of 32 rows x 16 nt columns
-constexpr int kGatherWatchBytes = 64;                          // behind them: a word per wave (WATCH forms)
 template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves>
 __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, int block_x, int block_y) {
     constexpr int NWV = EIGHT ? LONGW : 4;                     // waves of the workgroup
@@ -172,14 +171,6 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 #pragma unroll
     for (int q = 0; q < NT; ++q) tr[q] = buf + r0 * PITCH + within + (((q * 2 + cl) ^ sw0) << 4);
 
-    // WATCH: exponent bits of the piece's columns below N, and the largest exponents met at each position of a dword
-    constexpr unsigned int kExponents = BF16 ? 0x7f807f80u : 0x7c007c00u;
-    unsigned int exps[4] = {kExponents, kExponents, kExponents, kExponents}, largest = 0u;
-    if constexpr (NARROW) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-            exps[d] = kExponents & ((c * 8 + 2 * d < p.N ? 0xffffu : 0u) | (c * 8 + 2 * d + 1 < p.N ? 0xffff0000u : 0u));
-    }
     f32x4 acc[NT];
 #pragma unroll
     for (int q = 0; q < NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -264,6 +255,11 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             nhdr = ask_hdr(st);
             ndsc = desc2[(int64_t)st * 4 + kgroup];
         }
+        // WATCH forms took over from kernels with sixteen partial sums: a batch's steps are summed from zero and then added, which
+        // keeps their errors (512 x 4608 in 4 x 16 blocks, 25 steps to a wave: 1.26e-7 in one chain, 0.98e-7 before)
+        f32x4 part[NT];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
         StepRows R[SB];
         i16x8 PW[SB];
         if constexpr (!FIRST) R[0] = early;      // asked for during the batch before
@@ -291,13 +287,6 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 #pragma unroll
                 for (int i = 0; i < LI; ++i) {
                     const u32x4 v = (R[u].pad >> i) & 1u ? u32x4{0u, 0u, 0u, 0u} : R[u].rx[i];
-                    if constexpr (WATCH) {
-                        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-                        for (int d = 0; d < 4; ++d)
-                            largest = __builtin_bit_cast(unsigned int, __builtin_elementwise_max(__builtin_bit_cast(u16x2, largest),
-                                                                                                 __builtin_bit_cast(u16x2, v[d] & exps[d])));
-                    }
                     *reinterpret_cast<u32x4 *>(b + wr_off + i * (RPI * PITCH)) = v;
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -307,10 +296,15 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
                     const i16x4 lo = lds_tr_read(tr[q] + (u & 1) * (32 * PITCH));
                     const i16x4 hi = lds_tr_read(tr[NT == 4 ? q ^ 2 : q] + 4 * PITCH + (u & 1) * (32 * PITCH));
                     const i16x8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    acc[q] = mfma16<BF16>(x, PW[u], acc[q]);
+                    if constexpr (WATCH) part[q] = mfma16<BF16>(x, PW[u], part[q]);
+                    else acc[q] = mfma16<BF16>(x, PW[u], acc[q]);
                 }
                 __builtin_amdgcn_wave_barrier();
             }
+        }
+        if constexpr (WATCH) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q) { acc[q][0] += part[q][0]; acc[q][1] += part[q][1]; acc[q][2] += part[q][2]; acc[q][3] += part[q][3]; }
         }
     };
     if (s_beg < s_end) batch(s_beg, std::true_type{});
@@ -337,18 +331,28 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
         exact_row<BF16 ? GRIM_BF16 : GRIM_F16, 4>(*exact, X, p.N, p.ldx, (int64_t)t * 16 + (lane & 15), n, v);
         put(q, f32x4{v[0], v[1], v[2], v[3]});
     };
-    bool met = false;                            // this wave fetched an infinity or NaN
-    if constexpr (WATCH)
-        met = __builtin_amdgcn_ballot_w64((largest & 0xffffu) == (kExponents & 0xffffu) || (largest >> 16) == (kExponents >> 16)) != 0;
-    if constexpr (SOLO) {
-        if (WATCH && met) {
-#pragma unroll 1
-            for (int q = 0; q < NT; ++q) put_exact(q);
-            return;
-        }
-        // the wave owns the whole 16-row tile
+    // WATCH: has the lane a sum that is not finite in a column below N?  (An infinity or NaN among the rows of X a run keeps
+    // makes the sums of all 16 rows so, whether they keep it or not: no other lane needs a look.)
+    auto odd = [&](int q, const f32x4 &v) {
+        const int64_t n = n0 + q * 16 + 4 * (lane >> 4);
+        float z = 0.f;
 #pragma unroll
-        for (int q = 0; q < NT; ++q) put(q, acc[q]);
+        for (int e = 0; e < 4; ++e) z = __builtin_fmaf(!NARROW || n + e < p.N ? v[e] : 0.f, 0.f, z);
+        return z != z;
+    };
+    if constexpr (SOLO) {
+        // the wave owns the whole 16-row tile
+        unsigned int again = 0u;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            put(q, acc[q]);
+            if (WATCH && odd(q, acc[q])) again |= 1u << q;
+        }
+        if (WATCH && __builtin_amdgcn_ballot_w64(again != 0u)) {
+#pragma unroll 1
+            for (int q = 0; q < NT; ++q)
+                if ((again >> q) & 1u) put_exact(q);
+        }
         return;
     }
     // add the waves' partial tiles in wave order; wave q finishes sub-tile q.  A wave parks its
@@ -357,20 +361,9 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
     for (int q = 0; q < NT; ++q) red[wave * RPW + q * 64 + lane] = acc[q];
-    int *mets = reinterpret_cast<int *>(lds + NWV * gather_wave_lds(NT));      // WATCH: a word per wave
-    if (WATCH && lane == 0) mets[wave] = met;
     __syncthreads();
     if (wave >= NT) return;                      // the first waves finish the sub-tiles
     const int q = wave;
-    if constexpr (WATCH) {
-        int any = 0;
-#pragma unroll
-        for (int w = 0; w < NWV; ++w) any |= mets[w];
-        if (__builtin_amdgcn_readfirstlane(any)) {
-            put_exact(q);
-            return;
-        }
-    }
     // (the small-tile form's twelve: three sums of four, so that more partial tiles do not mean a longer chain of roundings)
     constexpr int CHAIN = NT == 2 && !NARROW ? 4 : NWV;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
@@ -386,6 +379,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
         else { sum[0] += s[0]; sum[1] += s[1]; sum[2] += s[2]; sum[3] += s[3]; }
     }
     put(q, sum);
+    if (WATCH && odd(q, sum)) put_exact(q);
 }
 
 constexpr int gather_waves(bool narrow, bool eight, int nt) { return !eight ? 4 : nt == 2 && !narrow ? kGatherSmallTileWaves : kGatherLongWaves; }

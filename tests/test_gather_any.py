@@ -114,3 +114,29 @@ def test_products_of_one_row_of_four(g, dtype, M, BR, kernel):
     X = gen.normal_activations(1, 4, dtype, seed=952)
     Yref, S = oracle_product(W, X, dtype, mask)
     assert_close(run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, 4, ldy=5, kernel=kernel), Yref, S, dtype, f"BR={BR}")
+
+
+@pytest.mark.parametrize("M,K,BR,BC,kr,kc,N", [(256, 1152, 1, 16, 1, 4, 9999),      # a wave per run, long chains of multiplies
+                                               (256, 1152, 4, 16, 2, 4, 9999),
+                                               (512, 4608, 64, 64, 16, 16, 3135),   # four waves to a run
+                                               (512, 4608, 4, 16, 2, 4, 1001),
+                                               (512, 4096, 32, 32, 32, 32, 1)])     # one column, dense blocks
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+def test_no_less_exact_than_the_vector_alus(g, dtype, M, K, BR, BC, kr, kc, N):
+    """These operands used to be multiplied on the vector ALUs in sixteen partial sums (or more).  The distance from a 64-bit
+    product is no larger now; the two differ by a few per cent either way."""
+    import torch
+    from helpers import to_device
+    mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=960)
+    W = gen.normal_weights(M, K, dtype, seed=961)
+    X = gen.normal_activations(K, N, dtype, seed=962, relu=N > 1)
+    A = pack_workload(g, W, dtype, mask)
+    kept = torch.from_numpy(gen.storage_to_f64(A.unpack(), dtype)).cuda()
+    ref = kept @ torch.from_numpy(gen.storage_to_f64(X, dtype)).cuda()
+    xd, y = to_device(X, dtype), torch.empty((M, N), dtype=torch.float32, device="cuda")
+    err = []
+    for kernel in (0, 1):
+        g.spmm(A, xd, N, N, y, N, kernel=kernel)
+        torch.cuda.synchronize()
+        err.append(float((y.double() - ref).norm() / ref.norm()))
+    assert err[0] <= 1.15 * err[1], err
