@@ -1,5 +1,7 @@
 // One step of a recurrent layer for a batch of columns in one launch on the matrix cores: the gate product(s) with the
 // cell in the epilogue (Section 3.1: an RNN layer is one product per time step; Section 6.3 times the GRU step by step).
+#include <algorithm>
+
 #include "rnn_cell.hpp"
 #include "spmm_exact.hpp"
 
@@ -38,16 +40,16 @@ struct __attribute__((packed, aligned(2))) RnnPiece {
     unsigned int d[4];
 };
 
-template <bool BF16, int CELL>
+// SB: steps a wave has in flight (steps past its last are fetched too: few where a run has few)
+template <bool BF16, int CELL, int SB>
 __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGatherParams p) {
     constexpr int GATES = CELL == 1 ? 4 : 3, NRUN = CELL == 1 ? 4 : 6, WPR = CELL == 1 ? 4 : 2, NWV = NRUN * WPR;
     constexpr int DT = BF16 ? GRIM_BF16 : GRIM_F16;
-    constexpr int PITCH = 32, SB = 6;            // bytes of a staged row; steps a wave has in flight
+    constexpr int PITCH = 32;                    // bytes of a staged row
     __shared__ __attribute__((aligned(16))) char lds[NWV * 2048];
-    __shared__ int odd_values[NWV];              // per wave: it met an infinity or NaN
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int run = wave / WPR, part = wave % WPR, mi = CELL == 2 ? run / 3 : 0, gate = CELL == 2 ? run % 3 : run;
+    const int run = wave / WPR, share = wave % WPR, mi = CELL == 2 ? run / 3 : 0, gate = CELL == 2 ? run % 3 : run;
     const RnnGatherMatrix &A = p.m[mi];
     const int unit0 = blockIdx.x * 16, n0 = blockIdx.y * 16, N = p.N;
     // stored run of the 16 gate rows from original row `row` on (in one strip, or strips stored in original order)
@@ -57,7 +59,7 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
     };
     const int t = stored_run(A, gate * p.H + unit0);
     const int g0 = A.usteps ? t * A.usteps : A.sptr[t], nst = A.usteps ? A.usteps : A.sptr[t + 1] - g0;
-    const int s_beg = g0 + nst * part / WPR, s_end = g0 + nst * (part + 1) / WPR;
+    const int s_beg = g0 + nst * share / WPR, s_end = g0 + nst * (share + 1) / WPR;
 
     // the cell's threads: (unit, column); their state and biases are asked for now
     const int cu = tid >> 4, cn = n0 + (tid & 15);
@@ -78,10 +80,6 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
     const int rs = lane >> 1, c = lane & 1, col = n0 + c * 8;
     const unsigned short *xcol = A.X + (col < N ? col : n0);
     const unsigned short *x_last = A.X + ((int64_t)(A.K - 1) * A.ldx + N - 8);
-    constexpr unsigned int kExponents = BF16 ? 0x7f807f80u : 0x7c007c00u;
-    unsigned int exps[4], largest = 0u;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) exps[d] = kExponents & ((col + 2 * d < N ? 0xffffu : 0u) | (col + 2 * d + 1 < N ? 0xffff0000u : 0u));
     char *buf = lds + wave * 2048;
     const int i16 = lane & 15, kgroup = lane >> 4, qd = i16 >> 2;
     const unsigned int below = (1u << i16) - 1u;
@@ -101,6 +99,7 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
         }
         u32x4 rx[SB];
         i16x8 w[SB];
+        f32x4 part = {0.f, 0.f, 0.f, 0.f};       // (half a batch is summed apart: see bcr_spmm_gather)
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             const bool pad = row[u] == 0xffffffffu;
@@ -125,30 +124,24 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
                     v = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
                 }
                 if (flags[u] >> 31) v = u32x4{0u, 0u, 0u, 0u};
-                typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    largest = __builtin_bit_cast(unsigned int, __builtin_elementwise_max(__builtin_bit_cast(u16x2, largest),
-                                                                                         __builtin_bit_cast(u16x2, v[d] & exps[d])));
                 char *b = buf + (u & 1) * 1024;
                 *reinterpret_cast<u32x4 *>(b + rs * PITCH + c * 16) = v;
                 __builtin_amdgcn_wave_barrier();
                 const i16x4 lo = lds_tr_read(tr + (u & 1) * 1024), hi = lds_tr_read(tr + 4 * PITCH + (u & 1) * 1024);
-                acc = mfma16<BF16>(i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, w[u], acc);
+                part = mfma16<BF16>(i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, w[u], part);
                 __builtin_amdgcn_wave_barrier();
+            }
+            if (u == SB - 1 || (SB > 4 && u == SB / 2 - 1)) {
+                acc[0] += part[0]; acc[1] += part[1]; acc[2] += part[2]; acc[3] += part[3];
+                part = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         }
     }
-    const bool met = __builtin_amdgcn_ballot_w64((largest & 0xffffu) == (kExponents & 0xffffu) || (largest >> 16) == (kExponents >> 16)) != 0;
     // lane: gate row lane % 16, columns 4 (lane / 16) .. + 3; the partial tile goes into the wave's own idle buffers
     *reinterpret_cast<f32x4 *>(buf + lane * 16) = acc;
-    if (lane == 0) odd_values[wave] = met;
     __syncthreads();
     if (!cell_thread) return;
     const int at = (cu + 16 * ((tid & 15) >> 2)) * 16 + (tid & 3) * 4;
-    int any = 0;
-#pragma unroll
-    for (int w = 0; w < NWV; ++w) any |= odd_values[w];
     float sum[6];
 #pragma unroll
     for (int j = 0; j < NRUN; ++j) {
@@ -157,7 +150,7 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
         for (int w = 1; w < WPR; ++w) s += *reinterpret_cast<const float *>(lds + (j * WPR + w) * 2048 + at);
         const RnnGatherMatrix &M = p.m[CELL == 2 ? j / 3 : 0];
         const int64_t grow = (int64_t)(CELL == 2 ? j % 3 : j) * p.H + unit;
-        if (any) {
+        if (__builtin_fmaf(s, 0.f, 0.f) != 0.f) {      // not finite: is there an infinity or NaN that the row keeps?
             float e[1];
             exact_row<DT, 1>(M.exact, M.X, N, M.ldx, (int64_t)stored_run(M, (int)(grow - cu)) * 16 + cu, cn, e);
             s = e[0];
@@ -208,13 +201,17 @@ grim_status launch_rnn_gather(const grim_bcr_matrix *A, const void *X, int64_t l
     p.h = cell.h; p.ldh = cell.ldh;
     p.H = cell.H; p.N = batch; p.hdt = cell.hdt;
     const dim3 grid((unsigned)(cell.H / 16), (unsigned)((batch + 15) / 16));
-    if (A2) {
-        if (A->dtype == GRIM_BF16) hipLaunchKernelGGL((bcr_rnn_gather<true, 2>), grid, dim3(768), 0, stream, p);
-        else hipLaunchKernelGGL((bcr_rnn_gather<false, 2>), grid, dim3(768), 0, stream, p);
-    } else {
-        if (A->dtype == GRIM_BF16) hipLaunchKernelGGL((bcr_rnn_gather<true, 1>), grid, dim3(1024), 0, stream, p);
-        else hipLaunchKernelGGL((bcr_rnn_gather<false, 1>), grid, dim3(1024), 0, stream, p);
-    }
+    const int share = (std::max(A->gather.max_steps, A2 ? A2->gather.max_steps : 0) + (A2 ? 1 : 3)) / (A2 ? 2 : 4);     // steps of a wave
+#define GRIM_RNN(BF, CE, TH)                                                                                              \
+    do {                                                                                                                  \
+        if (share <= 2) hipLaunchKernelGGL((bcr_rnn_gather<BF, CE, 2>), grid, dim3(TH), 0, stream, p);                    \
+        else if (share <= 3) hipLaunchKernelGGL((bcr_rnn_gather<BF, CE, 3>), grid, dim3(TH), 0, stream, p);               \
+        else if (share > 6 && share <= 8) hipLaunchKernelGGL((bcr_rnn_gather<BF, CE, 8>), grid, dim3(TH), 0, stream, p);  \
+        else hipLaunchKernelGGL((bcr_rnn_gather<BF, CE, 6>), grid, dim3(TH), 0, stream, p);                               \
+    } while (0)
+    if (A2) { if (A->dtype == GRIM_BF16) GRIM_RNN(true, 2, 768); else GRIM_RNN(false, 2, 768); }
+    else { if (A->dtype == GRIM_BF16) GRIM_RNN(true, 1, 1024); else GRIM_RNN(false, 1, 1024); }
+#undef GRIM_RNN
     return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
 }
 

@@ -303,6 +303,9 @@ def test_gru_step_of_several_columns_in_one_launch(dtype, H, BR, kr, kc, B, ld):
     (96, 32, 32, (8, 16), (4, 32), 64, 64),
     (64, 4096, 32, (8, 16), (16, 32), 9, 9),          # more than one batch of steps per wave
     (16, 32, 16, (4, 16), (8, 32), 1, 1),             # one column: the pieces of the last rows end behind X
+    # dense blocks, a step per 32 inputs: two, three, six and eight steps of a wave in flight, and one more than that
+    (32, 128, 32, (32,), (32,), 8, 8), (32, 192, 32, (32,), (32,), 5, 5), (32, 224, 32, (32,), (32,), 9, 9), (32, 256, 32, (32,), (32,), 7, 8),
+    (32, 384, 32, (32,), (32,), 16, 16), (32, 448, 32, (32,), (32,), 3, 3), (32, 992, 32, (32,), (32,), 5, 7), (32, 1024, 32, (32,), (32,), 6, 6),
 ])
 @pytest.mark.parametrize("odd", [None, np.inf, np.nan])
 def test_steps_of_a_batch_on_the_matrix_cores(dtype, H, I, BR, kr, kc, B, ld, odd):
