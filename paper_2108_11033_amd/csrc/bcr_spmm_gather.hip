@@ -1,3 +1,5 @@
+#include <algorithm>
+
 #include "spmm_gather_kernel.hpp"
 
 namespace grim {
@@ -80,7 +82,11 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     // save (12.0 -> 12.4 us on a 2304-row product, five-step strips 15.5 -> 24 us).
     p.touch = !narrow && A->gather.max_steps >= 40 ? 1 : 0;
     const bool solo = !narrow && !small_tiles && gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 1536);
-    const bool eight = !solo && A->gather.max_steps >= 16 && (narrow || small_tiles || (int64_t)p.ntiles * p.nbr <= 256);
+    // Narrow tiles: eight waves only where four need more than a batch of steps and every workgroup has a compute unit --
+    // 4608 x 2048 at four columns, 288 workgroups: 6.5 us with eight, 4.65 with four; 2048 x 2048 at nine, 20 steps: 5.7, 4.3.
+    const int64_t pairs = (int64_t)p.ntiles * p.nbr * (A2 ? 2 : 1);
+    const int longest = std::max(A->gather.max_steps, A2 ? A2->gather.max_steps : 0);
+    const bool eight = !solo && (narrow ? longest > 4 * gather_narrow_steps(nt) && pairs <= 256 : longest >= 16 && (small_tiles || pairs <= 256));
     const int64_t per_tile = solo ? (p.nbr + 3) / 4 : p.nbr;
     if (((int64_t)p.ntiles + 7) / 8 * 8 * per_tile > 0x7fffffff) return GRIM_ERR_SHAPE;
     int64_t nwg = 0;
@@ -90,6 +96,8 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     form->solo = solo;
     form->eight = eight;
     form->nt = nt;
+    // (steps past a wave's share are fetched too: no more than a short strip has)
+    form->steps = longest <= 8 ? 2 : longest <= 16 ? 4 : 8;
     form->aligned = N % 8 == 0 && ldx % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
                     (!A2 || reinterpret_cast<uintptr_t>(X2) % 16 == 0);
     form->nwg = nwg;
@@ -127,9 +135,9 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
     const int waves = gather_waves(narrow, eight, form.nt);
     const size_t lds = (size_t)waves * gather_wave_lds(form.nt);
     const dim3 grid((unsigned)nwg, A2 ? 2u : 1u), block(waves * 64);
-#define GRIM_GATHER(BF, AL, NR, SO, EI, NT)                                                                              \
+#define GRIM_GATHER(BF, AL, NR, SO, EI, ...)                                                                              \
     do {                                                                                                             \
-        auto kern = bcr_spmm_gather<BF, AL, NR, SO, EI, NT>;                                                          \
+        auto kern = bcr_spmm_gather<BF, AL, NR, SO, EI, __VA_ARGS__>;                                                          \
         static std::atomic<bool> attr_done{false};   /* raising a kernel's LDS limit is needed once per process */  \
         if (lds > 64 * 1024 && !attr_done) {                                                                         \
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -142,7 +150,12 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
         hipLaunchKernelGGL(kern, grid, block, lds, stream, p);                                                       \
     } while (0)
 #define GRIM_GATHER_AL(BF, AL)                                                                                       \
-    if (narrow && form.nt == 1) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 1); else GRIM_GATHER(BF, AL, true, false, false, 1); } \
+    if (narrow && form.nt == 1) {                                                                                    \
+        if (eight) GRIM_GATHER(BF, AL, true, false, true, 1);                                                        \
+        else if (form.steps == 2) GRIM_GATHER(BF, AL, true, false, false, 1, 2);                                     \
+        else if (form.steps == 4) GRIM_GATHER(BF, AL, true, false, false, 1, 4);                                     \
+        else GRIM_GATHER(BF, AL, true, false, false, 1);                                                             \
+    }                                                                                                                \
     else if (narrow && form.nt == 2) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 2); else GRIM_GATHER(BF, AL, true, false, false, 2); } \
     else if (narrow) { if (eight) GRIM_GATHER(BF, AL, true, false, true, 4); else GRIM_GATHER(BF, AL, true, false, false, 4); } \
     else if (form.nt == 2) GRIM_GATHER(BF, AL, false, false, true, 2);                                               \

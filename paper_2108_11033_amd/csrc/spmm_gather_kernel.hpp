@@ -60,6 +60,7 @@ struct GatherParams {
 struct GatherForm {
     bool aligned, narrow, solo, eight;
     int nt;                   // sub-tiles of 16 columns per tile
+    int steps;                // steps in flight of a 16-column tile on four waves
     int64_t nwg;
 };
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
@@ -87,8 +88,10 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // Its first NWV waves must call it together; `lds` = NWV * gather_wave_lds(NT) bytes of workgroup memory.
 // LONGW: the waves that split a strip in the EIGHT form (eight in the kernel of its own; a caller with more waves to
 // spare may pass more: fewer steps per wave, fewer dependent batches).
+constexpr int gather_narrow_steps(int nt) { return nt == 1 ? 8 : 4; }
 constexpr int gather_wave_lds(int nt) { return nt * 2048; }    // two step buffers of 32 rows x 16 nt columns
-template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves>
+// STEPS: steps a wave has in flight, where the form has a choice (0: as its registers allow).
+template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves, int STEPS = 0>
 __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, int block_x, int block_y) {
     constexpr int NWV = EIGHT ? LONGW : 4;                     // waves of the workgroup
     constexpr int TN = NT * 16, PITCH = TN * 2, CPR = 2 * NT;  // columns, bytes and 16-byte pieces of a staged row
@@ -96,7 +99,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     // forms of operands that other kernels used to take, which multiply kept weights only: an infinity or NaN in X must
     // not reach the rows of the run that do not keep its column
     constexpr bool WATCH = NARROW || !ALIGNED;
-    constexpr int SB = NT == 1 ? 8 : !NARROW && (NT == 2 || (WATCH && !EIGHT)) ? 3 : 4;      // steps a wave has in flight (as its registers allow)
+    constexpr int SB = STEPS ? STEPS : NARROW ? gather_narrow_steps(NT) : NT == 2 || (WATCH && !EIGHT) ? 3 : 4;
     static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
     // workgroup -> (tile, stored strip, or four of them for SOLO)
     const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -255,7 +258,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             nhdr = ask_hdr(st);
             ndsc = desc2[(int64_t)st * 4 + kgroup];
         }
-        // WATCH forms took over from kernels with sixteen partial sums: a batch's steps are summed from zero and then added, which
+        // WATCH forms took over from kernels with sixteen partial sums: a batch's steps (half of eight) are summed from zero and then added, which
         // keeps their errors (512 x 4608 in 4 x 16 blocks, 25 steps to a wave: 1.26e-7 in one chain, 0.98e-7 before)
         f32x4 part[NT];
 #pragma unroll
@@ -301,10 +304,13 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-        }
-        if constexpr (WATCH) {
+            if (WATCH && (u == SB - 1 || (SB > 4 && u == SB / 2 - 1))) {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) { acc[q][0] += part[q][0]; acc[q][1] += part[q][1]; acc[q][2] += part[q][2]; acc[q][3] += part[q][3]; }
+                for (int q = 0; q < NT; ++q) {
+                    acc[q][0] += part[q][0]; acc[q][1] += part[q][1]; acc[q][2] += part[q][2]; acc[q][3] += part[q][3];
+                    part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
         }
     };
     if (s_beg < s_end) batch(s_beg, std::true_type{});
@@ -383,10 +389,10 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 }
 
 constexpr int gather_waves(bool narrow, bool eight, int nt) { return !eight ? 4 : nt == 2 && !narrow ? kGatherSmallTileWaves : kGatherLongWaves; }
-template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT>
+template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT, int STEPS = 0>
 __global__ void __launch_bounds__((gather_waves(NARROW, EIGHT, NT) * 64), (EIGHT ? 2 : NARROW ? 2 : 4)) bcr_spmm_gather(GatherParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    gather_body<BF16, ALIGNED, NARROW, SOLO, EIGHT, NT, gather_waves(NARROW, EIGHT, NT)>(p, lds, blockIdx.x, blockIdx.y);
+    gather_body<BF16, ALIGNED, NARROW, SOLO, EIGHT, NT, gather_waves(NARROW, EIGHT, NT), STEPS>(p, lds, blockIdx.x, blockIdx.y);
 }
 
 }  // namespace grim

@@ -140,3 +140,18 @@ def test_no_less_exact_than_the_vector_alus(g, dtype, M, K, BR, BC, kr, kc, N):
         torch.cuda.synchronize()
         err.append(float((y.double() - ref).norm() / ref.norm()))
     assert err[0] <= 1.15 * err[1], err
+
+
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("steps", [1, 2, 8, 9, 16, 17, 32, 33, 65])
+@pytest.mark.parametrize("N", [8, 9, 15, 17, 33])
+def test_narrow_tiles_by_length_of_the_strips(g, dtype, steps, N):
+    """Dense blocks, a step per 32 columns of the matrix: the steps in flight and the waves of narrow tiles change at 8, 16 and
+    32 steps (16-column tiles) and at 16 (wider ones); a matrix with more strips than compute units keeps four waves."""
+    for M in (64, 4128) if N == 9 and steps in (17, 33) else (64,):
+        K = 32 * steps
+        mask = gen.random_mask(M, K, 16, 32, (16,), (32,), seed=970)
+        W = gen.normal_weights(M, K, dtype, seed=971)
+        X = gen.normal_activations(K, N, dtype, seed=972)
+        Yref, S = oracle_product(W, X, dtype, mask)
+        assert_close(run_spmm(g, pack_workload(g, W, dtype, mask), X, dtype, M, N), Yref, S, dtype, f"{M}x{K} N={N}")
