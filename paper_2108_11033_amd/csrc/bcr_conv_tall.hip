@@ -165,12 +165,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
             if (__builtin_amdgcn_ballot_w64(moved)) {        // (first or last channel; what lies outside the map is masked)
 #pragma unroll
                 for (int i = 0; i < LI * LW; ++i) {
-                    const u32x4 f = XW[u][i];
-                    unsigned __int128 x = (unsigned __int128)f[0] | (unsigned __int128)f[1] << 32 |
-                                          (unsigned __int128)f[2] << 64 | (unsigned __int128)f[3] << 96;
-                    const int d = off[i];
-                    x = d >= 8 || d <= -8 ? (unsigned __int128)0 : d > 0 ? x >> (16 * d) : x << (16 * -d);
-                    XW[u][i] = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
+                    XW[u][i] = conv_shift(XW[u][i], off[i]);
                 }
             }
         }

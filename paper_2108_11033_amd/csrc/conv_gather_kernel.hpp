@@ -136,6 +136,20 @@ struct __attribute__((packed, aligned(4))) ConvWindow {
     unsigned int d[4];
 };
 
+// Sixteen bytes fetched d elements before (d > 0) or behind the place they are wanted from, moved there: eight dwords, four of
+// them zero, shifted down by 0 .. 7 elements.
+__device__ __forceinline__ u32x4 conv_shift(const u32x4 &f, int d) {
+    const bool none = d >= 8 || d <= -8, up = d < 0;
+    const int e = up ? d + 8 : d;
+    const u32x4 zero = {0u, 0u, 0u, 0u}, lo = none || up ? zero : f, hi = !none && up ? f : zero;
+    const unsigned int a0 = e & 4 ? lo[2] : lo[0], a1 = e & 4 ? lo[3] : lo[1], a2 = e & 4 ? hi[0] : lo[2], a3 = e & 4 ? hi[1] : lo[3],
+                       a4 = e & 4 ? hi[2] : hi[0], a5 = e & 4 ? hi[3] : hi[1];
+    const unsigned int b0 = e & 2 ? a1 : a0, b1 = e & 2 ? a2 : a1, b2 = e & 2 ? a3 : a2, b3 = e & 2 ? a4 : a3, b4 = e & 2 ? a5 : a4;
+    const unsigned int sh = (e & 1) * 16u;
+    return u32x4{__builtin_amdgcn_alignbit(b1, b0, sh), __builtin_amdgcn_alignbit(b2, b1, sh), __builtin_amdgcn_alignbit(b3, b2, sh),
+                 __builtin_amdgcn_alignbit(b4, b3, sh)};
+}
+
 constexpr int kConvMaxTaps = 31;   // 5 bits of the packed (tap, window start) word, one value left for padding slots
 constexpr int kConvTableBytes = (kConvMaxTaps + 1) * 8 * 16;   // validity masks, behind the waves' step buffers
 
@@ -314,15 +328,19 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                     const int odd = e0 & 1;
                     vsel[u] |= (sel | (unsigned int)odd << 7) << (8 * i);
                     int ea = e0 - odd;
-                    if constexpr (SAFE) {
-                        const bool edge = e0 < 0 || (S2 ? ea + 8 : e0) > emax;
+                    if constexpr (SAFE && !S2) {
+                        const bool edge = e0 < 0 || e0 > emax;
                         edge_any |= edge;
                         ea = edge ? 0 : ea;
                     }
 #pragma unroll
                     for (int l = 0; l < LW; ++l) {
-                        // (byte offset below 2^31; a map of fewer than 16 elements: every window is put together below)
-                        const int el = SAFE && l > 0 && ea + 8 > emax ? 0 : ea + 8 * l;
+                        int el = ea + 8 * l;                             // (byte offset below 2^31)
+                        if constexpr (SAFE && S2) {
+                            const int ec = el < 0 ? 0 : el > emax ? emax : el;
+                            edge_any |= ec != el;
+                            el = ec;
+                        }
                         ConvWindow wv;
                         __builtin_memcpy(&wv, Fb + (unsigned int)(el * 2), 16);
                         RX[u][i][l] = u32x4{wv.d[0], wv.d[1], wv.d[2], wv.d[3]};
@@ -337,20 +355,25 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                         for (int i = 0; i < LI; ++i) {
                             unsigned int sel;
                             const int e0 = piece(u, i, sel);
-                            if (e0 < 0 || (S2 ? (e0 & ~1) + 8 : e0) > emax) {
-                                // the same elements the common path fetches (one early for an odd start), so
-                                // that the lane's neighbours find what they expect in its first dword
+                            if constexpr (S2) {
+                                // moved loads are shifted back into place (element by element the loads of a map's edge cost
+                                // a call with few steps a microsecond); what lies outside the map is masked
 #pragma unroll
                                 for (int l = 0; l < LW; ++l) {
-                                    unsigned int d[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                                    for (int j = 0; j < 8; ++j) {
-                                        const int e = (e0 & ~1) + 8 * l + j;
-                                        const unsigned int v = e >= 0 && e < p.total ? Fimg[e] : 0u;
-                                        d[j >> 1] |= v << ((j & 1) * 16);
-                                    }
-                                    RX[u][i][l] = u32x4{d[0], d[1], d[2], d[3]};
+                                    const int el = (e0 & ~1) + 8 * l, d = el - (el < 0 ? 0 : el > emax ? emax : el);
+                                    RX[u][i][l] = conv_shift(RX[u][i][l], d);
                                 }
+                            } else if (e0 < 0 || e0 > emax) {
+                                // the same elements the common path fetches (one early for an odd start), so
+                                // that the lane's neighbours find what they expect in its first dword
+                                unsigned int d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                                for (int j = 0; j < 8; ++j) {
+                                    const int e = (e0 & ~1) + j;
+                                    const unsigned int v = e >= 0 && e < p.total ? Fimg[e] : 0u;
+                                    d[j >> 1] |= v << ((j & 1) * 16);
+                                }
+                                RX[u][i][0] = u32x4{d[0], d[1], d[2], d[3]};
                             }
                         }
                     }
