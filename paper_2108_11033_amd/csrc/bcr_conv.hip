@@ -16,25 +16,28 @@ uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw
 static int conv_share(const grim_bcr_matrix *A) { return (A->gather.max_steps + kConvLongWaves - 1) / kConvLongWaves; }
 
 // 32-position tiles (two sub-tiles of 16) for maps of 14 x 14 and less, where 64-position tiles leave compute units without a
-// workgroup, if a wave's share of a strip's steps is one batch: of three steps, or (stride 1) of six where 64-position tiles
-// would take two batches (72 steps at 14 x 14: 12.0 -> 9.4 us; 36 steps at stride 2 onto 7 x 7: 11.9 -> 7.5)
+// workgroup.  Stride 1: if a wave's share of a strip's steps is one batch of six where 64-position tiles would take two (72 steps
+// at 14 x 14: 12.0 -> 9.4 us).  Stride 2, whose 64-position tiles have two steps in flight against three: once four waves of
+// those need a second batch (36 steps onto 7 x 7: 11.9 -> 7.5 us, 12 steps onto 7 x 7 8.0 -> 6.8, 54 steps 15.3 -> 11.7).
 static int conv_subtiles(const grim_bcr_matrix *A, int64_t positions, int32_t batch, int32_t stride, bool planned) {
-    return planned && A->gather.max_steps >= 16 && conv_share(A) <= (stride == 2 ? 3 : 6) &&
-                   (positions + 31) / 32 * batch * (int64_t)A->gather.nstrips <= 256 ? 2 : 4;
+    const bool long_enough = stride == 2 ? A->gather.max_steps > 8 : A->gather.max_steps >= 16 && conv_share(A) <= 6;
+    return planned && long_enough && (positions + 31) / 32 * batch * (int64_t)A->gather.nstrips <= 256 ? 2 : 4;
 }
 
 // Waves that split a strip's steps, by the number of (tile, strip) pairs: the launch forms of the row-gathering kernel (one
-// wave: a pair per wave); long strips and few pairs: twelve up to 256 pairs (one workgroup per compute unit), eight up to 512
-// (two per compute unit; 28 x 28 layers: 11.0 -> 9.4 us with 18 steps, 14.1 -> 13.3 us with 36)
-static int conv_strip_waves(const grim_bcr_matrix *A, int nt, int64_t pairs) {
+// wave: a pair per wave); few pairs and strips of more than a batch of four waves: twelve up to 256 pairs (one workgroup per
+// compute unit), eight up to 512 (two per compute unit; 28 x 28 layers: 11.0 -> 9.4 us with 18 steps, 14.1 -> 13.3 us with 36;
+// 13 steps on three 9 x 9 maps 12.3 -> 10.4).  At stride 2 four waves are as quick up to 15 steps.
+static int conv_strip_waves(const grim_bcr_matrix *A, int nt, int64_t pairs, int32_t stride) {
     if (gather_wave_per_strip(A, pairs, 4096)) return 1;
-    return A->gather.max_steps < 16 ? 4 : nt == 2 || pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 4;
+    if (nt == 2) return kConvLongWaves;
+    return A->gather.max_steps <= (stride == 2 ? 15 : 12) ? 4 : pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 4;
 }
 
 bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch) {
     const int64_t tiles = (positions + 63) / 64 * (int64_t)A->gather.nstrips;
     const int nt = conv_subtiles(A, positions, batch, 1, true), nt_one = conv_subtiles(A, positions, 1, 1, true);
-    return conv_strip_waves(A, nt, tiles * batch) == conv_strip_waves(A, nt_one, tiles);
+    return conv_strip_waves(A, nt, tiles * batch, 1) == conv_strip_waves(A, nt_one, tiles, 1);
 }
 
 grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw,
@@ -95,7 +98,7 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
     const int esz_out = odt == GRIM_F32 ? 4 : 2;
     p.yvec = (reinterpret_cast<uintptr_t>(Y) % (odt == GRIM_F32 ? 16 : 8) == 0 && ldy % 4 == 0 && (stride == 1 ? N : p.Wo) % 4 == 0 &&
               (batch == 1 || (y_img_stride * esz_out) % (odt == GRIM_F32 ? 16 : 8) == 0)) ? 4 : 1;
-    const int waves = conv_strip_waves(A, nt, (int64_t)p.ntiles * p.nbr);
+    const int waves = conv_strip_waves(A, nt, (int64_t)p.ntiles * p.nbr, stride);
     const bool solo = waves == 1;
     const int longw = waves > 4 ? waves : 0;
     const int64_t per_tile = solo ? (p.nbr + 3) / 4 : p.nbr;

@@ -768,3 +768,22 @@ def test_conv_plan_writes_the_bits_of_the_unplanned_convolution(dtype, M, BR, BC
     Y = _run_plan(g, A, F, dtype, M, kh, kh, 1)
     for b in range(B):
         assert np.array_equal(_run(g, A, F[b], dtype, M, cin, H, W, kh, kh), Y[b].astype(np.float32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("steps", [2, 8, 9, 12, 13, 15, 16, 37])
+@pytest.mark.parametrize("H,W,stride,B", [(13, 11, 1, 1), (13, 11, 2, 1), (23, 21, 1, 12), (23, 21, 2, 12)])
+def test_conv_plan_by_length_of_the_strips(dtype, steps, H, W, stride, B):
+    """Dense 1 x 1 layers, a step per 32 input channels: waves and tile widths change at 8, 12 and 15 steps, for few tiles and for
+    more than 256 of them."""
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload, TOL
+    M, cin = 48, 32 * steps
+    mask = gen.full_mask(M, cin, 16, 32)
+    Wt = gen.normal_weights(M, cin, dtype, seed=881)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=882, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
+    Y = _run_plan(g, pack_workload(g, Wt, dtype, mask), F, dtype, M, 1, 1, stride)
+    Yref, S = conv_ref.conv2d(Wm, F64, 1, 1, stride), conv_ref.conv2d(np.abs(Wm), np.abs(F64), 1, 1, stride)
+    assert (np.abs(Y - Yref) <= TOL[dtype] * S).all()
