@@ -181,6 +181,11 @@ static bool rnn_gather_matrix_ok(const grim_bcr_matrix *A, const void *X, int64_
 bool rnn_gather_applies(const grim_bcr_matrix *A, const void *X, int64_t ldx, const grim_bcr_matrix *A2, const void *X2, int64_t ldx2,
                         int64_t H, int32_t batch) {
     if (batch < 1 || batch > 64 || H / 16 * ((batch + 15) / 16) > 256) return false;
+    // (an LSTM's long runs on 56 and 64 aligned columns, which the products take as one tile: 1024 units and inputs in 8 x 32
+    // blocks, 56 columns 9.7 us as two launches, 10.4 here; 256 units, 1024 inputs, 64 columns 7.1 and 7.5)
+    if (!A2 && batch >= 56 && batch % 8 == 0 && ldx % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
+        (batch == 64 ? A->K >= 1024 : A->gather.max_steps > 24))
+        return false;
     return rnn_gather_matrix_ok(A, X, batch, ldx, H) && (!A2 || (A->dtype == A2->dtype && rnn_gather_matrix_ok(A2, X2, batch, ldx2, H)));
 }
 
