@@ -1,5 +1,7 @@
 // Row-gathering SpMM kernel for fp32: Y = W_bcr * X (Section 3.1; Section 4.4: the rows of X a block keeps are loaded once
 // and reused by all of its kept rows) on v_mfma_f32_16x16x4_f32, whose products and sums are fp32 multiply-adds.
+#include <algorithm>
+
 #include "spmm_exact.hpp"
 
 namespace grim {
@@ -16,7 +18,7 @@ namespace grim {
 // columns 4 NT kg + NT r + q (r, q < 4, NT) of one output row: contiguous.
 //
 // Bound: rows of X through L2 and the vector L1 (each run fetches the rows it keeps: 58 MB where X is 14 MB, 256 x 1152 in
-// 16 x 32 blocks at 3136 columns), then MFMA, 32 cycles each, 64 a step: 2.9 us there.  That product takes 11.7 us, on the
+// 16 x 32 blocks at 3136 columns), then MFMA, 32 cycles each, 16 a step: 2.9 us there.  That product takes 11.7 us, on the
 // vector ALUs 46.6; 512 x 4608 of mixed rates at 777 columns 25 against 129, 64 x 288 in 4 x 16 blocks at 20000 columns
 // 15.8 against 104, 256 x 256 at 64 columns 3.9 against 5.8.
 struct Gather32Params {
@@ -84,8 +86,24 @@ __global__ void __launch_bounds__(NWV * 64, 4) bcr_spmm_gather32(Gather32Params 
             dsc[u] = desc2[(int64_t)st * 4 + kg];
         }
     };
+    // Long runs: every eight batches the sums so far are added to the wave's part of `red`, for no longer chain of additions than
+    // the vector ALUs' (64 x 16384, 1024 steps over eight waves: 2.1e-7 in one chain, 1.45e-7 there).
+    int batches = 0;
+    bool folded = false;
+    auto fold = [&]() {
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            f32x4 &r = red[(wave * NT + q) * 64 + lane];
+            if (folded) { acc[q][0] += r[0]; acc[q][1] += r[1]; acc[q][2] += r[2]; acc[q][3] += r[3]; }
+            r = acc[q];
+            acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        folded = true;
+    };
     if (s_beg < s_end) ask_headers(s_beg);
     for (int s = s_beg; s < s_end; s += SB) {
+        if constexpr (!SOLO)
+            if (batches++ == 8) { fold(); batches = 1; }
         Piece rx[SB][4];
         f32x4 w[SB];
         unsigned int shifts = 0u;                // 2 bits per piece
@@ -191,8 +209,7 @@ __global__ void __launch_bounds__(NWV * 64, 4) bcr_spmm_gather32(Gather32Params 
         }
         return;
     }
-#pragma unroll
-    for (int q = 0; q < NT; ++q) red[(wave * NT + q) * 64 + lane] = acc[q];
+    fold();
     if (lane == 0) odd_values[wave] = met;
     __syncthreads();
     if (wave >= 4) return;                       // wave r finishes piece r of every lane
