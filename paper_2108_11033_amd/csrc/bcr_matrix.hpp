@@ -219,6 +219,7 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
                                const void *X2 = nullptr, float *Y2 = nullptr);
 // fp32 row-gathering kernel: any N, any ldx
 bool gather32_applies(const grim_bcr_matrix *A, const void *X);
+bool gather32_quicker(const grim_bcr_matrix *A, int64_t N);    // than the vector-ALU kernel, for N > 8
 grim_status launch_spmm_gather32(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                                  hipStream_t stream);
 bool gather_pair_applies(const grim_bcr_matrix *A, const void *X, const grim_bcr_matrix *A2, const void *X2, int64_t N,

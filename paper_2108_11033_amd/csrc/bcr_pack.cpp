@@ -998,7 +998,15 @@ static bool skinny_on_matrix_cores(const grim_bcr_matrix *A, const void *X_dev, 
     if (N == 1 && gemv_ok(A, 1) && spmv_exact_applies(A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->K)) return false;
     if (N < 8 && gemv_ok(A, N) && spmv_many_strips_applies(count, A->nbr, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->K, A->BC, (int32_t)N))
         return false;
-    return A->dtype == GRIM_F32 ? gather32_applies(A, X_dev) : gather_any_applies(A, X_dev, N, ldx);
+    if (A->dtype != GRIM_F32) return gather_any_applies(A, X_dev, N, ldx);
+    if (!gather32_applies(A, X_dev)) return false;
+    // Blocks of fewer than eight rows: a 16-row run is many times as long as the strips that the SpMV kernel takes side by side,
+    // until there is a run to every compute unit (1 x 16 blocks, three columns: 1024 x 4096 25.6 us there, 54.5 here; 8192 x 1024
+    // 82.0 and 26.8).
+    if (A->BR < 8 && A->M < 4096) return false;
+    // Two or three columns of a uniform matrix of twice as many runs, as long as they fit the SpMV kernel's memory twice: 8192 x
+    // 4096 at three 13.9 us there, 16.1 here (four columns of 12288 x 4096 41.9 and 26.0).
+    return !(N > 1 && N < 4 && A->gemv.uniform_kr > 0 && A->M >= 8192 && A->K >= 2048 && A->K * N <= 12 * 1024);
 }
 static grim_status launch_skinny(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, hipStream_t stream) {
     return A->dtype == GRIM_F32 ? launch_spmm_gather32(A, X, N, ldx, Y, ldy, stream) : launch_spmm_gather(A, X, N, ldx, Y, ldy, stream);
@@ -1043,7 +1051,7 @@ static SpmmRoute spmm_route(const grim_bcr_matrix *A, const void *X_dev, int64_t
         if (wide >= 0 && (staged < 0 || wide < staged) && (gather < 0 || wide < gather)) return ROUTE_WIDE;
         if (gather >= 0 && (staged < 0 || gather < staged)) return ROUTE_GATHER;
         if (gather < 0 && gather_any_applies(A, X_dev, N, ldx)) return ROUTE_GATHER_ANY;
-        if (gather32_applies(A, X_dev)) return ROUTE_GATHER32;
+        if (gather32_applies(A, X_dev) && gather32_quicker(A, N)) return ROUTE_GATHER32;
     }
     if (mma) return ROUTE_MMA;
     return A->BR > 64 ? ROUTE_NONE : ROUTE_FMA;

@@ -235,6 +235,24 @@ bool gather32_applies(const grim_bcr_matrix *A, const void *X) {
     return A->gather32.present && reinterpret_cast<uintptr_t>(X) % 4 == 0;
 }
 
+// Is this kernel the quicker one for N > 8 columns?  A run of blocks of a few rows has a group of four k slots per strip and
+// block, of whose sixteen rows few hold anything: its workgroup then takes longer than the workgroups of its strips on the
+// vector ALUs do side by side, until there are enough of those to fill the GPU.  Both times in us, by what they grew with
+// over 280 products of 1 to 64 rows to a block, 32 x 65536 to 4096 x 512 at 9 to 25088 columns: here a run's steps, one after
+// the other (0.05, 0.075 and 0.105 each at up to 16, 32 and 64 columns, 0.128 on unaligned rows of less than 64); there the
+// blocks of a strip that a wave walks, each a chain of fetches that eight kept columns share.  (256 x 1152 in 2 x 32 blocks
+// keeping 1 x 8, 64 columns: 10.5 us there, 19.5 here; 1024 x 1024 in 2 x 16 blocks at 64: 27.7, 18.3.)
+bool gather32_quicker(const grim_bcr_matrix *A, int64_t N) {
+    const GatherLayout &L = A->gather32;
+    const int nt = N > 32 ? 4 : N > 16 ? 2 : 1, waves = A->BR <= 16 ? 16 : A->BR <= 32 ? 8 : 4;
+    const double tiles = (double)((N + nt * 16 - 1) / (nt * 16)), rounds = std::max(1.0, (double)A->nbr * ((N + 63) / 64) / 256);
+    const double step = nt == 4 ? (N < 64 ? 0.128 : 0.105) : nt == 2 ? 0.075 : 0.05;
+    const double here = 4 + step * std::max((double)L.max_steps, (double)L.nsteps * tiles / 256);
+    const double kept = (double)A->col_idx.size() / (double)A->nb, block = kept < 8 ? 1.6 + 0.16 * kept : 2.9 * kept / 8;
+    const double there = 3 + block * (double)((A->nbc + waves - 1) / waves) * rounds;
+    return here * 1.05 <= there;
+}
+
 grim_status launch_spmm_gather32(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, hipStream_t stream) {
     const GatherLayout &L = A->gather32;
     if (!gather32_applies(A, X)) return GRIM_ERR_UNSUPPORTED;

@@ -16,6 +16,7 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *, const void *, int64_t, i
 bool gather_pair_applies(const grim_bcr_matrix *, const void *, const grim_bcr_matrix *, const void *, int64_t, int64_t) { return false; }
 bool gather_applies(const grim_bcr_matrix *, const void *, int64_t, int64_t) { return false; }
 bool gather_any_applies(const grim_bcr_matrix *, const void *, int64_t, int64_t) { return false; }
+bool gather32_quicker(const grim_bcr_matrix *, int64_t) { return false; }
 bool gather32_applies(const grim_bcr_matrix *, const void *) { return false; }
 grim_status launch_spmm_gather32(const grim_bcr_matrix *, const void *, int64_t, int64_t, float *, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
 bool gather_wave_per_strip(const grim_bcr_matrix *, int64_t, int64_t) { return false; }

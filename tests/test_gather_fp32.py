@@ -82,3 +82,36 @@ def test_non_finite_values_reach_the_rows_that_keep_them(g, dtype, BR, BC, N, va
     assert not np.isfinite(Y[hit, n]).any()
     Y[hit, n] = Yref[hit, n]
     assert_close(Y, Yref, S, dtype, f"{dtype} {BR}x{BC} N={N} {value}")
+
+
+@pytest.mark.parametrize("M,K,BR,BC,kr,kc,N", [(32, 16384, 16, 32, 16, 32, 40),      # 1024 steps over eight waves
+                                               (64, 4608, 1, 16, 1, 4, 70),
+                                               (512, 4608, 16, 32, 8, 8, 200)])
+def test_fp32_no_less_exact_than_the_vector_alus(g, M, K, BR, BC, kr, kc, N):
+    """The distance from a 64-bit product against that of the vector-ALU kernel with its sixteen partial sums, which took these
+    products before; the two differ by a few per cent either way."""
+    import torch
+    from helpers import to_device
+    mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=1400)
+    W = gen.normal_weights(M, K, gen.F32, seed=1401)
+    X = gen.normal_activations(K, N, gen.F32, seed=1402, relu=True)
+    A = pack_workload(g, W, gen.F32, mask)
+    ref = torch.from_numpy(A.unpack().astype(np.float64)).cuda() @ torch.from_numpy(X.astype(np.float64)).cuda()
+    xd, y = to_device(X, gen.F32), torch.empty((M, N), dtype=torch.float32, device="cuda")
+    err = []
+    for kernel in (0, 1):
+        g.spmm(A, xd, N, N, y, N, kernel=kernel)
+        torch.cuda.synchronize()
+        err.append(float((y.double() - ref).norm() / ref.norm()))
+    assert err[0] <= 1.15 * err[1], err
+
+
+@pytest.mark.parametrize("M,K,BR,BC,N", [(64, 576, 1, 16, 64), (256, 1152, 2, 32, 33), (1024, 1024, 2, 16, 64), (64, 576, 4, 16, 200),
+                                         (4096, 64, 1, 16, 3), (256, 1024, 2, 16, 8), (8192, 2048, 32, 32, 3)])
+def test_fp32_small_blocks_on_either_kernel(g, M, K, BR, BC, N):
+    """Blocks of a few rows and tall matrices, on both sides of the rules that choose between this kernel and the vector ALUs."""
+    mask, W, X = _case(gen.F32, M, K, BR, BC, N, 1500)
+    Yref, S = oracle_product(W, X, gen.F32, mask)
+    A = pack_workload(g, W, gen.F32, mask)
+    Y = run_spmv(g, A, X, gen.F32, M, N) if N <= 8 else run_spmm(g, A, X, gen.F32, M, N)
+    assert_close(Y, Yref, S, gen.F32, f"fp32 {M}x{K} {BR}x{BC} N={N}")
