@@ -174,11 +174,9 @@ grim_status grim_bcr_spmm_tuned(const grim_bcr_matrix *A, const void *X_dev, int
 
 /* grim_bcr_spmm_kernel_name -- which kernel family the grim_bcr_spmm_tuned call with these arguments
  * would launch: "bcr_spmm_wide" (first launch of a large
- * product), "bcr_spmm_gather", "bcr_spmm_mma" (staged), "bcr_spmm_fma" (fp32 multiply-adds, on the
- * matrix cores where the matrix has that layout), "bcr_spmv" (N <= 8, but see grim_bcr_spmv), or
- * "none" when the call would fail.  A product whose rows of X are not 8-byte aligned (N or ldx not a multiple of 4) runs on
- * the row-gathering kernel's any-alignment form where the matrix has that layout and is reported under the family that
- * takes such operands otherwise ("bcr_spmm_mma" with the staged layout, else "bcr_spmm_fma").  A static string; launches nothing.  For profiling and reports. */
+ * product), "bcr_spmm_gather", "bcr_spmm_mma" (staged), "bcr_spmm_gather32" (fp32 on the matrix cores), "bcr_spmm_fma"
+ * (vector ALUs), "bcr_spmv" (N <= 8, but see grim_bcr_spmv), or "none" when the call would fail.  A static string; launches
+ * nothing.  For profiling and reports. */
 const char *grim_bcr_spmm_kernel_name(const grim_bcr_matrix *A, const void *X_dev, int64_t N, int64_t ldx,
                                       int32_t tile_n, int32_t strips_per_wg, int32_t kernel);
 

@@ -1013,7 +1013,7 @@ static grim_status launch_skinny(const grim_bcr_matrix *A, const void *X, int64_
 }
 
 // which kernel family a grim_bcr_spmm_tuned call runs
-enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_GATHER_ANY, ROUTE_GATHER32, ROUTE_WIDE };
+enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_GATHER32, ROUTE_WIDE };
 
 // what the columns the wide-tile kernel leaves over cost on the kernels that take any N
 static double rest_cost(const grim_bcr_matrix *A, int64_t n) {
@@ -1050,7 +1050,9 @@ static SpmmRoute spmm_route(const grim_bcr_matrix *A, const void *X_dev, int64_t
         const double wide = wide_plan(A, X_dev, N, ldx, Y_dev, ldy, rest_cost, wide_tn, wide_cols);
         if (wide >= 0 && (staged < 0 || wide < staged) && (gather < 0 || wide < gather)) return ROUTE_WIDE;
         if (gather >= 0 && (staged < 0 || gather < staged)) return ROUTE_GATHER;
-        if (gather < 0 && gather_any_applies(A, X_dev, N, ldx)) return ROUTE_GATHER_ANY;
+        // (rows of X at any alignment: 360 products of 9 to 25087 columns, 64 x 576 to 1024 x 1024 and 512 x 4608, were quicker
+        // there than staged or on the vector ALUs, by 1.0 to 50 times)
+        if (gather < 0 && gather_any_applies(A, X_dev, N, ldx)) return ROUTE_GATHER;
         if (gather32_applies(A, X_dev) && gather32_quicker(A, N)) return ROUTE_GATHER32;
     }
     if (mma) return ROUTE_MMA;
@@ -1070,8 +1072,7 @@ grim_status grim_bcr_spmm_tuned(const grim_bcr_matrix *A, const void *X_dev, int
             return launch_spmv(nullptr, d, nullptr, 1, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc,
                                A->gemv.vec, A->gemv.krmax, A->gemv.kcmax, X_dev, 0, (int32_t)N, ldx, Y_dev, 0, ldy, stream);
         }
-        case ROUTE_GATHER:
-        case ROUTE_GATHER_ANY: return launch_spmm_gather(A, X_dev, N, ldx, Y_dev, ldy, stream);
+        case ROUTE_GATHER: return launch_spmm_gather(A, X_dev, N, ldx, Y_dev, ldy, stream);
         case ROUTE_GATHER32: return launch_spmm_gather32(A, X_dev, N, ldx, Y_dev, ldy, stream);
         case ROUTE_WIDE: {
             // whole rounds of fat workgroups, the few columns left over on whatever suits them: in the same launch when
@@ -1093,9 +1094,7 @@ grim_status grim_bcr_spmm_tuned(const grim_bcr_matrix *A, const void *X_dev, int
             if (kernel == 0 && tile_n == 0 && strips_per_wg == 0) {
                 // whole rounds of workgroups on the staged kernel, the few columns left over on whatever suits them
                 int tn = 0, g = 0;
-                // (whether the rest may take the row-gathering kernel hangs on N and the alignment of X alone: the cut
-                // is a multiple of 32 columns)
-                const int64_t n_main = mma_whole_rounds(A, N, gather_applies(A, X_dev, N, ldx), &tn, &g);
+                const int64_t n_main = mma_whole_rounds(A, N, &tn, &g);
                 if (n_main < N) {
                     st = launch_spmm_mma(A, X_dev, n_main, ldx, Y_dev, ldy, tn, g, stream);
                     if (st != GRIM_OK) return st;
@@ -1122,11 +1121,8 @@ const char *grim_bcr_spmm_kernel_name(const grim_bcr_matrix *A, const void *X_de
         case ROUTE_SPMV: return "bcr_spmv";
         case ROUTE_WIDE: return "bcr_spmm_wide";
         case ROUTE_GATHER: return "bcr_spmm_gather";
-        // (rows of X at any alignment: reported as the family that is otherwise the matrix's for such operands)
-        case ROUTE_GATHER_ANY: return A->mma.present ? "bcr_spmm_mma" : "bcr_spmm_fma";
         case ROUTE_MMA: return "bcr_spmm_mma";
-        // (fp32 multiply-adds on the vector ALUs or, where the matrix has that layout, on the matrix cores)
-        case ROUTE_GATHER32:
+        case ROUTE_GATHER32: return "bcr_spmm_gather32";
         case ROUTE_FMA: return "bcr_spmm_fma";
         case ROUTE_NONE: break;
     }

@@ -466,9 +466,9 @@ double mma_best_shape(const grim_bcr_matrix *A, int64_t N, int32_t tile_n, int32
 // workgroups and a few left over cost a whole round: 784 tiles on 256 compute units take 4 rounds for 3.06 rounds of
 // work.  Returns the number of leading columns that fill whole rounds (a multiple of the tile width) and the launch
 // shape for them when, by the cost model that also picks the kernel, these plus the remaining columns as a product of
-// their own (on the row-gathering kernel if `rest_may_gather`, else staged again) come cheaper than one launch; the
-// caller sends the remaining columns through the kernel choice.  Returns N when there is nothing to gain.
-int64_t mma_whole_rounds(const grim_bcr_matrix *A, int64_t N, bool rest_may_gather, int *tn_out, int *g_out) {
+// their own come cheaper than one launch; the caller sends the remaining columns through the kernel choice.  Returns N when
+// there is nothing to gain.
+int64_t mma_whole_rounds(const grim_bcr_matrix *A, int64_t N, int *tn_out, int *g_out) {
     int tn = 0, g = 0;
     const double cost_all = mma_best_shape(A, N, 0, 0, &tn, &g);
     if (cost_all < 0) return N;
@@ -486,7 +486,7 @@ int64_t mma_whole_rounds(const grim_bcr_matrix *A, int64_t N, bool rest_may_gath
     int t2 = 0, g2 = 0;
     const double cost_main = mma_best_shape(A, n_main, tn, g, &t2, &g2);
     double cost_rest = mma_best_shape(A, n_rest, 0, 0, &t2, &g2);
-    if (rest_may_gather && A->gather.present) {
+    if (A->gather.present) {
         const double c = gather_cost(A, n_rest);
         if (cost_rest < 0 || c < cost_rest) cost_rest = c;
     }

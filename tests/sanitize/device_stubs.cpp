@@ -28,7 +28,7 @@ bool conv_wide_applies(const grim_bcr_matrix *, const void *, int32_t, int32_t, 
 grim_status launch_conv_wide(const grim_bcr_matrix *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t, const float *, int32_t, void *, int32_t, int64_t, int64_t, hipStream_t) { return GRIM_ERR_UNSUPPORTED; }
 double gather_cost(const grim_bcr_matrix *, int64_t) { return 0.0; }
 double mma_best_shape(const grim_bcr_matrix *, int64_t, int32_t, int32_t, int *, int *) { return -1.0; }
-int64_t mma_whole_rounds(const grim_bcr_matrix *, int64_t N, bool, int *, int *) { return N; }
+int64_t mma_whole_rounds(const grim_bcr_matrix *, int64_t N, int *, int *) { return N; }
 grim_status launch_spmv(const GemvDesc *, const GemvDesc &, const GemvDesc *, int32_t, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, const void *, int64_t, int32_t, int64_t, float *, int64_t, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
 bool spmv_cell_applies(int, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t) { return false; }
 grim_status launch_spmv_cell(int, const GemvDesc &, const GemvDesc *, int64_t, int64_t, int32_t, int32_t, int32_t, int32_t, int32_t, const void *, int64_t, int32_t, int64_t, float *, int64_t, int64_t, const RnnCell &, hipStream_t) { return GRIM_ERR_DEVICE; }

@@ -131,15 +131,16 @@ def test_c2_at_224x224_full_size_sampled(g):
 @pytest.mark.parametrize("ragged", [20, 21])
 def test_staged_kernel_whole_rounds_and_a_remainder(g, ragged):
     """Free kernel choice at a size where the staged kernel's workgroups would leave a nearly empty last round: the
-    leading columns that fill whole rounds run on the staged kernel, the rest as a product of their own (the
-    row-gathering kernel when the remainder is a multiple of 4 columns, else the staged one again).  Sampled rows x the
-    columns around the cut, both ends and a random sample."""
+    leading columns that fill whole rounds run on the staged kernel, the rest as a product of their own.  (Rows of X that are
+    not 8-byte aligned run on the row-gathering kernel as a whole.)  Sampled rows x the columns around the cut, both ends and a
+    random sample."""
     torch, dev = torch_dev()
     wl0 = gen.c2_vgg_conv(64)
     A = pack_workload(g, wl0.W, wl0.dtype, wl0.mask)
     probe = torch.empty(16, dtype=torch.float16, device=dev)              # only the address is looked at
-    tiles = next((t for t in (259, 515, 771) if g.spmm_kernel_name(A, probe, 64 * t - ragged, 64 * t - ragged) == "bcr_spmm_mma"), None)
-    assert tiles is not None, "the staged kernel is never chosen for this matrix"
+    want = "bcr_spmm_mma" if ragged % 4 == 0 else "bcr_spmm_gather"
+    tiles = next((t for t in (259, 515, 771) if g.spmm_kernel_name(A, probe, 64 * t - ragged, 64 * t - ragged) == want), None)
+    assert tiles is not None, f"{want} is never chosen for this matrix"
     N, cut = 64 * tiles - ragged, 64 * (tiles - 3)
     X = gen.normal_activations(wl0.K, N, wl0.dtype, seed=95, relu=True)
     Y = run_spmm(g, A, X, wl0.dtype, wl0.M, N)
@@ -322,12 +323,12 @@ def test_spmv_falls_back_when_blocks_exceed_masks(g):
     A = pack_workload(g, W, dtype, mask)
     yref, S = oracle_product(W, x, dtype, mask)
     assert_close(run_spmv(g, A, x, dtype, M, 2), yref, S, dtype, "spmv 64x64 blocks")
-    # batches the row-gathering kernel takes (multiples of 4) go there, the rest to the vector-ALU kernel
+    # the SpMV kernels do not take such blocks: the row-gathering kernel does, at any alignment
     for batch in (4, 8, 5):
         xb = gen.normal_activations(K, batch, dtype, seed=153 + batch)
         yref, S = oracle_product(W, xb, dtype, mask)
         assert_close(run_spmv(g, A, xb, dtype, M, batch), yref, S, dtype, f"spmv 64x64 blocks, batch {batch}")
-        assert g.spmm_kernel_name(A, to_device(xb, dtype), batch, batch) == ("bcr_spmm_gather" if batch % 4 == 0 else "bcr_spmm_fma")
+        assert g.spmm_kernel_name(A, to_device(xb, dtype), batch, batch) == "bcr_spmm_gather"
 
 
 # ------------------------------------------------------------------ staged kernel: more tiles than compute units
@@ -571,7 +572,7 @@ def test_gather_kernel_block_heights(g, dtype, BR, BC):
 
 def test_kernel_choice_follows_the_cost_model(g):
     """grim_bcr_spmm_kernel_name reports the route; few tiles per strip group -> row-gathering kernel, very
-    many tiles of a many-strip matrix -> wide-tile staged kernel; fp32 -> FMA kernel; N <= 8 -> SpMV."""
+    many tiles of a many-strip matrix -> wide-tile staged kernel; fp32 -> its row-gathering kernel; N <= 8 -> SpMV."""
     torch, dev = torch_dev()
     wl = gen.c2_vgg_conv(200)
     A = pack_workload(g, wl.W, wl.dtype, wl.mask)
@@ -582,7 +583,7 @@ def test_kernel_choice_follows_the_cost_model(g):
     assert g.spmm_kernel_name(A, X, 4, 200) == "bcr_spmv"
     assert g.spmm_kernel_name(A, X, 8, 200) == "bcr_spmv"             # uniform blocks: a set of workgroups per column
     assert g.spmm_kernel_name(A, X, 8, 204) == "bcr_spmv"             # rows 8-byte aligned only
-    assert g.spmm_kernel_name(A, X, 199, 200) == "bcr_spmm_mma"       # rows not 8-byte aligned
+    assert g.spmm_kernel_name(A, X, 199, 200) == "bcr_spmm_gather"    # rows not 8-byte aligned
     assert g.spmm_kernel_name(A, X, 200, 200, kernel=1) == "bcr_spmm_fma"
     assert g.spmm_kernel_name(A, X, 200, 100) == "none"               # ldx < N
     big = torch.empty(16, dtype=torch.float16, device=dev)            # only the address is looked at
@@ -593,7 +594,8 @@ def test_kernel_choice_follows_the_cost_model(g):
     assert g.spmm_kernel_name(A, big, 50180, 50180) != "bcr_spmm_wide"     # N not a multiple of 8
     w1 = gen.c1_single_fp32()
     A1 = pack_workload(g, w1.W, w1.dtype, w1.mask)
-    assert g.spmm_kernel_name(A1, to_device(w1.X, w1.dtype), w1.N, w1.N) == "bcr_spmm_fma"
+    assert g.spmm_kernel_name(A1, to_device(w1.X, w1.dtype), w1.N, w1.N) == "bcr_spmm_gather32"
+    assert g.spmm_kernel_name(A1, to_device(w1.X, w1.dtype), w1.N, w1.N, kernel=1) == "bcr_spmm_fma"
     assert g.spmm_kernel_name(A1, to_device(w1.X, w1.dtype), w1.N, w1.N, kernel=3) == "none"
 
 
