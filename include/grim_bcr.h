@@ -311,16 +311,15 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *plan, const void *F_d
  * workgroup computes the four gate rows of BR hidden units for one column and applies the cell before it stores
  * anything (gates_dev still receives the pre-activations).  Other fp16 / bf16 steps of up to 64 columns with h_dev outside
  * xh_dev, H a multiple of 16 and of BR (or strips stored in their original order) and H / 16 x ceil(batch / 16) no more
- * than 256 are one launch on the matrix cores.  Otherwise two launches.
+ * than 256 are one launch on the matrix cores (but for 56 and 64 aligned columns of long gate rows).  Otherwise two launches.
  * Errors: NULL, SHAPE (batch < 1, H < 1, leading dimension too small, A->M != 4H), DTYPE, DEVICE,
  * UNSUPPORTED.
  */
 /* grim_bcr_rnn_step_launches -- how many kernels a recurrent step enqueues (for reports and tests; launches nothing):
  * grim_bcr_lstm_step of A (Ah = NULL) or grim_bcr_gru_step of (A, Ah) at this batch, for operands with the usual
  * alignment and a new state that does not overlap the step's inputs.  1 = the gate product(s) with the cell in the
- * epilogue, column by column (every column has the bits of a one-column step); 2 = product(s) in one launch, then the
- * cell -- or both in one launch on the matrix cores, where grim_bcr_lstm_step says so; 3 = a launch per product, then the
- * cell; 0 = the step would be refused. */
+ * epilogue; 2 = product(s) in one launch, then the cell; 3 = a launch per product, then the cell; 0 = the step would be
+ * refused. */
 int32_t grim_bcr_rnn_step_launches(const grim_bcr_matrix *A, const grim_bcr_matrix *Ah, int32_t batch);
 
 grim_status grim_lstm_cell(const float *gates_dev, int64_t ldg, const float *bias_dev, float *c_dev, int64_t ldc,
@@ -346,8 +345,8 @@ grim_status grim_bcr_lstm_step(const grim_bcr_matrix *A, const void *xh_dev, int
  * grim_bcr_gru_step = the two products (x_dev: I x batch, hin_dev: H x batch, both of the matrices'
  * element type; any batch >= 1: up to 8 columns run on the SpMV kernels, more on the SpMM kernels;
  * with equal leading dimensions on both sides one launch computes both products -- on the SpMV
- * kernels for W_i and W_h of one shape and block size, on the row-gathering SpMM kernel for 4 to 60
- * columns in multiples of 4)
+ * kernels for W_i and W_h of one shape and block size, on the row-gathering SpMM kernel for fewer
+ * than 64 columns)
  * into gi_dev and gh_dev, then grim_gru_cell writing hout_dev (may be hin_dev itself: the cell runs
  * after both products).  With fp16 / bf16 matrices of one shape, block size and kept counts, H a multiple of BR,
  * hout_dev overlapping neither x_dev nor hin_dev, and batch x H / BR workgroups no more than the GPU's compute

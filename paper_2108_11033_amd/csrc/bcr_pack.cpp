@@ -1381,23 +1381,25 @@ grim_status grim_bcr_lstm_step(const grim_bcr_matrix *A, const void *xh_dev, int
 
 int32_t grim_bcr_rnn_step_launches(const grim_bcr_matrix *A, const grim_bcr_matrix *Ah, int32_t batch) {
     if (!A || batch < 1 || !A->on_device) return 0;
+    // operands as allocators give them: aligned, a leading dimension of `batch`
+    const void *aligned = reinterpret_cast<const void *>(uintptr_t(256));
     if (!Ah) {
         if (A->M % 4 != 0) return 0;
-        const bool fused = A->gemv.present && spmv_cell_batch_ok(A->M / 4, A->BR, batch) &&
-                           spmv_cell_applies(1, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->M / 4);
-        return fused ? 1 : 2;
+        const int64_t H = A->M / 4;
+        const bool by_column = A->gemv.present && spmv_cell_batch_ok(H, A->BR, batch) &&
+                               spmv_cell_applies(1, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, H);
+        return by_column || rnn_gather_applies(A, aligned, batch, nullptr, nullptr, 0, H, batch) ? 1 : 2;
     }
     if (A->M != Ah->M || A->M % 3 != 0 || Ah->K != A->M / 3 || A->dtype != Ah->dtype || !Ah->on_device) return 0;
+    const int64_t H = A->M / 3;
     const bool same = A->K == Ah->K && A->BR == Ah->BR && A->BC == Ah->BC && A->gemv.present && Ah->gemv.present;
-    const bool fused = spmv_cell_batch_ok(A->M / 3, A->BR, batch) && same && A->gemv.uniform_kr == Ah->gemv.uniform_kr && A->gemv.uniform_kc == Ah->gemv.uniform_kc &&
-                       spmv_cell_applies(2, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, A->M / 3);
-    if (fused) return 1;
-    // both products in one launch (SpMV kernels up to 8 columns when the matrices have one shape; the row-gathering
-    // kernel below 64 columns), then the cell; otherwise a launch per product
-    const bool one_spmv = batch <= 8 && same && A->K * batch * dtype_size(A->dtype) <= kGemvMaxXBytes;
-    const bool one_gather = batch < 64 && A->gather.present && Ah->gather.present &&
-                            A->gather.nstrips == Ah->gather.nstrips;
-    return one_spmv || one_gather ? 2 : 3;
+    const bool by_column = spmv_cell_batch_ok(H, A->BR, batch) && same && A->gemv.uniform_kr == Ah->gemv.uniform_kr && A->gemv.uniform_kc == Ah->gemv.uniform_kc &&
+                           spmv_cell_applies(2, A->M, A->K, A->BR, A->BC, A->dtype, A->gemv.uniform_kr, A->gemv.uniform_kc, H);
+    if (by_column || rnn_gather_applies(A, aligned, batch, Ah, aligned, batch, H, batch)) return 1;
+    // both products in one launch (the row-gathering kernel below 64 columns, SpMV kernels up to 8 columns when the matrices
+    // have one shape), then the cell; otherwise a launch per product
+    const bool one_launch = gather_pair_applies(A, aligned, Ah, aligned, batch, batch) || (same && gemv_ok(A, batch) && gemv_ok(Ah, batch));
+    return one_launch ? 2 : 3;
 }
 
 // exchange words of the sequence kernel: allocated with the first sequence call on a matrix, freed with the matrix
