@@ -1326,7 +1326,12 @@ const char *grim_bcr_conv2d_kernel_name(const grim_bcr_matrix *A, int32_t Cin, i
     void *aligned = reinterpret_cast<void *>(uintptr_t(256));
     if (stride == 1 && conv_wide_applies(A, aligned, Cin, H, W, kh, kw, batch, Cin * HW, aligned, GRIM_F32, HW, A->M * HW))
         return "bcr_conv_wide";
-    return A->gather.present ? "bcr_conv_gather" : "none";
+    if (!A->gather.present) return "none";
+    try {
+        if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_tall_runs(A, count_run_steps<kConvTallRuns>(A), H, W, stride, batch)) return "bcr_conv_tall";
+    } catch (const std::bad_alloc &) {           // (a plan without memory for that layout does without it, too)
+    }
+    return "bcr_conv_gather";
 }
 
 grim_status grim_lstm_cell(const float *gates_dev, int64_t ldg, const float *bias_dev, float *c_dev, int64_t ldc,

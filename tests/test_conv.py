@@ -555,7 +555,7 @@ def test_conv_on_the_wide_tile_kernel(dtype, M, Cin, H, W, kh, kw, BR, BC, B, ep
     F = gen.normal_activations(Cin, B * H * W, dtype, seed=782, relu=True).reshape(Cin, B, H, W).transpose(1, 0, 2, 3).copy()
     A = pack_workload(g, Wt, dtype, mask)
     assert g.conv2d_kernel_name(A, Cin, H, W, kh, kw, B, 1) == "bcr_conv_wide"
-    assert g.conv2d_kernel_name(A, Cin, H, W, kh, kw, B, 2) == "bcr_conv_gather"
+    assert g.conv2d_kernel_name(A, Cin, H, W, kh, kw, B, 2) in ("bcr_conv_gather", "bcr_conv_tall")
     Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
     Yref = conv_ref.conv2d(Wm, F64, kh, kw, 1)
     S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, 1)
@@ -652,14 +652,15 @@ def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, col
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("M,BR,BC,H,W,kh,kw,stride,B,pad,cin", [
-    (96, 4, 16, 70, 75, 3, 3, 1, 1, 3, 32),      # a second 64-row run of 32 rows; odd sizes and strides; 18 steps over four waves
-    (64, 32, 32, 56, 56, 3, 3, 1, 4, 0, 96),     # one 64-row run, 196 tiles
-    (80, 16, 16, 40, 36, 3, 3, 1, 8, 0, 96),     # a run of 16 rows; strips that keep nothing
-    (256, 8, 16, 33, 47, 3, 3, 2, 4, 1, 64),     # stride 2, rows of 24 outputs
-    (128, 128, 32, 9, 9, 3, 3, 2, 48, 0, 32),    # blocks taller than a run; 5 x 5 outputs: one partly filled tile per image
+    (96, 4, 16, 70, 75, 3, 3, 1, 2, 3, 64),      # a second 64-row run of 32 rows; odd sizes and strides; 18 steps over four waves
+    (96, 4, 16, 41, 39, 3, 3, 1, 5, 3, 64),      # a last tile of 63 positions in each image
+    (64, 32, 32, 56, 56, 3, 3, 1, 4, 0, 192),    # one 64-row run, 196 tiles
+    (80, 16, 16, 40, 36, 3, 3, 2, 10, 0, 96),    # a run of 16 rows; strips that keep nothing
+    (256, 8, 16, 33, 47, 3, 3, 2, 6, 1, 64),     # stride 2, rows of 24 outputs
+    (128, 128, 32, 9, 9, 3, 3, 2, 80, 0, 32),    # blocks taller than a run; 5 x 5 outputs: one partly filled tile per image
     (192, 4, 16, 40, 40, 1, 1, 2, 8, 0, 32),     # fewer steps than waves
     (128, 4, 16, 3, 47, 1, 1, 2, 80, 0, 64),     # flat maps at stride 2: a tile of 48 positions
-    (96, 4, 16, 70, 75, 3, 3, 1, 2, 3, 32),      # (the first shape as a batch of two)
+    (96, 4, 16, 70, 75, 3, 3, 1, 1, 3, 64),      # one image of the first shape: on runs of 16 rows
 ])
 def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pad, cin):
     import paper_2108_11033_amd as g
@@ -672,7 +673,10 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
     Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
     Yref = conv_ref.conv2d(Wm, F64, kh, kw, stride) + bias[None, :, None, None]
     S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, stride) + np.abs(bias)[None, :, None, None]
-    Y = _run_plan(g, pack_workload(g, Wt, dtype, mask), F, dtype, M, kh, kw, stride, bias=bias, pad=pad)
+    A = pack_workload(g, Wt, dtype, mask)
+    # (one image at stride 1 has the bits of the unplanned call, which the 64-row runs do not)
+    assert g.conv2d_kernel_name(A, cin, H, W, kh, kw, B, stride) == ("bcr_conv_gather" if B == stride == 1 else "bcr_conv_tall")
+    Y = _run_plan(g, A, F, dtype, M, kh, kw, stride, bias=bias, pad=pad)
     assert np.isfinite(Y).all()
     assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
     assert np.abs(Y - Yref).max() <= TOL[dtype] * np.abs(Yref).max()
