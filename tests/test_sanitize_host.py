@@ -1,7 +1,8 @@
 """The host side of the library under the address and undefined-behaviour sanitizers (no GPU).
 
-csrc/bcr_pack.cpp -- validation, compaction into the canonical arrays, the three derived kernel layouts and
-their decoders, the BCRC export -- is built with g++ -fsanitize=address,undefined against stand-ins for the
+csrc/bcr_pack.cpp -- validation, compaction into the canonical arrays, the derived kernel layouts and
+their decoders, the BCRC export -- is built with g++ -fsanitize=address,undefined, with decoders for the layouts
+that the library itself has none for (tests/sanitize/derived_layouts.cpp), against stand-ins for the
 kernel launchers (tests/sanitize/device_stubs.cpp), and the host-side test files run against that build in a
 child interpreter with the sanitizer runtimes preloaded.  Any out-of-bounds access, use after free or
 undefined operation in the index-building code aborts the child and fails this test."""
@@ -30,7 +31,7 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
              "-fno-sanitize-recover=undefined", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
              "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2108_11033_amd", "csrc"),
              "-shared", "-fPIC", "-Wl,-Bsymbolic",
-             os.path.join(ROOT, "paper_2108_11033_amd", "csrc", "bcr_pack.cpp"),
+             os.path.join(ROOT, "tests", "sanitize", "derived_layouts.cpp"),
              os.path.join(ROOT, "tests", "sanitize", "device_stubs.cpp"), "-o", lib]
     res = subprocess.run(build, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-4000:]
