@@ -91,7 +91,7 @@ __device__ __forceinline__ void conv_finish(const ConvParams &p, int img, int64_
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         sum[e] += b;
-        if (p.relu) sum[e] = sum[e] <= 0.f ? 0.f : sum[e];    // NaN stays NaN
+        if (p.relu) sum[e] = __builtin_elementwise_maximum(sum[e], 0.f);    // NaN stays NaN
     }
     // how many of the four are outputs, and where the first goes
     int left = (int)(p.Nv - n);                  // below 4 only in the one tile of a map of fewer than 64 positions

@@ -561,7 +561,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         v[e] += b;
-                        if (p.relu) v[e] = v[e] <= 0.f ? 0.f : v[e];     // NaN stays NaN
+                        if (p.relu) v[e] = __builtin_elementwise_maximum(v[e], 0.f);     // NaN stays NaN
                     }
                     if (p.odt == GRIM_F32) {
                         __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p.Y + at));
@@ -586,7 +586,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
                     float v = acc[s][q][e];
                     if constexpr (CONV) {
                         v += p.bias ? p.bias[row0 + m] : 0.f;
-                        if (p.relu) v = v <= 0.f ? 0.f : v;
+                        if (p.relu) v = __builtin_elementwise_maximum(v, 0.f);
                     }
                     put((row0 + m) * p.ldy + col, v);
                 }
