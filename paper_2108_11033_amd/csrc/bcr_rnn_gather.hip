@@ -36,10 +36,6 @@ struct RnnGatherParams {
     int32_t H, N, hdt;
 };
 
-struct __attribute__((packed, aligned(2))) RnnPiece {
-    unsigned int d[4];
-};
-
 // SB: steps a wave has in flight (steps past its last are fetched too: few where a run has few)
 template <bool BF16, int CELL, int SB>
 __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGatherParams p) {
@@ -106,9 +102,7 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
             const unsigned short *src = xcol + (int64_t)(pad ? 0u : row[u]) * A.ldx;
             const int over = src > x_last ? (int)(src - x_last) : 0;
             flags[u] = (unsigned int)over | (pad ? 0x80000000u : 0u);
-            RnnPiece v;
-            __builtin_memcpy(&v, src - over, 16);
-            rx[u] = u32x4{v.d[0], v.d[1], v.d[2], v.d[3]};
+            rx[u] = load_piece_any(src - over);
             const bool kept = (dsc[u].x >> i16) & 1u;
             const i16x8 wv = pay[dsc[u].y + (kept ? __builtin_popcount(dsc[u].x & below) : 0)];
             w[u] = kept ? wv : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
@@ -117,12 +111,7 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
                 u32x4 v = rx[u];
-                if (__builtin_amdgcn_ballot_w64((flags[u] & 15u) != 0)) {        // (the last rows of X only)
-                    unsigned __int128 x = (unsigned __int128)v[0] | (unsigned __int128)v[1] << 32 |
-                                          (unsigned __int128)v[2] << 64 | (unsigned __int128)v[3] << 96;
-                    x >>= 16 * (flags[u] & 15u);
-                    v = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
-                }
+                if (__builtin_amdgcn_ballot_w64((flags[u] & 15u) != 0)) v = drop_elements(v, flags[u] & 15u);    // (the last rows of X only)
                 if (flags[u] >> 31) v = u32x4{0u, 0u, 0u, 0u};
                 char *b = buf + (u & 1) * 1024;
                 *reinterpret_cast<u32x4 *>(b + rs * PITCH + c * 16) = v;

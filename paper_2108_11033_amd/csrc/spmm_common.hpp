@@ -64,6 +64,19 @@ __device__ __forceinline__ int swizzle(int row) {
     return CPR == 8 ? (((row >> 1) & 3) << 1) : CPR > 8 ? ((row & 3) << 1) : (((row >> 1) & 1) << 1);
 }
 
+// 16 bytes of X at any 2-byte alignment: a single access on this GPU
+__device__ __forceinline__ u32x4 load_piece_any(const unsigned short *src) {
+    struct __attribute__((packed, aligned(2))) { unsigned int d[4]; } v;
+    __builtin_memcpy(&v, src, 16);
+    return u32x4{v.d[0], v.d[1], v.d[2], v.d[3]};
+}
+// A piece that would reach past the end of X is fetched `n` < 8 elements early; this moves it into place.
+__device__ __forceinline__ u32x4 drop_elements(u32x4 v, unsigned int n) {
+    unsigned __int128 x = (unsigned __int128)v[0] | (unsigned __int128)v[1] << 32 | (unsigned __int128)v[2] << 64 | (unsigned __int128)v[3] << 96;
+    x >>= 16 * n;
+    return u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
+}
+
 // Waves that split a long strip's steps in the few-workgroups form of the row-gathering kernels.  A 36-step strip of a
 // 14 x 14 layer: 8 waves of the product kernel (4 steps per batch) 7.66 us, 12 waves 7.63, 16 waves 8.56; the convolution
 // kernel (3 steps per batch) 11.0 us with 8, 8.6 us with 12 -- every wave then needs one batch only --, 9.7 us with 16.

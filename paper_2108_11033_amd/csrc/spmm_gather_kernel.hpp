@@ -67,10 +67,7 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
                          const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form,
                          bool may_take_small_tiles = true);
 
-// 16 bytes of X at any 2-byte alignment; four results at any 4-byte alignment (both are single accesses on this GPU)
-struct __attribute__((packed, aligned(2))) GatherPiece {
-    unsigned int d[4];
-};
+// four results at any 4-byte alignment (a single access on this GPU)
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // ALIGNED: rows of X are 16-byte aligned and N a multiple of 8.  Otherwise a piece is still one 16-byte load, at
@@ -217,13 +214,9 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             } else if constexpr (NARROW) {
                 const int over = src > x_last ? (int)(src - x_last) : 0;      // elements, below 8
                 r.pad |= (unsigned int)over << (8 + 4 * i);
-                GatherPiece v;
-                __builtin_memcpy(&v, src - over, 16);
-                r.rx[i] = u32x4{v.d[0], v.d[1], v.d[2], v.d[3]};
+                r.rx[i] = load_piece_any(src - over);
             } else {
-                GatherPiece v;
-                __builtin_memcpy(&v, src, 16);
-                r.rx[i] = u32x4{v.d[0], v.d[1], v.d[2], v.d[3]};
+                r.rx[i] = load_piece_any(src);
             }
         }
     };
@@ -258,8 +251,8 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             nhdr = ask_hdr(st);
             ndsc = desc2[(int64_t)st * 4 + kgroup];
         }
-        // WATCH forms took over from kernels with sixteen partial sums: a batch's steps (half of eight) are summed from zero and then added, which
-        // keeps their errors (512 x 4608 in 4 x 16 blocks, 25 steps to a wave: 1.26e-7 in one chain, 0.98e-7 before)
+        // WATCH forms took over from kernels with sixteen partial sums: a batch's steps (half of eight) are summed from
+        // zero and then added, which keeps their errors (512 x 4608 in 4 x 16 blocks, 25 steps to a wave: 1.26e-7 in one chain, 0.98e-7 before)
         f32x4 part[NT];
 #pragma unroll
         for (int q = 0; q < NT; ++q) part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -278,13 +271,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
                 if constexpr (NARROW && !ALIGNED) {
                     if (__builtin_amdgcn_ballot_w64(R[u].pad >> 8 != 0)) {       // (the last rows of X only)
 #pragma unroll
-                        for (int i = 0; i < LI; ++i) {
-                            const u32x4 f = R[u].rx[i];
-                            unsigned __int128 x = (unsigned __int128)f[0] | (unsigned __int128)f[1] << 32 |
-                                                  (unsigned __int128)f[2] << 64 | (unsigned __int128)f[3] << 96;
-                            x >>= 16 * ((R[u].pad >> (8 + 4 * i)) & 15u);
-                            R[u].rx[i] = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
-                        }
+                        for (int i = 0; i < LI; ++i) R[u].rx[i] = drop_elements(R[u].rx[i], (R[u].pad >> (8 + 4 * i)) & 15u);
                     }
                 }
 #pragma unroll
