@@ -10,8 +10,8 @@ namespace grim {
 // rows over and over: four runs of 4 x 16 blocks that keep 4 of 16 columns name 2.7 rows for every distinct one, four of
 // 8 x 16 or 16 x 16 blocks about 1.9.  Here the steps belong to runs of 64 rows (a layout the plan holds) and feed four
 // 16-row multiplies each.  Bound by the latency of a step's fetch over the two waves a SIMD holds (three steps in flight
-// spill; two asked for as a batch, without the rolling requests below, take 18.4 us where this takes 15.9: 256 channels,
-// 3 x 3, four 28 x 28 maps in 4 x 16 blocks, 25.0 on 16-row runs).
+// spill; two asked for as a batch, without the rolling requests below, take 18.4 us where this takes 15.7: 256 channels,
+// 3 x 3, four 28 x 28 maps in 4 x 16 blocks, 26.1 on 16-row runs).
 //
 // Workgroup = (tile of 64 positions, 64-row run), its waves split the run's steps.  64 accumulators and two steps in
 // flight leave two waves per SIMD, so a wave covers its own latencies: a step's windows are asked for D steps ahead, into

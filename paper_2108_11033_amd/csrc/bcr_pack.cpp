@@ -1193,11 +1193,11 @@ struct grim_bcr_conv_plan {
 // Runs of 64 rows pay once there are about as many (tile, run) pairs as two thirds of the compute units -- below that the
 // four times as many 16-row workgroups are quicker (512 channels on one 28 x 28 map, 104 pairs: 13.6 -> 19.4 us) -- and, at
 // stride 1, for strips of some length that name each row nearly twice and more.  Measured, 16-row against 64-row runs:
-// 256 channels, 3 x 3, four 28 x 28 maps in 16 x 32 / 8 x 16 / 16 x 16 / 32 x 32 / 4 x 16 blocks (rows named 1.5 / 1.9 /
-// 2.1 / 2.7 / 2.7 times) 13.5 -> 13.7, 18.0 -> 16.1, 17.9 -> 16.5, 18.2 -> 13.8, 25.7 -> 16.4 us; 128 channels on eight
-// 56 x 56 maps 21.9 -> 26.1, 31.8 -> 29.3, 32.2 -> 29.5, 32.1 -> 26.5, 41.5 -> 30.2; 1 x 1 with 8 steps 7.1 -> 7.5.  At
-// stride 2, where a window is two loads, 128 -> 256 channels from four 56 x 56 maps 13.5 -> 11.1, 17.2 -> 12.6, 17.0 ->
-// 12.6, 17.2 -> 12.0, 21.9 -> 12.6 and its 1 x 1 shortcut of four steps 7.6 -> 6.8.
+// 256 channels, 3 x 3, four 28 x 28 maps in 16 x 32 / 8 x 16 / 16 x 16 / 4 x 16 blocks (rows named 1.5 / 1.9 / 2.1 / 2.7
+// times) 13.5 -> 13.7 (not taken), 18.1 -> 15.7, 18.1 -> 16.0, 26.1 -> 15.7 us; 128 channels on eight 56 x 56 maps 21.9 ->
+// 26.1 (not taken), 32.3 -> 29.6, 32.4 -> 29.7, 41.7 -> 30.0; 1 x 1 with 8 steps 7.1 -> 7.5 (not taken).  At stride 2, where
+// a window is two loads, 128 -> 256 channels from four 56 x 56 maps 12.5 -> 10.6, 16.0 -> 11.8, 16.2 -> 11.9, 20.4 -> 12.0
+// and its 1 x 1 shortcut 7.0 -> 6.6, 7.6 -> 7.2, 7.8 -> 7.1, 8.8 -> 7.2.
 static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, int32_t H, int32_t W, int32_t stride, int32_t batch) {
     if (A->M <= 16 || tall.runs == 0 || tall.total * 4 > A->gather.nsteps * 3) return false;
     if (stride == 1 && (tall.longest < 12 || tall.total * 7 > A->gather.nsteps * 4)) return false;

@@ -14,8 +14,8 @@ namespace grim {
 // another this saves the second dispatch and the pre-activations' way through memory; the workgroup cannot be smaller,
 // since the cell needs all gates of a unit.
 // Bound: two dependent fetches (row numbers, then rows of X and weights) and the launch.  1024 units and inputs in 8 x 12 of
-// 32 x 32: LSTM 32 columns 9.1 -> 7.5 us per step, 9 columns 30.2 -> 8.4; GRU 32 columns 8.3 -> 7.0, 64 columns 12.4 -> 7.8;
-// LSTM of mixed rates, one column 11.5 -> 8.7.
+// 32 x 32: LSTM 32 columns 8.8 -> 7.2 us per step, 9 columns 29.9 -> 8.3; GRU 32 columns 7.8 -> 6.4, 64 columns 12.2 -> 7.3;
+// LSTM of mixed rates, one column 11.6 -> 8.4.
 struct RnnGatherMatrix {
     const int32_t *sptr;
     const uint32_t *rows, *desc;

@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     // (straight-line code, so that the wait for an older read leaves the younger ones in flight); a
                     // wave moves on as a whole, each lane with the first complete set of words it has seen (a slot is
                     // written again two steps later at the earliest, so a later read cannot show anything else).
-                    // (A set on one XCD: one read at a time is quicker, 2.39 -> 2.30 us per LSTM step of 1024 units.)
+                    // (A set on one XCD: one read at a time is quicker, 2.39 -> 2.30 us per step of one LSTM of 1024 units.)
                     unsigned int polls = 0;
                     bool ok = false, dead = false;
                     if constexpr (!PLACED) {

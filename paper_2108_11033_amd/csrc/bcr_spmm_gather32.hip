@@ -18,9 +18,9 @@ namespace grim {
 // columns 4 NT kg + NT r + q (r, q < 4, NT) of one output row: contiguous.
 //
 // Bound: rows of X through L2 and the vector L1 (each run fetches the rows it keeps: 58 MB where X is 14 MB, 256 x 1152 in
-// 16 x 32 blocks at 3136 columns), then MFMA, 32 cycles each, 16 a step: 2.9 us there.  That product takes 11.7 us, on the
-// vector ALUs 46.6; 512 x 4608 of mixed rates at 777 columns 25 against 129, 64 x 288 in 4 x 16 blocks at 20000 columns
-// 15.8 against 104, 256 x 256 at 64 columns 3.9 against 5.8.
+// 16 x 32 blocks at 3136 columns), then MFMA, 32 cycles each, 16 a step: 2.9 us there.  That product takes 11.6 us, on the
+// vector ALUs 46.9; 512 x 4608 of mixed rates at 777 columns 25.6 against 130, 64 x 288 in 4 x 16 blocks at 20000 columns
+// 17.6 against 106, 256 x 256 at 64 columns 3.3 against 4.8.
 struct Gather32Params {
     const int32_t *sptr;
     const int32_t *out_row;

@@ -73,7 +73,8 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // ALIGNED: rows of X are 16-byte aligned and N a multiple of 8.  Otherwise a piece is still one 16-byte load, at
 // whatever alignment its row has: from an 8-byte-aligned row it costs the vector L1 next to nothing more, from a row that
 // starts at an odd element about three aligned ones -- against the staged and vector-ALU kernels, which took such
-// products element by element before (512 x 4608 at 147 columns: 114 -> 7.7 us).
+// products element by element before (512 x 4608 in 4 x 16 blocks at 785 columns: 414 -> 25.6 us; in 16 x 32 blocks at 147,
+// with small tiles, 66 -> 5.0).
 // NARROW: N below the tile's width: one tile, whose pieces past N are fetched from column 0 and never stored.
 // NT: 16-column sub-tiles of a tile (4; 2 and 1 for products of at most 32 and 16 columns, whose pieces then take a half
 // or a quarter of the load instructions and LDS traffic of a padded 64-column tile; 2 also for long strips and few tiles).
