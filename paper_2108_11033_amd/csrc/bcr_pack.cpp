@@ -1015,11 +1015,11 @@ static grim_status launch_skinny(const grim_bcr_matrix *A, const void *X, int64_
 // which kernel family a grim_bcr_spmm_tuned call runs
 enum SpmmRoute { ROUTE_NONE, ROUTE_SPMV, ROUTE_FMA, ROUTE_MMA, ROUTE_GATHER, ROUTE_GATHER32, ROUTE_WIDE };
 
-// what the columns the wide-tile kernel leaves over cost on the kernels that take any N
+// what the columns the wide-tile kernel leaves over (a multiple of eight, like N) cost on the kernels that take any N
 static double rest_cost(const grim_bcr_matrix *A, int64_t n) {
     int tn = 0, g = 0;
     double best = A->mma.present ? mma_best_shape(A, n, 0, 0, &tn, &g) : -1.0;
-    if (A->gather.present && n % 4 == 0) {
+    if (A->gather.present) {
         const double c = gather_cost(A, n);
         if (best < 0 || c < best) best = c;
     }

@@ -64,8 +64,9 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     // fewer than 64 columns: one tile of the narrowest width that holds them
     // Long strips and few tiles (14 x 14 maps and less): 32-column tiles, whose twice as many workgroups have twelve waves
     // with three steps in flight -- 512 x 4608 at 147 columns 8.0 -> 5.0 us, at 64 / 196 / 256 columns 6.0 / 6.4 / 6.2 ->
-    // 4.0 / 5.1 / 4.6, 256 x 4608 in 16 x 16 blocks at 392 columns 8.5 -> 6.6 -- while every workgroup has a compute unit.
-    // Strips below 16 steps stay (256 x 1152 at 256 columns 3.8 us either way).
+    // 4.0 / 5.1 / 4.6, 256 x 4608 in 16 x 16 blocks at 392 columns 8.5 -> 6.6 -- while every workgroup has a compute unit: with
+    // 288 or 384 (tile, run) pairs 512 x 1152, 512 x 2304 and 1024 x 2304 take 4.5 to 4.9 us in 64-column tiles, 5.3 to 5.7 in
+    // these.  Strips below 16 steps stay (256 x 1152 at 256 columns 3.8 us either way).
     const bool small_tiles = may_take_small_tiles && N >= 64 && A->gather.max_steps >= 16 && (N + 31) / 32 * p.nbr <= 256;
     const int nt = small_tiles ? 2 : N > 32 ? 4 : N > 16 ? 2 : 1;
     p.ntiles = (int32_t)((N + nt * 16 - 1) / (nt * 16));
