@@ -158,6 +158,7 @@ grim_status launch_conv_wide(const grim_bcr_matrix *A, const void *F, int32_t Ci
     p.f_total = (int32_t)((batch - 1) * (int64_t)p.f_img_stride + (int64_t)Cin * HW);
     p.y_img_stride = batch > 1 ? y_img_stride : 0;
     p.bias = bias; p.relu = relu; p.odt = odt;
+    p.y_vec4 = reinterpret_cast<uintptr_t>(Y) % 8 == 0 && ldy % 4 == 0 && p.y_img_stride % 4 == 0 ? 1 : 0;
     const int tn = conv_wide_main_tile(A, p.KK);
     const int64_t per_round = 256 / p.ngroups;
     const int64_t n_main = N / tn / per_round * per_round * tn;

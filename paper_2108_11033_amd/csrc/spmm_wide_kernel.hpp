@@ -31,6 +31,7 @@ struct WideParams {
     int64_t y_img_stride;        // elements between the [M][ldy] outputs of two images
     const float *bias;           // M values added to every position of a row, or null
     int32_t relu, odt;           // max(., 0) after the bias; element type of Y
+    int32_t y_vec4;              // four consecutive 16-bit outputs of a row can be stored at once
 };
 
 // fp32 -> bf16, round to nearest even; NaN stays NaN
@@ -532,66 +533,86 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
 
     // ---- write the strip tiles of Y (original row order); streaming stores: Y is written once and not read here ----
     // CONV: the layer's epilogue (bias, rectifier, rounding to the next layer's element type); column n is position
-    // n % HW of image n / HW, whose [M][ldy] output starts y_img_stride elements after the previous image's
-    auto put = [&](int64_t at, float v) {
-        if (!CONV || p.odt == GRIM_F32) {
-            __builtin_nontemporal_store(v, &p.Y[at]);
-        } else if (p.odt == GRIM_F16) {
-            reinterpret_cast<_Float16 *>(p.Y)[at] = (_Float16)v;
-        } else {
-            reinterpret_cast<unsigned short *>(p.Y)[at] = wide_f32_to_bf16(v);
-        }
-    };
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int t = s == 0 ? tA : tB;
-        if (t >= p.nbr) continue;
-        const int64_t row0 = (int64_t)p.strip_order[t] * BR;
+    // n % HW of image n / HW, whose [M][ldy] output starts y_img_stride elements after the previous image's.  The output
+    // type is chosen once and a strip's biases are fetched before its first store: stores and loads share a counter, so a
+    // bias fetched between two stores is waited for behind the stores (512 channels, 3 x 3, eight 56 x 56 maps: 112 -> 94 us; 1 x 1, 512 -> 256
+    // channels on five 112 x 112 maps in 16-row blocks, whose four 16-bit outputs of a row are one store: 69 -> 44).
+    auto finish = [&](auto out_type) {
+        constexpr int ODT = decltype(out_type)::value;
+        using Out = typename Elem<ODT>::type;
+        Out *const Y = reinterpret_cast<Out *>(p.Y);
+        auto rounded = [](float v) {
+            if constexpr (ODT == GRIM_BF16) return wide_f32_to_bf16(v);
+            else return (Out)v;
+        };
+        int64_t col[NT];
 #pragma unroll
         for (int q = 0; q < NT; ++q) {
-            if constexpr (BR == 16) {
-                // D[n][m]: lane holds m = lane % 16, n = 4 * (lane / 16) + 0..3 (16-byte aligned: checked at launch)
-                const int64_t n = n0 + q * 16 + 4 * (lane >> 4);
-                const int64_t row = row0 + (lane & 15);
-                if constexpr (CONV) {
-                    const int64_t img = n / p.HW;
-                    const int64_t at = img * p.y_img_stride + row * p.ldy + (n - img * p.HW);
-                    f32x4 v = acc[s][q];
-                    const float b = p.bias ? p.bias[row] : 0.f;
+            const int64_t n = n0 + q * NSUB + (BR == 16 ? 4 * (lane >> 4) : lane & 31);
+            col[q] = n;
+            if constexpr (CONV) {
+                const unsigned int img = (unsigned int)n / (unsigned int)p.HW;       // (fewer than 2^30 positions: checked at launch)
+                col[q] = img * p.y_img_stride + ((unsigned int)n - img * (unsigned int)p.HW);
+            }
+        }
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        v[e] += b;
-                        if (p.relu) v[e] = __builtin_elementwise_maximum(v[e], 0.f);     // NaN stays NaN
-                    }
-                    if (p.odt == GRIM_F32) {
-                        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p.Y + at));
-                    } else {
+        for (int s = 0; s < 2; ++s) {
+            const int t = s == 0 ? tA : tB;
+            if (t >= p.nbr) continue;
+            const int64_t row0 = (int64_t)p.strip_order[t] * BR;
+            constexpr int NBIAS = BR == 16 ? 1 : 16;
+            // BR = 16: D[n][m]: lane holds m = lane % 16, n = 4 * (lane / 16) + 0..3
+            // BR = 32: D[m][n]: lane holds n = lane % 32, m = 8 * (e / 4) + 4 * (lane / 32) + e % 4
+            const int64_t lane_row = row0 + (BR == 16 ? lane & 15 : 4 * (lane >> 5));
+            float bias[NBIAS] = {};
+            if constexpr (CONV) {
+                if (p.bias) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) put(at + e, v[e]);
-                    }
-                } else {
-                    __builtin_nontemporal_store(acc[s][q], reinterpret_cast<f32x4 *>(p.Y + row * p.ldy + n));
+                    for (int e = 0; e < NBIAS; ++e) bias[e] = p.bias[lane_row + 8 * (e >> 2) + (e & 3)];
                 }
-            } else {
-                // D[m][n]: lane holds n = lane % 32, m = 8 * (e / 4) + 4 * (lane / 32) + e % 4
-                const int64_t n = n0 + q * 32 + (lane & 31);
-                int64_t col = n;
-                if constexpr (CONV) {
-                    const int64_t img = n / p.HW;
-                    col = img * p.y_img_stride + (n - img * p.HW);
-                }
+            }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            for (int q = 0; q < NT; ++q) {
+                Out *const at = Y + lane_row * p.ldy + col[q];
+                auto value = [&](int e) {
                     float v = acc[s][q][e];
                     if constexpr (CONV) {
-                        v += p.bias ? p.bias[row0 + m] : 0.f;
-                        if (p.relu) v = __builtin_elementwise_maximum(v, 0.f);
+                        v += bias[BR == 16 ? 0 : e];
+                        if (p.relu) v = __builtin_elementwise_maximum(v, 0.f);       // NaN stays NaN
                     }
-                    put((row0 + m) * p.ldy + col, v);
+                    return v;
+                };
+                if constexpr (BR == 16) {
+                    if constexpr (ODT == GRIM_F32) {       // (16-byte aligned: checked at launch)
+                        __builtin_nontemporal_store(f32x4{value(0), value(1), value(2), value(3)}, reinterpret_cast<f32x4 *>(at));
+                    } else {
+                        Out v[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = rounded(value(e));
+                        if (p.y_vec4) {
+                            uint2 w;
+                            __builtin_memcpy(&w, v, 8);
+                            *reinterpret_cast<uint2 *>(at) = w;
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) at[e] = v[e];
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        Out *const to = at + (8 * (e >> 2) + (e & 3)) * p.ldy;
+                        if constexpr (ODT == GRIM_F32) __builtin_nontemporal_store(value(e), to);
+                        else *to = rounded(value(e));
+                    }
                 }
             }
         }
+    };
+    if (!CONV || p.odt == GRIM_F32) finish(std::integral_constant<int, GRIM_F32>{});
+    else if constexpr (CONV) {
+        if (p.odt == GRIM_F16) finish(std::integral_constant<int, GRIM_F16>{});
+        else finish(std::integral_constant<int, GRIM_BF16>{});
     }
 }
 
