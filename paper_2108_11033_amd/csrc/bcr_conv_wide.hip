@@ -20,9 +20,10 @@ namespace grim {
 constexpr int kConvWideRestTile = 32;
 
 static size_t conv_wide_lds(const grim_bcr_matrix *A, int tn, int KK) {
-    // two stages, the (tap, piece) mask table, four per-chunk row tables
-    return 2 * (size_t)wide_stage_bytes(A->mmaw.chunk_rows, tn, A->mmaw.amax[2]) + (size_t)(KK + 1) * (tn / 8) * 16 +
-           4 * (size_t)wide_max_chunk_rows(A->BR) * 8;
+    // two stages; kConvAnyTap: the (tap, piece) mask table, four per-chunk row tables
+    const size_t stages = 2 * (size_t)wide_stage_bytes(A->mmaw.chunk_rows, tn, A->mmaw.amax[2]);
+    if (conv_tap_ways(tn, KK, A->mmaw.chunk_rows)) return stages;
+    return stages + (size_t)(KK + 1) * (tn / 8) * 16 + 4 * (size_t)wide_max_chunk_rows(A->BR) * 8;
 }
 
 // the widest compiled tile whose records fit the fetching waves' registers and whose stages fit LDS; 0: none
@@ -58,9 +59,9 @@ bool conv_wide_applies(const grim_bcr_matrix *A, const void *F, int32_t Cin, int
     return per_round > 0 && N / tn >= per_round;
 }
 
-template <bool BF16, int BR, int NT>
-static grim_status launch_conv_wide_inst(const WideParams &p, size_t lds, int64_t nwg, hipStream_t stream) {
-    auto kern = bcr_spmm_wide<BF16, BR, NT, true>;
+template <bool BF16, int BR, int NT, int FORM>
+static grim_status launch_conv_wide_form(const WideParams &p, size_t lds, int64_t nwg, hipStream_t stream) {
+    auto kern = bcr_spmm_wide<BF16, BR, NT, FORM>;
     static std::atomic<bool> attr_done{false};
     if (lds > 64 * 1024 && !attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
@@ -73,24 +74,30 @@ static grim_status launch_conv_wide_inst(const WideParams &p, size_t lds, int64_
     return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
 }
 
+template <bool BF16, int BR, int NT>
+static grim_status launch_conv_wide_inst(const WideParams &p, size_t lds, int64_t nwg, hipStream_t stream) {
+    return p.tap_ways ? launch_conv_wide_form<BF16, BR, NT, kConvByTap>(p, lds, nwg, stream)
+                      : launch_conv_wide_form<BF16, BR, NT, kConvAnyTap>(p, lds, nwg, stream);
+}
+
 // The wide-tile workgroups and, behind them in the same launch, the workgroups of the row-gathering convolution (its
 // twelve-wave form, row numbers split in the kernel) for the positions left over: they start on whichever compute unit
 // is done with its wide workgroup instead of behind a dispatch of their own.
-template <bool BF16, int BR, int NT>
+template <bool BF16, int BR, int NT, int FORM>
 __global__ void __launch_bounds__(kWideThreads) bcr_conv_wide_rest(WideParams wp, ConvParams cp, int wide_wgs) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     if ((int)blockIdx.x < wide_wgs) {
-        wide_body<BF16, BR, NT, true>(wp, lds, blockIdx.x);
+        wide_body<BF16, BR, NT, FORM>(wp, lds, blockIdx.x);
         return;
     }
     conv_gather_body<BF16, false, kConvLongWaves, 0>(cp, lds, (int)blockIdx.x - wide_wgs);
 }
 static_assert(kConvLongWaves * 64 == kWideThreads, "the two bodies share the workgroup's twelve waves");
 
-template <bool BF16, int BR, int NT>
-static grim_status launch_conv_wide_rest_inst(const WideParams &wp, const ConvParams &cp, size_t lds, int64_t wide_wgs, int64_t rest_wgs,
+template <bool BF16, int BR, int NT, int FORM>
+static grim_status launch_conv_wide_rest_form(const WideParams &wp, const ConvParams &cp, size_t lds, int64_t wide_wgs, int64_t rest_wgs,
                                               hipStream_t stream) {
-    auto kern = bcr_conv_wide_rest<BF16, BR, NT>;
+    auto kern = bcr_conv_wide_rest<BF16, BR, NT, FORM>;
     static std::atomic<bool> attr_done{false};
     if (lds > 64 * 1024 && !attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
@@ -103,12 +110,20 @@ static grim_status launch_conv_wide_rest_inst(const WideParams &wp, const ConvPa
     return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
 }
 
+template <bool BF16, int BR, int NT>
+static grim_status launch_conv_wide_rest_inst(const WideParams &wp, const ConvParams &cp, size_t lds, int64_t wide_wgs, int64_t rest_wgs,
+                                              hipStream_t stream) {
+    return wp.tap_ways ? launch_conv_wide_rest_form<BF16, BR, NT, kConvByTap>(wp, cp, lds, wide_wgs, rest_wgs, stream)
+                       : launch_conv_wide_rest_form<BF16, BR, NT, kConvAnyTap>(wp, cp, lds, wide_wgs, rest_wgs, stream);
+}
+
 // positions [n_begin, n_end) of the batch in tiles of tn (n_end - n_begin >= tn, both multiples of 8); with `rest`, its
 // workgroups (`rest_wgs` of them, `rest_lds` bytes of workgroup memory) behind the wide ones in the same launch
 static grim_status conv_wide_range(const grim_bcr_matrix *A, WideParams p, int tn, int64_t n_begin, int64_t n_end, hipStream_t stream,
                                    const ConvParams *rest = nullptr, int64_t rest_wgs = 0, size_t rest_lds = 0) {
     p.n_begin = n_begin;
     p.N = n_end;
+    p.tap_ways = conv_tap_ways(tn, p.KK, p.chunk_rows);
     p.ntiles = (int32_t)((n_end - n_begin + tn - 1) / tn);
     const int64_t nwg = ((int64_t)p.ntiles + 15) / 16 * 16 * p.ngroups;
     if (nwg + rest_wgs > 0x7fffffff) return GRIM_ERR_SHAPE;

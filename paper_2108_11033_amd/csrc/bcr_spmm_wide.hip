@@ -106,7 +106,7 @@ template <bool BF16, int BR, int NT>
 __global__ void __launch_bounds__(kWideThreads) bcr_spmm_wide_rest(WideParams wp, GatherParams gp, int wide_wgs) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     if ((int)blockIdx.x < wide_wgs) {
-        wide_body<BF16, BR, NT, false>(wp, lds, blockIdx.x);
+        wide_body<BF16, BR, NT, kConvNone>(wp, lds, blockIdx.x);
         return;
     }
     // (a workgroup number past the last (tile, strip) leaves as a whole: no wave may wait at a barrier others skip)

@@ -1,6 +1,7 @@
 // The wide-tile staged kernel (see bcr_spmm_wide.hip for the design): one template for the product on a matrix X in
 // memory and for the convolution whose im2col matrix is never formed (CONV: the fetching waves build the rows of
-// that matrix in LDS straight from the feature maps; everything after the fetch is the same).
+// that matrix in LDS straight from the feature maps; everything after the fetch is the same; two ways of dealing the
+// rows to the fetching threads, kConvAnyTap and kConvByTap).
 #pragma once
 #include <algorithm>
 
@@ -27,6 +28,7 @@ struct WideParams {
     int32_t kw_magic;            // ceil(256 / kw): tap / kw = tap * magic >> 8 (checked for every tap at launch)
     int32_t f_img_stride;        // elements
     int32_t f_total;             // elements from F to the end of the last image (f_total * 2 < 2^31)
+    int32_t tap_ways;            // kConvByTap: fetching threads that share the rows of one (tap, piece)
     int64_t n_begin;             // first column of this launch (N is its end)
     int64_t y_img_stride;        // elements between the [M][ldy] outputs of two images
     const float *bias;           // M values added to every position of a row, or null
@@ -68,13 +70,31 @@ __host__ __device__ inline int wide_stage_bytes(int chunk_rows, int tn, int amax
     return (chunk_rows + 1) * (tn * 2 + kWidePad) + amax * 16;
 }
 
+// How the convolution's rows of a chunk are dealt to the fetching threads.
+//   kConvAnyTap: 16-byte units in order; the row's channel and tap and the unit's validity mask come out of tables in LDS.
+//   kConvByTap:  a thread keeps one (tap, piece of the tile) and takes every tap_ways-th channel: the mask is four registers,
+//                a row's address one addition.  Taken where there is a thread for every (tap, piece) and the rows of a chunk
+//                are at most kTapUnits per thread (see conv_tap_ways); 5 x 5 kernels have more of them than there are threads.
+// 512 channels, 3 x 3, eight 56 x 56 maps, 32-row blocks of mixed rates 94 -> 78.5 us; 256 channels, 3 x 3, four 112 x 112 maps, 16-row
+// blocks 80 -> 67.5; 1 x 1, 512 -> 256 channels on three 112 x 112 maps 35.6 -> 30.6 (graphs of one call): two dependent LDS reads
+// and a table-driven address per unit are gone, a fetching wave's instructions per unit from about 35 to 12.
+constexpr int kConvNone = 0, kConvAnyTap = 1, kConvByTap = 2;
+constexpr int wide_tap_units(int tn) { return tn == 96 ? 11 : tn == 32 ? 8 : 15; }
+
+// Fetching threads per (tap, piece) of the form that keeps them apart; 0: that form does not apply
+constexpr int conv_tap_ways(int tn, int KK, int chunk_rows) {
+    const int pairs = KK * (tn / 8);
+    const int ways = pairs <= kWideFetchThreads ? kWideFetchThreads / pairs : 0;
+    return ways > 0 && ((chunk_rows + KK - 1) / KK + ways - 1) / ways <= wide_tap_units(tn) ? ways : 0;
+}
+
 // third dword of a raw buffer descriptor on this GPU family (32-bit data format); only the range check matters here
 constexpr unsigned int kBufferFlags = 0x00020000u;
 
 // BR = 16: v_mfma_f32_16x16x32, product taken as (X^T tile) x (W^T fragment): a lane ends with 4 consecutive
 //          columns of one output row.  BR = 32: v_mfma_f32_32x32x16, weights first: a lane holds one column, 16 rows.
 // (the body as a function of the workgroup's number, so that a kernel can run other workgroups next to these)
-template <bool BF16, int BR, int NT, bool CONV>
+template <bool BF16, int BR, int NT, int CONV>
 __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int block_x) {
     constexpr int NSUB = BR == 16 ? 16 : 32;
     constexpr int TN = NT * NSUB;
@@ -124,6 +144,151 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
         if (ft < 2 * (PITCH / 4)) {
             const int st = ft / (PITCH / 4), w = ft % (PITCH / 4);
             *reinterpret_cast<unsigned int *>(lds + st * stage_bytes + p.chunk_rows * PITCH + w * 4) = 0u;
+        }
+        // Where the records of the group's strips in a chunk start and how many 16-byte units they are: two table
+        // reads through the scalar cache, asked for at the top of a chunk period and used at its end, so that their
+        // latency runs under the period's stores
+        struct RecRange { int b0, units; };
+        auto rec_range = [&](int chunk) {
+            chunk = chunk < p.nchunks ? chunk : p.nchunks - 1;
+            const Table bp = bptr + (int64_t)chunk * (p.nbr + 1);
+            RecRange r;
+            r.b0 = __builtin_amdgcn_readfirstlane(bp[t0]);
+            r.units = __builtin_amdgcn_readfirstlane(bp[t1]) - r.b0;
+            return r;
+        };
+        // A chunk's records go from global memory straight into the stage's record area (no registers, no LDS store
+        // instructions): a wave's load puts lane l's 16 bytes at the wave's base (in M0) + 16 l; lanes past the range's
+        // end are masked off and write nothing.  The stage must be free when the load is ISSUED (see the loop below).
+        // Written as assembly so that the compiler's own wait insertion does not see these loads: it would otherwise
+        // drain every load of the wave before the next LDS store and before every barrier, which ends the rows'
+        // two-chunk prefetch.  The waits it computes for the rows stay valid -- loads it does not know of only make a
+        // wait for an older load stricter -- and the wait for the records themselves is explicit (landed_but_rows).
+        const int fwave = __builtin_amdgcn_readfirstlane(ft >> 6);
+        auto direct_records = [&](int chunk, const RecRange &r) {
+            const int sbase = (int)(uintptr_t)(__attribute__((address_space(3))) char *)lds + (chunk & 1) * stage_bytes + xbytes;
+            const unsigned char *src = p.recs + (int64_t)r.b0 * 16;
+#pragma unroll
+            for (int i = 0; i < SRU; ++i) {
+                if (i * kWideFetchThreads < r.units) {
+                    const int u = i * kWideFetchThreads + ft;
+                    if (u < r.units)
+                        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                                     :: "s"(sbase + (i * kWideFetchThreads + fwave * 64) * 16), "v"(src + (int64_t)u * 16)
+                                     : "memory", "m0");
+                }
+            }
+        };
+        if constexpr (CONV == kConvByTap) {
+            // Thread = (tap, 16-byte piece c of the tile, way): its unit i of a chunk is the row of its tap of the (way +
+            // tap_ways i)-th channel that begins its tap in the chunk.  Rows a thread has none of and rows past the chunk
+            // go into the padding bytes of row 0, which nobody reads; rows past K are never multiplied.
+            constexpr int U = wide_tap_units(TN);
+            const int pairs = p.KK * CPR;
+            const int way = ft / pairs, pair = ft - way * pairs;
+            const int tap = pair / CPR, c = pair - tap * CPR;
+            const int tr = tap / p.kw, tq = tap - tr * p.kw;
+            const int dr = tr - (p.kh >> 1), dq = tq - (p.kw >> 1);
+            const int64_t n = n0 + c * 8;
+            const int img = (int)(n / p.HW);
+            const int pos = (int)(n - (int64_t)img * p.HW);
+            unsigned int mask[4] = {0u, 0u, 0u, 0u};     // the positions whose shifted pixel lies inside the image
+            {
+                int h = pos / p.W, w = pos - h * p.W;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool ok = h + dr >= 0 && h + dr < p.H && w + dq >= 0 && w + dq < p.W;
+                    mask[j >> 1] |= ok ? (j & 1 ? 0xffff0000u : 0x0000ffffu) : 0u;
+                    if (++w == p.W) { w = 0; ++h; }
+                }
+            }
+            const bool idle = way >= p.tap_ways;
+            const int ebase = idle ? 0 : img * p.f_img_stride + pos + dr * p.W + dq + way * p.HW;
+            const int rbase = idle ? 1 << 20 : way * p.KK;             // (idle: every row is past the chunk)
+            const int estep = p.tap_ways * p.HW, rstep = p.tap_ways * p.KK;
+            const int spare = TN * 2 + (c & 1) * 16;
+            // first channel of a chunk and the tap its first row is
+            auto first_of = [&](int chunk, int &cin, int &t) {
+                const unsigned int k0 = (unsigned int)(chunk * p.chunk_rows);
+                cin = (int)__umulhi(k0 << 1, (unsigned int)p.kk_magic);
+                t = (int)k0 - cin * p.KK;
+            };
+            auto element = [&](int cin, int t) {                       // of the thread's unit 0 (its channel begins one later
+                return (int)((unsigned int)ebase + (unsigned int)(cin + (tap < t ? 1 : 0)) * (unsigned int)p.HW);   // if its tap of the first is past)
+            };
+            const int emax = p.f_total - 8;
+            auto load_taps = [&](int chunk, u32x4 (&rx)[U]) {
+                int cin, t;
+                first_of(chunk < p.nchunks ? chunk : p.nchunks - 1, cin, t);
+                unsigned int e = (unsigned int)element(cin, t);
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    const int ec = (int)e < 0 ? 0 : (int)e > emax ? emax : (int)e;      // (windows at the ends of the batch: see below)
+                    WideWindow wv;
+                    __builtin_memcpy(&wv, reinterpret_cast<const char *>(p.F) + (unsigned int)(ec * 2), 16);
+                    rx[i] = u32x4{wv.d[0], wv.d[1], wv.d[2], wv.d[3]};
+                    e += (unsigned int)estep;
+                }
+            };
+            // can a window of the chunk reach before the first or behind the last element of the batch?  (the same for the
+            // whole workgroup; windows of rows past K do not count)
+            const int img0 = (int)(n0 / p.HW), img1 = (int)((n0 + TN - 8) / p.HW);
+            const int64_t elo = (int64_t)img0 * p.f_img_stride + (n0 - (int64_t)img0 * p.HW) - ((p.kh >> 1) * p.W + (p.kw >> 1));
+            const int64_t ehi = (int64_t)img1 * p.f_img_stride + (n0 + TN - (int64_t)img1 * p.HW) +
+                                (p.kh - 1 - (p.kh >> 1)) * p.W + (p.kw - 1 - (p.kw >> 1));
+            const int last_cin = p.K / p.KK - 1;
+            auto store_taps = [&](int chunk, u32x4 (&rx)[U]) {
+                int cin, t;
+                first_of(chunk, cin, t);
+                const int cend = cin + (p.chunk_rows + p.KK - 1) / p.KK < last_cin ? cin + (p.chunk_rows + p.KK - 1) / p.KK : last_cin;
+                if (elo + (int64_t)cin * p.HW < 0 || ehi + (int64_t)cend * p.HW > p.f_total) {
+                    unsigned int e = (unsigned int)element(cin, t);
+#pragma unroll
+                    for (int i = 0; i < U; ++i) {
+                        const int ec = (int)e < 0 ? 0 : (int)e > emax ? emax : (int)e;
+                        const int d = (int)e - ec;    // the pixels wanted start d elements behind (before: d < 0) the ones loaded
+                        if (d != 0) {
+                            unsigned __int128 x = (unsigned __int128)rx[i][0] | (unsigned __int128)rx[i][1] << 32 |
+                                                  (unsigned __int128)rx[i][2] << 64 | (unsigned __int128)rx[i][3] << 96;
+                            x = d >= 8 || d <= -8 ? (unsigned __int128)0 : d > 0 ? x >> (16 * d) : x << (16 * -d);
+                            rx[i] = u32x4{(unsigned int)x, (unsigned int)(x >> 32), (unsigned int)(x >> 64), (unsigned int)(x >> 96)};
+                        }
+                        e += (unsigned int)estep;
+                    }
+                }
+                char *sbase = lds + (chunk & 1) * stage_bytes;
+                int row = rbase + tap - t + (tap < t ? p.KK : 0);
+                int at = row * PITCH + c * 16;
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    const u32x4 v = u32x4{rx[i][0] & mask[0], rx[i][1] & mask[1], rx[i][2] & mask[2], rx[i][3] & mask[3]};
+                    *reinterpret_cast<u32x4 *>(sbase + (row < p.chunk_rows ? at : spare)) = v;
+                    row += rstep;
+                    at += rstep * PITCH;
+                }
+            };
+            // A chunk's windows come out of the caches: asked for one period before they are written to LDS.  They have
+            // arrived when that period begins; waiting for them before the records are asked for keeps the wait from
+            // covering those too (loads return in order).
+            u32x4 RX[U];
+            RecRange rcur = rec_range(0), rnxt = rec_range(1);
+            load_taps(0, RX);
+            direct_records(0, rcur);
+            store_taps(0, RX);
+            rcur = rnxt;
+            load_taps(1, RX);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U) : "memory");
+            __syncthreads();
+            for (int ch = 0; ch < p.nchunks; ++ch) {
+                rnxt = rec_range(ch + 2);
+                __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0)
+                if (ch + 1 < p.nchunks) { direct_records(ch + 1, rcur); store_taps(ch + 1, RX); }
+                rcur = rnxt;
+                load_taps(ch + 2, RX);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U) : "memory");   // the records are in LDS
+                __syncthreads();
+            }
+            return;
         }
         // The thread's i-th unit of a chunk is unit i * 256 + ft = (row of the chunk, 16-byte piece of the row).
         // The loads of the rows are buffer loads, always issued: a row past the end of K is out of the buffer's range
@@ -203,40 +368,6 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
             const_cast<unsigned short *>(CONV ? p.F : p.X + n0), 0, CONV ? 16 : (int)(((int64_t)(p.K - 1) * p.ldx + TN) * 2), kBufferFlags);
         u32x4 RX0[SXU], RX1[SXU];
         // (past the last chunk the last one is fetched again and never stored)
-        // where the records of the group's strips in a chunk start and how many 16-byte units they are: two table
-        // reads through the scalar cache, asked for at the top of a chunk period and used at its end, so that their
-        // latency runs under the period's stores
-        struct RecRange { int b0, units; };
-        auto rec_range = [&](int chunk) {
-            chunk = chunk < p.nchunks ? chunk : p.nchunks - 1;
-            const Table bp = bptr + (int64_t)chunk * (p.nbr + 1);
-            RecRange r;
-            r.b0 = __builtin_amdgcn_readfirstlane(bp[t0]);
-            r.units = __builtin_amdgcn_readfirstlane(bp[t1]) - r.b0;
-            return r;
-        };
-        // A chunk's records go from global memory straight into the stage's record area (no registers, no LDS store
-        // instructions): a wave's load puts lane l's 16 bytes at the wave's base (in M0) + 16 l; lanes past the range's
-        // end are masked off and write nothing.  The stage must be free when the load is ISSUED (see the loop below).
-        // Written as assembly so that the compiler's own wait insertion does not see these loads: it would otherwise
-        // drain every load of the wave before the next LDS store and before every barrier, which ends the rows'
-        // two-chunk prefetch.  The waits it computes for the rows stay valid -- loads it does not know of only make a
-        // wait for an older load stricter -- and the wait for the records themselves is explicit (landed_but_rows).
-        const int fwave = __builtin_amdgcn_readfirstlane(ft >> 6);
-        auto direct_records = [&](int chunk, const RecRange &r) {
-            const int sbase = (int)(uintptr_t)(__attribute__((address_space(3))) char *)lds + (chunk & 1) * stage_bytes + xbytes;
-            const unsigned char *src = p.recs + (int64_t)r.b0 * 16;
-#pragma unroll
-            for (int i = 0; i < SRU; ++i) {
-                if (i * kWideFetchThreads < r.units) {
-                    const int u = i * kWideFetchThreads + ft;
-                    if (u < r.units)
-                        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                                     :: "s"(sbase + (i * kWideFetchThreads + fwave * 64) * 16), "v"(src + (int64_t)u * 16)
-                                     : "memory", "m0");
-                }
-            }
-        };
         // every load of this wave has arrived (the direct ones: is in LDS) except the youngest SXU: loads return in
         // order, and a chunk's rows are at least SXU load instructions, always issued
         auto landed_but_rows = [&]() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(SXU) : "memory"); };
@@ -520,7 +651,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
         }
     };
 
-    if constexpr (CONV) __syncthreads();         // (the fetching waves' table of validity masks)
+    if constexpr (CONV == kConvAnyTap) __syncthreads();         // (the fetching waves' tables)
     Entry en = entry_of(0);
     __syncthreads();
     for (int c = 0; c < p.nchunks; ++c) {
@@ -529,7 +660,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
         en = en1;
         __syncthreads();
     }
-    if (p.nchunks & 1) __syncthreads();          // (the fetching waves' periods come in pairs)
+    if (CONV != kConvByTap && (p.nchunks & 1)) __syncthreads();  // (the fetching waves' periods come in pairs)
 
     // ---- write the strip tiles of Y (original row order); streaming stores: Y is written once and not read here ----
     // CONV: the layer's epilogue (bias, rectifier, rounding to the next layer's element type); column n is position
@@ -616,7 +747,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     }
 }
 
-template <bool BF16, int BR, int NT, bool CONV = false>
+template <bool BF16, int BR, int NT, int CONV = kConvNone>
 __global__ void __launch_bounds__(kWideThreads) bcr_spmm_wide(WideParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     wide_body<BF16, BR, NT, CONV>(p, lds, blockIdx.x);

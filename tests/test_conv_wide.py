@@ -1,5 +1,5 @@
-"""Layers with a round of wide tiles and more (bcr_conv_wide): the epilogue's forms.  Compared with the conv reference and, where
-the same sums are stored in another form, bit for bit."""
+"""Layers with a round of wide tiles and more (bcr_conv_wide): the ways the rows of the im2col matrix are dealt to the fetching
+threads and the epilogue's forms.  Compared with the conv reference and, where the same sums are stored in another form, bit for bit."""
 from __future__ import annotations
 
 import numpy as np
@@ -19,6 +19,30 @@ def _layer(dtype, M, Cin, H, W, kh, kw, BR, BC, B, seed):
     A = pack_workload(g, Wt, dtype, mask)
     assert g.conv2d_kernel_name(A, Cin, H, W, kh, kw, B, 1) == "bcr_conv_wide"
     return g, A, Wt, mask, F
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,BR,BC,Cin,H,W,kh,kw,B", [
+    (256, 32, 27, 27, 64, 128, 3, 3, 3),     # 243 rows: a whole chunk of 192, then 51; channels that begin inside a chunk
+    (256, 32, 16, 16, 100, 88, 1, 3, 3),     # way after way of a flat kernel
+    (256, 32, 21, 11, 88, 96, 7, 3, 3),      # 21 taps: one thread per (tap, piece), the most there is room for
+    (256, 32, 23, 10, 88, 96, 23, 1, 3),     # 23 taps: through the tables
+    (128, 16, 30, 10, 130, 128, 3, 3, 3),    # 192-column tiles
+    (128, 16, 22, 12, 130, 128, 11, 1, 3),   # 192-column tiles, more taps than they have threads for
+    (128, 16, 25, 200, 130, 128, 1, 1, 3),   # a row per channel
+    (256, 32, 9, 5, 1, 24584, 3, 3, 1),      # windows a row above and below a map of one row
+    (256, 32, 9, 5, 8, 5, 3, 3, 700),        # maps smaller than a tile
+])
+def test_rows_of_every_kernel_shape(M, BR, BC, Cin, H, W, kh, kw, B):
+    from helpers import TOL
+    from oracle import conv_ref
+    from test_conv import _masked
+    g, A, Wt, mask, F = _layer(gen.F16, M, Cin, H, W, kh, kw, BR, BC, B, 920 + kh)
+    Wm, F64 = _masked(Wt, gen.F16, mask), gen.storage_to_f64(F, gen.F16)
+    pad = 4 if B > 1 else 0
+    Y = _run_plan(g, A, F, gen.F16, M, kh, kw, 1, pad=pad)
+    Yref, S = conv_ref.conv2d(Wm, F64, kh, kw, 1), conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, 1)
+    assert (np.abs(Y - Yref) <= TOL[gen.F16] * S).all()
 
 
 @pytest.mark.gpu
