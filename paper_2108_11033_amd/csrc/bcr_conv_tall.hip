@@ -257,16 +257,26 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
         if (tile_edge) walk(std::true_type{}); else walk(std::false_type{});
     }
 
-    // the waves' partial tiles, added in wave order; the waves finish the (16-row run, sub-tile) pairs in turn
+    // the waves' partial tiles, added in wave order; the waves finish the (16-row run, sub-tile) pairs in turn (their output
+    // channels and biases are asked for ahead of the barrier; at the start of the kernel they would not fit the registers)
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    constexpr int PAIRS = R * NT / NWV;
+    static_assert(R * NT % NWV == 0, "pairs are dealt evenly");
+    int row[PAIRS];
+    float bias[PAIRS];
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) row[j] = p.out_row[((int64_t)t * R + (wave + j * NWV) / NT) * 16 + i16];
 #pragma unroll
     for (int m = 0; m < R; ++m)
 #pragma unroll
         for (int q = 0; q < NT; ++q) red[wave * (WAVE_LDS / 16) + (m * NT + q) * 64 + lane] = acc[m][q];
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) bias[j] = p.bias && row[j] >= 0 ? p.bias[row[j]] : 0.f;
     __syncthreads();
     unsigned int again = 0u;                     // bit per pair: one of the lane's four sums is not finite
-    for (int i = wave; i < R * NT; i += NWV) {
-        const int64_t row = p.out_row[((int64_t)t * R + i / NT) * 16 + i16];
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) {
+        const int i = wave + j * NWV;
         f32x4 sum = red[i * 64 + lane];
 #pragma unroll
         for (int w = 1; w < NWV; ++w) {
@@ -277,7 +287,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) nan = __builtin_fmaf(sum[e], 0.f, nan);
         again |= nan != nan ? 1u << i : 0u;
-        if (row >= 0) conv_finish<S2>(p, img, row, n0 + i % NT * 16 + 4 * kgroup, sum);
+        if (row[j] >= 0) conv_finish<S2>(p, img, row[j], bias[j], n0 + i % NT * 16 + 4 * kgroup, sum);
     }
     if (__builtin_amdgcn_ballot_w64(again != 0u)) {
 #pragma unroll 1
@@ -291,7 +301,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
                 const float v = n + e < p.Nv ? conv_own_run<BF16, S2>(p, Fimg, run, i16, n + e) : 0.f;
                 sum[0] = e == 0 ? v : sum[0]; sum[1] = e == 1 ? v : sum[1]; sum[2] = e == 2 ? v : sum[2]; sum[3] = e == 3 ? v : sum[3];
             }
-            conv_finish<S2>(p, img, row, n, sum);
+            conv_finish<S2>(p, img, row, p.bias ? p.bias[row] : 0.f, n, sum);
         }
     }
 }

@@ -82,12 +82,11 @@ __device__ __forceinline__ u32x4 conv_piece_mask(const ConvParams &p, int tap, i
     return u32x4{m[0], m[1], m[2], m[3]};
 }
 
-// epilogue of a layer for four consecutive positions n .. n + 3 of output channel `row`: bias, rectifier,
+// epilogue of a layer for four consecutive positions n .. n + 3 of output channel `row`: bias `b`, rectifier,
 // rounding to the next layer's element type
 template <bool S2>
-__device__ __forceinline__ void conv_finish(const ConvParams &p, int img, int64_t row, int64_t n, f32x4 sum) {
+__device__ __forceinline__ void conv_finish(const ConvParams &p, int img, int64_t row, float b, int64_t n, f32x4 sum) {
     char *Yimg = static_cast<char *>(p.Y) + (int64_t)img * p.y_img_stride * (p.odt == GRIM_F32 ? 4 : 2);
-    const float b = p.bias ? p.bias[row] : 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         sum[e] += b;
@@ -197,6 +196,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     // The first batch's row numbers and block descriptors are asked for before the validity table is built,
     // so that their latency runs under it.
     const int kgroup0 = lane >> 4;
+    const int row = p.out_row[(int64_t)t * 16 + (lane & 15)];     // output channel and bias: asked for now, needed at the very end
     const uint2 *desc2 = reinterpret_cast<const uint2 *>(p.desc);
     const uint32_t *slots = PLAN ? p.plan : p.rows;
     unsigned int npk[SB];
@@ -217,6 +217,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
         const int tap = tid / CPR, cc = tid % CPR;
         vtab[tid] = conv_piece_mask<S2>(p, tap, n0 + cc * 8);
     }
+    const float bias = p.bias && row >= 0 ? p.bias[row] : 0.f;
     __syncthreads();
     if (SOLO && !active) return;                 // (no barrier follows in that form)
 
@@ -436,11 +437,10 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
         }
     }
 
-    const int64_t row = p.out_row[(int64_t)t * 16 + (lane & 15)];
     if constexpr (SOLO) {
         if (row >= 0) {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) conv_finish<S2>(p, img, row, n0 + q * 16 + 4 * (lane >> 4), acc[q]);
+            for (int q = 0; q < NT; ++q) conv_finish<S2>(p, img, row, bias, n0 + q * 16 + 4 * (lane >> 4), acc[q]);
         }
         return;
     }
@@ -457,7 +457,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
         const f32x4 v = red[w * (conv_wave_lds(NT) / 16) + q * 64 + lane];
         sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
     }
-    if (row >= 0) conv_finish<S2>(p, img, row, n0 + q * 16 + 4 * (lane >> 4), sum);
+    if (row >= 0) conv_finish<S2>(p, img, row, bias, n0 + q * 16 + 4 * (lane >> 4), sum);
 }
 
 template <bool BF16, bool SOLO, int LONGW, int MODE, int NT, int SB>
