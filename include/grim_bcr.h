@@ -259,7 +259,8 @@ grim_status grim_bcr_conv2d_act(const grim_bcr_matrix *A, const void *F_dev, int
  *                               kh, kw odd, padding kh / 2, kw / 2; stride 1 or 2 in both directions; the output
  *                               map is Ho x Wo = ceil(H / stride) x ceil(W / stride).  Allocates the plan's words
  *                               (4 bytes per kept im2col row, padded) on the device and, where 64-row runs pay for some
- *                               batch, a second copy of the weights in that layout (done without if there is no memory).  Errors: NULL, SHAPE, DEVICE,
+ *                               batch, a second copy of the weights in that layout, or a dense one (2 bytes per entry of
+ *                               the filter matrix, kept or not; done without if there is no memory).  Errors: NULL, SHAPE, DEVICE,
  *                               ALLOC, UNSUPPORTED (as grim_bcr_conv2d).
  *   grim_bcr_conv2d_plan        F_dev: batch images [Cin][H][W] of A's element type, image b at F_dev +
  *                               b * f_image_stride elements; out_dev: batch outputs [M][ldo] (ldo >= Ho * Wo) of
@@ -276,7 +277,7 @@ grim_status grim_bcr_conv2d_act(const grim_bcr_matrix *A, const void *F_dev, int
 /* grim_bcr_conv2d_kernel_name -- which kernel grim_bcr_conv2d / _act (batch 1, stride 1) or grim_bcr_conv2d_plan runs for
  * this layer with densely stored, 16-byte aligned operands ("bcr_conv_wide": the wide-tile kernel, for stride-1 layers of
  * at least 8 row strips with at least one round of 256 workgroups' worth of positions whose H * W is a multiple of 8;
- * "bcr_conv_gather": 16-row runs; "bcr_conv_tall": 64-row runs of a plan, at stride 2 and for batches;
+ * "bcr_conv_gather": 16-row runs; "bcr_conv_tall": 64-row runs of a plan, compact or dense, at stride 2 and for batches;
  * "none": refused).  A static string; launches nothing. */
 const char *grim_bcr_conv2d_kernel_name(const grim_bcr_matrix *A, int32_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw,
                                         int32_t batch, int32_t stride);

@@ -1,0 +1,330 @@
+// Planned convolution of kernels larger than 1 x 1 with 64 rows of the matrix to a workgroup, the im2col matrix never formed
+// (Section 3.1: CONV = filter matrix x im2col matrix).
+#include "conv_tall.hpp"
+
+namespace grim {
+
+// A 64-row run of a matrix in small blocks keeps nearly every row of the im2col matrix, and forming those rows -- kh * kw
+// shifted copies of each channel, masked and parked in LDS -- is most of what bcr_conv_tall does.  Here a channel's pixels
+// under a tile go to LDS once, eight channels of a pixel side by side (turned around in registers on the way), and a kernel
+// tap is an address: a lane's eight k values of a multiply are the eight channels of one pixel, always 16 aligned bytes, and a
+// position whose tap lies outside the image reads a pixel of zeros.  The weights are the plan's dense copy in the order the
+// multiplies take them: zeros are multiplied, but nothing is looked up, expanded or masked.
+//
+// Workgroup = (tile of 64 positions, 64-row run).  Its waves split the channels, each with pixels of its own in LDS: no
+// barrier until the partial tiles are added.  A step is 32 k values = four (tap, channel octet) pairs: 16 multiplies for 4 KB
+// of weights out of L2 and 4 KB of pixels out of LDS.
+//
+// 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 blocks 16.1 -> 10.9 us (1.9 of them multiplies at the matrix cores' rate,
+// 4 the launch), 448 on seven 52 x 12 maps 40 -> 24.5, the same from 103 x 24 at stride 2 118 -> 35.  Bound by the multiplies of a
+// compute unit's waves and the latency of a chunk's pixels before them; more pixels per task (eight channels) take registers that
+// spill, two steps of weights in flight instead of three cost 4 %.
+//
+// Infinities and NaNs: as in bcr_conv_tall, sums that are not finite are formed again from the 16-row runs.
+struct ConvPatchParams : ConvTallParams {
+    const unsigned char *dense;      // [run][channel chunk][step][16-row run][lane] 16 bytes
+    int32_t cin, chunks, steps;      // channels, chunks of 8 CO of them, steps per chunk
+    int32_t zero_at;                 // byte offset of the pixel of zeros
+    int32_t wave_lds;                // bytes per wave
+};
+
+constexpr int kPatchAhead = 3;                             // tasks of a chunk asked for ahead, in 64s: as the registers allow
+constexpr int kPatchDepth = 3;                             // steps of weights in flight
+constexpr int kPatchWaveBytes = 20480;                     // eight waves, or two workgroups of four, fill a compute unit's LDS
+constexpr int patch_pixel_bytes(int octets) { return octets == 1 ? 16 : octets * 16 + 16; }      // (padded: spreads reads and writes over the banks)
+
+template <bool BF16, int CO, int NWV>
+__global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p) {
+    constexpr int R = kConvTallRuns, NT = 4, TN = 64, SB = patch_pixel_bytes(CO);
+    constexpr int D = kPatchDepth;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tile, t;
+    if (!xcd_map_at(p.map, blockIdx.x, p.ntiles, &tile, &t) || t >= p.nbr) return;
+    const int img = __builtin_amdgcn_readfirstlane(tile / p.tiles_per_img);
+    tile = __builtin_amdgcn_readfirstlane(tile - img * p.tiles_per_img);
+    const unsigned short *Fimg = p.F + (int64_t)img * p.f_img_stride;
+    int n0 = tile * TN;
+    if (n0 + TN > p.Nv) n0 = p.Nv - TN;                    // ragged last tile: overlap the neighbour
+    n0 = n0 < 0 ? 0 : n0;                                  // fewer than 64 positions: one tile, its columns past them never stored
+    char *patch = lds + wave * p.wave_lds;
+
+    const int kgroup = lane >> 4, i16 = lane & 15;
+    const int c_beg = p.chunks * wave / NWV, c_end = p.chunks * (wave + 1) / NWV;
+    const i16x8 *wt = reinterpret_cast<const i16x8 *>(p.dense) + (int64_t)t * p.chunks * p.steps * (R * 64) + lane;
+    i16x8 PW[D][R];
+    // (a group of D steps past a chunk's last, or a chunk past the wave's last: any valid step, never used)
+    auto fetch_weights = [&](i16x8 (&w)[R], int chunk, int st) {
+        st = st < p.steps ? st : p.steps - 1;
+        const i16x8 *src = wt + (int64_t)(chunk * p.steps + st) * (R * 64);
+#pragma unroll
+        for (int m = 0; m < R; ++m) w[m] = src[m * 64];
+    };
+    if (c_beg < c_end) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) fetch_weights(PW[u], c_beg, u);
+    }
+
+    // the pixels (of a channel) that a tap of the tile's positions can meet: [plo, phi]
+    const int HW = p.N, centre = (p.kh >> 1) * p.W + (p.kw >> 1), s2 = p.stride == 2;
+    auto pixel_of = [&](int n, int &h, int &w) {
+        h = n / p.Wo;
+        w = n - h * p.Wo;
+        h <<= s2; w <<= s2;
+        return h * p.W + w;
+    };
+    int hh, ww;
+    int plo = pixel_of(n0, hh, ww) - centre;
+    plo = plo < 0 ? 0 : plo > HW - 8 ? HW - 8 : plo;
+    plo -= plo > 0 ? ((int)(reinterpret_cast<uintptr_t>(Fimg) >> 1) + plo) & 1 : 0;
+    plo = __builtin_amdgcn_readfirstlane(plo);
+    int phi = pixel_of(n0 + TN < p.Nv ? n0 + TN - 1 : p.Nv - 1, hh, ww) + centre;
+    phi = __builtin_amdgcn_readfirstlane(phi < HW - 1 ? phi : HW - 1);
+    const int tasks = ((phi - plo) / 8 + 1) * CO * 2;      // (eight pixels of four channels) to turn around per chunk
+
+    f32x4 acc[R][NT];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) acc[m][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // A chunk's pixels: task = four channels of eight pixels, loaded along the pixels, written along the channels (the last
+    // pixels of a channel are met by moving the eight back, onto pixels that are written twice with the same values).  The
+    // first kPatchAhead * 64 tasks of a chunk are asked for while the chunk before it is multiplied.
+    // 16 bytes at an odd element cost the vector L1 about three times what they cost at an even one: such a row is loaded one
+    // element early, its last element by itself, and shifted into place before it is written (maps of an odd number of pixels:
+    // 288 channels, 3 x 3, seven 95 x 27 maps at stride 2 32.3 -> 27.4 us)
+    const int fodd = (int)(reinterpret_cast<uintptr_t>(Fimg) >> 1) & 1;
+    const bool any_odd = ((HW | (plo + fodd) | fodd) & 1) != 0;       // (pieces start at plo + 8 q or at HW - 8, HW apart)
+    struct Task { u32x4 row[4]; unsigned int last[4]; };
+    auto load_task = [&](Task &in, int chunk, int id) {
+        const int o = id % (CO * 2), p8 = plo + id / (CO * 2) * 8, ch = (chunk * CO * 2 + o) * 4;
+        const int e = (ch < p.cin ? ch : p.cin - 4) * HW + (p8 < HW - 8 ? p8 : HW - 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int ei = e + i * HW, odd = ei > 0 ? (ei + fodd) & 1 : 0;
+            in.row[i] = load_piece_any(Fimg + (unsigned int)(ei - odd));
+            in.last[i] = any_odd && odd ? (unsigned int)Fimg[(unsigned int)(ei + 7)] : 0u;
+        }
+    };
+    auto store_task = [&](Task &task, int chunk, int id) {
+        const int o = id % (CO * 2), p8 = plo + id / (CO * 2) * 8, st = p8 < HW - 8 ? p8 : HW - 8, ch = (chunk * CO * 2 + o) * 4;
+        u32x4 (&in)[4] = task.row;
+        if (any_odd) {
+            const int e = (ch < p.cin ? ch : p.cin - 4) * HW + st;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ei = e + i * HW;
+                const unsigned int sh = ei > 0 && (ei + fodd) & 1 ? 16u : 0u;
+                in[i] = u32x4{__builtin_amdgcn_alignbit(in[i][1], in[i][0], sh), __builtin_amdgcn_alignbit(in[i][2], in[i][1], sh),
+                              __builtin_amdgcn_alignbit(in[i][3], in[i][2], sh), __builtin_amdgcn_alignbit(task.last[i], in[i][3], sh)};
+            }
+        }
+        if (ch >= p.cin) {                                 // (the last chunk's channels past the last)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) in[i] = u32x4{0u, 0u, 0u, 0u};
+        }
+        char *dst = patch + (st - plo) * SB + o * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const unsigned int pick = j & 1 ? 0x07060302u : 0x05040100u;
+            *reinterpret_cast<uint2 *>(dst + j * SB) = uint2{__builtin_amdgcn_perm(in[1][j >> 1], in[0][j >> 1], pick),
+                                                             __builtin_amdgcn_perm(in[3][j >> 1], in[2][j >> 1], pick)};
+        }
+    };
+    Task ahead[kPatchAhead];
+    auto ask_patch = [&](int chunk) {
+#pragma unroll
+        for (int a = 0; a < kPatchAhead; ++a)
+            if (a * 64 + lane < tasks) load_task(ahead[a], chunk, a * 64 + lane);
+    };
+    auto take_patch = [&](int chunk) {
+#pragma unroll
+        for (int a = 0; a < kPatchAhead; ++a)
+            if (a * 64 + lane < tasks) store_task(ahead[a], chunk, a * 64 + lane);
+        for (int id = kPatchAhead * 64 + lane; id < tasks; id += 64) {
+            Task in;
+            load_task(in, chunk, id);
+            store_task(in, chunk, id);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (c_beg < c_end) ask_patch(c_beg);
+
+    // per sub-tile: where the lane's position lies in the patch (centre tap, the lane's octet) and which taps see the image
+    const int octet = kgroup % CO;
+    int at[NT];
+    unsigned int sees[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const int n = n0 + q * 16 + i16;
+        const int pix = pixel_of(n < p.Nv ? n : p.Nv - 1, hh, ww);
+        at[q] = (pix - plo) * SB + octet * 16;
+        const int wlo = (p.kw >> 1) - ww, whi = p.W - ww + (p.kw >> 1);            // taps of a kernel row: [wlo, whi)
+        const unsigned int cols = ((1u << (whi < p.kw ? whi : p.kw)) - 1u) & ~((1u << (wlo > 0 ? wlo : 0)) - 1u);
+        sees[q] = 0u;
+        for (int r = 0; r < p.kh; ++r) {
+            const int y = hh + r - (p.kh >> 1);
+            sees[q] |= y >= 0 && y < p.H ? cols << (r * p.kw) : 0u;
+        }
+    }
+    const int zero_at = p.zero_at + octet * 16;
+    if (lane < CO) *reinterpret_cast<u32x4 *>(patch + p.zero_at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+
+    auto multiply = [&](int st, const i16x8 (&w)[R]) {
+        const int tap = (st * 4 + kgroup) / CO;            // (past the last tap: no position sees it)
+        const int tr = (int)(__umul24((unsigned int)tap, (unsigned int)p.kw_magic) >> 8), tq = tap - tr * p.kw;
+        const int toff = ((tr - (p.kh >> 1)) * p.W + tq - (p.kw >> 1)) * SB;
+        i16x8 x[NT];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int a = (sees[q] >> tap) & 1u ? at[q] + toff : zero_at;
+            x[q] = *reinterpret_cast<const i16x8 *>(patch + a);
+        }
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+#pragma unroll
+            for (int m = 0; m < R; ++m) acc[m][q] = mfma16<BF16>(x[q], w[m], acc[m][q]);
+    };
+    for (int chunk = c_beg; chunk < c_end; ++chunk) {
+        take_patch(chunk);
+        if (chunk + 1 < c_end) ask_patch(chunk + 1);
+#pragma unroll 1
+        for (int st = 0; st < p.steps; st += D) {
+            const bool last = st + D >= p.steps;           // (the next group is the next chunk's first)
+            const int nchunk = last && chunk + 1 < c_end ? chunk + 1 : chunk, nst = last ? 0 : st + D;
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                if (st + u < p.steps) multiply(st + u, PW[u]);
+                fetch_weights(PW[u], nchunk, nst + u);
+            }
+        }
+    }
+
+    // the waves' partial tiles, added in wave order; the waves finish the (16-row run, sub-tile) pairs in turn (as in bcr_conv_tall)
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    const int wave_red = p.wave_lds / 16;
+    constexpr int PAIRS = R * NT / NWV;
+    static_assert(R * NT % NWV == 0, "pairs are dealt evenly");
+    int row[PAIRS];
+    float bias[PAIRS];
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) row[j] = p.out_row[((int64_t)t * R + (wave + j * NWV) / NT) * 16 + i16];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) red[wave * wave_red + (m * NT + q) * 64 + lane] = acc[m][q];
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) bias[j] = p.bias && row[j] >= 0 ? p.bias[row[j]] : 0.f;
+    __syncthreads();
+    unsigned int again = 0u;                               // bit per pair: one of the lane's four sums is not finite
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) {
+        const int i = wave + j * NWV;
+        f32x4 sum = red[i * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < NWV; ++w) {
+            const f32x4 v = red[w * wave_red + i * 64 + lane];
+            sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
+        }
+        float nan = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nan = __builtin_fmaf(sum[e], 0.f, nan);
+        again |= nan != nan ? 1u << i : 0u;
+        if (row[j] >= 0) conv_finish<false>(p, img, row[j], bias[j], n0 + i % NT * 16 + 4 * kgroup, sum);
+    }
+    if (__builtin_amdgcn_ballot_w64(again != 0u)) {
+#pragma unroll 1
+        for (int i = wave; i < R * NT; i += NWV) {
+            const int run = t * R + i / NT, n = n0 + i % NT * 16 + 4 * kgroup;
+            const int64_t row = p.out_row[(int64_t)run * 16 + i16];
+            if (row < 0 || !((again >> i) & 1u)) continue;
+            f32x4 sum;
+#pragma unroll 1
+            for (int e = 0; e < 4; ++e) {
+                float v = 0.f;
+                if (n + e < p.Nv) v = s2 ? conv_own_run<BF16, true>(p, Fimg, run, i16, n + e) : conv_own_run<BF16, false>(p, Fimg, run, i16, n + e);
+                sum[0] = e == 0 ? v : sum[0]; sum[1] = e == 1 ? v : sum[1]; sum[2] = e == 2 ? v : sum[2]; sum[3] = e == 3 ? v : sum[3];
+            }
+            conv_finish<false>(p, img, row, p.bias ? p.bias[row] : 0.f, n, sum);
+        }
+    }
+}
+
+// Pixels of a channel that the 64 positions of a tile and their taps can span, in whole eights
+static int64_t patch_pixels(int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) {
+    const int64_t Wo = (W + stride - 1) / stride, turns = (63 + Wo - 1) / Wo;
+    const int64_t span = (stride == 2 ? 126 + 2 * (W - Wo) * turns : 63) + 2 * ((int64_t)(kh / 2) * W + kw / 2) + 1;
+    return ((span < (int64_t)H * W - 1 ? span : (int64_t)H * W - 1) / 8 + 1) * 8;
+}
+
+// Octets of channels to a chunk: the most that leave eight waves a chunk each, fit their share of LDS and are asked for in one
+// go (what is not is waited for once per 64 tasks: 416 -> 96 channels, 3 x 3, from 20 x 30 at stride 2 18.1 us with 4 octets);
+// 0: the layer is not for this kernel
+int32_t conv_patch_octets(int64_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) {
+    if (kh * kw < 2 || kh * kw > kConvMaxTaps || (int64_t)H * W < 8 || Cin < 8 || Cin % 4 != 0) return 0;
+    const int64_t pixels = patch_pixels(H, W, kh, kw, stride);
+    for (int32_t co = 4; co >= 1; co /= 2)
+        if ((co == 1 || (Cin >= 64 * co && pixels / 8 * 2 * co <= kPatchAhead * 64)) && (pixels + 1) * patch_pixel_bytes(co) <= kPatchWaveBytes)
+            return co;
+    return 0;
+}
+
+grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W,
+                              int32_t kh, int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
+                              int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride) {
+    ConvPatchParams p;
+    ConvForm form;
+    const grim_status st = conv_gather_setup(A, F, Cin, H, W, kh, kw, bias, relu, Y, odt, ldy, batch, stride, f_img_stride,
+                                             y_img_stride, own_words, 0, 0, 0, &p, &form);
+    if (st != GRIM_OK) return st;
+    p.own_sptr = p.sptr; p.own_plan = own_words; p.own_desc = p.desc; p.own_payload = p.payload; p.own_usteps = p.usteps;
+    p.out_row = L.d_out_row;
+    p.dense = L.d_weights;
+    p.nbr = (int32_t)L.runs;
+    p.cin = Cin;
+    p.chunks = L.chunks;
+    p.steps = L.steps;
+    const int64_t pixels = patch_pixels(H, W, kh, kw, stride);
+    p.zero_at = (int32_t)(pixels * patch_pixel_bytes(L.octets));
+    // positions are walked without padding of their rows: four of them are stored at once wherever their address allows it
+    p.Wp = p.Wo;
+    p.Nv = p.Ho * p.Wo;
+    const int wide = odt == GRIM_F32 ? 16 : 8, esz_out = odt == GRIM_F32 ? 4 : 2;
+    p.yvec = reinterpret_cast<uintptr_t>(Y) % wide == 0 && ldy % 4 == 0 && (batch == 1 || (y_img_stride * esz_out) % wide == 0) ? 4 : 1;
+    p.tiles_per_img = (p.Nv + 63) / 64;
+    if ((int64_t)p.tiles_per_img * batch > 0x7fffffff / 16) return GRIM_ERR_SHAPE;
+    p.ntiles = p.tiles_per_img * batch;
+    if (((int64_t)p.ntiles + 7) / 8 * 8 * p.nbr > 0x7fffffff) return GRIM_ERR_SHAPE;
+    int64_t nwg = 0;
+    p.map = xcd_map(p.ntiles, p.nbr, &nwg);
+    if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
+    const int waves = (int64_t)p.ntiles * p.nbr <= 256 ? 8 : 4;
+    p.wave_lds = p.zero_at + patch_pixel_bytes(L.octets);
+    p.wave_lds = p.wave_lds < kConvTallRuns * 4096 ? kConvTallRuns * 4096 : p.wave_lds;       // the partial tiles go there later
+    const size_t lds = (size_t)waves * p.wave_lds;
+#define GRIM_PATCH(BF, CO, NW)                                                                                       \
+    do {                                                                                                             \
+        auto kern = bcr_conv_patch<BF, CO, NW>;                                                                      \
+        static std::atomic<bool> attr_done{false};   /* raising a kernel's LDS limit is needed once per process */  \
+        if (lds > 64 * 1024 && !attr_done) {                                                                         \
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                    160 * 1024) != hipSuccess) {                                                     \
+                (void)hipGetLastError();                                                                             \
+                return GRIM_ERR_DEVICE;                                                                              \
+            }                                                                                                        \
+            attr_done = true;                                                                                        \
+        }                                                                                                            \
+        hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NW * 64), lds, stream, p);                                \
+    } while (0)
+#define GRIM_PATCH_CO(BF, CO) if (waves == 8) GRIM_PATCH(BF, CO, 8); else GRIM_PATCH(BF, CO, 4)
+#define GRIM_PATCH_DT(BF) if (L.octets == 4) { GRIM_PATCH_CO(BF, 4); } else if (L.octets == 2) { GRIM_PATCH_CO(BF, 2); } else { GRIM_PATCH_CO(BF, 1); }
+    if (A->dtype == GRIM_BF16) { GRIM_PATCH_DT(true) } else { GRIM_PATCH_DT(false) }
+#undef GRIM_PATCH_DT
+#undef GRIM_PATCH_CO
+#undef GRIM_PATCH
+    return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
+}
+
+}  // namespace grim

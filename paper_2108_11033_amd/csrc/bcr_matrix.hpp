@@ -90,6 +90,16 @@ struct GatherLayout {
     int64_t bytes = 0;
 };
 
+// A convolution plan's dense copy of the weights for bcr_conv_patch: 64-row runs of the stored order, the k values in the order
+// its multiplies take them.  A chunk is 8 octets channels; a step is four (tap, channel octet) pairs of a chunk.
+struct ConvDense {
+    bool present = false;
+    int64_t runs = 0;
+    int32_t octets = 0, chunks = 0, steps = 0;    // octets of channels to a chunk, chunks, steps per chunk
+    unsigned char *d_weights = nullptr;           // [runs][chunks][steps][4 16-row runs][64 lanes] 16 bytes
+    int32_t *d_out_row = nullptr;                 // [runs * 64] original row of every stored row (-1 past M)
+};
+
 // Layout for the SpMV kernel (BR, BC <= 32): the compact weights themselves plus one
 // row bit mask and one column bit mask per stored block.
 struct GemvLayout {
@@ -240,6 +250,11 @@ grim_status launch_conv_gather(const grim_bcr_matrix *A, const void *F, int32_t 
 grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh,
                              int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
                              int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride);
+// the same for kernels larger than 1 x 1 on a plan's dense copy of the weights; conv_patch_octets: 0 = the layer is not for it
+int32_t conv_patch_octets(int64_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride);
+grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W,
+                              int32_t kh, int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,
+                              int32_t batch, int32_t stride, int64_t f_img_stride, int64_t y_img_stride);
 // at stride 1, does a batch split a strip's sum over as many waves as one image does?  (Its sums then have the same bits.)
 bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch);
 uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw);

@@ -1188,6 +1188,8 @@ struct grim_bcr_conv_plan {
     GatherLayout tall;
     RunSteps tall_steps;
     void *d_tall = nullptr;          // one allocation for all of it
+    ConvDense dense;
+    void *d_dense = nullptr;
 };
 
 // Runs of 64 rows pay once there are about as many (tile, run) pairs as two thirds of the compute units -- below that the
@@ -1208,6 +1210,90 @@ static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, in
     return stride == 2 || !conv_batch_sums_as_one_image(A, positions, batch);
 }
 
+// The dense copy (bcr_conv_patch) multiplies every k value of a run, its workgroups are a fourth as many as those on 16-row runs,
+// and a step costs less: by nanoseconds of a compute unit, 65 per step of a 64-row run (1500 more at stride 2, whose tiles span
+// more pixels) against 90 per step of a 16-row run, the workgroups rounded to whole rounds there.  Measured, before -> on the
+// dense copy: 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 / 16 x 32 / mixed 32 x 32 blocks 16.1 / 13.7 / 12.0 -> 11.0 /
+// 11.1 / 11.0 us; 448 from seven 103 x 24 maps at stride 2 in 4 x 16 / 16 x 32 blocks 118 / 83 -> 35 / 35; 512 on eight 14 x 14
+// 19.5 -> 16.5; 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.5 -> 16.8.  Not taken: 128 -> 256 from four 56 x 56 at
+// stride 2 in 16 x 32 blocks 10.9 -> 11.6; 256 -> 512 from one 28 x 28 at stride 2 7.3 -> 13.4; 64 -> 128 from one 112 x 112 6.4 -> 9.
+static bool conv_on_dense_copy(const grim_bcr_matrix *A, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride, int32_t batch) {
+    if (!A->gather.present || A->gather.nstrips == 0 || A->M <= 16) return false;
+    const int64_t KK = (int64_t)kh * kw, Cin = A->K / KK;
+    const int32_t octets = conv_patch_octets(Cin, H, W, kh, kw, stride);
+    if (octets == 0) return false;
+    const int64_t Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
+    const int64_t steps = (Cin + 8 * octets - 1) / (8 * octets) * ((KK * octets + 3) / 4);
+    const int64_t tiles = (Ho * Wo + 63) / 64 * batch, runs = (A->M + 63) / 64;
+    if (runs * steps > (1 << 16)) return false;                              // (256 MB)
+    const int64_t dense = 65 * steps * std::max<int64_t>(256, tiles * runs) / 256 + (stride == 2 ? 1500 : 0);
+    const int64_t strips = 500 + 90 * ((tiles * A->gather.nstrips + 255) / 256) * A->gather.nsteps / A->gather.nstrips;
+    if (dense > strips) return false;
+    // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
+    return stride == 2 || !conv_batch_sums_as_one_image(A, (int64_t)H * W, batch);
+}
+
+// The plan's dense copy of the weights (ConvDense); without memory for it the plan does without.
+static void add_dense_layout(grim_bcr_conv_plan *P) {
+    const grim_bcr_matrix *A = P->A;
+    bool met = conv_on_dense_copy(A, P->H, P->W, P->kh, P->kw, P->stride, 1 << 20);
+    for (int32_t batch = 1; batch <= 64 && !met; ++batch) met = conv_on_dense_copy(A, P->H, P->W, P->kh, P->kw, P->stride, batch);
+    if (!met) return;
+    ConvDense &D = P->dense;
+    const int32_t octets = conv_patch_octets(P->Cin, P->H, P->W, P->kh, P->kw, P->stride);
+    const int32_t KK = P->kh * P->kw;
+    D.runs = (A->M + 63) / 64;
+    D.octets = octets;
+    D.chunks = (P->Cin + 8 * octets - 1) / (8 * octets);
+    D.steps = (KK * octets + 3) / 4;
+    const size_t run_values = (size_t)D.chunks * D.steps * kConvTallRuns * 512, run_rows = 16 * kConvTallRuns;
+    std::vector<uint16_t> w;
+    std::vector<int32_t> out_row;
+    std::vector<uint32_t> place;                 // of column k inside a run, for row 0 of the first 16
+    try {
+        w.assign((size_t)D.runs * run_values, 0);
+        out_row.assign((size_t)D.runs * run_rows, -1);
+        place.resize((size_t)A->K);
+    } catch (const std::bad_alloc &) {
+        return;
+    }
+    for (int32_t c = 0, k = 0; c < P->Cin; ++c)
+        for (int32_t tap = 0; tap < KK; ++tap, ++k) {
+            const int32_t pair = tap * octets + c % (8 * octets) / 8;        // (tap, channel octet): four to a step
+            place[(size_t)k] = (uint32_t)((((size_t)(c / (8 * octets)) * D.steps + pair / 4) * kConvTallRuns * 64 + pair % 4 * 16) * 8 + c % 8);
+        }
+    const uint16_t *src = reinterpret_cast<const uint16_t *>(A->weights.data());
+    int64_t t = 0;
+    for (int64_t p = 0; p < A->nbr; ++p) {
+        for (int32_t r = 0; r < A->BR; ++r) out_row[(size_t)(p * A->BR + r)] = (int32_t)((int64_t)A->strip_order[p] * A->BR + r);
+        for (int64_t c = 0; c < A->nbc; ++c, ++t) {
+            const uint16_t *v = src + A->blk_ptr[t];
+            for (int32_t i = A->row_ptr[t]; i < A->row_ptr[t + 1]; ++i) {
+                const size_t row = (size_t)(p * A->BR + A->row_idx[i]);
+                uint16_t *dst = w.data() + row / run_rows * run_values + (row % run_rows / 16 * 64 + row % 16) * 8;
+                for (int32_t j = A->col_ptr[t]; j < A->col_ptr[t + 1]; ++j) dst[place[(size_t)(c * A->BC + A->col_idx[j])]] = *v++;
+            }
+        }
+    }
+    Slab s;
+    const size_t o_w = s.add(w.size() * 2), o_q = s.add(out_row.size() * 4);
+    char *base = nullptr;
+    if (hipMalloc(reinterpret_cast<void **>(&base), s.total + 256) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (hipMemcpy(base + o_w, w.data(), w.size() * 2, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(base + o_q, out_row.data(), out_row.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(base);
+        return;
+    }
+    P->d_dense = base;
+    D.d_weights = reinterpret_cast<unsigned char *>(base + o_w);
+    D.d_out_row = reinterpret_cast<int32_t *>(base + o_q);
+    D.present = true;
+}
+
 // The layout of 64-row runs, if some batch would run on it.  A plan that cannot have it (no memory) does without.
 static void add_tall_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
@@ -1217,6 +1303,10 @@ static void add_tall_layout(grim_bcr_conv_plan *P) {
         steps = count_run_steps<kConvTallRuns>(A);
         // (the splits of a sum over waves follow one another with the batch: the largest stands for all that are not one image's)
         if (!conv_on_tall_runs(A, steps, P->H, P->W, P->stride, 1 << 20)) return;
+        bool met = !P->dense.present;            // by a batch that the dense copy is not for
+        for (int32_t batch = 1; batch <= 64 && !met; ++batch)
+            met = conv_on_tall_runs(A, steps, P->H, P->W, P->stride, batch) && !conv_on_dense_copy(A, P->H, P->W, P->kh, P->kw, P->stride, batch);
+        if (!met) return;
         build_gather_layout<kConvTallRuns>(A, L);
         for (uint32_t &r : L.rows) r = conv_plan_word(r, P->H, P->W, P->kh, P->kw);
     } catch (const std::bad_alloc &) {
@@ -1276,6 +1366,7 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
         return GRIM_ERR_DEVICE;
     }
     P->d_words = static_cast<uint32_t *>(ptr);
+    add_dense_layout(P.get());
     add_tall_layout(P.get());
     *out = P.release();
     return GRIM_OK;
@@ -1285,6 +1376,7 @@ void grim_bcr_conv_plan_free(grim_bcr_conv_plan *P) {
     if (!P) return;
     if (P->d_words) (void)hipFree(P->d_words);
     if (P->d_tall) (void)hipFree(P->d_tall);
+    if (P->d_dense) (void)hipFree(P->d_dense);
     delete P;
 }
 
@@ -1304,6 +1396,12 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev,
         const grim_status st = launch_conv_wide(P->A, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, batch, f_image_stride, bias_dev,
                                                 relu ? 1 : 0, out_dev, (int32_t)out_dt, ldo, out_image_stride,
                                                 static_cast<hipStream_t>(hip_stream));
+        if (st != GRIM_ERR_UNSUPPORTED) return st;
+    }
+    if (P->dense.present && conv_on_dense_copy(P->A, P->H, P->W, P->kh, P->kw, P->stride, batch)) {
+        const grim_status st = launch_conv_patch(P->A, P->dense, P->d_words, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
+                                                 (int32_t)out_dt, ldo, static_cast<hipStream_t>(hip_stream), batch, P->stride, f_image_stride,
+                                                 out_image_stride);
         if (st != GRIM_ERR_UNSUPPORTED) return st;
     }
     if (P->tall.present && conv_on_tall_runs(P->A, P->tall_steps, P->H, P->W, P->stride, batch)) {
@@ -1328,6 +1426,7 @@ const char *grim_bcr_conv2d_kernel_name(const grim_bcr_matrix *A, int32_t Cin, i
         return "bcr_conv_wide";
     if (!A->gather.present) return "none";
     try {
+        if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_dense_copy(A, H, W, kh, kw, stride, batch)) return "bcr_conv_tall";
         if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_tall_runs(A, count_run_steps<kConvTallRuns>(A), H, W, stride, batch)) return "bcr_conv_tall";
     } catch (const std::bad_alloc &) {           // (a plan without memory for that layout does without it, too)
     }

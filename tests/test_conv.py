@@ -684,6 +684,39 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,kw,stride,B,pad", [
+    (256, 4, 16, 256, 28, 28, 3, 3, 1, 4, 0),    # eight waves, a chunk of 32 channels each
+    (256, 4, 16, 128, 28, 28, 3, 3, 1, 8, 1),    # four waves; chunks of 16; every second image at an odd element
+    (144, 4, 4, 68, 31, 33, 3, 3, 1, 14, 3),     # a last run of 16 rows; channels that fill no chunk; odd maps, odd strides
+    (128, 4, 16, 272, 57, 31, 3, 3, 2, 6, 0),    # stride 2 of odd maps: the last column and row are outputs
+    (512, 4, 4, 36, 9, 9, 5, 5, 2, 96, 1),       # one partly filled tile of 25 positions per image
+    (512, 4, 4, 64, 3, 3, 3, 3, 1, 96, 0),       # nine pixels: two loads per channel that overlap
+    (512, 4, 4, 64, 2, 131, 3, 3, 2, 48, 1),     # rows of 66 outputs: a tile ends in the row it starts in
+    (192, 4, 16, 64, 17, 150, 1, 5, 1, 8, 0),    # flat and tall kernels
+    (192, 4, 16, 64, 40, 30, 7, 3, 1, 8, 1),
+    (128, 4, 16, 64, 6, 440, 3, 3, 1, 8, 0),     # a tile's pixels and their neighbours in the rows next to it: 946
+])
+def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pad):
+    """Layers of many steps per 64-row run and many tiles, as the plan's dense copy of the weights takes them."""
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload, TOL
+    K = cin * kh * kw
+    mask = gen.random_mask(M, K, BR, BC, (BR // 2, BR), (BC // 4, BC // 2), seed=900 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=901)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=902, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    bias = (0.05 * np.random.default_rng(903).standard_normal(M)).astype(np.float32)
+    Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
+    Yref = conv_ref.conv2d(Wm, F64, kh, kw, stride) + bias[None, :, None, None]
+    S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, stride) + np.abs(bias)[None, :, None, None]
+    A = pack_workload(g, Wt, dtype, mask)
+    Y = _run_plan(g, A, F, dtype, M, kh, kw, stride, bias=bias, pad=pad)
+    assert np.isfinite(Y).all()
+    assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
+    assert np.abs(Y - Yref).max() <= TOL[dtype] * np.abs(Yref).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B", [
     (128, 4, 16, 64, 28, 27, 3, 1, 9),       # 64-row runs
     (208, 16, 16, 64, 29, 31, 3, 2, 12),     # 64-row runs at stride 2, a last run of 16 rows
