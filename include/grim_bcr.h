@@ -203,7 +203,8 @@ grim_status grim_bcr_spmv(const grim_bcr_matrix *A, const void *x_dev, int32_t b
  * grid row per matrix) into one device table.
  * The matrices must outlive the group.
  * grim_bcr_spmv_batched computes y_i = W_i * x_i for i in [0, count): x_i starts at
- * x_dev + i * x_stride elements (K x batch, ldx), y_i at y_dev + i * y_stride floats.
+ * x_dev + i * x_stride elements (K x batch, ldx), y_i at y_dev + i * y_stride floats.  As for grim_bcr_spmv, groups the
+ * wave-per-strip kernels are not compiled for (and small launches of several columns) run on the matrix cores.
  */
 grim_status grim_bcr_group_create(const grim_bcr_matrix *const *mats, int32_t count,
                                   grim_bcr_group **out);

@@ -201,6 +201,9 @@ struct grim_bcr_group {
     int32_t uniform_kr = -1, uniform_kc = -1, vec = 1, krmax = 0, kcmax = 0;
     int device = -1;
     GemvDesc *d_table = nullptr;
+    // the matrices' row-gathering layouts, where all have one (16-bit types): a table of gather_entry_bytes() per matrix
+    void *d_gather = nullptr;
+    int64_t gather_runs = 0, gather_steps = 0;   // 16-row runs of a matrix; steps of all matrices together
 };
 
 namespace grim {
@@ -227,6 +230,11 @@ double wide_plan(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx
 grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y,
                                int64_t ldy, hipStream_t stream, const grim_bcr_matrix *A2 = nullptr,
                                const void *X2 = nullptr, float *Y2 = nullptr);
+// the same for the matrices of a group, N <= 16 columns each, in one launch
+size_t gather_entry_bytes();
+void gather_fill_entry(const grim_bcr_matrix *A, void *entry);
+grim_status launch_spmm_gather_many(const grim_bcr_group *G, const void *X, int64_t x_stride, int64_t N, int64_t ldx, float *Y, int64_t y_stride,
+                                    int64_t ldy, hipStream_t stream);
 // fp32 row-gathering kernel: any N, any ldx
 bool gather32_applies(const grim_bcr_matrix *A, const void *X);
 bool gather32_quicker(const grim_bcr_matrix *A, int64_t N);    // than the vector-ALU kernel, for N > 8

@@ -1702,6 +1702,32 @@ grim_status grim_bcr_gru_step(const grim_bcr_matrix *Ai, const grim_bcr_matrix *
                          ldhout, H, batch, hip_stream);
 }
 
+// The table of the matrices' row-gathering layouts, if all have one (without memory for it the group does without).
+static void add_group_gather(grim_bcr_group *G, const grim_bcr_matrix *const *mats) {
+    int64_t steps = 0;
+    for (int32_t i = 0; i < G->count; ++i) {
+        if (!mats[i]->gather.present || mats[i]->gather.nstrips != mats[0]->gather.nstrips) return;
+        steps += mats[i]->gather.nsteps;
+    }
+    const size_t each = gather_entry_bytes();
+    std::vector<unsigned char> table;
+    try {
+        table.resize(each * (size_t)G->count);
+    } catch (const std::bad_alloc &) {
+        return;
+    }
+    for (int32_t i = 0; i < G->count; ++i) gather_fill_entry(mats[i], table.data() + each * (size_t)i);
+    if (hipMalloc(&G->d_gather, table.size()) != hipSuccess) { (void)hipGetLastError(); G->d_gather = nullptr; return; }
+    if (hipMemcpy(G->d_gather, table.data(), table.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(G->d_gather);
+        G->d_gather = nullptr;
+        return;
+    }
+    G->gather_runs = mats[0]->gather.nstrips;
+    G->gather_steps = steps;
+}
+
 grim_status grim_bcr_group_create(const grim_bcr_matrix *const *mats, int32_t count, grim_bcr_group **out) {
     if (out) *out = nullptr;
     if (!mats || !out) return GRIM_ERR_NULL;
@@ -1740,8 +1766,26 @@ grim_status grim_bcr_group_create(const grim_bcr_matrix *const *mats, int32_t co
     if (hipMemcpy(G->d_table, table.data(), sizeof(GemvDesc) * count, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipGetLastError(); (void)hipFree(G->d_table); delete G; return GRIM_ERR_DEVICE;
     }
+    add_group_gather(G, mats);
     *out = G;
     return GRIM_OK;
+}
+
+// Groups the wave-per-strip SpMV kernels are not compiled for, and small launches of those for several columns, on the matrix
+// cores (16-bit types, one padded 16-column tile per run of 16 rows).  Before -> there: 64 of 2048 x 2048 of mixed rates at 1 / 8
+// columns 53.7 / 168 -> 34.4 / 26.8 us; 39 of 960 x 1632 keeping 10 x 10 at 8 25.4 -> 9.0; 12 of 2048 x 512 in 8 x 32 blocks of
+// mixed rates at 1 / 8 15.7 / 34.4 -> 6.3 / 5.3; 20 of 2048 x 4096 keeping 8 x 12 at 4 27.7 -> 20.4.
+static bool group_on_matrix_cores(const grim_bcr_group *G, int32_t batch) {
+    if (!G->d_gather || G->BR < 8) return false;
+    if (batch == 1) return !spmv_exact_applies(G->dtype, G->uniform_kr, G->uniform_kc, G->K);
+    // Uniform blocks, up to 2048 (matrix, run) pairs: 16 of 2048 x 1024 keeping 8 x 8 at 2 / 4 / 8 columns 5.9 / 7.4 / 9.2 -> 5.2 /
+    // 4.9 / 5.0 us, 32 of 1024 x 512 in 8 x 32 blocks 6.0 / 7.6 / 11.3 -> 5.1 / 5.1 / 4.9.  With 4096 pairs 64 of 1024 x 1024 at
+    // 2 6.9 us, 9.2 there; 32 of 2048 x 2048 in 16 x 32 blocks at 2 / 4 / 8 9.4 / 13.4 / 17.1, 16.1 / 16.2 / 16.8 there.
+    if (spmv_many_strips_applies(G->count, G->nbr, G->dtype, G->uniform_kr, G->uniform_kc, G->K, G->BC, batch))
+        return (int64_t)G->count * G->gather_runs <= 2048;
+    // (columns as sets of workgroups: the bits of a call for one matrix, which takes that form too)
+    if (spmv_column_sets_ok(G->count, G->nbr, batch) && spmv_exact_applies(G->dtype, G->uniform_kr, G->uniform_kc, G->K)) return false;
+    return true;
 }
 
 grim_status grim_bcr_spmv_batched(const grim_bcr_group *G, const void *x_dev, int64_t x_stride, int32_t batch, int64_t ldx,
@@ -1751,6 +1795,10 @@ grim_status grim_bcr_spmv_batched(const grim_bcr_group *G, const void *x_dev, in
     if (G->K * batch * dtype_size(G->dtype) > kGemvMaxXBytes) return GRIM_ERR_UNSUPPORTED;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev != G->device) return GRIM_ERR_DEVICE;
+    if (group_on_matrix_cores(G, batch)) {
+        const grim_status st = launch_spmm_gather_many(G, x_dev, x_stride, batch, ldx, y_dev, y_stride, ldy, static_cast<hipStream_t>(hip_stream));
+        if (st != GRIM_ERR_UNSUPPORTED) return st;
+    }
     GemvDesc none{nullptr, nullptr, nullptr, nullptr};
     return launch_spmv(G->d_table, none, nullptr, G->count, G->M, G->K, G->BR, G->BC, G->dtype, G->uniform_kr, G->uniform_kc, G->vec, G->krmax, G->kcmax,
                        x_dev, x_stride, batch, ldx, y_dev, y_stride, ldy, static_cast<hipStream_t>(hip_stream));
@@ -1759,6 +1807,7 @@ grim_status grim_bcr_spmv_batched(const grim_bcr_group *G, const void *x_dev, in
 void grim_bcr_group_free(grim_bcr_group *G) {
     if (!G) return;
     if (G->d_table) (void)hipFree(G->d_table);
+    if (G->d_gather) (void)hipFree(G->d_gather);
     delete G;
 }
 

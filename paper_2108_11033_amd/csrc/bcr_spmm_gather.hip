@@ -173,4 +173,59 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
 }
 
 
+// One 16-column tile for each of the matrices of a group (grid.y), whose layouts come out of a table.  Bound by latency (row
+// numbers, then rows of x and weights, then the sums) and hence by waves in flight: two steps per wave and 54 registers, eight waves
+// to a SIMD (four steps, 74 registers: 64 of 2048 x 2048 at 8 columns 29.3 -> 33.2 us, 30 of 1856 x 992 at one 11.6 -> 14.1).
+template <bool BF16, bool SOLO>
+__global__ void __launch_bounds__(256, 4) bcr_spmm_gather_many(GatherParams p, const GatherSecond *table, int64_t x_stride, int64_t y_stride) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    using Entry = const __attribute__((address_space(4))) GatherSecond *;       // (read once per wave, through the scalar cache)
+    const Entry m = (Entry)table + blockIdx.y;
+    p.sptr = m->sptr; p.out_row = m->out_row; p.rows = m->rows; p.desc = m->desc; p.payload = m->payload;
+    p.usteps = m->usteps;
+    p.exact.row_ptr = m->exact.row_ptr; p.exact.col_ptr = m->exact.col_ptr;
+    p.exact.row_idx = m->exact.row_idx; p.exact.col_idx = m->exact.col_idx;
+    p.exact.blk_ptr = m->exact.blk_ptr; p.exact.weights = m->exact.weights;
+    p.X += (int64_t)blockIdx.y * x_stride;
+    p.Y += (int64_t)blockIdx.y * y_stride;
+    gather_body<BF16, false, true, SOLO, false, 1, kGatherLongWaves, 2>(p, lds, blockIdx.x, 0);
+}
+
+size_t gather_entry_bytes() { return sizeof(GatherSecond); }
+void gather_fill_entry(const grim_bcr_matrix *A, void *entry) {
+    *static_cast<GatherSecond *>(entry) = GatherSecond{A->gather.d_sptr, A->gather.d_out_row, A->gather.d_rows, A->gather.d_desc, A->gather.d_payload,
+                                                       nullptr, nullptr, A->gather.usteps, (int32_t)A->K, exact_arrays(A)};
+}
+
+grim_status launch_spmm_gather_many(const grim_bcr_group *G, const void *X, int64_t x_stride, int64_t N, int64_t ldx, float *Y, int64_t y_stride,
+                                    int64_t ldy, hipStream_t stream) {
+    if (!G->d_gather || N > 16 || reinterpret_cast<uintptr_t>(X) % 2 != 0 || (G->K - 1) * ldx + N < 8) return GRIM_ERR_UNSUPPORTED;
+    GatherParams p = {};
+    p.X = static_cast<const unsigned short *>(X);
+    p.Y = Y;
+    p.N = N; p.ldx = ldx; p.ldy = ldy;
+    p.nbr = (int32_t)G->gather_runs;
+    p.ntiles = 1;
+    p.K = (int32_t)G->K;
+    p.exact.BR = G->BR; p.exact.BC = G->BC; p.exact.nbc = (int32_t)G->nbc;
+    // Enough (matrix, run) pairs to fill the GPU with a wave each: no split of a run over waves, no partial tiles.  Four waves to a
+    // run / a wave: 64 of 2048 x 2048 of mixed rates at 8 columns 29.3 / 26.8 us, 43 of 3872 x 1248 at one 34.9 / 30.3, 32 of 1024
+    // x 512 in 8 x 32 blocks (2048 pairs of 7 steps) at 4 5.4 / 5.1; 39 of 960 x 1632 (2340 of 16 steps) 9.0 / 10.1, 12 of 2048 x
+    // 512 (1536) 6.3 / 6.4, 8 of 736 x 1440 (368) 5.2 / 7.5.
+    const int64_t pairs = (int64_t)G->count * G->gather_runs;
+    const bool solo = pairs >= 3072 || (pairs >= 2048 && G->gather_steps <= 12 * pairs);
+    int64_t nwg = 0;
+    p.map = xcd_map(1, solo ? (G->gather_runs + 3) / 4 : G->gather_runs, &nwg);
+    if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
+    const dim3 grid((unsigned)nwg, (unsigned)G->count);
+    const size_t lds = 4 * gather_wave_lds(1);
+    const GatherSecond *table = static_cast<const GatherSecond *>(G->d_gather);
+#define GRIM_MANY(BF, SO) hipLaunchKernelGGL((bcr_spmm_gather_many<BF, SO>), grid, dim3(256), lds, stream, p, table, x_stride, y_stride)
+    if (G->dtype == GRIM_BF16) { if (solo) GRIM_MANY(true, true); else GRIM_MANY(true, false); }
+    else { if (solo) GRIM_MANY(false, true); else GRIM_MANY(false, false); }
+#undef GRIM_MANY
+    return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
+}
+
+
 }  // namespace grim

@@ -758,3 +758,67 @@ def test_device_call_errors(g):
     assert e.value.name == "GRIM_ERR_UNSUPPORTED"
     torch.cuda.synchronize()
     assert (Yd == 7.0).all()
+
+
+@pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
+@pytest.mark.parametrize("M,K,BR,BC,kr,kc,count,batch,pad", [
+    (352, 288, 32, 32, (4, 16), (4, 16), 5, 1, 0),       # mixed rates, 22 runs, four waves to a run
+    (352, 288, 32, 32, (0, 16), (1, 16), 5, 8, 0),       # blocks that keep no row
+    (40, 96, 8, 16, (1, 8), (1, 16), 3, 3, 1),           # a last run of 8 rows; columns at odd elements
+    (96, 96, 32, 32, 10, 10, 2, 7, 2),                   # uniform counts outside the compiled pairs
+    (16, 16, 16, 16, (16, 16), (3, 16), 1, 1, 0),        # one run of one step
+    (176, 128, 16, 32, (2, 8), (4, 16), 300, 2, 0),      # 3300 runs of few steps: a wave each
+    (144, 64, 8, 32, 4, 8, 228, 5, 1),                   # 2052 of one step: a wave each
+    (160, 2080, 32, 32, (8, 16), (8, 32), 210, 6, 0),    # 2100 of many steps: four waves to a run
+    (512, 256, 32, 32, 8, 8, 64, 3, 0),                  # uniform, 2048 runs: the most that go there
+])
+def test_spmv_groups_on_the_matrix_cores(g, dtype, M, K, BR, BC, kr, kc, count, batch, pad):
+    torch, dev = torch_dev()
+    from paper_2108_11033_amd import binding
+    n, ld = min(count, 3), batch + pad
+    mats, xs, refs = [], [], []
+    for i in range(n):
+        mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=950 + i)
+        W = gen.normal_weights(M, K, dtype, seed=960 + i)
+        x = gen.normal_activations(K, batch, dtype, seed=970 + i)
+        mats.append(pack_workload(g, W, dtype, mask))
+        xs.append(x)
+        refs.append(oracle_product(W, x, dtype, mask))
+    G = binding.group([mats[i % n] for i in range(count)])
+    xp = np.zeros((count, K, ld), dtype=xs[0].dtype)
+    for i in range(count):
+        xp[i, :, :batch] = xs[i % n]
+    yd = torch.full((count, M, ld), float("nan"), dtype=torch.float32, device=dev)
+    g.spmv_batched(G, to_device(xp, dtype), K * ld, batch, ld, yd, M * ld, ld, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    y = yd.cpu().numpy()
+    assert np.isnan(y[:, :, batch:]).all()
+    for i in range(n):
+        assert_close(y[i][:, :batch], refs[i][0], refs[i][1], dtype, f"matrix {i}")
+    assert all(y[i].tobytes() == y[i % n].tobytes() for i in range(count))
+
+
+@pytest.mark.parametrize("count", [2, 400])
+def test_spmv_groups_multiply_kept_weights_only(g, count):
+    """An infinity or NaN of one matrix's x reaches the rows that keep its column and no other, and no other matrix."""
+    torch, dev = torch_dev()
+    from paper_2108_11033_amd import binding
+    dtype, M, K, BR, BC, batch = gen.F16, 128, 128, 32, 32, 2
+    mask = gen.random_mask(M, K, BR, BC, (4, 16), (4, 16), seed=980)
+    W = gen.normal_weights(M, K, dtype, seed=981)
+    x = gen.normal_activations(K, batch, dtype, seed=982)
+    odd = x.copy()
+    odd[5, 0], odd[77, 1] = np.inf, np.nan
+    xp = np.stack([odd if i == 1 else x for i in range(count)])
+    A = pack_workload(g, W, dtype, mask)
+    G = binding.group([A] * count)
+    yd = torch.full((count, M, batch), 7.0, dtype=torch.float32, device=dev)
+    g.spmv_batched(G, to_device(xp, dtype), K * batch, batch, batch, yd, M * batch, batch, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    y = yd.cpu().numpy()
+    ref, scale = oracle_product(W, x, dtype, mask)
+    keep = np.asarray(A.unpack()) != 0
+    for i in range(count):
+        hit = np.stack([keep[:, 5], keep[:, 77]], axis=1) if i == 1 else np.zeros((M, batch), dtype=bool)
+        assert not np.isfinite(y[i][hit]).any()
+        assert_close(np.where(hit, 0.0, y[i]), np.where(hit, 0.0, ref), scale, dtype, f"matrix {i}")
