@@ -1,5 +1,6 @@
 // Planned convolution of kernels larger than 1 x 1 with 64 rows of the matrix to a workgroup, the im2col matrix never formed
 // (Section 3.1: CONV = filter matrix x im2col matrix).
+#include "conv_patch.hpp"
 #include "conv_tall.hpp"
 
 namespace grim {
@@ -67,20 +68,10 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     }
 
     // the pixels (of a channel) that a tap of the tile's positions can meet: [plo, phi]
-    const int HW = p.N, centre = (p.kh >> 1) * p.W + (p.kw >> 1), s2 = p.stride == 2;
-    auto pixel_of = [&](int n, int &h, int &w) {
-        h = n / p.Wo;
-        w = n - h * p.Wo;
-        h <<= s2; w <<= s2;
-        return h * p.W + w;
-    };
-    int hh, ww;
-    int plo = pixel_of(n0, hh, ww) - centre;
-    plo = plo < 0 ? 0 : plo > HW - 8 ? HW - 8 : plo;
-    plo -= plo > 0 ? ((int)(reinterpret_cast<uintptr_t>(Fimg) >> 1) + plo) & 1 : 0;
-    plo = __builtin_amdgcn_readfirstlane(plo);
-    int phi = pixel_of(n0 + TN < p.Nv ? n0 + TN - 1 : p.Nv - 1, hh, ww) + centre;
-    phi = __builtin_amdgcn_readfirstlane(phi < HW - 1 ? phi : HW - 1);
+    const int HW = p.N, centre = (p.kh >> 1) * p.W + (p.kw >> 1), fodd = (int)(reinterpret_cast<uintptr_t>(Fimg) >> 1) & 1;
+    const bool s2 = p.stride == 2;
+    const int plo = __builtin_amdgcn_readfirstlane(patch_first(n0, p.W, p.Wo, s2, centre, HW, fodd));
+    const int phi = __builtin_amdgcn_readfirstlane(patch_last(n0, p.Nv, p.W, p.Wo, s2, centre, HW));
     const int tasks = ((phi - plo) / 8 + 1) * CO * 2;      // (eight pixels of four channels) to turn around per chunk
 
     f32x4 acc[R][NT];
@@ -95,7 +86,6 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     // 16 bytes at an odd element cost the vector L1 about three times what they cost at an even one: such a row is loaded one
     // element early, its last element by itself, and shifted into place before it is written (maps of an odd number of pixels:
     // 288 channels, 3 x 3, seven 95 x 27 maps at stride 2 32.3 -> 27.4 us)
-    const int fodd = (int)(reinterpret_cast<uintptr_t>(Fimg) >> 1) & 1;
     const bool any_odd = ((HW | (plo + fodd) | fodd) & 1) != 0;       // (pieces start at plo + 8 q or at HW - 8, HW apart)
     struct Task { u32x4 row[4]; unsigned int last[4]; };
     auto load_task = [&](Task &in, int chunk, int id) {
@@ -159,7 +149,8 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
         const int n = n0 + q * 16 + i16;
-        const int pix = pixel_of(n < p.Nv ? n : p.Nv - 1, hh, ww);
+        int hh, ww;
+        const int pix = patch_pixel_of(n < p.Nv ? n : p.Nv - 1, p.W, p.Wo, s2, &hh, &ww);
         at[q] = (pix - plo) * SB + octet * 16;
         const int wlo = (p.kw >> 1) - ww, whi = p.W - ww + (p.kw >> 1);            // taps of a kernel row: [wlo, whi)
         const unsigned int cols = ((1u << (whi < p.kw ? whi : p.kw)) - 1u) & ~((1u << (wlo > 0 ? wlo : 0)) - 1u);
@@ -250,13 +241,6 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
             conv_finish<false>(p, img, row, p.bias ? p.bias[row] : 0.f, n, sum);
         }
     }
-}
-
-// Pixels of a channel that the 64 positions of a tile and their taps can span, in whole eights
-static int64_t patch_pixels(int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) {
-    const int64_t Wo = (W + stride - 1) / stride, turns = (63 + Wo - 1) / Wo;
-    const int64_t span = (stride == 2 ? 126 + 2 * (W - Wo) * turns : 63) + 2 * ((int64_t)(kh / 2) * W + kw / 2) + 1;
-    return ((span < (int64_t)H * W - 1 ? span : (int64_t)H * W - 1) / 8 + 1) * 8;
 }
 
 // Octets of channels to a chunk: the most that leave eight waves a chunk each, fit their share of LDS and are asked for in one

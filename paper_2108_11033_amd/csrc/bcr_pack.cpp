@@ -1211,12 +1211,14 @@ static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, in
 }
 
 // The dense copy (bcr_conv_patch) multiplies every k value of a run, its workgroups are a fourth as many as those on 16-row runs,
-// and a step costs less: by nanoseconds of a compute unit, 65 per step of a 64-row run (1500 more at stride 2, whose tiles span
-// more pixels) against 90 per step of a 16-row run, the workgroups rounded to whole rounds there.  Measured, before -> on the
-// dense copy: 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 / 16 x 32 / mixed 32 x 32 blocks 16.1 / 13.7 / 12.0 -> 11.0 /
-// 11.1 / 11.0 us; 448 from seven 103 x 24 maps at stride 2 in 4 x 16 / 16 x 32 blocks 118 / 83 -> 35 / 35; 512 on eight 14 x 14
-// 19.5 -> 16.5; 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.5 -> 16.8.  Not taken: 128 -> 256 from four 56 x 56 at
-// stride 2 in 16 x 32 blocks 10.9 -> 11.6; 256 -> 512 from one 28 x 28 at stride 2 7.3 -> 13.4; 64 -> 128 from one 112 x 112 6.4 -> 9.
+// and a step costs less.  Nanoseconds of a compute unit: 65 per step of a 64-row run and 30 steps' worth per workgroup (1000 more at
+// stride 2, whose tiles span more pixels) against 100 per step of a 16-row run and two steps' worth, in whole rounds up to four of
+// them.  Fitted to 49 layers, of which two that would gain 4 and 14 % stay and none that loses is taken.  Before -> on the dense
+// copy: 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 / 16 x 32 / mixed 32 x 32 blocks 16.1 / 13.7 / 12.0 -> 10.9 / 11.0 / 11.0
+// us; 448 from seven 103 x 24 maps at stride 2 in 4 x 16 / 16 x 32 blocks 118 / 83 -> 35 / 35; 512 on eight 14 x 14 19.5 -> 16.4;
+// 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.5 -> 16.8; 32 -> 128 on 24 maps of 28 x 28 in 4 x 16 blocks 17.3 -> 12.8.
+// Not taken: that layer in 16 x 32 blocks 10.3 -> 12.6; 128 -> 256 from four 56 x 56 at stride 2 in 16 x 32 blocks 10.8 -> 11.6;
+// 256 -> 512 from one 28 x 28 at stride 2 7.3 -> 13.4; 64 -> 128 from one 112 x 112 6.4 -> 9.0.
 static bool conv_on_dense_copy(const grim_bcr_matrix *A, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride, int32_t batch) {
     if (!A->gather.present || A->gather.nstrips == 0 || A->M <= 16) return false;
     const int64_t KK = (int64_t)kh * kw, Cin = A->K / KK;
@@ -1226,8 +1228,9 @@ static bool conv_on_dense_copy(const grim_bcr_matrix *A, int32_t H, int32_t W, i
     const int64_t steps = (Cin + 8 * octets - 1) / (8 * octets) * ((KK * octets + 3) / 4);
     const int64_t tiles = (Ho * Wo + 63) / 64 * batch, runs = (A->M + 63) / 64;
     if (runs * steps > (1 << 16)) return false;                              // (256 MB)
-    const int64_t dense = 65 * steps * std::max<int64_t>(256, tiles * runs) / 256 + (stride == 2 ? 1500 : 0);
-    const int64_t strips = 500 + 90 * ((tiles * A->gather.nstrips + 255) / 256) * A->gather.nsteps / A->gather.nstrips;
+    const int64_t pairs = tiles * A->gather.nstrips, rounds = pairs <= 1024 ? (pairs + 255) / 256 * 256 : pairs;
+    const int64_t dense = 65 * (steps + 30) * std::max<int64_t>(256, tiles * runs) / 256 + (stride == 2 ? 1000 : 0);
+    const int64_t strips = 1500 + 100 * rounds * (A->gather.nsteps + 2 * A->gather.nstrips) / (256 * A->gather.nstrips);
     if (dense > strips) return false;
     // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
     return stride == 2 || !conv_batch_sums_as_one_image(A, (int64_t)H * W, batch);

@@ -1,0 +1,39 @@
+// Which pixels of a channel a tile of bcr_conv_patch holds: the arithmetic of the kernel and its launcher, shared with the host
+// check that walks every tap of every position.
+#pragma once
+#include <cstdint>
+
+#include "host_device.hpp"
+
+namespace grim {
+
+// Pixel (of a channel) under the centre tap of output position n, and its row and column
+GRIM_HOST_DEVICE int patch_pixel_of(int n, int W, int Wo, bool s2, int *h, int *w) {
+    const int ho = n / Wo;
+    *h = ho << (s2 ? 1 : 0);
+    *w = (n - ho * Wo) << (s2 ? 1 : 0);
+    return *h * W + *w;
+}
+
+// The first and last pixel that a tap of positions [n0, n0 + 64) can meet; `odd`: the map starts at an odd element (the
+// first pixel is moved to an even one where there is one, and there are eight from it on)
+GRIM_HOST_DEVICE int patch_first(int n0, int W, int Wo, bool s2, int centre, int HW, int odd) {
+    int h, w;
+    int lo = patch_pixel_of(n0, W, Wo, s2, &h, &w) - centre;
+    lo = lo < 0 ? 0 : lo > HW - 8 ? HW - 8 : lo;
+    return lo - (lo > 0 ? (odd + lo) & 1 : 0);
+}
+GRIM_HOST_DEVICE int patch_last(int n0, int Nv, int W, int Wo, bool s2, int centre, int HW) {
+    int h, w;
+    const int hi = patch_pixel_of(n0 + 64 < Nv ? n0 + 63 : Nv - 1, W, Wo, s2, &h, &w) + centre;
+    return hi < HW - 1 ? hi : HW - 1;
+}
+
+// The most pixels any tile spans, in whole eights
+inline int64_t patch_pixels(int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) {
+    const int64_t Wo = (W + stride - 1) / stride, turns = (63 + Wo - 1) / Wo;
+    const int64_t span = (stride == 2 ? 126 + 2 * (W - Wo) * turns : 63) + 2 * ((int64_t)(kh / 2) * W + kw / 2) + 1;
+    return ((span < (int64_t)H * W - 1 ? span : (int64_t)H * W - 1) / 8 + 1) * 8;
+}
+
+}  // namespace grim

@@ -24,6 +24,14 @@ grim_status launch_conv_gather(const grim_bcr_matrix *, const void *, int32_t, i
 grim_status launch_conv_tall(const grim_bcr_matrix *, const GatherLayout &, const uint32_t *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, int32_t, void *, int32_t, int64_t, hipStream_t, int32_t, int32_t, int64_t, int64_t) { return GRIM_ERR_DEVICE; }
 bool conv_batch_sums_as_one_image(const grim_bcr_matrix *, int64_t, int32_t) { return true; }
 uint32_t conv_plan_word(uint32_t, int32_t, int32_t, int32_t, int32_t) { return 0; }
+// octets a plan's dense copy is made with (0: none), as a test asks
+static int g_patch_octets = 0;
+int32_t conv_patch_octets(int64_t, int32_t, int32_t, int32_t, int32_t, int32_t) { return g_patch_octets; }
+extern "C" void grim_stub_patch_octets(int octets) { g_patch_octets = octets; }
+grim_status launch_conv_patch(const grim_bcr_matrix *, const ConvDense &, const uint32_t *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, int32_t, void *, int32_t, int64_t, hipStream_t, int32_t, int32_t, int64_t, int64_t) { return GRIM_ERR_UNSUPPORTED; }
+size_t gather_entry_bytes() { return 8; }
+void gather_fill_entry(const grim_bcr_matrix *A, void *entry) { __builtin_memcpy(entry, &A, 8); }
+grim_status launch_spmm_gather_many(const grim_bcr_group *, const void *, int64_t, int64_t, int64_t, float *, int64_t, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
 bool conv_wide_applies(const grim_bcr_matrix *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t, const void *, int32_t, int64_t, int64_t) { return false; }
 grim_status launch_conv_wide(const grim_bcr_matrix *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, int32_t, int64_t, const float *, int32_t, void *, int32_t, int64_t, int64_t, hipStream_t) { return GRIM_ERR_UNSUPPORTED; }
 double gather_cost(const grim_bcr_matrix *, int64_t) { return 0.0; }

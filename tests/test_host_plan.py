@@ -54,3 +54,26 @@ def test_a_plan_holds_no_layout_it_cannot_use(device, M, cin, BR, BC, kr, kc, st
     assert device.grim_stub_live_allocations() == live + 1
     del plan
     A.free()
+
+
+@pytest.mark.parametrize("octets", [4, 2, 1])
+@pytest.mark.parametrize("M,cin,BR,BC,k", [(128, 64, 4, 16, 3), (40, 36, 8, 12, 3), (80, 20, 16, 20, 5), (64, 12, 64, 4, 3)])
+def test_a_plan_with_a_dense_copy_and_without_memory_for_it(device, octets, M, cin, BR, BC, k):
+    """A last run that is not full and channels that fill no chunk are written inside the copy (this runs under the address
+    sanitizer); its allocation failing leaves a plan without it."""
+    A = _matrix(M, cin * k * k, BR, BC, (BR // 2, BR), (BC // 2, BC))
+    device.grim_stub_patch_octets(octets)
+    try:
+        live = device.grim_stub_live_allocations()
+        plan = g.ConvPlan(A, cin, 28, 28, k, k, 2)
+        assert device.grim_stub_live_allocations() >= live + 2
+        del plan
+        assert device.grim_stub_live_allocations() == live
+        device.grim_stub_device(1, 1)
+        plan = g.ConvPlan(A, cin, 28, 28, k, k, 2)
+        assert device.grim_stub_live_allocations() == live + 1
+        del plan
+    finally:
+        device.grim_stub_patch_octets(0)
+        device.grim_stub_device(1, -1)
+    A.free()

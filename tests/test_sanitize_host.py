@@ -74,6 +74,22 @@ def test_convolution_loads_without_range_checks_stay_inside_the_map(tmp_path):
                             assert n == 0, (n, dict(Cin=Cin, H=H, W=W, kh=kh, kw=kw, stride=stride, tile=tn))
 
 
+def test_patch_convolution_holds_every_pixel_its_taps_meet(tmp_path):
+    """Every tap of every position of every tile of the patch convolution, by its own arithmetic (csrc/conv_patch.hpp): the pixel
+    is among those the tile loads, there is room for it, and no load leaves the channel."""
+    faults = _host_library(tmp_path, "conv_patches").conv_patch_faults
+    faults.restype = ctypes.c_int64
+    sizes = list(range(1, 20)) + [27, 28, 31, 33, 47, 48, 63, 64, 65, 66, 95, 112, 113, 131]
+    for stride in (1, 2):
+        for kh, kw in ((3, 3), (1, 3), (3, 1), (5, 5), (1, 5), (7, 3)):
+            for H in (1, 2, 3, 4, 5, 7, 8, 9, 14, 28, 33):
+                for W in sizes:
+                    if H * W < 8:
+                        continue
+                    for odd in (0, 1):
+                        assert faults(H, W, kh, kw, stride, odd) == 0, dict(H=H, W=W, kh=kh, kw=kw, stride=stride, odd=odd)
+
+
 def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
     """Workgroups of a sequence call wait for one another: placing its sets on XCDs must not put more of them on any XCD than
     the plain order does, or calls on several streams could each hold a part of one XCD and wait for the rest."""
