@@ -175,8 +175,10 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
 
 // One 16-column tile for each of the matrices of a group (grid.y), whose layouts come out of a table.  Bound by latency (row
 // numbers, then rows of x and weights, then the sums) and hence by waves in flight: two steps per wave and 54 registers, eight waves
-// to a SIMD (four steps, 74 registers: 64 of 2048 x 2048 at 8 columns 29.3 -> 33.2 us, 30 of 1856 x 992 at one 11.6 -> 14.1).
-template <bool BF16, bool SOLO>
+// to a SIMD; up to four columns just their bytes of a row of x are fetched, since 16 bytes at an odd element cost the vector L1 about three
+// times what they cost at an even one (64 of 2048 x 2048 of mixed rates at 1 / 2 / 3 / 4 columns 35.3 / 27.3 / 35.6 / 27.7 -> 24.4 /
+// 24.7 / 30.3 / 26.3 us, 43 of 3872 x 1248 at one 31.4 -> 21.2).  (Four steps, 74 registers: 64 of 2048 x 2048 at 8 columns 29.3 -> 33.2 us, 30 of 1856 x 992 at one 11.6 -> 14.1).
+template <bool BF16, bool SOLO, int COLS>
 __global__ void __launch_bounds__(256, 4) bcr_spmm_gather_many(GatherParams p, const GatherSecond *table, int64_t x_stride, int64_t y_stride) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     using Entry = const __attribute__((address_space(4))) GatherSecond *;       // (read once per wave, through the scalar cache)
@@ -188,7 +190,7 @@ __global__ void __launch_bounds__(256, 4) bcr_spmm_gather_many(GatherParams p, c
     p.exact.blk_ptr = m->exact.blk_ptr; p.exact.weights = m->exact.weights;
     p.X += (int64_t)blockIdx.y * x_stride;
     p.Y += (int64_t)blockIdx.y * y_stride;
-    gather_body<BF16, false, true, SOLO, false, 1, kGatherLongWaves, 2>(p, lds, blockIdx.x, 0);
+    gather_body<BF16, false, true, SOLO, false, 1, kGatherLongWaves, 2, COLS>(p, lds, blockIdx.x, 0);
 }
 
 size_t gather_entry_bytes() { return sizeof(GatherSecond); }
@@ -209,7 +211,7 @@ grim_status launch_spmm_gather_many(const grim_bcr_group *G, const void *X, int6
     p.K = (int32_t)G->K;
     p.exact.BR = G->BR; p.exact.BC = G->BC; p.exact.nbc = (int32_t)G->nbc;
     // Enough (matrix, run) pairs to fill the GPU with a wave each: no split of a run over waves, no partial tiles.  Four waves to a
-    // run / a wave: 64 of 2048 x 2048 of mixed rates at 8 columns 29.3 / 26.8 us, 43 of 3872 x 1248 at one 34.9 / 30.3, 32 of 1024
+    // run / a wave (16 bytes of a row): 64 of 2048 x 2048 of mixed rates at 8 columns 29.3 / 26.8 us, 43 of 3872 x 1248 at one 34.9 / 30.3, 32 of 1024
     // x 512 in 8 x 32 blocks (2048 pairs of 7 steps) at 4 5.4 / 5.1; 39 of 960 x 1632 (2340 of 16 steps) 9.0 / 10.1, 12 of 2048 x
     // 512 (1536) 6.3 / 6.4, 8 of 736 x 1440 (368) 5.2 / 7.5.
     const int64_t pairs = (int64_t)G->count * G->gather_runs;
@@ -220,9 +222,12 @@ grim_status launch_spmm_gather_many(const grim_bcr_group *G, const void *X, int6
     const dim3 grid((unsigned)nwg, (unsigned)G->count);
     const size_t lds = 4 * gather_wave_lds(1);
     const GatherSecond *table = static_cast<const GatherSecond *>(G->d_gather);
-#define GRIM_MANY(BF, SO) hipLaunchKernelGGL((bcr_spmm_gather_many<BF, SO>), grid, dim3(256), lds, stream, p, table, x_stride, y_stride)
-    if (G->dtype == GRIM_BF16) { if (solo) GRIM_MANY(true, true); else GRIM_MANY(true, false); }
-    else { if (solo) GRIM_MANY(false, true); else GRIM_MANY(false, false); }
+#define GRIM_MANY(BF, SO, CO) hipLaunchKernelGGL((bcr_spmm_gather_many<BF, SO, CO>), grid, dim3(256), lds, stream, p, table, x_stride, y_stride)
+#define GRIM_MANY_SO(BF, CO) if (solo) GRIM_MANY(BF, true, CO); else GRIM_MANY(BF, false, CO)
+#define GRIM_MANY_DT(BF) if (N == 1) { GRIM_MANY_SO(BF, 1); } else if (N == 2) { GRIM_MANY_SO(BF, 2); } else if (N == 3) { GRIM_MANY_SO(BF, 3); } else if (N == 4) { GRIM_MANY_SO(BF, 4); } else { GRIM_MANY_SO(BF, 0); }
+    if (G->dtype == GRIM_BF16) { GRIM_MANY_DT(true) } else { GRIM_MANY_DT(false) }
+#undef GRIM_MANY_DT
+#undef GRIM_MANY_SO
 #undef GRIM_MANY
     return hipGetLastError() == hipSuccess ? GRIM_OK : GRIM_ERR_DEVICE;
 }

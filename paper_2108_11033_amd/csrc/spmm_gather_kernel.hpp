@@ -89,7 +89,8 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int gather_narrow_steps(int nt) { return nt == 1 ? 8 : 4; }
 constexpr int gather_wave_lds(int nt) { return nt * 2048; }    // two step buffers of 32 rows x 16 nt columns
 // STEPS: steps a wave has in flight, where the form has a choice (0: as its registers allow).
-template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves, int STEPS = 0>
+// COLS: 0, or the columns there are (1 .. 4; NARROW, NT = 1): of a row of X just their bytes are fetched then.
+template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves, int STEPS = 0, int COLS = 0>
 __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, int block_x, int block_y) {
     constexpr int NWV = EIGHT ? LONGW : 4;                     // waves of the workgroup
     constexpr int TN = NT * 16, PITCH = TN * 2, CPR = 2 * NT;  // columns, bytes and 16-byte pieces of a staged row
@@ -212,6 +213,13 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             const unsigned short *src = xcol + (int64_t)row * p.ldx;
             if constexpr (ALIGNED) {
                 r.rx[i] = *reinterpret_cast<const u32x4 *>(src);
+            } else if constexpr (COLS > 0) {     // (n0 = 0; both lanes of a row fetch it, columns from COLS on are never stored)
+                static_assert(NARROW && NT == 1 && COLS <= 4, "whole rows of a 16-column tile");
+                struct __attribute__((packed, aligned(2))) { unsigned short e[COLS]; } v;
+                unsigned int d[2] = {0u, 0u};
+                __builtin_memcpy(&v, X + (int64_t)row * p.ldx, sizeof(v));
+                __builtin_memcpy(d, &v, sizeof(v));
+                r.rx[i] = u32x4{d[0], d[1], 0u, 0u};
             } else if constexpr (NARROW) {
                 const int over = src > x_last ? (int)(src - x_last) : 0;      // elements, below 8
                 r.pad |= (unsigned int)over << (8 + 4 * i);
@@ -269,7 +277,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
                 char *b = buf + (u & 1) * (32 * PITCH);
-                if constexpr (NARROW && !ALIGNED) {
+                if constexpr (NARROW && !ALIGNED && COLS == 0) {
                     if (__builtin_amdgcn_ballot_w64(R[u].pad >> 8 != 0)) {       // (the last rows of X only)
 #pragma unroll
                         for (int i = 0; i < LI; ++i) R[u].rx[i] = drop_elements(R[u].rx[i], (R[u].pad >> (8 + 4 * i)) & 15u);

@@ -769,6 +769,9 @@ def test_device_call_errors(g):
     (16, 16, 16, 16, (16, 16), (3, 16), 1, 1, 0),        # one run of one step
     (176, 128, 16, 32, (2, 8), (4, 16), 300, 2, 0),      # 3300 runs of few steps: a wave each
     (144, 64, 8, 32, 4, 8, 228, 5, 1),                   # 2052 of one step: a wave each
+    (96, 128, 16, 32, (2, 8), (4, 16), 7, 4, 1),         # four columns and their rows' own bytes, at odd elements
+    (96, 128, 16, 32, (2, 8), (4, 16), 7, 3, 0),
+    (96, 128, 16, 32, (2, 8), (4, 16), 7, 2, 1),
     (160, 2080, 32, 32, (8, 16), (8, 32), 210, 6, 0),    # 2100 of many steps: four waves to a run
     (512, 256, 32, 32, 8, 8, 64, 3, 0),                  # uniform, 2048 runs: the most that go there
 ])
