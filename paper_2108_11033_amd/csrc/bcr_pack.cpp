@@ -1228,9 +1228,10 @@ static bool conv_on_dense_copy(const grim_bcr_matrix *A, int32_t H, int32_t W, i
     const int64_t steps = (Cin + 8 * octets - 1) / (8 * octets) * ((KK * octets + 3) / 4);
     const int64_t tiles = (Ho * Wo + 63) / 64 * batch, runs = (A->M + 63) / 64;
     if (runs * steps > (1 << 16)) return false;                              // (256 MB)
-    const int64_t pairs = tiles * A->gather.nstrips, rounds = pairs <= 1024 ? (pairs + 255) / 256 * 256 : pairs;
-    const int64_t dense = 65 * (steps + 30) * std::max<int64_t>(256, tiles * runs) / 256 + (stride == 2 ? 1000 : 0);
-    const int64_t strips = 1500 + 100 * rounds * (A->gather.nsteps + 2 * A->gather.nstrips) / (256 * A->gather.nstrips);
+    const int64_t pairs = tiles * A->gather.nstrips;
+    const double rounds = pairs <= 1024 ? (double)((pairs + 255) / 256) : (double)pairs / 256.0;
+    const double dense = 65.0 * (double)(steps + 30) * (double)std::max<int64_t>(256, tiles * runs) / 256.0 + (stride == 2 ? 1000.0 : 0.0);
+    const double strips = 1500.0 + 100.0 * rounds * ((double)A->gather.nsteps / (double)A->gather.nstrips + 2.0);
     if (dense > strips) return false;
     // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
     return stride == 2 || !conv_batch_sums_as_one_image(A, (int64_t)H * W, batch);
