@@ -16,10 +16,18 @@ namespace grim {
 // barrier until the partial tiles are added.  A step is 32 k values = four (tap, channel octet) pairs: 16 multiplies for 4 KB
 // of weights out of L2 and 4 KB of pixels out of LDS.
 //
-// 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 blocks 16.1 -> 10.9 us (1.9 of them multiplies at the matrix cores' rate,
-// 4 the launch), 448 on seven 52 x 12 maps 40 -> 24.5, the same from 103 x 24 at stride 2 118 -> 35.  Bound by the multiplies of a
+// 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 blocks 16.5 -> 11.2 us (1.9 of them multiplies at the matrix cores' rate,
+// 4 the launch), 448 on seven 52 x 12 maps 40 -> 25.7, the same from 103 x 24 at stride 2 118 -> 36.  Bound by the multiplies of a
 // compute unit's waves and the latency of a chunk's pixels before them; more pixels per task (eight channels) take registers that
 // spill, two steps of weights in flight instead of three cost 4 %.
+//
+// Sums: the steps are all of K, not what a run keeps, so a plain fp32 chain over a wave's steps would be up to four times as long
+// as the one it takes the place of, and its error with it.  A chain ends after kPatchChain steps: its sum moves into a total,
+// what that addition rounds off begins the next chain, and the waves' totals are added in 64 bits.  Error of fp32 outputs (2-norm,
+// 1e-8) of the compact runs / one chain per wave / this: 448 channels on seven 52 x 12 maps in 16 x 32 blocks 9.1 / 13.0 / 8.7, 512
+// on 32 of 14 x 14 in 4 x 16 blocks 13.1 / 13.5 / 8.8, 192 channels, 5 x 5, on four 18 x 18 in 32 x 32 blocks 8.5 / 11.2 / 8.2.
+// It costs 0.2 us per layer for the 64 bits and 0.6 us per settled chain of a compute unit's waves: 11.0 -> 11.2, 25.2 -> 25.7, 47.0
+// -> 48.9, 16.6 -> 18.9 us.  (Waves' totals as a tree in fp32: an error of 9.1 -> 8.6 where the compact runs have 7.8.)
 //
 // Infinities and NaNs: as in bcr_conv_tall, sums that are not finite are formed again from the 16-row runs.
 struct ConvPatchParams : ConvTallParams {
@@ -29,15 +37,17 @@ struct ConvPatchParams : ConvTallParams {
     int32_t wave_lds;                // bytes per wave
 };
 
-constexpr int kPatchAhead = 3;                             // tasks of a chunk asked for ahead, in 64s: as the registers allow
+constexpr int kPatchTasks = 192;                           // tasks of a chunk that octets are chosen for
 constexpr int kPatchDepth = 3;                             // steps of weights in flight
+constexpr int kPatchChain = 12;                            // steps whose sums follow one another in fp32
 constexpr int kPatchWaveBytes = 20480;                     // eight waves, or two workgroups of four, fill a compute unit's LDS
 constexpr int patch_pixel_bytes(int octets) { return octets == 1 ? 16 : octets * 16 + 16; }      // (padded: spreads reads and writes over the banks)
 
-template <bool BF16, int CO, int NWV>
+// LONG: a wave has more than kPatchChain steps (its totals take the registers of a third task asked for ahead)
+template <bool BF16, int CO, int NWV, bool LONG>
 __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p) {
     constexpr int R = kConvTallRuns, NT = 4, TN = 64, SB = patch_pixel_bytes(CO);
-    constexpr int D = kPatchDepth;
+    constexpr int D = kPatchDepth, AHEAD = LONG ? 2 : 3;    // tasks of a chunk asked for ahead, in 64s: as the registers allow
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -53,14 +63,14 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 
     const int kgroup = lane >> 4, i16 = lane & 15;
     const int c_beg = p.chunks * wave / NWV, c_end = p.chunks * (wave + 1) / NWV;
-    const i16x8 *wt = reinterpret_cast<const i16x8 *>(p.dense) + (int64_t)t * p.chunks * p.steps * (R * 64) + lane;
+    const i16x8 *wt = reinterpret_cast<const i16x8 *>(p.dense) + (int64_t)t * p.chunks * p.steps * (R * 64);
     i16x8 PW[D][R];
     // (a group of D steps past a chunk's last, or a chunk past the wave's last: any valid step, never used)
     auto fetch_weights = [&](i16x8 (&w)[R], int chunk, int st) {
         st = st < p.steps ? st : p.steps - 1;
         const i16x8 *src = wt + (int64_t)(chunk * p.steps + st) * (R * 64);
 #pragma unroll
-        for (int m = 0; m < R; ++m) w[m] = src[m * 64];
+        for (int m = 0; m < R; ++m) w[m] = src[m * 64 + lane];
     };
     if (c_beg < c_end) {
 #pragma unroll
@@ -74,20 +84,34 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     const int phi = __builtin_amdgcn_readfirstlane(patch_last(n0, p.Nv, p.W, p.Wo, s2, centre, HW));
     const int tasks = ((phi - plo) / 8 + 1) * CO * 2;      // (eight pixels of four channels) to turn around per chunk
 
-    f32x4 acc[R][NT];
+    f32x4 acc[R][NT], tot[R][NT];
 #pragma unroll
     for (int m = 0; m < R; ++m)
 #pragma unroll
-        for (int q = 0; q < NT; ++q) acc[m][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < NT; ++q) acc[m][q] = tot[m][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // moves the sums into the totals; what an addition rounds off stays behind and is added with the steps that follow
+    auto settle = [&]() {
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float s = tot[m][q][e] + acc[m][q][e];
+                    acc[m][q][e] -= s - tot[m][q][e];
+                    tot[m][q][e] = s;
+                }
+    };
 
     // A chunk's pixels: task = four channels of eight pixels, loaded along the pixels, written along the channels (the last
     // pixels of a channel are met by moving the eight back, onto pixels that are written twice with the same values).  The
-    // first kPatchAhead * 64 tasks of a chunk are asked for while the chunk before it is multiplied.
+    // first AHEAD * 64 tasks of a chunk are asked for while the chunk before it is multiplied.
     // 16 bytes at an odd element cost the vector L1 about three times what they cost at an even one: such a row is loaded one
-    // element early, its last element by itself, and shifted into place before it is written (maps of an odd number of pixels:
-    // 288 channels, 3 x 3, seven 95 x 27 maps at stride 2 32.3 -> 27.4 us)
+    // element early and shifted into place before it is written, its last element fetched then, out of lines just read (maps of an
+    // odd number of pixels: 288 channels, 3 x 3, seven 95 x 27 maps at stride 2 32.3 -> 27.5 us)
     const bool any_odd = ((HW | (plo + fodd) | fodd) & 1) != 0;       // (pieces start at plo + 8 q or at HW - 8, HW apart)
-    struct Task { u32x4 row[4]; unsigned int last[4]; };
+    struct Task { u32x4 row[4]; };
+    struct Last { unsigned int row[4]; };
     auto load_task = [&](Task &in, int chunk, int id) {
         const int o = id % (CO * 2), p8 = plo + id / (CO * 2) * 8, ch = (chunk * CO * 2 + o) * 4;
         const int e = (ch < p.cin ? ch : p.cin - 4) * HW + (p8 < HW - 8 ? p8 : HW - 8);
@@ -95,10 +119,15 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
         for (int i = 0; i < 4; ++i) {
             const int ei = e + i * HW, odd = ei > 0 ? (ei + fodd) & 1 : 0;
             in.row[i] = load_piece_any(Fimg + (unsigned int)(ei - odd));
-            in.last[i] = any_odd && odd ? (unsigned int)Fimg[(unsigned int)(ei + 7)] : 0u;
         }
     };
-    auto store_task = [&](Task &task, int chunk, int id) {
+    auto load_last = [&](Last &in, int chunk, int id) {
+        const int o = id % (CO * 2), p8 = plo + id / (CO * 2) * 8, ch = (chunk * CO * 2 + o) * 4;
+        const int e = (ch < p.cin ? ch : p.cin - 4) * HW + (p8 < HW - 8 ? p8 : HW - 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) in.row[i] = (unsigned int)Fimg[(unsigned int)(e + i * HW + 7)];
+    };
+    auto store_task = [&](Task &task, const Last &tail, int chunk, int id) {
         const int o = id % (CO * 2), p8 = plo + id / (CO * 2) * 8, st = p8 < HW - 8 ? p8 : HW - 8, ch = (chunk * CO * 2 + o) * 4;
         u32x4 (&in)[4] = task.row;
         if (any_odd) {
@@ -108,7 +137,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
                 const int ei = e + i * HW;
                 const unsigned int sh = ei > 0 && (ei + fodd) & 1 ? 16u : 0u;
                 in[i] = u32x4{__builtin_amdgcn_alignbit(in[i][1], in[i][0], sh), __builtin_amdgcn_alignbit(in[i][2], in[i][1], sh),
-                              __builtin_amdgcn_alignbit(in[i][3], in[i][2], sh), __builtin_amdgcn_alignbit(task.last[i], in[i][3], sh)};
+                              __builtin_amdgcn_alignbit(in[i][3], in[i][2], sh), __builtin_amdgcn_alignbit(tail.row[i], in[i][3], sh)};
             }
         }
         if (ch >= p.cin) {                                 // (the last chunk's channels past the last)
@@ -123,20 +152,31 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
                                                              __builtin_amdgcn_perm(in[3][j >> 1], in[2][j >> 1], pick)};
         }
     };
-    Task ahead[kPatchAhead];
+    Task ahead[AHEAD];
+    // (what is derived from the lane is formed anew for every chunk: held over the loop it would not fit the registers)
     auto ask_patch = [&](int chunk) {
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
 #pragma unroll
-        for (int a = 0; a < kPatchAhead; ++a)
+        for (int a = 0; a < AHEAD; ++a)
             if (a * 64 + lane < tasks) load_task(ahead[a], chunk, a * 64 + lane);
     };
     auto take_patch = [&](int chunk) {
+        int lane = tid & 63;
+        asm volatile("" : "+v"(lane));
 #pragma unroll
-        for (int a = 0; a < kPatchAhead; ++a)
-            if (a * 64 + lane < tasks) store_task(ahead[a], chunk, a * 64 + lane);
-        for (int id = kPatchAhead * 64 + lane; id < tasks; id += 64) {
+        for (int a = 0; a < AHEAD; ++a)
+            if (a * 64 + lane < tasks) {
+                Last tail = {};
+                if (any_odd) load_last(tail, chunk, a * 64 + lane);
+                store_task(ahead[a], tail, chunk, a * 64 + lane);
+            }
+        for (int id = AHEAD * 64 + lane; id < tasks; id += 64) {
             Task in;
+            Last end = {};
             load_task(in, chunk, id);
-            store_task(in, chunk, id);
+            if (any_odd) load_last(end, chunk, id);
+            store_task(in, end, chunk, id);
         }
         __builtin_amdgcn_wave_barrier();
     };
@@ -178,6 +218,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 #pragma unroll
             for (int m = 0; m < R; ++m) acc[m][q] = mfma16<BF16>(x[q], w[m], acc[m][q]);
     };
+    int since = 0;                                         // steps since the last settling (a group that a chunk ends in counts whole)
     for (int chunk = c_beg; chunk < c_end; ++chunk) {
         take_patch(chunk);
         if (chunk + 1 < c_end) ask_patch(chunk + 1);
@@ -190,10 +231,14 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
                 if (st + u < p.steps) multiply(st + u, PW[u]);
                 fetch_weights(PW[u], nchunk, nst + u);
             }
+            if constexpr (LONG) {
+                since += D;
+                if (since >= kPatchChain && !(last && chunk + 1 == c_end)) { settle(); since = 0; }
+            }
         }
     }
 
-    // the waves' partial tiles, added in wave order; the waves finish the (16-row run, sub-tile) pairs in turn (as in bcr_conv_tall)
+    // the waves' partial tiles, added in 64 bits; the waves finish the (16-row run, sub-tile) pairs in turn (as in bcr_conv_tall)
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
     const int wave_red = p.wave_lds / 16;
     constexpr int PAIRS = R * NT / NWV;
@@ -205,7 +250,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 #pragma unroll
     for (int m = 0; m < R; ++m)
 #pragma unroll
-        for (int q = 0; q < NT; ++q) red[wave * wave_red + (m * NT + q) * 64 + lane] = acc[m][q];
+        for (int q = 0; q < NT; ++q) red[wave * wave_red + (m * NT + q) * 64 + lane] = LONG ? tot[m][q] + acc[m][q] : acc[m][q];
 #pragma unroll
     for (int j = 0; j < PAIRS; ++j) bias[j] = p.bias && row[j] >= 0 ? p.bias[row[j]] : 0.f;
     __syncthreads();
@@ -213,12 +258,20 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 #pragma unroll
     for (int j = 0; j < PAIRS; ++j) {
         const int i = wave + j * NWV;
-        f32x4 sum = red[i * 64 + lane];
+        double part[NWV][4];                               // (as a tree: the conversions' latencies side by side)
 #pragma unroll
-        for (int w = 1; w < NWV; ++w) {
+        for (int w = 0; w < NWV; ++w) {
             const f32x4 v = red[w * wave_red + i * 64 + lane];
-            sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[w][e] = (double)v[e];
         }
+#pragma unroll
+        for (int half = NWV / 2; half > 0; half /= 2)
+#pragma unroll
+            for (int w = 0; w < half; ++w)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[w][e] += part[w + half][e];
+        const f32x4 sum = {(float)part[0][0], (float)part[0][1], (float)part[0][2], (float)part[0][3]};
         float nan = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) nan = __builtin_fmaf(sum[e], 0.f, nan);
@@ -250,7 +303,7 @@ int32_t conv_patch_octets(int64_t Cin, int32_t H, int32_t W, int32_t kh, int32_t
     if (kh * kw < 2 || kh * kw > kConvMaxTaps || (int64_t)H * W < 8 || Cin < 8 || Cin % 4 != 0) return 0;
     const int64_t pixels = patch_pixels(H, W, kh, kw, stride);
     for (int32_t co = 4; co >= 1; co /= 2)
-        if ((co == 1 || (Cin >= 64 * co && pixels / 8 * 2 * co <= kPatchAhead * 64)) && (pixels + 1) * patch_pixel_bytes(co) <= kPatchWaveBytes)
+        if ((co == 1 || (Cin >= 64 * co && pixels / 8 * 2 * co <= kPatchTasks)) && (pixels + 1) * patch_pixel_bytes(co) <= kPatchWaveBytes)
             return co;
     return 0;
 }
@@ -288,9 +341,10 @@ grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, cons
     p.wave_lds = p.zero_at + patch_pixel_bytes(L.octets);
     p.wave_lds = p.wave_lds < kConvTallRuns * 4096 ? kConvTallRuns * 4096 : p.wave_lds;       // the partial tiles go there later
     const size_t lds = (size_t)waves * p.wave_lds;
-#define GRIM_PATCH(BF, CO, NW)                                                                                       \
+    const bool longer = (L.chunks + waves - 1) / waves * L.steps > kPatchChain;
+#define GRIM_PATCH(BF, CO, NW, LO)                                                                                   \
     do {                                                                                                             \
-        auto kern = bcr_conv_patch<BF, CO, NW>;                                                                      \
+        auto kern = bcr_conv_patch<BF, CO, NW, LO>;                                                                     \
         static std::atomic<bool> attr_done{false};   /* raising a kernel's LDS limit is needed once per process */  \
         if (lds > 64 * 1024 && !attr_done) {                                                                         \
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -302,7 +356,9 @@ grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, cons
         }                                                                                                            \
         hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(NW * 64), lds, stream, p);                                \
     } while (0)
-#define GRIM_PATCH_CO(BF, CO) if (waves == 8) GRIM_PATCH(BF, CO, 8); else GRIM_PATCH(BF, CO, 4)
+#define GRIM_PATCH_CO(BF, CO)                                                                                        \
+    if (waves == 8) { if (longer) GRIM_PATCH(BF, CO, 8, true); else GRIM_PATCH(BF, CO, 8, false); }                  \
+    else { if (longer) GRIM_PATCH(BF, CO, 4, true); else GRIM_PATCH(BF, CO, 4, false); }
 #define GRIM_PATCH_DT(BF) if (L.octets == 4) { GRIM_PATCH_CO(BF, 4); } else if (L.octets == 2) { GRIM_PATCH_CO(BF, 2); } else { GRIM_PATCH_CO(BF, 1); }
     if (A->dtype == GRIM_BF16) { GRIM_PATCH_DT(true) } else { GRIM_PATCH_DT(false) }
 #undef GRIM_PATCH_DT

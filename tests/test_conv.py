@@ -716,6 +716,30 @@ def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pa
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,BR,BC,kr,kc,cin,H,W,kh,stride,B", [
+    (512, 4, 16, 2, 4, 512, 14, 14, 3, 1, 32),     # 36 dense steps to a wave, chunks of 9
+    (448, 16, 32, 8, 8, 448, 52, 12, 3, 1, 7),     # 27 and 36, where 16-row runs have 9
+    (192, 32, 32, 8, 16, 192, 18, 18, 5, 1, 4),    # chunks of 13
+    (448, 4, 16, 2, 4, 448, 51, 11, 3, 2, 28),     # chunks of 5, odd maps
+    (128, 4, 16, 2, 4, 32, 28, 28, 3, 1, 24),      # a chunk of 3 to a wave
+])
+def test_conv_plan_dense_copy_sums(M, BR, BC, kr, kc, cin, H, W, kh, stride, B):
+    """The error of fp32 sums over a dense copy does not grow with the length of K.  A rounding adds a relative error of at most
+    2^-24 / sqrt(3) (rms, of the partial sum); the squares of the partial sums of a chain of 12 add up to 6.5 times the result's, the
+    additions of totals and waves to at most twice: sqrt(8.5 / 3) 2^-24.  (One chain over 36 steps and four waves: 1.35e-7.)"""
+    import paper_2108_11033_amd as g
+    from helpers import pack_workload
+    dtype, K = gen.F16, cin * kh * kh
+    mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=910 + H)
+    Wt = gen.normal_weights(M, K, dtype, seed=911)
+    F = gen.normal_activations(cin, B * H * W, dtype, seed=912, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
+    Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
+    Yref = np.stack([(Wm @ conv_ref.im2col(f, kh, kh)).reshape(M, H, W)[:, ::stride, ::stride] for f in F64])
+    Y = _run_plan(g, pack_workload(g, Wt, dtype, mask), F, dtype, M, kh, kh, stride)
+    assert np.linalg.norm(Y - Yref) <= np.sqrt(8.5 / 3.0) * 2.0 ** -24 * np.linalg.norm(Yref)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B", [
     (128, 4, 16, 64, 28, 27, 3, 1, 9),       # 64-row runs
