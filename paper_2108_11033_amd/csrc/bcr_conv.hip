@@ -2,6 +2,8 @@
 
 namespace grim {
 
+static_assert(kConvLongWaves == 12, "the launcher names the instantiations");
+
 // The window-start word of one k slot (row `k` of the im2col matrix, 0xffffffff: padding) for a convolution plan.
 uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw) {
     const int32_t KK = kh * kw;
@@ -12,33 +14,7 @@ uint32_t conv_plan_word(uint32_t k, int32_t H, int32_t W, int32_t kh, int32_t kw
     return (uint32_t)tap << 27 | (uint32_t)(eb + (1 << 25));
 }
 
-// a wave's share of the steps of the longest strip when twelve waves split it
-static int conv_share(const grim_bcr_matrix *A) { return (A->gather.max_steps + kConvLongWaves - 1) / kConvLongWaves; }
-
-// 32-position tiles (two sub-tiles of 16) for maps of 14 x 14 and less, where 64-position tiles leave compute units without a
-// workgroup.  Stride 1: if a wave's share of a strip's steps is one batch of six where 64-position tiles would take two (72 steps
-// at 14 x 14: 12.0 -> 9.4 us).  Stride 2, whose 64-position tiles have two steps in flight against three: once four waves of
-// those need a second batch (36 steps onto 7 x 7: 11.9 -> 7.5 us, 12 steps onto 7 x 7 8.0 -> 6.8, 54 steps 15.3 -> 11.7).
-static int conv_subtiles(const grim_bcr_matrix *A, int64_t positions, int32_t batch, int32_t stride, bool planned) {
-    const bool long_enough = stride == 2 ? A->gather.max_steps > 8 : A->gather.max_steps >= 16 && conv_share(A) <= 6;
-    return planned && long_enough && (positions + 31) / 32 * batch * (int64_t)A->gather.nstrips <= 256 ? 2 : 4;
-}
-
-// Waves that split a strip's steps, by the number of (tile, strip) pairs: the launch forms of the row-gathering kernel (one
-// wave: a pair per wave); few pairs and strips of more than a batch of four waves: twelve up to 256 pairs (one workgroup per
-// compute unit), eight up to 512 (two per compute unit; 28 x 28 layers: 11.0 -> 9.4 us with 18 steps, 14.1 -> 13.3 us with 36;
-// 13 steps on three 9 x 9 maps 12.3 -> 10.4).  At stride 2 four waves are as quick up to 15 steps.
-static int conv_strip_waves(const grim_bcr_matrix *A, int nt, int64_t pairs, int32_t stride) {
-    if (gather_wave_per_strip(A, pairs, 4096)) return 1;
-    if (nt == 2) return kConvLongWaves;
-    return A->gather.max_steps <= (stride == 2 ? 15 : 12) ? 4 : pairs <= 256 ? kConvLongWaves : pairs <= 512 ? 8 : 4;
-}
-
-bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch) {
-    const int64_t tiles = (positions + 63) / 64 * (int64_t)A->gather.nstrips;
-    const int nt = conv_subtiles(A, positions, batch, 1, true), nt_one = conv_subtiles(A, positions, 1, 1, true);
-    return conv_strip_waves(A, nt, tiles * batch, 1) == conv_strip_waves(A, nt_one, tiles, 1);
-}
+bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch) { return conv_batch_sums_as_one(A, positions, batch); }
 
 grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw,
                               const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, int32_t batch, int32_t stride,

@@ -37,11 +37,8 @@ struct ConvPatchParams : ConvTallParams {
     int32_t wave_lds;                // bytes per wave
 };
 
-constexpr int kPatchTasks = 192;                           // tasks of a chunk that octets are chosen for
 constexpr int kPatchDepth = 3;                             // steps of weights in flight
 constexpr int kPatchChain = 12;                            // steps whose sums follow one another in fp32
-constexpr int kPatchWaveBytes = 20480;                     // eight waves, or two workgroups of four, fill a compute unit's LDS
-constexpr int patch_pixel_bytes(int octets) { return octets == 1 ? 16 : octets * 16 + 16; }      // (padded: spreads reads and writes over the banks)
 
 // LONG: a wave has more than kPatchChain steps (its totals take the registers of a third task asked for ahead)
 template <bool BF16, int CO, int NWV, bool LONG>
@@ -296,17 +293,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     }
 }
 
-// Octets of channels to a chunk: the most that leave eight waves a chunk each, fit their share of LDS and are asked for in one
-// go (what is not is waited for once per 64 tasks: 416 -> 96 channels, 3 x 3, from 20 x 30 at stride 2 18.1 us with 4 octets);
-// 0: the layer is not for this kernel
-int32_t conv_patch_octets(int64_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) {
-    if (kh * kw < 2 || kh * kw > kConvMaxTaps || (int64_t)H * W < 8 || Cin < 8 || Cin % 4 != 0) return 0;
-    const int64_t pixels = patch_pixels(H, W, kh, kw, stride);
-    for (int32_t co = 4; co >= 1; co /= 2)
-        if ((co == 1 || (Cin >= 64 * co && pixels / 8 * 2 * co <= kPatchTasks)) && (pixels + 1) * patch_pixel_bytes(co) <= kPatchWaveBytes)
-            return co;
-    return 0;
-}
+int32_t conv_patch_octets(int64_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) { return patch_octets(Cin, H, W, kh, kw, stride); }
 
 grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, const uint32_t *own_words, const void *F, int32_t Cin, int32_t H, int32_t W,
                               int32_t kh, int32_t kw, const float *bias, int32_t relu, void *Y, int32_t odt, int64_t ldy, hipStream_t stream,

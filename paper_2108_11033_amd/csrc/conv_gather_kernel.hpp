@@ -1,5 +1,6 @@
 // Kernel of bcr_conv.hip as a header: the wide-tile convolution's launcher builds a kernel that runs both.
 #pragma once
+#include "conv_rules.hpp"
 #include "conv_window.hpp"
 #include "spmm_common.hpp"
 
@@ -149,7 +150,6 @@ __device__ __forceinline__ u32x4 conv_shift(const u32x4 &f, int d) {
                  __builtin_amdgcn_alignbit(b4, b3, sh)};
 }
 
-constexpr int kConvMaxTaps = 31;   // 5 bits of the packed (tap, window start) word, one value left for padding slots
 constexpr int kConvTableBytes = (kConvMaxTaps + 1) * 8 * 16;   // validity masks, behind the waves' step buffers
 
 // SOLO, EIGHT: as in the row-gathering kernel -- a (tile, strip) pair per wave for strips of a few steps, eight

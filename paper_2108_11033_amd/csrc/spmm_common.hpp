@@ -80,8 +80,7 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, unsigned int n) {
 // Waves that split a long strip's steps in the few-workgroups form of the row-gathering kernels.  A 36-step strip of a
 // 14 x 14 layer: 8 waves of the product kernel (4 steps per batch) 7.66 us, 12 waves 7.63, 16 waves 8.56; the convolution
 // kernel (3 steps per batch) 11.0 us with 8, 8.6 us with 12 -- every wave then needs one batch only --, 9.7 us with 16.
-constexpr int kGatherLongWaves = 8, kGatherSmallTileWaves = 12, kConvLongWaves = 12;
-static_assert(kConvLongWaves == 12, "the launcher names the instantiations");
+constexpr int kGatherLongWaves = 8, kGatherSmallTileWaves = 12;
 
 // Workgroup id -> (tile of columns, unit of the tile's work) for the kernels whose workgroups of one
 // tile fetch the same rows: ids are dealt to the 8 XCDs round-robin, each XCD has its own L2, so a

@@ -3,6 +3,7 @@
 // address and undefined-behaviour sanitizers on a machine without a GPU.  Every launcher reports that
 // there is no device; nothing here computes anything.
 #include "bcr_matrix.hpp"
+#include "conv_rules.hpp"
 
 namespace grim {
 grim_status launch_spmm_fma(const grim_bcr_matrix *, const void *, int64_t, int64_t, float *, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
@@ -19,14 +20,17 @@ bool gather_any_applies(const grim_bcr_matrix *, const void *, int64_t, int64_t)
 bool gather32_quicker(const grim_bcr_matrix *, int64_t) { return false; }
 bool gather32_applies(const grim_bcr_matrix *, const void *) { return false; }
 grim_status launch_spmm_gather32(const grim_bcr_matrix *, const void *, int64_t, int64_t, float *, int64_t, hipStream_t) { return GRIM_ERR_DEVICE; }
+// the convolutions' rules: the library's own where a test asks for them
+static int g_conv_rules = 0;
+extern "C" void grim_stub_conv_rules(int own) { g_conv_rules = own; }
 bool gather_wave_per_strip(const grim_bcr_matrix *, int64_t, int64_t) { return false; }
 grim_status launch_conv_gather(const grim_bcr_matrix *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, int32_t, void *, int32_t, int64_t, hipStream_t, int32_t, int32_t, int64_t, int64_t, const uint32_t *, int32_t, int64_t, int64_t) { return GRIM_ERR_DEVICE; }
 grim_status launch_conv_tall(const grim_bcr_matrix *, const GatherLayout &, const uint32_t *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, int32_t, void *, int32_t, int64_t, hipStream_t, int32_t, int32_t, int64_t, int64_t) { return GRIM_ERR_DEVICE; }
-bool conv_batch_sums_as_one_image(const grim_bcr_matrix *, int64_t, int32_t) { return true; }
+bool conv_batch_sums_as_one_image(const grim_bcr_matrix *A, int64_t positions, int32_t batch) { return !g_conv_rules || conv_batch_sums_as_one(A, positions, batch); }
 uint32_t conv_plan_word(uint32_t, int32_t, int32_t, int32_t, int32_t) { return 0; }
 // octets a plan's dense copy is made with (0: none), as a test asks
 static int g_patch_octets = 0;
-int32_t conv_patch_octets(int64_t, int32_t, int32_t, int32_t, int32_t, int32_t) { return g_patch_octets; }
+int32_t conv_patch_octets(int64_t Cin, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride) { return g_conv_rules ? patch_octets(Cin, H, W, kh, kw, stride) : g_patch_octets; }
 extern "C" void grim_stub_patch_octets(int octets) { g_patch_octets = octets; }
 grim_status launch_conv_patch(const grim_bcr_matrix *, const ConvDense &, const uint32_t *, const void *, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, int32_t, void *, int32_t, int64_t, hipStream_t, int32_t, int32_t, int64_t, int64_t) { return GRIM_ERR_UNSUPPORTED; }
 size_t gather_entry_bytes() { return 8; }
