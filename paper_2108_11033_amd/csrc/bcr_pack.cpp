@@ -1430,7 +1430,7 @@ const char *grim_bcr_conv2d_kernel_name(const grim_bcr_matrix *A, int32_t Cin, i
         return "bcr_conv_wide";
     if (!A->gather.present) return "none";
     try {
-        if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_dense_copy(A, H, W, kh, kw, stride, batch)) return "bcr_conv_tall";
+        if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_dense_copy(A, H, W, kh, kw, stride, batch)) return "bcr_conv_patch";
         if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_tall_runs(A, count_run_steps<kConvTallRuns>(A), H, W, stride, batch)) return "bcr_conv_tall";
     } catch (const std::bad_alloc &) {           // (a plan without memory for that layout does without it, too)
     }

@@ -440,6 +440,7 @@ def _run_plan(g, A, F, dtype, M, kh, kw, stride, bias=None, relu=False, out_dtyp
     (24, 9, 16, 3, 1, 16, 24, 2, 2, 5),
     (32, 1, 47, 1, 1, 16, 32, 2, 2, 1),      # 1 x 1 at stride 2 on flat maps: fewer than 64 positions in rows of 24
     (32, 3, 33, 1, 1, 16, 32, 2, 3, 0),
+    (64, 17, 150, 1, 5, 4, 16, 1, 8, 0),     # a flat kernel
 ])
 def test_conv_plan_batch_and_stride(dtype, Cin, H, W, kh, kw, BR, BC, stride, B, pad):
     import paper_2108_11033_amd as g
@@ -652,15 +653,16 @@ def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, col
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("M,BR,BC,H,W,kh,kw,stride,B,pad,cin", [
-    (96, 4, 16, 70, 75, 3, 3, 1, 2, 3, 64),      # a second 64-row run of 32 rows; odd sizes and strides; 18 steps over four waves
-    (96, 4, 16, 41, 39, 3, 3, 1, 5, 3, 64),      # a last tile of 63 positions in each image
-    (64, 32, 32, 56, 56, 3, 3, 1, 4, 0, 192),    # one 64-row run, 196 tiles
+    (96, 4, 18, 70, 75, 3, 3, 1, 2, 3, 66),      # a second 64-row run of 32 rows; odd sizes and strides; 18 steps over four waves
+    (96, 4, 18, 41, 39, 3, 3, 1, 5, 3, 66),      # a last tile of 63 positions in each image
+    (96, 4, 16, 41, 39, 1, 1, 1, 5, 3, 512),     # 1 x 1 of long strips
+    (96, 4, 16, 3, 1100, 3, 3, 1, 2, 3, 64),     # rows too wide for the pixels of a tile
     (80, 16, 16, 40, 36, 3, 3, 2, 10, 0, 96),    # a run of 16 rows; strips that keep nothing
-    (256, 8, 16, 33, 47, 3, 3, 2, 6, 1, 64),     # stride 2, rows of 24 outputs
     (128, 128, 32, 9, 9, 3, 3, 2, 80, 0, 32),    # blocks taller than a run; 5 x 5 outputs: one partly filled tile per image
     (192, 4, 16, 40, 40, 1, 1, 2, 8, 0, 32),     # fewer steps than waves
     (128, 4, 16, 3, 47, 1, 1, 2, 80, 0, 64),     # flat maps at stride 2: a tile of 48 positions
-    (96, 4, 16, 70, 75, 3, 3, 1, 1, 3, 64),      # one image of the first shape: on runs of 16 rows
+    (96, 4, 18, 33, 47, 3, 3, 2, 12, 1, 66),     # stride 2, rows of 24 outputs
+    (96, 4, 18, 70, 75, 3, 3, 1, 1, 3, 66),      # one image of the first shape: on runs of 16 rows
 ])
 def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pad, cin):
     import paper_2108_11033_amd as g
@@ -692,9 +694,14 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
     (512, 4, 4, 36, 9, 9, 5, 5, 2, 96, 1),       # one partly filled tile of 25 positions per image
     (512, 4, 4, 64, 3, 3, 3, 3, 1, 96, 0),       # nine pixels: two loads per channel that overlap
     (512, 4, 4, 64, 2, 131, 3, 3, 2, 48, 1),     # rows of 66 outputs: a tile ends in the row it starts in
-    (192, 4, 16, 64, 17, 150, 1, 5, 1, 8, 0),    # flat and tall kernels
+    (192, 4, 4, 192, 17, 150, 1, 5, 1, 8, 0),    # flat and tall kernels
+    (192, 4, 16, 192, 17, 150, 1, 5, 2, 24, 0),
     (192, 4, 16, 64, 40, 30, 7, 3, 1, 8, 1),
-    (128, 4, 16, 64, 6, 440, 3, 3, 1, 8, 0),     # a tile's pixels and their neighbours in the rows next to it: 946
+    (256, 4, 4, 64, 6, 440, 3, 3, 1, 8, 0),      # a tile's pixels and their neighbours in the rows next to it: 946
+    (64, 32, 32, 192, 56, 56, 3, 3, 1, 4, 0),    # one 64-row run, 196 tiles
+    (256, 8, 16, 64, 33, 47, 3, 3, 2, 6, 1),     # stride 2, rows of 24 outputs
+    (96, 4, 16, 64, 70, 75, 3, 3, 1, 2, 3),      # a second 64-row run of 32 rows; odd sizes and strides
+    (96, 4, 16, 64, 41, 39, 3, 3, 1, 5, 3),      # a last tile of 63 positions in each image
 ])
 def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pad):
     """Layers of many steps per 64-row run and many tiles, as the plan's dense copy of the weights takes them."""
@@ -709,6 +716,7 @@ def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pa
     Yref = conv_ref.conv2d(Wm, F64, kh, kw, stride) + bias[None, :, None, None]
     S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, stride) + np.abs(bias)[None, :, None, None]
     A = pack_workload(g, Wt, dtype, mask)
+    assert g.conv2d_kernel_name(A, cin, H, W, kh, kw, B, stride) == "bcr_conv_patch"
     Y = _run_plan(g, A, F, dtype, M, kh, kw, stride, bias=bias, pad=pad)
     assert np.isfinite(Y).all()
     assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
@@ -735,7 +743,9 @@ def test_conv_plan_dense_copy_sums(M, BR, BC, kr, kc, cin, H, W, kh, stride, B):
     F = gen.normal_activations(cin, B * H * W, dtype, seed=912, relu=True).reshape(cin, B, H, W).transpose(1, 0, 2, 3).copy()
     Wm, F64 = _masked(Wt, dtype, mask), gen.storage_to_f64(F, dtype)
     Yref = np.stack([(Wm @ conv_ref.im2col(f, kh, kh)).reshape(M, H, W)[:, ::stride, ::stride] for f in F64])
-    Y = _run_plan(g, pack_workload(g, Wt, dtype, mask), F, dtype, M, kh, kh, stride)
+    A = pack_workload(g, Wt, dtype, mask)
+    assert g.conv2d_kernel_name(A, cin, H, W, kh, kh, B, stride) == "bcr_conv_patch"
+    Y = _run_plan(g, A, F, dtype, M, kh, kh, stride)
     assert np.linalg.norm(Y - Yref) <= np.sqrt(8.5 / 3.0) * 2.0 ** -24 * np.linalg.norm(Yref)
 
 

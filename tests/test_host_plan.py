@@ -16,6 +16,14 @@ def device():
     lib.grim_stub_device(0, -1)
 
 
+@pytest.fixture
+def rules(device):
+    """With the library's own rules for the convolutions' launch forms."""
+    device.grim_stub_conv_rules(1)
+    yield device
+    device.grim_stub_conv_rules(0)
+
+
 def _matrix(M, K, BR, BC, kr, kc):
     mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=M + K)
     W = gen.normal_weights(M, K, gen.F16, seed=3)
@@ -76,4 +84,17 @@ def test_a_plan_with_a_dense_copy_and_without_memory_for_it(device, octets, M, c
     finally:
         device.grim_stub_patch_octets(0)
         device.grim_stub_device(1, -1)
+    A.free()
+
+
+@pytest.mark.parametrize("cin,BC,k,batch,stride,kernel", [
+    (256, 16, 3, 4, 1, "bcr_conv_patch"),
+    (256, 16, 3, 16, 2, "bcr_conv_patch"),
+    (258, 18, 3, 4, 1, "bcr_conv_tall"),         # channels that are no whole fours
+    (768, 16, 1, 16, 1, "bcr_conv_tall"),
+    (256, 16, 3, 1, 1, "bcr_conv_gather"),       # one image: the bits of the unplanned call
+])
+def test_the_kernel_a_plan_names(rules, cin, BC, k, batch, stride, kernel):
+    A = _matrix(256, cin * k * k, 4, BC, 2, 4)
+    assert g.conv2d_kernel_name(A, cin, 28, 28, k, k, batch, stride) == kernel
     A.free()
