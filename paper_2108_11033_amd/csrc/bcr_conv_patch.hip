@@ -324,7 +324,7 @@ grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, cons
     int64_t nwg = 0;
     p.map = xcd_map(p.ntiles, p.nbr, &nwg);
     if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
-    const int waves = (int64_t)p.ntiles * p.nbr <= 256 ? 8 : 4;
+    const int waves = patch_waves(p.ntiles, p.nbr);
     p.wave_lds = p.zero_at + patch_pixel_bytes(L.octets);
     p.wave_lds = p.wave_lds < kConvTallRuns * 4096 ? kConvTallRuns * 4096 : p.wave_lds;       // the partial tiles go there later
     const size_t lds = (size_t)waves * p.wave_lds;

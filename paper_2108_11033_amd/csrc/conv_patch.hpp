@@ -4,6 +4,7 @@
 #include <cstdint>
 
 #include "host_device.hpp"
+#include "xcd_map.hpp"
 
 namespace grim {
 
@@ -34,6 +35,16 @@ inline int64_t patch_pixels(int32_t H, int32_t W, int32_t kh, int32_t kw, int32_
     const int64_t Wo = (W + stride - 1) / stride, turns = (63 + Wo - 1) / Wo;
     const int64_t span = (stride == 2 ? 126 + 2 * (W - Wo) * turns : 63) + 2 * ((int64_t)(kh / 2) * W + kw / 2) + 1;
     return ((span < (int64_t)H * W - 1 ? span : (int64_t)H * W - 1) / 8 + 1) * 8;
+}
+
+// Waves of a workgroup: eight while every workgroup has a compute unit of its own, four, two of them to a compute unit, beyond.  What
+// counts is the launch, with the workgroups that xcd_map adds where tiles are no multiple of eight: 117 tiles of 2 runs make a
+// launch of 264, 33 to an XCD of 32 compute units (128 -> 96 channels, 3 x 3, on 13 maps of 23 x 23 16.2 us with eight waves, 12.5 with
+// four; 12.7 on 16-row runs).
+inline int patch_waves(int32_t tiles, int64_t runs) {
+    int64_t workgroups = 0;
+    xcd_map(tiles, runs, &workgroups);
+    return workgroups <= 256 ? 8 : 4;
 }
 
 }  // namespace grim

@@ -36,3 +36,11 @@ extern "C" int64_t conv_patch_faults(int H, int W, int kh, int kw, int stride, i
     }
     return bad;
 }
+
+// The most workgroups of a launch that one XCD is dealt, and the waves each has
+extern "C" int conv_patch_per_xcd(int tiles, int runs, int *waves) {
+    int64_t workgroups = 0;
+    grim::xcd_map(tiles, runs, &workgroups);
+    *waves = grim::patch_waves(tiles, runs);
+    return (int)((workgroups + 7) / 8);
+}

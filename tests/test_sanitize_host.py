@@ -90,6 +90,19 @@ def test_patch_convolution_holds_every_pixel_its_taps_meet(tmp_path):
                         assert faults(H, W, kh, kw, stride, odd) == 0, dict(H=H, W=W, kh=kh, kw=kw, stride=stride, odd=odd)
 
 
+def test_patch_convolution_workgroups_of_eight_waves_have_a_compute_unit_each(tmp_path):
+    """A workgroup of eight waves fills a compute unit: an XCD has 32, and one workgroup more would run behind the others."""
+    lib = _host_library(tmp_path, "conv_patches")
+    waves = ctypes.c_int()
+    seen = set()
+    for runs in range(1, 33):
+        for tiles in range(1, 600 // runs + 2):
+            each = lib.conv_patch_per_xcd(tiles, runs, ctypes.byref(waves))
+            assert waves.value == (8 if each <= 32 else 4), (tiles, runs, each)
+            seen.add((waves.value, tiles * runs <= 256))
+    assert seen == {(8, True), (4, True), (4, False)}
+
+
 def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
     """Workgroups of a sequence call wait for one another: placing its sets on XCDs must not put more of them on any XCD than
     the plain order does, or calls on several streams could each hold a part of one XCD and wait for the rest."""
