@@ -22,12 +22,13 @@ namespace grim {
 // spill, two steps of weights in flight instead of three cost 4 %.
 //
 // Sums: the steps are all of K, not what a run keeps, so a plain fp32 chain over a wave's steps would be up to four times as long
-// as the one it takes the place of, and its error with it.  A chain ends after kPatchChain steps: its sum moves into a total,
+// as the one it takes the place of, and its error with it.  A chain ends after up to kPatchChain steps: its sum moves into a total,
 // what that addition rounds off begins the next chain, and the waves' totals are added in 64 bits.  Error of fp32 outputs (2-norm,
 // 1e-8) of the compact runs / one chain per wave / this: 448 channels on seven 52 x 12 maps in 16 x 32 blocks 9.1 / 13.0 / 8.7, 512
-// on 32 of 14 x 14 in 4 x 16 blocks 13.1 / 13.5 / 8.8, 192 channels, 5 x 5, on four 18 x 18 in 32 x 32 blocks 8.5 / 11.2 / 8.2.
-// It costs 0.2 us per layer for the 64 bits and 0.6 us per settled chain of a compute unit's waves: 11.0 -> 11.2, 25.2 -> 25.7, 47.0
-// -> 48.9, 16.6 -> 18.9 us.  (Waves' totals as a tree in fp32: an error of 9.1 -> 8.6 where the compact runs have 7.8.)
+// on 32 of 14 x 14 in 4 x 16 blocks 13.1 / 13.5 / 8.8, 192 channels, 5 x 5, on four 18 x 18 in 32 x 32 blocks 8.5 / 11.2 / 7.7; of 126
+// layers of 32 to 512 channels 0.51 to 1.01 times the compact runs'.  It costs 0.2 us per layer for the 64 bits and 0.6 us per settled
+// chain of a compute unit's waves: 11.0 -> 11.1, 25.2 -> 25.8, 47.0 -> 48.5, 16.6 -> 18.9 us.  (Waves' totals as a tree in fp32: an
+// error of 9.1 -> 8.6 where the compact runs have 7.8.)
 //
 // Infinities and NaNs: as in bcr_conv_tall, sums that are not finite are formed again from the 16-row runs.
 struct ConvPatchParams : ConvTallParams {
@@ -35,10 +36,11 @@ struct ConvPatchParams : ConvTallParams {
     int32_t cin, chunks, steps;      // channels, chunks of 8 CO of them, steps per chunk
     int32_t zero_at;                 // byte offset of the pixel of zeros
     int32_t wave_lds;                // bytes per wave
+    int32_t chain, settlings;        // LONG: steps to a chain, chains of the longest wave but for its last
 };
 
 constexpr int kPatchDepth = 3;                             // steps of weights in flight
-constexpr int kPatchChain = 12;                            // steps whose sums follow one another in fp32
+constexpr int kPatchChain = 12;                            // steps whose sums follow one another in fp32, to the group that ends them
 
 // LONG: a wave has more than kPatchChain steps (its totals take the registers of a third task asked for ahead)
 template <bool BF16, int CO, int NWV, bool LONG>
@@ -215,7 +217,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 #pragma unroll
             for (int m = 0; m < R; ++m) acc[m][q] = mfma16<BF16>(x[q], w[m], acc[m][q]);
     };
-    int since = 0;                                         // steps since the last settling (a group that a chunk ends in counts whole)
+    int since = 0, settled = 0;                            // steps since the last settling, settlings
     for (int chunk = c_beg; chunk < c_end; ++chunk) {
         take_patch(chunk);
         if (chunk + 1 < c_end) ask_patch(chunk + 1);
@@ -229,8 +231,8 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
                 fetch_weights(PW[u], nchunk, nst + u);
             }
             if constexpr (LONG) {
-                since += D;
-                if (since >= kPatchChain && !(last && chunk + 1 == c_end)) { settle(); since = 0; }
+                since += p.steps - st < D ? p.steps - st : D;
+                if (since >= p.chain && settled < p.settlings) { settle(); since = 0; ++settled; }
             }
         }
     }
@@ -328,7 +330,11 @@ grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, cons
     p.wave_lds = p.zero_at + patch_pixel_bytes(L.octets);
     p.wave_lds = p.wave_lds < kConvTallRuns * 4096 ? kConvTallRuns * 4096 : p.wave_lds;       // the partial tiles go there later
     const size_t lds = (size_t)waves * p.wave_lds;
-    const bool longer = (L.chunks + waves - 1) / waves * L.steps > kPatchChain;
+    // (the longest wave's steps in as few chains as may be, as long as one another)
+    const int wave_steps = (L.chunks + waves - 1) / waves * L.steps, chains = (wave_steps + kPatchChain - 1) / kPatchChain;
+    const bool longer = chains > 1;
+    p.chain = (wave_steps + chains - 1) / chains - kPatchDepth / 2;          // (ends with the group whose end is nearest)
+    p.settlings = chains - 1;
 #define GRIM_PATCH(BF, CO, NW, LO)                                                                                   \
     do {                                                                                                             \
         auto kern = bcr_conv_patch<BF, CO, NW, LO>;                                                                     \
