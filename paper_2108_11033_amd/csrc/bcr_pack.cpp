@@ -11,6 +11,7 @@
 #include <system_error>
 
 #include "bcr_matrix.hpp"
+#include "conv_patch.hpp"
 
 using namespace grim;
 
@@ -1210,38 +1211,62 @@ static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, in
     return stride == 2 || !conv_batch_sums_as_one_image(A, positions, batch);
 }
 
-// The dense copy (bcr_conv_patch) multiplies every k value of a run, its workgroups are a fourth as many as those on 16-row runs,
-// and a step costs less.  Nanoseconds of a compute unit: 65 per step of a 64-row run and 30 steps' worth per workgroup (1000 more at
-// stride 2, whose tiles span more pixels) against 100 per step of a 16-row run and two steps' worth, in whole rounds up to four of
-// them.  Fitted to 49 layers, of which two that would gain 4 and 14 % stay and none that loses is taken.  Before -> on the dense
-// copy: 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 / 16 x 32 / mixed 32 x 32 blocks 16.1 / 13.7 / 12.0 -> 10.9 / 11.0 / 11.0
-// us; 448 from seven 103 x 24 maps at stride 2 in 4 x 16 / 16 x 32 blocks 118 / 83 -> 35 / 35; 512 on eight 14 x 14 19.5 -> 16.4;
-// 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.5 -> 16.8; 32 -> 128 on 24 maps of 28 x 28 in 4 x 16 blocks 17.3 -> 12.8.
-// Not taken: that layer in 16 x 32 blocks 10.3 -> 12.6; 128 -> 256 from four 56 x 56 at stride 2 in 16 x 32 blocks 10.8 -> 11.6;
-// 256 -> 512 from one 28 x 28 at stride 2 7.3 -> 13.4; 64 -> 128 from one 112 x 112 6.4 -> 9.0.
-static bool conv_on_dense_copy(const grim_bcr_matrix *A, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride, int32_t batch) {
+// The dense copy (bcr_conv_patch) where it is to be quicker than the kernel the layer would run on without it.  Microseconds, by the
+// forms the three kernels run in (workgroups of eight waves with a compute unit each, or of four waves in rounds of two to a compute
+// unit; a last round that is at most half full counts 0.7):
+//   dense    0.38 per step of a wave, 0.72 or 0.66 per 64 tasks (pixels of a chunk) of a wave, 2.6 or 5 per workgroup, 3.5 per launch
+//   64-row   1.07 or 1.03 per step of a wave (1.44 times that at stride 2), 4 or 5.35 per workgroup, 3.2 per launch
+//   16-row   0.107 per step of a strip and 0.45 per strip (1.3 times that at stride 2) in rounds of 256, 5.7 per launch
+// Fitted to 518 layers of 32 to 512 channels, 3 x 3 and 5 x 5, on 2 to 32 maps of 7 x 7 to 64 x 64, each run with and without the dense
+// copy; the estimates lie within 12 % (rms).  The dense copy has to be estimated 2 % ahead.  Of 718 layers, 200 of them not in the
+// fit, 341 get it, 15 of which lose 3 % or more, the worst 15 (steps of 64-row runs against those of 16-row runs alone: 385, of
+// which 52 lost, the worst 37 %); in all 16.85 ms without, 14.16 with this rule, 14.07 with the quicker one each time.
+// Without -> on the dense copy: 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 / 16 x 32 / mixed 32 x 32 blocks 16.5 / 13.7 / 11.9
+// -> 11.2 / 11.2 / 11.1 us; 448 from seven 103 x 24 maps at stride 2 in 4 x 16 / 16 x 32 blocks 119 / 82 -> 36 / 36; 512 on eight
+// 14 x 14 19.3 -> 17.4; 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.4 -> 18.9.  Not taken: 224 -> 160 on eight 47 x 47 maps in
+// mixed 32 x 32 blocks 29.0 -> 39.9; 288 -> 224 on 26 of 17 x 17 in 16 x 32 blocks 25.2 -> 34.4; 160 -> 192 from five 56 x 56 at stride 2
+// 11.0 -> 13.2; 320 -> 384 on five 35 x 35 31.6 -> 38.7.
+static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride, int32_t batch) {
     if (!A->gather.present || A->gather.nstrips == 0 || A->M <= 16) return false;
     const int64_t KK = (int64_t)kh * kw, Cin = A->K / KK;
     const int32_t octets = conv_patch_octets(Cin, H, W, kh, kw, stride);
     if (octets == 0) return false;
     const int64_t Ho = (H + stride - 1) / stride, Wo = (W + stride - 1) / stride;
-    const int64_t steps = (Cin + 8 * octets - 1) / (8 * octets) * ((KK * octets + 3) / 4);
-    const int64_t tiles = (Ho * Wo + 63) / 64 * batch, runs = (A->M + 63) / 64;
-    if (runs * steps > (1 << 16)) return false;                              // (256 MB)
-    const int64_t pairs = tiles * A->gather.nstrips;
-    const double rounds = pairs <= 1024 ? (double)((pairs + 255) / 256) : (double)pairs / 256.0;
-    const double dense = 65.0 * (double)(steps + 30) * (double)std::max<int64_t>(256, tiles * runs) / 256.0 + (stride == 2 ? 1000.0 : 0.0);
-    const double strips = 1500.0 + 100.0 * rounds * ((double)A->gather.nsteps / (double)A->gather.nstrips + 2.0);
-    if (dense > strips) return false;
+    const int64_t chunks = (Cin + 8 * octets - 1) / (8 * octets), steps = (KK * octets + 3) / 4, runs = (A->M + 63) / 64;
+    if (runs * chunks * steps > (1 << 16)) return false;                     // (256 MB)
     // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
-    return stride == 2 || !conv_batch_sums_as_one_image(A, (int64_t)H * W, batch);
+    if (stride == 1 && conv_batch_sums_as_one_image(A, (int64_t)H * W, batch)) return false;
+    auto rounds = [](int64_t n, int64_t slots) {
+        const int64_t whole = n / slots, rest = n % slots;
+        return n > 8 * slots ? (double)n / (double)slots : (double)whole + (rest == 0 ? 0.0 : 2 * rest <= slots ? 0.7 : 1.0);
+    };
+    const int64_t tiles = (Ho * Wo + 63) / 64 * batch;
+    const int64_t row_tiles = stride == 2 ? (Ho * ((Wo + 7) / 8 * 8) + 63) / 64 * batch : tiles;       // (rows padded to pieces there)
+    if (row_tiles > 0x7fffffff / 16) return false;                           // (refused by every launcher)
+    int64_t launched = 0;
+    xcd_map((int32_t)tiles, runs, &launched);
+    const double tasks = (double)((patch_pixels(H, W, kh, kw, stride) / 8 * 2 * octets + 63) / 64);
+    const int waves = patch_waves((int32_t)tiles, runs);
+    const double share = (double)((chunks + waves - 1) / waves) * (double)steps, turned = (double)((chunks + waves - 1) / waves) * tasks;
+    const double dense = 3.5 + (waves == 8 ? 2.6 + 0.375 * share + 0.72 * turned : rounds(launched, 512) * (5.0 + 0.385 * share + 0.66 * turned));
+    double without;
+    if (conv_on_tall_runs(A, tall, H, W, stride, batch)) {
+        const double step = (double)tall.total / (double)tall.runs * (stride == 2 ? 1.44 : 1.0);
+        xcd_map((int32_t)row_tiles, tall.runs, &launched);
+        without = 3.2 + (row_tiles * tall.runs <= 256 ? rounds(launched, 256) * (4.0 + 1.07 * step / 8.0) : rounds(launched, 512) * (5.35 + 1.03 * step / 4.0));
+    } else {
+        const int64_t pairs = row_tiles * A->gather.nstrips;
+        const double turns = pairs <= 1024 ? (double)((pairs + 255) / 256) : (double)pairs / 256.0;
+        without = 5.7 + 0.107 * turns * ((double)A->gather.nsteps / (double)A->gather.nstrips + 4.2) * (stride == 2 ? 1.3 : 1.0);
+    }
+    return dense * 1.02 <= without;
 }
 
 // The plan's dense copy of the weights (ConvDense); without memory for it the plan does without.
 static void add_dense_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
-    bool met = conv_on_dense_copy(A, P->H, P->W, P->kh, P->kw, P->stride, 1 << 20);
-    for (int32_t batch = 1; batch <= 64 && !met; ++batch) met = conv_on_dense_copy(A, P->H, P->W, P->kh, P->kw, P->stride, batch);
+    bool met = conv_on_dense_copy(A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, 1 << 20);
+    for (int32_t batch = 1; batch <= 64 && !met; ++batch) met = conv_on_dense_copy(A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch);
     if (!met) return;
     ConvDense &D = P->dense;
     const int32_t octets = conv_patch_octets(P->Cin, P->H, P->W, P->kh, P->kw, P->stride);
@@ -1302,14 +1327,13 @@ static void add_dense_layout(grim_bcr_conv_plan *P) {
 static void add_tall_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
     GatherLayout &L = P->tall;
-    RunSteps steps;
+    const RunSteps &steps = P->tall_steps;
     try {
-        steps = count_run_steps<kConvTallRuns>(A);
         // (the splits of a sum over waves follow one another with the batch: the largest stands for all that are not one image's)
         if (!conv_on_tall_runs(A, steps, P->H, P->W, P->stride, 1 << 20)) return;
         bool met = !P->dense.present;            // by a batch that the dense copy is not for
         for (int32_t batch = 1; batch <= 64 && !met; ++batch)
-            met = conv_on_tall_runs(A, steps, P->H, P->W, P->stride, batch) && !conv_on_dense_copy(A, P->H, P->W, P->kh, P->kw, P->stride, batch);
+            met = conv_on_tall_runs(A, steps, P->H, P->W, P->stride, batch) && !conv_on_dense_copy(A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch);
         if (!met) return;
         build_gather_layout<kConvTallRuns>(A, L);
         for (uint32_t &r : L.rows) r = conv_plan_word(r, P->H, P->W, P->kh, P->kw);
@@ -1337,7 +1361,6 @@ static void add_tall_layout(grim_bcr_conv_plan *P) {
         return;
     }
     P->d_tall = base;
-    P->tall_steps = steps;
     L.d_sptr = reinterpret_cast<int32_t *>(base + o_s);
     L.d_out_row = reinterpret_cast<int32_t *>(base + o_q);
     L.d_rows = reinterpret_cast<uint32_t *>(base + o_r);
@@ -1370,6 +1393,10 @@ grim_status grim_bcr_conv_plan_create(const grim_bcr_matrix *A, int32_t Cin, int
         return GRIM_ERR_DEVICE;
     }
     P->d_words = static_cast<uint32_t *>(ptr);
+    try {
+        P->tall_steps = count_run_steps<kConvTallRuns>(A);
+    } catch (const std::bad_alloc &) {           // (no runs: neither layout)
+    }
     add_dense_layout(P.get());
     add_tall_layout(P.get());
     *out = P.release();
@@ -1402,7 +1429,7 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev,
                                                 static_cast<hipStream_t>(hip_stream));
         if (st != GRIM_ERR_UNSUPPORTED) return st;
     }
-    if (P->dense.present && conv_on_dense_copy(P->A, P->H, P->W, P->kh, P->kw, P->stride, batch)) {
+    if (P->dense.present && conv_on_dense_copy(P->A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch)) {
         const grim_status st = launch_conv_patch(P->A, P->dense, P->d_words, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
                                                  (int32_t)out_dt, ldo, static_cast<hipStream_t>(hip_stream), batch, P->stride, f_image_stride,
                                                  out_image_stride);
@@ -1430,8 +1457,11 @@ const char *grim_bcr_conv2d_kernel_name(const grim_bcr_matrix *A, int32_t Cin, i
         return "bcr_conv_wide";
     if (!A->gather.present) return "none";
     try {
-        if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_dense_copy(A, H, W, kh, kw, stride, batch)) return "bcr_conv_patch";
-        if ((stride == 2 || (stride == 1 && batch > 1)) && conv_on_tall_runs(A, count_run_steps<kConvTallRuns>(A), H, W, stride, batch)) return "bcr_conv_tall";
+        if (stride == 2 || (stride == 1 && batch > 1)) {
+            const RunSteps tall = count_run_steps<kConvTallRuns>(A);
+            if (conv_on_dense_copy(A, tall, H, W, kh, kw, stride, batch)) return "bcr_conv_patch";
+            if (conv_on_tall_runs(A, tall, H, W, stride, batch)) return "bcr_conv_tall";
+        }
     } catch (const std::bad_alloc &) {           // (a plan without memory for that layout does without it, too)
     }
     return "bcr_conv_gather";

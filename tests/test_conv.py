@@ -655,6 +655,7 @@ def test_conv_plan_small_maps_of_long_strips(dtype, H, W, kh, kw, stride, B, col
 @pytest.mark.parametrize("M,BR,BC,H,W,kh,kw,stride,B,pad,cin", [
     (96, 4, 18, 70, 75, 3, 3, 1, 2, 3, 66),      # a second 64-row run of 32 rows; odd sizes and strides; 18 steps over four waves
     (96, 4, 18, 41, 39, 3, 3, 1, 5, 3, 66),      # a last tile of 63 positions in each image
+    (64, 32, 32, 56, 56, 3, 3, 1, 4, 0, 192),    # one 64-row run, 196 tiles
     (96, 4, 16, 41, 39, 1, 1, 1, 5, 3, 512),     # 1 x 1 of long strips
     (96, 4, 16, 3, 1100, 3, 3, 1, 2, 3, 64),     # rows too wide for the pixels of a tile
     (80, 16, 16, 40, 36, 3, 3, 2, 10, 0, 96),    # a run of 16 rows; strips that keep nothing
@@ -689,7 +690,7 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
 @pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,kw,stride,B,pad", [
     (256, 4, 16, 256, 28, 28, 3, 3, 1, 4, 0),    # eight waves, a chunk of 32 channels each
     (256, 4, 16, 128, 28, 28, 3, 3, 1, 8, 1),    # four waves; chunks of 16; every second image at an odd element
-    (144, 4, 4, 68, 31, 33, 3, 3, 1, 14, 3),     # a last run of 16 rows; channels that fill no chunk; odd maps, odd strides
+    (208, 4, 4, 68, 31, 33, 5, 5, 1, 14, 3),     # a last run of 16 rows; channels that fill no chunk; odd maps, odd strides
     (128, 4, 16, 272, 57, 31, 3, 3, 2, 6, 0),    # stride 2 of odd maps: the last column and row are outputs
     (512, 4, 4, 36, 9, 9, 5, 5, 2, 96, 1),       # one partly filled tile of 25 positions per image
     (512, 4, 4, 64, 3, 3, 3, 3, 1, 96, 0),       # nine pixels: two loads per channel that overlap
@@ -697,8 +698,8 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
     (192, 4, 4, 192, 17, 150, 1, 5, 1, 8, 0),    # flat and tall kernels
     (192, 4, 16, 192, 17, 150, 1, 5, 2, 24, 0),
     (192, 4, 16, 64, 40, 30, 7, 3, 1, 8, 1),
-    (256, 4, 4, 64, 6, 440, 3, 3, 1, 8, 0),      # a tile's pixels and their neighbours in the rows next to it: 946
-    (64, 32, 32, 192, 56, 56, 3, 3, 1, 4, 0),    # one 64-row run, 196 tiles
+    (256, 4, 4, 64, 6, 200, 5, 5, 1, 8, 0),      # a tile's pixels and their neighbours in the rows next to it: 868
+    (64, 4, 16, 192, 56, 56, 3, 3, 1, 4, 0),     # one 64-row run, 196 tiles
     (256, 8, 16, 64, 33, 47, 3, 3, 2, 6, 1),     # stride 2, rows of 24 outputs
     (96, 4, 16, 64, 70, 75, 3, 3, 1, 2, 3),      # a second 64-row run of 32 rows; odd sizes and strides
     (96, 4, 16, 64, 41, 39, 3, 3, 1, 5, 3),      # a last tile of 63 positions in each image

@@ -98,3 +98,26 @@ def test_the_kernel_a_plan_names(rules, cin, BC, k, batch, stride, kernel):
     A = _matrix(256, cin * k * k, 4, BC, 2, 4)
     assert g.conv2d_kernel_name(A, cin, 28, 28, k, k, batch, stride) == kernel
     A.free()
+
+
+MIXED_32 = ((4, 8, 16), (4, 8, 16))
+
+
+@pytest.mark.parametrize("cin,M,H,W,k,stride,batch,BR,BC,keep,dense", [
+    # microseconds without and on the dense copy
+    (224, 160, 47, 47, 3, 1, 8, 32, 32, MIXED_32, False),        # 29.0, 39.9
+    (288, 224, 17, 17, 3, 1, 26, 16, 32, (8, 8), False),         # 25.2, 34.4: a few workgroups behind a full round
+    (160, 192, 56, 56, 3, 2, 5, 16, 32, (8, 8), False),          # 11.0, 13.2
+    (320, 384, 35, 35, 3, 1, 5, 16, 32, (8, 8), False),          # 31.6, 38.7
+    (320, 64, 51, 41, 3, 1, 3, 8, 16, (4, 4), False),            # 14.3, 17.4
+    (128, 288, 59, 59, 3, 2, 3, 32, 32, MIXED_32, False),        # 10.5, 12.2
+    (256, 256, 28, 28, 3, 1, 4, 16, 32, (8, 8), True),           # 13.7, 11.2
+    (448, 448, 103, 24, 3, 2, 7, 16, 32, (8, 8), True),          # 82.1, 36.1
+    (512, 512, 14, 14, 3, 1, 8, 16, 32, (8, 8), True),           # 19.3, 17.4
+    (192, 192, 18, 18, 5, 1, 4, 32, 32, (8, 16), True),          # 20.4, 18.9
+    (32, 128, 28, 28, 3, 1, 24, 4, 16, (2, 4), True),            # 18.4, 12.5
+])
+def test_the_dense_copy_is_taken_where_it_is_quicker(rules, cin, M, H, W, k, stride, batch, BR, BC, keep, dense):
+    A = _matrix(M, cin * k * k, BR, BC, *keep)
+    assert (g.conv2d_kernel_name(A, cin, H, W, k, k, batch, stride) == "bcr_conv_patch") == dense
+    A.free()
