@@ -1226,6 +1226,8 @@ static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, in
 // 14 x 14 19.3 -> 17.4; 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.4 -> 18.9.  Not taken: 224 -> 160 on eight 47 x 47 maps in
 // mixed 32 x 32 blocks 29.0 -> 39.9; 288 -> 224 on 26 of 17 x 17 in 16 x 32 blocks 25.2 -> 34.4; 160 -> 192 from five 56 x 56 at stride 2
 // 11.0 -> 13.2; 320 -> 384 on five 35 x 35 31.6 -> 38.7.
+constexpr int64_t kConvWholeRounds = 8;          // rounds of workgroups that are counted whole
+
 static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride, int32_t batch) {
     if (!A->gather.present || A->gather.nstrips == 0 || A->M <= 16) return false;
     const int64_t KK = (int64_t)kh * kw, Cin = A->K / KK;
@@ -1236,9 +1238,9 @@ static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, i
     if (runs * chunks * steps > (1 << 16)) return false;                     // (256 MB)
     // (where a batch on 16-row runs has the bits of its images one by one, it keeps them)
     if (stride == 1 && conv_batch_sums_as_one_image(A, (int64_t)H * W, batch)) return false;
-    auto rounds = [](int64_t n, int64_t slots) {
-        const int64_t whole = n / slots, rest = n % slots;
-        return n > 8 * slots ? (double)n / (double)slots : (double)whole + (rest == 0 ? 0.0 : 2 * rest <= slots ? 0.7 : 1.0);
+    auto rounds = [](int64_t n, int64_t launch, int64_t slots) {             // of n workgroups, `launch` with those that only pad
+        const int64_t whole = launch / slots, rest = launch % slots;
+        return n > kConvWholeRounds * slots ? (double)n / (double)slots : (double)whole + (rest == 0 ? 0.0 : 2 * rest <= slots ? 0.7 : 1.0);
     };
     const int64_t tiles = (Ho * Wo + 63) / 64 * batch;
     const int64_t row_tiles = stride == 2 ? (Ho * ((Wo + 7) / 8 * 8) + 63) / 64 * batch : tiles;       // (rows padded to pieces there)
@@ -1248,12 +1250,13 @@ static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, i
     const double tasks = (double)((patch_pixels(H, W, kh, kw, stride) / 8 * 2 * octets + 63) / 64);
     const int waves = patch_waves((int32_t)tiles, runs);
     const double share = (double)((chunks + waves - 1) / waves) * (double)steps, turned = (double)((chunks + waves - 1) / waves) * tasks;
-    const double dense = 3.5 + (waves == 8 ? 2.6 + 0.375 * share + 0.72 * turned : rounds(launched, 512) * (5.0 + 0.385 * share + 0.66 * turned));
+    const double dense = 3.5 + (waves == 8 ? 2.6 + 0.375 * share + 0.72 * turned : rounds(tiles * runs, launched, 512) * (5.0 + 0.385 * share + 0.66 * turned));
     double without;
     if (conv_on_tall_runs(A, tall, H, W, stride, batch)) {
         const double step = (double)tall.total / (double)tall.runs * (stride == 2 ? 1.44 : 1.0);
         xcd_map((int32_t)row_tiles, tall.runs, &launched);
-        without = 3.2 + (row_tiles * tall.runs <= 256 ? rounds(launched, 256) * (4.0 + 1.07 * step / 8.0) : rounds(launched, 512) * (5.35 + 1.03 * step / 4.0));
+        const int64_t pairs = row_tiles * tall.runs;
+        without = 3.2 + (pairs <= 256 ? rounds(pairs, launched, 256) * (4.0 + 1.07 * step / 8.0) : rounds(pairs, launched, 512) * (5.35 + 1.03 * step / 4.0));
     } else {
         const int64_t pairs = row_tiles * A->gather.nstrips;
         const double turns = pairs <= 1024 ? (double)((pairs + 255) / 256) : (double)pairs / 256.0;
@@ -1262,12 +1265,29 @@ static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, i
     return dense * 1.02 <= without;
 }
 
+// Does `met` hold for some batch the plan can be called with?  The forms of the kernels, and with them what the rules answer, change
+// with the batch up to kConvWholeRounds rounds of 512 workgroups on 64-row runs; beyond, every estimate is linear in the batch, so
+// that what holds for any batch there holds for the first or for the last.
+static bool conv_some_batch(const grim_bcr_conv_plan *P, bool (*met)(const grim_bcr_conv_plan *, int32_t)) {
+    const int64_t Ho = (P->H + P->stride - 1) / P->stride, Wo = (P->W + P->stride - 1) / P->stride;
+    const int64_t tiles = (Ho * ((Wo + 7) / 8 * 8) + 63) / 64, pairs = (Ho * Wo + 63) / 64 * ((P->A->M + 63) / 64);
+    const int64_t last = std::max<int64_t>(1, (0x7fffffff / 16) / tiles), linear = std::min(last, kConvWholeRounds * 512 / pairs + 1);
+    for (int64_t batch = 1; batch <= linear; ++batch)
+        if (met(P, (int32_t)batch)) return true;
+    return met(P, (int32_t)last);
+}
+
+static bool plan_on_dense_copy(const grim_bcr_conv_plan *P, int32_t batch) {
+    return conv_on_dense_copy(P->A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch);
+}
+static bool plan_on_tall_runs(const grim_bcr_conv_plan *P, int32_t batch) {              // where it is not on a dense copy that it has
+    return conv_on_tall_runs(P->A, P->tall_steps, P->H, P->W, P->stride, batch) && !(P->dense.present && plan_on_dense_copy(P, batch));
+}
+
 // The plan's dense copy of the weights (ConvDense); without memory for it the plan does without.
 static void add_dense_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
-    bool met = conv_on_dense_copy(A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, 1 << 20);
-    for (int32_t batch = 1; batch <= 64 && !met; ++batch) met = conv_on_dense_copy(A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch);
-    if (!met) return;
+    if (!conv_some_batch(P, plan_on_dense_copy)) return;
     ConvDense &D = P->dense;
     const int32_t octets = conv_patch_octets(P->Cin, P->H, P->W, P->kh, P->kw, P->stride);
     const int32_t KK = P->kh * P->kw;
@@ -1327,14 +1347,8 @@ static void add_dense_layout(grim_bcr_conv_plan *P) {
 static void add_tall_layout(grim_bcr_conv_plan *P) {
     const grim_bcr_matrix *A = P->A;
     GatherLayout &L = P->tall;
-    const RunSteps &steps = P->tall_steps;
     try {
-        // (the splits of a sum over waves follow one another with the batch: the largest stands for all that are not one image's)
-        if (!conv_on_tall_runs(A, steps, P->H, P->W, P->stride, 1 << 20)) return;
-        bool met = !P->dense.present;            // by a batch that the dense copy is not for
-        for (int32_t batch = 1; batch <= 64 && !met; ++batch)
-            met = conv_on_tall_runs(A, steps, P->H, P->W, P->stride, batch) && !conv_on_dense_copy(A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch);
-        if (!met) return;
+        if (!conv_some_batch(P, plan_on_tall_runs)) return;
         build_gather_layout<kConvTallRuns>(A, L);
         for (uint32_t &r : L.rows) r = conv_plan_word(r, P->H, P->W, P->kh, P->kw);
     } catch (const std::bad_alloc &) {
@@ -1429,7 +1443,7 @@ grim_status grim_bcr_conv2d_plan(const grim_bcr_conv_plan *P, const void *F_dev,
                                                 static_cast<hipStream_t>(hip_stream));
         if (st != GRIM_ERR_UNSUPPORTED) return st;
     }
-    if (P->dense.present && conv_on_dense_copy(P->A, P->tall_steps, P->H, P->W, P->kh, P->kw, P->stride, batch)) {
+    if (P->dense.present && plan_on_dense_copy(P, batch)) {
         const grim_status st = launch_conv_patch(P->A, P->dense, P->d_words, F_dev, P->Cin, P->H, P->W, P->kh, P->kw, bias_dev, relu ? 1 : 0, out_dev,
                                                  (int32_t)out_dt, ldo, static_cast<hipStream_t>(hip_stream), batch, P->stride, f_image_stride,
                                                  out_image_stride);

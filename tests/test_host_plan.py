@@ -121,3 +121,22 @@ def test_the_dense_copy_is_taken_where_it_is_quicker(rules, cin, M, H, W, k, str
     A = _matrix(M, cin * k * k, BR, BC, *keep)
     assert (g.conv2d_kernel_name(A, cin, H, W, k, k, batch, stride) == "bcr_conv_patch") == dense
     A.free()
+
+
+@pytest.mark.parametrize("cin,M,H,W,stride,BR,BC,keep,kernel,batch", [
+    (64, 128, 13, 13, 1, 32, 32, MIXED_32, "bcr_conv_patch", 71),        # to 84
+    (32, 64, 46, 11, 2, 16, 32, (8, 8), "bcr_conv_patch", 77),           # to 85
+    (64, 256, 16, 4, 2, 32, 32, MIXED_32, "bcr_conv_tall", 65),          # to 128; on the dense copy before and after
+    (64, 256, 4, 35, 2, 32, 32, (8, 8), "bcr_conv_tall", 65),            # and all larger ones
+    (128, 224, 5, 5, 1, 16, 32, (8, 8), "bcr_conv_patch", 512),
+])
+def test_a_plan_holds_the_layouts_of_batches_above_64(rules, cin, M, H, W, stride, BR, BC, keep, kernel, batch):
+    """A few batches, or all from some number on, run on a layout that smaller ones do not use."""
+    A = _matrix(M, cin * 9, BR, BC, *keep)
+    names = [g.conv2d_kernel_name(A, cin, H, W, 3, 3, b, stride) for b in list(range(1, 65)) + [batch]]
+    assert kernel not in names[:64] and names[64] == kernel
+    live = rules.grim_stub_live_allocations()
+    plan = g.ConvPlan(A, cin, H, W, 3, 3, stride)
+    assert rules.grim_stub_live_allocations() == live + 1 + len({"bcr_conv_patch", "bcr_conv_tall"} & set(names))
+    del plan
+    A.free()
