@@ -752,14 +752,19 @@ def test_conv_plan_dense_copy_sums(M, BR, BC, kr, kc, cin, H, W, kh, stride, B):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
-@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B", [
-    (128, 4, 16, 64, 28, 27, 3, 1, 9),       # 64-row runs
-    (208, 16, 16, 64, 29, 31, 3, 2, 12),     # 64-row runs at stride 2, a last run of 16 rows
-    (48, 16, 32, 256, 13, 14, 3, 1, 1),      # 32-position tiles
-    (48, 16, 32, 256, 13, 14, 3, 2, 1),
-    (48, 8, 16, 16, 17, 19, 3, 1, 2),        # 64-position tiles
+@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B,kernel", [
+    (112, 4, 18, 198, 28, 27, 3, 1, 9, "bcr_conv_tall"),        # 64-row runs, a last one of 48 rows
+    (208, 16, 16, 64, 29, 31, 3, 2, 12, "bcr_conv_tall"),       # at stride 2, a last run of 16 rows
+    (208, 4, 16, 256, 29, 31, 3, 1, 3, "bcr_conv_patch"),       # a dense copy: eight waves, a last run of 16 rows, odd maps
+    (144, 4, 16, 128, 29, 27, 3, 1, 9, "bcr_conv_patch"),       # four waves
+    (208, 4, 16, 128, 29, 31, 3, 2, 12, "bcr_conv_patch"),      # at stride 2, eight waves
+    (144, 4, 8, 64, 30, 31, 5, 2, 24, "bcr_conv_patch"),        # four
+    (128, 4, 16, 64, 28, 27, 3, 1, 9, "bcr_conv_gather"),
+    (48, 16, 32, 256, 13, 14, 3, 1, 1, "bcr_conv_gather"),      # 32-position tiles
+    (48, 16, 32, 256, 13, 14, 3, 2, 1, "bcr_conv_gather"),
+    (48, 8, 16, 16, 17, 19, 3, 1, 2, "bcr_conv_gather"),        # 64-position tiles
 ])
-def test_conv_plan_infinities_and_nans_stay_in_the_16_row_runs_that_name_them(dtype, M, BR, BC, cin, H, W, kh, stride, B):
+def test_conv_plan_infinities_and_nans_stay_in_the_16_row_runs_that_name_them(dtype, M, BR, BC, cin, H, W, kh, stride, B, kernel):
     """A value of the feature map that is not finite may turn up in any row of a 16-row run (of the stored order) with a row
     that keeps its column; rows of other runs are right, and rows that keep it are not finite."""
     import paper_2108_11033_amd as g
@@ -779,6 +784,7 @@ def test_conv_plan_infinities_and_nans_stay_in_the_16_row_runs_that_name_them(dt
         spots[b, c, h, w] = True
     finite = np.where(spots, 0.0, clean)
     A = g.pack(Wt, dtype, BR, BC, mask.row_ptr, mask.row_idx, mask.col_ptr, mask.col_idx, no_reorder=True)
+    assert g.conv2d_kernel_name(A, cin, H, W, kh, kh, B, stride) == kernel
     Y = _run_plan(g, A, F, dtype, M, kh, kh, stride)
     keep = Wm != 0                                              # (no stored weight is zero)
     named = np.repeat(np.add.reduceat(keep, np.arange(0, M, 16), axis=0) > 0, 16, axis=0)[:M]
@@ -794,7 +800,8 @@ def test_conv_plan_infinities_and_nans_stay_in_the_16_row_runs_that_name_them(dt
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
 @pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,stride,B", [
-    (128, 4, 16, 64, 28, 27, 3, 1, 9),       # 64-row runs
+    (128, 4, 16, 64, 28, 27, 3, 1, 9),       # a dense copy
+    (112, 4, 18, 198, 28, 27, 3, 1, 9),      # 64-row runs
     (128, 16, 24, 8, 224, 224, 3, 1, 1),     # wide tiles, blocks of 16 and of 32 rows
     (256, 32, 32, 32, 96, 88, 1, 1, 3),
     (48, 16, 32, 32, 17, 19, 3, 2, 2),
