@@ -76,8 +76,10 @@ static grim_status launch_conv_wide_form(const WideParams &p, size_t lds, int64_
 
 template <bool BF16, int BR, int NT>
 static grim_status launch_conv_wide_inst(const WideParams &p, size_t lds, int64_t nwg, hipStream_t stream) {
-    return p.tap_ways ? launch_conv_wide_form<BF16, BR, NT, kConvByTap>(p, lds, nwg, stream)
-                      : launch_conv_wide_form<BF16, BR, NT, kConvAnyTap>(p, lds, nwg, stream);
+    if constexpr (BR * NT > 32) {                // (not the narrow tiles of a rest: conv_tap_ways)
+        if (p.tap_ways) return launch_conv_wide_form<BF16, BR, NT, kConvByTap>(p, lds, nwg, stream);
+    }
+    return launch_conv_wide_form<BF16, BR, NT, kConvAnyTap>(p, lds, nwg, stream);
 }
 
 // The wide-tile workgroups and, behind them in the same launch, the workgroups of the row-gathering convolution (its

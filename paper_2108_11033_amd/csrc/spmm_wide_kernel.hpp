@@ -5,6 +5,7 @@
 #pragma once
 #include <algorithm>
 
+#include "conv_taps.hpp"
 #include "spmm_common.hpp"
 
 namespace grim {
@@ -50,9 +51,7 @@ struct __attribute__((packed, aligned(2))) WideWindow {
 };
 
 constexpr int kWideMulWaves = 8;     // multiplying waves, two strips each
-constexpr int kWideFetchWaves = 4;   // fetching waves
 constexpr int kWideThreads = (kWideMulWaves + kWideFetchWaves) * 64;
-constexpr int kWideFetchThreads = kWideFetchWaves * 64;
 constexpr int kWideStrips = 2 * kWideMulWaves;   // strips per workgroup
 // 16-byte record units per fetching thread and chunk: 8 = 32 KB per (chunk, group), the layout's limit; the
 // 192-column shape, whose rows of X take more registers, has room for 4 (16 KB)
@@ -74,19 +73,12 @@ __host__ __device__ inline int wide_stage_bytes(int chunk_rows, int tn, int amax
 //   kConvAnyTap: 16-byte units in order; the row's channel and tap and the unit's validity mask come out of tables in LDS.
 //   kConvByTap:  a thread keeps one (tap, piece of the tile) and takes every tap_ways-th channel: the mask is four registers,
 //                a row's address one addition.  Taken where there is a thread for every (tap, piece) and the rows of a chunk
-//                are at most kTapUnits per thread (see conv_tap_ways); 5 x 5 kernels have more of them than there are threads.
+//                are at most wide_tap_units per thread (conv_tap_ways, conv_taps.hpp); 5 x 5 kernels have more of them than there are
+//                threads.
 // 512 channels, 3 x 3, eight 56 x 56 maps, 32-row blocks of mixed rates 94 -> 78.5 us; 256 channels, 3 x 3, four 112 x 112 maps, 16-row
 // blocks 80 -> 67.5; 1 x 1, 512 -> 256 channels on three 112 x 112 maps 35.6 -> 30.6 (graphs of one call): two dependent LDS reads
 // and a table-driven address per unit are gone, a fetching wave's instructions per unit from about 35 to 12.
 constexpr int kConvNone = 0, kConvAnyTap = 1, kConvByTap = 2;
-constexpr int wide_tap_units(int tn) { return tn == 96 ? 11 : tn == 32 ? 8 : 15; }
-
-// Fetching threads per (tap, piece) of the form that keeps them apart; 0: that form does not apply
-constexpr int conv_tap_ways(int tn, int KK, int chunk_rows) {
-    const int pairs = KK * (tn / 8);
-    const int ways = pairs <= kWideFetchThreads ? kWideFetchThreads / pairs : 0;
-    return ways > 0 && ((chunk_rows + KK - 1) / KK + ways - 1) / ways <= wide_tap_units(tn) ? ways : 0;
-}
 
 // third dword of a raw buffer descriptor on this GPU family (32-bit data format); only the range check matters here
 constexpr unsigned int kBufferFlags = 0x00020000u;

@@ -103,6 +103,19 @@ def test_patch_convolution_workgroups_of_eight_waves_have_a_compute_unit_each(tm
     assert seen == {(8, True), (4, True), (4, False)}
 
 
+def test_wide_convolution_rows_dealt_by_tap(tmp_path):
+    """Every row and piece of a chunk has one fetching thread, whichever tap the chunk begins with; the narrow tiles of a rest, which
+    are slower that way, keep the tables."""
+    faults = _host_library(tmp_path, "conv_taps").conv_tap_faults
+    for tn in (32, 96, 128, 192):
+        for KK in (1, 3, 5, 9, 15, 21, 25, 49):
+            for rows in (32, 64, 96, 128, 160, 192):
+                n = faults(tn, KK, rows)
+                assert n == (-1 if tn == 32 or KK * tn // 8 > 256 else n), (tn, KK, rows)
+                assert n <= 0, (n, tn, KK, rows)
+    assert faults(96, 9, 192) == faults(192, 9, 128) == faults(128, 1, 192) == 0
+
+
 def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
     """Workgroups of a sequence call wait for one another: placing its sets on XCDs must not put more of them on any XCD than
     the plain order does, or calls on several streams could each hold a part of one XCD and wait for the rest."""
