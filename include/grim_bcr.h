@@ -260,9 +260,12 @@ grim_status grim_bcr_conv2d_act(const grim_bcr_matrix *A, const void *F_dev, int
  *                               kh, kw odd, padding kh / 2, kw / 2; stride 1 or 2 in both directions; the output
  *                               map is Ho x Wo = ceil(H / stride) x ceil(W / stride).  Allocates the plan's words
  *                               (4 bytes per kept im2col row, padded) on the device and, where 64-row runs pay for some
- *                               batch, a second copy of the weights in that layout, or a dense one (2 bytes per entry of
- *                               the filter matrix, kept or not; done without if there is no memory).  Errors: NULL, SHAPE, DEVICE,
- *                               ALLOC, UNSUPPORTED (as grim_bcr_conv2d).
+ *                               batch (at stride 1: of more than one image), a second copy of the weights in that layout,
+ *                               or a dense one, kept or not: 4 KB per 64 rows and 32 places, one for each channel of a
+ *                               chunk of 8, 16 or 32 and each tap, filled up to whole chunks and whole 32s (3 x 3 in chunks
+ *                               of 8: 12 taps); at most 256 MB.  4.7 MB for 512 channels, 3 x 3.  A plan holds them
+ *                               whichever batches it is called with (it does without if there is no memory).
+ *                               Errors: NULL, SHAPE, DEVICE, ALLOC, UNSUPPORTED (as grim_bcr_conv2d).
  *   grim_bcr_conv2d_plan        F_dev: batch images [Cin][H][W] of A's element type, image b at F_dev +
  *                               b * f_image_stride elements; out_dev: batch outputs [M][ldo] (ldo >= Ho * Wo) of
  *                               element type out_dt, image b at out_dev + b * out_image_stride elements, overwritten
