@@ -687,24 +687,27 @@ def test_conv_plan_runs_of_64_rows(dtype, M, BR, BC, H, W, kh, kw, stride, B, pa
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [gen.F16, gen.BF16])
-@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,kw,stride,B,pad", [
-    (256, 4, 16, 256, 28, 28, 3, 3, 1, 4, 0),    # eight waves, a chunk of 32 channels each
-    (256, 4, 16, 128, 28, 28, 3, 3, 1, 8, 1),    # four waves; chunks of 16; every second image at an odd element
-    (208, 4, 4, 68, 31, 33, 5, 5, 1, 14, 3),     # a last run of 16 rows; channels that fill no chunk; odd maps, odd strides
-    (128, 4, 16, 272, 57, 31, 3, 3, 2, 6, 0),    # stride 2 of odd maps: the last column and row are outputs
-    (512, 4, 4, 36, 9, 9, 5, 5, 2, 96, 1),       # one partly filled tile of 25 positions per image
-    (512, 4, 4, 64, 3, 3, 3, 3, 1, 96, 0),       # nine pixels: two loads per channel that overlap
-    (512, 4, 4, 64, 2, 131, 3, 3, 2, 48, 1),     # rows of 66 outputs: a tile ends in the row it starts in
-    (192, 4, 4, 192, 17, 150, 1, 5, 1, 8, 0),    # flat and tall kernels
-    (192, 4, 16, 192, 17, 150, 1, 5, 2, 24, 0),
-    (192, 4, 16, 64, 40, 30, 7, 3, 1, 8, 1),
-    (256, 4, 4, 64, 6, 200, 5, 5, 1, 8, 0),      # a tile's pixels and their neighbours in the rows next to it: 868
-    (64, 4, 16, 192, 56, 56, 3, 3, 1, 4, 0),     # one 64-row run, 196 tiles
-    (256, 8, 16, 64, 33, 47, 3, 3, 2, 6, 1),     # stride 2, rows of 24 outputs
-    (96, 4, 16, 64, 70, 75, 3, 3, 1, 2, 3),      # a second 64-row run of 32 rows; odd sizes and strides
-    (96, 4, 16, 64, 41, 39, 3, 3, 1, 5, 3),      # a last tile of 63 positions in each image
+@pytest.mark.parametrize("M,BR,BC,cin,H,W,kh,kw,stride,B,pad,dense", [
+    (256, 4, 16, 256, 28, 28, 3, 3, 1, 4, 0, True),   # eight waves, a chunk of 32 channels each
+    (256, 4, 16, 128, 28, 28, 3, 3, 1, 8, 1, True),   # four waves; chunks of 16; every second image at an odd element
+    (208, 4, 4, 68, 31, 33, 5, 5, 1, 14, 3, True),    # a last run of 16 rows; channels that fill no chunk; odd maps, odd strides
+    (128, 4, 16, 272, 57, 31, 3, 3, 2, 6, 0, True),   # stride 2 of odd maps: the last column and row are outputs
+    (512, 4, 4, 36, 9, 9, 5, 5, 2, 96, 1, True),      # one partly filled tile of 25 positions per image
+    (512, 4, 4, 64, 3, 3, 3, 3, 1, 96, 0, True),      # nine pixels: two loads per channel that overlap
+    (512, 4, 4, 64, 2, 131, 3, 3, 2, 48, 1, True),    # rows of 66 outputs: a tile ends in the row it starts in
+    (192, 4, 4, 192, 17, 150, 1, 5, 1, 8, 0, True),   # flat and tall kernels
+    (192, 4, 16, 192, 17, 150, 1, 5, 2, 24, 0, True),
+    (192, 4, 16, 64, 40, 30, 7, 3, 1, 8, 1, True),
+    (256, 4, 4, 64, 6, 200, 5, 5, 1, 8, 0, True),     # a tile's pixels and their neighbours in the rows next to it: 868
+    (64, 4, 16, 192, 56, 56, 3, 3, 1, 4, 0, True),    # one 64-row run, 196 tiles
+    (256, 8, 16, 64, 33, 47, 3, 3, 2, 6, 1, True),    # stride 2, rows of 24 outputs
+    (96, 4, 16, 64, 70, 75, 3, 3, 1, 2, 3, True),     # a second 64-row run of 32 rows; odd sizes and strides
+    (96, 4, 16, 64, 41, 39, 3, 3, 1, 5, 3, True),     # a last tile of 63 positions in each image
+    (144, 4, 4, 68, 31, 33, 3, 3, 1, 14, 3, False),   # layers that are quicker without it
+    (192, 4, 16, 64, 17, 150, 1, 5, 1, 8, 0, False),
+    (128, 4, 16, 64, 6, 440, 3, 3, 1, 8, 0, False),
 ])
-def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pad):
+def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pad, dense):
     """Layers of many steps per 64-row run and many tiles, as the plan's dense copy of the weights takes them."""
     import paper_2108_11033_amd as g
     from helpers import pack_workload, TOL
@@ -717,7 +720,7 @@ def test_conv_plan_dense_copy(dtype, M, BR, BC, cin, H, W, kh, kw, stride, B, pa
     Yref = conv_ref.conv2d(Wm, F64, kh, kw, stride) + bias[None, :, None, None]
     S = conv_ref.conv2d(np.abs(Wm), np.abs(F64), kh, kw, stride) + np.abs(bias)[None, :, None, None]
     A = pack_workload(g, Wt, dtype, mask)
-    assert g.conv2d_kernel_name(A, cin, H, W, kh, kw, B, stride) == "bcr_conv_patch"
+    assert (g.conv2d_kernel_name(A, cin, H, W, kh, kw, B, stride) == "bcr_conv_patch") == dense
     Y = _run_plan(g, A, F, dtype, M, kh, kw, stride, bias=bias, pad=pad)
     assert np.isfinite(Y).all()
     assert (np.abs(Y - Yref) / S).max() <= TOL[dtype]
