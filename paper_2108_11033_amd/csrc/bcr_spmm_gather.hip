@@ -212,7 +212,7 @@ grim_status launch_spmm_gather_many(const grim_bcr_group *G, const void *X, int6
     const int64_t pairs = (int64_t)G->count * G->gather_runs;
     const bool solo = pairs >= 3072 || (pairs >= 2048 && G->gather_steps <= 12 * pairs);
     int64_t nwg = 0;
-    p.map = xcd_map(1, solo ? (G->gather_runs + 3) / 4 : G->gather_runs, &nwg);
+    p.map = xcd_map_one_tile(solo ? (G->gather_runs + 3) / 4 : G->gather_runs, &nwg);
     if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
     const dim3 grid((unsigned)nwg, (unsigned)G->count);
     const size_t lds = 4 * gather_wave_lds(1);

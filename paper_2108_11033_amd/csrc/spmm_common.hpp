@@ -83,20 +83,5 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, unsigned int n) {
 // kernel (3 steps per batch) 11.0 us with 8, 8.6 us with 12 -- every wave then needs one batch only --, 9.7 us with 16.
 constexpr int kGatherLongWaves = 8, kGatherSmallTileWaves = 12;
 
-// false: the workgroup has no tile
-__device__ __forceinline__ bool xcd_map_at(const XcdMap &m, int id, int ntiles, int *tile, int *unit) {
-    const int xcd = id & 7, slot = id >> 3;
-    if (slot < m.tail_slot0) {
-        *tile = (slot / m.per_tile) * 8 + xcd;
-        *unit = slot % m.per_tile;
-        return true;
-    }
-    const int s2 = slot - m.tail_slot0;
-    const int part = (s2 / m.per_part) * 8 + xcd;
-    *tile = m.tail_tile0 + (part >> m.shift);
-    *unit = ((s2 % m.per_part) << m.shift) + (part & ((1 << m.shift) - 1));
-    return *tile < ntiles;
-}
-
 
 }  // namespace grim

@@ -1,6 +1,8 @@
-// How the workgroups of a launch are dealt to the XCDs (the device's half, xcd_map_at, is in spmm_common.hpp).
+// How the workgroups of a launch are dealt to the XCDs.
 #pragma once
 #include <cstdint>
+
+#include "host_device.hpp"
 
 namespace grim {
 
@@ -26,6 +28,31 @@ inline XcdMap xcd_map(int32_t ntiles, int64_t per_tile, int64_t *nwg) {
     m.per_part = (int32_t)((per_tile + (1 << m.shift) - 1) >> m.shift);
     *nwg = 8 * (full * per_tile + (int64_t)((r << m.shift) / 8) * m.per_part);
     return m;
+}
+
+// The same for a launch of many matrices of one tile each (grid.x workgroups to a matrix, grid.y matrices): a workgroup's unit is its
+// id, and no id is added, so that ids running on over the matrices are dealt to the XCDs evenly.  With grid.x filled up to a
+// multiple of 8 each matrix would begin on the first XCD again, and matrices of two units would run on two XCDs (236 of 32 x 1824 of
+// mixed rates at 6 columns 10.1 us, 4.3 this way; 225 of 32 x 3936 at one 12.9, 5.0; 211 of 64 x 1440 keeping 10 x 10 at 5 9.1, 6.2).
+inline XcdMap xcd_map_one_tile(int64_t units, int64_t *nwg) {
+    const XcdMap m = xcd_map(1, units, nwg);
+    *nwg = units;
+    return m;
+}
+
+// false: the workgroup has no tile
+GRIM_HOST_DEVICE bool xcd_map_at(const XcdMap &m, int id, int ntiles, int *tile, int *unit) {
+    const int xcd = id & 7, slot = id >> 3;
+    if (slot < m.tail_slot0) {
+        *tile = (slot / m.per_tile) * 8 + xcd;
+        *unit = slot % m.per_tile;
+        return true;
+    }
+    const int s2 = slot - m.tail_slot0;
+    const int part = (s2 / m.per_part) * 8 + xcd;
+    *tile = m.tail_tile0 + (part >> m.shift);
+    *unit = ((s2 % m.per_part) << m.shift) + (part & ((1 << m.shift) - 1));
+    return *tile < ntiles;
 }
 
 }  // namespace grim

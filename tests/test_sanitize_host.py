@@ -116,6 +116,14 @@ def test_wide_convolution_rows_dealt_by_tap(tmp_path):
     assert faults(96, 9, 192) == faults(192, 9, 128) == faults(128, 1, 192) == 0
 
 
+def test_groups_of_small_matrices_are_dealt_to_all_xcds(tmp_path):
+    """Every unit of every matrix of a group has one workgroup, and no XCD has more of them than its share."""
+    excess = _host_library(tmp_path, "group_map").group_map_excess
+    for units in list(range(1, 40)) + [63, 64, 65, 128, 234]:
+        for count in (1, 2, 3, 7, 8, 100, 211):
+            assert excess(units, count) == 0, (units, count)
+
+
 def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
     """Workgroups of a sequence call wait for one another: placing its sets on XCDs must not put more of them on any XCD than
     the plain order does, or calls on several streams could each hold a part of one XCD and wait for the rest."""
