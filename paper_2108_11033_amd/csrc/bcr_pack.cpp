@@ -12,6 +12,7 @@
 
 #include "bcr_matrix.hpp"
 #include "conv_patch.hpp"
+#include "group_rules.hpp"
 
 using namespace grim;
 
@@ -1826,11 +1827,8 @@ grim_status grim_bcr_group_create(const grim_bcr_matrix *const *mats, int32_t co
 static bool group_on_matrix_cores(const grim_bcr_group *G, int32_t batch) {
     if (!G->d_gather || G->BR < 8) return false;
     if (batch == 1) return !spmv_exact_applies(G->dtype, G->uniform_kr, G->uniform_kc, G->K);
-    // Uniform blocks, up to 2048 (matrix, run) pairs: 16 of 2048 x 1024 keeping 8 x 8 at 2 / 4 / 8 columns 5.9 / 7.4 / 9.2 -> 5.2 /
-    // 4.9 / 5.0 us, 32 of 1024 x 512 in 8 x 32 blocks 6.0 / 7.6 / 11.3 -> 5.1 / 5.1 / 4.9.  With 4096 pairs 64 of 1024 x 1024 at
-    // 2 6.9 us, 9.2 there; 32 of 2048 x 2048 in 16 x 32 blocks at 2 / 4 / 8 9.4 / 13.4 / 17.1, 16.1 / 16.2 / 16.8 there.
     if (spmv_many_strips_applies(G->count, G->nbr, G->dtype, G->uniform_kr, G->uniform_kc, G->K, G->BC, batch))
-        return (int64_t)G->count * G->gather_runs <= 2048;
+        return group_quicker_on_matrix_cores(G->count, G->nbr, G->nbc, G->uniform_kr, G->uniform_kc, G->K, G->gather_runs, G->gather_steps, batch);
     // (columns as sets of workgroups: the bits of a call for one matrix, which takes that form too)
     if (spmv_column_sets_ok(G->count, G->nbr, batch) && spmv_exact_applies(G->dtype, G->uniform_kr, G->uniform_kc, G->K)) return false;
     return true;

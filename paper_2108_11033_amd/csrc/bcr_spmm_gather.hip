@@ -1,6 +1,7 @@
 #include <algorithm>
 
 #include "conv_rules.hpp"
+#include "group_rules.hpp"
 #include "spmm_gather_kernel.hpp"
 
 namespace grim {
@@ -205,12 +206,7 @@ grim_status launch_spmm_gather_many(const grim_bcr_group *G, const void *X, int6
     p.ntiles = 1;
     p.K = (int32_t)G->K;
     p.exact.BR = G->BR; p.exact.BC = G->BC; p.exact.nbc = (int32_t)G->nbc;
-    // Enough (matrix, run) pairs to fill the GPU with a wave each: no split of a run over waves, no partial tiles.  Four waves to a
-    // run / a wave (16 bytes of a row): 64 of 2048 x 2048 of mixed rates at 8 columns 29.3 / 26.8 us, 43 of 3872 x 1248 at one 34.9 / 30.3, 32 of 1024
-    // x 512 in 8 x 32 blocks (2048 pairs of 7 steps) at 4 5.4 / 5.1; 39 of 960 x 1632 (2340 of 16 steps) 9.0 / 10.1, 12 of 2048 x
-    // 512 (1536) 6.3 / 6.4, 8 of 736 x 1440 (368) 5.2 / 7.5.
-    const int64_t pairs = (int64_t)G->count * G->gather_runs;
-    const bool solo = pairs >= 3072 || (pairs >= 2048 && G->gather_steps <= 12 * pairs);
+    const bool solo = group_run_to_a_wave((int64_t)G->count * G->gather_runs, G->gather_steps);
     int64_t nwg = 0;
     p.map = xcd_map_one_tile(solo ? (G->gather_runs + 3) / 4 : G->gather_runs, &nwg);
     if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;

@@ -124,6 +124,23 @@ def test_groups_of_small_matrices_are_dealt_to_all_xcds(tmp_path):
             assert excess(units, count) == 0, (units, count)
 
 
+def test_uniform_groups_run_on_the_matrix_cores_where_they_are_quicker(tmp_path):
+    on_cores = _host_library(tmp_path, "group_map").group_on_matrix_cores
+    for (count, M, K, BR, BC, kr, kc, kept, batch), quicker in (
+            # microseconds wave per strip, on the matrix cores
+            ((16, 1824, 1696, 16, 32, 4, 12, 12, 2), False),      # 6.0, 8.5
+            ((33, 896, 1632, 16, 32, 4, 12, 12, 2), False),       # 5.9, 8.6
+            ((8, 3744, 1376, 8, 32, 4, 8, 14, 3), False),         # 7.3, 10.4
+            ((199, 128, 1504, 16, 32, 4, 12, 12, 8), False),      # 7.9, 11.5
+            ((226, 128, 1952, 16, 32, 4, 12, 12, 5), False),      # 8.4, 13.4
+            ((9, 2880, 1888, 8, 32, 4, 8, 14, 2), False),         # 7.0, 10.1
+            ((16, 2048, 1024, 32, 32, 8, 8, 8, 2), True),         # 5.9, 4.4
+            ((16, 2048, 1024, 32, 32, 8, 8, 8, 8), True),         # 9.0, 4.9
+            ((32, 1024, 512, 8, 32, 4, 8, 14, 2), True),          # 6.0, 4.5
+            ((64, 1024, 1024, 32, 32, 8, 8, 8, 2), False)):       # 6.9, 9.2: 4096 pairs
+        assert on_cores(count, M, K, BR, BC, kr, kc, kept, batch) == quicker, (count, M, K, BR, BC, kr, kc, batch)
+
+
 def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
     """Workgroups of a sequence call wait for one another: placing its sets on XCDs must not put more of them on any XCD than
     the plain order does, or calls on several streams could each hold a part of one XCD and wait for the rest."""
