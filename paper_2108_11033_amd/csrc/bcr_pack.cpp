@@ -1822,8 +1822,8 @@ grim_status grim_bcr_group_create(const grim_bcr_matrix *const *mats, int32_t co
 
 // Groups the wave-per-strip SpMV kernels are not compiled for, and small launches of those for several columns, on the matrix
 // cores (16-bit types, one padded 16-column tile per run of 16 rows).  Before -> there: 64 of 2048 x 2048 of mixed rates at 1 / 8
-// columns 53.7 / 168 -> 24.4 / 26.8 us; 39 of 960 x 1632 keeping 10 x 10 at 8 25.4 -> 9.0; 12 of 2048 x 512 in 8 x 32 blocks of
-// mixed rates at 1 / 8 15.7 / 34.4 -> 5.3 / 5.3; 20 of 2048 x 4096 keeping 8 x 12 at 4 27.7 -> 19.6.
+// columns 54.3 / 168 -> 24.6 / 28.3 us; 39 of 960 x 1632 keeping 10 x 10 at 8 25.5 -> 9.2; 12 of 2048 x 512 in 8 x 32 blocks of
+// mixed rates at 1 / 8 15.8 / 34.5 -> 4.9 / 5.3; 20 of 2048 x 4096 keeping 8 x 12 at 4 27.2 -> 19.0.
 static bool group_on_matrix_cores(const grim_bcr_group *G, int32_t batch) {
     if (!G->d_gather || G->BR < 8) return false;
     if (batch == 1) return !spmv_exact_applies(G->dtype, G->uniform_kr, G->uniform_kc, G->K);

@@ -75,7 +75,7 @@ __host__ __device__ inline int wide_stage_bytes(int chunk_rows, int tn, int amax
 //                a row's address one addition.  Taken where there is a thread for every (tap, piece) and the rows of a chunk
 //                are at most wide_tap_units per thread (conv_tap_ways, conv_taps.hpp); 5 x 5 kernels have more of them than there are
 //                threads.
-// 512 channels, 3 x 3, eight 56 x 56 maps, 32-row blocks of mixed rates 94 -> 78.5 us; 256 channels, 3 x 3, four 112 x 112 maps, 16-row
+// 512 channels, 3 x 3, eight 56 x 56 maps, 32-row blocks of mixed rates 88 -> 74 us; 256 channels, 3 x 3, four 112 x 112 maps, 16-row
 // blocks 80 -> 67.5; 1 x 1, 512 -> 256 channels on three 112 x 112 maps 35.6 -> 30.6 (graphs of one call): two dependent LDS reads
 // and a table-driven address per unit are gone, a fetching wave's instructions per unit from about 35 to 12.
 constexpr int kConvNone = 0, kConvAnyTap = 1, kConvByTap = 2;
@@ -658,7 +658,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     // CONV: the layer's epilogue (bias, rectifier, rounding to the next layer's element type); column n is position
     // n % HW of image n / HW, whose [M][ldy] output starts y_img_stride elements after the previous image's.  The output
     // type is chosen once and a strip's biases are fetched before its first store: stores and loads share a counter, so a
-    // bias fetched between two stores is waited for behind the stores (512 channels, 3 x 3, eight 56 x 56 maps: 112 -> 94 us; 1 x 1, 512 -> 256
+    // bias fetched between two stores is waited for behind the stores (512 channels, 3 x 3, eight 56 x 56 maps: 107 -> 88 us; 1 x 1, 512 -> 256
     // channels on five 112 x 112 maps in 16-row blocks, whose four 16-bit outputs of a row are one store: 69 -> 44).
     auto finish = [&](auto out_type) {
         constexpr int ODT = decltype(out_type)::value;
