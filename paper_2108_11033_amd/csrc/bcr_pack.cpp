@@ -11,7 +11,7 @@
 #include <system_error>
 
 #include "bcr_matrix.hpp"
-#include "conv_patch.hpp"
+#include "conv_rules.hpp"
 #include "group_rules.hpp"
 
 using namespace grim;
@@ -1217,16 +1217,20 @@ static bool conv_on_tall_runs(const grim_bcr_matrix *A, const RunSteps &tall, in
 // unit; a last round that is at most half full counts 0.7):
 //   dense    0.38 per step of a wave, 0.72 or 0.66 per 64 tasks (pixels of a chunk) of a wave, 2.6 or 5 per workgroup, 3.5 per launch
 //   64-row   1.07 or 1.03 per step of a wave (1.44 times that at stride 2), 4 or 5.35 per workgroup, 3.2 per launch
-//   16-row   0.107 per step of a strip and 0.45 per strip (1.3 times that at stride 2) in rounds of 256, 5.7 per launch
-// Fitted to 518 layers of 32 to 512 channels, 3 x 3 and 5 x 5, on 2 to 32 maps of 7 x 7 to 64 x 64, each run with and without the dense
-// copy; the estimates lie within 12 % (rms).  The dense copy has to be estimated 2 % ahead.  Of 718 layers, 200 of them not in the
-// fit, 341 get it, 15 of which lose 3 % or more, the worst 15 (steps of 64-row runs against those of 16-row runs alone: 385, of
-// which 52 lost, the worst 37 %); in all 16.85 ms without, 14.16 with this rule, 14.07 with the quicker one each time.
+//   16-row   0.107 per step of a strip and 0.45 per strip (1.3 times that at stride 2) in rounds of 256, 5.7 per launch; a strip to a
+//            wave 0.105 and 0.16, 9.3 per launch; four waves to a strip at stride 2 0.13 and 0.18; 32-position tiles, all of them at
+//            once, 0.066 per step of the longest strip, 5.7 per launch
+// Fitted to 518 layers of 32 to 512 channels, 3 x 3 and 5 x 5, on 2 to 32 maps of 7 x 7 to 64 x 64, the last three forms to 1667 of
+// 3845 more on 1 to 24 maps of 5 x 5 to 112 x 112, each run with and without the dense copy; the estimates lie within 12 % (rms).  The
+// dense copy has to be estimated 2 % ahead.  Of the 3845 layers 1594 get it, 32 of which lose 3 % or more, the worst 15 (with one form
+// of 16-row runs 1728 and 140, the worst 65: small maps at stride 2 on 32-position tiles); in all 79.4 ms without, 67.3 with this
+// rule, 66.5 with the quicker one each time.
 // Without -> on the dense copy: 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 / 16 x 32 / mixed 32 x 32 blocks 16.5 / 13.7 / 11.9
 // -> 11.2 / 11.2 / 11.1 us; 448 from seven 103 x 24 maps at stride 2 in 4 x 16 / 16 x 32 blocks 119 / 82 -> 36 / 36; 512 on eight
 // 14 x 14 19.3 -> 17.4; 5 x 5, 192 on four 18 x 18 maps in 32 x 32 blocks 20.4 -> 18.9.  Not taken: 224 -> 160 on eight 47 x 47 maps in
 // mixed 32 x 32 blocks 29.0 -> 39.9; 288 -> 224 on 26 of 17 x 17 in 16 x 32 blocks 25.2 -> 34.4; 160 -> 192 from five 56 x 56 at stride 2
-// 11.0 -> 13.2; 320 -> 384 on five 35 x 35 31.6 -> 38.7.
+// 11.0 -> 13.2; 320 -> 384 on five 35 x 35 31.6 -> 38.7; 320 -> 224 from seven 8 x 8 at stride 2 in 4 x 16 blocks 8.9 -> 12.7; 384 on four 68 x 68
+// 74.7 -> 86.
 constexpr int64_t kConvWholeRounds = 8;          // rounds of workgroups that are counted whole
 
 static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, int32_t H, int32_t W, int32_t kh, int32_t kw, int32_t stride, int32_t batch) {
@@ -1260,8 +1264,14 @@ static bool conv_on_dense_copy(const grim_bcr_matrix *A, const RunSteps &tall, i
         without = 3.2 + (pairs <= 256 ? rounds(pairs, launched, 256) * (4.0 + 1.07 * step / 8.0) : rounds(pairs, launched, 512) * (5.35 + 1.03 * step / 4.0));
     } else {
         const int64_t pairs = row_tiles * A->gather.nstrips;
+        const int nt = conv_subtiles(A, stride == 2 ? Ho * ((Wo + 7) / 8 * 8) : Ho * Wo, batch, stride, true);
+        const int strip_waves = conv_strip_waves(A, nt, pairs, stride);
         const double turns = pairs <= 1024 ? (double)((pairs + 255) / 256) : (double)pairs / 256.0;
-        without = 5.7 + 0.107 * turns * ((double)A->gather.nsteps / (double)A->gather.nstrips + 4.2) * (stride == 2 ? 1.3 : 1.0);
+        const double strip = (double)A->gather.nsteps / (double)A->gather.nstrips;
+        if (nt == 2) without = 5.67 + 0.066 * (double)A->gather.max_steps;
+        else if (stride == 1 && strip_waves == 1) without = 9.27 + turns * (0.105 * strip + 0.16);
+        else if (stride == 2 && strip_waves == 4) without = 5.7 + turns * (0.1315 * strip + 0.18);
+        else without = 5.7 + 0.107 * turns * (strip + 4.2) * (stride == 2 ? 1.3 : 1.0);
     }
     return dense * 1.02 <= without;
 }

@@ -111,6 +111,10 @@ MIXED_32 = ((4, 8, 16), (4, 8, 16))
     (320, 384, 35, 35, 3, 1, 5, 16, 32, (8, 8), False),          # 31.6, 38.7
     (320, 64, 51, 41, 3, 1, 3, 8, 16, (4, 4), False),            # 14.3, 17.4
     (128, 288, 59, 59, 3, 2, 3, 32, 32, MIXED_32, False),        # 10.5, 12.2
+    (320, 224, 8, 8, 3, 2, 7, 4, 16, (2, 4), False),             # 8.9, 12.7: 32-position tiles
+    (256, 128, 10, 10, 3, 2, 4, 16, 16, (4, 8), False),          # 7.6, 9.5
+    (128, 128, 35, 8, 5, 2, 4, 4, 16, (2, 4), False),            # 9.3, 13.0
+    (384, 384, 68, 68, 3, 1, 4, 16, 32, (8, 8), False),          # 74.7, 86.4: a strip to a wave
     (256, 256, 28, 28, 3, 1, 4, 16, 32, (8, 8), True),           # 13.7, 11.2
     (448, 448, 103, 24, 3, 2, 7, 16, 32, (8, 8), True),          # 82.1, 36.1
     (512, 512, 14, 14, 3, 1, 8, 16, 32, (8, 8), True),           # 19.3, 17.4
@@ -124,11 +128,11 @@ def test_the_dense_copy_is_taken_where_it_is_quicker(rules, cin, M, H, W, k, str
 
 
 @pytest.mark.parametrize("cin,M,H,W,stride,BR,BC,keep,kernel,batch", [
-    (64, 128, 13, 13, 1, 32, 32, MIXED_32, "bcr_conv_patch", 71),        # to 84
+    (64, 224, 7, 7, 1, 32, 32, (8, 8), "bcr_conv_patch", 83),            # to 128
     (32, 64, 46, 11, 2, 16, 32, (8, 8), "bcr_conv_patch", 77),           # to 85
     (64, 256, 16, 4, 2, 32, 32, MIXED_32, "bcr_conv_tall", 65),          # to 128; on the dense copy before and after
     (64, 256, 4, 35, 2, 32, 32, (8, 8), "bcr_conv_tall", 65),            # and all larger ones
-    (128, 224, 5, 5, 1, 16, 32, (8, 8), "bcr_conv_patch", 512),
+    (192, 64, 9, 9, 2, 32, 32, MIXED_32, "bcr_conv_patch", 129),
 ])
 def test_a_plan_holds_the_layouts_of_batches_above_64(rules, cin, M, H, W, stride, BR, BC, keep, kernel, batch):
     """A few batches, or all from some number on, run on a layout that smaller ones do not use."""
