@@ -73,6 +73,18 @@ constexpr int kSeqXVec = 4;   // 16-byte pieces of a step's inputs a thread fetc
 constexpr int kSeqPolls = 2;    // reads of an exchange word a waiting workgroup sends out at once ...
 constexpr int kSeqPollGap = 8;  // ... this many times 64 cycles apart (2 x 8, 3 x 5 .. 12, 4 x 4 measured: LSTM alike, the GRU best with two)
 
+// Words between workgroups of one XCD.  A store of agent scope is carried through to memory and seen by the other workgroups
+// of its own XCD, too, only after that round trip; a store of workgroup scope stays in the XCD's L2, which is where the loads of
+// agent scope (past the vector L1) of all its workgroups look: an exchange of 1024 words among 32 workgroups takes 0.61 us a
+// round instead of 1.09.  Where a workgroup runs is read from the hardware and not assumed: the words of the first step, stored
+// at agent scope, carry their writer's XCD in the top bits of the tag, and a workgroup that has seen its own in all of
+// them stores its later words so.  (The numbers agree for all of a set or for none: every workgroup compares the same words.)
+constexpr int kSeqTagShift = 28;                                  // (XCD numbers have four bits)
+constexpr unsigned int kSeqTagBits = (1u << kSeqTagShift) - 1u;
+__device__ __forceinline__ unsigned int seq_xcd() {
+    return (unsigned int)__builtin_amdgcn_s_getreg(20 | 31 << 11) & 15u;    // the whole of hardware register 20, XCC_ID
+}
+
 // MULTI: a workgroup carries more than one sequence.  PLACED: every set of workgroups on an XCD of its own (1-D grid);
 // otherwise grid.y is the set.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
 template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
@@ -106,8 +118,11 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     const int hld = CELL == 2 ? p.K2 : p.K1;                                  // elements from one sequence's h to the next's
     float *part = reinterpret_cast<float *>(smem + xbytes + wave * tbytes);
     float *gl = reinterpret_cast<float *>(smem + xbytes + NWV * tbytes);      // [B][NWV][32]
-    __shared__ int flag_word;
-    volatile int *flag = &flag_word;
+    __shared__ int flag_word, apart_word;
+    volatile int *flag = &flag_word, *apart = &apart_word;
+    // PLACED: the XCD this workgroup runs on, and whether the whole set has been seen to run there (step 1)
+    const unsigned int xcd = PLACED ? seq_xcd() : 0u;
+    bool one_l2 = false;
 
     // this lane's block: weights into registers for the whole sequence
     const GemvGlobal d = to_global(mi ? p.d2 : p.d1);
@@ -144,7 +159,10 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
             if (CELL == 2 && p.bias2) b[3 + k] = p.bias2[k * (int64_t)H + ju];
         }
     }
-    if (tid == 0) *flag = 0;
+    if (tid == 0) {
+        *flag = 0;
+        *apart = 0;
+    }
 
     const int ngrp = p.BR <= 16 ? 4 : 2;
     const int r_out = p.BR <= 16 ? lane & 15 : lane & 31;
@@ -215,6 +233,9 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
             constexpr int NJ = MULTI ? 2 : 1;
             constexpr int NP = MULTI ? 2 : kSeqPolls;               // (several sequences: twice the words per read, fewer registers left)
             bool bad = false;
+            // (the words of the first step carry their writer's XCD above the tag)
+            const unsigned int tag_mask = PLACED && t == 1 ? kSeqTagBits : 0xffffffffu;
+            unsigned int others = 0;
             for (int q0 = 0; q0 < NQ && !bad; q0 += NJ) {
                 for (int base = tid; base < H && !bad; base += 4 * NTHR) {
                     unsigned long long v[NJ * 4], w[NP][NJ * 4];
@@ -235,7 +256,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
 #pragma unroll
                         for (int k = 0; k < NJ * 4; ++k) {
                             const unsigned int tag = (unsigned int)(r[k] >> 32);
-                            if (tag != (unsigned int)t) ok = ok < 0 ? ok : 0;
+                            if ((tag & tag_mask) != (unsigned int)t) ok = ok < 0 ? ok : 0;
                             if (tag == kSeqPoison) ok = -1;
                         }
                         return ok;
@@ -280,6 +301,12 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                         }
                         dead = st_ < 0 || (!ok && ++polls >= p.max_polls);
                     }
+                    if constexpr (PLACED) {
+                        if (t == 1) {
+#pragma unroll
+                            for (int k = 0; k < NJ * 4; ++k) others |= (unsigned int)(v[k] >> 32 >> kSeqTagShift) ^ xcd;
+                        }
+                    }
                     if (!ok) {
                         *flag = 1;
                         bad = true;
@@ -301,8 +328,10 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     }
                 }
             }
+            if (PLACED && others) *apart = 1;
         }
         __syncthreads();
+        if (PLACED && t == 1) one_l2 = *apart == 0;
         if (*flag) {                                                  // the same value for every thread
             gave_up = true;
             break;
@@ -424,8 +453,11 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     if (p.hs32) p.hs32[((int64_t)t * p.B + b0 + bb) * p.ldhs32 + ju] = h;
                 }
             }
-            const unsigned long long word = (unsigned long long)pair | ((unsigned long long)(unsigned int)(t + 1) << 32);
-            __hip_atomic_store(exch + ((size_t)((t + 1) & 1) * NQ + cq) * H + ju, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned int tag = (unsigned int)(t + 1) | (PLACED && t == 0 ? xcd << kSeqTagShift : 0u);
+            const unsigned long long word = (unsigned long long)pair | ((unsigned long long)tag << 32);
+            unsigned long long *to = exch + ((size_t)((t + 1) & 1) * NQ + cq) * H + ju;
+            if (PLACED && one_l2) __hip_atomic_store(to, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            else __hip_atomic_store(to, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 
