@@ -14,13 +14,18 @@
 //      [strip row][block] table in a fixed order, exactly as the one-step kernel does),
 //   3. applies the cell to its BR units and publishes their new h.
 // Workgroups exchange h through a small buffer of 8-byte words (the new h of one hidden unit for two sequences of the
-// batch, already rounded to the element type the next product reads; step tag), two slots used in turn:
+// batch, or of two neighbouring units where a workgroup carries one sequence, already rounded to the element type the
+// next product reads; step tag), two slots used in turn:
 // a producer writes a word with one atomic store, consumers re-read a word until its tag is the step they need.
 // Values and tag travel together, so no fence and no separate counter is needed.  Slot t & 1 can be overwritten with
 // h_{t+2} only by a workgroup that has read all of h_{t+1}, which exists only when every workgroup has finished
 // reading h_t: two slots are enough.  Every wait is bounded: after `max_polls` unsuccessful reads a workgroup gives
 // up, marks its own words as poisoned (which ends every other workgroup's wait at once) and sets *status; all
 // workgroups then leave the kernel normally.
+// A step is a chain of latencies with one wave per SIMD, so what it waits for is kept short: of the 1.9 us a step of eight LSTM
+// sequences of 1024 units took, 0.15 went into a flat load of the flag that says a wait was given up (now read as LDS beside the
+// gather and looked at behind the products), 0.1 into the tags of a complete read (one comparison now), 0.1 into words
+// that held one unit each: 1.68 us now.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,6 +51,7 @@ struct SeqParams {
     int32_t I, H, T;
     int32_t B;                     // sequences side by side (1 .. 32), dealt to grid.y sets of workgroups
     int32_t SPB, NQ;               // sequences per workgroup; pairs of them = exchange words per hidden unit
+    int32_t unit_pairs;            // one sequence per workgroup: an exchange word holds two hidden units
     int32_t xvec16;                // rows of xs can be copied with 16-byte loads
     const void *xs;                // T x B rows of I inputs, row t * B + b
     int64_t ldxs;
@@ -85,6 +91,21 @@ __device__ __forceinline__ unsigned int seq_xcd() {
     return (unsigned int)__builtin_amdgcn_s_getreg(20 | 31 << 11) & 15u;    // the whole of hardware register 20, XCC_ID
 }
 
+// v + v of the lane 32 (16) further round, without a trip through LDS: the swap of a register with a copy of itself leaves
+// the lower halves (even quarters) of v in one and the upper (odd) in the other
+__device__ __forceinline__ float seq_halves(float v) {
+    const unsigned int a = __builtin_bit_cast(unsigned int, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const unsigned int lower = r[0], upper = r[1];
+    return __builtin_bit_cast(float, lower) + __builtin_bit_cast(float, upper);
+}
+__device__ __forceinline__ float seq_quarters(float v) {
+    const unsigned int a = __builtin_bit_cast(unsigned int, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const unsigned int even = r[0], odd = r[1];
+    return __builtin_bit_cast(float, even) + __builtin_bit_cast(float, odd);
+}
+
 // MULTI: a workgroup carries more than one sequence.  PLACED: every set of workgroups on an XCD of its own (1-D grid);
 // otherwise grid.y is the set.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
 template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
@@ -118,8 +139,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     const int hld = CELL == 2 ? p.K2 : p.K1;                                  // elements from one sequence's h to the next's
     float *part = reinterpret_cast<float *>(smem + xbytes + wave * tbytes);
     float *gl = reinterpret_cast<float *>(smem + xbytes + NWV * tbytes);      // [B][NWV][32]
-    __shared__ int flag_word, apart_word;
-    volatile int *flag = &flag_word, *apart = &apart_word;
+    __shared__ int flag, apart;
     // PLACED: the XCD this workgroup runs on, and whether the whole set has been seen to run there (step 1)
     const unsigned int xcd = PLACED ? seq_xcd() : 0u;
     bool one_l2 = false;
@@ -148,6 +168,8 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     const int cq = MULTI ? tid / p.BR : 0, cu = tid - cq * p.BR;
     const bool cell_thread = MULTI ? cq < NQ : tid < p.BR;
     const int64_t ju = (int64_t)unit * p.BR + cu;
+    const int64_t jw = !MULTI && p.unit_pairs ? ju >> 1 : ju;                 // its word, and whether this thread writes it
+    const bool writes = MULTI || !p.unit_pairs || (cu & 1) == 0;
     float st[2] = {0.f, 0.f}, b[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (cell_thread) {
 #pragma unroll
@@ -160,8 +182,8 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
         }
     }
     if (tid == 0) {
-        *flag = 0;
-        *apart = 0;
+        flag = 0;
+        apart = 0;
     }
 
     const int ngrp = p.BR <= 16 ? 4 : 2;
@@ -199,20 +221,31 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     for (int z = lane; z < (p.BR * kPartStride + 3) / 4; z += 64)
         reinterpret_cast<gu32x4 *>(part)[z] = gu32x4{0u, 0u, 0u, 0u};
     bool gave_up = false;
+    // A step's outputs leave the registers when the next step's h has been read, and the next inputs are asked for then:
+    // loads return in order and behind older stores, so either would be waited for with the exchange words.
+    float out32[2] = {0.f, 0.f};
+    unsigned int out16 = 0;
+    auto outputs = [&](int t) {
+        if (cell_thread) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int bb = 2 * cq + k;
+                if (bb < B) {
+                    static_cast<unsigned short *>(p.hs)[((int64_t)t * p.B + b0 + bb) * p.ldhs + ju] = (unsigned short)(out16 >> (16 * k));
+                    if (p.hs32) p.hs32[((int64_t)t * p.B + b0 + bb) * p.ldhs32 + ju] = out32[k];
+                }
+            }
+        }
+    };
     __syncthreads();
 
     for (int t = 0; t < p.T; ++t) {
         // ---- 1. x_t and h_t (the state BEFORE this step: h0, or what step t - 1 published under tag t)
         if (p.xvec16) {
-            // x_t was asked for a step ago; x_{t+1} is asked for now and travels while this step waits for h
-            const int tn = t + 1 < p.T ? t + 1 : t;
-            const GRIM_GLOBAL T *xg = xs0 + (int64_t)tn * p.B * p.ldxs;
+            // x_t was asked for during the products of the step before
 #pragma unroll
             for (int k = 0; k < XV; ++k)
-                if (k * NTHR < nxv) {                                 // the same for all threads
-                    if (tid + k * NTHR < nxv) *reinterpret_cast<gu32x4 *>(xin + xdst[k]) = xr[k];
-                    xr[k] = *reinterpret_cast<const GRIM_GLOBAL gu32x4 *>(xg + xsrc[k]);
-                }
+                if (k * NTHR < nxv && tid + k * NTHR < nxv) *reinterpret_cast<gu32x4 *>(xin + xdst[k]) = xr[k];
         } else {
             for (int bb = 0; bb < B; ++bb) {
                 const GRIM_GLOBAL T *xg = xs0 + ((int64_t)t * p.B + bb) * p.ldxs;
@@ -232,34 +265,36 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
             const unsigned long long *ex = exch + (size_t)(t & 1) * NQ * H;
             constexpr int NJ = MULTI ? 2 : 1;
             constexpr int NP = MULTI ? 2 : kSeqPolls;               // (several sequences: twice the words per read, fewer registers left)
-            bool bad = false;
             // (the words of the first step carry their writer's XCD above the tag)
             const unsigned int tag_mask = PLACED && t == 1 ? kSeqTagBits : 0xffffffffu;
             unsigned int others = 0;
-            for (int q0 = 0; q0 < NQ && !bad; q0 += NJ) {
-                for (int base = tid; base < H && !bad; base += 4 * NTHR) {
-                    unsigned long long v[NJ * 4], w[NP][NJ * 4];
-                    auto ask = [&](unsigned long long (&r)[NJ * 4]) {
+            // the words of NJ pairs of sequences (of one sequence: a word is one hidden unit, or two of them), NI per
+            // thread and row of nw words, and what is done with word e of pair q
+            auto words = [&](auto per_thread, int nw, int q0, auto park) {
+                constexpr int NI = decltype(per_thread)::value;
+                for (int base = tid; base < nw; base += NI * NTHR) {
+                    unsigned long long v[NJ * NI];
+                    auto ask = [&](unsigned long long (&r)[NJ * NI]) {
 #pragma unroll
                         for (int j = 0; j < NJ; ++j) {
                             const int q = q0 + j < NQ ? q0 + j : NQ - 1;
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int e = base + i * NTHR < H ? base + i * NTHR : H - 1;
-                                r[j * 4 + i] = __hip_atomic_load(ex + (size_t)q * H + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            for (int i = 0; i < NI; ++i) {
+                                const int e = base + i * NTHR < nw ? base + i * NTHR : nw - 1;
+                                r[j * NI + i] = __hip_atomic_load(ex + (size_t)q * H + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                             }
                         }
                     };
                     // 1: all tags are t, 0: not yet, -1: a workgroup has given up
-                    auto seen = [&](const unsigned long long (&r)[NJ * 4]) {
-                        int ok = 1;
+                    auto seen = [&](const unsigned long long (&r)[NJ * NI]) {
+                        unsigned int differ = 0;
 #pragma unroll
-                        for (int k = 0; k < NJ * 4; ++k) {
-                            const unsigned int tag = (unsigned int)(r[k] >> 32);
-                            if ((tag & tag_mask) != (unsigned int)t) ok = ok < 0 ? ok : 0;
-                            if (tag == kSeqPoison) ok = -1;
-                        }
-                        return ok;
+                        for (int k = 0; k < NJ * NI; ++k) differ |= (unsigned int)(r[k] >> 32) ^ (unsigned int)t;
+                        if ((differ & tag_mask) == 0) return 1;
+                        int st_ = 0;
+#pragma unroll
+                        for (int k = 0; k < NJ * NI; ++k) st_ = (unsigned int)(r[k] >> 32) == kSeqPoison ? -1 : st_;
+                        return st_;
                     };
                     // NP reads of every word go out at once, a fraction of a round trip apart, and are examined in turn
                     // (straight-line code, so that the wait for an older read leaves the younger ones in flight); a
@@ -267,74 +302,80 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     // written again two steps later at the earliest, so a later read cannot show anything else).
                     // (A set on one XCD: one read at a time is quicker, 2.39 -> 2.30 us per step of one LSTM of 1024 units.)
                     unsigned int polls = 0;
-                    bool ok = false, dead = false;
+                    int st_ = 0;
                     if constexpr (!PLACED) {
+                        unsigned long long r[NP][NJ * NI];
 #pragma unroll
                         for (int d = 0; d < NP; ++d) {
-                            ask(w[d]);
+                            ask(r[d]);
                             if (d + 1 < NP) __builtin_amdgcn_s_sleep(kSeqPollGap);
                         }
                         bool waiting = true;
 #pragma unroll
                         for (int d = 0; d < NP; ++d) {
                             if (waiting) {                          // (the same for the whole wave)
-                                const int st_ = seen(w[d]);
-                                if (st_ > 0 && !ok) {
+                                if (st_ == 0) {
 #pragma unroll
-                                    for (int k = 0; k < NJ * 4; ++k) v[k] = w[d][k];
-                                    ok = true;
+                                    for (int k = 0; k < NJ * NI; ++k) v[k] = r[d][k];
+                                    st_ = seen(v);
+                                    if (st_ == 0 && ++polls >= p.max_polls) st_ = -1;
                                 }
-                                dead = dead || st_ < 0 || (!ok && ++polls >= p.max_polls);
-                                waiting = __builtin_amdgcn_ballot_w64(!ok && !dead) != 0;
+                                waiting = __builtin_amdgcn_ballot_w64(st_ == 0) != 0;
                             }
                         }
                     }
                     // one read at a time (from here on)
-                    while (!ok && !dead) {
+                    while (st_ == 0) {
                         if (!PLACED || polls) __builtin_amdgcn_s_sleep(1);
-                        ask(w[0]);
-                        const int st_ = seen(w[0]);
-                        if (st_ > 0) {
-#pragma unroll
-                            for (int k = 0; k < NJ * 4; ++k) v[k] = w[0][k];
-                            ok = true;
-                        }
-                        dead = st_ < 0 || (!ok && ++polls >= p.max_polls);
+                        ask(v);
+                        st_ = seen(v);
+                        if (st_ == 0 && ++polls >= p.max_polls) st_ = -1;
+                    }
+                    if (st_ < 0) {
+                        flag = 1;
+                        return;
                     }
                     if constexpr (PLACED) {
                         if (t == 1) {
 #pragma unroll
-                            for (int k = 0; k < NJ * 4; ++k) others |= (unsigned int)(v[k] >> 32 >> kSeqTagShift) ^ xcd;
+                            for (int k = 0; k < NJ * NI; ++k) others |= (unsigned int)(v[k] >> 32 >> kSeqTagShift) ^ xcd;
                         }
-                    }
-                    if (!ok) {
-                        *flag = 1;
-                        bad = true;
-                        break;
                     }
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) {
                         if (q0 + j < NQ) {
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int e = base + i * NTHR;
-                                if (e < H) {
-                                    const unsigned int pair = (unsigned int)v[j * 4 + i];
-                                    hin[(2 * (q0 + j)) * hld + e] = (unsigned short)(pair & 0xffffu);
-                                    if (2 * (q0 + j) + 1 < B) hin[(2 * (q0 + j) + 1) * hld + e] = (unsigned short)(pair >> 16);
-                                }
-                            }
+                            for (int i = 0; i < NI; ++i)
+                                if (base + i * NTHR < nw) park(q0 + j, base + i * NTHR, (unsigned int)v[j * NI + i]);
                         }
                     }
                 }
+            };
+            if constexpr (MULTI) {
+                for (int q0 = 0; q0 < NQ; q0 += NJ)
+                    words(std::integral_constant<int, 4>{}, H, q0, [&](int q, int e, unsigned int pair) {
+                        hin[2 * q * hld + e] = (unsigned short)(pair & 0xffffu);
+                        if (2 * q + 1 < B) hin[(2 * q + 1) * hld + e] = (unsigned short)(pair >> 16);
+                    });
+            } else if (p.unit_pairs) {
+                words(std::integral_constant<int, 2>{}, H / 2, 0,
+                      [&](int, int e, unsigned int pair) { reinterpret_cast<unsigned int *>(hin)[e] = pair; });
+            } else {
+                words(std::integral_constant<int, 4>{}, H, 0, [&](int, int e, unsigned int value) { hin[e] = (unsigned short)value; });
             }
-            if (PLACED && others) *apart = 1;
+            if (PLACED && others) apart = 1;
         }
         __syncthreads();
-        if (PLACED && t == 1) one_l2 = *apart == 0;
-        if (*flag) {                                                  // the same value for every thread
-            gave_up = true;
-            break;
+        // (read here, looked at behind the products: the same value for every thread)
+        const int stop = flag;
+        if (PLACED && t == 1) one_l2 = __builtin_amdgcn_readfirstlane(apart) == 0;
+        if (t > 0) outputs(t - 1);
+        if (p.xvec16) {
+            const int tn = t + 1 < p.T ? t + 1 : t;
+            const GRIM_GLOBAL T *xg = xs0 + (int64_t)tn * p.B * p.ldxs;
+#pragma unroll
+            for (int k = 0; k < XV; ++k)
+                if (k * NTHR < nxv) xr[k] = *reinterpret_cast<const GRIM_GLOBAL gu32x4 *>(xg + xsrc[k]);     // (the same for all threads)
         }
 
         // ---- 2. per sequence: the block's KC activations, the products, the strip's row sums.  One table per wave
@@ -407,15 +448,14 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     s += v[q].x;
                     s += v[q].y;
                 }
-                const float s2 = s + __shfl_xor(s, 16);
-                return s2 + __shfl_xor(s2, 32);
+                return seq_halves(seq_quarters(s));
             }
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
                 s += v[q].x;
                 s += v[q].y;
             }
-            return s + __shfl_xor(s, 32);
+            return seq_halves(s);
         };
         for (int bs = 0; bs < B; bs += NS) {
             float acc[NS][KR];
@@ -429,6 +469,10 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                 const float rs = row_sum(v[s]);
                 if (bs + s < B && grp == 0 && r_out < p.BR) gl[((bs + s) * NWV + wave) * 32 + r_out] = rs;
             }
+        }
+        if (__builtin_amdgcn_readfirstlane(stop)) {
+            gave_up = true;
+            break;
         }
         __syncthreads();
 
@@ -447,25 +491,29 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                         h = gru_cell_apply(g[0] + b[0], g[32] + b[1], g[64] + b[2], g[96] + b[3], g[128] + b[4], g[160] + b[5], st[k]);
                         st[k] = h;
                     }
-                    const unsigned short hr = seq_round<DT>(h);
-                    pair |= (unsigned int)hr << (16 * k);
-                    static_cast<unsigned short *>(p.hs)[((int64_t)t * p.B + b0 + bb) * p.ldhs + ju] = hr;
-                    if (p.hs32) p.hs32[((int64_t)t * p.B + b0 + bb) * p.ldhs32 + ju] = h;
+                    pair |= (unsigned int)seq_round<DT>(h) << (16 * k);
+                    out32[k] = h;
                 }
             }
+            out16 = pair;
+            if (!MULTI && p.unit_pairs)                                // the neighbour's value beside this one (lanes 2 k, 2 k + 1)
+                pair |= (unsigned int)__builtin_amdgcn_update_dpp(0, (int)pair, 0xb1, 0xf, 0xf, true) << 16;
             const unsigned int tag = (unsigned int)(t + 1) | (PLACED && t == 0 ? xcd << kSeqTagShift : 0u);
             const unsigned long long word = (unsigned long long)pair | ((unsigned long long)tag << 32);
-            unsigned long long *to = exch + ((size_t)((t + 1) & 1) * NQ + cq) * H + ju;
-            if (PLACED && one_l2) __hip_atomic_store(to, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            else __hip_atomic_store(to, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long *to = exch + ((size_t)((t + 1) & 1) * NQ + cq) * H + jw;
+            if (writes) {
+                if (PLACED && one_l2) __hip_atomic_store(to, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                else __hip_atomic_store(to, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
+    if (!gave_up) outputs(p.T - 1);
 
     if (gave_up) {
         if (cell_thread) {
             const unsigned long long word = (unsigned long long)kSeqPoison << 32;
-            __hip_atomic_store(exch + (size_t)cq * H + ju, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(exch + ((size_t)NQ + cq) * H + ju, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(exch + (size_t)cq * H + jw, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(exch + ((size_t)NQ + cq) * H + jw, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (tid == 0) __hip_atomic_store(p.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
@@ -591,6 +639,8 @@ grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, con
     int sets = 1, per_wg = 1;
     seq_split(H, BR, batch, compute_units(), &sets, &per_wg);
     p.B = batch; p.SPB = per_wg; p.NQ = (per_wg + 1) / 2;
+    // two hidden units to a word where both are the same workgroup's and h starts at a multiple of four bytes in LDS
+    p.unit_pairs = per_wg == 1 && BR % 2 == 0 && (kind == 2 || I % 2 == 0) ? 1 : 0;
     // pieces a thread fetches ahead: one when a workgroup carries one sequence, up to kSeqXVec otherwise
     p.xvec16 = (I % 8 == 0 && K1 % 8 == 0 && per_wg * (I / 8) <= (per_wg > 1 ? kSeqXVec : 1) * exact_waves(kind) * 64 &&
                 ldxs % 8 == 0 && reinterpret_cast<uintptr_t>(xs) % 16 == 0) ? 1 : 0;

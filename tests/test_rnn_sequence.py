@@ -444,3 +444,29 @@ def test_sequences_of_separate_matrices_on_separate_streams():
         for a, b in zip(alone, together):
             assert int(a[2]) == 0 and int(b[2]) == 0
             assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("H,I,BR,BC,kr,kc,B", [
+    (90, 30, 9, 10, 4, 4, 8),           # strips of an odd number of rows: a hidden unit to an exchange word
+    (64, 11, 16, 15, 4, 4, 1),          # h at an odd element of [x; h]: the same
+    (1280, 256, 32, 32, 4, 4, 8),       # two units to a word, more words than two per thread; eight sets, each on one XCD
+    (1280, 256, 32, 32, 4, 4, 1),       # the same in the plain order
+    (2016, 32, 8, 32, 4, 8, 1),         # 252 workgroups of four units each, two rounds of words
+])
+def test_lstm_sequence_forms_of_the_exchange_words(H, I, BR, BC, kr, kc, B):
+    """A step's error is TOL of sums of order 1, carried on by at most one per further step (as in the test above)."""
+    from helpers import TOL
+    torch, dev, g = _gpu()
+    dtype, T = gen.F16, 9
+    A, Wm = _lstm_case(g, dtype, H, I, BR, BC, kr, kc, seed=2100 + H + I, scale=6.0 if H < 512 else 2.0)
+    rng = np.random.default_rng(2101)
+    xs = np.stack([_inputs(T, I, dtype, 2110 + b) for b in range(B)], axis=1)
+    bias = (0.2 * rng.standard_normal(4 * H)).astype(np.float32)
+    h0 = np.stack([gen.round_to_storage((0.5 * rng.standard_normal(H)).astype(np.float32), dtype) for _ in range(B)])
+    c0 = rng.standard_normal((B, H)).astype(np.float32)
+    status, hs, hs32, c = _run_lstm_batch(torch, dev, g, A, xs, dtype, bias, h0, c0)
+    assert status == 0
+    for b in range(B):
+        hs_ref, _ = _lstm_reference(Wm, np.ascontiguousarray(xs[:, b]), dtype, bias, h0[b], c0[b])
+        for t in range(T):
+            assert np.abs(hs32[t, b] - hs_ref[t]).max() <= TOL[dtype] * (1 + t), f"sequence {b}, step {t}"
