@@ -131,6 +131,10 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     if (wave >= NW) {
         // ------------------------------------------------------------------ fetching waves
         const int ft = tid - NW * 64;            // 0 .. 255
+        // A convolution of 16-row blocks waits for its windows and not for its multiplies: its fetching waves go first where
+        // a SIMD has the choice (256 channels, 3 x 3, four 112 x 112 maps 64.1 -> 54.2 us, mixed rates 68.0 -> 64.8).  The
+        // 32-row form, which multiplies twice as much per window, loses by it (76.8 -> 80.9), products gain nothing.
+        if constexpr (CONV == kConvByTap && BR == 16) __builtin_amdgcn_s_setprio(1);
         // zero rows (gather target of padded k slots), one per stage
         static_assert(2 * (PITCH / 4) <= kWideFetchThreads, "one thread per dword of the two zero rows");
         if (ft < 2 * (PITCH / 4)) {
@@ -506,6 +510,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     // group's first half takes the k-th lightest of the second half
     const int tA = t0 + wave, tB = t0 + 2 * NW - 1 - wave;
 
+    auto lds_address = [](const char *at) { return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const char *)at; };
     struct Hdr { unsigned int rr; uint2 dsc; };
     auto load_hdr = [&](const char *h) {
         Hdr f;
@@ -545,13 +550,15 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     // gathered rows and the header of the step after it -- are issued BEFORE the current item is multiplied and land in
     // a second set of registers; items are taken in pairs so that the two sets swap roles without a copy (a copy
     // would wait for the load it copies).  The scheduling barriers keep the compiler from moving the multiplies ahead
-    // of the loads: the LDS round trip of one item has to run under the multiplies of the item before it.  Whether
-    // a lane's row is kept is applied to its weights only when they are used.
-    struct Frag { i16x8 x[NTB]; i16x8 w; unsigned int kept; };
+    // of the loads: the LDS round trip of one item has to run under the multiplies of the item before it.  A lane whose
+    // row the block does not keep reads its weights from the stage's zero row (zeroed in registers instead, four more
+    // instructions a step: 512 x 4608 of mixed rates in 32-row blocks at 25 088 columns 79.4 us, 76.6 so).
+    struct Frag { i16x8 x[NTB]; i16x8 w; };
     auto compute = [&](int ch, const Entry &en) {
         const int n = en.nA + en.nB;
         if (n <= 0) return;
         const char *stage = lds + (ch & 1) * stage_bytes;
+        const unsigned int zero_row = lds_address(stage) + p.chunk_rows * PITCH;
         const char *regA = stage + xbytes + en.offA, *regB = stage + xbytes + en.offB;
         // virtual step v of the wave's list: strip A's steps, then strip B's (clamped to the last one)
         auto region_of = [&](int v) { return v < en.nA ? regA : regB; };
@@ -564,24 +571,19 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
             const int b = it % NB;
             if (b == 0) {
                 int v = it / NB;
-                const bool past = v >= n;                 // a step past the list: any valid loads, zero weights
-                v = past ? n - 1 : v;
-                const char *region = region_of(v);
-                f.kept = past ? 0u : h.dsc.x & mybit;
-                const int idx = f.kept ? __builtin_popcount(h.dsc.x & below) : 0;
-                f.w = *reinterpret_cast<const i16x8 *>(region + (h.dsc.y + idx) * 16);
+                v = v < n ? v : n - 1;                    // (a step past the list is loaded and not multiplied)
+                const unsigned int at = lds_address(region_of(v)) + (__builtin_popcount(h.dsc.x & below) + h.dsc.y) * 16;
+                f.w = *(__attribute__((address_space(3))) const i16x8 *)(uintptr_t)(h.dsc.x & mybit ? at : zero_row);
             } else {
-                f.kept = prev.kept;
                 f.w = prev.w;
             }
             load_x(stage, h, b, f.x);
         };
         auto multiply = [&](Acc (&a)[NT], int b, const Frag &f) {
-            const i16x8 w = f.kept ? f.w : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
             for (int j = 0; j < NTB; ++j) {
-                if constexpr (BR == 16) a[b * NTB + j] = mfma16<BF16>(f.x[j], w, a[b * NTB + j]);
-                else a[b * NTB + j] = mfma32<BF16>(w, f.x[j], a[b * NTB + j]);
+                if constexpr (BR == 16) a[b * NTB + j] = mfma16<BF16>(f.x[j], f.w, a[b * NTB + j]);
+                else a[b * NTB + j] = mfma32<BF16>(f.w, f.x[j], a[b * NTB + j]);
             }
         };
         Frag fa, fb;
