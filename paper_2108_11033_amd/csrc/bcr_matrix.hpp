@@ -22,16 +22,17 @@ inline int dtype_size(int dt) { return dt == GRIM_F32 ? 4 : 2; }
 
 // Layout for the matrix-core SpMM kernel (fp16 / bf16, BR = 16 or 32).
 // K is cut into chunks of `chunk_rows` consecutive rows of X.  For every (chunk, stored strip)
-// the kept columns of the strip's blocks inside the chunk are laid out as groups of 8 k slots
-// (a block's columns are padded to a multiple of 8 with the all-zero staged row), `ks / 8`
-// groups per MFMA step.  A (chunk, strip) region is
+// the kept columns of the strip's blocks inside the chunk are laid out one after the other, eight
+// to a group of k slots whichever blocks they belong to (the last step of a region is padded with the
+// all-zero staged row), `ks / 8` groups per MFMA step.  (Groups of one block each, padded to eight: a
+// quarter more steps where 12 columns are kept, a seventh for 4, 8 or 16 at random.)  A (chunk, strip) region is
 //   [steps x header][payload]
 //   header : per step, the staged-row numbers of its k slots (u16, ordered so that the pair a
-//            lane names in its two LDS transpose reads is adjacent), then per group the block's
-//            row bit mask (u32) and the offset of the group's weights in 16-byte units from the
+//            lane names in its two LDS transpose reads is adjacent), then per group the
+//            bit mask of the rows that keep any of its columns (u32) and the offset of the group's weights in 16-byte units from the
 //            region start (u32);
-//   payload: per group, for every KEPT row of the block 8 weights (16 bytes) -- compact: pruned
-//            rows are not stored; a lane finds its row by popcount of the mask below its bit.
+//   payload: per group, for every row of that mask 8 weights (16 bytes; zero at the columns whose
+//            block does not keep the row) -- compact: other rows are not stored; a lane finds its row by popcount of the mask below its bit.
 // Regions are stored chunk-major, strips in stored order inside a chunk, so what a workgroup
 // (a group of consecutive stored strips) needs for one chunk is one contiguous byte range.
 struct MmaLayout {

@@ -55,8 +55,9 @@ bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks
     L.cptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
     L.bptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
     L.recs.clear();
-    struct Group { int64_t t; int32_t j0; };           // stored block (-1: empty), first kept-column position
-    std::vector<Group> groups;
+    // the kept columns of a (chunk, strip), one after the other whatever block they belong to
+    struct Slot { int64_t t, w; uint32_t mask; int32_t kc; uint16_t row; };   // stored block, its column's first weight, its rows; staged row
+    std::vector<Slot> slots;
     int64_t step = 0;
     const uint16_t *w = reinterpret_cast<const uint16_t *>(A->weights.data());
     const uint16_t zero_row = (uint16_t)L.chunk_rows;
@@ -65,51 +66,56 @@ bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks
         for (int64_t st = 0; st < A->nbr; ++st) {
             L.cptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)step;
             L.bptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)(L.recs.size() / 16);
-            groups.clear();
+            slots.clear();
             for (int64_t c = c0; c < c1; ++c) {
                 const int64_t t = st * A->nbc + c;
                 const int32_t kr = A->row_ptr[t + 1] - A->row_ptr[t], kc = A->col_ptr[t + 1] - A->col_ptr[t];
                 if (kr == 0 || kc == 0) continue;       // nothing to multiply
-                for (int32_t j0 = 0; j0 < kc; j0 += 8) groups.push_back({t, j0});
+                uint32_t mask = 0;
+                for (int32_t qq = A->row_ptr[t]; qq < A->row_ptr[t + 1]; ++qq) mask |= 1u << A->row_idx[qq];
+                for (int32_t j = 0; j < kc; ++j)
+                    slots.push_back({t, A->blk_ptr[t] + j, mask, kc, (uint16_t)((c - c0) * A->BC + A->col_idx[A->col_ptr[t] + j])});
             }
-            while (groups.size() % ng) groups.push_back({-1, 0});
-            const size_t nst = groups.size() / ng;
+            const size_t ngroups = (slots.size() + L.ks - 1) / L.ks * ng;
+            const size_t nst = ngroups / ng;
             const size_t region0 = L.recs.size();
             L.recs.resize(region0 + nst * hdr, 0);
             uint32_t pay16 = (uint32_t)(nst * hdr / 16);    // next free payload unit, from the region start
-            for (size_t q = 0; q < groups.size(); ++q) {
-                const Group &gp = groups[q];
+            for (size_t q = 0; q < ngroups; ++q) {
                 const size_t sidx = q / ng, g = q % ng;
-                unsigned char *h = L.recs.data() + region0 + sidx * hdr;
+                const Slot *gs = slots.data() + std::min(q * 8, slots.size());
+                const int32_t n = (int32_t)std::min<size_t>(8, slots.size() - std::min(q * 8, slots.size()));
                 uint16_t rows[8];
                 uint32_t rowmask = 0, off = 0;
-                int32_t kr = 0, kc = 0;
-                int64_t c = 0;
-                if (gp.t >= 0) {
-                    kr = A->row_ptr[gp.t + 1] - A->row_ptr[gp.t];
-                    kc = A->col_ptr[gp.t + 1] - A->col_ptr[gp.t];
-                    c = gp.t % A->nbc;
-                    for (int32_t qq = A->row_ptr[gp.t]; qq < A->row_ptr[gp.t + 1]; ++qq) rowmask |= 1u << A->row_idx[qq];
+                for (int32_t e = 0; e < 8; ++e) {
+                    rows[e] = e < n ? gs[e].row : zero_row;
+                    if (e < n) rowmask |= gs[e].mask;
                 }
-                for (int32_t e = 0; e < 8; ++e)
-                    rows[e] = (gp.t >= 0 && gp.j0 + e < kc)
-                                  ? (uint16_t)((c - c0) * A->BC + A->col_idx[A->col_ptr[gp.t] + gp.j0 + e])
-                                  : zero_row;
                 // slot rows: quad qd of the group pairs slot qd with slot qd + 4
+                unsigned char *h = L.recs.data() + region0 + sidx * hdr;
                 uint16_t *hs = reinterpret_cast<uint16_t *>(h) + g * 8;
                 for (int32_t qd = 0; qd < 4; ++qd) {
                     hs[2 * qd] = rows[qd];
                     hs[2 * qd + 1] = rows[qd + 4];
                 }
-                if (gp.t >= 0) {
+                if (n > 0) {
                     off = pay16;
+                    const int32_t kr = __builtin_popcount(rowmask);
                     const size_t p0 = L.recs.size();
                     L.recs.resize(p0 + (size_t)kr * 16, 0);
                     h = L.recs.data() + region0 + sidx * hdr;     // resize may move the buffer
                     uint16_t *pw = reinterpret_cast<uint16_t *>(L.recs.data() + p0);
-                    for (int32_t i = 0; i < kr; ++i)
-                        for (int32_t e = 0; e < 8 && gp.j0 + e < kc; ++e)
-                            pw[i * 8 + e] = w[A->blk_ptr[gp.t] + (int64_t)i * kc + gp.j0 + e];
+                    if (gs[0].t == gs[n - 1].t) {
+                        for (int32_t i = 0; i < kr; ++i)
+                            for (int32_t e = 0; e < n; ++e) pw[i * 8 + e] = w[gs[e].w + (int64_t)i * gs[e].kc];
+                    } else {
+                        int32_t i = 0;
+                        for (uint32_t m = rowmask; m; m &= m - 1, ++i) {
+                            const uint32_t bit = m & (0u - m);
+                            for (int32_t e = 0; e < n; ++e)
+                                if (gs[e].mask & bit) pw[i * 8 + e] = w[gs[e].w + (int64_t)__builtin_popcount(gs[e].mask & (bit - 1)) * gs[e].kc];
+                        }
+                    }
                     pay16 += (uint32_t)kr;
                 }
                 uint32_t *hd = reinterpret_cast<uint32_t *>(h + L.ks * 2) + g * 2;
