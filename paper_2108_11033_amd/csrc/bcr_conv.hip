@@ -70,6 +70,8 @@ grim_status conv_gather_setup(const grim_bcr_matrix *A, const void *F, int32_t C
     p.tiles_per_img = (int32_t)((Nv - p.pos_begin + nt * 16 - 1) / (nt * 16));
     if ((int64_t)p.tiles_per_img * batch > 0x7fffffff / 16) return GRIM_ERR_SHAPE;
     p.ntiles = p.tiles_per_img * batch;
+    p.tiles_inv = divide_inverse(p.tiles_per_img);
+    p.row_inv = divide_inverse(stride == 2 ? p.Wp : W);
     // four consecutive outputs of a row in one store: 16 bytes of fp32, 8 bytes of fp16 / bf16
     const int esz_out = odt == GRIM_F32 ? 4 : 2;
     p.yvec = (reinterpret_cast<uintptr_t>(Y) % (odt == GRIM_F32 ? 16 : 8) == 0 && ldy % 4 == 0 && (stride == 1 ? N : p.Wo) % 4 == 0 &&

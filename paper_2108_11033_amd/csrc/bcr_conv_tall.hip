@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
     if (n0 + TN > p.Nv) n0 = p.Nv - TN;          // ragged last tile: overlap the neighbour
     n0 = n0 < 0 ? 0 : n0;                        // fewer than 64 positions: one tile, its columns past them never stored
     const int g0 = p.usteps ? t * p.usteps : p.sptr[t], nst = p.usteps ? p.usteps : p.sptr[t + 1] - g0;
-    const int s_beg = g0 + (int)((int64_t)nst * wave / NWV), s_end = g0 + (int)((int64_t)nst * (wave + 1) / NWV);
+    const int s_beg = g0 + wave_share(nst, wave, NWV), s_end = g0 + wave_share(nst, wave + 1, NWV);
     char *buf = lds + wave * WAVE_LDS;
 
     const int kgroup = lane >> 4, i16 = lane & 15;

@@ -57,8 +57,8 @@ __global__ void __launch_bounds__(NWV * 64, 4) bcr_spmm_gather32(Gather32Params 
     int64_t n0 = (int64_t)tile * TN;
     if (!NARROW && n0 + TN > p.N) n0 = p.N - TN;   // ragged last tile: overlap the neighbour (same sums, same bits)
     const int g0 = p.usteps ? t * p.usteps : p.sptr[t], nst = p.usteps ? p.usteps : p.sptr[t + 1] - g0;
-    const int s_beg = SOLO ? g0 : g0 + (int)((int64_t)nst * wave / NWV);
-    const int s_end = SOLO ? g0 + nst : g0 + (int)((int64_t)nst * (wave + 1) / NWV);
+    const int s_beg = SOLO ? g0 : g0 + wave_share(nst, wave, NWV);
+    const int s_end = SOLO ? g0 + nst : g0 + wave_share(nst, wave + 1, NWV);
 
     const int i16 = lane & 15, kg = lane >> 4;
     const unsigned int below = (1u << i16) - 1u;

@@ -45,6 +45,7 @@ struct ConvParams {
     // (tap << 27 | start + 2^25; tap = KK for padding slots); null: the kernel splits the row numbers itself
     const uint32_t *plan;
     int32_t batch, tiles_per_img;        // images; ntiles = batch * tiles_per_img
+    uint32_t tiles_inv, row_inv;         // divide_by: tiles_per_img; positions of a row as the tiles walk it (W, or Wp at stride 2)
     int64_t f_img_stride, y_img_stride;  // elements between images of F and of Y
     // The 64 positions of a tile are output positions; stride 2: of output rows padded to Wp, a multiple of 8, so that a
     // lane's 8 positions never straddle two rows (Ho x Wo outputs; stride 1: Wp is not used)
@@ -81,6 +82,24 @@ __device__ __forceinline__ u32x4 conv_piece_mask(const ConvParams &p, int tap, i
         }
     }
     return u32x4{m[0], m[1], m[2], m[3]};
+}
+
+// the same for two of the positions, nb and nb + 1 (a row of positions has `rowlen` of them): a dword of the mask
+template <bool S2>
+__device__ __forceinline__ unsigned int conv_pair_mask(const ConvParams &p, int tap, int nb, int rowlen) {
+    const int r = (tap * p.kw_magic) >> 8, q = tap - r * p.kw;
+    const int dr = r - (p.kh >> 1), dq = q - (p.kw >> 1);
+    const int h0 = divide_by(nb, rowlen, p.row_inv), w0 = nb - h0 * rowlen;
+    unsigned int m = 0u;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        int h = h0, w = w0 + j;
+        if (!S2 && w >= rowlen) { w -= rowlen; ++h; }          // (positions past the last, of a small map: h >= H, never stored)
+        if constexpr (S2) { h *= 2; w *= 2; }
+        const bool ok = tap < p.KK && h + dr >= 0 && h + dr < p.H && w + dq >= 0 && w + dq < p.W;
+        m |= ok ? (j ? 0xffff0000u : 0x0000ffffu) : 0u;
+    }
+    return m;
 }
 
 // epilogue of a layer for four consecutive positions n .. n + 3 of output channel `row`: bias `b`, rectifier,
@@ -171,14 +190,17 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     constexpr int RPI = 64 / CPR, LI = 32 / RPI;               // rows per load instruction, windows per lane and step
     constexpr int LW = S2 ? 2 : 1;               // 16-byte loads per window (stride 2: 16 elements, of which every second one counts)
     constexpr int NWV = EIGHT ? LONGW : 4;       // waves of the workgroup
+    // (what the prologue needs of the arguments in one trip through the scalar cache: where each is asked for when it is
+    // first used, the trips follow one another)
+    asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
+                 "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.tiles_per_img), "s"(p.tiles_inv), "s"(p.nbr),
+                 "s"(p.usteps), "s"(p.plan), "s"(p.rows), "s"(p.desc), "s"(p.out_row), "s"(p.F), "s"(p.f_img_stride), "s"(p.Nv));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile, unit;
     if (!xcd_map_at(p.map, block_x, p.ntiles, &tile, &unit)) return;
-    // (a division by a run-time value is done on the vector ALU even for uniform operands; without the
-    // readfirstlane everything derived from the image and tile numbers would live in vector registers)
-    const int img_l = __builtin_amdgcn_readfirstlane(tile / p.tiles_per_img);
-    tile = __builtin_amdgcn_readfirstlane(tile - img_l * p.tiles_per_img);
+    const int img_l = divide_by(tile, p.tiles_per_img, p.tiles_inv);
+    tile -= img_l * p.tiles_per_img;
     const int img = img_l + p.img0;
     const unsigned short *Fimg = p.F + (int64_t)img * p.f_img_stride;
     const int t_raw = SOLO ? unit * 4 + wave : unit;
@@ -190,36 +212,14 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
 
     // one dependent memory round trip less at the start when every run has the same number of steps
     const int g0 = p.usteps ? t * p.usteps : p.sptr[t], nst = p.usteps ? p.usteps : p.sptr[t + 1] - g0;
-    const int s_beg = SOLO ? g0 : g0 + (int)((int64_t)nst * wave / NWV);
-    const int s_end = SOLO ? g0 + nst : g0 + (int)((int64_t)nst * (wave + 1) / NWV);
+    const int s_beg = SOLO ? g0 : g0 + wave_share(nst, wave, NWV);
+    const int s_end = SOLO ? g0 + nst : g0 + wave_share(nst, wave + 1, NWV);
     char *buf = lds + wave * conv_wave_lds(NT);
-    // The first batch's row numbers and block descriptors are asked for before the validity table is built,
-    // so that their latency runs under it.
-    const int kgroup0 = lane >> 4;
     const int row = p.out_row[(int64_t)t * 16 + (lane & 15)];     // output channel and bias: asked for now, needed at the very end
     const uint2 *desc2 = reinterpret_cast<const uint2 *>(p.desc);
     const uint32_t *slots = PLAN ? p.plan : p.rows;
-    unsigned int npk[SB];
-    uint2 ndsc[SB];
-#pragma unroll
-    for (int u = 0; u < SB; ++u) {
-        int st = s_beg + u;
-        st = st < s_end ? st : s_end - 1;
-        st = st < 0 ? 0 : st;                    // (a wave without steps: any valid step, never used)
-        npk[u] = slots[(int64_t)st * 32 + (lane & 7) * 4 + ((lane >> 3) & 3)];
-        ndsc[u] = desc2[(int64_t)st * 4 + kgroup0];
-    }
-    // per (tap, piece of the tile) the 16-byte validity mask of the piece's 8 positions; entry KK
-    // is all zero (padding slots).
     u32x4 *vtab = reinterpret_cast<u32x4 *>(lds + NWV * conv_wave_lds(NT));
     const int ph = p.kh >> 1, pw = p.kw >> 1;
-    if (tid < (p.KK + 1) * CPR) {
-        const int tap = tid / CPR, cc = tid % CPR;
-        vtab[tid] = conv_piece_mask<S2>(p, tap, n0 + cc * 8);
-    }
-    const float bias = p.bias && row >= 0 ? p.bias[row] : 0.f;
-    __syncthreads();
-    if (SOLO && !active) return;                 // (no barrier follows in that form)
 
     // fetch side: lane = (row slot rs, piece c): positions n0 + 8 c .. n0 + 8 c + 7 of the tile
     const int rs = lane / CPR, c = lane % CPR;
@@ -235,16 +235,12 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     const unsigned int buf_lds = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)buf;
     const unsigned int tr0 = x0 + ((cl ^ sw0) << 4), tr1 = x1 + ((cl ^ sw1) << 4);           // offsets in a step buffer
 
-    f32x4 acc[NT];
-#pragma unroll
-    for (int q = 0; q < NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-
     const i16x8 *pay = reinterpret_cast<const i16x8 *>(p.payload);
     const char *Fb = reinterpret_cast<const char *>(Fimg);
     const int HW = p.N, wstep = p.W - p.kw, emax = p.total - 8;
     const int centre = ph * p.W + pw;            // offset of the centre tap: window starts are relative to it
     // element (inside a channel) under the centre tap for the first of the 8 positions of piece cc
-    auto pos_off = [&](int cc) { return conv_piece_start<S2>(n0 + cc * 8, p.W, p.Ho, p.Wp); };
+    auto pos_off = [&](int cc) { return conv_piece_start<S2>(n0 + cc * 8, p.W, p.Ho, p.Wp, p.row_inv); };
     // Stride 1: the tile's first position goes into the (uniform) window start of a k slot and a lane adds only its
     // piece's 8 c -- this split, not the sum formed per lane, is what keeps the fetch loop within its registers.
     const int tile_pos = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0)) : n0;
@@ -252,34 +248,52 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     // can a window of this tile start before the feature map or end behind it?  (only in the first / last channel)
     bool tile_edge = conv_tile_at_edge<S2>(pos_off(0), pos_off(CPR - 1), centre, HW);
     if constexpr (S2) tile_edge = __builtin_amdgcn_readfirstlane(tile_edge) != 0;
-    for (int s = s_beg; s < s_end; s += SB) {
-        const int nb = s_end - s < SB ? s_end - s : SB;
-        // Lane j takes k slot j % 32 of every step of the batch: it splits the slot's row number once into
-        // (window start for the tile's first column, tap) and the lanes that fetch the slot's eight row
-        // pieces pick that pair up with a lane permute -- one integer division per lane and step instead of
-        // four.  Packed as tap (or KK for padding) << 27 | window start + 2^25.
-        unsigned int pk[SB];
-        uint2 dsc[SB];
+    // A batch: the slot words and block descriptors of SB steps (past the wave's last: the last again), then their windows
+    // and weights, all in registers at once.
+    //   Where many waves split a strip (few workgroups, a batch or two per wave: the form is all latency) a lane reads the
+    // plan's words of its own LI windows.  Handed on by lane permutes as below, each window is asked for behind a trip through
+    // LDS (512 channels, 3 x 3, 14 x 14: 6.9 us; 6.1 so, with the windows ahead of the validity table).  With four waves
+    // and many workgroups the loads are what is short and the words' cost 1 to 3 % (192 channels, 5 x 5, six 56 x 56 maps 112 us, 115 so).
+    //   Otherwise lane j takes k slot j % 32 of every step -- without a plan it splits the slot's row number into (window
+    // start for the tile's first column, tap) -- and the lanes that fetch the slot's row pieces pick that pair up with a
+    // lane permute: one integer division per lane and step instead of four.
+    // Packed as tap (or KK for padding) << 27 | window start + 2^25.
+    constexpr bool OWN = PLAN && EIGHT;          // a lane has the words of its windows
+    constexpr bool NEED_PK = !OWN || (!S2 && NT == 4);        // ... or the word of k slot lane % 32
+    constexpr bool OWN_EXT = OWN && !S2 && NT == 2;          // the last lane of a row piece asks for the element behind its window itself
+    unsigned int pk[SB], words[SB][LI];
+    uint2 dsc[SB];
+    u32x4 RX[SB][LI][LW];
+    unsigned int vsel[SB];                   // per step, 8 bits per window: validity mask (the tap; KK: padding) | odd start << 7
+    i16x8 PW[SB];
+    unsigned int ext[SB][OWN_EXT ? LI : 1];
+    auto ask_words = [&](int st, unsigned int (&w)[LI]) {
+        if constexpr (NT == 4) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(slots + (int64_t)st * 32 + rs * 4);
+#pragma unroll
+            for (int i = 0; i < LI; ++i) w[i] = v[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < LI; ++i) w[i] = slots[(int64_t)st * 32 + (rs & 7) * 4 + (rs >> 3) + 2 * i];
+        }
+    };
+    auto step = [&](int s) { return s < s_end ? s : s_end - 1 < 0 ? 0 : s_end - 1; };     // (a wave without steps: any valid step, never used)
+    auto ask_headers = [&](int s) {
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
-            if (s == s_beg) {
-                pk[u] = npk[u];
-                dsc[u] = ndsc[u];
-            } else {
-                const int st = s + (u < nb ? u : nb - 1);
-                pk[u] = slots[(int64_t)st * 32 + (lane & 7) * 4 + ((lane >> 3) & 3)];
-                dsc[u] = desc2[(int64_t)st * 4 + kgroup];
-            }
+            const int st = step(s + u);
+            if constexpr (OWN) ask_words(st, words[u]);
+            if constexpr (NEED_PK) pk[u] = slots[(int64_t)st * 32 + (lane & 7) * 4 + ((lane >> 3) & 3)];
+            dsc[u] = desc2[(int64_t)st * 4 + kgroup];
         }
-        u32x4 RX[SB][LI][LW];
-        unsigned int vsel[SB];                   // per step, 8 bits per window: validity mask (the tap; KK: padding) | odd start << 7
-        i16x8 PW[SB];
-        unsigned int ext[SB];
+    };
+    auto ask_windows = [&](int s) {
         // window start of piece (u, i) for this lane, and the selector of its validity mask
+        const int own = cofs + tile_pos;
         auto piece = [&](int u, int i, unsigned int &sel) {
-            const unsigned int v = (unsigned int)__shfl((int)pk[u], i * RPI + rs);
+            const unsigned int v = OWN ? words[u][i] : (unsigned int)__shfl((int)pk[u], i * RPI + rs);
             sel = v >> 27;
-            return (int)(v & 0x7ffffffu) + cofs;
+            return (int)(v & 0x7ffffffu) + (OWN ? own : cofs);
         };
         // SAFE: the tile touches the first or last positions of the feature map, where a window can reach
         // outside it (first / last channel only); every other tile skips those checks altogether.
@@ -287,13 +301,13 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
             constexpr bool SAFE = decltype(safe_tag)::value;
 #pragma unroll
             for (int u = 0; u < SB; ++u) {
-                bool is_pad;
-                int eb;                          // window start for the tile's first position
-                if constexpr (PLAN) {            // already split when the plan was made
+                bool is_pad = false;
+                int eb = 0;                      // window start for the tile's first position
+                if constexpr (PLAN && NEED_PK) { // already split when the plan was made
                     is_pad = (int)(pk[u] >> 27) == p.KK;
                     eb = (int)(pk[u] & 0x7ffffffu) - (1 << 25) + tile_pos;
-                    pk[u] = (pk[u] & 0xf8000000u) | (unsigned int)(eb + (1 << 25));
-                } else {
+                    if constexpr (!OWN) pk[u] = (pk[u] & 0xf8000000u) | (unsigned int)(eb + (1 << 25));
+                } else if constexpr (!PLAN) {
                     is_pad = pk[u] == 0xffffffffu;
                     const unsigned int kk = is_pad ? 0u : pk[u];
                     // (24-bit multiplies: Cin, H * W, W and the tap numbers are all below 2^24)
@@ -309,13 +323,14 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                 // element is therefore fetched one element early; when the step is written the lane shifts it
                 // by 16 bits and takes its last element from the next lane's first dword.  The last lane of a
                 // row piece has no such neighbour: lanes 0..31 fetch the boundary element of their k slot with
-                // one extra 2-byte load per step, handed over by a lane permute.  (Stride 2: the window's 16 elements
+                // one extra 2-byte load per step, handed over by a lane permute (on 32-position tiles, whose form is all
+                // latency, the last lane asks for it itself).  (Stride 2: the window's 16 elements
                 // start at the even element below, and the even or the odd eight of them are the window.)
-                if constexpr (!S2) {
+                if constexpr (!S2 && !OWN_EXT) {
                     const int e7 = eb + (CPR - 1) * 8;
                     bool need = lane < 32 && !is_pad && (e7 & 1);
                     if constexpr (SAFE) need = need && e7 + 7 >= 0 && e7 + 7 < p.total;
-                    ext[u] = need ? (unsigned int)Fimg[e7 + 7] : 0u;
+                    ext[u][0] = need ? (unsigned int)Fimg[e7 + 7] : 0u;
                 }
             }
             bool edge_any = false;
@@ -329,6 +344,11 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                     const int odd = e0 & 1;
                     vsel[u] |= (sel | (unsigned int)odd << 7) << (8 * i);
                     int ea = e0 - odd;
+                    if constexpr (OWN_EXT) {
+                        bool need = c == CPR - 1 && odd != 0 && (int)sel != p.KK;
+                        if constexpr (SAFE) need = need && e0 + 7 >= 0 && e0 + 7 < p.total;
+                        ext[u][i] = need ? (unsigned int)Fimg[e0 + 7] : 0u;
+                    }
                     if constexpr (SAFE && !S2) {
                         const bool edge = e0 < 0 || e0 > emax;
                         edge_any |= edge;
@@ -350,6 +370,11 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
             }
             if constexpr (SAFE) {
                 if (__builtin_amdgcn_ballot_w64(edge_any)) {
+                    // (the words are read again: kept for this rare branch, they would not fit beside the windows)
+                    if constexpr (OWN) {
+#pragma unroll
+                        for (int u = 0; u < SB; ++u) ask_words(step(s + u), words[u]);
+                    }
 #pragma unroll
                     for (int u = 0; u < SB; ++u) {
 #pragma unroll
@@ -389,6 +414,29 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
             const i16x8 wv = pay[idx];
             PW[u] = kept ? wv : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
         }
+    };
+    // The first batch's headers, and where many waves split a strip its windows too, travel while the validity table is
+    // built: per (tap, piece of the tile) the 16-byte mask of the piece's 8 positions, a dword per thread; entry KK is all
+    // zero (padding slots).  (With four waves a second copy of the windows' code costs as much as their latency, which
+    // other workgroups hide: 1 x 1, 160 channels on eight 42 x 65 maps 15.8 us, 16.4 so.)
+    ask_headers(s_beg);
+    if (EIGHT && s_beg < s_end) ask_windows(s_beg);
+    for (int z = tid; z < (p.KK + 1) * CPR * 4; z += NWV * 64) {
+        const int e = z >> 2, tap = e / CPR, cc = e % CPR;
+        reinterpret_cast<unsigned int *>(vtab)[z] = conv_pair_mask<S2>(p, tap, n0 + cc * 8 + (z & 3) * 2, S2 ? p.Wp : p.W);
+    }
+    const float bias = p.bias && row >= 0 ? p.bias[row] : 0.f;
+    __syncthreads();
+    if (SOLO && !active) return;                 // (no barrier follows in that form)
+
+    f32x4 acc[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int s = s_beg; s < s_end; s += SB) {
+        const int nb = s_end - s < SB ? s_end - s : SB;
+        if (s != s_beg) ask_headers(s);
+        if (!EIGHT || s != s_beg) ask_windows(s);
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
@@ -411,7 +459,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
                         // the dword after the lane's four: the next lane's first one, or the boundary element
                         const unsigned int w0 = f[0];
                         const unsigned int nxt = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)w0, 0x101 /* row_shl:1 */, 0xf, 0xf, true);
-                        const unsigned int bnd = (unsigned int)__shfl((int)ext[u], i * RPI + rs);
+                        const unsigned int bnd = OWN_EXT ? ext[u][OWN_EXT ? i : 0] : (unsigned int)__shfl((int)ext[u][0], i * RPI + rs);
                         const unsigned int w4 = c == CPR - 1 ? bnd : nxt;
                         v = u32x4{__builtin_amdgcn_alignbit(f[1], w0, sh) & vm[0], __builtin_amdgcn_alignbit(f[2], f[1], sh) & vm[1],
                                   __builtin_amdgcn_alignbit(f[3], f[2], sh) & vm[2], __builtin_amdgcn_alignbit(w4, f[3], sh) & vm[3]};

@@ -65,6 +65,9 @@ __device__ __forceinline__ int swizzle(int row) {
     return CPR == 8 ? (((row >> 1) & 3) << 1) : CPR > 8 ? ((row & 3) << 1) : (((row >> 1) & 1) << 1);
 }
 
+// first of the `nst` steps of a strip (below 2^28) that wave `wave` of `waves` takes
+__device__ __forceinline__ int wave_share(int nst, int wave, int waves) { return (int)((unsigned int)nst * (unsigned int)wave / (unsigned int)waves); }
+
 // 16 bytes of X at any 2-byte alignment: a single access on this GPU
 __device__ __forceinline__ u32x4 load_piece_any(const unsigned short *src) {
     struct __attribute__((packed, aligned(2))) { unsigned int d[4]; } v;

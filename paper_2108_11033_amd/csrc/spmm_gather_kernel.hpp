@@ -145,8 +145,8 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     }
     // one dependent memory round trip less at the start when every run has the same number of steps
     const int g0 = usteps ? t * usteps : sptr[t], nst = usteps ? usteps : sptr[t + 1] - g0;
-    const int s_beg = SOLO ? g0 : g0 + (int)((int64_t)nst * wave / NWV);
-    const int s_end = SOLO ? g0 + nst : g0 + (int)((int64_t)nst * (wave + 1) / NWV);
+    const int s_beg = SOLO ? g0 : g0 + wave_share(nst, wave, NWV);
+    const int s_end = SOLO ? g0 + nst : g0 + wave_share(nst, wave + 1, NWV);
     char *buf = lds + wave * gather_wave_lds(NT);    // two step buffers of 32 rows x TN columns
 
     // fetch side: lane = (row slot rs, 16-byte piece c); its i-th load is k slot i * RPI + rs

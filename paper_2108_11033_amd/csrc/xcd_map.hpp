@@ -6,6 +6,15 @@
 
 namespace grim {
 
+// n / d for 0 <= n < 2^31 with `inverse` = divide_inverse(d), made on the host: a launch's numbers are uniform, and a division by
+// a run-time value takes the scalar unit thirty instructions and a trip to the vector ALU and back.  The product is short of
+// the quotient by one at most: the inverse is short of 2^32 / d by less than two, n below 2^31.
+inline uint32_t divide_inverse(int32_t d) { return 0xffffffffu / (uint32_t)(d > 0 ? d : 1); }
+GRIM_HOST_DEVICE int divide_by(int n, int d, uint32_t inverse) {
+    const int q = (int)(((uint64_t)(uint32_t)n * inverse) >> 32);
+    return q + (n - q * d >= d ? 1 : 0);
+}
+
 // Workgroup id -> (tile of columns, unit of the tile's work) for the kernels whose workgroups of one
 // tile fetch the same rows: ids are dealt to the 8 XCDs round-robin, each XCD has its own L2, so a
 // tile's units go to one XCD.  With that alone the last ntiles % 8 tiles (all of them when there
@@ -17,6 +26,7 @@ struct XcdMap {
     int32_t tail_tile0;       // first tail tile, a multiple of 8
     int32_t shift;            // tail tiles are cut into 1 << shift parts ...
     int32_t per_part;         // ... of this many units
+    uint32_t per_tile_inv, per_part_inv;
 };
 inline XcdMap xcd_map(int32_t ntiles, int64_t per_tile, int64_t *nwg) {
     XcdMap m;
@@ -26,6 +36,8 @@ inline XcdMap xcd_map(int32_t ntiles, int64_t per_tile, int64_t *nwg) {
     m.tail_tile0 = full * 8;
     m.shift = r == 0 ? 0 : r % 4 == 0 ? 1 : r % 2 == 0 ? 2 : 3;
     m.per_part = (int32_t)((per_tile + (1 << m.shift) - 1) >> m.shift);
+    m.per_tile_inv = divide_inverse(m.per_tile);
+    m.per_part_inv = divide_inverse(m.per_part);
     *nwg = 8 * (full * per_tile + (int64_t)((r << m.shift) / 8) * m.per_part);
     return m;
 }
@@ -44,14 +56,16 @@ inline XcdMap xcd_map_one_tile(int64_t units, int64_t *nwg) {
 GRIM_HOST_DEVICE bool xcd_map_at(const XcdMap &m, int id, int ntiles, int *tile, int *unit) {
     const int xcd = id & 7, slot = id >> 3;
     if (slot < m.tail_slot0) {
-        *tile = (slot / m.per_tile) * 8 + xcd;
-        *unit = slot % m.per_tile;
+        const int q = divide_by(slot, m.per_tile, m.per_tile_inv);
+        *tile = q * 8 + xcd;
+        *unit = slot - q * m.per_tile;
         return true;
     }
     const int s2 = slot - m.tail_slot0;
-    const int part = (s2 / m.per_part) * 8 + xcd;
+    const int q = divide_by(s2, m.per_part, m.per_part_inv);
+    const int part = q * 8 + xcd;
     *tile = m.tail_tile0 + (part >> m.shift);
-    *unit = ((s2 % m.per_part) << m.shift) + (part & ((1 << m.shift) - 1));
+    *unit = ((s2 - q * m.per_part) << m.shift) + (part & ((1 << m.shift) - 1));
     return *tile < ntiles;
 }
 
