@@ -16,9 +16,9 @@ namespace grim {
 // barrier until the partial tiles are added.  A step is 32 k values = four (tap, channel octet) pairs: 16 multiplies for 4 KB
 // of weights out of L2 and 4 KB of pixels out of LDS.
 //
-// 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 blocks 16.5 -> 11.2 us (1.9 of them multiplies at the matrix cores' rate,
-// 4 the launch), 448 on seven 52 x 12 maps 40 -> 25.7, the same from 103 x 24 at stride 2 118 -> 36.  Bound by the multiplies of a
-// compute unit's waves and the latency of a chunk's pixels before them; more pixels per task (eight channels) take registers that
+// 256 channels, 3 x 3, four 28 x 28 maps in 4 x 16 blocks 16.5 -> 11.1 us (1.9 of them multiplies at the matrix cores' rate,
+// 4 the launch), 448 on seven 52 x 12 maps 40 -> 25.7, the same from 103 x 24 at stride 2 118 -> 36.  Bound by what a compute unit takes
+// in (295 KB of weights and 65 KB of pixels at some 30 bytes a cycle, from its first cycles on) and the multiplies of its waves; more pixels per task (eight channels) take registers that
 // spill, two steps of weights in flight instead of three cost 4 %.
 //
 // Sums: the steps are all of K, not what a run keeps, so a plain fp32 chain over a wave's steps would be up to four times as long
@@ -37,9 +37,13 @@ struct ConvPatchParams : ConvTallParams {
     int32_t zero_at;                 // byte offset of the pixel of zeros
     int32_t wave_lds;                // bytes per wave
     int32_t chain, settlings;        // LONG: steps to a chain, chains of the longest wave but for its last
+    uint32_t wo_inv;                 // divide_by: Wo
+    uint32_t row_ones;               // bit r * kw of every kernel row r
 };
 
-constexpr int kPatchDepth = 3;                             // steps of weights in flight
+// steps of weights in flight (five: 11.5 where this takes 11.2; a compute unit's weights, 295 KB for 256 channels, 3 x 3, come at
+// some 30 bytes a cycle however early they are asked for)
+constexpr int kPatchDepth = 3;
 constexpr int kPatchChain = 12;                            // steps whose sums follow one another in fp32, to the group that ends them
 
 // LONG: a wave has more than kPatchChain steps (its totals take the registers of a third task asked for ahead)
@@ -48,12 +52,17 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     constexpr int R = kConvTallRuns, NT = 4, TN = 64, SB = patch_pixel_bytes(CO);
     constexpr int D = kPatchDepth, AHEAD = LONG ? 2 : 3;    // tasks of a chunk asked for ahead, in 64s: as the registers allow
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    // (the arguments in one trip through the scalar cache, as in bcr_conv_gather)
+    asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
+                 "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.tiles_per_img), "s"(p.tiles_inv), "s"(p.nbr),
+                 "s"(p.F), "s"(p.f_img_stride), "s"(p.Nv), "s"(p.W), "s"(p.Wo), "s"(p.wo_inv), "s"(p.N), "s"(p.stride), "s"(p.kh), "s"(p.kw),
+                 "s"(p.cin), "s"(p.chunks), "s"(p.steps), "s"(p.dense), "s"(p.wave_lds), "s"(p.out_row));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile, t;
     if (!xcd_map_at(p.map, blockIdx.x, p.ntiles, &tile, &t) || t >= p.nbr) return;
-    const int img = __builtin_amdgcn_readfirstlane(tile / p.tiles_per_img);
-    tile = __builtin_amdgcn_readfirstlane(tile - img * p.tiles_per_img);
+    const int img = divide_by(tile, p.tiles_per_img, p.tiles_inv);
+    tile -= img * p.tiles_per_img;
     const unsigned short *Fimg = p.F + (int64_t)img * p.f_img_stride;
     int n0 = tile * TN;
     if (n0 + TN > p.Nv) n0 = p.Nv - TN;                    // ragged last tile: overlap the neighbour
@@ -71,16 +80,11 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
 #pragma unroll
         for (int m = 0; m < R; ++m) w[m] = src[m * 64 + lane];
     };
-    if (c_beg < c_end) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) fetch_weights(PW[u], c_beg, u);
-    }
-
     // the pixels (of a channel) that a tap of the tile's positions can meet: [plo, phi]
     const int HW = p.N, centre = (p.kh >> 1) * p.W + (p.kw >> 1), fodd = (int)(reinterpret_cast<uintptr_t>(Fimg) >> 1) & 1;
     const bool s2 = p.stride == 2;
-    const int plo = __builtin_amdgcn_readfirstlane(patch_first(n0, p.W, p.Wo, s2, centre, HW, fodd));
-    const int phi = __builtin_amdgcn_readfirstlane(patch_last(n0, p.Nv, p.W, p.Wo, s2, centre, HW));
+    const int plo = patch_first(n0, p.W, p.Wo, p.wo_inv, s2, centre, HW, fodd);
+    const int phi = patch_last(n0, p.Nv, p.W, p.Wo, p.wo_inv, s2, centre, HW);
     const int tasks = ((phi - plo) / 8 + 1) * CO * 2;      // (eight pixels of four channels) to turn around per chunk
 
     f32x4 acc[R][NT], tot[R][NT];
@@ -179,7 +183,12 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
         }
         __builtin_amdgcn_wave_barrier();
     };
-    if (c_beg < c_end) ask_patch(c_beg);
+    // the first pixels, and the weights behind them (loads return in order, and the pixels are wanted first)
+    if (c_beg < c_end) {
+        ask_patch(c_beg);
+#pragma unroll
+        for (int u = 0; u < D; ++u) fetch_weights(PW[u], c_beg, u);
+    }
 
     // per sub-tile: where the lane's position lies in the patch (centre tap, the lane's octet) and which taps see the image
     const int octet = kgroup % CO;
@@ -189,15 +198,13 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     for (int q = 0; q < NT; ++q) {
         const int n = n0 + q * 16 + i16;
         int hh, ww;
-        const int pix = patch_pixel_of(n < p.Nv ? n : p.Nv - 1, p.W, p.Wo, s2, &hh, &ww);
+        const int pix = patch_pixel_of(n < p.Nv ? n : p.Nv - 1, p.W, p.Wo, p.wo_inv, s2, &hh, &ww);
         at[q] = (pix - plo) * SB + octet * 16;
         const int wlo = (p.kw >> 1) - ww, whi = p.W - ww + (p.kw >> 1);            // taps of a kernel row: [wlo, whi)
         const unsigned int cols = ((1u << (whi < p.kw ? whi : p.kw)) - 1u) & ~((1u << (wlo > 0 ? wlo : 0)) - 1u);
-        sees[q] = 0u;
-        for (int r = 0; r < p.kh; ++r) {
-            const int y = hh + r - (p.kh >> 1);
-            sees[q] |= y >= 0 && y < p.H ? cols << (r * p.kw) : 0u;
-        }
+        const int rlo = (p.kh >> 1) - hh, rhi = p.H - hh + (p.kh >> 1);            // kernel rows: [rlo, rhi)
+        const unsigned int rows = p.row_ones & ((1u << (rhi < p.kh ? rhi : p.kh) * p.kw) - 1u) & ~((1u << (rlo > 0 ? rlo : 0) * p.kw) - 1u);
+        sees[q] = cols * rows;                             // (cols has kw bits: its copies do not meet)
     }
     const int zero_at = p.zero_at + octet * 16;
     if (lane < CO) *reinterpret_cast<u32x4 *>(patch + p.zero_at + lane * 16) = u32x4{0u, 0u, 0u, 0u};
@@ -218,6 +225,8 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
             for (int m = 0; m < R; ++m) acc[m][q] = mfma16<BF16>(x[q], w[m], acc[m][q]);
     };
     int since = 0, settled = 0;                            // steps since the last settling, settlings
+    // (Leaving out the last group's requests, which nobody waits for, in a copy of the group behind the loop costs more than they do:
+    // 448 channels on seven 52 x 12 maps 25.7 us, 26.9 so.)
     for (int chunk = c_beg; chunk < c_end; ++chunk) {
         take_patch(chunk);
         if (chunk + 1 < c_end) ask_patch(chunk + 1);
@@ -327,6 +336,10 @@ grim_status launch_conv_patch(const grim_bcr_matrix *A, const ConvDense &L, cons
     p.map = xcd_map(p.ntiles, p.nbr, &nwg);
     if (nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
     const int waves = patch_waves(p.ntiles, p.nbr);
+    p.wo_inv = divide_inverse(p.Wo);
+    p.tiles_inv = divide_inverse(p.tiles_per_img);
+    p.row_ones = 0;
+    for (int r = 0; r < kh; ++r) p.row_ones |= 1u << (r * kw);
     p.wave_lds = p.zero_at + patch_pixel_bytes(L.octets);
     p.wave_lds = p.wave_lds < kConvTallRuns * 4096 ? kConvTallRuns * 4096 : p.wave_lds;       // the partial tiles go there later
     const size_t lds = (size_t)waves * p.wave_lds;

@@ -34,8 +34,8 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile, t;
     if (!xcd_map_at(p.map, blockIdx.x, p.ntiles, &tile, &t) || t >= p.nbr) return;
-    const int img = __builtin_amdgcn_readfirstlane(tile / p.tiles_per_img);
-    tile = __builtin_amdgcn_readfirstlane(tile - img * p.tiles_per_img);
+    const int img = divide_by(tile, p.tiles_per_img, p.tiles_inv);
+    tile -= img * p.tiles_per_img;
     const unsigned short *Fimg = p.F + (int64_t)img * p.f_img_stride;
     int n0 = tile * TN;
     if (n0 + TN > p.Nv) n0 = p.Nv - TN;          // ragged last tile: overlap the neighbour
@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
 
     const char *Fb = reinterpret_cast<const char *>(Fimg);
     const int emax = p.total - 8, centre = (p.kh >> 1) * p.W + (p.kw >> 1);
-    auto pos_off = [&](int cc) { return conv_piece_start<S2>(n0 + cc * 8, p.W, p.Ho, p.Wp); };       // as in bcr_conv_gather
+    auto pos_off = [&](int cc) { return conv_piece_start<S2>(n0 + cc * 8, p.W, p.Ho, p.Wp, p.row_inv); };       // as in bcr_conv_gather
     const int tile_pos = S2 ? __builtin_amdgcn_readfirstlane(pos_off(0)) : n0;
     const int cofs = (S2 ? pos_off(c) - tile_pos : c * 8) - (1 << 25);
     bool tile_edge = conv_tile_at_edge<S2>(pos_off(0), pos_off(CPR - 1), centre, p.N);
@@ -283,6 +283,7 @@ grim_status launch_conv_tall(const grim_bcr_matrix *A, const GatherLayout &L, co
     p.nbr = (int32_t)L.nstrips;
     p.usteps = L.usteps;
     p.tiles_per_img = (p.Nv + 63) / 64;
+    p.tiles_inv = divide_inverse(p.tiles_per_img);
     p.ntiles = p.tiles_per_img * batch;
     int64_t nwg = 0;
     p.map = xcd_map(p.ntiles, p.nbr, &nwg);

@@ -8,26 +8,35 @@
 
 namespace grim {
 
-// Pixel (of a channel) under the centre tap of output position n, and its row and column
-GRIM_HOST_DEVICE int patch_pixel_of(int n, int W, int Wo, bool s2, int *h, int *w) {
-    const int ho = n / Wo;
+// Pixel (of a channel) under the centre tap of output position n, and its row and column; wo_inverse: divide_inverse(Wo)
+GRIM_HOST_DEVICE int patch_pixel_of(int n, int W, int Wo, uint32_t wo_inverse, bool s2, int *h, int *w) {
+    const int ho = divide_by(n, Wo, wo_inverse);
     *h = ho << (s2 ? 1 : 0);
     *w = (n - ho * Wo) << (s2 ? 1 : 0);
     return *h * W + *w;
 }
+GRIM_HOST_DEVICE int patch_pixel_of(int n, int W, int Wo, bool s2, int *h, int *w) {
+    return patch_pixel_of(n, W, Wo, 0xffffffffu / (uint32_t)Wo, s2, h, w);
+}
 
 // The first and last pixel that a tap of positions [n0, n0 + 64) can meet; `odd`: the map starts at an odd element (the
 // first pixel is moved to an even one where there is one, and there are eight from it on)
-GRIM_HOST_DEVICE int patch_first(int n0, int W, int Wo, bool s2, int centre, int HW, int odd) {
+GRIM_HOST_DEVICE int patch_first(int n0, int W, int Wo, uint32_t wo_inverse, bool s2, int centre, int HW, int odd) {
     int h, w;
-    int lo = patch_pixel_of(n0, W, Wo, s2, &h, &w) - centre;
+    int lo = patch_pixel_of(n0, W, Wo, wo_inverse, s2, &h, &w) - centre;
     lo = lo < 0 ? 0 : lo > HW - 8 ? HW - 8 : lo;
     return lo - (lo > 0 ? (odd + lo) & 1 : 0);
 }
-GRIM_HOST_DEVICE int patch_last(int n0, int Nv, int W, int Wo, bool s2, int centre, int HW) {
+GRIM_HOST_DEVICE int patch_last(int n0, int Nv, int W, int Wo, uint32_t wo_inverse, bool s2, int centre, int HW) {
     int h, w;
-    const int hi = patch_pixel_of(n0 + 64 < Nv ? n0 + 63 : Nv - 1, W, Wo, s2, &h, &w) + centre;
+    const int hi = patch_pixel_of(n0 + 64 < Nv ? n0 + 63 : Nv - 1, W, Wo, wo_inverse, s2, &h, &w) + centre;
     return hi < HW - 1 ? hi : HW - 1;
+}
+GRIM_HOST_DEVICE int patch_first(int n0, int W, int Wo, bool s2, int centre, int HW, int odd) {
+    return patch_first(n0, W, Wo, 0xffffffffu / (uint32_t)Wo, s2, centre, HW, odd);
+}
+GRIM_HOST_DEVICE int patch_last(int n0, int Nv, int W, int Wo, bool s2, int centre, int HW) {
+    return patch_last(n0, Nv, W, Wo, 0xffffffffu / (uint32_t)Wo, s2, centre, HW);
 }
 
 // The most pixels any tile spans, in whole eights

@@ -148,3 +148,11 @@ def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
     for sets in range(1, 33):
         for wgs in (1, 2, 3, 7, 8, 31, 32, 64):
             assert excess(sets, wgs) == 0, (sets, wgs)
+
+
+def test_division_by_an_inverse_made_beforehand(tmp_path):
+    """Quotients around multiples of the divisor, up to the largest numbers a launch can hold, are those of the division."""
+    faults = _host_library(tmp_path, "divide").divide_faults
+    for d in list(range(1, 70)) + [127, 128, 129, 196, 255, 1000, 3136, 4097, 65535, 65536, 65537, 1 << 24, (1 << 30) + 1, (1 << 31) - 1]:
+        for k in [0, 1, 2, 3, 100, 65535, 65536] + [(((1 << 31) - 1) // d) * f // 7 for f in range(8)]:
+            assert faults(min(k * d, (1 << 31) - 1), d) == 0, (k, d)
