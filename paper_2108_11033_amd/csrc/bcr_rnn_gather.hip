@@ -47,6 +47,9 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int run = wave / WPR, share = wave % WPR, mi = CELL == 2 ? run / 3 : 0, gate = CELL == 2 ? run % 3 : run;
     const RnnGatherMatrix &A = p.m[mi];
+    // (the arguments in one trip through the scalar cache, as in bcr_spmm_gather)
+    asm volatile("" ::"s"(A.sptr), "s"(A.rows), "s"(A.desc), "s"(A.payload), "s"(A.strip_pos), "s"(A.X), "s"(A.ldx), "s"(A.usteps), "s"(A.K),
+                 "s"(A.BR), "s"(p.H), "s"(p.N), "s"(p.state), "s"(p.lds), "s"(p.bias), "s"(p.bias2));
     const int unit0 = blockIdx.x * 16, n0 = blockIdx.y * 16, N = p.N;
     // stored run of the 16 gate rows from original row `row` on (in one strip, or strips stored in original order)
     auto stored_run = [&](const RnnGatherMatrix &M, int row) {

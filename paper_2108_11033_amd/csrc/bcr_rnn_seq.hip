@@ -91,21 +91,6 @@ __device__ __forceinline__ unsigned int seq_xcd() {
     return (unsigned int)__builtin_amdgcn_s_getreg(20 | 31 << 11) & 15u;    // the whole of hardware register 20, XCC_ID
 }
 
-// v + v of the lane 32 (16) further round, without a trip through LDS: the swap of a register with a copy of itself leaves
-// the lower halves (even quarters) of v in one and the upper (odd) in the other
-__device__ __forceinline__ float seq_halves(float v) {
-    const unsigned int a = __builtin_bit_cast(unsigned int, v);
-    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
-    const unsigned int lower = r[0], upper = r[1];
-    return __builtin_bit_cast(float, lower) + __builtin_bit_cast(float, upper);
-}
-__device__ __forceinline__ float seq_quarters(float v) {
-    const unsigned int a = __builtin_bit_cast(unsigned int, v);
-    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
-    const unsigned int even = r[0], odd = r[1];
-    return __builtin_bit_cast(float, even) + __builtin_bit_cast(float, odd);
-}
-
 // MULTI: a workgroup carries more than one sequence.  PLACED: every set of workgroups on an XCD of its own (1-D grid);
 // otherwise grid.y is the set.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
 template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
@@ -448,14 +433,14 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     s += v[q].x;
                     s += v[q].y;
                 }
-                return seq_halves(seq_quarters(s));
+                return lane_halves(lane_quarters(s));
             }
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
                 s += v[q].x;
                 s += v[q].y;
             }
-            return seq_halves(s);
+            return lane_halves(s);
         };
         for (int bs = 0; bs < B; bs += NS) {
             float acc[NS][KR];

@@ -48,6 +48,10 @@ __global__ void __launch_bounds__(NWV * 64, 4) bcr_spmm_gather32(Gather32Params 
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
     __shared__ f32x4 red[SOLO ? 1 : NWV * NT * 64];
     __shared__ int odd_values[NWV];              // per wave: it met an infinity or NaN
+    // (the arguments in one trip through the scalar cache, as in bcr_spmm_gather)
+    asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
+                 "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.nbr), "s"(p.usteps), "s"(p.sptr), "s"(p.out_row),
+                 "s"(p.rows), "s"(p.desc), "s"(p.payload), "s"(p.X), "s"(p.N), "s"(p.ldx), "s"(p.K));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile, unit;

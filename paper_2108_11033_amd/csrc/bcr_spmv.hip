@@ -236,6 +236,11 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_spmv_wave_exact(Ge
     constexpr int PB = exact_pad_period(NV);     // one vector of padding after every PB blocks (0: none)
     static_assert(KR * KC * ESZ % 16 == 0 && (ESZ == 4 || KC % 2 == 0) && KC <= 32 && KR <= 32, "block shape");
     extern __shared__ __attribute__((aligned(16))) char smem[];
+    // (what the prologue needs of the arguments in one trip through the scalar cache: asked for where each is first used, the
+    // trips follow one another)
+    asm volatile("" ::"s"(p.table), "s"(p.single.weights), "s"(p.single.masks), "s"(p.single.strip_order), "s"(p.x), "s"(p.y), "s"(p.x_stride),
+                 "s"(p.K), "s"(p.nbc), "s"(p.BC), "s"(p.BR), "s"(p.seg_blocks), "s"(p.xvec16), "s"(p.sps), "s"(p.wpg), "s"(p.nbr_total), "s"(p.wbytes),
+                 "s"(p.ldx));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // GRU: both input vectors sit in LDS, the hidden-side one behind the input-side one
@@ -354,10 +359,11 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_spmv_wave_exact(Ge
         auto src_of = [&](int v) { return v < nxv1 ? xsrc + v : xsrc2 + (v - nxv1); };
         // unit u of a vector goes 4 bytes further for every block before its own: four 4-byte stores
         const int upb = p.BC * ESZ / 16;                           // 16-byte units per block (padded layout only)
+        const int upb_shift = upb > 0 && (upb & (upb - 1)) == 0 ? __builtin_ctz(upb) : -1;        // (a power of two: no division per unit)
         auto put = [&](int v, const gu32x4 &val) {
             const int u = v < nxv1 ? v : v - nxv1;
             unsigned int *dst = reinterpret_cast<unsigned int *>(reinterpret_cast<char *>(xs0) + (v < nxv1 ? 0 : xbytes1)) +
-                                u * 4 + (xsk ? u / upb : 0);
+                                u * 4 + (xsk ? (upb_shift >= 0 ? u >> upb_shift : u / upb) : 0);
             dst[0] = val[0];
             dst[1] = val[1];
             dst[2] = val[2];
@@ -519,8 +525,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_spmv_wave_exact(Ge
                     s += v.y;
                 }
             }
-            const float s2 = s + __shfl_xor(s, 16);
-            rs = s2 + __shfl_xor(s2, 32);
+            rs = lane_halves(lane_quarters(s));
         } else {
             float s = 0.f;
             if (r_out < p.BR) {
@@ -532,7 +537,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_spmv_wave_exact(Ge
                     s += v.y;
                 }
             }
-            rs = s + __shfl_xor(s, 32);
+            rs = lane_halves(s);
         }
         yacc += rs;                                               // the same value in every lane group
         __builtin_amdgcn_wave_barrier();                          // table consumed before the next item refills LDS

@@ -100,6 +100,11 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     constexpr bool WATCH = NARROW || !ALIGNED;
     constexpr int SB = STEPS ? STEPS : NARROW ? gather_narrow_steps(NT) : NT == 2 || (WATCH && !EIGHT) ? 3 : 4;
     static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
+    // (what the prologue needs of the arguments in one trip through the scalar cache: asked for where each is first used, the
+    // trips follow one another)
+    asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
+                 "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.nbr), "s"(p.usteps), "s"(p.sptr), "s"(p.out_row),
+                 "s"(p.rows), "s"(p.desc), "s"(p.payload), "s"(p.X), "s"(p.N), "s"(p.ldx), "s"(p.K));
     // workgroup -> (tile, stored strip, or four of them for SOLO)
     const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile, unit;

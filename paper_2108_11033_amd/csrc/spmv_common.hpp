@@ -98,6 +98,21 @@ constexpr int kPartStride = 66;                    // floats per strip row of th
 // a 16-byte unit of the copy may not straddle two blocks.)  Elements of padding per block:
 __host__ __device__ inline int exact_x_skew(int BC, int esz) { return (BC * esz) % 16 == 0 ? 4 / esz : 0; }
 
+// v + v of the lane 32 (16) further round, without a trip through LDS: the swap of a register with a copy of itself leaves
+// the lower halves (even quarters) of v in one and the upper (odd) in the other
+__device__ __forceinline__ float lane_halves(float v) {
+    const unsigned int a = __builtin_bit_cast(unsigned int, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const unsigned int lower = r[0], upper = r[1];
+    return __builtin_bit_cast(float, lower) + __builtin_bit_cast(float, upper);
+}
+__device__ __forceinline__ float lane_quarters(float v) {
+    const unsigned int a = __builtin_bit_cast(unsigned int, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const unsigned int even = r[0], odd = r[1];
+    return __builtin_bit_cast(float, even) + __builtin_bit_cast(float, odd);
+}
+
 // Lanes read their blocks with 16-byte loads at a common offset from bases NV vectors apart;
 // 16 such vectors span the LDS banks.  When NV shares a factor g with 16 the bases of 16
 // neighbouring lanes fall on only 16/g distinct bank groups, so one vector of padding goes
