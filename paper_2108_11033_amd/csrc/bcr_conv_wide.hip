@@ -21,7 +21,8 @@ constexpr int kConvWideRestTile = 32;
 
 static size_t conv_wide_lds(const grim_bcr_matrix *A, int tn, int KK) {
     // two stages; kConvAnyTap: the (tap, piece) mask table, four per-chunk row tables
-    const size_t stages = 2 * (size_t)wide_stage_bytes(A->mmaw.chunk_rows, tn, A->mmaw.amax[2]);
+    const size_t out = A->BR == 32 ? wide_out_bytes(tn) : 0;      // the outputs' way through LDS, when the stages are done with
+    const size_t stages = std::max(2 * (size_t)wide_stage_bytes(A->mmaw.chunk_rows, tn, A->mmaw.amax[2]), out);
     if (conv_tap_ways(tn, KK, A->mmaw.chunk_rows)) return stages;
     return stages + (size_t)(KK + 1) * (tn / 8) * 16 + 4 * (size_t)wide_max_chunk_rows(A->BR) * 8;
 }
@@ -176,6 +177,7 @@ grim_status launch_conv_wide(const grim_bcr_matrix *A, const void *F, int32_t Ci
     p.y_img_stride = batch > 1 ? y_img_stride : 0;
     p.bias = bias; p.relu = relu; p.odt = odt;
     p.y_vec4 = reinterpret_cast<uintptr_t>(Y) % 8 == 0 && ldy % 4 == 0 && p.y_img_stride % 4 == 0 ? 1 : 0;
+    p.y_vec8 = reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 8 == 0 && p.y_img_stride % 8 == 0 ? 1 : 0;
     const int tn = conv_wide_main_tile(A, p.KK);
     const int64_t per_round = 256 / p.ngroups;
     const int64_t n_main = N / tn / per_round * per_round * tn;

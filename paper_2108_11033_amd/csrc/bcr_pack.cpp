@@ -58,6 +58,7 @@ bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks
     // the kept columns of a (chunk, strip), one after the other whatever block they belong to
     struct Slot { int64_t t, w; uint32_t mask; int32_t kc; uint16_t row; };   // stored block, its column's first weight, its rows; staged row
     std::vector<Slot> slots;
+    slots.reserve((size_t)chunk_blocks * A->BC);
     int64_t step = 0;
     const uint16_t *w = reinterpret_cast<const uint16_t *>(A->weights.data());
     const uint16_t zero_row = (uint16_t)L.chunk_rows;
@@ -109,11 +110,10 @@ bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks
                         for (int32_t i = 0; i < kr; ++i)
                             for (int32_t e = 0; e < n; ++e) pw[i * 8 + e] = w[gs[e].w + (int64_t)i * gs[e].kc];
                     } else {
-                        int32_t i = 0;
-                        for (uint32_t m = rowmask; m; m &= m - 1, ++i) {
-                            const uint32_t bit = m & (0u - m);
-                            for (int32_t e = 0; e < n; ++e)
-                                if (gs[e].mask & bit) pw[i * 8 + e] = w[gs[e].w + (int64_t)__builtin_popcount(gs[e].mask & (bit - 1)) * gs[e].kc];
+                        for (int32_t e = 0; e < n; ++e) {
+                            const uint16_t *src = w + gs[e].w;
+                            for (uint32_t m = gs[e].mask; m; m &= m - 1, src += gs[e].kc)
+                                pw[__builtin_popcount(rowmask & ((m & (0u - m)) - 1)) * 8 + e] = *src;
                         }
                     }
                     pay16 += (uint32_t)kr;

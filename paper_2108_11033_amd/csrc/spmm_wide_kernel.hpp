@@ -34,7 +34,7 @@ struct WideParams {
     int64_t y_img_stride;        // elements between the [M][ldy] outputs of two images
     const float *bias;           // M values added to every position of a row, or null
     int32_t relu, odt;           // max(., 0) after the bias; element type of Y
-    int32_t y_vec4;              // four consecutive 16-bit outputs of a row can be stored at once
+    int32_t y_vec4, y_vec8;      // four, eight consecutive 16-bit outputs of a row can be stored at once
 };
 
 // fp32 -> bf16, round to nearest even; NaN stays NaN
@@ -43,6 +43,19 @@ __device__ __forceinline__ unsigned short wide_f32_to_bf16(float f) {
     if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (unsigned short)(u >> 16);
+}
+
+// two values rounded to a 16-bit type, nearest even, NaN stays NaN: one instruction on this GPU
+template <int ODT>
+__device__ __forceinline__ unsigned int wide_pair(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    if constexpr (ODT == GRIM_BF16) {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(unsigned int, __builtin_convertvector((f32x2{a, b}), bf16x2));
+    } else {
+        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(unsigned int, __builtin_convertvector((f32x2{a, b}), f16x2));
+    }
 }
 
 // 16 bytes of a feature map at any 2-byte alignment
@@ -68,6 +81,11 @@ constexpr int wide_gcd(int a, int b) { return b == 0 ? a : wide_gcd(b, a % b); }
 __host__ __device__ inline int wide_stage_bytes(int chunk_rows, int tn, int amax) {
     return (chunk_rows + 1) * (tn * 2 + kWidePad) + amax * 16;
 }
+
+// Bytes between the rows of a strip's 16-bit outputs where they pass through LDS (32-row strips), and LDS for all of them: 16
+// bytes of padding put the two rows a write names on different banks.
+constexpr int wide_out_pitch(int tn) { return tn * 2 + 16; }
+constexpr int wide_out_bytes(int tn) { return kWideMulWaves * 32 * wide_out_pitch(tn); }
 
 // How the convolution's rows of a chunk are dealt to the fetching threads.
 //   kConvAnyTap: 16-byte units in order; the row's channel and tap and the unit's validity mask come out of tables in LDS.
@@ -662,6 +680,53 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     // type is chosen once and a strip's biases are fetched before its first store: stores and loads share a counter, so a
     // bias fetched between two stores is waited for behind the stores (512 channels, 3 x 3, eight 56 x 56 maps: 107 -> 88 us; 1 x 1, 512 -> 256
     // channels on five 112 x 112 maps in 16-row blocks, whose four 16-bit outputs of a row are one store: 69 -> 44).
+    //
+    // 16-bit outputs of 32-row strips: a lane's 16 sums of a sub-tile are one column of 16 rows.  Stored as they stand they are
+    // 96 stores of 64 bytes a row with as many addresses, and the rounding to bf16 six instructions a value: 5 of the 74 us
+    // of the layer above, all of it instructions.  A strip goes through LDS, idle by now, and leaves in 16-byte pieces.
+    auto finish_through_lds = [&](auto out_type) {
+        constexpr int ODT = decltype(out_type)::value;
+        constexpr int OP = wide_out_pitch(TN), PIECES = TN / 8, RPP = 64 / PIECES;        // pieces of a row, rows per pass
+        char *const mine = lds + wave * (32 * OP);
+        const int c = lane % PIECES, r = lane / PIECES;
+        const unsigned int n = (unsigned int)n0 + c * 8, img = n / (unsigned int)p.HW;     // (a piece lies in one image)
+        unsigned short *const Y = reinterpret_cast<unsigned short *>(p.Y) + img * p.y_img_stride + (n - img * (unsigned int)p.HW);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int t = s == 0 ? tA : tB;
+            if (t >= p.nbr) continue;
+            const int64_t row0 = (int64_t)p.strip_order[t] * BR;
+            float bias[16] = {};
+            if (p.bias) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) bias[e] = p.bias[row0 + 4 * (lane >> 5) + 8 * (e >> 2) + (e & 3)];
+            }
+            char *const at = mine + 4 * (lane >> 5) * OP + (lane & 31) * 2;
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) {
+                    float v[2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        v[k] = acc[s][q][e + k] + bias[e + k];
+                        if (p.relu) v[k] = __builtin_elementwise_maximum(v[k], 0.f);       // NaN stays NaN
+                    }
+                    const unsigned int two = wide_pair<ODT>(v[0], v[1]);
+                    char *const to = at + 8 * (e >> 2) * OP + (e & 3) * OP + q * 64;
+                    *reinterpret_cast<unsigned short *>(to) = (unsigned short)two;
+                    *reinterpret_cast<unsigned short *>(to + OP) = (unsigned short)(two >> 16);
+                }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k * RPP < 32; ++k) {
+                const int row = r + k * RPP;
+                if (row < 32 && r < RPP)
+                    *reinterpret_cast<u32x4 *>(Y + (row0 + row) * p.ldy) = *reinterpret_cast<const u32x4 *>(mine + row * OP + c * 16);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
     auto finish = [&](auto out_type) {
         constexpr int ODT = decltype(out_type)::value;
         using Out = typename Elem<ODT>::type;
@@ -736,6 +801,13 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     };
     if (!CONV || p.odt == GRIM_F32) finish(std::integral_constant<int, GRIM_F32>{});
     else if constexpr (CONV) {
+        if constexpr (BR == 32) {
+            if (p.y_vec8) {
+                if (p.odt == GRIM_F16) finish_through_lds(std::integral_constant<int, GRIM_F16>{});
+                else finish_through_lds(std::integral_constant<int, GRIM_BF16>{});
+                return;
+            }
+        }
         if (p.odt == GRIM_F16) finish(std::integral_constant<int, GRIM_F16>{});
         else finish(std::integral_constant<int, GRIM_BF16>{});
     }
