@@ -120,6 +120,13 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     static_assert(NT % NTB == 0, "sub-tiles come in whole batches");
     using Acc = typename std::conditional<BR == 16, f32x4, f32x16>::type;
 
+    // (what the prologue needs of the arguments in one trip through the scalar cache)
+    asm volatile("" ::"s"(p.recs), "s"(p.cptr), "s"(p.bptr), "s"(p.nbr), "s"(p.nchunks), "s"(p.chunk_rows), "s"(p.ntiles), "s"(p.ngroups), "s"(p.amax),
+                 "s"(p.N), "s"(p.K));
+    if constexpr (CONV != kConvNone)
+        asm volatile("" ::"s"(p.F), "s"(p.H), "s"(p.W), "s"(p.HW), "s"(p.kh), "s"(p.kw), "s"(p.KK), "s"(p.kk_magic), "s"(p.f_img_stride), "s"(p.f_total),
+                     "s"(p.tap_ways), "s"(p.n_begin));
+    else asm volatile("" ::"s"(p.X), "s"(p.ldx));
     const int xbytes = (p.chunk_rows + 1) * PITCH;            // X rows + zero row
     const int stage_bytes = xbytes + p.amax * 16;
 
@@ -203,9 +210,10 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
             const int tap = pair / CPR, c = pair - tap * CPR;
             const int tr = tap / p.kw, tq = tap - tr * p.kw;
             const int dr = tr - (p.kh >> 1), dq = tq - (p.kw >> 1);
-            const int64_t n = n0 + c * 8;
-            const int img = (int)(n / p.HW);
-            const int pos = (int)(n - (int64_t)img * p.HW);
+            // (fewer than 2^30 positions: checked at launch; a 64-bit division is 150 instructions)
+            const unsigned int n = (unsigned int)n0 + c * 8;
+            const int img = (int)(n / (unsigned int)p.HW);
+            const int pos = (int)(n - (unsigned int)img * (unsigned int)p.HW);
             unsigned int mask[4] = {0u, 0u, 0u, 0u};     // the positions whose shifted pixel lies inside the image
             {
                 int h = pos / p.W, w = pos - h * p.W;
@@ -246,7 +254,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
             };
             // can a window of the chunk reach before the first or behind the last element of the batch?  (the same for the
             // whole workgroup; windows of rows past K do not count)
-            const int img0 = (int)(n0 / p.HW), img1 = (int)((n0 + TN - 8) / p.HW);
+            const int img0 = (int)((unsigned int)n0 / (unsigned int)p.HW), img1 = (int)((unsigned int)(n0 + TN - 8) / (unsigned int)p.HW);
             const int64_t elo = (int64_t)img0 * p.f_img_stride + (n0 - (int64_t)img0 * p.HW) - ((p.kh >> 1) * p.W + (p.kw >> 1));
             const int64_t ehi = (int64_t)img1 * p.f_img_stride + (n0 + TN - (int64_t)img1 * p.HW) +
                                 (p.kh - 1 - (p.kh >> 1)) * p.W + (p.kw - 1 - (p.kw >> 1));
@@ -319,9 +327,9 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
             const int u = i * kWideFetchThreads + ft;
             const int row = u / CPR, c = u - row * CPR;
             if constexpr (CONV) {
-                const int64_t n = n0 + c * 8;
-                const int img = (int)(n / p.HW);
-                xoff[i] = img * p.f_img_stride + (int)(n - (int64_t)img * p.HW);
+                const unsigned int n = (unsigned int)n0 + c * 8;
+                const unsigned int img = n / (unsigned int)p.HW;
+                xoff[i] = (int)img * p.f_img_stride + (int)(n - img * (unsigned int)p.HW);
             } else {
                 xoff[i] = (int)(row * p.ldx * 2 + c * 16);      // below 2^31: checked at launch
             }
@@ -336,8 +344,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
                 const int tap = e / CPR, c = e - tap * CPR;
                 const int r = tap / p.kw, q = tap - r * p.kw;
                 const int dr = r - (p.kh >> 1), dq = q - (p.kw >> 1);
-                const int64_t n = n0 + c * 8;
-                const int pos = (int)(n % p.HW);
+                const int pos = (int)(((unsigned int)n0 + c * 8) % (unsigned int)p.HW);
                 int h = pos / p.W, w = pos - h * p.W;
                 unsigned int m[4] = {0u, 0u, 0u, 0u};
                 if (tap < p.KK) {
