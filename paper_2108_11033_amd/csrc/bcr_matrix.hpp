@@ -303,6 +303,7 @@ grim_status launch_rnn_gather(const grim_bcr_matrix *A, const void *X, int64_t l
 // sequences side by side (1 .. kSeqMaxBatch); exch: at most 2 * batch * H words of 8 bytes; hidden sizes up to kSeqMaxH
 constexpr int64_t kSeqMaxH = 8192;
 constexpr int32_t kSeqMaxBatch = 32;
+constexpr int64_t kSeqClaimWords = 272;                            // words of a claim (bcr_rnn_seq.hip) behind the exchange words
 bool rnn_seq_applies(int kind, int32_t BR, int32_t BC, int32_t dtype, int32_t ukr, int32_t ukc, int64_t K1, int64_t K2,
                      int64_t I, int64_t H, int32_t batch);
 grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, const int32_t *pos1, const int32_t *pos2,

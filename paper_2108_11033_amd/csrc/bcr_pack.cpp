@@ -1577,7 +1577,7 @@ static grim_status seq_exchange_of(const grim_bcr_matrix *A, int64_t H, void **o
     if (!A->seq_exch) {
         void *ptr = nullptr;
         // two slots of at most one word per hidden unit and sequence, for the largest batch
-        if (hipMalloc(&ptr, (size_t)(2 * H) * kSeqMaxBatch * 8) != hipSuccess) {
+        if (hipMalloc(&ptr, ((size_t)(2 * H) * kSeqMaxBatch + kSeqClaimWords) * 8) != hipSuccess) {
             (void)hipGetLastError();
             return GRIM_ERR_ALLOC;
         }

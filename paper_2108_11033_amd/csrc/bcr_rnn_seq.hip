@@ -42,6 +42,20 @@ constexpr unsigned int kSeqPoison = 0xffffffffu;   // tag of a word whose produc
 constexpr unsigned int kSeqDefaultPolls = 1u << 21;
 constexpr size_t kSeqMaxLds = 160 * 1024 - 256;    // dynamic part: the kernel also has a few static bytes
 
+// How the workgroups of sets that are no multiple of eight come together: the sets are claimed.  Every XCD gets as many workgroups,
+// enough for all sets between them, and as soon as a set's worth of them runs on an XCD they take a set; what is not needed leaves
+// at once.  A call that runs alone thus has each set on one XCD, where words stay in its L2.  Where calls overlap and no set
+// fills up -- each could hold some of the compute units and wait for the rest -- a workgroup that has waited long enough
+// calls it off, and the first workgroups to ask, wherever they run, make up the sets: a call needs no more of the chip at
+// once than in the plain order.
+struct SeqClaim {
+    struct Xcd { unsigned int arrived, owns[31]; } xcd[16];        // workgroups that run; the set that each wgs of them have taken, plus one
+    unsigned int complete, ready, mode, asked;                     // sets' worths that run; that have a set; kClaim*; workgroups that asked
+};
+static_assert(sizeof(SeqClaim) <= kSeqClaimWords * 8, "room for the claim");
+constexpr unsigned int kClaimPlaced = 1, kClaimSpread = 2;         // SeqClaim::mode (0: open)
+constexpr int kSeqClaimPolls = 64;                                 // reads of the mode before a workgroup calls it off (about 1 us each)
+
 struct SeqParams {
     GemvDesc d1, d2;               // LSTM: the gate matrix; GRU: W_i and W_h
     const int32_t *pos1, *pos2;    // stored position of every original strip
@@ -62,7 +76,9 @@ struct SeqParams {
     int64_t ldhs;
     float *hs32;                   // optional fp32 copy of the outputs
     int64_t ldhs32;
-    unsigned long long *exch;      // grid.y x 2 x NQ x H words (two 16-bit values, tag); all tags zero at launch
+    unsigned long long *exch;      // sets x 2 x NQ x H words (two 16-bit values, tag); all tags zero at launch
+    SeqClaim *claim;               // kSeqClaimed: zero at launch
+    int32_t sets;
     int32_t *status;               // set to 1 by a workgroup that gives up
     uint32_t max_polls;
 };
@@ -91,12 +107,50 @@ __device__ __forceinline__ unsigned int seq_xcd() {
     return (unsigned int)__builtin_amdgcn_s_getreg(20 | 31 << 11) & 15u;    // the whole of hardware register 20, XCC_ID
 }
 
-// MULTI: a workgroup carries more than one sequence.  PLACED: every set of workgroups on an XCD of its own (1-D grid);
-// otherwise grid.y is the set.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
-template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
+// One thread of a workgroup: its set and its number in the set, or set -1: not needed.
+__device__ inline void seq_claim(SeqClaim *c, int sets, int wgs, int *set, int *unit) {
+    constexpr int AGENT = __HIP_MEMORY_SCOPE_AGENT, RELAXED = __ATOMIC_RELAXED;
+    SeqClaim::Xcd *const x = &c->xcd[seq_xcd()];
+    const int number = (int)__hip_atomic_fetch_add(&x->arrived, 1u, RELAXED, AGENT);
+    const int slot = number / wgs;
+    if (number % wgs == wgs - 1) {
+        const unsigned int k = __hip_atomic_fetch_add(&c->complete, 1u, RELAXED, AGENT);
+        if ((int)k < sets) {
+            // (acknowledged before it is counted, so that whoever sees the mode sees it; read on this XCD only)
+            __hip_atomic_store(&x->owns[slot < 31 ? slot : 30], k + 1, RELAXED, AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if ((int)__hip_atomic_fetch_add(&c->ready, 1u, RELAXED, AGENT) == sets - 1) {
+                unsigned int open = 0;
+                (void)__hip_atomic_compare_exchange_strong(&c->mode, &open, kClaimPlaced, RELAXED, RELAXED, AGENT);
+            }
+        }
+    }
+    unsigned int mode = 0;
+    for (int polls = 0; polls < kSeqClaimPolls && mode == 0; ++polls) {
+        if (polls) __builtin_amdgcn_s_sleep(4);
+        mode = __hip_atomic_load(&c->mode, RELAXED, AGENT);
+    }
+    if (mode == 0) {
+        (void)__hip_atomic_compare_exchange_strong(&c->mode, &mode, kClaimSpread, RELAXED, RELAXED, AGENT);
+        if (mode == 0) mode = kClaimSpread;          // (mode: what was there before)
+    }
+    if (mode == kClaimPlaced) {
+        *set = slot < 31 ? (int)__hip_atomic_load(&x->owns[slot], RELAXED, AGENT) - 1 : -1;
+        *unit = number % wgs;
+    } else {
+        const int asked = (int)__hip_atomic_fetch_add(&c->asked, 1u, RELAXED, AGENT);
+        *set = asked < sets * wgs ? asked / wgs : -1;
+        *unit = asked % wgs;
+    }
+}
+
+// MULTI: a workgroup carries more than one sequence.  FORM: kSeqPlain: grid.y is the set; kSeqPlaced: every set of workgroups on
+// an XCD of its own (1-D grid); kSeqClaimed: see SeqClaim.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
+template <int DT, int KR, int KC, int CELL, bool MULTI, int FORM>
 __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams p) {
     using T = typename GElem<DT>::type;
     static_assert(sizeof(T) == 2, "two-byte element types");
+    constexpr bool PLACED = FORM != kSeqPlain;
     constexpr int NWV = exact_waves(CELL), NTHR = NWV * 64;
     constexpr int NV = KR * KC * 2 / 16;
     static_assert(KR * KC * 2 % 16 == 0 && KC % 2 == 0 && KC <= 32 && KR <= 32, "block shape");
@@ -108,7 +162,15 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     const int H = p.H;
     // this workgroup's sequences: b0 .. b0 + B - 1 of the p.B
     int set = blockIdx.y, unit = blockIdx.x;
-    if constexpr (PLACED) seq_placed_at(blockIdx.x, H / p.BR, &set, &unit);
+    if constexpr (FORM == kSeqPlaced) seq_placed_at(blockIdx.x, H / p.BR, &set, &unit);
+    if constexpr (FORM == kSeqClaimed) {
+        __shared__ int place[2];
+        if (tid == 0) seq_claim(p.claim, p.sets, H / p.BR, &place[0], &place[1]);
+        __syncthreads();
+        set = __builtin_amdgcn_readfirstlane(place[0]);
+        unit = __builtin_amdgcn_readfirstlane(place[1]);
+        if (set < 0) return;
+    }
     const int b0 = set * p.SPB;
     const int B = MULTI ? (p.SPB < p.B - b0 ? p.SPB : p.B - b0) : 1;
     const int NQ = MULTI ? p.NQ : 1;
@@ -512,13 +574,13 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
 // zeroes the exchange words' tags and the status word (a kernel, not a memset: callers may capture the launch)
 __global__ void __launch_bounds__(256) rnn_seq_clear(unsigned long long *exch, int64_t words, int32_t *status) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < words) exch[i] = 0ull;
+    if (i < words) exch[i] = 0ull;                 // (the words of a claim behind them among these)
     if (i == 0) *status = 0;
 }
 
-template <int DT, int KR, int KC, int CELL, bool MULTI, bool PLACED>
+template <int DT, int KR, int KC, int CELL, bool MULTI, int FORM>
 static grim_status launch_seq_inst(const SeqParams &p, dim3 grid, size_t lds, hipStream_t stream) {
-    auto kern = bcr_rnn_seq<DT, KR, KC, CELL, MULTI, PLACED>;
+    auto kern = bcr_rnn_seq<DT, KR, KC, CELL, MULTI, FORM>;
     static std::atomic<bool> attr_done{false};
     if (lds > 64 * 1024 && !attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSeqMaxLds) != hipSuccess) {
@@ -532,14 +594,17 @@ static grim_status launch_seq_inst(const SeqParams &p, dim3 grid, size_t lds, hi
 }
 
 template <int DT, int CELL>
-static grim_status launch_seq(const SeqParams &p, int kr, int kc, bool placed, dim3 grid, size_t lds, hipStream_t stream) {
+static grim_status launch_seq(const SeqParams &p, int kr, int kc, int form, dim3 grid, size_t lds, hipStream_t stream) {
 #define GRIM_SEQ(R, C)                                                                                             \
     if (kr == (R) && kc == (C)) {                                                                                  \
-        if (placed)                                                                                                \
-            return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, true>(p, grid, lds, stream)                   \
-                             : launch_seq_inst<DT, R, C, CELL, false, true>(p, grid, lds, stream);                 \
-        return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, false>(p, grid, lds, stream)                      \
-                         : launch_seq_inst<DT, R, C, CELL, false, false>(p, grid, lds, stream);                    \
+        if (form == kSeqClaimed)                                                                                   \
+            return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, kSeqClaimed>(p, grid, lds, stream)            \
+                             : launch_seq_inst<DT, R, C, CELL, false, kSeqClaimed>(p, grid, lds, stream);          \
+        if (form == kSeqPlaced)                                                                                    \
+            return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, kSeqPlaced>(p, grid, lds, stream)             \
+                             : launch_seq_inst<DT, R, C, CELL, false, kSeqPlaced>(p, grid, lds, stream);           \
+        return p.SPB > 1 ? launch_seq_inst<DT, R, C, CELL, true, kSeqPlain>(p, grid, lds, stream)                  \
+                         : launch_seq_inst<DT, R, C, CELL, false, kSeqPlain>(p, grid, lds, stream);                \
     }
     GRIM_SEQ(4, 4) GRIM_SEQ(4, 8) GRIM_SEQ(4, 12) GRIM_SEQ(4, 16)
     GRIM_SEQ(8, 4) GRIM_SEQ(8, 8) GRIM_SEQ(8, 12) GRIM_SEQ(8, 16)
@@ -636,26 +701,33 @@ grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, con
     p.exch = static_cast<unsigned long long *>(exch);
     p.status = status;
     p.max_polls = max_polls ? max_polls : kSeqDefaultPolls;
-    const int64_t words = (int64_t)sets * 2 * p.NQ * H;                // at most 2 * kSeqMaxBatch * H
+    const int64_t wgs = H / BR;
+    const int form = seq_sets_on_xcds(sets) ? kSeqPlaced : seq_sets_claimed(sets, wgs, T) ? kSeqClaimed : kSeqPlain;
+    int64_t words = (int64_t)sets * 2 * p.NQ * H;                      // at most 2 * kSeqMaxBatch * H
+    p.sets = sets;
+    p.claim = nullptr;
+    if (form == kSeqClaimed) {                                         // (behind the words of the sets: there is room for it behind the most)
+        p.claim = reinterpret_cast<SeqClaim *>(p.exch + words);
+        words += kSeqClaimWords;
+    }
     hipLaunchKernelGGL(rnn_seq_clear, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, p.exch, words, status);
     if (hipGetLastError() != hipSuccess) return GRIM_ERR_DEVICE;
     // Eight sequences through an LSTM layer of 1024 / 512 / 256 units 2.59 / 2.33 / 2.23 us per step in the plain order, 2.36 /
     // 2.01 / 1.93 placed; GRU 2.64 / 2.47 / 2.40 -> 2.38 / 2.12 / 2.11; 32 sequences of 1024 units 5.5 -> 5.4, GRU 6.0 -> 5.9.
-    const bool placed = seq_sets_on_xcds(sets);
-    const int64_t wgs = H / BR;
-    const dim3 grid(placed ? (unsigned)(sets * wgs) : (unsigned)wgs, placed ? 1u : (unsigned)sets);
+    const dim3 grid(form == kSeqClaimed ? 8u * (unsigned)((sets + 7) / 8 * wgs) : form == kSeqPlaced ? (unsigned)(sets * wgs) : (unsigned)wgs,
+                    form == kSeqPlain ? (unsigned)sets : 1u);
     const size_t lds = seq_lds_bytes(kind, K1, K2, BR, per_wg);
     if (kind == 1)
-        return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 1>(p, ukr, ukc, placed, grid, lds, stream)
-                                 : launch_seq<GRIM_BF16, 1>(p, ukr, ukc, placed, grid, lds, stream);
-    return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 2>(p, ukr, ukc, placed, grid, lds, stream)
-                             : launch_seq<GRIM_BF16, 2>(p, ukr, ukc, placed, grid, lds, stream);
+        return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 1>(p, ukr, ukc, form, grid, lds, stream)
+                                 : launch_seq<GRIM_BF16, 1>(p, ukr, ukc, form, grid, lds, stream);
+    return dtype == GRIM_F16 ? launch_seq<GRIM_F16, 2>(p, ukr, ukc, form, grid, lds, stream)
+                             : launch_seq<GRIM_BF16, 2>(p, ukr, ukc, form, grid, lds, stream);
 }
 
 // Exchange words for callers that must not allocate: one array per GPU, part of the loaded code object, shared by
 // every such call on that GPU (calls that overlap in time on one GPU race).  Its name is a host-side stand-in; the
 // device address is asked for once per device, with that device current, and only that address is handed to kernels.
-static __device__ __align__(256) unsigned long long scratch[2 * kSeqMaxH];
+static __device__ __align__(256) unsigned long long scratch[2 * kSeqMaxH + kSeqClaimWords];
 
 grim_status rnn_seq_static_exchange(void **out) {
     constexpr int kMaxDevices = 64;

@@ -1,5 +1,7 @@
 // Which sets of workgroups of the sequence kernel are placed on an XCD of their own, and how.
 #pragma once
+#include <cstdint>
+
 #include "host_device.hpp"
 
 namespace grim {
@@ -16,6 +18,15 @@ GRIM_HOST_DEVICE void seq_placed_at(int id, int wgs, int *set, int *unit) {
     const int slot = id >> 3;
     *set = slot / wgs * 8 + (id & 7);
     *unit = slot % wgs;
+}
+
+// Forms of a call: sets in grid.y, placed as above, or claimed by the XCDs (bcr_rnn_seq.hip).  Claimed are sets of workgroups that an
+// XCD's 32 compute units hold one each of, in sequences long enough to pay for the claim (2 us; a step on one XCD is 0.4 to 0.5 us
+// shorter than one across them: an LSTM of 1024 / 512 / 256 units, one sequence of 64 steps 132 / 129 / 130 -> 107 / 104 / 96 us, GRU
+// 137 / 139 / 149 -> 114 / 109 / 104, four sequences of 1024 units 135 -> 109, 137 -> 116).
+constexpr int kSeqPlain = 0, kSeqPlaced = 1, kSeqClaimed = 2;
+GRIM_HOST_DEVICE bool seq_sets_claimed(int sets, int64_t wgs, int steps) {
+    return sets % 8 != 0 && wgs > 1 && (sets + 7) / 8 * wgs <= 32 && steps >= 8;
 }
 
 }  // namespace grim

@@ -470,3 +470,54 @@ def test_lstm_sequence_forms_of_the_exchange_words(H, I, BR, BC, kr, kc, B):
         hs_ref, _ = _lstm_reference(Wm, np.ascontiguousarray(xs[:, b]), dtype, bias, h0[b], c0[b])
         for t in range(T):
             assert np.abs(hs32[t, b] - hs_ref[t]).max() <= TOL[dtype] * (1 + t), f"sequence {b}, step {t}"
+
+
+@pytest.mark.parametrize("cell,H,BR,BC,kr,kc,B", [
+    ("lstm", 256, 32, 32, 8, 12, 1),        # one set
+    ("lstm", 256, 32, 32, 8, 12, 3),
+    ("lstm", 96, 32, 32, 8, 12, 13),        # two sets to an XCD, sixteen slots for thirteen
+    ("lstm", 64, 32, 32, 8, 8, 31),         # four
+    ("lstm", 1024, 32, 32, 4, 8, 12),       # six sets of two sequences a workgroup
+    ("gru", 512, 32, 32, 8, 8, 5),
+    ("gru", 32, 16, 16, 4, 4, 9),           # sets of two workgroups
+])
+@pytest.mark.parametrize("streams", [1, 4])
+def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams):
+    """Calls whose sets XCDs take as they fill up, alone and four at a time on streams of their own: the bits of sequences of seven
+    steps and the rest, which run in the plain order (fewer than eight steps)."""
+    from helpers import pack_workload, to_device
+    torch, dev, g = _gpu()
+    dtype, I, T = gen.F16, H, 14
+    cases = []
+    for k in range(streams):
+        if cell == "lstm":
+            mats = [_lstm_case(g, dtype, H, I, BR, BC, kr, kc, seed=2300 + 10 * k + H, scale=2.0)[0]]
+        else:
+            mats = [pack_workload(g, _scaled_weights(3 * H, H, dtype, 2401 + 10 * k + j, 2.0), dtype,
+                                  gen.random_mask(3 * H, H, BR, BC, kr, kc, seed=2400 + 10 * k + j)) for j in range(2)]
+        xs = np.concatenate([_inputs(T, I, dtype, 2450 + 40 * k + b)[:, None] for b in range(B)], axis=1).reshape(T * B, I)
+        cases.append((mats, to_device(xs, dtype), torch.cuda.Stream() if streams > 1 else torch.cuda.current_stream()))
+
+    def call(mats, xs, stream, cuts):
+        h0, st = torch.zeros((B, H), dtype=xs.dtype, device=dev), torch.zeros((B, H), dtype=torch.float32, device=dev)
+        hs = torch.empty((T * B, H), dtype=xs.dtype, device=dev)
+        status = torch.full((len(cuts),), -1, dtype=torch.int32, device=dev)
+        stream.wait_stream(torch.cuda.current_stream())
+        for i, (t0, t1) in enumerate(cuts):
+            x, out, h = xs[t0 * B:t1 * B], hs[t0 * B:t1 * B], h0 if t0 == 0 else hs[(t0 - 1) * B:t0 * B]
+            if cell == "lstm":
+                g.lstm_sequence_batch(mats[0], x, I, t1 - t0, B, None, h, st, out, H, None, 0, status[i:], 0, stream)
+            else:
+                g.gru_sequence_batch(mats[0], mats[1], x, I, t1 - t0, B, None, None, h, st, out, H, None, 0, status[i:], 0, stream)
+        return hs, st, status, h0
+
+    plain = []
+    for case in cases:
+        plain.append(call(*case, [(0, 7), (7, T)]))
+        torch.cuda.synchronize()
+    for _ in range(3):
+        whole = [call(*case, [(0, T)]) for case in cases]
+        torch.cuda.synchronize()
+        for a, b in zip(plain, whole):
+            assert (a[2] == 0).all() and (b[2] == 0).all()
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
