@@ -250,15 +250,17 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     if constexpr (S2) tile_edge = __builtin_amdgcn_readfirstlane(tile_edge) != 0;
     // A batch: the slot words and block descriptors of SB steps (past the wave's last: the last again), then their windows
     // and weights, all in registers at once.
-    //   Where many waves split a strip (few workgroups, a batch or two per wave: the form is all latency) a lane reads the
+    //   Where twelve waves split a strip (few workgroups, a batch or two per wave: the form is all latency) a lane reads the
     // plan's words of its own LI windows.  Handed on by lane permutes as below, each window is asked for behind a trip through
-    // LDS (512 channels, 3 x 3, 14 x 14: 6.9 us; 6.1 so, with the windows ahead of the validity table).  With four waves
-    // and many workgroups the loads are what is short and the words' cost 1 to 3 % (192 channels, 5 x 5, six 56 x 56 maps 112 us, 115 so).
+    // LDS (512 channels, 3 x 3, 14 x 14: 6.9 us; 6.3 so, with the windows ahead of the validity table).  With fewer waves and
+    // more workgroups the loads are what is short and the words' cost 1 to 4 % (192 channels, 5 x 5, six 56 x 56 maps 112 us, 115
+    // so; eight waves: 64 -> 96 channels, 3 x 3, 72 x 72 9.4, 9.8 so).
     //   Otherwise lane j takes k slot j % 32 of every step -- without a plan it splits the slot's row number into (window
     // start for the tile's first column, tap) -- and the lanes that fetch the slot's row pieces pick that pair up with a
     // lane permute: one integer division per lane and step instead of four.
     // Packed as tap (or KK for padding) << 27 | window start + 2^25.
-    constexpr bool OWN = PLAN && EIGHT;          // a lane has the words of its windows
+    constexpr bool ALONE = LONGW == kConvLongWaves;           // twelve waves: a workgroup has its compute unit to itself
+    constexpr bool OWN = PLAN && ALONE;          // a lane has the words of its windows
     constexpr bool NEED_PK = !OWN || (!S2 && NT == 4);        // ... or the word of k slot lane % 32
     constexpr bool OWN_EXT = OWN && !S2 && NT == 2;          // the last lane of a row piece asks for the element behind its window itself
     unsigned int pk[SB], words[SB][LI];
@@ -415,12 +417,12 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
             PW[u] = kept ? wv : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
         }
     };
-    // The first batch's headers, and where many waves split a strip its windows too, travel while the validity table is
+    // The first batch's headers, and where twelve waves split a strip its windows too, travel while the validity table is
     // built: per (tap, piece of the tile) the 16-byte mask of the piece's 8 positions, a dword per thread; entry KK is all
-    // zero (padding slots).  (With four waves a second copy of the windows' code costs as much as their latency, which
+    // zero (padding slots).  (With fewer a second copy of the windows' code costs as much as their latency, which
     // other workgroups hide: 1 x 1, 160 channels on eight 42 x 65 maps 15.8 us, 16.4 so.)
     ask_headers(s_beg);
-    if (EIGHT && s_beg < s_end) ask_windows(s_beg);
+    if (ALONE && s_beg < s_end) ask_windows(s_beg);
     for (int z = tid; z < (p.KK + 1) * CPR * 4; z += NWV * 64) {
         const int e = z >> 2, tap = e / CPR, cc = e % CPR;
         reinterpret_cast<unsigned int *>(vtab)[z] = conv_pair_mask<S2>(p, tap, n0 + cc * 8 + (z & 3) * 2, S2 ? p.Wp : p.W);
@@ -436,7 +438,7 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     for (int s = s_beg; s < s_end; s += SB) {
         const int nb = s_end - s < SB ? s_end - s : SB;
         if (s != s_beg) ask_headers(s);
-        if (!EIGHT || s != s_beg) ask_windows(s);
+        if (!ALONE || s != s_beg) ask_windows(s);
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
