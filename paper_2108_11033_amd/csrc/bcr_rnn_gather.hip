@@ -42,7 +42,8 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
     constexpr int GATES = CELL == 1 ? 4 : 3, NRUN = CELL == 1 ? 4 : 6, WPR = CELL == 1 ? 4 : 2, NWV = NRUN * WPR;
     constexpr int DT = BF16 ? GRIM_BF16 : GRIM_F16;
     constexpr int PITCH = 32;                    // bytes of a staged row
-    __shared__ __attribute__((aligned(16))) char lds[NWV * 2048];
+    constexpr int WLDS = SB * 1024;              // a step buffer of 32 rows x 16 columns for every step in flight
+    __shared__ __attribute__((aligned(16))) char lds[NWV * WLDS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int run = wave / WPR, share = wave % WPR, mi = CELL == 2 ? run / 3 : 0, gate = CELL == 2 ? run % 3 : run;
@@ -79,7 +80,7 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
     const int rs = lane >> 1, c = lane & 1, col = n0 + c * 8;
     const unsigned short *xcol = A.X + (col < N ? col : n0);
     const unsigned short *x_last = A.X + ((int64_t)(A.K - 1) * A.ldx + N - 8);
-    char *buf = lds + wave * 2048;
+    char *buf = lds + wave * WLDS;
     const int i16 = lane & 15, kgroup = lane >> 4, qd = i16 >> 2;
     const unsigned int below = (1u << i16) - 1u;
     const char *tr = buf + (kgroup * 8 + qd) * PITCH + (i16 & 3) * 8;
@@ -110,19 +111,26 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
             const i16x8 wv = pay[dsc[u].y + (kept ? __builtin_popcount(dsc[u].x & below) : 0)];
             w[u] = kept ? wv : i16x8{0, 0, 0, 0, 0, 0, 0, 0};
         }
+        // All steps are parked before the first is multiplied (steps past the last again, and not multiplied): one trip through LDS
+        // for all of them, not one after the other
+        i16x8 x[SB];
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
-            if (u < nb) {
-                u32x4 v = rx[u];
-                if (__builtin_amdgcn_ballot_w64((flags[u] & 15u) != 0)) v = drop_elements(v, flags[u] & 15u);    // (the last rows of X only)
-                if (flags[u] >> 31) v = u32x4{0u, 0u, 0u, 0u};
-                char *b = buf + (u & 1) * 1024;
-                *reinterpret_cast<u32x4 *>(b + rs * PITCH + c * 16) = v;
-                __builtin_amdgcn_wave_barrier();
-                const i16x4 lo = lds_tr_read(tr + (u & 1) * 1024), hi = lds_tr_read(tr + 4 * PITCH + (u & 1) * 1024);
-                part = mfma16<BF16>(i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}, w[u], part);
-                __builtin_amdgcn_wave_barrier();
-            }
+            u32x4 v = rx[u];
+            if (__builtin_amdgcn_ballot_w64((flags[u] & 15u) != 0)) v = drop_elements(v, flags[u] & 15u);    // (the last rows of X only)
+            if (flags[u] >> 31) v = u32x4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4 *>(buf + u * 1024 + rs * PITCH + c * 16) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < SB; ++u) {
+            const i16x4 lo = lds_tr_read(tr + u * 1024), hi = lds_tr_read(tr + 4 * PITCH + u * 1024);
+            x[u] = i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < SB; ++u) {
+            if (u < nb) part = mfma16<BF16>(x[u], w[u], part);
             if (u == SB - 1 || (SB > 4 && u == SB / 2 - 1)) {
                 acc[0] += part[0]; acc[1] += part[1]; acc[2] += part[2]; acc[3] += part[3];
                 part = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -137,9 +145,9 @@ __global__ void __launch_bounds__(CELL == 1 ? 1024 : 768) bcr_rnn_gather(RnnGath
     float sum[6];
 #pragma unroll
     for (int j = 0; j < NRUN; ++j) {
-        float s = *reinterpret_cast<const float *>(lds + j * WPR * 2048 + at);
+        float s = *reinterpret_cast<const float *>(lds + j * WPR * WLDS + at);
 #pragma unroll
-        for (int w = 1; w < WPR; ++w) s += *reinterpret_cast<const float *>(lds + (j * WPR + w) * 2048 + at);
+        for (int w = 1; w < WPR; ++w) s += *reinterpret_cast<const float *>(lds + (j * WPR + w) * WLDS + at);
         const RnnGatherMatrix &M = p.m[CELL == 2 ? j / 3 : 0];
         const int64_t grow = (int64_t)(CELL == 2 ? j % 3 : j) * p.H + unit;
         if (__builtin_fmaf(s, 0.f, 0.f) != 0.f) {      // not finite: is there an infinity or NaN that the row keeps?
