@@ -130,7 +130,8 @@ grim_status launch_spmm_gather(const grim_bcr_matrix *A, const void *X, int64_t 
     const bool narrow = form.narrow, solo = form.solo, eight = form.eight, aligned = form.aligned;
     const int64_t nwg = form.nwg;
     const int waves = gather_waves(narrow, eight, form.nt);
-    const size_t lds = (size_t)waves * gather_wave_lds(form.nt);
+    const int in_flight = gather_steps(aligned, narrow, eight, form.nt, 0);      // (of the forms that park a batch as a whole)
+    const size_t lds = (size_t)waves * gather_wave_lds(form.nt, gather_buffers(narrow, form.nt, in_flight));
     const dim3 grid((unsigned)nwg, A2 ? 2u : 1u), block(waves * 64);
 #define GRIM_GATHER(BF, AL, NR, SO, EI, ...)                                                                              \
     do {                                                                                                             \

@@ -83,11 +83,18 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // EIGHT: eight waves split a strip's steps instead of four (few workgroups, long strips: the 14 x 14 layers)
 // The body of the kernel as a function of the workgroup's number (block_x; block_y: second product of a pair), so that
 // another kernel can run such workgroups next to its own (the wide-tile kernel does, for the columns it leaves over).
-// Its first NWV waves must call it together; `lds` = NWV * gather_wave_lds(NT) bytes of workgroup memory.
+// Its first NWV waves must call it together; `lds` = NWV * gather_wave_lds(..) bytes of workgroup memory.
 // LONGW: the waves that split a strip in the EIGHT form (eight in the kernel of its own; a caller with more waves to
 // spare may pass more: fewer steps per wave, fewer dependent batches).
 constexpr int gather_narrow_steps(int nt) { return nt == 1 ? 8 : 4; }
-constexpr int gather_wave_lds(int nt) { return nt * 2048; }    // two step buffers of 32 rows x 16 nt columns
+constexpr int gather_steps(bool aligned, bool narrow, bool eight, int nt, int steps) {
+    return steps ? steps : narrow ? gather_narrow_steps(nt) : nt == 2 || (!aligned && !eight) ? 3 : 4;
+}
+// Step buffers of a wave, 32 rows x 16 nt columns each: two, or one for every step in flight on small tiles (NT = 2, twelve
+// waves), which are all latency: three steps through LDS in one trip, 512 x 4608 at 64 / 147 / 196 / 256 columns 4.14 / 4.85 / 5.04 / 4.27
+// -> 4.09 / 4.70 / 4.80 / 4.11 us.  (Below 64 columns 4.25 -> 4.1 at 32 and 9.0 -> 9.2 at 17: not there.)
+constexpr int gather_buffers(bool narrow, int nt, int steps) { return nt == 2 && !narrow ? steps : 2; }
+constexpr int gather_wave_lds(int nt, int buffers = 2) { return buffers * nt * 1024; }
 // STEPS: steps a wave has in flight, where the form has a choice (0: as its registers allow).
 // COLS: 0, or the columns there are (1 .. 4; NARROW, NT = 1): of a row of X just their bytes are fetched then.
 template <bool BF16, bool ALIGNED, bool NARROW, bool SOLO, bool EIGHT, int NT = 4, int LONGW = kGatherLongWaves, int STEPS = 0, int COLS = 0>
@@ -98,7 +105,9 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     // forms of operands that other kernels used to take, which multiply kept weights only: an infinity or NaN in X must
     // not reach the rows of the run that do not keep its column
     constexpr bool WATCH = NARROW || !ALIGNED;
-    constexpr int SB = STEPS ? STEPS : NARROW ? gather_narrow_steps(NT) : NT == 2 || (WATCH && !EIGHT) ? 3 : 4;
+    constexpr int SB = gather_steps(ALIGNED, NARROW, EIGHT, NT, STEPS);
+    constexpr int WLDS = gather_wave_lds(NT, gather_buffers(NARROW, NT, SB));
+    constexpr bool ALL = gather_buffers(NARROW, NT, SB) > 2;           // a batch is parked as a whole
     static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
     // (what the prologue needs of the arguments in one trip through the scalar cache: asked for where each is first used, the
     // trips follow one another)
@@ -152,7 +161,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     const int g0 = usteps ? t * usteps : sptr[t], nst = usteps ? usteps : sptr[t + 1] - g0;
     const int s_beg = SOLO ? g0 : g0 + wave_share(nst, wave, NWV);
     const int s_end = SOLO ? g0 + nst : g0 + wave_share(nst, wave + 1, NWV);
-    char *buf = lds + wave * gather_wave_lds(NT);    // two step buffers of 32 rows x TN columns
+    char *buf = lds + wave * WLDS;
 
     // fetch side: lane = (row slot rs, 16-byte piece c); its i-th load is k slot i * RPI + rs
     const int rs = lane / CPR, c = lane % CPR;
@@ -278,32 +287,60 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
             if (FIRST || u > 0) ask_rows(R[u], hdr[u]);
             PW[u] = ask_weights(dsc[u]);
         }
+        auto park = [&](int u) {
+            char *b = buf + (ALL ? u : u & 1) * (32 * PITCH);
+            if constexpr (NARROW && !ALIGNED && COLS == 0) {
+                if (__builtin_amdgcn_ballot_w64(R[u].pad >> 8 != 0)) {       // (the last rows of X only)
+#pragma unroll
+                    for (int i = 0; i < LI; ++i) R[u].rx[i] = drop_elements(R[u].rx[i], (R[u].pad >> (8 + 4 * i)) & 15u);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < LI; ++i) {
+                const u32x4 v = (R[u].pad >> i) & 1u ? u32x4{0u, 0u, 0u, 0u} : R[u].rx[i];
+                *reinterpret_cast<u32x4 *>(b + wr_off + i * (RPI * PITCH)) = v;
+            }
+        };
+        auto gathered = [&](int u, i16x8 (&x)[NT]) {
+            const int at = (ALL ? u : u & 1) * (32 * PITCH);
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                const i16x4 lo = lds_tr_read(tr[q] + at);
+                const i16x4 hi = lds_tr_read(tr[NT == 4 ? q ^ 2 : q] + 4 * PITCH + at);
+                x[q] = i16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            }
+        };
+        auto multiply = [&](int u, const i16x8 (&x)[NT]) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                if constexpr (WATCH) part[q] = mfma16<BF16>(x[q], PW[u], part[q]);
+                else acc[q] = mfma16<BF16>(x[q], PW[u], acc[q]);
+            }
+        };
+        i16x8 xs[ALL ? SB : 1][NT];
+        if constexpr (ALL) {
+            // (steps past the wave's last are parked and read again and not multiplied)
+#pragma unroll
+            for (int u = 0; u < SB; ++u) park(u);
+            __builtin_amdgcn_wave_barrier();
+            if (s + SB < s_end) ask_rows(early, nhdr);
+#pragma unroll
+            for (int u = 0; u < SB; ++u) gathered(u, xs[u]);
+            __builtin_amdgcn_wave_barrier();
+        }
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             if (u < nb) {
-                char *b = buf + (u & 1) * (32 * PITCH);
-                if constexpr (NARROW && !ALIGNED && COLS == 0) {
-                    if (__builtin_amdgcn_ballot_w64(R[u].pad >> 8 != 0)) {       // (the last rows of X only)
-#pragma unroll
-                        for (int i = 0; i < LI; ++i) R[u].rx[i] = drop_elements(R[u].rx[i], (R[u].pad >> (8 + 4 * i)) & 15u);
-                    }
+                if constexpr (ALL) {
+                    multiply(u, xs[u]);
+                } else {
+                    park(u);
+                    __builtin_amdgcn_wave_barrier();
+                    if (u == 0 && s + SB < s_end) ask_rows(early, nhdr);   // set 0's rows are out of their registers
+                    gathered(u, xs[0]);
+                    multiply(u, xs[0]);
+                    __builtin_amdgcn_wave_barrier();
                 }
-#pragma unroll
-                for (int i = 0; i < LI; ++i) {
-                    const u32x4 v = (R[u].pad >> i) & 1u ? u32x4{0u, 0u, 0u, 0u} : R[u].rx[i];
-                    *reinterpret_cast<u32x4 *>(b + wr_off + i * (RPI * PITCH)) = v;
-                }
-                __builtin_amdgcn_wave_barrier();
-                if (u == 0 && s + SB < s_end) ask_rows(early, nhdr);   // set 0's rows are out of their registers
-#pragma unroll
-                for (int q = 0; q < NT; ++q) {
-                    const i16x4 lo = lds_tr_read(tr[q] + (u & 1) * (32 * PITCH));
-                    const i16x4 hi = lds_tr_read(tr[NT == 4 ? q ^ 2 : q] + 4 * PITCH + (u & 1) * (32 * PITCH));
-                    const i16x8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    if constexpr (WATCH) part[q] = mfma16<BF16>(x, PW[u], part[q]);
-                    else acc[q] = mfma16<BF16>(x, PW[u], acc[q]);
-                }
-                __builtin_amdgcn_wave_barrier();
             }
             if (WATCH && (u == SB - 1 || (SB > 4 && u == SB / 2 - 1))) {
 #pragma unroll
@@ -364,7 +401,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     }
     // add the waves' partial tiles in wave order; wave q finishes sub-tile q.  A wave parks its
     // partial tile in its own (now idle) step buffers.
-    constexpr int RPW = gather_wave_lds(NT) / 16;
+    constexpr int RPW = WLDS / 16;
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
     for (int q = 0; q < NT; ++q) red[wave * RPW + q * 64 + lane] = acc[q];
