@@ -41,7 +41,7 @@ bool gather_pair_applies(const grim_bcr_matrix *A, const void *X, const grim_bcr
 
 // Parameters, grid and kernel form of a launch (see launch_spmm_gather); GRIM_ERR_UNSUPPORTED when the kernel does not apply.
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
-                         const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form, bool may_take_small_tiles) {
+                         const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form, bool alone) {
     if (!gather_any_applies(A, X, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     if (A2 && !gather_pair_applies(A, X, A2, X2, N, ldx)) return GRIM_ERR_UNSUPPORTED;
     GatherParams p;
@@ -63,7 +63,7 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     // 4.0 / 5.1 / 4.6, 256 x 4608 in 16 x 16 blocks at 392 columns 8.5 -> 6.6 -- while every workgroup has a compute unit: with
     // 288 or 384 (tile, run) pairs 512 x 1152, 512 x 2304 and 1024 x 2304 take 4.5 to 4.9 us in 64-column tiles, 5.3 to 5.7 in
     // these.  Strips below 16 steps stay (256 x 1152 at 256 columns 3.8 us either way).
-    const bool small_tiles = may_take_small_tiles && N >= 64 && A->gather.max_steps >= 16 && (N + 31) / 32 * p.nbr <= 256;
+    const bool small_tiles = alone && N >= 64 && A->gather.max_steps >= 16 && (N + 31) / 32 * p.nbr <= 256;
     const int nt = small_tiles ? 2 : N > 32 ? 4 : N > 16 ? 2 : 1;
     p.ntiles = (int32_t)((N + nt * 16 - 1) / (nt * 16));
     p.second = GatherSecond{p.sptr, p.out_row, p.rows, p.desc, p.payload, p.X, p.Y, p.usteps, p.K, exact_arrays(A)};
@@ -74,10 +74,9 @@ grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int
     // strips of at most 8 steps (two batches of a wave) with enough (tile, strip) pairs to fill the GPU: wave per pair;
     // long strips and fewer workgroups than compute units: eight waves per strip
     const bool narrow = N < 64;
-    // Long strips only: a wave then runs ten and more dependent batches, and having the rows in L2 shortens each (the
-    // last 512 columns of a 4608-row product: 10 -> 7.7 us); with 18-step strips the extra requests cost more than they
-    // save (12.0 -> 12.4 us on a 2304-row product, five-step strips 15.5 -> 24 us).
-    p.touch = !narrow && A->gather.max_steps >= 40 ? 1 : 0;
+    // Beside the wide-tile kernel and for long strips only: with 512 x 4608 and 512 to 1024 columns left over, products of 24 576
+    // columns and those 1 to 2 % faster; strips of 18 steps took 12.4 us for 12.0 on a 2304-row product.
+    p.touch = !alone && A->gather.max_steps >= 40 ? 1 : 0;
     const bool solo = !narrow && !small_tiles && gather_wave_per_strip(A, (int64_t)p.ntiles * p.nbr, 1536);
     // Narrow tiles: eight waves only where four need more than a batch of steps and every workgroup has a compute unit --
     // 4608 x 2048 at four columns, 288 workgroups: 6.5 us with eight, 4.65 with four; 2048 x 2048 at nine, 20 steps: 5.7, 4.3.

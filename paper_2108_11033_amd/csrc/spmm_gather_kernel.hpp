@@ -49,7 +49,7 @@ struct GatherParams {
     int32_t nbr, ntiles;      // nbr: 16-row runs of the stored row order
     int32_t usteps;           // > 0: steps of every run (sptr is not read)
     int32_t K;                // rows of X
-    int32_t touch;            // start the tile's rows of X on their way from HBM when the workgroup starts
+    int32_t touch;            // beside the wide-tile kernel: start the tile's rows of X on their way from HBM when the workgroup starts
     XcdMap map;
     ExactArrays exact;
     GatherSecond second;
@@ -65,7 +65,7 @@ struct GatherForm {
 };
 grim_status gather_setup(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                          const grim_bcr_matrix *A2, const void *X2, float *Y2, GatherParams *out, GatherForm *form,
-                         bool may_take_small_tiles = true);
+                         bool alone = true);      // false: workgroups beside the wide-tile kernel's
 
 // four results at any 4-byte alignment (a single access on this GPU)
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -107,6 +107,7 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
     constexpr bool WATCH = NARROW || !ALIGNED;
     constexpr int SB = gather_steps(ALIGNED, NARROW, EIGHT, NT, STEPS);
     constexpr int WLDS = gather_wave_lds(NT, gather_buffers(NARROW, NT, SB));
+    constexpr bool kTouch = !NARROW && NT == 4 && EIGHT && LONGW > kGatherLongWaves;      // (the wide-tile kernel's)
     constexpr bool ALL = gather_buffers(NARROW, NT, SB) > 2;           // a batch is parked as a whole
     static_assert(NT == 1 || NT == 2 || NT == 4, "pieces of a row are dealt to 2, 4 or 8 lanes");
     // (what the prologue needs of the arguments in one trip through the scalar cache: asked for where each is first used, the
@@ -141,13 +142,16 @@ __device__ __forceinline__ void gather_body(const GatherParams &p, char *lds, in
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // A wave learns which rows of X it needs only after a first round trip (row numbers), and fetches them in one or
-    // two batches: with X in HBM that is up to three dependent trips to memory.  The strips of a tile run at the same
-    // time on one XCD and together keep nearly every row of the tile (16 strips keeping a quarter each leave 1 % out),
-    // so each workgroup starts its share of ALL the tile's rows on their way into that XCD's L2 right now -- one byte
-    // from the first and the last 128-byte line of every row piece, values never used -- and the fetches proper find
-    // them there or on their way.
-    if constexpr (!NARROW) {
+    // Beside the wide-tile kernel, whose stream of X and Y keeps pushing lines out of L2: a wave learns which rows of X it needs
+    // only after a first round trip (row numbers), and fetches them in one or two batches: up to three dependent trips to
+    // memory.  The strips of a tile run at the same time on one XCD and together keep nearly every row of the tile (16 strips
+    // keeping a quarter each leave 1 % out), so each workgroup starts its share of ALL the tile's rows on their way into that
+    // XCD's L2 right now -- one byte from the first and the last 128-byte line of every row piece, values never used -- and the
+    // fetches proper find them there or on their way.  Alone on the GPU the same requests are only in the way of the first
+    // fetches: few strips to a tile make many requests of each workgroup (bf16 / f16, 4608 rows of X: 512 x 784 / 785 columns
+    // 18.0 / 20.2 with -> 16.7 / 19.0 us, 128 x 784 9.15 -> 7.68, 64 x 6272 / 12 543 21.9 / 73.2 -> 14.9 / 40.1; 16 384 rows,
+    // 256 x 784 20.6 -> 15.9; nothing was faster with them).
+    if constexpr (kTouch) {
         if (p.touch) {
             const int units = p.map.per_tile;                          // workgroups of this tile
             const int per = (K + units - 1) / units;
