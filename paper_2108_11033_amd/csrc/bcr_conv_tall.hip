@@ -30,6 +30,12 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
     constexpr int WAVE_LDS = R * NT * 1024;      // D step buffers of 4 KB, later the partial tiles
     static_assert(D * 32 * PITCH <= WAVE_LDS, "step buffers fit");
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    // (the arguments in one trip through the scalar cache, as in bcr_conv_gather; with the table of masks made a dword per thread, without
+    // divisions by run-time values: 1 x 1 at stride 2, 128 -> 256 channels on four 56 x 56 maps in 4 x 16 blocks 6.82 -> 6.67 us, 96 -> 128 on
+    // three 112 x 112 7.46 -> 7.29.  Asking for the first windows ahead of that table's barrier makes the walk wait for everything: 11.0.)
+    asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
+                 "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.tiles_per_img), "s"(p.tiles_inv), "s"(p.nbr),
+                 "s"(p.usteps), "s"(p.plan), "s"(p.desc), "s"(p.payload), "s"(p.F), "s"(p.f_img_stride), "s"(p.Nv), "s"(p.W), "s"(p.kw), "s"(p.KK));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int tile, t;
@@ -60,7 +66,9 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
 #pragma unroll
     for (int u = 0; u < D; ++u) ask_header(hd[u], s_beg + u);
     u32x4 *vtab = reinterpret_cast<u32x4 *>(lds + NWV * WAVE_LDS);
-    for (int e = tid; e < (p.KK + 1) * CPR; e += NWV * 64) vtab[e] = conv_piece_mask<S2>(p, e / CPR, n0 + e % CPR * 8);
+    const int rowlen = S2 ? p.Wp : p.W;
+    for (int e = tid; e < (p.KK + 1) * CPR * 4; e += NWV * 64)
+        reinterpret_cast<unsigned int *>(vtab)[e] = conv_pair_mask<S2>(p, e / (CPR * 4), n0 + e % (CPR * 4) * 2, rowlen);
     __syncthreads();
 
     const int rs = lane >> 3, c = lane & 7;

@@ -63,28 +63,8 @@ __device__ __forceinline__ unsigned short conv_f32_to_bf16(float f) {
     return (unsigned short)(u >> 16);
 }
 
-// which of the 8 positions from nb on see a pixel of the image under a kernel tap, as a 16-byte mask; tap KK: none
-template <bool S2>
-__device__ __forceinline__ u32x4 conv_piece_mask(const ConvParams &p, int tap, int nb) {
-    const int r = tap / p.kw, q = tap - r * p.kw;
-    const int dr = r - (p.kh >> 1), dq = q - (p.kw >> 1);
-    const int rowlen = S2 ? p.Wp : p.W;
-    const int h0 = nb / rowlen, w0 = nb - h0 * rowlen;
-    unsigned int m[4] = {0u, 0u, 0u, 0u};
-    if (tap < p.KK) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            int h = S2 ? h0 * 2 : h0, w = S2 ? (w0 + j) * 2 : w0 + j;
-            if constexpr (!S2)
-                while (w >= p.W) { w -= p.W; ++h; }    // once at most for W >= 8 (positions past the last, of a small map: h >= H, never stored)
-            const bool ok = h + dr >= 0 && h + dr < p.H && w + dq >= 0 && w + dq < p.W;
-            m[j >> 1] |= ok ? (j & 1 ? 0xffff0000u : 0x0000ffffu) : 0u;
-        }
-    }
-    return u32x4{m[0], m[1], m[2], m[3]};
-}
-
-// the same for two of the positions, nb and nb + 1 (a row of positions has `rowlen` of them): a dword of the mask
+// which of two positions, nb and nb + 1 (a row of positions has `rowlen` of them), see a pixel of the image under a kernel tap: a
+// dword of the 16-byte mask of 8 positions; tap KK: none
 template <bool S2>
 __device__ __forceinline__ unsigned int conv_pair_mask(const ConvParams &p, int tap, int nb, int rowlen) {
     const int r = (tap * p.kw_magic) >> 8, q = tap - r * p.kw;
