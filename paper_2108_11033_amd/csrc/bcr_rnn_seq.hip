@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
             const unsigned int tag_mask = PLACED && t == 1 ? kSeqTagBits : 0xffffffffu;
             unsigned int others = 0;
             // the words of NJ pairs of sequences (of one sequence: a word is one hidden unit, or two of them), NI per
-            // thread and row of nw words, and what is done with word e of pair q
+            // thread and row of nw words, and what is done with word e of pair q; false: a wait has been given up
             auto words = [&](auto per_thread, int nw, int q0, auto park) {
                 constexpr int NI = decltype(per_thread)::value;
                 for (int base = tid; base < nw; base += NI * NTHR) {
@@ -380,7 +380,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     }
                     if (st_ < 0) {
                         flag = 1;
-                        return;
+                        return false;
                     }
                     if constexpr (PLACED) {
                         if (t == 1) {
@@ -397,13 +397,15 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                         }
                     }
                 }
+                return true;
             };
             if constexpr (MULTI) {
-                for (int q0 = 0; q0 < NQ; q0 += NJ)
-                    words(std::integral_constant<int, 4>{}, H, q0, [&](int q, int e, unsigned int pair) {
+                seq_waits(NQ, NJ, [&](int q0) {
+                    return words(std::integral_constant<int, 4>{}, H, q0, [&](int q, int e, unsigned int pair) {
                         hin[2 * q * hld + e] = (unsigned short)(pair & 0xffffu);
                         if (2 * q + 1 < B) hin[(2 * q + 1) * hld + e] = (unsigned short)(pair >> 16);
                     });
+                });
             } else if (p.unit_pairs) {
                 words(std::integral_constant<int, 2>{}, H / 2, 0,
                       [&](int, int e, unsigned int pair) { reinterpret_cast<unsigned int *>(hin)[e] = pair; });

@@ -1,4 +1,5 @@
-// Which sets of workgroups of the sequence kernel are placed on an XCD of their own, and how.
+// Rules of the sequence kernel that the host can check: which sets of workgroups run on an XCD of their own and how, and when a
+// thread's waits end.
 #pragma once
 #include <cstdint>
 
@@ -27,6 +28,15 @@ GRIM_HOST_DEVICE void seq_placed_at(int id, int wgs, int *set, int *unit) {
 constexpr int kSeqPlain = 0, kSeqPlaced = 1, kSeqClaimed = 2;
 GRIM_HOST_DEVICE bool seq_sets_claimed(int sets, int64_t wgs, int steps) {
     return sets % 8 != 0 && wgs > 1 && (sets + 7) / 8 * wgs <= 32 && steps >= 8;
+}
+
+// A step's waits of one thread, `per_wait` of the `pairs` of its workgroup's sequences at a time: once one has been given up (false)
+// no further one begins, so that a thread gives up after its limit of reads however many sequences its workgroup carries.
+template <class Wait>
+GRIM_HOST_DEVICE bool seq_waits(int pairs, int per_wait, Wait wait) {
+    for (int q0 = 0; q0 < pairs; q0 += per_wait)
+        if (!wait(q0)) return false;
+    return true;
 }
 
 }  // namespace grim

@@ -19,3 +19,15 @@ extern "C" int seq_placement_excess(int sets, int wgs) {
     }
     return *std::max_element(load.begin(), load.end()) - (sets * wgs + 7) / 8;
 }
+
+// reads a thread makes in a step of `pairs` pairs of sequences, `per_wait` at a time, whose wait number `fails` (< 0: none) never ends
+// and is given up after max_polls of them
+extern "C" int64_t seq_reads_of_a_step(int pairs, int per_wait, int fails, int max_polls) {
+    int64_t reads = 0;
+    const bool complete = grim::seq_waits(pairs, per_wait, [&](int q0) {
+        const bool ends = fails < 0 || q0 / per_wait < fails;
+        reads += ends ? 1 : max_polls;
+        return ends;
+    });
+    return complete == (fails < 0) ? reads : -1;
+}

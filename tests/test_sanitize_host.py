@@ -150,6 +150,17 @@ def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
             assert excess(sets, wgs) == 0, (sets, wgs)
 
 
+def test_a_step_of_many_sequences_gives_up_after_one_wait(tmp_path):
+    """A wait that is given up is a thread's last of the step, whichever of its workgroup's pairs of sequences it was for."""
+    reads = _host_library(tmp_path, "seq_placement").seq_reads_of_a_step
+    reads.restype = ctypes.c_int64
+    for pairs in range(1, 17):
+        waits = (pairs + 1) // 2
+        assert reads(pairs, 2, -1, 1000) == waits
+        for fails in range(waits):
+            assert reads(pairs, 2, fails, 1000) == fails + 1000, (pairs, fails)
+
+
 def test_division_by_an_inverse_made_beforehand(tmp_path):
     """Quotients around multiples of the divisor, up to the largest numbers a launch can hold, are those of the division."""
     faults = _host_library(tmp_path, "divide").divide_faults
