@@ -42,19 +42,7 @@ constexpr unsigned int kSeqPoison = 0xffffffffu;   // tag of a word whose produc
 constexpr unsigned int kSeqDefaultPolls = 1u << 21;
 constexpr size_t kSeqMaxLds = 160 * 1024 - 256;    // dynamic part: the kernel also has a few static bytes
 
-// How the workgroups of sets that are no multiple of eight come together: the sets are claimed.  Every XCD gets as many workgroups,
-// enough for all sets between them, and as soon as a set's worth of them runs on an XCD they take a set; what is not needed leaves
-// at once.  A call that runs alone thus has each set on one XCD, where words stay in its L2.  Where calls overlap and no set
-// fills up -- each could hold some of the compute units and wait for the rest -- a workgroup that has waited long enough
-// calls it off, and the first workgroups to ask, wherever they run, make up the sets: a call needs no more of the chip at
-// once than in the plain order.
-struct SeqClaim {
-    struct Xcd { unsigned int arrived, owns[31]; } xcd[16];        // workgroups that run; the set that each wgs of them have taken, plus one
-    unsigned int complete, ready, mode, asked;                     // sets' worths that run; that have a set; kClaim*; workgroups that asked
-};
 static_assert(sizeof(SeqClaim) <= kSeqClaimWords * 8, "room for the claim");
-constexpr unsigned int kClaimPlaced = 1, kClaimSpread = 2;         // SeqClaim::mode (0: open)
-constexpr int kSeqClaimPolls = 64;                                 // reads of the mode before a workgroup calls it off (about 1 us each)
 
 struct SeqParams {
     GemvDesc d1, d2;               // LSTM: the gate matrix; GRU: W_i and W_h
@@ -107,42 +95,22 @@ __device__ __forceinline__ unsigned int seq_xcd() {
     return (unsigned int)__builtin_amdgcn_s_getreg(20 | 31 << 11) & 15u;    // the whole of hardware register 20, XCC_ID
 }
 
-// One thread of a workgroup: its set and its number in the set, or set -1: not needed.
-__device__ inline void seq_claim(SeqClaim *c, int sets, int wgs, int *set, int *unit) {
-    constexpr int AGENT = __HIP_MEMORY_SCOPE_AGENT, RELAXED = __ATOMIC_RELAXED;
-    SeqClaim::Xcd *const x = &c->xcd[seq_xcd()];
-    const int number = (int)__hip_atomic_fetch_add(&x->arrived, 1u, RELAXED, AGENT);
-    const int slot = number / wgs;
-    if (number % wgs == wgs - 1) {
-        const unsigned int k = __hip_atomic_fetch_add(&c->complete, 1u, RELAXED, AGENT);
-        if ((int)k < sets) {
-            // (acknowledged before it is counted, so that whoever sees the mode sees it; read on this XCD only)
-            __hip_atomic_store(&x->owns[slot < 31 ? slot : 30], k + 1, RELAXED, AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if ((int)__hip_atomic_fetch_add(&c->ready, 1u, RELAXED, AGENT) == sets - 1) {
-                unsigned int open = 0;
-                (void)__hip_atomic_compare_exchange_strong(&c->mode, &open, kClaimPlaced, RELAXED, RELAXED, AGENT);
-            }
-        }
+// The claim's words (seq_claim): agent scope, as the workgroups of a call run on all XCDs
+struct SeqClaimMemory {
+    static constexpr int SCOPE = __HIP_MEMORY_SCOPE_AGENT, ORDER = __ATOMIC_RELAXED;
+    __device__ static unsigned int add_one(unsigned int *at) { return __hip_atomic_fetch_add(at, 1u, ORDER, SCOPE); }
+    __device__ static unsigned int load(unsigned int *at) { return __hip_atomic_load(at, ORDER, SCOPE); }
+    __device__ static void store_and_wait(unsigned int *at, unsigned int v) {
+        __hip_atomic_store(at, v, ORDER, SCOPE);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    unsigned int mode = 0;
-    for (int polls = 0; polls < kSeqClaimPolls && mode == 0; ++polls) {
-        if (polls) __builtin_amdgcn_s_sleep(4);
-        mode = __hip_atomic_load(&c->mode, RELAXED, AGENT);
+    __device__ static unsigned int set_if_zero(unsigned int *at, unsigned int v) {
+        unsigned int was = 0;
+        (void)__hip_atomic_compare_exchange_strong(at, &was, v, ORDER, ORDER, SCOPE);
+        return was;
     }
-    if (mode == 0) {
-        (void)__hip_atomic_compare_exchange_strong(&c->mode, &mode, kClaimSpread, RELAXED, RELAXED, AGENT);
-        if (mode == 0) mode = kClaimSpread;          // (mode: what was there before)
-    }
-    if (mode == kClaimPlaced) {
-        *set = slot < 31 ? (int)__hip_atomic_load(&x->owns[slot], RELAXED, AGENT) - 1 : -1;
-        *unit = number % wgs;
-    } else {
-        const int asked = (int)__hip_atomic_fetch_add(&c->asked, 1u, RELAXED, AGENT);
-        *set = asked < sets * wgs ? asked / wgs : -1;
-        *unit = asked % wgs;
-    }
-}
+    __device__ static void pause() { __builtin_amdgcn_s_sleep(4); }
+};
 
 // MULTI: a workgroup carries more than one sequence.  FORM: kSeqPlain: grid.y is the set; kSeqPlaced: every set of workgroups on
 // an XCD of its own (1-D grid); kSeqClaimed: see SeqClaim.  (A run-time switch instead costs the plain form 2 to 5 % of a step.)
@@ -165,7 +133,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     if constexpr (FORM == kSeqPlaced) seq_placed_at(blockIdx.x, H / p.BR, &set, &unit);
     if constexpr (FORM == kSeqClaimed) {
         __shared__ int place[2];
-        if (tid == 0) seq_claim(p.claim, p.sets, H / p.BR, &place[0], &place[1]);
+        if (tid == 0) seq_claim(p.claim, SeqClaimMemory{}, seq_xcd(), p.sets, H / p.BR, kSeqClaimPolls, &place[0], &place[1]);
         __syncthreads();
         set = __builtin_amdgcn_readfirstlane(place[0]);
         unit = __builtin_amdgcn_readfirstlane(place[1]);

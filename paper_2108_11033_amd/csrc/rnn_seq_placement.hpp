@@ -30,6 +30,54 @@ GRIM_HOST_DEVICE bool seq_sets_claimed(int sets, int64_t wgs, int steps) {
     return sets % 8 != 0 && wgs > 1 && (sets + 7) / 8 * wgs <= 32 && steps >= 8;
 }
 
+// How the workgroups of claimed sets come together.  Every XCD gets as many workgroups,
+// enough for all sets between them, and as soon as a set's worth of them runs on an XCD they take a set; what is not needed leaves
+// at once.  A call that runs alone thus has each set on one XCD, where words stay in its L2.  Where calls overlap and no set
+// fills up -- each could hold some of the compute units and wait for the rest -- a workgroup that has waited long enough
+// calls it off, and the first workgroups to ask, wherever they run, make up the sets: a call needs no more of the chip at
+// once than in the plain order.
+constexpr int kSeqClaimSlots = 31;                                 // sets' worths of one XCD that can take a set: no call has more sets to claim
+struct SeqClaim {
+    struct Xcd { unsigned int arrived, owns[kSeqClaimSlots]; } xcd[16];   // workgroups that run; the set that each wgs of them have taken, plus one
+    unsigned int complete, ready, mode, asked;                     // sets' worths that run; that have a set; kClaim*; workgroups that asked
+};
+constexpr unsigned int kClaimPlaced = 1, kClaimSpread = 2;         // SeqClaim::mode (0: open)
+constexpr int kSeqClaimPolls = 64;                                 // reads of the mode before a workgroup calls it off (about 1 us each)
+
+// One thread of a workgroup that runs on XCD `xcd`: its set and its number in the set, or set -1: not needed.  The words are reached
+// through `memory`, whose operations are single atomic accesses.
+template <class Memory>
+GRIM_HOST_DEVICE void seq_claim(SeqClaim *c, const Memory &memory, unsigned int xcd, int sets, int wgs, int max_polls, int *set, int *unit) {
+    SeqClaim::Xcd *const x = &c->xcd[xcd & 15u];
+    const int number = (int)memory.add_one(&x->arrived);
+    const int slot = number / wgs;
+    if (number % wgs == wgs - 1 && slot < kSeqClaimSlots) {
+        const unsigned int k = memory.add_one(&c->complete);
+        if ((int)k < sets) {
+            // (acknowledged before it is counted, so that whoever sees the mode sees it; read on this XCD only)
+            memory.store_and_wait(&x->owns[slot], k + 1);
+            if ((int)memory.add_one(&c->ready) == sets - 1) (void)memory.set_if_zero(&c->mode, kClaimPlaced);
+        }
+    }
+    unsigned int mode = 0;
+    for (int polls = 0; polls < max_polls && mode == 0; ++polls) {
+        if (polls) memory.pause();
+        mode = memory.load(&c->mode);
+    }
+    if (mode == 0) {
+        mode = memory.set_if_zero(&c->mode, kClaimSpread);
+        if (mode == 0) mode = kClaimSpread;
+    }
+    if (mode == kClaimPlaced) {
+        *set = slot < kSeqClaimSlots ? (int)memory.load(&x->owns[slot]) - 1 : -1;
+        *unit = number % wgs;
+    } else {
+        const int asked = (int)memory.add_one(&c->asked);
+        *set = asked < sets * wgs ? asked / wgs : -1;
+        *unit = asked % wgs;
+    }
+}
+
 // A step's waits of one thread, `per_wait` of the `pairs` of its workgroup's sequences at a time: once one has been given up (false)
 // no further one begins, so that a thread gives up after its limit of reads however many sequences its workgroup carries.
 template <class Wait>

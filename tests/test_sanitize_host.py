@@ -150,6 +150,24 @@ def test_sequence_sets_placed_on_xcds_crowd_none(tmp_path):
             assert excess(sets, wgs) == 0, (sets, wgs)
 
 
+@pytest.mark.parametrize("polls", [0, 1, 4, 64])
+def test_claimed_sets_have_every_workgroup_once(tmp_path, polls):
+    """Whatever order the workgroups of a call run in, wherever, and whenever one of them calls the claim off: every (set, number) is
+    one workgroup's, placed sets are on one XCD each, and the call ends where the chip has room for its sets."""
+    outcome = _host_library(tmp_path, "seq_claim").seq_claim_outcome
+    modes = {}
+    for sets, wgs in [(1, 2), (1, 32), (3, 8), (5, 16), (7, 4), (9, 2), (12, 8), (13, 3), (15, 16), (25, 2), (25, 8), (29, 2), (31, 2), (31, 8)]:
+        for xcds in range(4):
+            grid = 8 * ((sets + 7) // 8) * wgs
+            for room in sorted({sets * wgs, (sets * wgs + grid) // 2, grid}):
+                for seed in range(3 if grid > 64 else 20):
+                    mode = outcome(sets, wgs, xcds, polls, room, seed)
+                    assert mode > 0, (mode, sets, wgs, xcds, room, seed)
+                    modes.setdefault(mode, 0)
+                    modes[mode] += 1
+    assert 2 in modes and (polls < 64 or modes[1] > modes[2]), modes          # called off with few polls, mostly placed with many
+
+
 def test_a_step_of_many_sequences_gives_up_after_one_wait(tmp_path):
     """A wait that is given up is a thread's last of the step, whichever of its workgroup's pairs of sequences it was for."""
     reads = _host_library(tmp_path, "seq_placement").seq_reads_of_a_step
