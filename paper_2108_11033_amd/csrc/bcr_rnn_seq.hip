@@ -66,7 +66,7 @@ struct SeqParams {
     int64_t ldhs32;
     unsigned long long *exch;      // sets x 2 x NQ x H words (two 16-bit values, tag); all tags zero at launch
     SeqClaim *claim;               // kSeqClaimed: zero at launch
-    int32_t sets;
+    int32_t sets, claim_polls;
     int32_t *status;               // set to 1 by a workgroup that gives up
     uint32_t max_polls;
 };
@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
     if constexpr (FORM == kSeqPlaced) seq_placed_at(blockIdx.x, H / p.BR, &set, &unit);
     if constexpr (FORM == kSeqClaimed) {
         __shared__ int place[2];
-        if (tid == 0) seq_claim(p.claim, SeqClaimMemory{}, seq_xcd(), p.sets, H / p.BR, kSeqClaimPolls, &place[0], &place[1]);
+        if (tid == 0) seq_claim(p.claim, SeqClaimMemory{}, seq_xcd(), p.sets, H / p.BR, p.claim_polls, &place[0], &place[1]);
         __syncthreads();
         set = __builtin_amdgcn_readfirstlane(place[0]);
         unit = __builtin_amdgcn_readfirstlane(place[1]);
@@ -675,6 +675,7 @@ grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, con
     const int form = seq_sets_on_xcds(sets) ? kSeqPlaced : seq_sets_claimed(sets, wgs, T) ? kSeqClaimed : kSeqPlain;
     int64_t words = (int64_t)sets * 2 * p.NQ * H;                      // at most 2 * kSeqMaxBatch * H
     p.sets = sets;
+    p.claim_polls = seq_claim_polls(p.max_polls);
     p.claim = nullptr;
     if (form == kSeqClaimed) {                                         // (behind the words of the sets: there is room for it behind the most)
         p.claim = reinterpret_cast<SeqClaim *>(p.exch + words);

@@ -21,28 +21,37 @@ GRIM_HOST_DEVICE void seq_placed_at(int id, int wgs, int *set, int *unit) {
     *unit = slot % wgs;
 }
 
-// Forms of a call: sets in grid.y, placed as above, or claimed by the XCDs (bcr_rnn_seq.hip).  Claimed are sets of workgroups that an
-// XCD's 32 compute units hold one each of, in sequences long enough to pay for the claim (2 us; a step on one XCD is 0.4 to 0.5 us
-// shorter than one across them: an LSTM of 1024 / 512 / 256 units, one sequence of 64 steps 132 / 129 / 130 -> 107 / 104 / 96 us, GRU
-// 137 / 139 / 149 -> 114 / 109 / 104, four sequences of 1024 units 135 -> 109, 137 -> 116).
+// Forms of a call: sets in grid.y, placed as above, or claimed by the XCDs (seq_claim below).  Claimed are sets of workgroups that an
+// XCD's 32 compute units hold one each of, in sequences long enough to pay for the claim: a step on one XCD is 0.4 to 0.6 us
+// shorter than one across them, the claim takes 3 to 4 us for one set, 4 to 5 for up to eight, up to 8 for 25.  us per call in the plain
+// order / claimed, of 8, 10, 12, 16 steps (LSTM, 32-row blocks): 1024 units, one sequence 21.2 / 21.8, 25.2 / 24.9, 29.3 / 28.2, 37.3 / 34.6;
+// seven 21.9 / 22.9, 26.1 / 26.1, 30.1 / 29.3, 38.4 / 35.5; 256 units, one 21.4 / 18.7; twelve 21.0 / 22.1, 24.9 / 25.3, 28.8 / 28.3, 36.5 / 33.8;
+// 25 of them 21.0 / 24.0, 24.8 / 26.7, 28.7 / 29.5, 36.5 / 34.9.  Of 64 steps, one sequence of 1024 / 512 / 256 units 128 / 125 / 130 -> 110 / 104 / 95.
+// What it costs where other work fills the chip: the call ends when its last workgroup has had a compute unit, also those that have nothing
+// to do.  Beside products of 4096 x 4096 on another stream one sequence of 1024 units takes 123 / 131 us for 16 steps, 177 / 213 for 64, three
+// 115 / 145 and 187 / 240; 256 units (64 workgroups, not 256) 116 / 113 and 167 / 144.
 constexpr int kSeqPlain = 0, kSeqPlaced = 1, kSeqClaimed = 2;
 GRIM_HOST_DEVICE bool seq_sets_claimed(int sets, int64_t wgs, int steps) {
-    return sets % 8 != 0 && wgs > 1 && (sets + 7) / 8 * wgs <= 32 && steps >= 8;
+    return sets % 8 != 0 && wgs > 1 && (sets + 7) / 8 * wgs <= 32 && steps >= (sets > 8 ? 16 : wgs > 16 ? 10 : 8);
 }
 
-// How the workgroups of claimed sets come together.  Every XCD gets as many workgroups,
-// enough for all sets between them, and as soon as a set's worth of them runs on an XCD they take a set; what is not needed leaves
-// at once.  A call that runs alone thus has each set on one XCD, where words stay in its L2.  Where calls overlap and no set
-// fills up -- each could hold some of the compute units and wait for the rest -- a workgroup that has waited long enough
-// calls it off, and the first workgroups to ask, wherever they run, make up the sets: a call needs no more of the chip at
-// once than in the plain order.
+// How the workgroups of claimed sets come together.  Every XCD gets as many workgroups, enough for all sets between them (up to eight
+// times as many as the sets have), and as soon as a set's worth of them runs on an XCD they take a set.  All of them wait until
+// every set is taken; those that are in none then leave.  A call that runs alone thus has each set on one XCD, where words stay in
+// its L2.  Where calls overlap and no set fills up -- each could hold some of the compute units and wait for the rest -- a
+// workgroup that has waited long enough calls it off, and the first workgroups to ask, wherever they run, make up the sets: the
+// call then waits for no more workgroups to run at once than in the plain order.
 constexpr int kSeqClaimSlots = 31;                                 // sets' worths of one XCD that can take a set: no call has more sets to claim
 struct SeqClaim {
     struct Xcd { unsigned int arrived, owns[kSeqClaimSlots]; } xcd[16];   // workgroups that run; the set that each wgs of them have taken, plus one
     unsigned int complete, ready, mode, asked;                     // sets' worths that run; that have a set; kClaim*; workgroups that asked
 };
 constexpr unsigned int kClaimPlaced = 1, kClaimSpread = 2;         // SeqClaim::mode (0: open)
-constexpr int kSeqClaimPolls = 64;                                 // reads of the mode before a workgroup calls it off (about 1 us each)
+// Reads of the mode (1 us each) before a workgroup calls it off: less than the shortest claimed sequence takes.  A call that runs alone needs
+// no more than eight (four call off one of 1024 units: 110 -> 128 us); 8 to 64 are alike beside other work.  A caller's own limit on
+// the reads of a wait shortens this one in proportion.
+constexpr int kSeqClaimPolls = 16;
+GRIM_HOST_DEVICE int seq_claim_polls(uint32_t max_polls) { return (int)(max_polls >> 15) < kSeqClaimPolls ? (int)(max_polls >> 15) : kSeqClaimPolls; }
 
 // One thread of a workgroup that runs on XCD `xcd`: its set and its number in the set, or set -1: not needed.  The words are reached
 // through `memory`, whose operations are single atomic accesses.

@@ -20,6 +20,8 @@ extern "C" int seq_placement_excess(int sets, int wgs) {
     return *std::max_element(load.begin(), load.end()) - (sets * wgs + 7) / 8;
 }
 
+extern "C" int seq_form_is_claimed(int sets, int wgs, int steps) { return grim::seq_sets_claimed(sets, wgs, steps); }
+
 // reads a thread makes in a step of `pairs` pairs of sequences, `per_wait` at a time, whose wait number `fails` (< 0: none) never ends
 // and is given up after max_polls of them
 extern "C" int64_t seq_reads_of_a_step(int pairs, int per_wait, int fails, int max_polls) {

@@ -482,12 +482,14 @@ def test_lstm_sequence_forms_of_the_exchange_words(H, I, BR, BC, kr, kc, B):
     ("gru", 32, 16, 16, 4, 4, 9),           # sets of two workgroups
 ])
 @pytest.mark.parametrize("streams", [1, 4])
-def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams):
+@pytest.mark.parametrize("max_polls", [0, 30000])
+def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams, max_polls):
     """Calls whose sets XCDs take as they fill up, alone and four at a time on streams of their own: the bits of sequences of seven
-    steps and the rest, which run in the plain order (fewer than eight steps)."""
+    steps and fewer, which run in the plain order.  With a limit of 30 000 reads to a wait the first workgroup that asks calls the claim
+    off, and the sets are made up of workgroups from anywhere."""
     from helpers import pack_workload, to_device
     torch, dev, g = _gpu()
-    dtype, I, T = gen.F16, H, 14
+    dtype, I, T = gen.F16, H, 20
     cases = []
     for k in range(streams):
         if cell == "lstm":
@@ -498,7 +500,7 @@ def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams):
         xs = np.concatenate([_inputs(T, I, dtype, 2450 + 40 * k + b)[:, None] for b in range(B)], axis=1).reshape(T * B, I)
         cases.append((mats, to_device(xs, dtype), torch.cuda.Stream() if streams > 1 else torch.cuda.current_stream()))
 
-    def call(mats, xs, stream, cuts):
+    def call(mats, xs, stream, cuts, polls=0):
         h0, st = torch.zeros((B, H), dtype=xs.dtype, device=dev), torch.zeros((B, H), dtype=torch.float32, device=dev)
         hs = torch.empty((T * B, H), dtype=xs.dtype, device=dev)
         status = torch.full((len(cuts),), -1, dtype=torch.int32, device=dev)
@@ -506,17 +508,17 @@ def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams):
         for i, (t0, t1) in enumerate(cuts):
             x, out, h = xs[t0 * B:t1 * B], hs[t0 * B:t1 * B], h0 if t0 == 0 else hs[(t0 - 1) * B:t0 * B]
             if cell == "lstm":
-                g.lstm_sequence_batch(mats[0], x, I, t1 - t0, B, None, h, st, out, H, None, 0, status[i:], 0, stream)
+                g.lstm_sequence_batch(mats[0], x, I, t1 - t0, B, None, h, st, out, H, None, 0, status[i:], polls, stream)
             else:
-                g.gru_sequence_batch(mats[0], mats[1], x, I, t1 - t0, B, None, None, h, st, out, H, None, 0, status[i:], 0, stream)
+                g.gru_sequence_batch(mats[0], mats[1], x, I, t1 - t0, B, None, None, h, st, out, H, None, 0, status[i:], polls, stream)
         return hs, st, status, h0
 
     plain = []
     for case in cases:
-        plain.append(call(*case, [(0, 7), (7, T)]))
+        plain.append(call(*case, [(0, 7), (7, 14), (14, T)]))
         torch.cuda.synchronize()
     for _ in range(3):
-        whole = [call(*case, [(0, T)]) for case in cases]
+        whole = [call(*case, [(0, T)], max_polls) for case in cases]
         torch.cuda.synchronize()
         for a, b in zip(plain, whole):
             assert (a[2] == 0).all() and (b[2] == 0).all()

@@ -168,6 +168,20 @@ def test_claimed_sets_have_every_workgroup_once(tmp_path, polls):
     assert 2 in modes and (polls < 64 or modes[1] > modes[2]), modes          # called off with few polls, mostly placed with many
 
 
+def test_sets_are_claimed_where_that_is_quicker(tmp_path):
+    claimed = _host_library(tmp_path, "seq_placement").seq_form_is_claimed
+    for (sets, wgs, steps), quicker in (
+            # microseconds in the plain order, claimed
+            ((1, 32, 8), False), ((1, 32, 10), True),             # 21.2, 21.8; 25.2, 24.9
+            ((7, 32, 8), False), ((7, 32, 12), True),             # 21.9, 22.9; 30.1, 29.3
+            ((1, 8, 8), True), ((7, 8, 8), True),                 # 21.4, 18.7; 21.0, 20.6
+            ((12, 8, 8), False), ((12, 8, 10), False), ((12, 8, 16), True),      # 21.0, 22.1; 24.9, 25.3; 36.5, 33.8
+            ((25, 8, 12), False), ((25, 8, 16), True),            # 28.7, 29.5; 36.5, 34.9
+            ((12, 16, 8), False), ((12, 16, 16), True),           # 21.6, 23.5; 37.6, 35.4
+            ((8, 32, 64), False), ((9, 32, 64), False)):          # placed by their numbers; no room for two sets on an XCD
+        assert bool(claimed(sets, wgs, steps)) == quicker, (sets, wgs, steps)
+
+
 def test_a_step_of_many_sequences_gives_up_after_one_wait(tmp_path):
     """A wait that is given up is a thread's last of the step, whichever of its workgroup's pairs of sequences it was for."""
     reads = _host_library(tmp_path, "seq_placement").seq_reads_of_a_step
