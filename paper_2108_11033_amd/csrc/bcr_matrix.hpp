@@ -8,6 +8,8 @@
 
 #include "grim_bcr.h"
 
+#include "rnn_seq_placement.hpp"
+
 namespace grim {
 
 constexpr int kConvTallRuns = 4;        // 16-row runs that share the steps of a convolution plan's layout of tall runs
@@ -300,10 +302,7 @@ bool rnn_gather_applies(const grim_bcr_matrix *A, const void *X, int64_t ldx, co
 grim_status launch_rnn_gather(const grim_bcr_matrix *A, const void *X, int64_t ldx, float *G, int64_t ldg, const grim_bcr_matrix *A2,
                               const void *X2, int64_t ldx2, float *G2, int64_t ldg2, int32_t batch, const RnnCell &cell, hipStream_t stream);
 // a recurrent layer over a whole sequence in one launch (kind 1: LSTM, K1 = I + H; kind 2: GRU, K1 = I, K2 = H), `batch`
-// sequences side by side (1 .. kSeqMaxBatch); exch: at most 2 * batch * H words of 8 bytes; hidden sizes up to kSeqMaxH
-constexpr int64_t kSeqMaxH = 8192;
-constexpr int32_t kSeqMaxBatch = 32;
-constexpr int64_t kSeqClaimWords = 272;                            // words of a claim (bcr_rnn_seq.hip) behind the exchange words
+// sequences side by side (1 .. kSeqMaxBatch); exch: seq_exchange_words of the matrix's rows; hidden sizes up to kSeqMaxH
 bool rnn_seq_applies(int kind, int32_t BR, int32_t BC, int32_t dtype, int32_t ukr, int32_t ukc, int64_t K1, int64_t K2,
                      int64_t I, int64_t H, int32_t batch);
 grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, const int32_t *pos1, const int32_t *pos2,

@@ -1572,12 +1572,11 @@ int32_t grim_bcr_rnn_step_launches(const grim_bcr_matrix *A, const grim_bcr_matr
 }
 
 // exchange words of the sequence kernel: allocated with the first sequence call on a matrix, freed with the matrix
-static grim_status seq_exchange_of(const grim_bcr_matrix *A, int64_t H, void **out) {
+static grim_status seq_exchange_of(const grim_bcr_matrix *A, void **out) {
     std::lock_guard<std::mutex> hold(A->seq_lock);
     if (!A->seq_exch) {
         void *ptr = nullptr;
-        // two slots of at most one word per hidden unit and sequence, for the largest batch
-        if (hipMalloc(&ptr, ((size_t)(2 * H) * kSeqMaxBatch + kSeqClaimWords) * 8) != hipSuccess) {
+        if (hipMalloc(&ptr, (size_t)seq_exchange_words(A->M) * 8) != hipSuccess) {
             (void)hipGetLastError();
             return GRIM_ERR_ALLOC;
         }
@@ -1634,7 +1633,7 @@ grim_status grim_bcr_lstm_sequence_batch(const grim_bcr_matrix *A, const void *x
     if (ldxs < I || ldhs < H || (hs32_dev && ldhs32 < H)) return GRIM_ERR_SHAPE;
     if (!grim_bcr_rnn_sequence_batch_supported(A, nullptr, batch)) return GRIM_ERR_UNSUPPORTED;
     void *exch = nullptr;
-    st = seq_exchange_of(A, H, &exch);
+    st = seq_exchange_of(A, &exch);
     if (st != GRIM_OK) return st;
     return launch_rnn_seq(1, desc_of(A), nullptr, A->dev.strip_pos, nullptr, A->BR, A->BC, A->dtype, A->gemv.uniform_kr,
                           A->gemv.uniform_kc, A->K, 0, I, H, T, batch, xs_dev, ldxs, h0_dev, bias_dev, nullptr, c_dev, hs_dev,
@@ -1682,7 +1681,7 @@ grim_status grim_bcr_gru_sequence_batch(const grim_bcr_matrix *Ai, const grim_bc
     if (ldxs < I || ldhs < H || (hs32_dev && ldhs32 < H)) return GRIM_ERR_SHAPE;
     if (!grim_bcr_rnn_sequence_batch_supported(Ai, Ah, batch)) return GRIM_ERR_UNSUPPORTED;
     void *exch = nullptr;
-    st = seq_exchange_of(Ah, H, &exch);
+    st = seq_exchange_of(Ah, &exch);
     if (st != GRIM_OK) return st;
     const GemvDesc dh = desc_of(Ah);
     return launch_rnn_seq(2, desc_of(Ai), &dh, Ai->dev.strip_pos, Ah->dev.strip_pos, Ai->BR, Ai->BC, Ai->dtype,

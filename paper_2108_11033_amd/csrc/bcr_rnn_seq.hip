@@ -606,16 +606,6 @@ static int compute_units() {
     return n;
 }
 
-// `batch` sequences on H / BR workgroups per set: as many sets as the compute units hold (at most one per sequence),
-// then several sequences per workgroup
-static void seq_split(int64_t H, int BR, int batch, int cus, int *sets, int *per_wg) {
-    const int64_t wgs = H / BR;
-    int g = (int)std::min<int64_t>(batch, std::max<int64_t>(1, cus / wgs));
-    const int spb = (batch + g - 1) / g;
-    *per_wg = spb;
-    *sets = (batch + spb - 1) / spb;
-}
-
 // kind 1: LSTM (K1 = I + H), kind 2: GRU (K1 = I, K2 = H).  The matrices qualify when they hold two-byte elements in
 // blocks of at most 32 x 32 that all keep one compiled (rows, columns) pair, a strip has at most 64 column blocks
 // (a lane keeps one block), H is a multiple of BR and one workgroup per BR hidden units fits the GPU at once; 1 .. 32
@@ -673,7 +663,7 @@ grim_status launch_rnn_seq(int kind, const GemvDesc &d1, const GemvDesc *d2, con
     p.max_polls = max_polls ? max_polls : kSeqDefaultPolls;
     const int64_t wgs = H / BR;
     const int form = seq_sets_on_xcds(sets) ? kSeqPlaced : seq_sets_claimed(sets, wgs, T) ? kSeqClaimed : kSeqPlain;
-    int64_t words = (int64_t)sets * 2 * p.NQ * H;                      // at most 2 * kSeqMaxBatch * H
+    int64_t words = seq_call_words(H, sets, per_wg);
     p.sets = sets;
     p.claim_polls = seq_claim_polls(p.max_polls);
     p.claim = nullptr;

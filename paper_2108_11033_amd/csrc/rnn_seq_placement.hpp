@@ -1,11 +1,32 @@
 // Rules of the sequence kernel that the host can check: which sets of workgroups run on an XCD of their own and how, and when a
 // thread's waits end.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 
 #include "host_device.hpp"
 
 namespace grim {
+
+constexpr int64_t kSeqMaxH = 8192;
+constexpr int32_t kSeqMaxBatch = 32;
+constexpr int64_t kSeqClaimWords = 272;                            // words of a claim (seq_claim below) behind the exchange words
+
+// `batch` sequences on H / BR workgroups per set: as many sets as the compute units hold (at most one per sequence),
+// then several sequences per workgroup
+inline void seq_split(int64_t H, int BR, int batch, int cus, int *sets, int *per_wg) {
+    const int64_t wgs = H / BR;
+    int g = (int)std::min<int64_t>(batch, std::max<int64_t>(1, cus / wgs));
+    const int spb = (batch + g - 1) / g;
+    *per_wg = spb;
+    *sets = (batch + spb - 1) / spb;
+}
+
+// Exchange words of a call: two slots of one word per hidden unit and pair of a workgroup's sequences, for every set
+inline int64_t seq_call_words(int64_t H, int sets, int per_wg) { return (int64_t)sets * 2 * ((per_wg + 1) / 2) * H; }
+// Words, a claim's among them, that a matrix of M rows has for the largest batch of any sequence that it may be part of: one of 4 H rows
+// is an LSTM's, one of 3 H rows a GRU's, and 12 n rows can be both in turn.
+inline int64_t seq_exchange_words(int64_t M) { return seq_call_words(M / 3, kSeqMaxBatch, 1) + kSeqClaimWords; }
 
 // A set's workgroups on one XCD (workgroup ids are dealt to the eight of them round-robin): the exchange words of a set are
 // then written and read from there alone.  Workgroups of a call wait for one another, so all of them have to be resident:

@@ -33,3 +33,15 @@ extern "C" int64_t seq_reads_of_a_step(int pairs, int per_wait, int fails, int m
     });
     return complete == (fails < 0) ? reads : -1;
 }
+
+// words by which the call with the most exchange words (of 1 .. 32 sequences through a layer of H units in strips of BR rows, on `cus`
+// compute units) exceeds what a matrix of M rows has; <= 0: there is room
+extern "C" int64_t seq_words_missing(int64_t M, int64_t H, int BR, int cus) {
+    int64_t most = 0;
+    for (int batch = 1; batch <= grim::kSeqMaxBatch; ++batch) {
+        int sets, per_wg;
+        grim::seq_split(H, BR, batch, cus, &sets, &per_wg);
+        most = std::max(most, grim::seq_call_words(H, sets, per_wg) + grim::kSeqClaimWords);
+    }
+    return most - grim::seq_exchange_words(M);
+}

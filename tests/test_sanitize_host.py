@@ -182,6 +182,18 @@ def test_sets_are_claimed_where_that_is_quicker(tmp_path):
         assert bool(claimed(sets, wgs, steps)) == quicker, (sets, wgs, steps)
 
 
+def test_a_matrix_has_room_for_the_words_of_every_sequence(tmp_path):
+    """Its exchange words are allocated by the first call on it; 12 n rows are an LSTM's gate matrix of 3 n units and the hidden
+    side of a GRU of 4 n."""
+    missing = _host_library(tmp_path, "seq_placement").seq_words_missing
+    missing.restype, missing.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    for n in (1, 2, 5, 8, 10, 24, 32, 85, 96, 256, 341):
+        for H in (3 * n, 4 * n):
+            for BR in [d for d in (1, 2, 3, 4, 5, 8, 16, 32) if H % d == 0 and H // d <= 256]:
+                for cus in (32, 80, 256, 304):
+                    assert missing(12 * n, H, BR, cus) <= 0, (n, H, BR, cus)
+
+
 def test_a_step_of_many_sequences_gives_up_after_one_wait(tmp_path):
     """A wait that is given up is a thread's last of the step, whichever of its workgroup's pairs of sequences it was for."""
     reads = _host_library(tmp_path, "seq_placement").seq_reads_of_a_step
