@@ -482,14 +482,12 @@ def test_lstm_sequence_forms_of_the_exchange_words(H, I, BR, BC, kr, kc, B):
     ("gru", 32, 16, 16, 4, 4, 9),           # sets of two workgroups
 ])
 @pytest.mark.parametrize("streams", [1, 4])
-@pytest.mark.parametrize("max_polls", [0, 30000])
-def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams, max_polls):
+def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams):
     """Calls whose sets XCDs take as they fill up, alone and four at a time on streams of their own: the bits of sequences of seven
-    steps and fewer, which run in the plain order.  With a limit of 30 000 reads to a wait the first workgroup that asks calls the claim
-    off, and the sets are made up of workgroups from anywhere."""
+    steps and the rest, which run in the plain order (fewer than eight steps)."""
     from helpers import pack_workload, to_device
     torch, dev, g = _gpu()
-    dtype, I, T = gen.F16, H, 20
+    dtype, I, T = gen.F16, H, 14
     cases = []
     for k in range(streams):
         if cell == "lstm":
@@ -500,7 +498,7 @@ def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams, max_poll
         xs = np.concatenate([_inputs(T, I, dtype, 2450 + 40 * k + b)[:, None] for b in range(B)], axis=1).reshape(T * B, I)
         cases.append((mats, to_device(xs, dtype), torch.cuda.Stream() if streams > 1 else torch.cuda.current_stream()))
 
-    def call(mats, xs, stream, cuts, polls=0):
+    def call(mats, xs, stream, cuts):
         h0, st = torch.zeros((B, H), dtype=xs.dtype, device=dev), torch.zeros((B, H), dtype=torch.float32, device=dev)
         hs = torch.empty((T * B, H), dtype=xs.dtype, device=dev)
         status = torch.full((len(cuts),), -1, dtype=torch.int32, device=dev)
@@ -508,14 +506,61 @@ def test_sequences_of_claimed_sets(cell, H, BR, BC, kr, kc, B, streams, max_poll
         for i, (t0, t1) in enumerate(cuts):
             x, out, h = xs[t0 * B:t1 * B], hs[t0 * B:t1 * B], h0 if t0 == 0 else hs[(t0 - 1) * B:t0 * B]
             if cell == "lstm":
-                g.lstm_sequence_batch(mats[0], x, I, t1 - t0, B, None, h, st, out, H, None, 0, status[i:], polls, stream)
+                g.lstm_sequence_batch(mats[0], x, I, t1 - t0, B, None, h, st, out, H, None, 0, status[i:], 0, stream)
             else:
-                g.gru_sequence_batch(mats[0], mats[1], x, I, t1 - t0, B, None, None, h, st, out, H, None, 0, status[i:], polls, stream)
+                g.gru_sequence_batch(mats[0], mats[1], x, I, t1 - t0, B, None, None, h, st, out, H, None, 0, status[i:], 0, stream)
         return hs, st, status, h0
 
     plain = []
     for case in cases:
-        plain.append(call(*case, [(0, 7), (7, 14), (14, T)]))
+        plain.append(call(*case, [(0, 7), (7, T)]))
+        torch.cuda.synchronize()
+    for _ in range(3):
+        whole = [call(*case, [(0, T)]) for case in cases]
+        torch.cuda.synchronize()
+        for a, b in zip(plain, whole):
+            assert (a[2] == 0).all() and (b[2] == 0).all()
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("cell,H,B", [
+    ("lstm", 256, 1),           # one set
+    ("lstm", 96, 13),           # two sets to an XCD, sixteen slots for thirteen
+    ("lstm", 64, 31),           # four
+    ("gru", 512, 5),
+])
+@pytest.mark.parametrize("streams", [1, 4])
+@pytest.mark.parametrize("max_polls", [0, 30000])
+def test_sequences_of_claimed_sets_placed_and_called_off(cell, H, B, streams, max_polls):
+    """Twenty steps, for which every number of sets is claimed, against the same in calls of seven and fewer, which run in the plain
+    order: the same bits.  With a limit of 30 000 reads to a wait the first workgroup that asks calls the claim off, and the sets are
+    made up of workgroups from anywhere."""
+    from helpers import pack_workload, to_device
+    torch, dev, g = _gpu()
+    dtype, T, rows = gen.F16, 20, (4 if cell == "lstm" else 3) * H
+    cases = []
+    for k in range(streams):
+        mats = [pack_workload(g, _scaled_weights(rows, K, dtype, 2501 + 10 * k + j, 2.0), dtype,
+                              gen.random_mask(rows, K, 32, 32, 8, 8, seed=2500 + 10 * k + j))
+                for j, K in enumerate([2 * H] if cell == "lstm" else [H, H])]
+        xs = np.concatenate([_inputs(T, H, dtype, 2550 + 40 * k + b)[:, None] for b in range(B)], axis=1).reshape(T * B, H)
+        cases.append((mats, to_device(xs, dtype), torch.cuda.Stream() if streams > 1 else torch.cuda.current_stream()))
+
+    def call(mats, xs, stream, cuts, polls):
+        h, st = torch.zeros((B, H), dtype=xs.dtype, device=dev), torch.zeros((B, H), dtype=torch.float32, device=dev)
+        hs = torch.empty((T * B, H), dtype=xs.dtype, device=dev)
+        status = torch.full((len(cuts),), -1, dtype=torch.int32, device=dev)
+        kept = [h]
+        stream.wait_stream(torch.cuda.current_stream())
+        run = g.lstm_sequence_batch if cell == "lstm" else g.gru_sequence_batch
+        for i, (t0, t1) in enumerate(cuts):
+            run(*mats, xs[t0 * B:t1 * B], H, t1 - t0, B, *[None] * len(mats), h, st, hs[t0 * B:t1 * B], H, None, 0, status[i:], polls, stream)
+            h = hs[(t1 - 1) * B:t1 * B]
+        return hs, st, status, kept
+
+    plain = []
+    for case in cases:
+        plain.append(call(*case, [(0, 7), (7, 14), (14, T)], 0))
         torch.cuda.synchronize()
     for _ in range(3):
         whole = [call(*case, [(0, T)], max_polls) for case in cases]
