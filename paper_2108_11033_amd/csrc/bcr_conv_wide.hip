@@ -19,19 +19,10 @@ namespace grim {
 // tile widths compiled for the convolution: the widest for the whole rounds, 32 columns for what is left
 constexpr int kConvWideRestTile = 32;
 
-static size_t conv_wide_lds(const grim_bcr_matrix *A, int tn, int KK) {
-    // two stages; kConvAnyTap: the (tap, piece) mask table, four per-chunk row tables
-    const size_t out = A->BR == 32 ? wide_out_bytes(tn) : 0;      // the outputs' way through LDS, when the stages are done with
-    const size_t stages = std::max(2 * (size_t)wide_stage_bytes(A->mmaw.chunk_rows, tn, A->mmaw.amax[2]), out);
-    if (conv_tap_ways(tn, KK, A->mmaw.chunk_rows)) return stages;
-    return stages + (size_t)(KK + 1) * (tn / 8) * 16 + 4 * (size_t)wide_max_chunk_rows(A->BR) * 8;
-}
-
 // the widest compiled tile whose records fit the fetching waves' registers and whose stages fit LDS; 0: none
 static int conv_wide_main_tile(const grim_bcr_matrix *A, int KK) {
     for (int tn : {192, 128, 96}) {
-        if (A->BR == 32 ? tn != 96 : tn == 96) continue;
-        if ((int64_t)A->mmaw.amax[2] <= (int64_t)wide_sru(tn) * kWideFetchThreads && conv_wide_lds(A, tn, KK) <= 160 * 1024) return tn;
+        if (conv_wide_fits(A->mmaw, A->BR, tn, KK)) return tn;
     }
     return 0;
 }
@@ -131,7 +122,7 @@ static grim_status conv_wide_range(const grim_bcr_matrix *A, WideParams p, int t
     const int64_t nwg = ((int64_t)p.ntiles + 15) / 16 * 16 * p.ngroups;
     if (nwg + rest_wgs > 0x7fffffff) return GRIM_ERR_SHAPE;
     if (rest) {
-        const size_t lds2 = std::max(conv_wide_lds(A, tn, p.KK), rest_lds);
+        const size_t lds2 = std::max((size_t)conv_wide_lds(A->mmaw, A->BR, tn, p.KK), rest_lds);
         if (lds2 > 160 * 1024) return GRIM_ERR_UNSUPPORTED;
         const bool bf2 = A->dtype == GRIM_BF16;
         if (A->BR == 16) {
@@ -142,7 +133,7 @@ static grim_status conv_wide_range(const grim_bcr_matrix *A, WideParams p, int t
         if (tn == 96) return bf2 ? launch_conv_wide_rest_inst<true, 32, 3>(p, *rest, lds2, nwg, rest_wgs, stream) : launch_conv_wide_rest_inst<false, 32, 3>(p, *rest, lds2, nwg, rest_wgs, stream);
         return GRIM_ERR_UNSUPPORTED;
     }
-    const size_t lds = conv_wide_lds(A, tn, p.KK);
+    const size_t lds = (size_t)conv_wide_lds(A->mmaw, A->BR, tn, p.KK);
     const bool bf = A->dtype == GRIM_BF16;
     if (A->BR == 16) {
         if (tn == 192) return bf ? launch_conv_wide_inst<true, 16, 12>(p, lds, nwg, stream) : launch_conv_wide_inst<false, 16, 12>(p, lds, nwg, stream);

@@ -13,6 +13,7 @@
 #include "bcr_matrix.hpp"
 #include "conv_rules.hpp"
 #include "group_rules.hpp"
+#include "staged_room.hpp"
 
 using namespace grim;
 
@@ -44,90 +45,8 @@ grim_status validate_sets(int64_t nb, int32_t B, const int32_t *ptr, const uint1
 
 // ---- derived layout: matrix-core SpMM ---------------------------------------------------
 
-bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks, int32_t max_chunk_rows, int gsel,
-                          int64_t max_group_bytes) {
-    L.chunk_blocks = chunk_blocks;
-    L.chunk_rows = L.chunk_blocks * A->BC;
-    L.nchunks = (int32_t)((A->nbc + L.chunk_blocks - 1) / L.chunk_blocks);
-    L.ks = A->BR == 16 ? 32 : 16;
-    const int32_t ng = L.ks / 8;                       // groups of 8 k slots per step
-    const int32_t hdr = L.ks * 2 + ng * 8;             // header bytes per step (a multiple of 16)
-    L.cptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
-    L.bptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
-    L.recs.clear();
-    // the kept columns of a (chunk, strip), one after the other whatever block they belong to
-    struct Slot { int64_t t, w; uint32_t mask; int32_t kc; uint16_t row; };   // stored block, its column's first weight, its rows; staged row
-    std::vector<Slot> slots;
-    slots.reserve((size_t)chunk_blocks * A->BC);
-    int64_t step = 0;
-    const uint16_t *w = reinterpret_cast<const uint16_t *>(A->weights.data());
-    const uint16_t zero_row = (uint16_t)L.chunk_rows;
-    for (int32_t ch = 0; ch < L.nchunks; ++ch) {
-        const int64_t c0 = (int64_t)ch * L.chunk_blocks, c1 = std::min<int64_t>(A->nbc, c0 + L.chunk_blocks);
-        for (int64_t st = 0; st < A->nbr; ++st) {
-            L.cptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)step;
-            L.bptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)(L.recs.size() / 16);
-            slots.clear();
-            for (int64_t c = c0; c < c1; ++c) {
-                const int64_t t = st * A->nbc + c;
-                const int32_t kr = A->row_ptr[t + 1] - A->row_ptr[t], kc = A->col_ptr[t + 1] - A->col_ptr[t];
-                if (kr == 0 || kc == 0) continue;       // nothing to multiply
-                uint32_t mask = 0;
-                for (int32_t qq = A->row_ptr[t]; qq < A->row_ptr[t + 1]; ++qq) mask |= 1u << A->row_idx[qq];
-                for (int32_t j = 0; j < kc; ++j)
-                    slots.push_back({t, A->blk_ptr[t] + j, mask, kc, (uint16_t)((c - c0) * A->BC + A->col_idx[A->col_ptr[t] + j])});
-            }
-            const size_t ngroups = (slots.size() + L.ks - 1) / L.ks * ng;
-            const size_t nst = ngroups / ng;
-            const size_t region0 = L.recs.size();
-            L.recs.resize(region0 + nst * hdr, 0);
-            uint32_t pay16 = (uint32_t)(nst * hdr / 16);    // next free payload unit, from the region start
-            for (size_t q = 0; q < ngroups; ++q) {
-                const size_t sidx = q / ng, g = q % ng;
-                const Slot *gs = slots.data() + std::min(q * 8, slots.size());
-                const int32_t n = (int32_t)std::min<size_t>(8, slots.size() - std::min(q * 8, slots.size()));
-                uint16_t rows[8];
-                uint32_t rowmask = 0, off = 0;
-                for (int32_t e = 0; e < 8; ++e) {
-                    rows[e] = e < n ? gs[e].row : zero_row;
-                    if (e < n) rowmask |= gs[e].mask;
-                }
-                // slot rows: quad qd of the group pairs slot qd with slot qd + 4
-                unsigned char *h = L.recs.data() + region0 + sidx * hdr;
-                uint16_t *hs = reinterpret_cast<uint16_t *>(h) + g * 8;
-                for (int32_t qd = 0; qd < 4; ++qd) {
-                    hs[2 * qd] = rows[qd];
-                    hs[2 * qd + 1] = rows[qd + 4];
-                }
-                if (n > 0) {
-                    off = pay16;
-                    const int32_t kr = __builtin_popcount(rowmask);
-                    const size_t p0 = L.recs.size();
-                    L.recs.resize(p0 + (size_t)kr * 16, 0);
-                    h = L.recs.data() + region0 + sidx * hdr;     // resize may move the buffer
-                    uint16_t *pw = reinterpret_cast<uint16_t *>(L.recs.data() + p0);
-                    if (gs[0].t == gs[n - 1].t) {
-                        for (int32_t i = 0; i < kr; ++i)
-                            for (int32_t e = 0; e < n; ++e) pw[i * 8 + e] = w[gs[e].w + (int64_t)i * gs[e].kc];
-                    } else {
-                        for (int32_t e = 0; e < n; ++e) {
-                            const uint16_t *src = w + gs[e].w;
-                            for (uint32_t m = gs[e].mask; m; m &= m - 1, src += gs[e].kc)
-                                pw[__builtin_popcount(rowmask & ((m & (0u - m)) - 1)) * 8 + e] = *src;
-                        }
-                    }
-                    pay16 += (uint32_t)kr;
-                }
-                uint32_t *hd = reinterpret_cast<uint32_t *>(h + L.ks * 2) + g * 2;
-                hd[0] = rowmask;
-                hd[1] = off;
-            }
-            step += (int64_t)nst;
-        }
-        L.cptr[(size_t)ch * (A->nbr + 1) + A->nbr] = (int32_t)step;
-        L.bptr[(size_t)ch * (A->nbr + 1) + A->nbr] = (int32_t)(L.recs.size() / 16);
-    }
-    L.nsteps = step;
+// most units any (group of strips, chunk) holds
+void staged_amax(const grim_bcr_matrix *A, MmaLayout &L) {
     for (int gi = 0; gi < 4; ++gi) {
         const int64_t Gs = 4 << gi;
         int32_t amax = 0;
@@ -138,27 +57,155 @@ bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks
         }
         L.amax[gi] = amax;
     }
-    // fits the kernel's smallest launch (strip groups of 4 << gsel)?
-    return L.chunk_rows <= max_chunk_rows && (int64_t)L.amax[gsel] * 16 <= max_group_bytes && L.recs.size() < (size_t(1) << 31) * 16;
+}
+
+// Where the regions of a layout with groups of one block each lie (no records): false where they are too many
+bool size_one_block_groups(const grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks) {
+    L.chunk_blocks = chunk_blocks;
+    L.chunk_rows = chunk_blocks * A->BC;
+    L.nchunks = (int32_t)((A->nbc + chunk_blocks - 1) / chunk_blocks);
+    L.ks = A->BR == 16 ? 32 : 16;
+    const int32_t ng = L.ks / 8, hdr = L.ks * 2 + ng * 8;
+    L.bptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
+    int64_t units = 0;
+    for (int32_t ch = 0; ch < L.nchunks; ++ch) {
+        const int64_t c0 = (int64_t)ch * chunk_blocks, c1 = std::min<int64_t>(A->nbc, c0 + chunk_blocks);
+        for (int64_t st = 0; st <= A->nbr; ++st) {
+            L.bptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)units;
+            if (st == A->nbr) break;
+            int64_t groups = 0;
+            for (int64_t t = st * A->nbc + c0; t < st * A->nbc + c1; ++t) {
+                const int32_t kr = A->row_ptr[t + 1] - A->row_ptr[t], kc = A->col_ptr[t + 1] - A->col_ptr[t];
+                if (kr == 0) continue;
+                groups += (kc + 7) / 8;
+                units += (int64_t)((kc + 7) / 8) * kr;
+            }
+            units += (groups + ng - 1) / ng * hdr / 16;
+        }
+        if (units >= int64_t(1) << 31) return false;
+    }
+    staged_amax(A, L);
+    return true;
+}
+
+// packed: the kept columns of a (chunk, strip) one after the other, eight to a group whichever blocks they belong to; otherwise a
+// block's columns begin a group
+bool build_mma_layout_for(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_blocks, bool packed) {
+    L.chunk_blocks = chunk_blocks;
+    L.chunk_rows = L.chunk_blocks * A->BC;
+    L.nchunks = (int32_t)((A->nbc + L.chunk_blocks - 1) / L.chunk_blocks);
+    L.ks = A->BR == 16 ? 32 : 16;
+    const int32_t ng = L.ks / 8;                       // groups of 8 k slots per step
+    const int32_t hdr = L.ks * 2 + ng * 8;             // header bytes per step (a multiple of 16)
+    L.cptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
+    L.bptr.assign((size_t)L.nchunks * (A->nbr + 1), 0);
+    L.recs.clear();
+    L.recs.reserve(A->weights.size() * 5 / 4 + A->col_idx.size() * 3);
+    const uint16_t *w = reinterpret_cast<const uint16_t *>(A->weights.data());
+    const uint16_t zero_row = (uint16_t)L.chunk_rows;
+    int64_t step = 0;
+    uint16_t dense[32][8] = {};                        // weights of the group being filled
+    uint16_t rows[8];                                  // its staged rows
+    uint32_t rowmask = 0;
+    int32_t slots = 0;
+    size_t region0 = 0, group = 0;
+    auto flush_group = [&]() {
+        if (slots == 0) return;
+        const size_t q = group++, p0 = L.recs.size();
+        L.recs.resize(p0 + (size_t)__builtin_popcount(rowmask) * 16);
+        unsigned char *h = L.recs.data() + region0 + q / ng * hdr, *dst = L.recs.data() + p0;
+        // slot rows: quad qd of the group pairs slot qd with slot qd + 4
+        uint16_t *hs = reinterpret_cast<uint16_t *>(h) + q % ng * 8;
+        for (int32_t e = 0; e < slots; ++e) hs[e < 4 ? 2 * e : 2 * (e - 4) + 1] = rows[e];
+        uint32_t *hd = reinterpret_cast<uint32_t *>(h + L.ks * 2) + q % ng * 2;
+        hd[0] = rowmask;
+        hd[1] = (uint32_t)((p0 - region0) / 16);
+        for (uint32_t m = rowmask; m; m &= m - 1, dst += 16) {
+            uint16_t *r = dense[__builtin_ctz(m)];
+            std::memcpy(dst, r, 16);
+            std::memset(r, 0, 16);
+        }
+        rowmask = 0;
+        slots = 0;
+    };
+    for (int32_t ch = 0; ch < L.nchunks; ++ch) {
+        const int64_t c0 = (int64_t)ch * L.chunk_blocks, c1 = std::min<int64_t>(A->nbc, c0 + L.chunk_blocks);
+        for (int64_t st = 0; st < A->nbr; ++st) {
+            L.cptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)step;
+            L.bptr[(size_t)ch * (A->nbr + 1) + st] = (int32_t)(L.recs.size() / 16);
+            int64_t cols = 0, groups = 0;
+            for (int64_t t = st * A->nbc + c0; t < st * A->nbc + c1; ++t) {
+                if (A->row_ptr[t + 1] == A->row_ptr[t]) continue;       // nothing to multiply
+                const int32_t kc = A->col_ptr[t + 1] - A->col_ptr[t];
+                cols += kc;
+                groups += (kc + 7) / 8;
+            }
+            if (packed) groups = (cols + 7) / 8;
+            const size_t nst = (size_t)((groups + ng - 1) / ng);
+            region0 = L.recs.size();
+            group = 0;
+            L.recs.resize(region0 + nst * hdr, 0);
+            for (size_t s = 0; s < nst; ++s) {
+                uint16_t *hs = reinterpret_cast<uint16_t *>(L.recs.data() + region0 + s * hdr);
+                std::fill(hs, hs + L.ks, zero_row);
+            }
+            for (int64_t c = c0; c < c1; ++c) {
+                const int64_t t = st * A->nbc + c;
+                const int32_t r0 = A->row_ptr[t], r1 = A->row_ptr[t + 1], k0 = A->col_ptr[t], kc = A->col_ptr[t + 1] - k0;
+                if (r0 == r1) continue;
+                for (int32_t j = 0; j < kc;) {
+                    const int32_t n = std::min<int32_t>(kc - j, 8 - slots);
+                    for (int32_t e = 0; e < n; ++e) rows[slots + e] = (uint16_t)((c - c0) * A->BC + A->col_idx[k0 + j + e]);
+                    const uint16_t *src = w + A->blk_ptr[t] + j;
+                    for (int32_t q = r0; q < r1; ++q, src += kc) {
+                        rowmask |= 1u << A->row_idx[q];
+                        std::memcpy(&dense[A->row_idx[q]][slots], src, (size_t)n * 2);
+                    }
+                    slots += n;
+                    j += n;
+                    if (slots == 8) flush_group();
+                }
+                if (!packed) flush_group();
+            }
+            flush_group();
+            step += (int64_t)nst;
+        }
+        L.cptr[(size_t)ch * (A->nbr + 1) + A->nbr] = (int32_t)step;
+        L.bptr[(size_t)ch * (A->nbr + 1) + A->nbr] = (int32_t)(L.recs.size() / 16);
+    }
+    L.nsteps = step;
+    staged_amax(A, L);
+    return L.recs.size() < (size_t(1) << 31) * 16;
 }
 
 // max_rows: most rows of X per chunk; gsel / max_group_bytes: the records of a group of 4 << gsel strips must fit
 // max_group_bytes per chunk (the kernel's LDS room for them)
 void build_mma_layout(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_rows_opt, int32_t max_rows, int gsel,
-                      int64_t max_group_bytes) {
+                      int64_t max_group_bytes, bool wide) {
     L.present = false;
     if (A->dtype == GRIM_F32) return;
     if (A->BR != 16 && A->BR != 32) return;
     if (A->BC > max_rows) return;
     const int32_t want = chunk_rows_opt > 0 ? std::min<int32_t>(chunk_rows_opt, max_rows) : max_rows;
-    // largest chunk whose weight records still leave room in LDS; denser matrices get smaller chunks
-    int32_t blocks = std::max<int32_t>(1, want / A->BC);
-    bool fits = build_mma_layout_for(A, L, blocks, max_rows, gsel, max_group_bytes);
-    while (!fits && blocks > 1) {
+    const auto fits = [&](const MmaLayout &R) { return R.chunk_rows <= max_rows && (int64_t)R.amax[gsel] * 16 <= max_group_bytes; };
+    // largest chunk whose weight records still leave room in LDS; denser matrices get smaller chunks.  Groups that several blocks
+    // share store the rows of all of them, so they take fewer steps and, at some kept counts, more room (512 x 4608 of mixed rates in 32 x 32
+    // blocks: 7 % more): they are taken where they have room in every launch form that groups of one block each would have room in.
+    const int32_t most = std::max<int32_t>(1, want / A->BC);
+    MmaLayout one;
+    int32_t blocks = most;
+    bool any = size_one_block_groups(A, one, blocks) && fits(one);
+    while (!any && blocks > 1) {
         blocks = (blocks + 1) / 2;
-        fits = build_mma_layout_for(A, L, blocks, max_rows, gsel, max_group_bytes);
+        any = size_one_block_groups(A, one, blocks) && fits(one);
     }
-    if (!fits) {   // even one column block per chunk overflows LDS: leave this matrix to the FMA kernel
+    bool done = false;
+    for (int32_t b = most; !done && b >= blocks; b = (b + 1) / 2) {
+        done = build_mma_layout_for(A, L, b, true) && fits(L) && (!any || fits_wherever(L, one, A->BR, wide));
+        if (b == 1) break;
+    }
+    if (!done && any) done = build_mma_layout_for(A, L, blocks, false);
+    if (!done) {   // even one column block per chunk overflows LDS: leave this matrix to the FMA kernel
         L.cptr.clear(); L.bptr.clear(); L.recs.clear();
         return;
     }
@@ -736,8 +783,8 @@ grim_status grim_bcr_pack(const void *W_host, grim_dtype dt, int64_t M, int64_t 
             // (each layout is built from the canonical arrays alone: the three that write the most run side by side when
             // there is enough to write -- 4096 x 2048 at 10.7x: 11.6 -> 6.6 ms for the whole pack)
             const int32_t rows_opt = opt ? opt->chunk_rows : 0;
-            auto mma = [&]() { build_mma_layout(A, A->mma, rows_opt, kMmaMaxChunkRows, 0, 16 * 1024); };
-            auto wide = [&]() { build_mma_layout(A, A->mmaw, rows_opt, wide_max_chunk_rows(A->BR), 2, kWideMaxRecordBytes); };
+            auto mma = [&]() { build_mma_layout(A, A->mma, rows_opt, kMmaMaxChunkRows, 0, 16 * 1024, false); };
+            auto wide = [&]() { build_mma_layout(A, A->mmaw, rows_opt, wide_max_chunk_rows(A->BR), 2, kWideMaxRecordBytes, true); };
             std::future<void> f1, f2;
             if (A->nnz >= 32 * 1024 && dt != GRIM_F32) {
                 try {

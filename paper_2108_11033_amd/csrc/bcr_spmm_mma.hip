@@ -7,6 +7,7 @@
 // (work-sorted, Section 4.2) order so the waves of a workgroup carry near-equal work.  Accumulation is fp32,
 // order fixed, no atomics.
 #include "spmm_common.hpp"
+#include "staged_room.hpp"
 
 namespace grim {
 
@@ -24,13 +25,6 @@ struct MmaParams {
     int32_t xvec;   // widest aligned vector (elements: 8, 4 or 1) for rows of X
     int32_t yvec;   // 4 when rows of Y allow aligned float4 stores, else 1
 };
-
-
-// LDS bytes of one stage: staged X rows + zero row, then room for amax 16-byte units of
-// records rounded up to whole 1 KB slots
-__host__ __device__ inline int mma_stage_bytes(int chunk_rows, int pitch, int amax) {
-    return (chunk_rows + 1) * pitch + ((amax * 16 + 1023) / 1024 + 1) * 1024;
-}
 
 // Workgroup = NW consumer waves + NP producer waves; LDS holds two stages, each
 //   [chunk_rows staged rows of X | one zero row | the chunk's step records].
@@ -377,31 +371,6 @@ __global__ void __launch_bounds__((NW + NP) * 64) bcr_spmm_mma(MmaParams p) {
 
 bool mma_supported(const grim_bcr_matrix *A) { return A->mma.present; }
 
-static int amax_of(const grim_bcr_matrix *A, int g) { return A->mma.amax[g <= 4 ? 0 : g <= 8 ? 1 : g <= 16 ? 2 : 3]; }
-
-// Compiled launch shapes.  Groups of 4 strips use 4 consumer waves, larger groups 8 (LDS reads
-// per MFMA are high, so a second consumer wave per SIMD hides their latency); always 8
-// producer waves (two teams of 4), each holding SX slots of X and SR slots of records.
-struct MmaShape { int tn, strips, nw, sx, sr; };
-static bool mma_shape(int BR, int tn, int strips, MmaShape *out) {
-    const int sx = tn == 32 ? 4 : tn == 64 ? 8 : tn == 128 ? 16 : 0;      // 256 staged rows
-    const int sr = strips == 4 ? 4 : strips == 8 ? 8 : strips == 16 ? 12 : 0;
-    if (!sx || !sr) return false;
-    if (tn == 128 && strips != 4) return false;
-    const int nw = strips == 4 ? 4 : 8;
-    if (BR == 32 && (strips / nw) * (tn / 32) > 4) return false;           // accumulator registers
-    *out = MmaShape{tn, strips, nw, sx, sr};
-    return true;
-}
-static bool mma_shape_fits(const grim_bcr_matrix *A, int tn, int strips) {
-    MmaShape sh;
-    if (!mma_shape(A->BR, tn, strips, &sh)) return false;
-    const int rps = 1024 / (tn * 2), amax = amax_of(A, strips);
-    if ((A->mma.chunk_rows + rps - 1) / rps > 4 * sh.sx) return false;
-    if ((amax * 16 + 1023) / 1024 > 4 * sh.sr) return false;
-    return 2 * (int64_t)mma_stage_bytes(A->mma.chunk_rows, tn * 2, amax) + (int64_t)A->mma.nchunks * (strips + 1) * 8 <= 160 * 1024;
-}
-
 template <bool BF16, int BR, int NT, int SPW, int NW, int SX, int SR>
 static grim_status launch_mma_inst(const MmaParams &p, hipStream_t stream) {
     constexpr int TN = NT * (BR == 16 ? 16 : 32);
@@ -427,7 +396,7 @@ static grim_status launch_mma_br(MmaParams &p, const grim_bcr_matrix *A, int til
     constexpr int NSUB = BR == 16 ? 16 : 32;
     p.ntiles = (int32_t)((p.N + tile_n - 1) / tile_n);
     p.ngroups = (p.nbr + strips - 1) / strips;
-    p.amax = amax_of(A, strips);
+    p.amax = mma_amax(A->mma, strips);
 #define GRIM_CASE(TN_, G_, NW_, SX_, SR_) \
     if (tile_n == TN_ && strips == G_) return launch_mma_inst<BF16, BR, TN_ / NSUB, G_ / NW_, NW_, SX_, SR_>(p, stream);
     GRIM_CASE(32, 4, 4, 4, 4) GRIM_CASE(32, 8, 8, 4, 8) GRIM_CASE(32, 16, 8, 4, 12)
@@ -450,7 +419,7 @@ double mma_best_shape(const grim_bcr_matrix *A, int64_t N, int32_t tile_n, int32
         for (int g : {16, 8, 4}) {
             if (strips_per_wg && g != strips_per_wg) continue;
             if (g > 4 && A->nbr <= g / 2) continue;
-            if (!mma_shape_fits(A, t, g)) continue;
+            if (!mma_shape_fits(A->mma, A->BR, t, g)) continue;
             const int64_t nwg = ((N + t - 1) / t) * ((A->nbr + g - 1) / g);
             const double rounds = (double)((nwg + 255) / 256);
             const double bytes = (double)A->K * t * 2 * (t == 32 ? 1.8 : 1.0) +
@@ -474,7 +443,7 @@ int64_t mma_whole_rounds(const grim_bcr_matrix *A, int64_t N, int *tn_out, int *
     if (cost_all < 0) return N;
     *tn_out = tn; *g_out = g;
     const int64_t ntiles = (N + tn - 1) / tn, ngroups = (A->nbr + g - 1) / g;
-    const int64_t lds = 2 * (int64_t)mma_stage_bytes(A->mma.chunk_rows, tn * 2, amax_of(A, g)) + (int64_t)A->mma.nchunks * (g + 1) * 8;
+    const int64_t lds = 2 * (int64_t)mma_stage_bytes(A->mma.chunk_rows, tn * 2, mma_amax(A->mma, g)) + (int64_t)A->mma.nchunks * (g + 1) * 8;
     const int threads = ((g == 4 ? 4 : 8) + 8) * 64;
     int64_t per_cu = 160 * 1024 / lds;
     if (per_cu > 2048 / threads) per_cu = 2048 / threads;
@@ -503,7 +472,7 @@ grim_status launch_spmm_mma(const grim_bcr_matrix *A, const void *X, int64_t N, 
     if (!tn || !strips) {
         if (mma_best_shape(A, N, tile_n, strips_per_wg, &tn, &strips) < 0) return GRIM_ERR_UNSUPPORTED;
     }
-    if (!mma_shape_fits(A, tn, strips)) return GRIM_ERR_UNSUPPORTED;
+    if (!mma_shape_fits(A->mma, A->BR, tn, strips)) return GRIM_ERR_UNSUPPORTED;
     MmaParams p;
     p.recs = A->mma.d_recs;
     p.cptr = A->mma.d_cptr;

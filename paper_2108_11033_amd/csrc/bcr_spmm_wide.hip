@@ -22,13 +22,6 @@
 
 namespace grim {
 
-// compiled tile widths: BR = 16: 128 and 192 columns, BR = 32: 96 columns (its accumulators leave no room for more)
-static bool wide_tile_ok(int BR, int tn) { return BR == 16 ? (tn == 128 || tn == 192) : BR == 32 ? tn == 96 : false; }
-
-static int64_t wide_lds_bytes(const grim_bcr_matrix *A, int tn) {
-    return 2 * (int64_t)wide_stage_bytes(A->mmaw.chunk_rows, tn, A->mmaw.amax[2]);
-}
-
 bool wide_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ldx, const float *Y, int64_t ldy, int32_t tile_n) {
     if (!A->mmaw.present || A->dtype == GRIM_F32) return false;
     if (reinterpret_cast<uintptr_t>(X) % 16 != 0 || ldx % 8 != 0 || N % 8 != 0) return false;      // 16-byte row pieces
@@ -37,8 +30,7 @@ bool wide_applies(const grim_bcr_matrix *A, const void *X, int64_t N, int64_t ld
     if (A->K * ldx * 2 >= (int64_t(1) << 31)) return false;                                        // 32-bit buffer offsets
     for (int tn : {96, 128, 192}) {
         if (tile_n && tn != tile_n) continue;
-        if (wide_tile_ok(A->BR, tn) && N >= tn && wide_lds_bytes(A, tn) <= 160 * 1024 &&
-            (int64_t)A->mmaw.amax[2] <= (int64_t)wide_sru(tn) * kWideFetchThreads) return true;
+        if (N >= tn && wide_fits(A->mmaw, A->BR, tn)) return true;
     }
     return false;
 }
@@ -142,7 +134,7 @@ grim_status launch_spmm_wide(const grim_bcr_matrix *A, const void *X, int64_t N,
     int64_t nwg = 0;
     const grim_status st = wide_setup(A, X, N, ldx, Y, ldy, tile_n, &p, &tn, &nwg);
     if (st != GRIM_OK) return st;
-    const size_t lds = (size_t)wide_lds_bytes(A, tn);
+    const size_t lds = (size_t)wide_lds_bytes(A->mmaw, tn);
     const bool bf = A->dtype == GRIM_BF16;
     if (A->BR == 16) {
         if (tn == 128) return bf ? launch_wide_inst<true, 16, 8>(p, lds, nwg, stream) : launch_wide_inst<false, 16, 8>(p, lds, nwg, stream);
@@ -168,7 +160,7 @@ grim_status launch_spmm_wide_with_rest(const grim_bcr_matrix *A, const void *X, 
     if (st != GRIM_OK) return st;
     if (!form.aligned || form.narrow || form.solo || !form.eight) return GRIM_ERR_UNSUPPORTED;
     if (wide_wgs + form.nwg > 0x7fffffff) return GRIM_ERR_SHAPE;
-    const size_t lds = std::max<size_t>((size_t)wide_lds_bytes(A, tn), (size_t)(kWideMulWaves + kWideFetchWaves) * gather_wave_lds(4));
+    const size_t lds = std::max<size_t>((size_t)wide_lds_bytes(A->mmaw, tn), (size_t)(kWideMulWaves + kWideFetchWaves) * gather_wave_lds(4));
     const bool bf = A->dtype == GRIM_BF16;
     if (A->BR == 16) {
         if (tn == 128)

@@ -5,8 +5,8 @@
 #pragma once
 #include <algorithm>
 
-#include "conv_taps.hpp"
 #include "spmm_common.hpp"
+#include "staged_room.hpp"
 
 namespace grim {
 
@@ -63,29 +63,7 @@ struct __attribute__((packed, aligned(2))) WideWindow {
     unsigned int d[4];
 };
 
-constexpr int kWideMulWaves = 8;     // multiplying waves, two strips each
-constexpr int kWideThreads = (kWideMulWaves + kWideFetchWaves) * 64;
-constexpr int kWideStrips = 2 * kWideMulWaves;   // strips per workgroup
-// 16-byte record units per fetching thread and chunk: 8 = 32 KB per (chunk, group), the layout's limit; the
-// 192-column shape, whose rows of X take more registers, has room for 4 (16 KB)
-constexpr int wide_sru(int tn) { return tn == 192 ? 4 : 8; }
-static_assert(wide_sru(128) * kWideFetchThreads * 16 == kWideMaxRecordBytes, "record staging registers cover the layout's limit");
-
-// Rows of a stage are padded by 32 bytes: consecutive rows then start 32 bytes apart modulo the 256-byte bank line
-// (pitches 224, 288 and 416 give eight distinct offsets), so the four rows one transpose read gathers -- 32 bytes
-// of each -- spread over the banks without a swizzle, and the addresses of a row's sub-tiles differ by constants.
-constexpr int kWidePad = 32;
-
 constexpr int wide_gcd(int a, int b) { return b == 0 ? a : wide_gcd(b, a % b); }
-
-__host__ __device__ inline int wide_stage_bytes(int chunk_rows, int tn, int amax) {
-    return (chunk_rows + 1) * (tn * 2 + kWidePad) + amax * 16;
-}
-
-// Bytes between the rows of a strip's 16-bit outputs where they pass through LDS (32-row strips), and LDS for all of them: 16
-// bytes of padding put the two rows a write names on different banks.
-constexpr int wide_out_pitch(int tn) { return tn * 2 + 16; }
-constexpr int wide_out_bytes(int tn) { return kWideMulWaves * 32 * wide_out_pitch(tn); }
 
 // How the convolution's rows of a chunk are dealt to the fetching threads.
 //   kConvAnyTap: 16-byte units in order; the row's channel and tap and the unit's validity mask come out of tables in LDS.

@@ -43,6 +43,15 @@ bool decode(const grim_bcr_matrix *A, const grim::GatherLayout &L, int slots, bo
 }  // namespace
 
 extern "C" {
+// a staged layout's rows to a chunk, chunks and most 16-byte units a chunk holds for groups of 4, 8, 16, 32 strips
+int grim_test_staged_sizes(const grim_bcr_matrix *A, int wide, int64_t *out) {
+    const grim::MmaLayout &L = wide ? A->mmaw : A->mma;
+    if (!L.present) return 1;
+    out[0] = L.chunk_rows;
+    out[1] = L.nchunks;
+    for (int g = 0; g < 4; ++g) out[2 + g] = L.amax[g];
+    return 0;
+}
 // 0: decoded into W; 1: the matrix has no such layout; 2: the layout is not in order
 int grim_test_decode_gather32(const grim_bcr_matrix *A, unsigned char *W, int64_t ldw) {
     if (!A->gather32.present) return 1;

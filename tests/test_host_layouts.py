@@ -147,3 +147,82 @@ def test_layouts_without_a_decoder_in_the_library(decoders, dtype, reorder, M, K
     assert res == (0 if has else 1)
     if has:
         assert got.tobytes() == ref.tobytes()
+
+
+def _sizes_of_one_block_groups(mask, M, K, BR, BC, max_rows, g_most, most_bytes):
+    """Sizes of a staged layout in which every group of k slots belongs to one block, at the largest chunk that fits."""
+    nbr, nbc = M // BR, K // BC
+    kr, kc = np.diff(mask.row_ptr).reshape(nbr, nbc), np.diff(mask.col_ptr).reshape(nbr, nbc)
+    ng, hdr = (4, 6) if BR == 16 else (2, 3)                    # groups to a step, 16-byte units of a step's header
+    groups = np.where(kr > 0, (kc + 7) // 8, 0)
+    blocks = max(1, max_rows // BC)
+    while True:
+        nchunks = -(-nbc // blocks)
+        most = {}
+        for g in (4, 8, 16, 32):
+            most[g] = max(int(sum(-(-int(groups[s, c:c + blocks].sum()) // ng) * hdr + int((groups * kr)[s, c:c + blocks].sum())
+                                  for s in range(t, min(nbr, t + g)))) for c in range(0, nbc, blocks) for t in range(0, nbr, g))
+        if most[g_most] * 16 <= most_bytes or blocks == 1:
+            return blocks * BC, nchunks, most
+        blocks = (blocks + 1) // 2
+
+
+def _wide_forms(BR, rows, nchunks, most):
+    """(tile, kernel taps; 0: a product) that have room for the records: eight 16-byte units per fetching thread (four beside the rows of
+    192 columns), two stages and the tables of a convolution that needs them in 160 KB."""
+    forms = set()
+    for tn in (96,) if BR == 32 else (128, 192):
+        stages = 2 * ((rows + 1) * (2 * tn + 32) + 16 * most[16])
+        if most[16] > 256 * (4 if tn == 192 else 8) or stages > 160 * 1024:
+            continue
+        forms.add((tn, 0))
+        for taps in range(1, 256):
+            ways = 256 // (taps * (tn // 8))
+            by_tap = ways > 0 and -(-(-(-rows // taps)) // ways) <= (11 if tn == 96 else 15)
+            tables = 0 if by_tap else (taps + 1) * (tn // 8) * 16 + 4 * (192 if BR == 32 else 128) * 8
+            if stages + tables <= 160 * 1024:
+                forms.add((tn, taps))
+    return forms
+
+
+def _staged_forms(BR, rows, nchunks, most):
+    """(tile, strips) that have room: 16 KB of records for four strips, 32 for eight, 48 for sixteen, two stages in 160 KB."""
+    forms = set()
+    for tn in (32, 64, 128):
+        for strips in (4, 8, 16):
+            if (tn == 128 and strips != 4) or (BR == 32 and strips // min(strips, 8) * (tn // 32) > 4):
+                continue
+            kb = -(-most[strips] * 16 // 1024)
+            if kb <= {4: 16, 8: 32, 16: 48}[strips] and 2 * ((rows + 1) * tn * 2 + (kb + 1) * 1024) + nchunks * (strips + 1) * 8 <= 160 * 1024:
+                forms.add((tn, strips))
+    return forms
+
+
+@pytest.mark.parametrize("BR,BC,kr,kc", [
+    (16, 16, (6,), (4, 8)),             # groups that blocks share take more room than 192-column tiles have
+    (16, 16, (8,), (4, 12)),
+    (16, 16, (4, 8, 16), (6, 10)),
+    (32, 16, (12,), (4, 8, 16)),        # ... and would need smaller chunks
+    (32, 16, (8, 16, 32), (4, 8, 16)),
+    (32, 16, (10,), (4, 8)),
+    (32, 32, (16,), (12,)),
+    (32, 32, (8, 16, 32), (6, 10)),
+    (32, 32, (4, 8, 16), (4, 8, 16)),
+    (16, 32, (8,), (8,)),
+])
+def test_staged_layouts_have_room_in_every_form_that_one_block_groups_have(decoders, BR, BC, kr, kc):
+    """A launch form that a caller asks for by its tile is refused where a chunk's records have no room: packing columns of several
+    blocks into a group must not take one away, nor a row from a chunk."""
+    M, K = 16 * BR, 768
+    for seed in range(4):
+        mask = gen.random_mask(M, K, BR, BC, kr, kc, seed=900 + seed)
+        W = gen.normal_weights(M, K, gen.F16, seed=901)
+        A = g.pack(W, gen.F16, BR, BC, mask.row_ptr, mask.row_idx, mask.col_ptr, mask.col_idx, host_only=2, no_reorder=True)
+        for wide, forms, max_rows, g_most, most_bytes in ((0, _staged_forms, 256, 4, 16 * 1024),
+                                                          (1, _wide_forms, 192 if BR == 32 else 128, 16, 32 * 1024)):
+            out = np.zeros(6, dtype=np.int64)
+            assert decoders.grim_test_staged_sizes(A.handle, wide, out.ctypes.data_as(ctypes.c_void_p)) == 0
+            rows, nchunks, most = _sizes_of_one_block_groups(mask, M, K, BR, BC, max_rows, g_most, most_bytes)
+            assert out[0] >= rows, (wide, seed, out, rows)
+            missing = forms(BR, rows, nchunks, most) - forms(BR, int(out[0]), int(out[1]), dict(zip((4, 8, 16, 32), out[2:].tolist())))
+            assert not missing, (wide, seed, sorted(missing)[:5], out, rows, most)
