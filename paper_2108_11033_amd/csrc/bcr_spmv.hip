@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(gemv_threads(B), (B == 1 ? 6 : 1)) bcr_spmv(Ge
     const int tid = threadIdx.x;
     const int64_t t = blockIdx.x;            // stored strip
     const int64_t mi = blockIdx.y;           // matrix of the group
-    const GemvGlobal d = to_global(p.table ? p.table[mi] : mi ? p.second : p.single);
+    const GemvGlobal d = gemv_matrix(p, mi);
     const GRIM_GLOBAL char *W = d.weights;
     const GRIM_GLOBAL T *x = (const GRIM_GLOBAL T *)p.x + mi * p.x_stride;
     GRIM_GLOBAL float *y = (GRIM_GLOBAL float *)p.y + mi * p.y_stride;
@@ -236,11 +236,6 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_spmv_wave_exact(Ge
     constexpr int PB = exact_pad_period(NV);     // one vector of padding after every PB blocks (0: none)
     static_assert(KR * KC * ESZ % 16 == 0 && (ESZ == 4 || KC % 2 == 0) && KC <= 32 && KR <= 32, "block shape");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // (what the prologue needs of the arguments in one trip through the scalar cache: asked for where each is first used, the
-    // trips follow one another)
-    asm volatile("" ::"s"(p.table), "s"(p.single.weights), "s"(p.single.masks), "s"(p.single.strip_order), "s"(p.x), "s"(p.y), "s"(p.x_stride),
-                 "s"(p.K), "s"(p.nbc), "s"(p.BC), "s"(p.BR), "s"(p.seg_blocks), "s"(p.xvec16), "s"(p.sps), "s"(p.wpg), "s"(p.nbr_total), "s"(p.wbytes),
-                 "s"(p.ldx));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // GRU: both input vectors sit in LDS, the hidden-side one behind the input-side one
@@ -254,7 +249,7 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_spmv_wave_exact(Ge
     char *wl = smem + xbytes + wave * p.wbytes;
     float *part = reinterpret_cast<float *>(wl);                  // reuses the weights' space
 
-    const GemvGlobal d = to_global(p.table ? p.table[mi] : mi ? p.second : p.single);
+    const GemvGlobal d = gemv_matrix(p, mi);
     const GRIM_GLOBAL char *W = d.weights;
     const GRIM_GLOBAL T *x = (const GRIM_GLOBAL T *)p.x + (CELL == 2 ? 0 : mi * p.x_stride) + bq;
     GRIM_GLOBAL float *y = (GRIM_GLOBAL float *)p.y + mi * p.y_stride + bq;
@@ -688,7 +683,7 @@ __global__ void __launch_bounds__(512) bcr_spmv_wave_exact_b(GemvParams p) {
     float *ybuf = reinterpret_cast<float *>(wl + p.wbytes - 8 * 32 * 4);   // [8][32], behind weights and table
 
     const int64_t mi = blockIdx.y;
-    const GemvGlobal d = to_global(p.table ? p.table[mi] : mi ? p.second : p.single);
+    const GemvGlobal d = gemv_matrix(p, mi);
     const GRIM_GLOBAL char *W = d.weights;
     const GRIM_GLOBAL T *x = (const GRIM_GLOBAL T *)p.x + mi * p.x_stride;
     GRIM_GLOBAL float *y = (GRIM_GLOBAL float *)p.y + mi * p.y_stride;
