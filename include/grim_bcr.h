@@ -397,7 +397,11 @@ grim_status grim_bcr_gru_step(const grim_bcr_matrix *Ai, const grim_bcr_matrix *
  * with batch 1 would give.  More than 32, or a workgroup's vectors not fitting its local memory
  * (sequences per workgroup x (I + H) x 2 bytes plus tables within 160 KB): GRIM_ERR_UNSUPPORTED;
  * grim_bcr_rnn_sequence_batch_supported tells in advance.  The calls without _batch are batch = 1.
- * The exchange buffer holds 2 x 32 x H words of 8 bytes.
+ * The exchange buffer holds 64 words of 8 bytes per hidden unit of the largest layer that the matrix can be part of (a third of its rows),
+ * and 272 more.
+ * A long call whose sets of workgroups are no multiple of eight launches up to eight times the workgroups it needs, so that every
+ * XCD has enough of them for a set of its own; those that are not needed leave when the sets are made up, and the call ends when its
+ * last workgroup has had a compute unit.
  * Requirements: fp16 / bf16, blocks of at most 32 x 32 all keeping the same (rows, columns)
  * out of {4, 8, 16} x {4, 8, 12, 16} (not 16 x 16), at most 64 column blocks per matrix, H a multiple of BR,
  * H <= 8192 and H / BR workgroups <= the GPU's compute units; otherwise GRIM_ERR_UNSUPPORTED (loop over the step
@@ -429,8 +433,8 @@ grim_status grim_bcr_gru_sequence_batch(const grim_bcr_matrix *Ai, const grim_bc
 /*
  * grim_bcr_lstm_sequence_noalloc -- grim_bcr_lstm_sequence for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): same arguments, same kernels,
- * same results, but the exchange words live in a static device array of the library (2 x 8192 words of 8 bytes
- * = 128 KB per GPU, held until the process ends) instead of a buffer allocated with the matrix.  The call
+ * same results, but the exchange words live in a static device array of the library (2 x 8192 + 272 words of 8 bytes,
+ * 130 KB per GPU, held until the process ends) instead of a buffer allocated with the matrix.  The call
  * allocates and frees nothing, on the device or through any library.  H > 8192 is GRIM_ERR_UNSUPPORTED.  All such
  * calls on one GPU share the array (whatever the matrix): calls that overlap in time on one GPU race -- enqueue them
  * on one stream.  The words are cleared by a small kernel at the start of every call, so the call can be captured.
