@@ -105,6 +105,7 @@ __global__ void __launch_bounds__(kWideThreads) bcr_spmm_wide_rest(WideParams wp
     const int vblock = (int)blockIdx.x - wide_wgs;
     int tile, unit;
     if (!xcd_map_at(gp.map, vblock, gp.ntiles, &tile, &unit) || unit >= gp.nbr) return;
+    gather_arguments(gp);
     gather_body<BF16, true, false, false, true, 4, kWideMulWaves + kWideFetchWaves>(gp, lds, vblock, 0);
 }
 
