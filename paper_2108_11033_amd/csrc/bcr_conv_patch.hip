@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_patch(ConvPatchParams p)
     constexpr int R = kConvTallRuns, NT = 4, TN = 64, SB = patch_pixel_bytes(CO);
     constexpr int D = kPatchDepth, AHEAD = LONG ? 2 : 3;    // tasks of a chunk asked for ahead, in 64s: as the registers allow
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    // (the arguments in one trip through the scalar cache, as in bcr_conv_gather)
+    // (what the way to the first pixels needs of the arguments in one trip through the scalar cache, as in bcr_conv_gather)
     asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
                  "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.tiles_per_img), "s"(p.tiles_inv), "s"(p.nbr),
                  "s"(p.F), "s"(p.f_img_stride), "s"(p.Nv), "s"(p.W), "s"(p.Wo), "s"(p.wo_inv), "s"(p.N), "s"(p.stride), "s"(p.kh), "s"(p.kw),

@@ -30,7 +30,7 @@ __global__ void __launch_bounds__(NWV * 64, 2) bcr_conv_tall(ConvTallParams p) {
     constexpr int WAVE_LDS = R * NT * 1024;      // D step buffers of 4 KB, later the partial tiles
     static_assert(D * 32 * PITCH <= WAVE_LDS, "step buffers fit");
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    // (the arguments in one trip through the scalar cache, as in bcr_conv_gather; with the table of masks made a dword per thread, without
+    // (most of the arguments in one trip through the scalar cache, as in bcr_conv_gather; with the table of masks made a dword per thread, without
     // divisions by run-time values: 1 x 1 at stride 2, 128 -> 256 channels on four 56 x 56 maps in 4 x 16 blocks 6.82 -> 6.67 us, 96 -> 128 on
     // three 112 x 112 7.46 -> 7.29.  Asking for the first windows ahead of that table's barrier makes the walk wait for everything: 11.0.)
     asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),

@@ -170,8 +170,8 @@ __device__ __forceinline__ void conv_gather_body(const ConvParams &p, char *lds,
     constexpr int RPI = 64 / CPR, LI = 32 / RPI;               // rows per load instruction, windows per lane and step
     constexpr int LW = S2 ? 2 : 1;               // 16-byte loads per window (stride 2: 16 elements, of which every second one counts)
     constexpr int NWV = EIGHT ? LONGW : 4;       // waves of the workgroup
-    // (what the prologue needs of the arguments in one trip through the scalar cache: where each is asked for when it is
-    // first used, the trips follow one another)
+    // (what the way to the first slot words needs of the arguments in one trip through the scalar cache: where each is asked for
+    // when it is first used, the trips follow one another.  The map's sizes, the taps and the payload come a trip later, beside those words)
     asm volatile("" ::"s"(p.map.per_tile), "s"(p.map.tail_slot0), "s"(p.map.tail_tile0), "s"(p.map.shift), "s"(p.map.per_part),
                  "s"(p.map.per_tile_inv), "s"(p.map.per_part_inv), "s"(p.ntiles), "s"(p.tiles_per_img), "s"(p.tiles_inv), "s"(p.nbr),
                  "s"(p.usteps), "s"(p.plan), "s"(p.rows), "s"(p.desc), "s"(p.out_row), "s"(p.F), "s"(p.f_img_stride), "s"(p.Nv));

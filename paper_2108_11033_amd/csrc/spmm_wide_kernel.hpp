@@ -98,7 +98,7 @@ __device__ __forceinline__ void wide_body(const WideParams &p, char *lds, int bl
     static_assert(NT % NTB == 0, "sub-tiles come in whole batches");
     using Acc = typename std::conditional<BR == 16, f32x4, f32x16>::type;
 
-    // (what the prologue needs of the arguments in one trip through the scalar cache)
+    // (most of what the prologue needs of the arguments in one trip through the scalar cache; the tables of steps follow)
     asm volatile("" ::"s"(p.recs), "s"(p.cptr), "s"(p.bptr), "s"(p.nbr), "s"(p.nchunks), "s"(p.chunk_rows), "s"(p.ntiles), "s"(p.ngroups), "s"(p.amax),
                  "s"(p.N), "s"(p.K));
     if constexpr (CONV != kConvNone)
