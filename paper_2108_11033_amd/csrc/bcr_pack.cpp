@@ -201,7 +201,7 @@ void build_mma_layout(grim_bcr_matrix *A, MmaLayout &L, int32_t chunk_rows_opt, 
     }
     bool done = false;
     for (int32_t b = most; !done && b >= blocks; b = (b + 1) / 2) {
-        done = build_mma_layout_for(A, L, b, true) && fits(L) && (!any || fits_wherever(L, one, A->BR, wide));
+        done = build_mma_layout_for(A, L, b, true) && fits(L) && (!any || fits_wherever(L, one, A->BR, A->K, wide));
         if (b == 1) break;
     }
     if (!done && any) done = build_mma_layout_for(A, L, blocks, false);

@@ -85,14 +85,14 @@ inline bool mma_shape_fits(const MmaLayout &L, int BR, int tn, int strips) {
     return 2 * (int64_t)mma_stage_bytes(L.chunk_rows, tn * 2, amax) + (int64_t)L.nchunks * (strips + 1) * 8 <= kStagedLds;
 }
 
-// Has `L` room in every compiled form that `other` has room in?  (wide: the wide-tile kernel's forms, products and convolutions of any
-// number of taps; otherwise the staged kernel's)
-inline bool fits_wherever(const MmaLayout &L, const MmaLayout &other, int BR, bool wide) {
+// Has `L` room in every compiled form that `other`, of the same matrix with K columns, has room in?  (wide: the wide-tile kernel's forms,
+// products and convolutions of every number of taps that divides K -- kernels are odd both ways; otherwise the staged kernel's)
+inline bool fits_wherever(const MmaLayout &L, const MmaLayout &other, int BR, int64_t K, bool wide) {
     if (wide) {
         for (int tn : {96, 128, 192}) {
             if (wide_fits(other, BR, tn) && !wide_fits(L, BR, tn)) return false;
-            for (int KK = 1; KK <= 255; ++KK)
-                if (conv_wide_fits(other, BR, tn, KK) && !conv_wide_fits(L, BR, tn, KK)) return false;
+            for (int KK = 1; KK <= 255; KK += 2)
+                if (K % KK == 0 && conv_wide_fits(other, BR, tn, KK) && !conv_wide_fits(L, BR, tn, KK)) return false;
         }
         return true;
     }

@@ -167,7 +167,7 @@ def _sizes_of_one_block_groups(mask, M, K, BR, BC, max_rows, g_most, most_bytes)
         blocks = (blocks + 1) // 2
 
 
-def _wide_forms(BR, rows, nchunks, most):
+def _wide_forms(BR, K, rows, nchunks, most):
     """(tile, kernel taps; 0: a product) that have room for the records: eight 16-byte units per fetching thread (four beside the rows of
     192 columns), two stages and the tables of a convolution that needs them in 160 KB."""
     forms = set()
@@ -176,7 +176,7 @@ def _wide_forms(BR, rows, nchunks, most):
         if most[16] > 256 * (4 if tn == 192 else 8) or stages > 160 * 1024:
             continue
         forms.add((tn, 0))
-        for taps in range(1, 256):
+        for taps in (t for t in range(1, 256, 2) if K % t == 0):                # (kernels are odd both ways)
             ways = 256 // (taps * (tn // 8))
             by_tap = ways > 0 and -(-(-(-rows // taps)) // ways) <= (11 if tn == 96 else 15)
             tables = 0 if by_tap else (taps + 1) * (tn // 8) * 16 + 4 * (192 if BR == 32 else 128) * 8
@@ -185,7 +185,7 @@ def _wide_forms(BR, rows, nchunks, most):
     return forms
 
 
-def _staged_forms(BR, rows, nchunks, most):
+def _staged_forms(BR, K, rows, nchunks, most):
     """(tile, strips) that have room: 16 KB of records for four strips, 32 for eight, 48 for sixteen, two stages in 160 KB."""
     forms = set()
     for tn in (32, 64, 128):
@@ -224,5 +224,5 @@ def test_staged_layouts_have_room_in_every_form_that_one_block_groups_have(decod
             assert decoders.grim_test_staged_sizes(A.handle, wide, out.ctypes.data_as(ctypes.c_void_p)) == 0
             rows, nchunks, most = _sizes_of_one_block_groups(mask, M, K, BR, BC, max_rows, g_most, most_bytes)
             assert out[0] >= rows, (wide, seed, out, rows)
-            missing = forms(BR, rows, nchunks, most) - forms(BR, int(out[0]), int(out[1]), dict(zip((4, 8, 16, 32), out[2:].tolist())))
+            missing = forms(BR, K, rows, nchunks, most) - forms(BR, K, int(out[0]), int(out[1]), dict(zip((4, 8, 16, 32), out[2:].tolist())))
             assert not missing, (wide, seed, sorted(missing)[:5], out, rows, most)
