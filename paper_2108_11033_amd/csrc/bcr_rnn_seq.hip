@@ -284,7 +284,8 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
             const unsigned int tag_mask = PLACED && t == 1 ? kSeqTagBits : 0xffffffffu;
             unsigned int others = 0;
             // the words of NJ pairs of sequences (of one sequence: a word is one hidden unit, or two of them), NI per
-            // thread and row of nw words, and what is done with word e of pair q; false: a wait has been given up
+            // thread and row of nw words, and what is done with word e of pair q
+            int gone = 0;                                             // this thread has given a wait up
             auto words = [&](auto per_thread, int nw, int q0, auto park) {
                 constexpr int NI = decltype(per_thread)::value;
                 for (int base = tid; base < nw; base += NI * NTHR) {
@@ -348,7 +349,8 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                     }
                     if (st_ < 0) {
                         flag = 1;
-                        return false;
+                        gone = 1;
+                        return;
                     }
                     if constexpr (PLACED) {
                         if (t == 1) {
@@ -365,14 +367,16 @@ __global__ void __launch_bounds__(exact_waves(CELL) * 64) bcr_rnn_seq(SeqParams 
                         }
                     }
                 }
-                return true;
             };
             if constexpr (MULTI) {
+                // (a wave leaves as a whole: a loop that its lanes leave one by one costs up to 2 % of a call, 22 sequences through an LSTM of 384
+                // units, 25 steps 84.4 us, 83.3 so, 82.6 without an end to the waits)
                 seq_waits(NQ, NJ, [&](int q0) {
-                    return words(std::integral_constant<int, 4>{}, H, q0, [&](int q, int e, unsigned int pair) {
+                    words(std::integral_constant<int, 4>{}, H, q0, [&](int q, int e, unsigned int pair) {
                         hin[2 * q * hld + e] = (unsigned short)(pair & 0xffffu);
                         if (2 * q + 1 < B) hin[(2 * q + 1) * hld + e] = (unsigned short)(pair >> 16);
                     });
+                    return __builtin_amdgcn_ballot_w64(gone != 0) == 0;
                 });
             } else if (p.unit_pairs) {
                 words(std::integral_constant<int, 2>{}, H / 2, 0,
